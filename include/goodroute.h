@@ -160,21 +160,12 @@ int gr_score_route(gr_fleet* f, int64_t n_req,
                    float* out_T, void* hip_stream);
 
 /*
- * gr_score_route for callers that cannot allocate device memory or call anything that might:
- * code under HIP graph capture, tight serving loops, harnesses that forbid it.  Same inputs,
- * outputs and answers as gr_score_route's pair-by-pair pass (a thread per (request, instance)
- * pair, whatever gr_set_small_batch_pairs says; no out_T), for at most
- * GR_NOALLOC_MAX_REQUESTS requests per call; more is GR_ERR_TOO_LARGE.  The running
- * selections of the pass (16 bytes per request) live in a fixed array of 64 KiB in the
- * library's device image instead of the handle's workspace; the call queues three kernels on
- * the stream (one sets the array's slots for this batch; two more, for the capability order,
- * on the first scoring call after a status build and whenever the stream is being captured)
- * and calls no hipMalloc, hipFree,
- * memset, copy or synchronisation.  Every GPU holds one such array for the life of the
- * process and every call on that GPU uses it, whatever the handle: calls that overlap on one
- * GPU (two streams, two threads, two handles) race and must be serialised by the caller.
- * The handle must have been created on the current device (the array's address is looked up
- * once per device, in gr_create).
+ * gr_score_route for callers that want the same work queued whatever the batch: code under HIP
+ * graph capture, tight serving loops.  Same inputs, outputs and answers as gr_score_route's
+ * pair-by-pair pass (whatever gr_set_small_batch_pairs says; no out_T), for at most
+ * GR_NOALLOC_MAX_REQUESTS requests per call; more is GR_ERR_TOO_LARGE.  The call queues one
+ * kernel on the stream (two for fleets of more than 4 096 instances) and calls no hipMalloc,
+ * hipFree, memset, copy or synchronisation.
  */
 #define GR_NOALLOC_MAX_REQUESTS 4096
 int gr_score_route_noalloc(gr_fleet* f, int64_t n_req,
@@ -326,7 +317,8 @@ int gr_set_batch_cap(gr_fleet* f, const int32_t* cap);
  * of Eq. 2 is tabulated once per (distinct length, instance), and tiles of 32
  * requests run against all instances.  A batch of a few requests (the paper
  * routes one arriving request at a time) skips grouping and table: a thread
- * per (request, instance) pair finds its own segment by binary search.
+ * per (request, instance) pair searches the instance's own tables, and the
+ * whole call is one kernel.
  *
  *   max_pairs   gr_score_route and gr_route_feedback score a batch (a chunk)
  *               pair by pair when n_req * (n_inst rounded up to 128) is at

@@ -9,10 +9,10 @@ namespace gr {
 namespace {
 
 const char* const kKernelNames[kNumKernels] = {
-    "k_build", "k_rank_count", "k_rank_final",
+    "k_build", "k_rank",
     "k_hist<route>", "k_scan<route>", "k_group<route>", "k_tile<route>",
     "k_hist<migrate>", "k_scan<migrate>", "k_group<migrate>", "k_tile<migrate>",
-    "k_hits<route>", "k_direct", "k_direct_finish"};
+    "k_hits<route>", "k_direct", "k_direct_merge"};
 
 template <typename T>
 bool dev_alloc(T** p, size_t n)
@@ -71,6 +71,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     f->epl = 1;
     while (kWave * f->epl < max_entries_per_inst) f->epl *= 2;
     f->cap = kWave * f->epl;
+    f->n_split = split_count(f->cap);
     f->m_pad = ((n_inst + 2 * kWave - 1) / (2 * kWave)) * (2 * kWave);
     f->bins = max_len + 1;
     f->row_cap = f->req_cap < f->bins ? f->req_cap : f->bins;
@@ -84,7 +85,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
         dev_alloc(&f->tabR, tab) && dev_alloc(&f->tabGH, tab) && dev_alloc(&f->headGH, n_inst) &&
         dev_alloc(&f->hN, n_inst) && dev_alloc(&f->hD, n_inst) &&
         dev_alloc(&f->emaQ, n_inst) && dev_alloc(&f->emaP, n_inst) && dev_alloc(&f->emaD, n_inst) &&
-        dev_alloc(&f->rank_acc, n_inst) && dev_alloc(&f->rank, n_inst) && dev_alloc(&f->order, f->m_pad) && dev_alloc(&f->posK, f->m_pad) &&
+        dev_alloc(&f->instK, n_inst) && dev_alloc(&f->tabS, (size_t)n_inst * f->n_split) && dev_alloc(&f->rank, n_inst) && dev_alloc(&f->order, f->m_pad) && dev_alloc(&f->posK, f->m_pad) &&
         dev_alloc(&f->act_inst, f->max_active) && dev_alloc(&f->counters, 1) &&
         dev_alloc(&f->pend_cnt, n_inst) && dev_alloc(&f->commit_mark, n_inst) && dev_alloc(&f->pend_touched, n_inst) && dev_alloc(&f->pend_prompt, tab) && dev_alloc(&f->pend_len, tab) &&
         dev_alloc(&f->scratch_finish, f->max_active) && dev_alloc(&f->batch_cap, n_inst) &&
@@ -94,7 +95,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
         dev_alloc(&f->recs, f->req_cap) && dev_alloc(&f->memo, (size_t)f->row_cap * f->m_pad) &&
         dev_alloc(&f->tile_row, (size_t)(f->req_cap / kTileReq + f->row_cap + 1)) &&
         dev_alloc(&f->grp_min, (size_t)f->row_cap * (f->m_pad / kMemoP)) && dev_alloc(&f->grp_k, f->m_pad / kMemoP) &&
-        dev_alloc(&f->direct_best, 2 * (size_t)kDirectMax);
+        dev_alloc(&f->direct_part, (size_t)kDirectParts);
     if (!ok) { gr_destroy(f); return GR_ERR_NOMEM; }
 
     ClassCoef* host = static_cast<ClassCoef*>(malloc(sizeof(ClassCoef) * n_class));
@@ -108,19 +109,13 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     const hipError_t e6 = hipMemset(f->pend_cnt, 0, sizeof(int) * n_inst);
     const hipError_t e8 = hipMemset(f->pend_touched, 0, sizeof(int) * n_inst);
     const hipError_t e9 = hipMemset(f->commit_mark, 0, sizeof(int) * n_inst);
-    const hipError_t e7 = hipMemset(f->direct_best, 0xFF, sizeof(unsigned long long) * 2 * kDirectMax);
     free(host);
-    if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess || e4 != hipSuccess || e5 != hipSuccess || e6 != hipSuccess || e7 != hipSuccess || e8 != hipSuccess || e9 != hipSuccess ||
+    if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess || e4 != hipSuccess || e5 != hipSuccess || e6 != hipSuccess || e8 != hipSuccess || e9 != hipSuccess ||
         hipDeviceSynchronize() != hipSuccess) {
         gr_destroy(f);
         return GR_ERR_HIP;
     }
     if (score_prepare(f) != GR_OK || status_prepare() != GR_OK) { gr_destroy(f); return GR_ERR_HIP; }
-    {   // the address of the fixed scratch array on this device, for gr_score_route_noalloc
-        unsigned long long* unused = nullptr;
-        const int rc = static_scratch(f->device, &unused);
-        if (rc != GR_OK && rc != GR_ERR_TOO_LARGE) { gr_destroy(f); return rc; }
-    }
     *out = f;
     return GR_OK;
 }
@@ -129,10 +124,10 @@ int gr_destroy(gr_fleet* f)
 {
     if (!f) return GR_OK;
     (void)hipDeviceSynchronize();
-    void* ptrs[] = {f->cls, f->inst_class, f->tabR, f->tabGH, f->headGH, f->hN, f->hD, f->emaQ, f->emaP, f->emaD, f->rank_acc,
+    void* ptrs[] = {f->cls, f->inst_class, f->tabR, f->tabGH, f->headGH, f->hN, f->hD, f->emaQ, f->emaP, f->emaD, f->instK, f->tabS,
                     f->rank, f->order, f->posK, f->act_inst, f->pend_cnt, f->commit_mark, f->pend_touched, f->pend_prompt, f->pend_len,
                     f->scratch_finish, f->batch_cap, f->counters, f->len_cnt, f->len_base, f->row_len,
-                    f->row_off, f->tile_off, f->len_row, f->len_ceil, f->totals, f->recs, f->memo, f->tile_row, f->grp_min, f->grp_k, f->direct_best};
+                    f->row_off, f->tile_off, f->len_row, f->len_ceil, f->totals, f->recs, f->memo, f->tile_row, f->grp_min, f->grp_k, f->direct_part};
     int rc = GR_OK;
     for (void* p : ptrs)
         if (p && hipFree(p) != hipSuccess) rc = GR_ERR_HIP;
@@ -204,7 +199,7 @@ int gr_score_route_noalloc(gr_fleet* f, int64_t n_req, const int32_t* ctx0, cons
     src.n = n_req;
     ScoreOut o{};
     o.inst = out_inst; o.slack = out_slack; o.fallback = out_fallback;
-    return launch_score_static(f, src, o, static_cast<hipStream_t>(hip_stream));
+    return launch_direct(f, src, o, static_cast<hipStream_t>(hip_stream));
 }
 
 int gr_score_route_cached(gr_fleet* f, int64_t n_req, const int32_t* ctx0, const int32_t* pred_len,
@@ -299,11 +294,6 @@ int gr_observe(gr_fleet* f, double weight, const float* obs_wait, const float* o
     if (!f || !(weight >= 0.0 && weight <= 1.0)) return GR_ERR_INVALID_ARG;
     if (!obs_wait && !obs_prefill && !obs_decode) return GR_OK;
     f->tables_current = false;      // (a blended table holds the smoothed status)
-    // the capability order of the current tables carries the prefill estimate as it is now
-    if (f->has_status && !f->ranks_current) {
-        const int rc = launch_ranks(f, nullptr, static_cast<hipStream_t>(hip_stream));
-        if (rc != GR_OK) return rc;
-    }
     return launch_ema(f, weight, obs_wait, obs_prefill, obs_decode, static_cast<hipStream_t>(hip_stream));
 }
 

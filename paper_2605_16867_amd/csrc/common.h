@@ -40,7 +40,12 @@ constexpr int kTileReq = 32;       // requests of one length scored together by 
 constexpr int kGroupBlock = 1024;  // threads per workgroup of the grouping kernels (their cost is the pass over the LDS bins)
 constexpr int kMemoU = 256;        // lengths per pass of a workgroup of the memo kernel
 constexpr int kDirectMax = 4096;   // most requests of a batch scored pair by pair, without grouping
+constexpr int kDirectSpan = 4096;  // instances that one workgroup takes of a request scored pair by pair
+constexpr int kDirectParts = 16384;  // room for the selections of such parts
 constexpr int kMemoP = 16;         // instances (waves) per workgroup of the memo kernel
+
+// Splitters of an instance's sorted lengths, by table size (strides of 8, 8, 16, 32, 32, 64 lengths).
+constexpr int split_count(int cap) { return cap <= 64 ? 8 : cap <= 512 ? 16 : 32; }
 
 struct ClassCoef {
     double delta, alpha, beta, gamma;
@@ -74,9 +79,16 @@ struct ScoreOut {
     int* n_selected;     // may be null: number of requests scored
 };
 
+// Alg. 1's two selections over a share of the instances.
+struct DirectPart {
+    uint32_t any_T, any_g;      // least latency (as an integer of the same order) and its instance; all ones: none
+    uint32_t d_hi, d_lo;        // d_g of the feasible choice as an integer that falls with d_g; all ones: none
+    uint32_t g, T;              // the feasible choice and its latency
+};
+
 enum KernelId {
-    kBuild = 0, kRankCount, kRankFinal, kHistRoute, kScanRoute, kGroupRoute, kTileRoute,
-    kHistMigrate, kScanMigrate, kGroupMigrate, kTileMigrate, kHitsRoute, kDirect, kDirectFinish,
+    kBuild = 0, kRank, kHistRoute, kScanRoute, kGroupRoute, kTileRoute,
+    kHistMigrate, kScanMigrate, kGroupMigrate, kTileMigrate, kHitsRoute, kDirect, kDirectMerge,
     kNumKernels
 };
 
@@ -110,6 +122,7 @@ struct gr_fleet {
     int64_t req_cap = 0;   // requests one scoring pass may hold
     int epl = 0;           // sort words per lane of the status build: 1, 2, 4 .. 32
     int cap = 0;           // 64 * epl >= max_entries: table entries per instance
+    int n_split = 0;       // splitters per instance: 8 (cap 64), 16 (to 512), 32
     int m_pad = 0;         // instances rounded up to a multiple of 128 (two blocks of 64 positions)
     int bins = 0;          // max_len + 1
     int64_t row_cap = 0;   // rows of the memo table
@@ -130,7 +143,10 @@ struct gr_fleet {
     float2* headGH = nullptr; // [M] (Gq, H) of segment 0: (q_g, alpha + beta*(N+1) + gamma*sum of contexts)
     int* hN = nullptr;       // [M] entries per instance
     double* hD = nullptr;    // [M] d_g
-    int* rank_acc = nullptr; // [M] partial counts of the rank kernels
+    // [M] what a pair needs of its instance besides the tables: (delta, gamma) of the latency's prefill
+    // part T = E + c0 * (delta + gamma * L), blended as the tables are; the curvature gamma of E; entries (int bits)
+    float4* instK = nullptr;
+    uint16_t* tabS = nullptr; // [M][n_split] every (cap / n_split)-th of the sorted lengths: the first step of a search
     int* rank = nullptr;     // [M]
     int* order = nullptr;    // [m_pad] order[rank[g]] = g
     float2* posK = nullptr;  // [m_pad] (delta, gamma) of the instance at each position of the capability order
@@ -163,7 +179,7 @@ struct gr_fleet {
     bool ranks_current = false;    // rank, order and posK belong to the current d_g (else the next scoring pass makes them)
     int* pend_touched = nullptr;   // [M] 1: given requests since its table was built
     int64_t small_batch_pairs = int64_t(1) << 18;   // largest batch, in pairs, scored pair by pair
-    unsigned long long* direct_best = nullptr;   // [2][kDirectMax] running selections of a small batch (all ones between calls)
+    gr::DirectPart* direct_part = nullptr;       // [kDirectParts] selections of the parts of a wide fleet, scored pair by pair
 };
 
 namespace gr {
@@ -187,16 +203,12 @@ struct ProfScope {
 };
 
 
-// What the two steps of the capability order need (Alg. 1's argmax d_g: rank 0 = largest d_g,
-// equal d_g by index).  They run as kernels of their own or as extra workgroups of the first two
-// kernels of a scoring pass (see launch_score).
+// What the capability order needs (Alg. 1's argmax d_g: rank 0 = largest d_g, equal d_g by index).
+// It is made by a kernel of its own or by extra workgroups of the first kernel of a grouped
+// scoring pass (see launch_score).
 struct RankArgs {
     const double* d;        // [M] d_g
-    int* rank_acc;          // [M] partial counts, zero before the count and again after the final step
-    const ClassCoef* cls;
-    const int* inst_class;
-    const double* emaP;
-    double lam;
+    const float4* instK;    // [M] see gr_fleet
     int *rank, *order;
     float2* posK;
     int* out_rank;          // may be null
@@ -216,8 +228,7 @@ size_t score_lds_bytes(const gr_fleet* f);
 int score_prepare(gr_fleet* f);
 int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& out, hipStream_t s,
                  bool small_batch_ok = false);
-int static_scratch(int device, unsigned long long** out);
-int launch_score_static(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream_t s);
+int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream_t s);
 int launch_hits(gr_fleet* f, const ReqSrc& src, const int* hit_off, const int* hit_inst, const int* hit_len,
                 int64_t n_hits, const ScoreOut& out, hipStream_t s);
 
@@ -259,48 +270,87 @@ __device__ inline int wave_incl_scan_i32(int v)
     return v;
 }
 
-// rank_g = #{h : d_h > d_g} + #{h < g : d_h = d_g}, counted over tiles of 64 instances x kThreads
-// competitors (tile `bx` of the instances, tile `by` of the competitors) and added up with
-// atomics.  `comp`: kThreads doubles of LDS.  Every thread of the workgroup must call it.
-template <int kThreads>
-__device__ inline void rank_count_tile(const RankArgs& a, int bx, int by, double* comp)
-{
-    const int tid = threadIdx.x;
-    const int g = bx * kWave + (tid & (kWave - 1));
-    const int h0 = by * kThreads;
-    comp[tid] = h0 + tid < a.n_inst ? a.d[h0 + tid] : 0.0;
-    __syncthreads();
-    if (g >= a.n_inst) return;
-    const double dg = a.d[g];
-    const int part = tid / kWave;                 // which 64 of the competitors
-    const int lim = min(kWave, a.n_inst - h0 - part * kWave);
-    int r = 0;
-    for (int j = 0; j < lim; ++j) {
-        const double dh = comp[part * kWave + j];
-        r += (dh > dg) || (dh == dg && h0 + part * kWave + j < g);
-    }
-    if (r) atomicAdd(&a.rank_acc[g], r);
-}
+constexpr int kRankPer = 8;      // instances that kRankWaves waves rank together
+constexpr int kRankWaves = 4;
 
-// The counts are complete: rank, order[rank] = g and the prefill coefficients per position.
-__device__ inline void rank_final_item(const RankArgs& a, int g)
+// Workgroup `wg` of kThreads threads of the capability order: the ranks of kThreads / 256 runs of
+// kRankPer instances,
+//   rank_g = #{h : d_h > d_g} + #{h < g : d_h = d_g},
+// and with them order[rank] = g and the prefill coefficients per position.  Four waves share a run
+// and split the competitors, a lane per competitor, each lane with its own counts, added up over the
+// wave and then through LDS.  The time is that of the reads: the status build has just written d, so
+// each XCD fetches it from memory, and a wave that read its 4 096 competitors in four batches waited
+// four times.  A quarter of them is one batch.  On 4 096 instances 10.8 us with ballots added up by the scalar unit, 9.2 with a
+// wave per run, 5.9 us this way (and 7.3 + 3.8 us as two kernels that count with atomics and finish).
+// Competitors that lie wholly before or behind the run take one comparison each.
+// Every thread of the workgroup must call it.  `sums`: kThreads / 64 * kRankPer ints of LDS.
+template <int kThreads>
+__device__ inline void rank_block(const RankArgs& a, int wg, int* sums)
 {
+    constexpr int kRuns = kThreads / (kRankWaves * kWave);
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int quarter = wave % kRankWaves, g0 = (wg * kRuns + wave / kRankWaves) * kRankPer;
+    if (g0 < a.n_inst) {
+        double dg[kRankPer];
+        int r[kRankPer] = {};
+#pragma unroll
+        for (int j = 0; j < kRankPer; ++j) dg[j] = a.d[min(g0 + j, a.n_inst - 1)];
+        constexpr int kAhead = 16;
+        const int per = ((a.n_inst + kRankWaves - 1) / kRankWaves + kWave - 1) / kWave * kWave;
+        const int h_end = min((quarter + 1) * per, a.n_inst);
+        for (int h0 = quarter * per; h0 < h_end; h0 += kAhead * kWave) {
+            double dh[kAhead];
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                const int h = h0 + k * kWave + lane;
+                dh[k] = h < h_end ? a.d[h] : -__builtin_inf();      // ahead of nobody
+            }
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                const int hb = h0 + k * kWave;
+                if (hb >= h_end) break;
+                if (hb + kWave <= g0) {
+#pragma unroll
+                    for (int j = 0; j < kRankPer; ++j) r[j] += dh[k] >= dg[j];
+                } else if (hb >= g0 + kRankPer) {
+#pragma unroll
+                    for (int j = 0; j < kRankPer; ++j) r[j] += dh[k] > dg[j];
+                } else {
+#pragma unroll
+                    for (int j = 0; j < kRankPer; ++j) r[j] += dh[k] > dg[j] || (dh[k] == dg[j] && hb + lane < g0 + j);
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < kRankPer; ++j) {
+            const int all = wave_incl_scan_i32(r[j]);
+            if (lane == kWave - 1) sums[wave * kRankPer + j] = all;
+        }
+    }
+    __syncthreads();
+    if (quarter != 0 || lane >= kRankPer) return;
+    const int g = g0 + lane;
     if (g < a.n_inst) {
-        const int r = a.rank_acc[g];
-        a.rank_acc[g] = 0;
+        int r = 0;
+#pragma unroll
+        for (int q = 0; q < kRankWaves; ++q) r += sums[(wave + q) * kRankPer + lane];
         if ((unsigned)r >= (unsigned)a.n_inst) return;      // (counts are below n_inst by construction; never index past the tables)
-        const ClassCoef cc = a.cls[a.inst_class[g]];
+        const float4 k = a.instK[g];
         a.rank[g] = r;
         a.order[r] = g;
-        // T = E + c0 * (delta + gamma * L); blended: keep * that + lam * p_g * c0
-        const double keep = 1.0 - a.lam;
-        a.posK[r] = a.lam != 0.0 ? make_float2((float)(keep * cc.delta + a.lam * a.emaP[g]), (float)(keep * cc.gamma))
-                                 : make_float2((float)cc.delta, (float)cc.gamma);
+        a.posK[r] = make_float2(k.x, k.y);
         if (a.out_rank) a.out_rank[g] = r;
     } else if (g < a.m_pad) {
         a.order[g] = -1;     // positions past the last instance
         a.posK[g] = make_float2(0.f, 0.f);
     }
+}
+
+// Workgroups of kThreads threads that rank every instance (and fill the padded positions).
+constexpr int rank_blocks(int m_pad, int threads)
+{
+    const int per = threads / (kRankWaves * kWave) * kRankPer;
+    return (m_pad + per - 1) / per;
 }
 
 }  // namespace gr

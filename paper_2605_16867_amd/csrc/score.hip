@@ -19,15 +19,8 @@
 // A batch of a few requests skips grouping and table: a thread per pair with
 // its own binary search (k_direct).
 #include <cfloat>
-#include <mutex>
 
 #include "common.h"
-
-// The running selections of the pair-by-pair pass for callers that may not allocate: a fixed
-// array in the library's own device image (each GPU the library runs on holds a copy of it
-// until the process ends).  Host code never uses this name as an address: it asks the runtime
-// for the array's address on the current device once (static_scratch below) and passes that.
-static __device__ __align__(256) unsigned long long scratch[2 * gr::kDirectMax];
 
 namespace gr {
 namespace {
@@ -50,16 +43,14 @@ __device__ __forceinline__ bool fetch_len(const ReqSrc& s, int64_t i, int max_le
 // global atomic per length the workgroup has seen.
 //
 // Workgroups past the first `hist_blocks` do something else that has to happen before the
-// requests are put in order and costs a launch of its own otherwise: the counting step of the
-// capability order (tile b of `rank_bx` x .. tiles, see rank_count_tile; none when rank_bx = 0).
+// requests are put in order and costs a launch of its own otherwise: the capability order.
 template <bool kMigrate, int kItems>
 __global__ __launch_bounds__(kGroupBlock) void k_hist(ReqSrc s, int* __restrict__ len_cnt, int bins, int max_len,
-                                                      int hist_blocks, RankArgs ranks, int rank_bx)
+                                                      int hist_blocks, RankArgs ranks)
 {
     extern __shared__ uint32_t lds[];
     if ((int)blockIdx.x >= hist_blocks) {
-        const int b = blockIdx.x - hist_blocks;
-        rank_count_tile<kGroupBlock>(ranks, b % rank_bx, b / rank_bx, reinterpret_cast<double*>(lds));
+        rank_block<kGroupBlock>(ranks, blockIdx.x - hist_blocks, reinterpret_cast<int*>(lds));
         return;
     }
     const int tid = threadIdx.x;
@@ -97,19 +88,13 @@ static_assert(kMaxLen + 1 <= kWave * kScanChunks * kScanWaves * kScanGroups, "ev
 // of passing sums from workgroup to workgroup each workgroup adds up
 // everything before its own lengths itself; the last one also has the totals.
 // The histogram is left as it is (the scatter clears it for the next call).
-// Workgroups past the first kScanGroups finish the capability order (rank_final_item), whose
-// counts the previous launch completed.
 __global__ __launch_bounds__(kScanBlock) void k_scan(const int* __restrict__ len_cnt, int* __restrict__ len_base,
                                                      int* __restrict__ row_len, int* __restrict__ row_off,
                                                      int* __restrict__ tile_off, int* __restrict__ len_row,
                                                      int* __restrict__ len_ceil, int* __restrict__ totals,
-                                                     int* __restrict__ out_n, int bins, RankArgs ranks)
+                                                     int* __restrict__ out_n, int bins)
 {
     __shared__ int w_req[2][kScanWaves], w_tile[2][kScanWaves], w_rows[2][kScanWaves];
-    if (blockIdx.x >= kScanGroups) {
-        rank_final_item(ranks, (blockIdx.x - kScanGroups) * kScanBlock + threadIdx.x);
-        return;
-    }
     const int lane = lane_id(), wave = threadIdx.x / kWave;
     const int chunks = (bins + kWave - 1) / kWave;
     const int per = (chunks + kScanWaves * kScanGroups - 1) / (kScanWaves * kScanGroups);    // 1 or 2
@@ -1300,18 +1285,16 @@ struct DirectArgs {
     const int *ctx0, *pred_len;
     const float* budget;
     const int* exclude;
-    const int *order, *hN;
-    const ClassCoef* cls;
-    const int* inst_class;
-    const uint16_t* tabR;
-    const float2 *tabGH, *headGH, *posK;
-    unsigned long long *best_feasible, *best_any;     // [n] each, all ones on entry
+    const float4* instK;
+    const double* hD;
+    const uint16_t *tabR, *tabS;
+    const float2 *tabGH, *headGH;
+    DirectPart* parts_out;   // [n][parts]
     int* out_inst;
     float* out_slack;
     uint8_t* out_fallback;
     float* out_T;
-    int n, n_inst, m_pad, cap, max_len;
-    float keep;
+    int n, n_inst, cap, max_len, parts;
 };
 
 // a float as an unsigned integer of the same order
@@ -1326,95 +1309,220 @@ __device__ inline float from_ordered_bits(uint32_t u)
     return __uint_as_float(u ^ ((u >> 31) ? 0x80000000u : 0xFFFFFFFFu));
 }
 
-// A batch of a few requests (one arriving request is the paper's own case):
-// grouping by length and a table of per-length values would cost more than
-// they save, so every pair gets a thread, which finds its segment by a binary
-// search over the instance's sorted lengths (Eq. 2's decode term in closed
-// form, the same expression as in the memo kernel) and forms T = E + c0 * kappa.
-// Thread = position in capability order, blockIdx.y = request.  Alg. 1's two
-// selections are two 64-bit minima per request, reduced over the wave and then
-// with one atomic each: (position, T) over the feasible pairs, i.e. the first
-// feasible instance in capability order, and (T, instance index) over all, i.e.
-// the least latency with ties to the lowest index.
-__global__ __launch_bounds__(kBlock) void k_direct(DirectArgs a)
+// a double as an unsigned integer of the opposite order
+__device__ inline unsigned long long falling_bits(double v)
 {
-    const int p = blockIdx.x * kBlock + threadIdx.x, r = blockIdx.y;
-    const int L = min(max(a.pred_len[r], 0), a.max_len);
-    const float c0 = (float)a.ctx0[r], Lf = (float)L, D = a.budget[r];
-    const float Dc = D > FLT_MAX ? FLT_MAX : D;       // padded positions hold +inf and stay infeasible
-    const int ex = a.exclude ? a.exclude[r] : -1;
-    const int g = p < a.m_pad ? a.order[p] : -1;
-    unsigned long long feas = ~0ull, any = ~0ull;
-    if (g >= 0) {
-        const int N = a.hN[g];
-        const uint16_t* __restrict__ R = a.tabR + (size_t)g * a.cap;
-        int k = 0;                                    // #{R_i <= L}
-        for (int step = a.cap; step >= 1; step >>= 1) {
-            const int probe = k + step;
-            if (probe <= N && (int)R[probe - 1] <= L) k = probe;
-        }
-        const float2 gh = k > 0 ? a.tabGH[(size_t)g * a.cap + k - 1] : a.headGH[g];
-        const float gam = a.keep * (float)a.cls[a.inst_class[g]].gamma;
-        const float tri = Lf * (Lf - 1.0f) * 0.5f;
-        const float E = fmaf(Lf, gh.y, gh.x) + tri * (gam * (float)(N - k + 1));
-        const float T = fmaf(c0, kappa_of(a.posK[p], Lf), E);
-        if (a.out_T) a.out_T[(size_t)r * a.n_inst + g] = T;
-        if (g != ex) {
-            const unsigned long long tb = ordered_bits(T);
-            any = (tb << 32) | (unsigned)g;
-            if (T <= Dc) feas = ((unsigned long long)p << 32) | tb;
-        }
-    }
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) {
-        const unsigned long long f2 = __shfl_xor(feas, d, kWave), a2 = __shfl_xor(any, d, kWave);
-        feas = f2 < feas ? f2 : feas;
-        any = a2 < any ? a2 : any;
-    }
-    if (lane_id() == 0) {
-        if (feas != ~0ull) atomicMin(&a.best_feasible[r], feas);
-        if (any != ~0ull) atomicMin(&a.best_any[r], any);
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    return ~(b ^ ((b >> 63) ? ~0ull : 0x8000000000000000ull));
+}
+
+__device__ inline DirectPart no_selection() { return DirectPart{~0u, ~0u, ~0u, ~0u, ~0u, ~0u}; }
+
+__device__ inline void take_better(DirectPart& b, const DirectPart& o)
+{
+    // (values, not references: a choice between two structs' members keeps both in memory)
+    const uint32_t oT = o.any_T, og = o.any_g, oh = o.d_hi, ol = o.d_lo, ofg = o.g, ofT = o.T;
+    const uint32_t bT = b.any_T, bg = b.any_g, bh = b.d_hi, bl = b.d_lo, bfg = b.g, bfT = b.T;
+    const bool less = oT < bT || (oT == bT && og < bg);
+    const bool better = oh < bh || (oh == bh && (ol < bl || (ol == bl && ofg < bfg)));
+    b = DirectPart{less ? oT : bT, less ? og : bg, better ? oh : bh, better ? ol : bl, better ? ofg : bfg, better ? ofT : bfT};
+}
+
+template <int kCtrl, int kRowMask>
+__device__ inline uint32_t min_dpp(uint32_t v)      // (all ones where the lane has no source)
+{
+    return min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, kCtrl, kRowMask, 0xf, false));
+}
+
+// The least value over the wave, or over the lane's row of 16 (kRow), for every lane.
+template <bool kRow>
+__device__ inline uint32_t min_over(uint32_t v)
+{
+    if constexpr (kRow) {
+        v = min_dpp<0x128, 0xf>(v);      // row_ror 8, 4, 2, 1
+        v = min_dpp<0x124, 0xf>(v);
+        v = min_dpp<0x122, 0xf>(v);
+        return min_dpp<0x121, 0xf>(v);
+    } else {
+        v = min_dpp<0x111, 0xf>(v);      // row_shr 1, 2, 4, 8
+        v = min_dpp<0x112, 0xf>(v);
+        v = min_dpp<0x114, 0xf>(v);
+        v = min_dpp<0x118, 0xf>(v);
+        v = min_dpp<0x142, 0xa>(v);      // row_bcast 15 into rows 1 and 3, 31 into rows 2 and 3
+        v = min_dpp<0x143, 0xc>(v);
+        return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
     }
 }
 
-// The two selections of each request into Alg. 1's answer; they are set back to all ones.
-__global__ __launch_bounds__(kBlock) void k_direct_finish(DirectArgs a)
+// The best of the lanes' selections, word by word: a minimum and, among the lanes that hold it, the
+// least of the next word (a minimum through DPP is one instruction per step; comparing whole
+// selections pairwise takes twenty).
+template <bool kRow>
+__device__ inline DirectPart best_over(const DirectPart& b)
 {
-    const int r = blockIdx.x * kBlock + threadIdx.x;
-    if (r >= a.n) return;
-    const unsigned long long feas = a.best_feasible[r], any = a.best_any[r];
-    a.best_feasible[r] = ~0ull;
-    a.best_any[r] = ~0ull;
-    const bool found = feas != ~0ull;
-    int g = -1;
-    float T = 0.f;
-    if (found) {
-        g = a.order[(int)(feas >> 32)];
-        T = from_ordered_bits((uint32_t)feas);
-    } else if (any != ~0ull) {
-        g = (int)(uint32_t)any;
-        T = from_ordered_bits((uint32_t)(any >> 32));
+    DirectPart r = no_selection();
+    r.any_T = min_over<kRow>(b.any_T);
+    r.any_g = min_over<kRow>(b.any_T == r.any_T ? b.any_g : ~0u);
+    if (__ballot(b.g != ~0u)) {
+        r.d_hi = min_over<kRow>(b.d_hi);
+        bool in = b.d_hi == r.d_hi;
+        r.d_lo = min_over<kRow>(in ? b.d_lo : ~0u);
+        in = in && b.d_lo == r.d_lo;
+        r.g = min_over<kRow>(in ? b.g : ~0u);
+        r.T = min_over<kRow>(in && b.g == r.g ? b.T : ~0u);
     }
+    return r;
+}
+
+__device__ inline void direct_answer(const DirectArgs& a, int r, const DirectPart& b)
+{
+    const bool found = b.g != ~0u;
+    const uint32_t fg = b.g, ag = b.any_g, fT = b.T, aT = b.any_T;
+    const int g = (int)(found ? fg : ag);          // (-1: nobody is allowed)
+    const float T = from_ordered_bits(found ? fT : aT);
     a.out_inst[r] = g;
     a.out_slack[r] = g >= 0 ? a.budget[r] - T : 0.f;
     if (a.out_fallback) a.out_fallback[r] = !found;
 }
 
-__global__ void k_set_int(int* p, int v) { *p = v; }
-
-// all ones = "no selection yet", for the first n requests of both halves
-__global__ __launch_bounds__(kBlock) void k_fill_ones(unsigned long long* __restrict__ best, int n)
+// how many of the 16-bit lengths in `w` are at most L
+__device__ inline int count_upto(const uint4& w, uint32_t L)
 {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) {
-        best[i] = ~0ull;
-        best[kDirectMax + i] = ~0ull;
+    const uint32_t lim = (L << 16) | 0xFFFFu;
+    int c = 0;
+    c += ((w.x & 0xFFFFu) <= L) + (w.x <= lim) + ((w.y & 0xFFFFu) <= L) + (w.y <= lim);
+    c += ((w.z & 0xFFFFu) <= L) + (w.z <= lim) + ((w.w & 0xFFFFu) <= L) + (w.w <= lim);
+    return c;
+}
+
+// A batch of a few requests (one arriving request is the paper's own case): grouping by length and
+// a table of per-length values would cost more than they save, so kLanes lanes take a request, each
+// an instance (or a few), and form T = E + c0 * kappa with E from the instance's own tables (the
+// same expression as in the memo kernel).
+//
+// What bounds it is the chain of dependent reads, so the segment #{R_i <= L} is found in two steps
+// instead of a binary search's ten: the splitters (every stride-th sorted length, a table of their
+// own, 16 or 32 bytes), then the one stride they leave, read whole.  Alg. 1's argmax d_g is taken
+// from d_g itself (the selections carry it), so no capability order is needed; the selections of
+// the lanes are combined in registers and, between the waves of a request, through LDS, so there is
+// no second launch and no workspace.  Fleets of more than kDirectSpan instances take several
+// workgroups per request, combined by k_direct_merge.
+template <int kLanes, int kU, bool kLargeTab>     // kU: instances of a lane in flight together
+__global__ __launch_bounds__(kLanes <= 64 ? kBlock : kLanes) void k_direct(DirectArgs a)
+{
+    constexpr int kThreads = kLanes <= 64 ? kBlock : kLanes;
+    constexpr int kPerGroup = kThreads / kLanes;              // requests per workgroup
+    constexpr int kS = kLargeTab ? 4 : 2, kB = kLargeTab ? 8 : 4;   // most 16-byte words of splitters, of a stride
+    const int sub = threadIdx.x % kLanes;
+    int r, part = 0;
+    if (kPerGroup > 1) {
+        r = blockIdx.x * kPerGroup + threadIdx.x / kLanes;
+    } else {
+        r = blockIdx.x / a.parts;
+        part = blockIdx.x % a.parts;
+    }
+    const bool live = r < a.n;
+    const int rc = min(r, a.n - 1);
+    const int L = min(max(a.pred_len[rc], 0), a.max_len);
+    const float c0 = (float)a.ctx0[rc], Lf = (float)L, D = a.budget[rc];
+    const float Dc = D > FLT_MAX ? FLT_MAX : D;
+    const int ex = a.exclude ? a.exclude[rc] : -1;
+    const float tri = Lf * (Lf - 1.0f) * 0.5f;
+    const int n_split = split_count(a.cap), stride = a.cap / n_split, s_words = n_split / 8, b_words = stride / 8;
+    const int g_begin = part * kDirectSpan, g_end = a.parts > 1 ? min(g_begin + kDirectSpan, a.n_inst) : a.n_inst;
+
+    DirectPart best = no_selection();
+    for (int g0 = g_begin + sub; g0 < g_end; g0 += kLanes * kU) {
+        int g[kU], k[kU];
+        uint4 w[kU][kB > kS ? kB : kS];
+        float4 K[kU];
+        float2 gh[kU];
+        double d[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            g[u] = min(g0 + u * kLanes, g_end - 1);           // (a repeat of the last one changes nothing)
+            const uint4* __restrict__ S = reinterpret_cast<const uint4*>(a.tabS + (size_t)g[u] * n_split);
+#pragma unroll
+            for (int i = 0; i < kS; ++i)
+                if (i < s_words) w[u][i] = S[i];
+            K[u] = a.instK[g[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            int b = 0;
+#pragma unroll
+            for (int i = 0; i < kS; ++i)
+                if (i < s_words) b += count_upto(w[u][i], (uint32_t)L);
+            k[u] = min(b, n_split - 1) * stride;              // (all of a full table: counted below)
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const uint4* __restrict__ R = reinterpret_cast<const uint4*>(a.tabR + (size_t)g[u] * a.cap + k[u]);
+#pragma unroll
+            for (int i = 0; i < kB; ++i)
+                if (i < b_words) w[u][i] = R[i];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+#pragma unroll
+            for (int i = 0; i < kB; ++i)
+                if (i < b_words) k[u] += count_upto(w[u][i], (uint32_t)L);
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            gh[u] = k[u] > 0 ? a.tabGH[(size_t)g[u] * a.cap + k[u] - 1] : a.headGH[g[u]];
+            d[u] = a.hD[g[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int N = __float_as_int(K[u].w);
+            const float E = fmaf(Lf, gh[u].y, gh[u].x) + tri * (K[u].z * (float)(N - k[u] + 1));
+            const float T = fmaf(c0, kappa_of(make_float2(K[u].x, K[u].y), Lf), E);
+            if (a.out_T && live) a.out_T[(size_t)r * a.n_inst + g[u]] = T;
+            if (g[u] != ex) {
+                const unsigned long long db = falling_bits(d[u]);
+                const uint32_t tb = ordered_bits(T);
+                DirectPart one{tb, (uint32_t)g[u], ~0u, ~0u, ~0u, ~0u};
+                if (T <= Dc) { one.d_hi = (uint32_t)(db >> 32); one.d_lo = (uint32_t)db; one.g = (uint32_t)g[u]; one.T = tb; }
+                take_better(best, one);
+            }
+        }
+    }
+
+    if constexpr (kLanes <= 64) {
+        best = best_over<kLanes == 16>(best);
+        if (sub == 0 && live) direct_answer(a, r, best);
+    } else {
+        constexpr int kN = kLanes / kWave;
+        static_assert(kN <= 16, "one row of lanes takes the waves' selections");
+        __shared__ DirectPart waves[kN];
+        best = best_over<false>(best);
+        if (lane_id() == 0) waves[threadIdx.x / kWave] = best;
+        __syncthreads();
+        if (threadIdx.x < 16) {
+            best = no_selection();
+            if (threadIdx.x < kN) best = waves[threadIdx.x];
+            best = best_over<true>(best);
+            if (threadIdx.x == 0) {
+                if (a.parts == 1) direct_answer(a, r, best);
+                else a.parts_out[(size_t)r * a.parts + part] = best;
+            }
+        }
     }
 }
 
-constexpr int kMaxDevices = 64;
-std::mutex scratch_mutex;
-unsigned long long* scratch_ptr[kMaxDevices];      // the array's address on each device, once asked for
+// The parts of each request of a wide fleet, a wave per request.
+__global__ __launch_bounds__(kBlock) void k_direct_merge(DirectArgs a)
+{
+    const int r = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
+    if (r >= a.n) return;
+    DirectPart best = no_selection();
+    for (int i = lane_id(); i < a.parts; i += kWave) take_better(best, a.parts_out[(size_t)r * a.parts + i]);
+    best = best_over<false>(best);
+    if (lane_id() == 0) direct_answer(a, r, best);
+}
+
+__global__ void k_set_int(int* p, int v) { *p = v; }
 
 template <typename K>
 bool set_lds(K kernel, size_t bytes)
@@ -1450,26 +1558,40 @@ int score_prepare(gr_fleet*)
     return ok ? GR_OK : GR_ERR_HIP;
 }
 
-// Alg. 1 pair by pair for up to kDirectMax requests; `best`: 2 * kDirectMax running selections,
-// all ones on entry for the requests of this batch, and left so.
-static int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, unsigned long long* best, hipStream_t s)
+// Alg. 1 pair by pair for up to kDirectMax requests.
+int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream_t s)
 {
-    const int64_t n = src.n;
+    const int n = (int)src.n, M = f->n_inst;
+    if (n == 0) return GR_OK;
+    if (src.n > kDirectMax) return GR_ERR_TOO_LARGE;
     DirectArgs d{};
     d.ctx0 = src.ctx0; d.pred_len = src.pred_len; d.budget = src.budget; d.exclude = src.exclude;
-    d.order = f->order; d.hN = f->hN; d.cls = f->cls; d.inst_class = f->inst_class;
-    d.tabR = f->tabR; d.tabGH = f->tabGH; d.headGH = f->headGH; d.posK = f->posK;
-    d.best_feasible = best; d.best_any = best + kDirectMax;
+    d.instK = f->instK; d.hD = f->hD; d.tabR = f->tabR; d.tabS = f->tabS; d.tabGH = f->tabGH; d.headGH = f->headGH;
+    d.parts_out = f->direct_part;
     d.out_inst = out.inst; d.out_slack = out.slack; d.out_fallback = out.fallback; d.out_T = out.T;
-    d.n = (int)n; d.n_inst = f->n_inst; d.m_pad = f->m_pad; d.cap = f->cap; d.max_len = f->max_len;
-    d.keep = (float)(1.0 - f->lam_built);
+    d.n = n; d.n_inst = M; d.cap = f->cap; d.max_len = f->max_len;
+    d.parts = (M + kDirectSpan - 1) / kDirectSpan;
+    if ((int64_t)n * d.parts > kDirectParts) d.parts = 1;      // (many requests fill the chip as they are)
+    // lanes per request: an instance each as far as a workgroup goes (few requests: the chain of reads
+    // of one instance is the time of the call); 64 lanes leave the fewest idle on small fleets
+    const int lanes = M <= 16 ? 16 : M <= 64 ? 64 : M <= 512 ? 256 : 1024;
     {
         ProfScope ps(f, kDirect, s);
-        hipLaunchKernelGGL(k_direct, dim3((f->m_pad + kBlock - 1) / kBlock, (unsigned)n), dim3(kBlock), 0, s, d);
+#define GR_LAUNCH_DIRECT(N, U) do { \
+        const dim3 grid(N <= 64 ? (n + kBlock / N - 1) / (kBlock / N) : n * d.parts), block(N <= 64 ? kBlock : N); \
+        if (f->cap > 512) hipLaunchKernelGGL((k_direct<N, (U > 2 ? 2 : U), true>), grid, block, 0, s, d); \
+        else hipLaunchKernelGGL((k_direct<N, U, false>), grid, block, 0, s, d); } while (0)
+        if (lanes == 16) GR_LAUNCH_DIRECT(16, 1);
+        else if (lanes == 64) GR_LAUNCH_DIRECT(64, 1);
+        else if (lanes == 256) GR_LAUNCH_DIRECT(256, 1);
+        else if (M <= 1024) GR_LAUNCH_DIRECT(1024, 1);
+        else GR_LAUNCH_DIRECT(1024, 4);
+#undef GR_LAUNCH_DIRECT
     }
-    {
-        ProfScope ps(f, kDirectFinish, s);
-        hipLaunchKernelGGL(k_direct_finish, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, d);
+    if (d.parts > 1) {
+        ProfScope ps(f, kDirectMerge, s);
+        constexpr int per = kBlock / kWave;
+        hipLaunchKernelGGL(k_direct_merge, dim3((n + per - 1) / per), dim3(kBlock), 0, s, d);
     }
     return hipGetLastError() == hipSuccess ? GR_OK : GR_ERR_HIP;
 }
@@ -1483,42 +1605,6 @@ static int ranks_needed(const gr_fleet* f, hipStream_t s, bool* needed)
     return GR_OK;
 }
 
-int static_scratch(int device, unsigned long long** out)
-{
-    if (device < 0 || device >= kMaxDevices) return GR_ERR_TOO_LARGE;
-    std::lock_guard<std::mutex> lock(scratch_mutex);
-    if (!scratch_ptr[device]) {
-        int current = -1;
-        if (hipGetDevice(&current) != hipSuccess || current != device) return GR_ERR_INVALID_ARG;
-        void* p = nullptr;
-        if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) return GR_ERR_HIP;
-        scratch_ptr[device] = static_cast<unsigned long long*>(p);
-    }
-    *out = scratch_ptr[device];
-    return GR_OK;
-}
-
-int launch_score_static(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream_t s)
-{
-    if (src.n == 0) return GR_OK;
-    if (src.n > kDirectMax) return GR_ERR_TOO_LARGE;
-    unsigned long long* best = nullptr;
-    const int rc = static_scratch(f->device, &best);
-    if (rc != GR_OK) return rc;
-    // the array keeps whatever the last call on this GPU left (a call that was cut short may
-    // have left selections behind): set this batch's slots before use, with a kernel, so that
-    // the call can be recorded into a graph
-    hipLaunchKernelGGL(k_fill_ones, dim3((unsigned)((src.n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, best, (int)src.n);
-    if (hipGetLastError() != hipSuccess) return GR_ERR_HIP;
-    bool with_ranks = false;       // the capability order of the current status (two small kernels, no allocation)
-    if (ranks_needed(f, s, &with_ranks) != GR_OK) return GR_ERR_HIP;
-    if (with_ranks) {
-        const int rc2 = launch_ranks(f, nullptr, s);
-        if (rc2 != GR_OK) return rc2;
-    }
-    return launch_direct(f, src, out, best, s);
-}
-
 int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& out, hipStream_t s,
                  bool small_batch_ok)
 {
@@ -1527,24 +1613,16 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         if (out.n_selected) hipLaunchKernelGGL(k_set_int, dim3(1), dim3(1), 0, s, out.n_selected, 0);
         return hipGetLastError() == hipSuccess ? GR_OK : GR_ERR_HIP;
     }
-    // up to about two million pairs (the default) a thread per pair is cheaper than the five kernels
-    // of the grouped pass
+    if (small_batch_ok && !migrate && n <= kDirectMax && n * f->m_pad <= f->small_batch_pairs)
+        return launch_direct(f, src, out, s);
     // The capability order of the current status, if nobody has made it yet, comes first.  While
     // the stream is being captured it always does: a recorded pass may be replayed after a status
     // build that was recorded elsewhere.
     bool with_ranks = false;
     if (ranks_needed(f, s, &with_ranks) != GR_OK) return GR_ERR_HIP;
-    if (small_batch_ok && !migrate && n <= kDirectMax && n * f->m_pad <= f->small_batch_pairs) {
-        if (with_ranks) {
-            const int rc = launch_ranks(f, nullptr, s);
-            if (rc != GR_OK) return rc;
-        }
-        return launch_direct(f, src, out, f->direct_best, s);
-    }
-    // In the grouped pass it rides along with the first two launches.
+    // In the grouped pass it rides along with the first launch.
     const RankArgs ranks = rank_args(f, nullptr);
-    const int rank_bx = with_ranks ? (f->n_inst + kWave - 1) / kWave : 0;
-    const int rank_blocks = rank_bx * ((f->n_inst + kGroupBlock - 1) / kGroupBlock);
+    const int order_blocks = with_ranks ? rank_blocks(f->m_pad, kGroupBlock) : 0;
     const int bins = f->bins;
     // Requests per thread of the grouping kernels.  Every workgroup pays a pass over all length
     // bins and one global atomic per length it has seen, so the histogram of a large batch is
@@ -1557,23 +1635,21 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     const auto blocks_for = [n](int items) {
         return (unsigned)((n + (int64_t)kGroupBlock * items - 1) / ((int64_t)kGroupBlock * items));
     };
-    size_t hist_lds = (size_t)((bins + 1) / 2) * 4;
+    const size_t hist_lds = max((size_t)((bins + 1) / 2) * 4, kGroupBlock / kWave * kRankPer * sizeof(int));
     const size_t scat_lds = (size_t)bins * 4;
-    if (hist_lds < kGroupBlock * sizeof(double)) hist_lds = kGroupBlock * sizeof(double);   // (the counting step's competitors)
     const int off = migrate ? kHistMigrate - kHistRoute : 0;
     {
         ProfScope ps(f, kHistRoute + off, s);
-#define GR_LAUNCH_HIST(M, I) hipLaunchKernelGGL((k_hist<M, I>), dim3(blocks_for(I) + rank_blocks), dim3(kGroupBlock), hist_lds, s, src, \
-                                                f->len_cnt, bins, f->max_len, (int)blocks_for(I), ranks, rank_bx)
+#define GR_LAUNCH_HIST(M, I) hipLaunchKernelGGL((k_hist<M, I>), dim3(blocks_for(I) + order_blocks), dim3(kGroupBlock), hist_lds, s, src, \
+                                                f->len_cnt, bins, f->max_len, (int)blocks_for(I), ranks)
         if (migrate) { if (h_items == 16) GR_LAUNCH_HIST(true, 16); else GR_LAUNCH_HIST(true, 4); }
         else { if (h_items == 16) GR_LAUNCH_HIST(false, 16); else GR_LAUNCH_HIST(false, 4); }
 #undef GR_LAUNCH_HIST
     }
     {
         ProfScope ps(f, kScanRoute + off, s);
-        const int final_blocks = with_ranks ? (f->m_pad + kScanBlock - 1) / kScanBlock : 0;
-        hipLaunchKernelGGL(k_scan, dim3(kScanGroups + final_blocks), dim3(kScanBlock), 0, s, f->len_cnt, f->len_base, f->row_len,
-                           f->row_off, f->tile_off, f->len_row, f->len_ceil, f->totals, out.n_selected, bins, ranks);
+        hipLaunchKernelGGL(k_scan, dim3(kScanGroups), dim3(kScanBlock), 0, s, f->len_cnt, f->len_base, f->row_len,
+                           f->row_off, f->tile_off, f->len_row, f->len_ceil, f->totals, out.n_selected, bins);
     }
     if (with_ranks) f->ranks_current = true;
     const int64_t max_rows = n < bins ? n : bins;

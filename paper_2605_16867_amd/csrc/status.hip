@@ -34,7 +34,8 @@ struct BuildArgs {
     int* hN;
     double* hD;
     int* act_inst;
-    int* rank_acc;
+    float4* instK;
+    uint16_t* tabS;
     int* counters;
     int64_t n_active, n_queued;
     int n_inst, max_entries, max_len;
@@ -49,6 +50,16 @@ struct BuildArgs {
     double lam;
     const double *emaQ, *emaP, *emaD;
 };
+
+// The coefficients of a pair's latency that depend on the instance alone (see gr_fleet::instK);
+// `bp`: its smoothed prefill seconds per token.
+__device__ __forceinline__ float4 inst_coef(const BuildArgs& a, const ClassCoef& cc, double bp, int n)
+{
+    const double keep = 1.0 - a.lam;
+    const float gam = (float)keep * (float)cc.gamma;
+    return a.lam != 0.0 ? make_float4((float)(keep * cc.delta + a.lam * bp), (float)(keep * cc.gamma), gam, __int_as_float(n))
+                        : make_float4((float)cc.delta, (float)cc.gamma, gam, __int_as_float(n));
+}
 
 // Median of three; the compiler turns this shape into one v_med3_u32.
 __device__ __forceinline__ uint32_t med3_u32(uint32_t a, uint32_t b, uint32_t c)
@@ -188,6 +199,15 @@ __device__ __forceinline__ void bitonic_sort_split(uint32_t (&key)[kEPL], int la
     }
 }
 
+// Sorted length number `v` of instance g, `len`, if it is one of the splitters of a search (every
+// (kCap / splitters)-th; a lane's share of consecutive lengths never spans more than one stride).
+template <int kCap>
+__device__ __forceinline__ void store_splitter(uint16_t* tabS, int g, int v, uint16_t len)
+{
+    constexpr int kSplit = split_count(kCap), kStride = kCap / kSplit;
+    if ((v + 1) % kStride == 0) tabS[(size_t)g * kSplit + v / kStride] = len;
+}
+
 // Exclusive prefix over the lanes of a wave, and the total.
 __device__ __forceinline__ long long wave_excl_scan(long long v, long long& total)
 {
@@ -215,10 +235,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
     {   // feedback routing: an instance that has been given nothing since its table was built keeps it
         const bool touched = a.pend_touched[g] != 0;
         if (lane == 0 && touched) a.pend_touched[g] = 0;
-        if (a.only_touched && !touched) {
-            if (lane == 0) a.rank_acc[g] = 0;
-            return;
-        }
+        if (a.only_touched && !touched) return;
     }
     int* ctx = reinterpret_cast<int*>(smem) + wave * 3 * kCap;  // this wave's contexts, by entry index
     int* olen = ctx + kCap;    // under a batch cap: length and context as given (ctx then holds them
@@ -447,7 +464,13 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
             const long long s64 = sstar, tri_s = s64 * (s64 - 1) / 2;
             Y1 = Y; X1 = X; P1 = Pc;
             uint16_t* dstR = a.tabR + (size_t)g * kCap;
+            uint16_t* dstS = a.tabS + (size_t)g * split_count(kCap);
+            constexpr int kStride = kCap / split_count(kCap);
             float2* dstGH = a.tabGH + (size_t)g * kCap;
+            const auto put_R = [&](int slot, uint16_t len) {
+                dstR[slot] = len;
+                if ((slot + 1) % kStride == 0) dstS[slot / kStride] = len;
+            };
 #pragma unroll
             for (int r = 0; r < kEPL; ++r) {
                 const int v = lane * kEPL + r;
@@ -463,11 +486,11 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
                     double Gq = q_adm + (cc.beta * Ys + cc.gamma * Xs);
                     double Hs = cc.alpha + (cc.beta * (n_after + 1.0) + cc.gamma * S_next);
                     if (blended) { Gq = keep * Gq + a.lam * bq; Hs = keep * Hs + a.lam * bd; }
-                    dstR[w] = (uint16_t)(R[r] - sstar);
+                    put_R(w, (uint16_t)(R[r] - sstar));
                     dstGH[w] = make_float2((float)Gq, (float)Hs);
                 } else {                                          // the slots behind the survivors
                     const int slot = v < Nrun ? Nleft + v : v;
-                    dstR[slot] = (uint16_t)0xFFFFu;
+                    put_R(slot, (uint16_t)0xFFFFu);
                     dstGH[slot] = make_float2(0.f, 0.f);
                 }
             }
@@ -477,7 +500,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
                 if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
                 a.headGH[g] = make_float2((float)Gq0, (float)H0);
                 a.hN[g] = Nleft;
-                a.rank_acc[g] = 0;
+                a.instK[g] = inst_coef(a, cc, bp, Nleft);
                 if (!a.use_pending) a.pend_cnt[g] = 0;
                 // the next decode step that runs: the first one played above, else the batch as it stands
                 double d = d_first >= 0.0 ? d_first
@@ -540,6 +563,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
         } else {
             dstGH[0] = tGH[0];
         }
+        store_splitter<kCap>(a.tabS, g, lane * kEPL + kEPL - 1, tR[kEPL - 1]);
     }
     if (lane == 0) {
         const double Cd = (double)Ctot;
@@ -547,7 +571,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
         if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
         a.headGH[g] = make_float2((float)Gq0, (float)H0);
         a.hN[g] = Nrun;
-        a.rank_acc[g] = 0;
+        a.instK[g] = inst_coef(a, cc, bp, Nrun);
         if (!a.use_pending) a.pend_cnt[g] = 0;
         // the next decode step that runs: the first one played above, else the batch as it stands
         double d = d_first >= 0.0 ? d_first : fma(cc.gamma, Cd, fma(cc.beta, (double)Nrun, cc.alpha));
@@ -623,10 +647,7 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
     if (g >= a.n_inst) return;
     // feedback routing: an instance that has been given nothing since its table was built keeps it
     // (the mark is cleared at the very end, when every wave of the instance has read it)
-    if (a.only_touched && a.pend_touched[g] == 0) {
-        if (lane == 0 && part == 0) a.rank_acc[g] = 0;
-        return;
-    }
+    if (a.only_touched && a.pend_touched[g] == 0) return;
     // LDS of an instance, all by entry index: contexts; budgets on the way in and finish times on the
     // way out (the caller's arrays are read and written in their own order, 64 consecutive entries
     // per instruction; the sorted order reaches them through LDS); flags, a byte each
@@ -863,13 +884,14 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
         } else {
             dstGH[0] = tGH[0];
         }
+        store_splitter<kCap>(a.tabS, g, first + lane * kEPL + kEPL - 1, tR[kEPL - 1]);
     }
     if (lane == 0 && part == 0) {
         double Gq0 = q, H0 = fma(cc.gamma, Ctot, fma(cc.beta, (double)(N + 1), cc.alpha));
         if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
         a.headGH[g] = make_float2((float)Gq0, (float)H0);
         a.hN[g] = N;
-        a.rank_acc[g] = 0;
+        a.instK[g] = inst_coef(a, cc, bp, N);
         a.pend_touched[g] = 0;
         if (!a.use_pending) a.pend_cnt[g] = 0;
         double d = fma(cc.gamma, Ctot, fma(cc.beta, (double)N, cc.alpha));     // the next decode step
@@ -879,17 +901,12 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
     }
 }
 
-// Capability order of Alg. 1's argmax d_g as two kernels of their own (see common.h for the
-// steps; a scoring pass normally runs them as extra workgroups of its first two kernels).
-__global__ __launch_bounds__(kBlock) void k_rank_count(RankArgs a)
+// Capability order of Alg. 1's argmax d_g as a kernel of its own (see common.h; a grouped scoring
+// pass normally makes it in extra workgroups of its first kernel).
+__global__ __launch_bounds__(kBlock) void k_rank(RankArgs a)
 {
-    __shared__ double comp[kBlock];
-    rank_count_tile<kBlock>(a, blockIdx.x, blockIdx.y, comp);
-}
-
-__global__ __launch_bounds__(kBlock) void k_rank_final(RankArgs a)
-{
-    rank_final_item(a, blockIdx.x * kBlock + threadIdx.x);
+    __shared__ int sums[kBlock / kWave * kRankPer];
+    rank_block<kBlock>(a, blockIdx.x, sums);
 }
 
 // One step of the exponential moving average of Alg. 1, q <- w * sample + (1 - w) * q, for
@@ -1135,8 +1152,7 @@ int status_prepare()
 RankArgs rank_args(const gr_fleet* f, int* out_rank)
 {
     RankArgs r{};
-    r.d = f->hD; r.rank_acc = f->rank_acc; r.cls = f->cls; r.inst_class = f->inst_class;
-    r.emaP = f->emaP; r.lam = f->lam_built;
+    r.d = f->hD; r.instK = f->instK;
     r.rank = f->rank; r.order = f->order; r.posK = f->posK; r.out_rank = out_rank;
     r.n_inst = f->n_inst; r.m_pad = f->m_pad;
     return r;
@@ -1145,14 +1161,9 @@ RankArgs rank_args(const gr_fleet* f, int* out_rank)
 int launch_ranks(gr_fleet* f, int* out_rank, hipStream_t s)
 {
     const RankArgs r = rank_args(f, out_rank);
-    const int M = f->n_inst;
     {
-        ProfScope ps(f, kRankCount, s);
-        hipLaunchKernelGGL(k_rank_count, dim3((M + kWave - 1) / kWave, (M + kBlock - 1) / kBlock), dim3(kBlock), 0, s, r);
-    }
-    {
-        ProfScope ps(f, kRankFinal, s);
-        hipLaunchKernelGGL(k_rank_final, dim3((f->m_pad + kBlock - 1) / kBlock), dim3(kBlock), 0, s, r);
+        ProfScope ps(f, kRank, s);
+        hipLaunchKernelGGL(k_rank, dim3(rank_blocks(f->m_pad, kBlock)), dim3(kBlock), 0, s, r);
     }
     if (hipGetLastError() != hipSuccess) return GR_ERR_HIP;
     f->ranks_current = true;
@@ -1170,7 +1181,7 @@ int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s)
     b.cls = f->cls; b.inst_class = f->inst_class;
     b.tabR = f->tabR; b.tabGH = f->tabGH; b.headGH = f->headGH;
     b.hN = f->hN; b.hD = f->hD; b.act_inst = f->act_inst;
-    b.rank_acc = f->rank_acc; b.counters = f->counters;
+    b.instK = f->instK; b.tabS = f->tabS; b.counters = f->counters;
     b.n_active = in.n_active; b.n_queued = in.n_queued;
     b.n_inst = f->n_inst; b.max_entries = f->max_entries; b.max_len = f->max_len;
     b.pend_cnt = f->pend_cnt; b.pend_prompt = f->pend_prompt; b.pend_len = f->pend_len;
