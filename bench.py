@@ -8,7 +8,10 @@ in HBM: gr_build_status, gr_score_route over the incoming batch, gr_risk_scan
 Prints ONE JSON line.  ``value`` is pair-estimates per second over the timed
 steps: (incoming x instances) + (flagged x (instances - 1)) + one finish
 estimate per held request in each of the two status builds, divided by wall
-time.  ``roofline`` describes the kernel that took the most time, timed with
+time.  Every such pair is decided; its latency E(length, instance) + tokens * rate(instance)
+is not formed one by one: E is tabulated per (distinct length, instance) and a request meets the
+exact minima and bounds of that table (see csrc/score.hip), with Alg. 1's choice over all pairs as
+the result.  ``roofline`` describes the kernel that took the most time, timed with
 HIP events around each of its launches inside the timed region;
 ``cpu_baseline`` is the CPU reference timed on this machine's host cores on a
 bounded sample of the same fleet.
@@ -28,15 +31,15 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
-FP32_VECTOR_PEAK_TFLOPS = 157.3  # 256 CU x 128 lanes x 2 flop x 2.4 GHz (packed FMA)
 
 # Algorithmic work per unit, independent of how the kernels are organised.
-# Scoring, per (request, instance) pair: Eq. 2 from per-(instance, length) terms
-# (one multiply-add = 2 flops) and the pair's part in the selections of Alg. 1
-# (one comparison: the running least latency, which also decides feasibility
-# because the feasible set is non-empty exactly when the least latency meets the
-# deadline): 3 operations, counted as flops.
-OPS_PER_PAIR = 3.0
+# Table of a scoring pass: one 4-byte value per (distinct length, instance) written, the instances' tables read.
+MEMO_BYTES_PER_VALUE = 4.0
+TABLE_BYTES_PER_ENTRY = 10.0
+# Selection, per request: tokens, length, deadline read; instance and slack written (a risk scan also
+# reads the request's instance, its generated tokens and its flag).
+SELECT_BYTES_PER_REQUEST = 20.0
+SELECT_EXTRA_BYTES_MIGRATE = 9.0
 # Status build, per held request: read prompt, generated, remaining (12 B), write
 # finish (4 B) and one table entry (2 B sorted length + 8 B segment coefficients);
 # the risk scan also reads the budget (4 B) and writes the flag (1 B).
@@ -230,7 +233,7 @@ def main():
     torch.cuda.synchronize()
     launches_all = h.gr_profile_read_launches(prof_slots * a.steps)
     prof_all = {n: (sum(v), len(v)) for n, v in launches_all.items()}
-    heaviest = max((n for n in prof_all if n.startswith(("k_tile", "k_build")) and prof_all[n][1]),
+    heaviest = max((n for n in prof_all if n.startswith(("k_memo", "k_select", "k_build")) and prof_all[n][1]),
                    key=lambda n: prof_all[n][0])
     # timed region: HIP events around the launches of that kernel only (an event pair costs a few
     # microseconds of stream time: around each of the dozen launches of a step, about a tenth of it)
@@ -276,6 +279,8 @@ def main():
     pairs_step = pairs_route + pairs_mig + 2 * entries
     ms_step = dt / a.steps * 1e3
 
+    flag_np = flag.cpu().numpy().astype(bool)
+    rows = {"route": len(np.unique(fl.in_len)), "migrate": len(np.unique(fl.act_rem_refreshed[flag_np]))}
     kernels = {}
     for name, (ms, cnt) in prof.items():
         if not cnt:
@@ -284,14 +289,16 @@ def main():
         each = sorted(launches[name])
         k = {"avg_ms": avg_ms, "median_ms": each[len(each) // 2], "p99_ms": each[min(len(each) - 1, int(0.99 * len(each)))],
              "launches_per_step": cnt / a.steps}
-        if name.startswith("k_tile"):
-            pairs = (pairs_route if "route" in name else pairs_mig) / (cnt / a.steps)     # per launch
-            k.update(bound="alu", pairs=pairs, pairs_per_s=pairs / (avg_ms * 1e-3),
-                     achieved=pairs * OPS_PER_PAIR / (avg_ms * 1e-3) / 1e12,
-                     peak=FP32_VECTOR_PEAK_TFLOPS, unit="TFLOP/s")
+        side = "route" if "route" in name else "migrate"
+        by = None
+        if name.startswith("k_memo") and cnt == a.steps:
+            by = rows[side] * M * MEMO_BYTES_PER_VALUE + entries * TABLE_BYTES_PER_ENTRY
+        elif name.startswith("k_select") and cnt == a.steps:
+            by = R * SELECT_BYTES_PER_REQUEST if side == "route" else na * (SELECT_BYTES_PER_REQUEST + SELECT_EXTRA_BYTES_MIGRATE)
         elif name == "k_build" and cnt == 2 * a.steps:
             # two launches per step: plain build, and the scan's rebuild with budget + flag
             by = entries * (BUILD_BYTES_PER_ENTRY + SCAN_EXTRA_BYTES_PER_ENTRY / 2)
+        if by:
             k.update(bound="hbm", achieved=by / (avg_ms * 1e-3) / 1e9, peak=HBM_PEAK_GBS, unit="GB/s")
         if "achieved" in k:
             k["frac"] = k["achieved"] / k["peak"]

@@ -85,14 +85,14 @@ enum {
  *   max_requests              upper bound of n_req of one gr_score_route call
  * Hard limits: max_entries_per_inst <= 2048; max_len <= 32767.
  * Device memory held by the handle until gr_destroy, all of it allocated here: with
- * cap = max_entries_per_inst rounded up to 64, 128, .. 2048, M' = n_inst rounded up to a
- * multiple of 128 and N = max(max_requests, n_inst * max_entries_per_inst),
+ * cap = max_entries_per_inst rounded up to 64, 128, .. 2048, M' = the instances of every class
+ * rounded up to a multiple of 16 and added up, and N = max(max_requests, n_inst * max_entries_per_inst),
  *   18 * n_inst * cap bytes          instance tables and the lists of feedback routing,
  *   8 * n_inst * max_entries_per_inst bytes   per held request (its instance, a spare finish time),
- *   4.25 * M' * min(max_len + 1, N) bytes     the per-(distinct length, instance) table of a scoring
- *                                    pass, reserved for the worst case whatever the batches turn
- *                                    out to be (285 MB for 4 096 instances and max_len 16 384),
- *   16.2 * N bytes                   the requests of a scoring pass in grouped order,
+ *   (4.25 * M' + 12 * n_class) * min(max_len + 1, N) bytes   the per-(distinct length, instance) table
+ *                                    of a scoring pass with its minima, reserved for the worst case
+ *                                    whatever the batches turn out to be (290 MB for 4 096 instances of
+ *                                    6 classes and max_len 16 384),
  * plus a few arrays of n_inst or max_len + 1 words.
  */
 int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
@@ -313,17 +313,17 @@ int gr_set_batch_cap(gr_fleet* f, const int32_t* cap);
 
 /*
  * How a batch is scored.  Alg. 1 is the same either way; the work is laid out
- * differently.  A large batch is grouped by predicted length, the decode term
- * of Eq. 2 is tabulated once per (distinct length, instance), and tiles of 32
- * requests run against all instances.  A batch of a few requests (the paper
- * routes one arriving request at a time) skips grouping and table: a thread
- * per (request, instance) pair searches the instance's own tables, and the
- * whole call is one kernel.
+ * differently.  For a large batch the decode term of Eq. 2 is tabulated once per
+ * (distinct length, instance), with its minima over runs of instances, and a
+ * request looks at the instances of a run only where the minimum of the run
+ * leaves it in question.  A batch of a few requests (the paper routes one
+ * arriving request at a time) skips the table: a thread per (request, instance)
+ * pair searches the instance's own tables, and the whole call is one kernel.
  *
  *   max_pairs   gr_score_route and gr_route_feedback score a batch (a chunk)
  *               pair by pair when n_req * (n_inst rounded up to 128) is at
  *               most this and n_req <= 4096.  0: never.  Default 262 144.
- * gr_score_route_cached and gr_risk_scan always take the grouped path.
+ * gr_score_route_cached and gr_risk_scan always take the table.
  * Equal latencies go to the lowest instance index either way.
  */
 int gr_set_small_batch_pairs(gr_fleet* f, int64_t max_pairs);

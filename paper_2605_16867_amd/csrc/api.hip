@@ -1,6 +1,6 @@
 // Host entry points of libgoodroute: the fleet handle, argument checks and the
 // order in which the kernels of status.hip and score.hip are queued.
-#include <cstdlib>
+#include <algorithm>
 #include <new>
 
 #include "common.h"
@@ -10,14 +10,56 @@ namespace {
 
 const char* const kKernelNames[kNumKernels] = {
     "k_build", "k_rank",
-    "k_hist<route>", "k_scan<route>", "k_group<route>", "k_tile<route>",
-    "k_hist<migrate>", "k_scan<migrate>", "k_group<migrate>", "k_tile<migrate>",
-    "k_hits<route>", "k_direct", "k_direct_merge"};
+    "k_mark<route>", "k_scan<route>", "k_memo<route>", "k_class<route>", "k_select<route>",
+    "k_scan<migrate>", "k_memo<migrate>", "k_class<migrate>", "k_select<migrate>",
+    "k_hits<route>", "k_pairs<route>", "k_direct", "k_direct_merge"};
 
 template <typename T>
 bool dev_alloc(T** p, size_t n)
 {
     return hipMalloc(reinterpret_cast<void**>(p), (n ? n : 1) * sizeof(T)) == hipSuccess;
+}
+
+// The fleet as the kernels read it: coefficients, classes, and the instances class by class, every
+// class padded to whole runs of kMemoP positions (see gr_fleet).
+struct FleetTables {
+    std::vector<ClassCoef> coef;
+    std::vector<float2> coef32;
+    std::vector<int2> cls_run, run_cls;
+    std::vector<int> slot, slot_of;
+};
+
+bool make_tables(FleetTables& t, int n_inst, int n_class, const double* delta, const double* alpha, const double* beta,
+                 const double* gamma, const int32_t* inst_class) noexcept
+{
+    try {
+        std::vector<int> per_class(n_class, 0), next(n_class), by_step(n_class);
+        for (int g = 0; g < n_inst; ++g) ++per_class[inst_class[g]];
+        for (int c = 0; c < n_class; ++c) {
+            t.coef.push_back(ClassCoef{delta[c], alpha[c], beta[c], gamma[c]});
+            t.coef32.push_back(make_float2((float)delta[c], (float)gamma[c]));
+            by_step[c] = c;
+        }
+        // classes of slow steps first: their instances are the just-enough choices, and a search that
+        // meets them first passes over most of the others (any order gives the same answers)
+        std::stable_sort(by_step.begin(), by_step.end(), [&](int x, int y) { return alpha[x] > alpha[y]; });
+        t.cls_run.resize(n_class);
+        for (const int c : by_step) {
+            const int run = (int)t.run_cls.size(), runs = (per_class[c] + kMemoP - 1) / kMemoP;
+            t.cls_run[c] = make_int2(run, runs);
+            t.run_cls.insert(t.run_cls.end(), runs, make_int2(run * kMemoP, per_class[c]));
+            next[c] = run * kMemoP;
+        }
+        t.slot.assign(t.run_cls.size() * kMemoP, -1);
+        t.slot_of.resize(n_inst);
+        for (int g = 0; g < n_inst; ++g) {
+            t.slot_of[g] = next[inst_class[g]]++;
+            t.slot[t.slot_of[g]] = g;
+        }
+        return true;
+    } catch (...) {
+        return false;
+    }
 }
 
 bool status_args_ok(const gr_fleet* f, const int32_t* act_off, const int32_t* act_prompt,
@@ -62,6 +104,8 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
         if (inst_class[g] < 0 || inst_class[g] >= n_class) return GR_ERR_INVALID_ARG;
     if ((int64_t)n_inst * max_entries_per_inst > (int64_t(1) << 30)) return GR_ERR_TOO_LARGE;
 
+    FleetTables tab_h;
+    if (!make_tables(tab_h, n_inst, n_class, delta, alpha, beta, gamma, inst_class)) return GR_ERR_NOMEM;
     gr_fleet* f = new (std::nothrow) gr_fleet;
     if (!f) return GR_ERR_NOMEM;
     f->n_inst = n_inst; f->n_class = n_class;
@@ -73,49 +117,60 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     f->cap = kWave * f->epl;
     f->n_split = split_count(f->cap);
     f->m_pad = ((n_inst + 2 * kWave - 1) / (2 * kWave)) * (2 * kWave);
+    f->n_run = (int)tab_h.run_cls.size();
+    f->m_pos = f->n_run * kMemoP;
+    f->run_pad = (f->n_run + kMemoP - 1) / kMemoP * kMemoP;
+    f->c_pad = (n_class + 3) / 4 * 4;
     f->bins = max_len + 1;
     f->row_cap = f->req_cap < f->bins ? f->req_cap : f->bins;
-    if (f->row_cap < 1) f->row_cap = 1;
+    f->row_cap = (f->row_cap + kMemoU - 1) / kMemoU * kMemoU;
+    if (f->row_cap < kMemoU) f->row_cap = kMemoU;
     if (hipGetDevice(&f->device) != hipSuccess) { delete f; return GR_ERR_HIP; }
-    if (score_lds_bytes(f) > 160 * 1024) { delete f; return GR_ERR_TOO_LARGE; }
 
-    const size_t tab = (size_t)n_inst * f->cap;
+    const size_t tab = (size_t)n_inst * f->cap, seen_bytes = (size_t)(f->bins + 15) / 16 * 16;
     const bool ok =
         dev_alloc(&f->cls, n_class) && dev_alloc(&f->inst_class, n_inst) &&
         dev_alloc(&f->tabR, tab) && dev_alloc(&f->tabGH, tab) && dev_alloc(&f->headGH, n_inst) &&
         dev_alloc(&f->hN, n_inst) && dev_alloc(&f->hD, n_inst) &&
         dev_alloc(&f->emaQ, n_inst) && dev_alloc(&f->emaP, n_inst) && dev_alloc(&f->emaD, n_inst) &&
-        dev_alloc(&f->instK, n_inst) && dev_alloc(&f->tabS, (size_t)n_inst * f->n_split) && dev_alloc(&f->rank, n_inst) && dev_alloc(&f->order, f->m_pad) && dev_alloc(&f->posK, f->m_pad) &&
+        dev_alloc(&f->instK, n_inst) && dev_alloc(&f->tabS, (size_t)n_inst * f->n_split) &&
+        dev_alloc(&f->clsK, n_class) && dev_alloc(&f->slot_inst, f->m_pos) && dev_alloc(&f->slot_of, n_inst) && dev_alloc(&f->slot_key, f->m_pos) && dev_alloc(&f->run_cls, f->n_run) && dev_alloc(&f->cls_run, n_class) &&
+        dev_alloc(&f->order, f->m_pos) && dev_alloc(&f->pos_of, n_inst) && dev_alloc(&f->posK, f->m_pos) && dev_alloc(&f->posKey, f->m_pos) && dev_alloc(&f->run_head, f->n_run) &&
         dev_alloc(&f->act_inst, f->max_active) && dev_alloc(&f->counters, 1) &&
         dev_alloc(&f->pend_cnt, n_inst) && dev_alloc(&f->commit_mark, n_inst) && dev_alloc(&f->pend_touched, n_inst) && dev_alloc(&f->pend_prompt, tab) && dev_alloc(&f->pend_len, tab) &&
         dev_alloc(&f->scratch_finish, f->max_active) && dev_alloc(&f->batch_cap, n_inst) &&
-        dev_alloc(&f->len_cnt, f->bins) && dev_alloc(&f->len_base, f->bins) &&
-        dev_alloc(&f->row_len, f->row_cap) && dev_alloc(&f->row_off, f->row_cap + 1) &&
-        dev_alloc(&f->tile_off, f->row_cap + 1) && dev_alloc(&f->len_row, f->bins) && dev_alloc(&f->len_ceil, f->bins) && dev_alloc(&f->totals, 4) &&
-        dev_alloc(&f->recs, f->req_cap) && dev_alloc(&f->memo, (size_t)f->row_cap * f->m_pad) &&
-        dev_alloc(&f->tile_row, (size_t)(f->req_cap / kTileReq + f->row_cap + 1)) &&
-        dev_alloc(&f->grp_min, (size_t)f->row_cap * (f->m_pad / kMemoP)) && dev_alloc(&f->grp_k, f->m_pad / kMemoP) &&
+        dev_alloc(&f->seen, seen_bytes) && dev_alloc(&f->late_cnt, (size_t)n_inst * 4) &&
+        dev_alloc(&f->row_len, f->row_cap) && dev_alloc(&f->len_row, f->bins) && dev_alloc(&f->totals, 4) &&
+        dev_alloc(&f->memo, (size_t)f->row_cap * f->m_pos) && dev_alloc(&f->grp_min, (size_t)f->row_cap * f->run_pad) &&
+        dev_alloc(&f->run_k, f->n_run) && dev_alloc(&f->class_min, (size_t)f->row_cap * f->c_pad) &&
+        dev_alloc(&f->class_next, (size_t)f->row_cap * n_class) &&
         dev_alloc(&f->direct_part, (size_t)kDirectParts);
     if (!ok) { gr_destroy(f); return GR_ERR_NOMEM; }
 
-    ClassCoef* host = static_cast<ClassCoef*>(malloc(sizeof(ClassCoef) * n_class));
-    if (!host) { gr_destroy(f); return GR_ERR_NOMEM; }
-    for (int c = 0; c < n_class; ++c) host[c] = ClassCoef{delta[c], alpha[c], beta[c], gamma[c]};
-    const hipError_t e1 = hipMemcpy(f->cls, host, sizeof(ClassCoef) * n_class, hipMemcpyHostToDevice);
-    const hipError_t e2 = hipMemcpy(f->inst_class, inst_class, sizeof(int) * n_inst, hipMemcpyHostToDevice);
-    const hipError_t e3 = hipMemset(f->counters, 0, sizeof(int));
-    const hipError_t e4 = hipMemset(f->len_cnt, 0, sizeof(int) * f->bins);
-    const hipError_t e5 = hipMemset(f->totals, 0, sizeof(int) * 4);
-    const hipError_t e6 = hipMemset(f->pend_cnt, 0, sizeof(int) * n_inst);
-    const hipError_t e8 = hipMemset(f->pend_touched, 0, sizeof(int) * n_inst);
-    const hipError_t e9 = hipMemset(f->commit_mark, 0, sizeof(int) * n_inst);
-    free(host);
-    if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess || e4 != hipSuccess || e5 != hipSuccess || e6 != hipSuccess || e8 != hipSuccess || e9 != hipSuccess ||
-        hipDeviceSynchronize() != hipSuccess) {
+    bool sent = true;
+    const auto send = [&](void* to, const void* from, size_t bytes) {
+        sent = sent && hipMemcpy(to, from, bytes, hipMemcpyHostToDevice) == hipSuccess;
+    };
+    const auto clear = [&](void* p, size_t bytes) { sent = sent && hipMemset(p, 0, bytes) == hipSuccess; };
+    send(f->cls, tab_h.coef.data(), sizeof(ClassCoef) * n_class);
+    send(f->clsK, tab_h.coef32.data(), sizeof(float2) * n_class);
+    send(f->cls_run, tab_h.cls_run.data(), sizeof(int2) * n_class);
+    send(f->run_cls, tab_h.run_cls.data(), sizeof(int2) * f->n_run);
+    send(f->slot_inst, tab_h.slot.data(), sizeof(int) * f->m_pos);
+    send(f->slot_of, tab_h.slot_of.data(), sizeof(int) * n_inst);
+    send(f->inst_class, inst_class, sizeof(int) * n_inst);
+    clear(f->counters, sizeof(int));
+    clear(f->seen, seen_bytes);
+    clear(f->slot_key, sizeof(unsigned long long) * f->m_pos);
+    clear(f->totals, sizeof(int) * 4);
+    clear(f->pend_cnt, sizeof(int) * n_inst);
+    clear(f->pend_touched, sizeof(int) * n_inst);
+    clear(f->commit_mark, sizeof(int) * n_inst);
+    if (!sent || hipDeviceSynchronize() != hipSuccess) {
         gr_destroy(f);
         return GR_ERR_HIP;
     }
-    if (score_prepare(f) != GR_OK || status_prepare() != GR_OK) { gr_destroy(f); return GR_ERR_HIP; }
+    if (status_prepare() != GR_OK) { gr_destroy(f); return GR_ERR_HIP; }
     *out = f;
     return GR_OK;
 }
@@ -125,9 +180,9 @@ int gr_destroy(gr_fleet* f)
     if (!f) return GR_OK;
     (void)hipDeviceSynchronize();
     void* ptrs[] = {f->cls, f->inst_class, f->tabR, f->tabGH, f->headGH, f->hN, f->hD, f->emaQ, f->emaP, f->emaD, f->instK, f->tabS,
-                    f->rank, f->order, f->posK, f->act_inst, f->pend_cnt, f->commit_mark, f->pend_touched, f->pend_prompt, f->pend_len,
-                    f->scratch_finish, f->batch_cap, f->counters, f->len_cnt, f->len_base, f->row_len,
-                    f->row_off, f->tile_off, f->len_row, f->len_ceil, f->totals, f->recs, f->memo, f->tile_row, f->grp_min, f->grp_k, f->direct_part};
+                    f->clsK, f->slot_inst, f->slot_of, f->slot_key, f->run_cls, f->cls_run, f->order, f->pos_of, f->posK, f->posKey, f->run_head, f->act_inst, f->pend_cnt, f->commit_mark, f->pend_touched, f->pend_prompt, f->pend_len,
+                    f->scratch_finish, f->batch_cap, f->counters, f->seen, f->late_cnt, f->row_len,
+                    f->len_row, f->totals, f->memo, f->grp_min, f->run_k, f->class_min, f->class_next, f->direct_part};
     int rc = GR_OK;
     for (void* p : ptrs)
         if (p && hipFree(p) != hipSuccess) rc = GR_ERR_HIP;
@@ -210,7 +265,7 @@ int gr_score_route_cached(gr_fleet* f, int64_t n_req, const int32_t* ctx0, const
 {
     if (n_hits < 0 || (n_req > 0 && !hit_off) || (n_hits > 0 && (!hit_inst || !hit_len)))
         return GR_ERR_INVALID_ARG;
-    // (the correction below reads the per-length table of the grouped pass)
+    // (the correction below reads the per-length table)
     const int rc = score_route(f, n_req, ctx0, pred_len, budget, exclude_inst, out_inst, out_slack,
                                out_fallback, out_T, hip_stream, false);
     if (rc != GR_OK || n_req == 0) return rc;

@@ -35,28 +35,18 @@ constexpr int kWave = 64;
 constexpr int kWaves = kBlock / kWave;
 constexpr int kMaxEntries = 2048;
 constexpr int kMaxClasses = 64;
-constexpr int kMaxLen = 32767;     // one LDS counter per length in the grouping kernels
-constexpr int kTileReq = 32;       // requests of one length scored together by one wave
-constexpr int kGroupBlock = 1024;  // threads per workgroup of the grouping kernels (their cost is the pass over the LDS bins)
-constexpr int kMemoU = 256;        // lengths per pass of a workgroup of the memo kernel
+constexpr int kMaxLen = 32767;     // lengths and row numbers are kept in 16 bits
+constexpr int kMemoU = 256;        // distinct lengths per block of the table of a scoring pass
 constexpr int kDirectMax = 4096;   // most requests of a batch scored pair by pair, without grouping
 constexpr int kDirectSpan = 4096;  // instances that one workgroup takes of a request scored pair by pair
 constexpr int kDirectParts = 16384;  // room for the selections of such parts
-constexpr int kMemoP = 16;         // instances (waves) per workgroup of the memo kernel
+constexpr int kMemoP = 16;         // positions of a run of the class order
 
 // Splitters of an instance's sorted lengths, by table size (strides of 8, 8, 16, 32, 32, 64 lengths).
 constexpr int split_count(int cap) { return cap <= 64 ? 8 : cap <= 512 ? 16 : 32; }
 
 struct ClassCoef {
     double delta, alpha, beta, gamma;
-};
-
-// One request in grouped order.
-struct ReqRec {
-    float c0;   // tokens to prefill
-    float D;    // budget
-    int pex;    // excluded instance as a position in capability order, -1 none
-    int orig;   // index in the caller's arrays
 };
 
 // Where a batch of requests comes from: the caller's arrays (routing) or the
@@ -87,8 +77,8 @@ struct DirectPart {
 };
 
 enum KernelId {
-    kBuild = 0, kRank, kHistRoute, kScanRoute, kGroupRoute, kTileRoute,
-    kHistMigrate, kScanMigrate, kGroupMigrate, kTileMigrate, kHitsRoute, kDirect, kDirectMerge,
+    kBuild = 0, kRank, kMarkRoute, kScanRoute, kMemoRoute, kClassRoute, kSelectRoute,
+    kScanMigrate, kMemoMigrate, kClassMigrate, kSelectMigrate, kHitsRoute, kPairsRoute, kDirect, kDirectMerge,
     kNumKernels
 };
 
@@ -124,8 +114,12 @@ struct gr_fleet {
     int cap = 0;           // 64 * epl >= max_entries: table entries per instance
     int n_split = 0;       // splitters per instance: 8 (cap 64), 16 (to 512), 32
     int m_pad = 0;         // instances rounded up to a multiple of 128 (two blocks of 64 positions)
+    int m_pos = 0;         // positions of the class order: every class rounded up to whole runs of kMemoP
+    int n_run = 0;         // m_pos / kMemoP
+    int run_pad = 0;       // n_run rounded up to whole runs of kMemoP: row length of grp_min
+    int c_pad = 0;         // n_class rounded up to a multiple of 4: row length of class_min
     int bins = 0;          // max_len + 1
-    int64_t row_cap = 0;   // rows of the memo table
+    int64_t row_cap = 0;   // rows of the memo table, rounded up to whole blocks of kMemoU
     int device = 0;
     bool has_status = false;
     // smoothed black-box status (Sec. 3.3) and the weight it is blended in with
@@ -147,9 +141,21 @@ struct gr_fleet {
     // part T = E + c0 * (delta + gamma * L), blended as the tables are; the curvature gamma of E; entries (int bits)
     float4* instK = nullptr;
     uint16_t* tabS = nullptr; // [M][n_split] every (cap / n_split)-th of the sorted lengths: the first step of a search
-    int* rank = nullptr;     // [M]
-    int* order = nullptr;    // [m_pad] order[rank[g]] = g
-    float2* posK = nullptr;  // [m_pad] (delta, gamma) of the instance at each position of the capability order
+    // Class order: the instances class by class, every class padded to whole runs of kMemoP positions,
+    // inside a class in capability order (largest d_g first, equal d_g by index).  Without a blend the
+    // instances of a run then share the prefill part of T(r, g), and which of them is least or
+    // feasible depends on E alone.
+    float2* clsK = nullptr;       // [n_class] (delta, gamma) as single precision
+    int* slot_inst = nullptr;     // [m_pos] the instances class by class in index order, -1: padding
+    int* slot_of = nullptr;       // [M] slot of each instance
+    unsigned long long* slot_key = nullptr;   // [m_pos] d_g of each slot's instance as an integer that falls with it
+    int2* run_cls = nullptr;      // [n_run] first position of the run's class, instances of the class
+    int2* cls_run = nullptr;      // [n_class] first run of the class, runs of the class
+    int* order = nullptr;         // [m_pos] instance at each position, -1: padding
+    int* pos_of = nullptr;        // [M] position of each instance
+    float2* posK = nullptr;       // [m_pos] (delta, gamma) of the instance at each position
+    unsigned long long* posKey = nullptr;   // [m_pos] d_g as an integer that falls with it
+    uint4* run_head = nullptr;    // [n_run] the first position of each run: its key (low, high word), instance
     int* act_inst = nullptr; // [max_active] instance of each active request
     // feedback routing: the caller's last status inputs, and the requests routed since, per instance
     gr::StatusIn last_in{};
@@ -162,21 +168,19 @@ struct gr_fleet {
     bool has_cap = false;
     int* counters = nullptr; // [1] GR_DEV_* bits
     // scoring workspace
-    int* len_cnt = nullptr;   // [bins] requests per length; all zero between calls
-    int* len_base = nullptr;  // [bins] next free slot of each length in grouped order
-    int* row_len = nullptr;   // [row_cap] the distinct lengths, ascending
-    int* row_off = nullptr;   // [row_cap+1] first request of each distinct length
-    int* tile_off = nullptr;  // [row_cap+1] first tile of each distinct length
-    int* len_row = nullptr;   // [bins] row of each length present in the last batch
-    int* len_ceil = nullptr;  // [bins] rows shorter than each length = the first row at least that long
-    int* totals = nullptr;    // [4] requests, distinct lengths, tiles
-    gr::ReqRec* recs = nullptr;  // [req_cap] requests in grouped order
-    float* memo = nullptr;       // [row_cap][m_pad] E per distinct length and position
-    int* tile_row = nullptr;     // [req_cap / kTileReq + row_cap + 1] the row of every tile
-    float* grp_min = nullptr;    // [m_pad / kMemoP][row_cap] least E of each run of kMemoP positions, per row
-    float2* grp_k = nullptr;     // [m_pad / kMemoP] least delta and least gamma of each run
+    uint8_t* seen = nullptr;  // [bins, to 16] 1: some request of the batch has the length; all zero between calls
+    int* late_cnt = nullptr;  // [4][M] flagged requests, counted by the build (late_parts counts per instance)
+    int late_parts = 0;
+    int* row_len = nullptr;   // [row_cap] the distinct lengths ("rows"), ascending
+    uint16_t* len_row = nullptr;  // [bins] rows shorter than each length = its row if it has one
+    int* totals = nullptr;    // [4] -, distinct lengths
+    float* memo = nullptr;       // [row_cap / kMemoU][m_pos][kMemoU] E per distinct length and position
+    float* grp_min = nullptr;    // [row_cap][run_pad] least E of each run, per row
+    float4* run_k = nullptr;     // [n_run] least delta of the run, gamma, largest delta, lowest instance (int bits)
+    float* class_min = nullptr;  // [row_cap][c_pad] least E of each class, per row
+    uint2* class_next = nullptr; // [row_cap][n_class] next larger E of the class (bits), lowest instance that has the least
     bool tables_current = false;   // every instance's table is from the last inputs, blend weight and caps
-    bool ranks_current = false;    // rank, order and posK belong to the current d_g (else the next scoring pass makes them)
+    bool ranks_current = false;    // the class order belongs to the current d_g (else the next scoring pass makes it)
     int* pend_touched = nullptr;   // [M] 1: given requests since its table was built
     int64_t small_batch_pairs = int64_t(1) << 18;   // largest batch, in pairs, scored pair by pair
     gr::DirectPart* direct_part = nullptr;       // [kDirectParts] selections of the parts of a wide fleet, scored pair by pair
@@ -203,29 +207,27 @@ struct ProfScope {
 };
 
 
-// What the capability order needs (Alg. 1's argmax d_g: rank 0 = largest d_g, equal d_g by index).
-// It is made by a kernel of its own or by extra workgroups of the first kernel of a grouped
-// scoring pass (see launch_score).
-struct RankArgs {
-    const double* d;        // [M] d_g
+// What the class order needs (see gr_fleet).
+struct OrderArgs {
+    const unsigned long long* key;    // [m_pos] d_g as an integer that falls with it, by slot
     const float4* instK;    // [M] see gr_fleet
-    int *rank, *order;
+    const int* slot_inst;
+    const int2* run_cls;
+    int *order, *pos_of;
     float2* posK;
-    int* out_rank;          // may be null
-    int n_inst, m_pad;
+    unsigned long long* posKey;
+    uint4* run_head;
+    int m_pos;
 };
 
 // status.hip
 int status_prepare();
 int launch_ranks(gr_fleet* f, int* out_rank, hipStream_t s);
-RankArgs rank_args(const gr_fleet* f, int* out_rank);
 int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s);
 int launch_commit(gr_fleet* f, int64_t n, const int* inst, const int* ctx0, const int* pred_len, hipStream_t s);
 int launch_ema(gr_fleet* f, double w, const float* s_q, const float* s_p, const float* s_d, hipStream_t s);
 
 // score.hip
-size_t score_lds_bytes(const gr_fleet* f);
-int score_prepare(gr_fleet* f);
 int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& out, hipStream_t s,
                  bool small_batch_ok = false);
 int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream_t s);
@@ -270,55 +272,56 @@ __device__ inline int wave_incl_scan_i32(int v)
     return v;
 }
 
+// a double as an unsigned integer of the opposite order (both zeros alike, NaNs have a place too)
+__device__ inline unsigned long long falling_bits(double v)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v + 0.0);
+    return ~(b ^ ((b >> 63) ? ~0ull : 0x8000000000000000ull));
+}
+
 constexpr int kRankPer = 8;      // instances that kRankWaves waves rank together
 constexpr int kRankWaves = 4;
+static_assert(kMemoP % kRankPer == 0, "the instances ranked together are of one class");
 
-// Workgroup `wg` of kThreads threads of the capability order: the ranks of kThreads / 256 runs of
-// kRankPer instances,
+// Workgroup `wg` of kThreads threads of the class order: the ranks of kThreads / 256 runs of kRankPer
+// instances among those of their class,
 //   rank_g = #{h : d_h > d_g} + #{h < g : d_h = d_g},
-// and with them order[rank] = g and the prefill coefficients per position.  Four waves share a run
+// which place each instance behind its class's first position.  Four waves share the instances
 // and split the competitors, a lane per competitor, each lane with its own counts, added up over the
-// wave and then through LDS.  The time is that of the reads: the status build has just written d, so
-// each XCD fetches it from memory, and a wave that read its 4 096 competitors in four batches waited
-// four times.  A quarter of them is one batch.  On 4 096 instances 10.8 us with ballots added up by the scalar unit, 9.2 with a
-// wave per run, 5.9 us this way (and 7.3 + 3.8 us as two kernels that count with atomics and finish).
-// Competitors that lie wholly before or behind the run take one comparison each.
+// wave and then through LDS.  The time is that of the reads (the status build has just written d, so
+// each XCD fetches it from memory): a wave reads its share of the competitors in one batch.
 // Every thread of the workgroup must call it.  `sums`: kThreads / 64 * kRankPer ints of LDS.
 template <int kThreads>
-__device__ inline void rank_block(const RankArgs& a, int wg, int* sums)
+__device__ inline void order_block(const OrderArgs& a, int wg, int* sums)
 {
     constexpr int kRuns = kThreads / (kRankWaves * kWave);
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int quarter = wave % kRankWaves, g0 = (wg * kRuns + wave / kRankWaves) * kRankPer;
-    if (g0 < a.n_inst) {
-        double dg[kRankPer];
+    const int quarter = wave % kRankWaves, s0 = (wg * kRuns + wave / kRankWaves) * kRankPer;
+    const int s = s0 + lane;
+    int first = 0, cnt = 0, g = -1;
+    float4 k{};
+    unsigned long long own = 0;
+    if (s0 < a.m_pos) {
+        const int2 rc = a.run_cls[s0 / kMemoP];
+        first = rc.x; cnt = rc.y;
+        if (quarter == 0 && lane < kRankPer && s < first + cnt) { g = a.slot_inst[s]; k = a.instK[g]; own = a.key[s]; }
+        unsigned long long dg[kRankPer];
         int r[kRankPer] = {};
 #pragma unroll
-        for (int j = 0; j < kRankPer; ++j) dg[j] = a.d[min(g0 + j, a.n_inst - 1)];
-        constexpr int kAhead = 16;
-        const int per = ((a.n_inst + kRankWaves - 1) / kRankWaves + kWave - 1) / kWave * kWave;
-        const int h_end = min((quarter + 1) * per, a.n_inst);
+        for (int j = 0; j < kRankPer; ++j) dg[j] = a.key[s0 + j];
+        constexpr int kAhead = 8;
+        const int per = ((cnt + kRankWaves - 1) / kRankWaves + kWave - 1) / kWave * kWave;
+        const int h_end = min((quarter + 1) * per, cnt), mine = s0 - first;
         for (int h0 = quarter * per; h0 < h_end; h0 += kAhead * kWave) {
-            double dh[kAhead];
+            unsigned long long dh[kAhead];
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) dh[k] = a.key[first + min(h0 + k * kWave + lane, h_end - 1)];
 #pragma unroll
             for (int k = 0; k < kAhead; ++k) {
                 const int h = h0 + k * kWave + lane;
-                dh[k] = h < h_end ? a.d[h] : -__builtin_inf();      // ahead of nobody
-            }
 #pragma unroll
-            for (int k = 0; k < kAhead; ++k) {
-                const int hb = h0 + k * kWave;
-                if (hb >= h_end) break;
-                if (hb + kWave <= g0) {
-#pragma unroll
-                    for (int j = 0; j < kRankPer; ++j) r[j] += dh[k] >= dg[j];
-                } else if (hb >= g0 + kRankPer) {
-#pragma unroll
-                    for (int j = 0; j < kRankPer; ++j) r[j] += dh[k] > dg[j];
-                } else {
-#pragma unroll
-                    for (int j = 0; j < kRankPer; ++j) r[j] += dh[k] > dg[j] || (dh[k] == dg[j] && hb + lane < g0 + j);
-                }
+                for (int j = 0; j < kRankPer; ++j)
+                    r[j] += h < h_end && (dh[k] < dg[j] || (dh[k] == dg[j] && h < mine + j));
             }
         }
 #pragma unroll
@@ -328,29 +331,28 @@ __device__ inline void rank_block(const RankArgs& a, int wg, int* sums)
         }
     }
     __syncthreads();
-    if (quarter != 0 || lane >= kRankPer) return;
-    const int g = g0 + lane;
-    if (g < a.n_inst) {
-        int r = 0;
+    if (quarter != 0 || lane >= kRankPer || s >= a.m_pos) return;
+    if (s < first + cnt) {
+        int p = first;
 #pragma unroll
-        for (int q = 0; q < kRankWaves; ++q) r += sums[(wave + q) * kRankPer + lane];
-        if ((unsigned)r >= (unsigned)a.n_inst) return;      // (counts are below n_inst by construction; never index past the tables)
-        const float4 k = a.instK[g];
-        a.rank[g] = r;
-        a.order[r] = g;
-        a.posK[r] = make_float2(k.x, k.y);
-        if (a.out_rank) a.out_rank[g] = r;
-    } else if (g < a.m_pad) {
-        a.order[g] = -1;     // positions past the last instance
-        a.posK[g] = make_float2(0.f, 0.f);
+        for (int q = 0; q < kRankWaves; ++q) p += sums[(wave + q) * kRankPer + lane];
+        a.pos_of[g] = p;
+        a.order[p] = g;
+        a.posK[p] = make_float2(k.x, k.y);
+        a.posKey[p] = own;
+        if (p % kMemoP == 0) a.run_head[p / kMemoP] = make_uint4((uint32_t)own, (uint32_t)(own >> 32), (uint32_t)g, 0u);
+    } else {
+        a.order[s] = -1;     // positions past the last instance of the class
+        a.posK[s] = make_float2(__builtin_inff(), 0.f);
+        a.posKey[s] = ~0ull;
     }
 }
 
-// Workgroups of kThreads threads that rank every instance (and fill the padded positions).
-constexpr int rank_blocks(int m_pad, int threads)
+// Workgroups of kThreads threads that place every instance (and fill the padded positions).
+constexpr int order_blocks(int m_pos, int threads)
 {
     const int per = threads / (kRankWaves * kWave) * kRankPer;
-    return (m_pad + per - 1) / per;
+    return (m_pos + per - 1) / per;
 }
 
 }  // namespace gr

@@ -36,9 +36,14 @@ struct BuildArgs {
     int* act_inst;
     float4* instK;
     uint16_t* tabS;
+    const int* slot_of;
+    unsigned long long* slot_key;
     int* counters;
     int64_t n_active, n_queued;
     int n_inst, max_entries, max_len;
+    // for the migration pass of a risk scan: which lengths flagged requests have, and how many are flagged
+    uint8_t* seen;
+    int* late_cnt;
     // requests routed since the caller's status (feedback routing): per instance, queued behind the queue
     int* pend_cnt;
     const int *pend_prompt, *pend_len;
@@ -299,13 +304,18 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
     const bool blended = a.lam != 0.0;
     const double keep = 1.0 - a.lam;
     const double bq = blended ? a.emaQ[g] : 0.0, bp = blended ? a.emaP[g] : 0.0, bd = blended ? a.emaD[g] : 0.0;
+    int n_late = 0;
     // what a request of the instance is told: entry i, white-box finish time, its length and context as given
     auto report = [&](int i, double fin, double len0, double ctx0) {
         if (blended)   // black-box finish: d per remaining token; a queued request also waits and prefills
             fin = keep * fin + a.lam * (i < A ? bd * len0 : (bq + bp * ctx0) + bd * len0);
         if (i < A) {
             a.out_act_finish[a0 + i] = (float)fin;
-            if (a.act_budget) a.out_flag[a0 + i] = fin > (double)a.act_budget[a0 + i];
+            if (a.act_budget) {
+                const bool late = fin > (double)a.act_budget[a0 + i];
+                a.out_flag[a0 + i] = late;
+                if (late) { a.seen[(int)len0] = 1; ++n_late; }
+            }
         } else if (a.out_q_finish && i < A + Q) {
             a.out_q_finish[q0 + i - A] = (float)fin;
         }
@@ -494,7 +504,9 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
                     dstGH[slot] = make_float2(0.f, 0.f);
                 }
             }
+            if (a.act_budget) n_late = wave_sum(n_late);
             if (lane == 0) {
+                if (a.act_budget) a.late_cnt[g] = n_late;
                 const double Cd = (double)((Ctot - Pstar) + (long long)Nleft * s64);
                 double Gq0 = q_adm, H0 = cc.alpha + (cc.beta * (double)(Nleft + 1) + cc.gamma * Cd);
                 if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
@@ -507,6 +519,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
                                           : fma(cc.gamma, (double)Ctot, fma(cc.beta, (double)Nrun, cc.alpha));
                 if (blended) d = keep * d + a.lam * bd;
                 a.hD[g] = d;
+                a.slot_key[a.slot_of[g]] = falling_bits(d);
                 if (a.out_d) a.out_d[g] = d;
             }
             return;
@@ -565,7 +578,9 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
         }
         store_splitter<kCap>(a.tabS, g, lane * kEPL + kEPL - 1, tR[kEPL - 1]);
     }
+    if (a.act_budget) n_late = wave_sum(n_late);
     if (lane == 0) {
+        if (a.act_budget) a.late_cnt[g] = n_late;
         const double Cd = (double)Ctot;
         double Gq0 = q, H0 = cc.alpha + (cc.beta * (double)(Nrun + 1) + cc.gamma * Cd);
         if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
@@ -577,6 +592,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
         double d = d_first >= 0.0 ? d_first : fma(cc.gamma, Cd, fma(cc.beta, (double)Nrun, cc.alpha));
         if (blended) d = keep * d + a.lam * bd;
         a.hD[g] = d;
+        a.slot_key[a.slot_of[g]] = falling_bits(d);
         if (a.out_d) a.out_d[g] = d;
     }
 }
@@ -840,6 +856,19 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
     if (a.act_budget) {
 #pragma unroll
         for (int r = 0; r < kEPL; ++r) flag_lds[idx[r]] = (uint8_t)((late >> r) & 1u);
+        // the lengths of flagged requests, for the migration pass (a byte each; of equal neighbours in
+        // the sorted order one is enough), and how many there are
+        unsigned mig = 0;
+#pragma unroll
+        for (int r = 0; r < kEPL; ++r) mig |= (unsigned)(r < mine && idx[r] < A) << r;
+        mig &= late;
+#pragma unroll
+        for (int r = 0; r < kEPL; ++r) {
+            const bool again = r + 1 < kEPL && ((mig >> (r + 1)) & 1u) && Ri[r + 1 < kEPL ? r + 1 : r] == Ri[r];
+            if (((mig >> r) & 1u) && !again) a.seen[Ri[r]] = 1;
+        }
+        const int n_late = wave_incl_scan_i32(__popc(mig));
+        if (lane == kWave - 1) a.late_cnt[part * a.n_inst + g] = n_late;
     }
     if constexpr (kSplit == 1) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -897,16 +926,65 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
         double d = fma(cc.gamma, Ctot, fma(cc.beta, (double)N, cc.alpha));     // the next decode step
         if (blended) d = keep * d + a.lam * bd;
         a.hD[g] = d;
+        a.slot_key[a.slot_of[g]] = falling_bits(d);
         if (a.out_d) a.out_d[g] = d;
     }
 }
 
-// Capability order of Alg. 1's argmax d_g as a kernel of its own (see common.h; a grouped scoring
-// pass normally makes it in extra workgroups of its first kernel).
-__global__ __launch_bounds__(kBlock) void k_rank(RankArgs a)
+// The capability rank of every instance, for the caller (Alg. 1's argmax d_g: rank 0 = largest d_g,
+// equal d_g by index).  Four waves share a run of kRankPer instances and split the competitors, a
+// lane per competitor, each lane with its own counts.  The time is that of the reads: the status
+// build has just written d, so each XCD fetches it from memory, and a wave that read its 4 096
+// competitors in four batches waited four times.  A quarter of them is one batch.  On 4 096
+// instances 10.8 us with ballots added up by the scalar unit, 9.2 with a wave per run, 5.9 us this way.
+// Competitors that lie wholly before or behind the run take one comparison each.
+__global__ __launch_bounds__(kBlock) void k_rank(const double* __restrict__ d, int* __restrict__ out_rank, int n_inst)
 {
-    __shared__ int sums[kBlock / kWave * kRankPer];
-    rank_block<kBlock>(a, blockIdx.x, sums);
+    static_assert(kBlock == kRankWaves * kWave, "a workgroup ranks one run");
+    __shared__ int sums[kRankWaves * kRankPer];
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int g0 = blockIdx.x * kRankPer;
+    double dg[kRankPer];
+    int r[kRankPer] = {};
+#pragma unroll
+    for (int j = 0; j < kRankPer; ++j) dg[j] = d[min(g0 + j, n_inst - 1)];
+    constexpr int kAhead = 16;
+    const int per = ((n_inst + kRankWaves - 1) / kRankWaves + kWave - 1) / kWave * kWave;
+    const int h_end = min((wave + 1) * per, n_inst);
+    for (int h0 = wave * per; h0 < h_end; h0 += kAhead * kWave) {
+        double dh[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const int h = h0 + k * kWave + lane;
+            dh[k] = h < h_end ? d[h] : -__builtin_inf();      // ahead of nobody
+        }
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const int hb = h0 + k * kWave;
+            if (hb >= h_end) break;
+            if (hb + kWave <= g0) {
+#pragma unroll
+                for (int j = 0; j < kRankPer; ++j) r[j] += dh[k] >= dg[j];
+            } else if (hb >= g0 + kRankPer) {
+#pragma unroll
+                for (int j = 0; j < kRankPer; ++j) r[j] += dh[k] > dg[j];
+            } else {
+#pragma unroll
+                for (int j = 0; j < kRankPer; ++j) r[j] += dh[k] > dg[j] || (dh[k] == dg[j] && hb + lane < g0 + j);
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kRankPer; ++j) {
+        const int all = wave_incl_scan_i32(r[j]);
+        if (lane == kWave - 1) sums[wave * kRankPer + j] = all;
+    }
+    __syncthreads();
+    if (wave != 0 || lane >= kRankPer || g0 + lane >= n_inst) return;
+    int all = 0;
+#pragma unroll
+    for (int q = 0; q < kRankWaves; ++q) all += sums[q * kRankPer + lane];
+    out_rank[g0 + lane] = all;
 }
 
 // One step of the exponential moving average of Alg. 1, q <- w * sample + (1 - w) * q, for
@@ -1072,21 +1150,22 @@ constexpr size_t lean_lds() { return (size_t)kBuildWaves * lean_inst_words(kWave
 constexpr int kSimds = 1024;      // 256 compute units of four
 
 template <int kEPL, int kSplit>
-void launch_build_split(const BuildArgs& b, int M, hipStream_t s)
+int launch_build_split(const BuildArgs& b, int M, hipStream_t s)
 {
     constexpr size_t lds = split_lds<kEPL, kSplit>();
     hipLaunchKernelGGL((k_build_lean<kEPL / kSplit, kSplit>), dim3(M), dim3(kSplit * kWave), lds, s, b);
+    return kSplit;
 }
 
-// kEPL: sort words per lane if one wave takes an instance
+// kEPL: sort words per lane if one wave takes an instance.  Returns the waves that share an instance.
 template <int kEPL>
-void launch_build(const BuildArgs& b, int M, hipStream_t s)
+int launch_build(const BuildArgs& b, int M, hipStream_t s)
 {
     const dim3 grid((M + kBuildWaves - 1) / kBuildWaves);
     const size_t lds = (size_t)kBuildWaves * kWave * kEPL * sizeof(int);
     if (b.batch_cap) {
         hipLaunchKernelGGL((k_build_capped<kEPL>), grid, dim3(kBlock), 3 * lds, s, b);
-        return;
+        return 1;
     }
     // fewer instances than the chip takes waves at four per SIMD: several waves per instance
     // (measured on 1 024 instances x 1 000 requests: 19.8 us with one wave each, 17.7 with two, 16.0 with
@@ -1095,6 +1174,7 @@ void launch_build(const BuildArgs& b, int M, hipStream_t s)
     if constexpr (kEPL >= 4) if (room >= 4) return launch_build_split<kEPL, 4>(b, M, s);
     if constexpr (kEPL >= 2) if (room >= 2) return launch_build_split<kEPL, 2>(b, M, s);
     hipLaunchKernelGGL((k_build_lean<kEPL, 1>), grid, dim3(kBlock), lean_lds<kEPL>(), s, b);
+    return 1;
 }
 
 }  // namespace
@@ -1149,25 +1229,13 @@ int status_prepare()
     return ok ? GR_OK : GR_ERR_HIP;
 }
 
-RankArgs rank_args(const gr_fleet* f, int* out_rank)
-{
-    RankArgs r{};
-    r.d = f->hD; r.instK = f->instK;
-    r.rank = f->rank; r.order = f->order; r.posK = f->posK; r.out_rank = out_rank;
-    r.n_inst = f->n_inst; r.m_pad = f->m_pad;
-    return r;
-}
-
 int launch_ranks(gr_fleet* f, int* out_rank, hipStream_t s)
 {
-    const RankArgs r = rank_args(f, out_rank);
     {
         ProfScope ps(f, kRank, s);
-        hipLaunchKernelGGL(k_rank, dim3(rank_blocks(f->m_pad, kBlock)), dim3(kBlock), 0, s, r);
+        hipLaunchKernelGGL(k_rank, dim3((f->n_inst + kRankPer - 1) / kRankPer), dim3(kBlock), 0, s, f->hD, out_rank, f->n_inst);
     }
-    if (hipGetLastError() != hipSuccess) return GR_ERR_HIP;
-    f->ranks_current = true;
-    return GR_OK;
+    return hipGetLastError() == hipSuccess ? GR_OK : GR_ERR_HIP;
 }
 
 int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s)
@@ -1181,27 +1249,30 @@ int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s)
     b.cls = f->cls; b.inst_class = f->inst_class;
     b.tabR = f->tabR; b.tabGH = f->tabGH; b.headGH = f->headGH;
     b.hN = f->hN; b.hD = f->hD; b.act_inst = f->act_inst;
-    b.instK = f->instK; b.tabS = f->tabS; b.counters = f->counters;
+    b.instK = f->instK; b.tabS = f->tabS; b.slot_of = f->slot_of; b.slot_key = f->slot_key; b.counters = f->counters;
     b.n_active = in.n_active; b.n_queued = in.n_queued;
     b.n_inst = f->n_inst; b.max_entries = f->max_entries; b.max_len = f->max_len;
+    b.seen = f->seen; b.late_cnt = f->late_cnt;
     b.pend_cnt = f->pend_cnt; b.pend_prompt = f->pend_prompt; b.pend_len = f->pend_len;
     b.use_pending = in.use_pending;
     b.pend_touched = f->pend_touched; b.only_touched = in.use_pending && in.only_touched;
     b.batch_cap = f->has_cap ? f->batch_cap : nullptr;
     b.lam = f->lam; b.emaQ = f->emaQ; b.emaP = f->emaP; b.emaD = f->emaD;
     const int M = f->n_inst;
+    int parts = 1;
     {
         ProfScope ps(f, kBuild, s);
         switch (f->epl) {
-            case 1: launch_build<1>(b, M, s); break;
-            case 2: launch_build<2>(b, M, s); break;
-            case 4: launch_build<4>(b, M, s); break;
-            case 8: launch_build<8>(b, M, s); break;
-            case 16: launch_build<16>(b, M, s); break;
-            default: launch_build<32>(b, M, s); break;
+            case 1: parts = launch_build<1>(b, M, s); break;
+            case 2: parts = launch_build<2>(b, M, s); break;
+            case 4: parts = launch_build<4>(b, M, s); break;
+            case 8: parts = launch_build<8>(b, M, s); break;
+            case 16: parts = launch_build<16>(b, M, s); break;
+            default: parts = launch_build<32>(b, M, s); break;
         }
     }
-    // the capability order: now if the caller wants to see it, else with the next scoring pass
+    if (in.act_budget) f->late_parts = parts;
+    // the class order is made by the next scoring pass that needs it
     f->ranks_current = false;
     f->lam_built = f->lam;
     if (in.out_rank) {
