@@ -346,32 +346,6 @@ __device__ inline float from_ordered_bits(uint32_t u)
     return __uint_as_float(u ^ ((u >> 31) ? 0x80000000u : 0xFFFFFFFFu));
 }
 
-template <int kCtrl, int kRowMask>
-__device__ inline uint32_t min_dpp(uint32_t v)      // (all ones where the lane has no source)
-{
-    return min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, kCtrl, kRowMask, 0xf, false));
-}
-
-// The least value over the wave, or over the lane's row of 16 (kRow), for every lane.
-template <bool kRow>
-__device__ inline uint32_t min_over(uint32_t v)
-{
-    if constexpr (kRow) {
-        v = min_dpp<0x128, 0xf>(v);      // row_ror 8, 4, 2, 1
-        v = min_dpp<0x124, 0xf>(v);
-        v = min_dpp<0x122, 0xf>(v);
-        return min_dpp<0x121, 0xf>(v);
-    } else {
-        v = min_dpp<0x111, 0xf>(v);      // row_shr 1, 2, 4, 8
-        v = min_dpp<0x112, 0xf>(v);
-        v = min_dpp<0x114, 0xf>(v);
-        v = min_dpp<0x118, 0xf>(v);
-        v = min_dpp<0x142, 0xa>(v);      // row_bcast 15 into rows 1 and 3, 31 into rows 2 and 3
-        v = min_dpp<0x143, 0xc>(v);
-        return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
-    }
-}
-
 // ------------------------------------------------------------------ Alg. 1, runs first
 // kappa = delta + gamma * L, the same instruction wherever a pair's latency is formed
 __device__ inline float kappa_of(float2 dg, float Lf) { return fmaf(dg.y, Lf, dg.x); }

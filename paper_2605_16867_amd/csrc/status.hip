@@ -213,11 +213,41 @@ __device__ __forceinline__ void store_splitter(uint16_t* tabS, int g, int v, uin
     if ((v + 1) % kStride == 0) tabS[(size_t)g * kSplit + v / kStride] = len;
 }
 
+// v of the lane `ctrl` names (0 where there is none or the row is masked out), both halves
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ long long dpp_or_zero_i64(long long v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)v, kCtrl, kRowMask, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), kCtrl, kRowMask, 0xf, false);
+    return ((long long)hi << 32) | (unsigned)lo;
+}
+
+// Inclusive prefix sum over the lanes of a wave (see wave_incl_scan_i32 for the pattern).
+__device__ __forceinline__ long long wave_incl_scan_i64(long long v)
+{
+    v += dpp_or_zero_i64<0x111, 0xf>(v);   // row_shr:1
+    v += dpp_or_zero_i64<0x112, 0xf>(v);   // row_shr:2
+    v += dpp_or_zero_i64<0x114, 0xf>(v);   // row_shr:4
+    v += dpp_or_zero_i64<0x118, 0xf>(v);   // row_shr:8
+    v += dpp_or_zero_i64<0x142, 0xa>(v);   // row_bcast:15 into rows 1, 3
+    v += dpp_or_zero_i64<0x143, 0xc>(v);   // row_bcast:31 into rows 2, 3
+    return v;
+}
+
+// The last lane's value: of a prefix sum, the total.
+__device__ __forceinline__ long long last_lane_i64(long long v)
+{
+    const int lo = __builtin_amdgcn_readlane((int)v, kWave - 1), hi = __builtin_amdgcn_readlane((int)(v >> 32), kWave - 1);
+    return ((long long)hi << 32) | (unsigned)lo;
+}
+
+__device__ __forceinline__ long long wave_sum_i64(long long v) { return last_lane_i64(wave_incl_scan_i64(v)); }
+
 // Exclusive prefix over the lanes of a wave, and the total.
 __device__ __forceinline__ long long wave_excl_scan(long long v, long long& total)
 {
-    const long long incl = wave_incl_scan(v);
-    total = __shfl(incl, kWave - 1, kWave);
+    const long long incl = wave_incl_scan_i64(v);
+    total = last_lane_i64(incl);
     return incl - v;
 }
 
@@ -226,7 +256,15 @@ constexpr int kBuildWaves = kBlock / kWave;
 constexpr int log2_of(int v) { return v <= 1 ? 0 : 1 + log2_of(v / 2); }
 
 // The build under batch caps (a kernel of its own: the event loop's registers would cost the
-// plain build, k_build_lean below, a wave per SIMD).
+// plain build, k_build_lean below, a wave per SIMD).  The loop over the events is one chain, so what
+// bounds the kernel is the length of a turn: the next departure is found and the sums are formed
+// without leaving the registers (DPP; through the LDS crossbar each step of a reduction waited
+// for the one before it, and a turn had thirty-six), finish times go to LDS and reach the caller's
+// arrays in entry order at the end, where a budget is also read (in the loop its read stood in
+// the chain).  And as long as
+// nobody can be admitted nothing is played at all.  1 024 instances of 200 running and 40 queued
+// requests, caps of 120 to 288: 94 us, 54 with the shorter turns, 32 without the turns before the
+// first admission.
 template <int kEPL>
 __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
 {
@@ -242,9 +280,11 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
         if (lane == 0 && touched) a.pend_touched[g] = 0;
         if (a.only_touched && !touched) return;
     }
-    int* ctx = reinterpret_cast<int*>(smem) + wave * 3 * kCap;  // this wave's contexts, by entry index
-    int* olen = ctx + kCap;    // under a batch cap: length and context as given (ctx then holds them
-    int* octx = olen + kCap;   // as they are when a newcomer would be admitted)
+    // this wave's entries, by index: white-box finish times (none yet: -1), and contexts (once the
+    // events have been played, as they are when a newcomer would be admitted)
+    double* fin_lds = reinterpret_cast<double*>(smem) + wave * kCap;
+    int* ctx = reinterpret_cast<int*>(reinterpret_cast<double*>(smem) + kBuildWaves * kCap) + wave * kCap;
+    constexpr double kNoFinish = -1.0;
 
     const ClassCoef cc = a.cls[a.inst_class[g]];
     // offsets are clamped into the arrays, so broken CSR data cannot index outside them
@@ -288,8 +328,10 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
             if (i >= A) qsum += c;
             if (rem < 0 || rem > a.max_len) { rem = min(max(rem, 0), a.max_len); status |= GR_DEV_LEN_CLAMPED; }
             word = ((uint32_t)rem << kIdxBits) | (uint32_t)i;
-            ctx[i] = c;
+            c_in[r] = c;
         }
+        ctx[i] = c_in[r];
+        fin_lds[i] = kNoFinish;
         key[r] = word;
     }
     // (stores on their own: a store between two uses of loaded words would make the second wait for it)
@@ -297,27 +339,45 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
     for (int r = 0; r < kEPL; ++r)
         if (r * kWave + lane < A) a.act_inst[a0 + r * kWave + lane] = g;
     if (status) atomicOr(&a.counters[0], status);
-    if (Q + P > 0) qsum = wave_sum(qsum);   // Q and P are the same in every lane
+    if (Q + P > 0) qsum = wave_sum_i64(qsum);   // Q and P are the same in every lane
     double q = cc.delta * (double)qsum;
 
     // with a blend, every estimate below is keep * (white-box value) + lam * (Eq. 2 with the smoothed status)
     const bool blended = a.lam != 0.0;
     const double keep = 1.0 - a.lam;
     const double bq = blended ? a.emaQ[g] : 0.0, bp = blended ? a.emaP[g] : 0.0, bd = blended ? a.emaD[g] : 0.0;
-    int n_late = 0;
-    // what a request of the instance is told: entry i, white-box finish time, its length and context as given
-    auto report = [&](int i, double fin, double len0, double ctx0) {
-        if (blended)   // black-box finish: d per remaining token; a queued request also waits and prefills
-            fin = keep * fin + a.lam * (i < A ? bd * len0 : (bq + bp * ctx0) + bd * len0);
-        if (i < A) {
-            a.out_act_finish[a0 + i] = (float)fin;
-            if (a.act_budget) {
-                const bool late = fin > (double)a.act_budget[a0 + i];
-                a.out_flag[a0 + i] = late;
-                if (late) { a.seen[(int)len0] = 1; ++n_late; }
+    // what a request of the instance is told, at the end and in entry order
+    const auto report_all = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        int n_late = 0;
+#pragma unroll 4
+        for (int r = 0; r < kEPL; ++r) {
+            const int i = r * kWave + lane;
+            double fin = fin_lds[i];
+            if (i >= A + Q || fin == kNoFinish) continue;
+            // (length and prompt as given are read again: kept through the events they would spill)
+            const float bud = a.act_budget && i < A ? a.act_budget[a0 + i] : 0.f;
+            int rem = 0;
+            if (a.act_budget || blended) rem = min(max(i < A ? a.act_rem[a0 + i] : a.q_len[q0 + i - A], 0), a.max_len);
+            if (blended)   // black-box finish: d per remaining token; a queued request also waits and prefills
+                fin = keep * fin + a.lam * (i < A ? bd * (double)rem
+                                                  : (bq + bp * (double)a.q_prompt[q0 + i - A]) + bd * (double)rem);
+            if (i < A) {
+                a.out_act_finish[a0 + i] = (float)fin;
+                if (a.act_budget) {
+                    const bool late = fin > (double)bud;
+                    a.out_flag[a0 + i] = late;
+                    if (late) { a.seen[rem] = 1; ++n_late; }
+                }
+            } else if (a.out_q_finish) {
+                a.out_q_finish[q0 + i - A] = (float)fin;
             }
-        } else if (a.out_q_finish && i < A + Q) {
-            a.out_q_finish[q0 + i - A] = (float)fin;
+        }
+        if (a.act_budget) {
+            n_late = wave_incl_scan_i32(n_late);
+            if (lane == kWave - 1) a.late_cnt[g] = n_late;
         }
     };
 
@@ -338,17 +398,73 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
 #pragma unroll
         for (int r = 0; r < kEPL; ++r) {
             const int i = r * kWave + lane;
-            const int len0 = i < N ? (int)(key[r] >> kIdxBits) : 0, c0 = i < N ? ctx[i] : 0;
+            const int len0 = i < N ? (int)(key[r] >> kIdxBits) : 0;
             fstep[r] = i < A ? len0 : (i < N ? 0x7fffffff : 0);     // queued: not in yet; none: gone
-            cbase[r] = c0;
-            if (i < N) { olen[i] = len0; octx[i] = c0; }
+            cbase[r] = ctx[i];
         }
         long long C = 0;
 #pragma unroll
         for (int r = 0; r < kEPL; ++r) C += r * kWave + lane < A ? cbase[r] : 0;
-        C = wave_sum(C);
+        C = wave_sum_i64(C);
         int n = A, s = 0, next_q = A;     // batch size, steps done, next entry of the queue
         double t = 0.0;
+        // More running than the cap allows: nobody is admitted until enough of them have left, and up to
+        // then every finish time is the closed form over the sorted lengths: the turns of the loop
+        // below start with the first admission.  (An entry without a token left is the loop's business.)
+        if (A >= cap_g && A < N) {
+            uint32_t run[kEPL];
+#pragma unroll
+            for (int r = 0; r < kEPL; ++r) run[r] = r * kWave + lane < A ? key[r] : 0xFFFFFFFFu;
+            bitonic_sort<kEPL>(run, lane);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            int R[kEPL], cx[kEPL];
+            long long yl = 0, xl = 0, cl = 0;
+#pragma unroll
+            for (int r = 0; r < kEPL; ++r) {
+                const bool valid = lane * kEPL + r < A;
+                R[r] = valid ? (int)(run[r] >> kIdxBits) : 0;
+                cx[r] = valid ? ctx[run[r] & kIdxMask] : 0;
+                yl += R[r];
+                xl += (long long)cx[r] * R[r] + (long long)(R[r] * (R[r] - 1) / 2);
+                cl += cx[r];
+            }
+            if (__builtin_amdgcn_readfirstlane(R[0]) > 0) {
+                long long Y, X, Pc, Ctot;
+                Y = wave_excl_scan(yl, Ctot); X = wave_excl_scan(xl, Ctot); Pc = wave_excl_scan(cl, Ctot);
+                const int leave = A - cap_g + 1;      // departures until there is room
+                int step = 0;
+#pragma unroll
+                for (int r = 0; r < kEPL; ++r)
+                    if (lane * kEPL + r == leave - 1) step = R[r];
+                step = __shfl(step, (leave - 1) / kEPL, kWave);
+                double t_at = 0.0;
+                int gone = 0;
+                long long goneC = 0;
+#pragma unroll
+                for (int r = 0; r < kEPL; ++r) {
+                    const int v = lane * kEPL + r;
+                    const long long Rr = R[r], triR = (long long)(R[r] * (R[r] - 1) / 2);
+                    Y += Rr; X += (long long)cx[r] * Rr + triR; Pc += cx[r];
+                    if (v < A && R[r] <= step) {
+                        const double n_after = (double)(A - v - 1), S_next = (double)(Ctot - Pc), Rd = (double)Rr;
+                        const double I1 = (double)Y + n_after * Rd;
+                        const double I2 = (double)X + Rd * S_next + n_after * (double)triR;
+                        const double fin = fma(cc.gamma, I2, fma(cc.beta, I1, cc.alpha * Rd));
+                        fin_lds[run[r] & kIdxMask] = fin;
+                        if (v == leave - 1) t_at = fin;
+                        ++gone;
+                        goneC += cx[r];
+                    }
+                }
+                d_first = fma(cc.gamma, (double)C, fma(cc.beta, (double)n, cc.alpha));
+                t = __shfl(t_at, (leave - 1) / kEPL, kWave);
+                s = step;
+                n -= (int)wave_sum_i64(gone);
+                C += (long long)n * s - wave_sum_i64(goneC);
+            }
+        }
         for (int guard = 0; guard <= 2 * N + 2; ++guard) {
             const int k = min(cap_g - n, N - next_q);
             if (k > 0) {                   // admit entries next_q .. next_q + k - 1: prefill, then into the batch
@@ -362,38 +478,37 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
                         cbase[r] -= s;
                     }
                 }
-                sumP = wave_sum(sumP);
+                sumP = wave_sum_i64(sumP);
                 t += cc.delta * (double)sumP;
                 n += k; C += sumP; next_q += k;
             }
             if (next_q == N) break;        // the queue is empty: what follows is departures only (below)
             // next departure
-            int smin = 0x7fffffff;
+            uint32_t smin = 0x7fffffff;
 #pragma unroll
-            for (int r = 0; r < kEPL; ++r) smin = min(smin, fstep[r] > s ? fstep[r] : 0x7fffffff);
-#pragma unroll
-            for (int dlt = kWave / 2; dlt > 0; dlt >>= 1) smin = min(smin, __shfl_xor(smin, dlt, kWave));
-            if (smin == 0x7fffffff) break;            // (nobody is running: cannot be, the batch has room then)
+            for (int r = 0; r < kEPL; ++r) smin = min(smin, fstep[r] > s ? (uint32_t)fstep[r] : 0x7fffffffu);
+            smin = min_over<false>(smin);
+            if (smin == 0x7fffffffu) break;           // (nobody is running: cannot be, the batch has room then)
             const double step_now = fma(cc.gamma, (double)C, fma(cc.beta, (double)n, cc.alpha));
             if (d_first < 0.0) d_first = step_now;
-            const long long ks = smin - s;
+            const long long ks = (int)smin - s;
             // ks steps of a fixed batch: contexts grow by one per member and step
             t += (double)ks * step_now + cc.gamma * ((double)n * (double)(ks * (ks - 1) / 2));
             C += (long long)n * ks;
-            s = smin;
+            s = (int)smin;
             int gone = 0;
             long long goneC = 0;
 #pragma unroll
             for (int r = 0; r < kEPL; ++r) {
-                if (fstep[r] == s) {
-                    const int i = r * kWave + lane;
-                    ++gone;
+                const bool leaves = fstep[r] == s;
+                if (leaves) {
                     goneC += cbase[r] + s;
-                    report(i, t, (double)olen[i], (double)octx[i]);
+                    fin_lds[r * kWave + lane] = t;
                 }
+                gone += __popcll(__ballot(leaves));
             }
-            n -= wave_sum(gone);
-            C -= wave_sum(goneC);
+            n -= gone;
+            C -= wave_sum_i64(goneC);
         }
         // what is left, as of now: the sort words and contexts the closed form is built from
         q = t;
@@ -453,7 +568,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
                     const double I1 = (double)Y1 + n_after * Rd;
                     const double I2 = (double)X1 + Rd * S_next + n_after * (double)triR;
                     const double fin = q + fma(cc.gamma, I2, fma(cc.beta, I1, cc.alpha * Rd));
-                    report(idx[r], fin, (double)olen[idx[r]], (double)octx[idx[r]]);
+                    fin_lds[idx[r]] = fin;
                     if (v == kstar - 1) { q_adm = fin; sstar = R[r]; }
                 }
             }
@@ -468,8 +583,8 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
                     ++gone; yg += R[r]; cg += cx[r];
                     xg += (long long)cx[r] * R[r] + (long long)(R[r] * (R[r] - 1) / 2);
                 }
-            const int vstar = (int)wave_sum(gone);
-            const long long Ystar = wave_sum(yg), Xstar = wave_sum(xg), Pstar = wave_sum(cg);
+            const int vstar = (int)wave_sum_i64(gone);
+            const long long Ystar = wave_sum_i64(yg), Xstar = wave_sum_i64(xg), Pstar = wave_sum_i64(cg);
             const int Nleft = Nrun - vstar;
             const long long s64 = sstar, tri_s = s64 * (s64 - 1) / 2;
             Y1 = Y; X1 = X; P1 = Pc;
@@ -504,9 +619,8 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
                     dstGH[slot] = make_float2(0.f, 0.f);
                 }
             }
-            if (a.act_budget) n_late = wave_sum(n_late);
+            report_all();
             if (lane == 0) {
-                if (a.act_budget) a.late_cnt[g] = n_late;
                 const double Cd = (double)((Ctot - Pstar) + (long long)Nleft * s64);
                 double Gq0 = q_adm, H0 = cc.alpha + (cc.beta * (double)(Nleft + 1) + cc.gamma * Cd);
                 if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
@@ -551,7 +665,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
             const double I1 = Yd + n_after * Rd;
             const double I2 = Xd + Rd * S_next + n_after * (double)triR;
             const double fin = q + fma(cc.gamma, I2, fma(cc.beta, I1, cc.alpha * Rd));
-            report(idx[r], fin, capped ? (double)olen[idx[r]] : Rd, capped ? (double)octx[idx[r]] : (double)cx[r]);
+            fin_lds[idx[r]] = fin;
         }
     }
     {
@@ -578,9 +692,8 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
         }
         store_splitter<kCap>(a.tabS, g, lane * kEPL + kEPL - 1, tR[kEPL - 1]);
     }
-    if (a.act_budget) n_late = wave_sum(n_late);
+    report_all();
     if (lane == 0) {
-        if (a.act_budget) a.late_cnt[g] = n_late;
         const double Cd = (double)Ctot;
         double Gq0 = q, H0 = cc.alpha + (cc.beta * (double)(Nrun + 1) + cc.gamma * Cd);
         if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
