@@ -45,6 +45,10 @@ constexpr int kMemoP = 16;         // positions of a run of the class order
 // Splitters of an instance's sorted lengths, by table size (strides of 8, 8, 16, 32, 32, 64 lengths).
 constexpr int split_count(int cap) { return cap <= 64 ? 8 : cap <= 512 ? 16 : 32; }
 
+// Where the pair (Gq, H) of instance g's segment k = 0 .. cap is kept: segment 1, the first of the
+// sorted entries, at a multiple of 16 bytes.
+__host__ __device__ constexpr size_t gh_at(int g, int k, int cap) { return (size_t)g * (cap + 2) + 1 + k; }
+
 struct ClassCoef {
     double delta, alpha, beta, gamma;
 };
@@ -133,8 +137,7 @@ struct gr_fleet {
     // per-instance tables written by the status build
     // E_g(L) = Gq + L*H + tri(L)*gamma*(n+1) on the segment after the k shortest requests (n still running)
     uint16_t* tabR = nullptr; // [M][cap] remaining lengths, ascending; 0xFFFF past the last entry
-    float2* tabGH = nullptr;  // [M][cap] (Gq, H) of segment k = index + 1
-    float2* headGH = nullptr; // [M] (Gq, H) of segment 0: (q_g, alpha + beta*(N+1) + gamma*sum of contexts)
+    float2* tabGH = nullptr;  // [M][cap + 2] (Gq, H) of segment k, see gh_at; segment 0 is (q_g, alpha + beta*(N+1) + gamma*sum of contexts)
     int* hN = nullptr;       // [M] entries per instance
     double* hD = nullptr;    // [M] d_g
     // [M] what a pair needs of its instance besides the tables: (delta, gamma) of the latency's prefill
@@ -175,7 +178,7 @@ struct gr_fleet {
     uint16_t* len_row = nullptr;  // [bins] rows shorter than each length = its row if it has one
     int* totals = nullptr;    // [4] -, distinct lengths
     float* memo = nullptr;       // [row_cap / kMemoU][m_pos][kMemoU] E per distinct length and position
-    float* grp_min = nullptr;    // [row_cap][run_pad] least E of each run, per row
+    float* grp_min = nullptr;    // [row_cap][run_pad] least E of each run, per row (see runs_at)
     float4* run_k = nullptr;     // [n_run] least delta of the run, gamma, largest delta, lowest instance (int bits)
     float* class_min = nullptr;  // [row_cap][c_pad] least E of each class, per row
     uint2* class_next = nullptr; // [row_cap][n_class] next larger E of the class (bits), lowest instance that has the least

@@ -145,9 +145,9 @@ struct MemoArgs {
     const uint16_t* len_row;
     const float4* instK;
     const uint16_t *tabR, *tabS;
-    const float2 *tabGH, *headGH;
+    const float2* tabGH;
     float* memo;           // see memo_at
-    float* grp_min;        // [rows][run_pad]
+    float* grp_min;        // see runs_at
     float4* run_k;         // [n_run]
     const float2* posK;
     uint4* seen;           // cleared here for the next batch (its reader is done)
@@ -161,6 +161,25 @@ __device__ inline size_t memo_at(int64_t row, int pos, int m_pos)
     return ((size_t)(row / kMemoU) * m_pos + pos) * kMemoU + (size_t)(row % kMemoU);
 }
 
+// The runs' least values: row by row where a request's lanes take 16 runs of its row at a time, in
+// blocks like the table where the classes' least values are formed first, a lane per row.
+template <bool kBlocks>
+__device__ inline size_t runs_at(int64_t row, int run_pad)
+{
+    return kBlocks ? (size_t)(row / kMemoU) * run_pad * kMemoU + (size_t)(row % kMemoU) : (size_t)row * run_pad;
+}
+template <bool kBlocks>
+constexpr int kRunStride = kBlocks ? kMemoU : 1;
+
+// minimum of two values of which none is a NaN that must not come out quiet (the compiler guards
+// against that with an instruction per operand)
+__device__ inline float min_plain(float a, float b)
+{
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
 // E of every (distinct length, instance).  A workgroup takes a run of kMemoP positions of the class
 // order and a block of kMemoU consecutive distinct lengths ("rows", ascending), a wave four of the
 // positions, a lane four rows.  The segment of a row is k = #{R_i <= L}.  The instance's lengths R
@@ -171,14 +190,16 @@ __device__ inline size_t memo_at(int64_t row, int pos, int m_pos)
 //
 // A lane keeps its rows' values in registers from the counters to the store and the minimum over
 // positions is a running one, so there is no transpose and one barrier.  Kernel time on 4 096 instances of
-// 512 requests: 2 726 rows 31 us, 7 061 rows 55 us; with the table laid out row by row, a wave per instance,
-// a pass through LDS to turn a block and the minimum taken over lanes, 42 and 65 us.
+// 512 requests: 2 726 rows 25 us, 7 061 rows 46 us (116 MB written: 2.5 TB/s; the rest is the vector ALU
+// and the chain of reads a workgroup begins with); with the table laid out row by row, a wave per
+// instance, a pass through LDS to turn a block and the minimum taken over lanes, 42 and 65 us.  The runs'
+// minima written row by row cost 4 and 6 us more.  Seven waves per SIMD: at eight the registers spill (65 us).
 constexpr int kMemoWaves = kBlock / kWave;
 constexpr int kMemoInst = kMemoP / kMemoWaves;      // instances of a wave
 static_assert(kMemoU == 4 * kWave, "a lane owns four consecutive rows");
 
-template <bool kLargeTab>
-__global__ __launch_bounds__(kBlock) void k_memo(MemoArgs a)
+template <bool kLargeTab, bool kBlocks>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 7))) void k_memo(MemoArgs a)
 {
     constexpr int kS = kLargeTab ? 4 : 2, kB = kLargeTab ? 8 : 4;   // most 16-byte words of splitters, of a stride
     __shared__ int cnt_lds[kMemoWaves][kMemoInst][kMemoU];
@@ -208,7 +229,6 @@ __global__ __launch_bounds__(kBlock) void k_memo(MemoArgs a)
     // entries up to the block's first row (lanes 0 .. 3: exclusive) and up to its last (lanes 4 .. 7)
     int my_g, my_k = 0;
     float4 my_K{};
-    float2 my_head{};
     {
         const bool last = lane & kMemoInst;
         my_g = a.order[p0 + lane % kMemoInst];
@@ -216,7 +236,6 @@ __global__ __launch_bounds__(kBlock) void k_memo(MemoArgs a)
         const uint32_t L = (uint32_t)(last ? a.row_len[ue - 1] : ub > 0 ? a.row_len[ub - 1] : 0);
         const int n_split = split_count(a.cap), stride = a.cap / n_split, s_words = n_split / 8, b_words = stride / 8;
         my_K = a.instK[g];
-        my_head = a.headGH[g];
         uint4 w[kB];
         const uint4* __restrict__ S = reinterpret_cast<const uint4*>(a.tabS + (size_t)g * n_split);
 #pragma unroll
@@ -285,9 +304,9 @@ __global__ __launch_bounds__(kBlock) void k_memo(MemoArgs a)
             c.x += before; c.y += before; c.z += before; c.w += before;
         }
         k[j][0] = kb[j] + c.x; k[j][1] = kb[j] + c.y; k[j][2] = kb[j] + c.z; k[j][3] = kb[j] + c.w;
-        const float2* __restrict__ GH = a.tabGH + (size_t)max(g[j], 0) * a.cap;
+        const char* __restrict__ GH = reinterpret_cast<const char*>(a.tabGH + gh_at(max(g[j], 0), 0, a.cap));
 #pragma unroll
-        for (int i = 0; i < 4; ++i) gh[j][i] = GH[(unsigned)max(k[j][i] - 1, 0)];
+        for (int i = 0; i < 4; ++i) gh[j][i] = *reinterpret_cast<const float2*>(GH + (unsigned)k[j][i] * (unsigned)sizeof(float2));
     }
     float least[4] = {__builtin_inff(), __builtin_inff(), __builtin_inff(), __builtin_inff()};
 #pragma unroll
@@ -295,14 +314,11 @@ __global__ __launch_bounds__(kBlock) void k_memo(MemoArgs a)
         if (g[j] < 0) continue;
         const float gam = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_K.z), j));
         const int N = __builtin_amdgcn_readlane(__float_as_int(my_K.w), j);
-        const float hx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_head.x), j));
-        const float hy = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_head.y), j));
         float E[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float Gq = k[j][i] > 0 ? gh[j][i].x : hx, H = k[j][i] > 0 ? gh[j][i].y : hy;
-            E[i] = fmaf(Lf[i], H, Gq) + tri[i] * (gam * (float)(N - k[j][i] + 1));
-            least[i] = fminf(least[i], E[i]);
+            E[i] = fmaf(Lf[i], gh[j][i].y, gh[j][i].x) + tri[i] * (gam * (float)(N - k[j][i] + 1));
+            least[i] = min_plain(least[i], E[i]);
         }
         *reinterpret_cast<float4*>(a.memo + ((size_t)pass * a.m_pos + p0 + j) * kMemoU + 4 * lane) = make_float4(E[0], E[1], E[2], E[3]);
     }
@@ -311,8 +327,8 @@ __global__ __launch_bounds__(kBlock) void k_memo(MemoArgs a)
     {
         float m = min_lds[0][tid];
 #pragma unroll
-        for (int w = 1; w < kMemoWaves; ++w) m = fminf(m, min_lds[w][tid]);
-        if (ub + tid < ue) a.grp_min[(size_t)(ub + tid) * a.run_pad + run] = m;
+        for (int w = 1; w < kMemoWaves; ++w) m = min_plain(m, min_lds[w][tid]);
+        if (ub + tid < ue) a.grp_min[runs_at<kBlocks>(ub + tid, a.run_pad) + (size_t)run * kRunStride<kBlocks>] = m;
     }
 
     // what the selection needs of the run: its least and largest delta (gamma is the same for all of
@@ -376,56 +392,98 @@ struct ClassArgs {
 
 // Per row and class: the least E, the lowest instance that has it, and the least E above it among
 // what could still change the answer.  Without a blend the prefill part is the same for all of a
-// class, so these decide a request's least latency (k_select).  16 lanes per (row, class): the
-// class's runs, then the positions of the runs that hold the least E.
+// class, so these decide a request's least latency (k_select).  A workgroup takes 64 rows and one
+// class, a lane per row (the reads are whole cache lines) and a quarter of the class's runs per wave: the
+// runs first, then four positions per wave of the run that holds the least E.
 __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
 {
-    const int sub = threadIdx.x % kGroup;
-    const int64_t at = (int64_t)blockIdx.x * (kBlock / kGroup) + threadIdx.x / kGroup;
-    const int64_t u = at / a.n_class;
-    const int c = (int)(at % a.n_class);
-    if (u >= a.totals[1]) return;
+    constexpr int kW = kBlock / kWave;
+    static_assert(kMemoU % kWave == 0, "the rows of a workgroup are in one block");
+    __shared__ float m1_lds[kW][kWave], m2_lds[kW][kWave];
+    __shared__ int r1_lds[kW][kWave], low_lds[kW][kWave];
+    const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int c = blockIdx.x % a.n_class;
+    const int64_t u0 = (int64_t)(blockIdx.x / a.n_class) * kWave, u = u0 + lane;
+    const int U = a.totals[1];
+    if (u0 >= U) return;
     const int2 cr = a.cls_run[c];
-    const float* __restrict__ runs = a.grp_min + u * a.run_pad + cr.x;
     const float inf = __builtin_inff();
-    constexpr int kAhead = 4;
-    float least = inf;
-    for (int r0 = 0; r0 < cr.y; r0 += kAhead * kGroup) {
+    const float* __restrict__ runs = a.grp_min + runs_at<true>(u, a.run_pad) + (size_t)cr.x * kMemoU;
+    const float* __restrict__ E = a.memo + memo_at(u, cr.x * kMemoP, a.m_pos);
+    const int* __restrict__ order = a.order + cr.x * kMemoP;
+
+    float m1 = inf, m2 = inf;       // of this wave's runs: the least, the least of the others
+    int r1 = 0;
+    constexpr int kAhead = 8;
+    for (int r0 = w; r0 < cr.y; r0 += kAhead * kW) {
         float e[kAhead];
 #pragma unroll
-        for (int k = 0; k < kAhead; ++k) {
-            const int r = r0 + k * kGroup + sub;
-            e[k] = runs[min(r, cr.y - 1)];
-        }
+        for (int k = 0; k < kAhead; ++k) e[k] = runs[(size_t)min(r0 + k * kW, cr.y - 1) * kMemoU];
 #pragma unroll
-        for (int k = 0; k < kAhead; ++k) least = fminf(least, e[k]);
-    }
-    const float E1 = from_ordered_bits(min_over<true>(ordered_bits(least)));
-    float above = inf;            // this lane's least E above E1
-    int low = 0x7fffffff;         // lowest instance at E1
-    for (int r0 = 0; r0 < cr.y; r0 += kGroup) {
-        const int r = r0 + sub;
-        const float e = r < cr.y ? runs[r] : inf;
-        if (e > E1) above = fminf(above, e);
-        uint32_t mask = group_ballot(e == E1 && E1 < inf);
-        while (mask) {
-            const int run = r0 + __ffs(mask) - 1;
-            mask &= mask - 1;
-            // (a run whose instances all come behind the one at hand changes nothing: where one of
-            // its other latencies ties with the least one, the instance at hand wins as well)
-            if (__float_as_int(a.run_k[cr.x + run].w) > low) continue;
-            const int p = run * kMemoP + sub;
-            const float v = a.memo[memo_at(u, cr.x * kMemoP + p, a.m_pos)];
-            const int g = a.order[cr.x * kMemoP + p];
-            if (v > E1) above = fminf(above, v);
-            low = min(low, (int)min_over<true>(v == E1 && g >= 0 ? (uint32_t)g : 0x7fffffffu));
+        for (int k = 0; k < kAhead; ++k) {
+            const int r = r0 + k * kW;
+            if (r >= cr.y) break;
+            if (e[k] < m1) { m2 = m1; m1 = e[k]; r1 = r; }
+            else m2 = fminf(m2, e[k]);
         }
     }
-    const uint32_t next = min_over<true>(ordered_bits(above));
-    if (sub == 0) {
-        a.class_min[u * a.c_pad + c] = E1;
-        a.class_next[u * a.n_class + c] = make_uint2(__float_as_uint(from_ordered_bits(next)), (uint32_t)low);
+    m1_lds[w][lane] = m1; m2_lds[w][lane] = m2; r1_lds[w][lane] = r1;
+    __syncthreads();
+    float E1 = inf, above = inf;
+    int tied = 0;                   // runs that hold the least E
+    r1 = 0;
+#pragma unroll
+    for (int q = 0; q < kW; ++q)
+        if (m1_lds[q][lane] < E1) { E1 = m1_lds[q][lane]; r1 = r1_lds[q][lane]; }
+#pragma unroll
+    for (int q = 0; q < kW; ++q) {
+        const float x = m1_lds[q][lane], y = m2_lds[q][lane];
+        tied += (x == E1) + (y == E1);
+        if (x > E1) above = fminf(above, x);
+        if (y > E1) above = fminf(above, y);
     }
+    const bool any = u < U && E1 < inf;
+    int low = 0x7fffffff;
+    const auto take = [&](int p) {
+        const float v = E[(size_t)p * kMemoU];
+        const int g = order[p];
+        if (g < 0) return;
+        if (v > E1) above = fminf(above, v);
+        else if (v == E1) low = min(low, g);
+    };
+    if (any) {
+#pragma unroll
+        for (int k = 0; k < kMemoP / kW; ++k) take(r1 * kMemoP + w * (kMemoP / kW) + k);
+    }
+    low_lds[w][lane] = low;
+    if (__syncthreads_or(any && tied > 1)) {
+        // Several runs hold the least E: those are looked at as well, unless all of a run's instances
+        // come behind the one at hand (where another latency of such a run ties with the least one, the
+        // instance at hand wins as well).
+        if (any && tied > 1) {
+            int low1 = low_lds[0][lane];
+#pragma unroll
+            for (int q = 1; q < kW; ++q) low1 = min(low1, low_lds[q][lane]);
+            for (int r = w; r < cr.y; r += kW) {
+                const float e = runs[(size_t)r * kMemoU];
+                if (e > E1) above = fminf(above, e);
+                else if (r != r1 && __float_as_int(a.run_k[cr.x + r].w) < low1)
+                    for (int p = r * kMemoP; p < (r + 1) * kMemoP; ++p) take(p);
+            }
+        }
+        __syncthreads();
+        low_lds[w][lane] = low;
+    }
+    m2_lds[w][lane] = above;
+    __syncthreads();
+    if (w != 0 || u >= U) return;
+#pragma unroll
+    for (int q = 1; q < kW; ++q) {
+        low = min(low, low_lds[q][lane]);
+        above = fminf(above, m2_lds[q][lane]);
+    }
+    a.class_min[u * a.c_pad + c] = E1;
+    a.class_next[u * a.n_class + c] = make_uint2(__float_as_uint(above), (uint32_t)low);
 }
 
 struct SelectArgs {
@@ -485,7 +543,7 @@ __device__ __forceinline__ void answer(const SelectArgs& a, int64_t i, int g, fl
 // settle): the run with the least bound is looked at, then every other run whose bound does not
 // exceed the least latency at hand (equal ones only if they hold a lower instance).  kChunks x
 // kGroup runs are read together: the reads of the runs' values are what a request waits for.
-template <int kChunks>
+template <int kChunks, bool kBlocks>
 struct Selection {
     const SelectArgs& a;
     const int sub, ex;
@@ -503,9 +561,9 @@ struct Selection {
     float m1, m2;
     int r1;
 
-    __device__ __forceinline__ Selection(const SelectArgs& args, const Request& q, int sub_)
-        : a(args), sub(sub_), ex(q.ex), runs(args.grp_min + (size_t)args.len_row[q.L] * args.run_pad),
-          E(args.memo + memo_at(args.len_row[q.L], 0, args.m_pos)), Lf((float)q.L), c0((float)q.c0),
+    __device__ __forceinline__ Selection(const SelectArgs& args, const Request& q, int row, int sub_)
+        : a(args), sub(sub_), ex(q.ex), runs(args.grp_min + runs_at<kBlocks>(row, args.run_pad)),
+          E(args.memo + memo_at(row, 0, args.m_pos)), Lf((float)q.L), c0((float)q.c0),
           Dc(q.D > FLT_MAX ? FLT_MAX : q.D) {}
 
     __device__ __forceinline__ float bound(float e, const float4& k) const
@@ -526,10 +584,12 @@ struct Selection {
         for (int r0 = 0; r0 < n; r0 += kChunks * kGroup) {
             float b[kChunks];
             float4 k[kChunks];
+            uint4 head[kChunks];      // (read with the rest where a feasible run is known to be there)
 #pragma unroll
             for (int j = 0; j < kChunks; ++j) {
                 const int r = first + min(r0 + j * kGroup + sub, n - 1);
-                b[j] = runs[r];
+                if (!kLeast) head[j] = a.run_head[r];
+                b[j] = runs[(size_t)r * kRunStride<kBlocks>];
                 k[j] = a.run_k[r];
             }
             uint32_t any = 0;
@@ -544,11 +604,10 @@ struct Selection {
                 if (kFeasible) any |= group_ballot(b[j] <= Dc);
             }
             if (!kFeasible || !any) continue;
-            uint4 head[kChunks];
             bool in[kChunks];
 #pragma unroll
             for (int j = 0; j < kChunks; ++j) {
-                head[j] = a.run_head[first + min(r0 + j * kGroup + sub, n - 1)];
+                if (kLeast) head[j] = a.run_head[first + min(r0 + j * kGroup + sub, n - 1)];
                 in[j] = b[j] <= Dc;
             }
             for (;;) {
@@ -615,7 +674,7 @@ struct Selection {
         if (!group_ballot(m2 <= bestT && m2 < inf)) return;
         for (int rb = 0; rb < n; rb += kGroup) {       // some lane has a second run to look at: all runs again
             const int r = first + min(rb + sub, n - 1);
-            const float b = rb + sub < n ? bound(runs[r], a.run_k[r]) : inf;
+            const float b = rb + sub < n ? bound(runs[(size_t)r * kRunStride<kBlocks>], a.run_k[r]) : inf;
             uint32_t again = group_ballot(b <= bestT && b < inf && r != r1);
             while (again) {
                 const int lo = __ffs(again) - 1;
@@ -646,7 +705,7 @@ __global__ __launch_bounds__(kBlock) void k_select(SelectArgs a)
         if (sub == 0) answer<kMigrate>(a, i, -1, 0.f, false);      // not flagged: no migration target
         return;
     }
-    Selection<kChunks> sel(a, q, sub);
+    Selection<kChunks, false> sel(a, q, a.len_row[q.L], sub);
     sel.template scan<true, true>(0, a.n_run);
     if (sel.feasG < 0) sel.settle(0, a.n_run);
     sel.template report<kMigrate>(i, q.D);
@@ -656,13 +715,12 @@ __global__ __launch_bounds__(kBlock) void k_select(SelectArgs a)
 // classes hold a feasible instance): the runs of one class after the other, as long as a class can
 // still improve on the choice.
 template <bool kMigrate, int kChunks>
-__device__ __forceinline__ void select_by_class(const SelectArgs& a, int64_t i, int sub)
+__device__ __forceinline__ void select_by_class(const SelectArgs& a, int64_t i, const Request& q, int row, int sub)
 {
     const float inf = __builtin_inff();
-    const Request q = fetch<kMigrate>(a.s, i, a.max_len);
-    Selection<kChunks> sel(a, q, sub);
+    Selection<kChunks, true> sel(a, q, row, sub);
     const int c = min(sub, a.n_class - 1);
-    const float e = a.class_min[(size_t)a.len_row[q.L] * a.c_pad + c];
+    const float e = a.class_min[(size_t)row * a.c_pad + c];
     const int2 range = a.cls_run[c];
     const uint4 head = a.run_head[min(range.x, a.n_run - 1)];
     const unsigned long long key = ((unsigned long long)head.y << 32) | head.x;
@@ -704,7 +762,8 @@ __device__ __forceinline__ void select_by_class(const SelectArgs& a, int64_t i, 
 template <bool kMigrate, int kLanes, int kItems>
 __global__ __launch_bounds__(kBlock) void k_select_by_class(SelectArgs a)
 {
-    __shared__ int todo[kLanes * kItems];
+    struct Left { Request q; int row, index; };      // (kept: reading a request again is two more trips to memory)
+    __shared__ Left todo[kLanes * kItems];
     __shared__ int n_todo;
     const int tid = threadIdx.x;
     if (tid == 0) n_todo = 0;
@@ -765,14 +824,16 @@ __global__ __launch_bounds__(kBlock) void k_select_by_class(SelectArgs a)
                 int at = 0;
                 if (lane_id() == 0) at = atomicAdd(&n_todo, __popcll(m));
                 at = __builtin_amdgcn_readfirstlane(at);
-                if (later) todo[at + __popcll(m & ((1ull << lane_id()) - 1ull))] = it * kLanes + tid;
+                if (later) todo[at + __popcll(m & ((1ull << lane_id()) - 1ull))] = Left{q[it], (int)row[it], it * kLanes + tid};
             }
         }
     }
     __syncthreads();
     const int n = n_todo;
-    for (int k = tid / kGroup; k < n; k += kBlock / kGroup)
-        select_by_class<kMigrate, 4>(a, index(todo[k] / kLanes, todo[k] % kLanes), tid % kGroup);
+    for (int k = tid / kGroup; k < n; k += kBlock / kGroup) {
+        const Left& t = todo[k];
+        select_by_class<kMigrate, 4>(a, index(t.index / kLanes, t.index % kLanes), t.q, t.row, tid % kGroup);
+    }
 }
 
 struct PairsArgs {
@@ -884,7 +945,7 @@ struct DirectArgs {
     const float4* instK;
     const double* hD;
     const uint16_t *tabR, *tabS;
-    const float2 *tabGH, *headGH;
+    const float2* tabGH;
     DirectPart* parts_out;   // [n][parts]
     int* out_inst;
     float* out_slack;
@@ -1011,7 +1072,7 @@ __global__ __launch_bounds__(kLanes <= 64 ? kBlock : kLanes) void k_direct(Direc
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            gh[u] = k[u] > 0 ? a.tabGH[(size_t)g[u] * a.cap + k[u] - 1] : a.headGH[g[u]];
+            gh[u] = a.tabGH[gh_at(g[u], k[u], a.cap)];
             d[u] = a.hD[g[u]];
         }
 #pragma unroll
@@ -1075,7 +1136,7 @@ int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream
     if (src.n > kDirectMax) return GR_ERR_TOO_LARGE;
     DirectArgs d{};
     d.ctx0 = src.ctx0; d.pred_len = src.pred_len; d.budget = src.budget; d.exclude = src.exclude;
-    d.instK = f->instK; d.hD = f->hD; d.tabR = f->tabR; d.tabS = f->tabS; d.tabGH = f->tabGH; d.headGH = f->headGH;
+    d.instK = f->instK; d.hD = f->hD; d.tabR = f->tabR; d.tabS = f->tabS; d.tabGH = f->tabGH;
     d.parts_out = f->direct_part;
     d.out_inst = out.inst; d.out_slack = out.slack; d.out_fallback = out.fallback; d.out_T = out.T;
     d.n = n; d.n_inst = M; d.cap = f->cap; d.max_len = f->max_len;
@@ -1106,8 +1167,8 @@ int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream
 }
 
 constexpr int64_t kByClassMin = int64_t(1) << 17;      // requests from which the classes are looked at first
-// and from which a workgroup takes 1 024 of them (64 otherwise): a scan of 1.02 M 67.9 us instead of
-// 74.6, of 262 144 44.7 instead of 41.2
+// and from which a workgroup takes 512 of them (64 otherwise; kernel time of a scan of 2.1 M with 1 024
+// 38 us, with 512 33)
 constexpr int64_t kByClassMany = int64_t(1) << 19;
 
 // Whether a scoring pass on stream `s` has to make the class order first.
@@ -1124,12 +1185,12 @@ static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, hipStr
 {
     const int64_t n = a.s.n;
     if (by_class) {
-        // large batches: four requests per lane of a whole workgroup; else a wave's worth per workgroup,
+        // large batches: two requests per lane of a whole workgroup; else a wave's worth per workgroup,
         // so that the second half has the lanes when many requests need it
         const bool many = n >= kByClassMany;
-        const int64_t per = many ? 4 * kBlock : kWave;
+        const int64_t per = many ? 2 * kBlock : kWave;
         a.segments = (int)((n + per - 1) / per);
-        if (many) hipLaunchKernelGGL((k_select_by_class<kMigrate, kBlock, 4>), dim3(a.segments), dim3(kBlock), 0, s, a);
+        if (many) hipLaunchKernelGGL((k_select_by_class<kMigrate, kBlock, 2>), dim3(a.segments), dim3(kBlock), 0, s, a);
         else hipLaunchKernelGGL((k_select_by_class<kMigrate, kWave, 1>), dim3(a.segments), dim3(kBlock), 0, s, a);
         return;
     }
@@ -1172,19 +1233,6 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     }
     if (with_order) f->ranks_current = true;
     const int64_t max_rows = n < f->bins ? n : f->bins;
-    {
-        MemoArgs m{};
-        m.totals = f->totals; m.row_len = f->row_len; m.len_row = f->len_row; m.order = f->order; m.instK = f->instK;
-        m.tabR = f->tabR; m.tabS = f->tabS; m.tabGH = f->tabGH; m.headGH = f->headGH; m.memo = f->memo; m.grp_min = f->grp_min;
-        m.run_k = f->run_k; m.posK = f->posK;
-        m.seen = reinterpret_cast<uint4*>(f->seen); m.seen_words = (f->bins + 15) / 16;
-        m.n_run = f->n_run; m.m_pos = f->m_pos; m.run_pad = f->run_pad; m.cap = f->cap;
-        // (workgroups for as many rows as there may be; those past the last row end at once)
-        const dim3 grid((unsigned)(f->n_run * ((max_rows + kMemoU - 1) / kMemoU)));
-        ProfScope ps(f, kMemoRoute + off, s);
-        if (f->cap > 512) hipLaunchKernelGGL(k_memo<true>, grid, dim3(kBlock), 0, s, m);
-        else hipLaunchKernelGGL(k_memo<false>, grid, dim3(kBlock), 0, s, m);
-    }
     // Classes first in large batches on fleets of many runs.  (A blend gives every instance its own
     // prefill rate: the bounds of the runs have to do.)  Whole routing call, us, a group of lanes per
     // request / classes first; in brackets with deadlines that most requests can meet, where
@@ -1197,14 +1245,30 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     // 512 x 512 requests 57.6 / 41.2 (42.0 / 42.0), 4 096 x 512 544 / 110 (278 / 137).
     const bool by_class = f->lam_built == 0.0 && n >= kByClassMin && f->n_class <= kGroup && f->n_run >= 4 * f->n_class &&
                           f->n_run >= (migrate ? 2 * kGroup : 4 * kGroup);
+    {
+        MemoArgs m{};
+        m.totals = f->totals; m.row_len = f->row_len; m.len_row = f->len_row; m.order = f->order; m.instK = f->instK;
+        m.tabR = f->tabR; m.tabS = f->tabS; m.tabGH = f->tabGH; m.memo = f->memo; m.grp_min = f->grp_min;
+        m.run_k = f->run_k; m.posK = f->posK;
+        m.seen = reinterpret_cast<uint4*>(f->seen); m.seen_words = (f->bins + 15) / 16;
+        m.n_run = f->n_run; m.m_pos = f->m_pos; m.run_pad = f->run_pad; m.cap = f->cap;
+        // (workgroups for as many rows as there may be; those past the last row end at once)
+        const dim3 grid((unsigned)(f->n_run * ((max_rows + kMemoU - 1) / kMemoU)));
+        ProfScope ps(f, kMemoRoute + off, s);
+#define GR_LAUNCH_MEMO(B) do { \
+        if (f->cap > 512) hipLaunchKernelGGL((k_memo<true, B>), grid, dim3(kBlock), 0, s, m); \
+        else hipLaunchKernelGGL((k_memo<false, B>), grid, dim3(kBlock), 0, s, m); } while (0)
+        if (by_class) GR_LAUNCH_MEMO(true);
+        else GR_LAUNCH_MEMO(false);
+#undef GR_LAUNCH_MEMO
+    }
     if (by_class) {
         ClassArgs c{};
         c.totals = f->totals; c.cls_run = f->cls_run; c.order = f->order; c.memo = f->memo; c.grp_min = f->grp_min;
         c.run_k = f->run_k; c.class_min = f->class_min; c.class_next = f->class_next;
         c.n_class = f->n_class; c.c_pad = f->c_pad; c.m_pos = f->m_pos; c.run_pad = f->run_pad;
         ProfScope ps(f, kClassRoute + off, s);
-        constexpr int per = kBlock / kGroup;
-        hipLaunchKernelGGL(k_class, dim3((unsigned)((max_rows * f->n_class + per - 1) / per)), dim3(kBlock), 0, s, c);
+        hipLaunchKernelGGL(k_class, dim3((unsigned)((max_rows + kWave - 1) / kWave * f->n_class)), dim3(kBlock), 0, s, c);
     }
     {
         SelectArgs a{};

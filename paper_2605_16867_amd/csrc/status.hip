@@ -30,7 +30,6 @@ struct BuildArgs {
     const int* inst_class;
     uint16_t* tabR;
     float2* tabGH;
-    float2* headGH;
     int* hN;
     double* hD;
     int* act_inst;
@@ -591,7 +590,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
             uint16_t* dstR = a.tabR + (size_t)g * kCap;
             uint16_t* dstS = a.tabS + (size_t)g * split_count(kCap);
             constexpr int kStride = kCap / split_count(kCap);
-            float2* dstGH = a.tabGH + (size_t)g * kCap;
+            float2* dstGH = a.tabGH + gh_at(g, 1, kCap);
             const auto put_R = [&](int slot, uint16_t len) {
                 dstR[slot] = len;
                 if ((slot + 1) % kStride == 0) dstS[slot / kStride] = len;
@@ -624,7 +623,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
                 const double Cd = (double)((Ctot - Pstar) + (long long)Nleft * s64);
                 double Gq0 = q_adm, H0 = cc.alpha + (cc.beta * (double)(Nleft + 1) + cc.gamma * Cd);
                 if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
-                a.headGH[g] = make_float2((float)Gq0, (float)H0);
+                a.tabGH[gh_at(g, 0, kCap)] = make_float2((float)Gq0, (float)H0);
                 a.hN[g] = Nleft;
                 a.instK[g] = inst_coef(a, cc, bp, Nleft);
                 if (!a.use_pending) a.pend_cnt[g] = 0;
@@ -670,7 +669,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
     }
     {
         uint16_t* dstR = a.tabR + (size_t)g * kCap + lane * kEPL;
-        float2* dstGH = a.tabGH + (size_t)g * kCap + lane * kEPL;
+        float2* dstGH = a.tabGH + gh_at(g, 1, kCap) + lane * kEPL;
         if constexpr (kEPL >= 8) {
 #pragma unroll
             for (int r = 0; r < kEPL; r += 8) {
@@ -697,7 +696,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
         const double Cd = (double)Ctot;
         double Gq0 = q, H0 = cc.alpha + (cc.beta * (double)(Nrun + 1) + cc.gamma * Cd);
         if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
-        a.headGH[g] = make_float2((float)Gq0, (float)H0);
+        a.tabGH[gh_at(g, 0, kCap)] = make_float2((float)Gq0, (float)H0);
         a.hN[g] = Nrun;
         a.instK[g] = inst_coef(a, cc, bp, Nrun);
         if (!a.use_pending) a.pend_cnt[g] = 0;
@@ -1006,7 +1005,7 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
     }
     {
         uint16_t* dstR = a.tabR + (size_t)g * kCap + first + lane * kEPL;
-        float2* dstGH = a.tabGH + (size_t)g * kCap + first + lane * kEPL;
+        float2* dstGH = a.tabGH + gh_at(g, 1, kCap) + first + lane * kEPL;
         if constexpr (kEPL >= 8) {
 #pragma unroll
             for (int r = 0; r < kEPL; r += 8) {
@@ -1031,7 +1030,7 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
     if (lane == 0 && part == 0) {
         double Gq0 = q, H0 = fma(cc.gamma, Ctot, fma(cc.beta, (double)(N + 1), cc.alpha));
         if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
-        a.headGH[g] = make_float2((float)Gq0, (float)H0);
+        a.tabGH[gh_at(g, 0, kCap)] = make_float2((float)Gq0, (float)H0);
         a.hN[g] = N;
         a.instK[g] = inst_coef(a, cc, bp, N);
         a.pend_touched[g] = 0;
@@ -1360,7 +1359,7 @@ int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s)
     b.out_act_finish = in.out_act_finish; b.out_q_finish = in.out_q_finish;
     b.out_d = in.out_d; b.out_flag = in.out_flag;
     b.cls = f->cls; b.inst_class = f->inst_class;
-    b.tabR = f->tabR; b.tabGH = f->tabGH; b.headGH = f->headGH;
+    b.tabR = f->tabR; b.tabGH = f->tabGH;
     b.hN = f->hN; b.hD = f->hD; b.act_inst = f->act_inst;
     b.instK = f->instK; b.tabS = f->tabS; b.slot_of = f->slot_of; b.slot_key = f->slot_key; b.counters = f->counters;
     b.n_active = in.n_active; b.n_queued = in.n_queued;
