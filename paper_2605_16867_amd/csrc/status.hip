@@ -759,23 +759,23 @@ constexpr int lean_inst_words(int cap) { return 2 * cap + cap / 4; }
 // up with sorted positions part * 64 * kEPL onwards.  The results are the same bit for bit (the
 // sums are exact); a fleet with fewer instances than the chip has SIMDs gets shorter dependent
 // chains and more waves to overlap them.
-template <int kEPL, int kSplit>
-__global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_build_lean(BuildArgs a)
+//
+// The work is that of kEPL * 64 * kSplit words; the tables have room for kTab >= that many entries.
+struct InstanceIn {
+    int g, a0, q0, A, Q, P, status;     // the instance, its slices of the caller's arrays and their lengths, GR_DEV_* bits
+};
+
+template <int kEPL, int kSplit, int kTab>
+__device__ __forceinline__ void build_instance(const BuildArgs& a, const InstanceIn& in, int wave, uint32_t* smem)
 {
-    extern __shared__ uint32_t smem[];
     constexpr int kWords = kWave * kEPL;         // sort words of a wave
-    constexpr int kCap = kWords * kSplit;        // of an instance
+    constexpr int kCap = kWords * kSplit;        // of the instance
     constexpr int kIdxBits = log2_of(kCap);
     constexpr uint32_t kIdxMask = (1u << kIdxBits) - 1u;
     const int lane = lane_id();
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int g = kSplit == 1 ? blockIdx.x * kBuildWaves + wave : blockIdx.x;   // wave-uniform: what follows is scalar
+    const int g = in.g;
     const int part = kSplit == 1 ? 0 : wave;
     const int first = part * kWords;             // this wave's first entry, and its first sorted position
-    if (g >= a.n_inst) return;
-    // feedback routing: an instance that has been given nothing since its table was built keeps it
-    // (the mark is cleared at the very end, when every wave of the instance has read it)
-    if (a.only_touched && a.pend_touched[g] == 0) return;
     // LDS of an instance, all by entry index: contexts; budgets on the way in and finish times on the
     // way out (the caller's arrays are read and written in their own order, 64 consecutive entries
     // per instruction; the sorted order reaches them through LDS); flags, a byte each
@@ -788,17 +788,8 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
     double* sums = reinterpret_cast<double*>(smem + kInstWords + 2 * kCap);         // (split) four totals per wave
 
     const ClassCoef cc = a.cls[a.inst_class[g]];
-    // offsets are clamped into the arrays, so broken CSR data cannot index outside them
-    const int a0 = (int)min((int64_t)max(a.act_off[g], 0), a.n_active);
-    const int q0 = (int)min((int64_t)max(a.q_off[g], 0), a.n_queued);
-    int A = (int)max(min((int64_t)a.act_off[g + 1], a.n_active) - a0, (int64_t)0);
-    int Q = (int)max(min((int64_t)a.q_off[g + 1], a.n_queued) - q0, (int64_t)0);
-    int status = 0;
-    if (A > a.max_entries) { A = a.max_entries; status |= GR_DEV_ENTRIES_DROPPED; }
-    if (Q > a.max_entries - A) { Q = a.max_entries - A; status |= GR_DEV_ENTRIES_DROPPED; }
-    int P = a.use_pending ? min(a.pend_cnt[g], kCap) : 0;
-    if (P > a.max_entries - A - Q) { P = a.max_entries - A - Q; status |= GR_DEV_ENTRIES_DROPPED; }
-    const int N = A + Q + P;
+    const int a0 = in.a0, q0 = in.q0, A = in.A, Q = in.Q, P = in.P, N = A + Q + P;
+    int status = in.status;
 
     // the instance's slice of each array of running requests (A entries from a0 on)
     const auto slice = [&](const void* base, size_t elem) {
@@ -826,8 +817,8 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
     }
     long long qsum = 0;
     if (Q + P > 0) {     // queued requests, and those routed since the status (feedback routing)
-        const int* pp = a.pend_prompt + (size_t)g * kCap;
-        const int* pl = a.pend_len + (size_t)g * kCap;
+        const int* pp = a.pend_prompt + (size_t)g * kTab;
+        const int* pl = a.pend_len + (size_t)g * kTab;
 #pragma unroll
         for (int r = 0; r < kEPL; ++r) {
             const int i = first + r * kWave + lane;
@@ -1004,8 +995,8 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
             if (r < mine && idx[r] >= A && idx[r] < A + Q) a.out_q_finish[q0 + idx[r] - A] = fin32[r];
     }
     {
-        uint16_t* dstR = a.tabR + (size_t)g * kCap + first + lane * kEPL;
-        float2* dstGH = a.tabGH + gh_at(g, 1, kCap) + first + lane * kEPL;
+        uint16_t* dstR = a.tabR + (size_t)g * kTab + first + lane * kEPL;
+        float2* dstGH = a.tabGH + gh_at(g, 1, kTab) + first + lane * kEPL;
         if constexpr (kEPL >= 8) {
 #pragma unroll
             for (int r = 0; r < kEPL; r += 8) {
@@ -1025,12 +1016,20 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
         } else {
             dstGH[0] = tGH[0];
         }
-        store_splitter<kCap>(a.tabS, g, first + lane * kEPL + kEPL - 1, tR[kEPL - 1]);
+        store_splitter<kTab>(a.tabS, g, first + lane * kEPL + kEPL - 1, tR[kEPL - 1]);
+        if constexpr (kTab > kCap) {      // the lengths past these words: none, 16 bytes at a time
+            constexpr int kStep = kTab / split_count(kTab);
+            const uint4 none = make_uint4(~0u, ~0u, ~0u, ~0u);
+            for (int v = kCap + (part * kWave + lane) * 8; v < kTab; v += kSplit * kWave * 8) {
+                *reinterpret_cast<uint4*>(a.tabR + (size_t)g * kTab + v) = none;
+                if ((v + 8) % kStep == 0) a.tabS[(size_t)g * split_count(kTab) + v / kStep] = (uint16_t)0xFFFFu;
+            }
+        }
     }
     if (lane == 0 && part == 0) {
         double Gq0 = q, H0 = fma(cc.gamma, Ctot, fma(cc.beta, (double)(N + 1), cc.alpha));
         if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
-        a.tabGH[gh_at(g, 0, kCap)] = make_float2((float)Gq0, (float)H0);
+        a.tabGH[gh_at(g, 0, kTab)] = make_float2((float)Gq0, (float)H0);
         a.hN[g] = N;
         a.instK[g] = inst_coef(a, cc, bp, N);
         a.pend_touched[g] = 0;
@@ -1041,6 +1040,42 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
         a.slot_key[a.slot_of[g]] = falling_bits(d);
         if (a.out_d) a.out_d[g] = d;
     }
+}
+
+// A handle's tables have room for the most an instance may hold, which can be several times what
+// it does hold: with kFit an instance that a half or a quarter of the sort words would do for takes
+// those (see fit_words).
+template <int kEPL, int kSplit, bool kFit>
+__global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_build_lean(BuildArgs a)
+{
+    extern __shared__ uint32_t smem[];
+    constexpr int kTab = kWave * kEPL * kSplit;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    InstanceIn in;
+    in.g = kSplit == 1 ? blockIdx.x * kBuildWaves + wave : blockIdx.x;   // wave-uniform: what follows is scalar
+    const int g = in.g;
+    if (g >= a.n_inst) return;
+    // feedback routing: an instance that has been given nothing since its table was built keeps it
+    // (the mark is cleared at the very end, when every wave of the instance has read it)
+    if (a.only_touched && a.pend_touched[g] == 0) return;
+    // offsets are clamped into the arrays, so broken CSR data cannot index outside them
+    in.a0 = (int)min((int64_t)max(a.act_off[g], 0), a.n_active);
+    in.q0 = (int)min((int64_t)max(a.q_off[g], 0), a.n_queued);
+    in.A = (int)max(min((int64_t)a.act_off[g + 1], a.n_active) - in.a0, (int64_t)0);
+    in.Q = (int)max(min((int64_t)a.q_off[g + 1], a.n_queued) - in.q0, (int64_t)0);
+    in.status = 0;
+    if (in.A > a.max_entries) { in.A = a.max_entries; in.status |= GR_DEV_ENTRIES_DROPPED; }
+    if (in.Q > a.max_entries - in.A) { in.Q = a.max_entries - in.A; in.status |= GR_DEV_ENTRIES_DROPPED; }
+    in.P = a.use_pending ? min(a.pend_cnt[g], kTab) : 0;
+    if (in.P > a.max_entries - in.A - in.Q) { in.P = a.max_entries - in.A - in.Q; in.status |= GR_DEV_ENTRIES_DROPPED; }
+    const int N = in.A + in.Q + in.P;
+    if constexpr (kFit) {
+        if constexpr (kEPL >= 4)
+            if (N <= kTab / 4) return build_instance<kEPL / 4, kSplit, kTab>(a, in, wave, smem);
+        if constexpr (kEPL >= 2)
+            if (N <= kTab / 2) return build_instance<kEPL / 2, kSplit, kTab>(a, in, wave, smem);
+    }
+    build_instance<kEPL, kSplit, kTab>(a, in, wave, smem);
 }
 
 // The capability rank of every instance, for the caller (Alg. 1's argmax d_g: rank 0 = largest d_g,
@@ -1261,11 +1296,23 @@ constexpr size_t lean_lds() { return (size_t)kBuildWaves * lean_inst_words(kWave
 
 constexpr int kSimds = 1024;      // 256 compute units of four
 
+// Whether instances pick the number of sort words by what they hold: where half of the words would do
+// for the average one, and in feedback routing, whose handles are made with room for what is routed
+// (256 instances of 512 to 560 requests in tables for 2 048: 8.5 us instead of 10.0).  Elsewhere the
+// choice is one more thing to wait for before the first read (1 024 x 1 000: 15.4 instead of 14.3 us).
+bool fit_words(const BuildArgs& b, int M, int cap)
+{
+    return b.use_pending || (b.n_active + b.n_queued) * 2 <= (int64_t)M * cap;
+}
+
 template <int kEPL, int kSplit>
 int launch_build_split(const BuildArgs& b, int M, hipStream_t s)
 {
     constexpr size_t lds = split_lds<kEPL, kSplit>();
-    hipLaunchKernelGGL((k_build_lean<kEPL / kSplit, kSplit>), dim3(M), dim3(kSplit * kWave), lds, s, b);
+    if (fit_words(b, M, kWave * kEPL))
+        hipLaunchKernelGGL((k_build_lean<kEPL / kSplit, kSplit, true>), dim3(M), dim3(kSplit * kWave), lds, s, b);
+    else
+        hipLaunchKernelGGL((k_build_lean<kEPL / kSplit, kSplit, false>), dim3(M), dim3(kSplit * kWave), lds, s, b);
     return kSplit;
 }
 
@@ -1285,7 +1332,7 @@ int launch_build(const BuildArgs& b, int M, hipStream_t s)
     const int room = 4 * kSimds / M;
     if constexpr (kEPL >= 4) if (room >= 4) return launch_build_split<kEPL, 4>(b, M, s);
     if constexpr (kEPL >= 2) if (room >= 2) return launch_build_split<kEPL, 2>(b, M, s);
-    hipLaunchKernelGGL((k_build_lean<kEPL, 1>), grid, dim3(kBlock), lean_lds<kEPL>(), s, b);
+    hipLaunchKernelGGL((k_build_lean<kEPL, 1, false>), grid, dim3(kBlock), lean_lds<kEPL>(), s, b);
     return 1;
 }
 
@@ -1329,13 +1376,13 @@ int status_prepare()
                                        (int)bytes) == hipSuccess;
     };
     constexpr size_t word = kBuildWaves * kWave * sizeof(int);     // per sort word per lane
-    set(k_build_lean<1, 1>, lean_lds<1>()); set(k_build_lean<2, 1>, lean_lds<2>()); set(k_build_lean<4, 1>, lean_lds<4>());
-    set(k_build_lean<8, 1>, lean_lds<8>()); set(k_build_lean<16, 1>, lean_lds<16>()); set(k_build_lean<32, 1>, lean_lds<32>());
-    set(k_build_lean<1, 2>, split_lds<2, 2>()); set(k_build_lean<2, 2>, split_lds<4, 2>());
-    set(k_build_lean<4, 2>, split_lds<8, 2>()); set(k_build_lean<8, 2>, split_lds<16, 2>());
-    set(k_build_lean<16, 2>, split_lds<32, 2>());
-    set(k_build_lean<1, 4>, split_lds<4, 4>()); set(k_build_lean<2, 4>, split_lds<8, 4>());
-    set(k_build_lean<4, 4>, split_lds<16, 4>()); set(k_build_lean<8, 4>, split_lds<32, 4>());
+    set(k_build_lean<1, 1, false>, lean_lds<1>()); set(k_build_lean<2, 1, false>, lean_lds<2>()); set(k_build_lean<4, 1, false>, lean_lds<4>());
+    set(k_build_lean<8, 1, false>, lean_lds<8>()); set(k_build_lean<16, 1, false>, lean_lds<16>()); set(k_build_lean<32, 1, false>, lean_lds<32>());
+    set(k_build_lean<1, 2, false>, split_lds<2, 2>()); set(k_build_lean<1, 2, true>, split_lds<2, 2>()); set(k_build_lean<2, 2, false>, split_lds<4, 2>()); set(k_build_lean<2, 2, true>, split_lds<4, 2>());
+    set(k_build_lean<4, 2, false>, split_lds<8, 2>()); set(k_build_lean<4, 2, true>, split_lds<8, 2>()); set(k_build_lean<8, 2, false>, split_lds<16, 2>()); set(k_build_lean<8, 2, true>, split_lds<16, 2>());
+    set(k_build_lean<16, 2, false>, split_lds<32, 2>()); set(k_build_lean<16, 2, true>, split_lds<32, 2>());
+    set(k_build_lean<1, 4, false>, split_lds<4, 4>()); set(k_build_lean<1, 4, true>, split_lds<4, 4>()); set(k_build_lean<2, 4, false>, split_lds<8, 4>()); set(k_build_lean<2, 4, true>, split_lds<8, 4>());
+    set(k_build_lean<4, 4, false>, split_lds<16, 4>()); set(k_build_lean<4, 4, true>, split_lds<16, 4>()); set(k_build_lean<8, 4, false>, split_lds<32, 4>()); set(k_build_lean<8, 4, true>, split_lds<32, 4>());
     set(k_build_capped<1>, 3 * word * 1); set(k_build_capped<2>, 3 * word * 2); set(k_build_capped<4>, 3 * word * 4);
     set(k_build_capped<8>, 3 * word * 8); set(k_build_capped<16>, 3 * word * 16); set(k_build_capped<32>, 3 * word * 32);
     return ok ? GR_OK : GR_ERR_HIP;
