@@ -302,7 +302,12 @@ int gr_route_feedback(gr_fleet* f, int64_t n_req, int64_t chunk, const int32_t* 
         ScoreOut o{};
         o.inst = out_inst + s0; o.slack = out_slack + s0; o.fallback = out_fallback ? out_fallback + s0 : nullptr;
         int rc = launch_score(f, src, false, o, s, true);
-        if (rc == GR_OK) rc = launch_commit(f, n, out_inst + s0, ctx0 + s0, pred_len + s0, s);
+        // the chunk's requests join the queues: in the build itself where a wave holds the chunk (the
+        // build under caps is a kernel of its own and does not)
+        const bool in_build = n <= kWave && !f->has_cap;
+        in.chunk_n = in_build ? (int)n : 0;
+        in.chunk_inst = out_inst + s0; in.chunk_ctx0 = ctx0 + s0; in.chunk_len = pred_len + s0;
+        if (rc == GR_OK && !in_build) rc = launch_commit(f, n, out_inst + s0, ctx0 + s0, pred_len + s0, s);
         // instances that were given nothing keep their tables, unless those are from an earlier blend
         // weight or earlier caps
         in.only_touched = f->tables_current ? 1 : 0;

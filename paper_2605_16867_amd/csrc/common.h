@@ -104,6 +104,9 @@ struct StatusIn {
     uint8_t* out_flag;
     int use_pending = 0;      // count the requests routed since the caller's status (feedback routing)
     int only_touched = 0;     // rebuild only the instances that have been given requests since the last build
+    // a chunk just decided, to be taken into the lists by the build (see BuildArgs); 0: none
+    int chunk_n = 0;
+    const int *chunk_inst = nullptr, *chunk_ctx0 = nullptr, *chunk_len = nullptr;
 };
 
 }  // namespace gr

@@ -45,10 +45,14 @@ struct BuildArgs {
     int* late_cnt;
     // requests routed since the caller's status (feedback routing): per instance, queued behind the queue
     int* pend_cnt;
-    const int *pend_prompt, *pend_len;
+    int *pend_prompt, *pend_len;
     int use_pending;     // 0: a fresh status from the caller, the lists are emptied
     int* pend_touched;   // 1: given requests since its table was built
     int only_touched;    // leave the instances with a 0 there as they are
+    // a chunk of up to kWave requests that has just been decided and joins the lists in this build
+    // (0: no such chunk, or its requests are in the lists already); those not chosen count as not touched
+    int chunk_n;
+    const int *chunk_inst, *chunk_ctx0, *chunk_len;
     const int* batch_cap;   // per instance: requests that may decode together; null = no bound
     // blend with the smoothed black-box status (Sec. 3.3): weight lam on it, 0 = none
     double lam;
@@ -763,6 +767,8 @@ constexpr int lean_inst_words(int cap) { return 2 * cap + cap / 4; }
 // The work is that of kEPL * 64 * kSplit words; the tables have room for kTab >= that many entries.
 struct InstanceIn {
     int g, a0, q0, A, Q, P, status;     // the instance, its slices of the caller's arrays and their lengths, GR_DEV_* bits
+    int pend;                           // entries in its list, not counting those of the chunk
+    unsigned long long joins;           // requests of the chunk that were sent here
 };
 
 template <int kEPL, int kSplit, int kTab>
@@ -819,13 +825,32 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
     if (Q + P > 0) {     // queued requests, and those routed since the status (feedback routing)
         const int* pp = a.pend_prompt + (size_t)g * kTab;
         const int* pl = a.pend_len + (size_t)g * kTab;
+        const int listed = A + Q + min(in.pend, P);      // entries before those of the chunk
+        int join_ctx = 0, join_len = 0;                  // lane j: the j-th request of the chunk that was sent here
+        if (in.joins) {
+            const bool mine = (in.joins >> lane) & 1ull;
+            const int nth = __popcll(in.joins & ((1ull << lane) - 1ull));
+            const int ctx0 = a.chunk_ctx0[min(lane, a.chunk_n - 1)], len = a.chunk_len[min(lane, a.chunk_n - 1)];
+            // (the others send to the last lane, which nobody looks at unless every lane is `mine`)
+            join_ctx = __builtin_amdgcn_ds_permute((mine ? nth : kWave - 1) * 4, ctx0);
+            join_len = __builtin_amdgcn_ds_permute((mine ? nth : kWave - 1) * 4, len);
+            if (mine && part == 0 && in.pend + nth < kTab) {
+                a.pend_prompt[(size_t)g * kTab + in.pend + nth] = ctx0;
+                a.pend_len[(size_t)g * kTab + in.pend + nth] = len;
+            }
+        }
 #pragma unroll
         for (int r = 0; r < kEPL; ++r) {
             const int i = first + r * kWave + lane;
+            int jc = 0, jl = 0;
+            if (in.joins) {
+                jc = __builtin_amdgcn_ds_bpermute((i - listed) * 4, join_ctx);
+                jl = __builtin_amdgcn_ds_bpermute((i - listed) * 4, join_len);
+            }
             if (i >= A && i < N) {
                 const bool queued = i < A + Q;
-                rem_in[r] = queued ? a.q_len[q0 + i - A] : pl[i - A - Q];
-                c_in[r] = queued ? a.q_prompt[q0 + i - A] : pp[i - A - Q];
+                rem_in[r] = i >= listed ? jl : queued ? a.q_len[q0 + i - A] : pl[i - A - Q];
+                c_in[r] = i >= listed ? jc : queued ? a.q_prompt[q0 + i - A] : pp[i - A - Q];
                 qsum += c_in[r];
             }
         }
@@ -1034,6 +1059,7 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
         a.instK[g] = inst_coef(a, cc, bp, N);
         a.pend_touched[g] = 0;
         if (!a.use_pending) a.pend_cnt[g] = 0;
+        else if (in.joins) a.pend_cnt[g] = in.pend + __popcll(in.joins);     // (every wave has read it: the sort's barriers)
         double d = fma(cc.gamma, Ctot, fma(cc.beta, (double)N, cc.alpha));     // the next decode step
         if (blended) d = keep * d + a.lam * bd;
         a.hD[g] = d;
@@ -1057,7 +1083,14 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
     if (g >= a.n_inst) return;
     // feedback routing: an instance that has been given nothing since its table was built keeps it
     // (the mark is cleared at the very end, when every wave of the instance has read it)
-    if (a.only_touched && a.pend_touched[g] == 0) return;
+    in.joins = 0;
+    if (a.chunk_n) {
+        const int lane = lane_id();
+        in.joins = __ballot(lane < a.chunk_n && a.chunk_inst[min(lane, a.chunk_n - 1)] == g);
+        if (a.only_touched && !in.joins) return;
+    } else if (a.only_touched && a.pend_touched[g] == 0) {
+        return;
+    }
     // offsets are clamped into the arrays, so broken CSR data cannot index outside them
     in.a0 = (int)min((int64_t)max(a.act_off[g], 0), a.n_active);
     in.q0 = (int)min((int64_t)max(a.q_off[g], 0), a.n_queued);
@@ -1066,7 +1099,9 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
     in.status = 0;
     if (in.A > a.max_entries) { in.A = a.max_entries; in.status |= GR_DEV_ENTRIES_DROPPED; }
     if (in.Q > a.max_entries - in.A) { in.Q = a.max_entries - in.A; in.status |= GR_DEV_ENTRIES_DROPPED; }
-    in.P = a.use_pending ? min(a.pend_cnt[g], kTab) : 0;
+    in.pend = a.use_pending ? a.pend_cnt[g] : 0;
+    in.P = in.pend + __popcll(in.joins);
+    if (in.P > kTab) { in.P = kTab; if (in.joins) in.status |= GR_DEV_ENTRIES_DROPPED; }
     if (in.P > a.max_entries - in.A - in.Q) { in.P = a.max_entries - in.A - in.Q; in.status |= GR_DEV_ENTRIES_DROPPED; }
     const int N = in.A + in.Q + in.P;
     if constexpr (kFit) {
@@ -1153,7 +1188,8 @@ __global__ __launch_bounds__(kBlock) void k_ema(int n_inst, double w, const floa
 // of earlier requests of the chunk that were sent to the same instance.  That order matters under
 // batch caps (admission is first come, first served), so it must not depend on how the hardware
 // schedules waves.  A chunk that fits one wave is placed by that wave (lanes are in request
-// order).  A larger chunk under caps takes two kernels: the first marks the instances that were
+// order); without caps the build takes it in itself (InstanceIn::joins): 256 instances, 64 requests at
+// a time, 17.8 us a round with a launch of its own for this, 14.1 without.  A larger chunk under caps takes two kernels: the first marks the instances that were
 // chosen at all, the second gives every marked instance a wave that walks the chunk in order.
 // Without caps the order of a queue shows in no output (the requests behind it wait for all of
 // them either way; sums and sorted lengths do not depend on it), and a larger chunk is placed by
@@ -1415,6 +1451,7 @@ int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s)
     b.pend_cnt = f->pend_cnt; b.pend_prompt = f->pend_prompt; b.pend_len = f->pend_len;
     b.use_pending = in.use_pending;
     b.pend_touched = f->pend_touched; b.only_touched = in.use_pending && in.only_touched;
+    b.chunk_n = in.chunk_n; b.chunk_inst = in.chunk_inst; b.chunk_ctx0 = in.chunk_ctx0; b.chunk_len = in.chunk_len;
     b.batch_cap = f->has_cap ? f->batch_cap : nullptr;
     b.lam = f->lam; b.emaQ = f->emaQ; b.emaP = f->emaP; b.emaD = f->emaD;
     const int M = f->n_inst;
