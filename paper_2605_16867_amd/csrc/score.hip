@@ -1000,7 +1000,7 @@ __device__ inline void direct_answer(const DirectArgs& a, int r, const DirectPar
 // A batch of a few requests (one arriving request is the paper's own case): grouping by length and
 // a table of per-length values would cost more than they save, so kLanes lanes take a request, each
 // an instance (or a few), and form T = E + c0 * kappa with E from the instance's own tables (the
-// same expression as in the memo kernel).
+// same expression as in k_memo).
 //
 // What bounds it is the chain of dependent reads, so the segment #{R_i <= L} is found in two steps
 // instead of a binary search's ten: the splitters (every stride-th sorted length, a table of their
