@@ -184,6 +184,7 @@ struct gr_fleet {
     float* grp_min = nullptr;    // [row_cap][run_pad] least E of each run, per row (see runs_at)
     float4* run_k = nullptr;     // [n_run] least delta of the run, gamma, largest delta, lowest instance (int bits)
     float* class_min = nullptr;  // [row_cap][c_pad] least E of each class, per row
+    float4* cls_bound = nullptr; // [n_class] least delta of the class, gamma, largest delta
     uint2* class_next = nullptr; // [row_cap][n_class] next larger E of the class (bits), lowest instance that has the least
     bool tables_current = false;   // every instance's table is from the last inputs, blend weight and caps
     bool ranks_current = false;    // the class order belongs to the current d_g (else the next scoring pass makes it)

@@ -387,6 +387,7 @@ struct ClassArgs {
     const float4* run_k;
     float* class_min;
     uint2* class_next;
+    float4* cls_bound;
     int n_class, c_pad, m_pos, run_pad;
 };
 
@@ -395,6 +396,7 @@ struct ClassArgs {
 // class, so these decide a request's least latency (k_select).  A workgroup takes 64 rows and one
 // class, a lane per row (the reads are whole cache lines) and a quarter of the class's runs per wave: the
 // runs first, then four positions per wave of the run that holds the least E.
+template <bool kBlocks>
 __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
 {
     constexpr int kW = kBlock / kWave;
@@ -408,7 +410,19 @@ __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
     if (u0 >= U) return;
     const int2 cr = a.cls_run[c];
     const float inf = __builtin_inff();
-    const float* __restrict__ runs = a.grp_min + runs_at<true>(u, a.run_pad) + (size_t)cr.x * kMemoU;
+    if (u0 == 0 && w == 0) {        // least and largest delta of the class, and its gamma, as for a run
+        float4 k = make_float4(inf, 0.f, -inf, 0.f);
+        for (int r = lane; r < cr.y; r += kWave) {
+            const float4 x = a.run_k[cr.x + r];
+            k = make_float4(fminf(k.x, x.x), fmaxf(k.y, x.y), fmaxf(k.z, x.z), 0.f);
+        }
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1)
+            k = make_float4(fminf(k.x, __shfl_xor(k.x, d, kWave)), fmaxf(k.y, __shfl_xor(k.y, d, kWave)),
+                            fmaxf(k.z, __shfl_xor(k.z, d, kWave)), 0.f);
+        if (lane == 0) a.cls_bound[c] = k;
+    }
+    const float* __restrict__ runs = a.grp_min + runs_at<kBlocks>(min(u, (int64_t)U - 1), a.run_pad) + (size_t)cr.x * kRunStride<kBlocks>;
     const float* __restrict__ E = a.memo + memo_at(u, cr.x * kMemoP, a.m_pos);
     const int* __restrict__ order = a.order + cr.x * kMemoP;
 
@@ -418,7 +432,7 @@ __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
     for (int r0 = w; r0 < cr.y; r0 += kAhead * kW) {
         float e[kAhead];
 #pragma unroll
-        for (int k = 0; k < kAhead; ++k) e[k] = runs[(size_t)min(r0 + k * kW, cr.y - 1) * kMemoU];
+        for (int k = 0; k < kAhead; ++k) e[k] = runs[(size_t)min(r0 + k * kW, cr.y - 1) * kRunStride<kBlocks>];
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) {
             const int r = r0 + k * kW;
@@ -465,7 +479,7 @@ __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
 #pragma unroll
             for (int q = 1; q < kW; ++q) low1 = min(low1, low_lds[q][lane]);
             for (int r = w; r < cr.y; r += kW) {
-                const float e = runs[(size_t)r * kMemoU];
+                const float e = runs[(size_t)r * kRunStride<kBlocks>];
                 if (e > E1) above = fminf(above, e);
                 else if (r != r1 && __float_as_int(a.run_k[cr.x + r].w) < low1)
                     for (int p = r * kMemoP; p < (r + 1) * kMemoP; ++p) take(p);
@@ -499,6 +513,7 @@ struct SelectArgs {
     const float* class_min;
     const uint2* class_next;
     const float2* clsK;
+    const float4* cls_bound;
     int* out_inst;
     float* out_slack;
     uint8_t* out_fallback;
@@ -711,20 +726,19 @@ __global__ __launch_bounds__(kBlock) void k_select(SelectArgs a)
     sel.template report<kMigrate>(i, q.D);
 }
 
-// The same where the least E of every class is known (and no blend: then that decides exactly which
-// classes hold a feasible instance): the runs of one class after the other, as long as a class can
-// still improve on the choice.
-template <bool kMigrate, int kChunks>
+// The same where the least E of every class is known: the runs of one class after the other, as long
+// as the bound of a class (formed like that of a run; exact without a blend) leaves it in question.
+template <bool kMigrate, int kChunks, bool kBlocks>
 __device__ __forceinline__ void select_by_class(const SelectArgs& a, int64_t i, const Request& q, int row, int sub)
 {
     const float inf = __builtin_inff();
-    Selection<kChunks, true> sel(a, q, row, sub);
+    Selection<kChunks, kBlocks> sel(a, q, row, sub);
     const int c = min(sub, a.n_class - 1);
     const float e = a.class_min[(size_t)row * a.c_pad + c];
     const int2 range = a.cls_run[c];
     const uint4 head = a.run_head[min(range.x, a.n_run - 1)];
     const unsigned long long key = ((unsigned long long)head.y << 32) | head.x;
-    const float T = sub < a.n_class && e < inf ? fmaf(sel.c0, kappa_of(a.clsK[c], sel.Lf), e) : inf;
+    const float T = sub < a.n_class && e < inf ? sel.bound(e, a.cls_bound[c]) : inf;      // (none of the class's is less)
     bool feasible = T <= sel.Dc;
     for (;;) {
         const bool in = feasible && sel.improves(key, (int)head.z);
@@ -749,6 +763,22 @@ __device__ __forceinline__ void select_by_class(const SelectArgs& a, int64_t i, 
         }
     }
     sel.template report<kMigrate>(i, q.D);
+}
+
+// A group of lanes per request, over the classes first (a blend gives every instance its own prefill
+// rate: no class minimum decides a request by itself).
+template <bool kMigrate>
+__global__ __launch_bounds__(kBlock) void k_select_blended(SelectArgs a)
+{
+    const int sub = threadIdx.x % kGroup;
+    const int64_t i = (int64_t)blockIdx.x * (kBlock / kGroup) + threadIdx.x / kGroup;
+    if (i >= a.s.n) return;
+    const Request q = fetch<kMigrate>(a.s, i, a.max_len);
+    if (!q.scored) {
+        if (sub == 0) answer<kMigrate>(a, i, -1, 0.f, false);      // not flagged: no migration target
+        return;
+    }
+    select_by_class<kMigrate, 4, false>(a, i, q, a.len_row[q.L], sub);
 }
 
 // A lane per request over the classes first; what that does not decide (a deadline that somebody
@@ -832,7 +862,7 @@ __global__ __launch_bounds__(kBlock) void k_select_by_class(SelectArgs a)
     const int n = n_todo;
     for (int k = tid / kGroup; k < n; k += kBlock / kGroup) {
         const Left& t = todo[k];
-        select_by_class<kMigrate, 4>(a, index(t.index / kLanes, t.index % kLanes), t.q, t.row, tid % kGroup);
+        select_by_class<kMigrate, 4, kMigrate>(a, index(t.index / kLanes, t.index % kLanes), t.q, t.row, tid % kGroup);
     }
 }
 
@@ -1184,6 +1214,11 @@ template <bool kMigrate>
 static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, hipStream_t s)
 {
     const int64_t n = a.s.n;
+    const dim3 grid((unsigned)((n + kBlock / kGroup - 1) / (kBlock / kGroup)));
+    if (by_class && f->lam_built != 0.0) {
+        hipLaunchKernelGGL(k_select_blended<kMigrate>, grid, dim3(kBlock), 0, s, a);
+        return;
+    }
     if (by_class) {
         // large batches: two requests per lane of a whole workgroup; else a wave's worth per workgroup,
         // so that the second half has the lanes when many requests need it
@@ -1194,7 +1229,6 @@ static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, hipStr
         else hipLaunchKernelGGL((k_select_by_class<kMigrate, kWave, 1>), dim3(a.segments), dim3(kBlock), 0, s, a);
         return;
     }
-    const dim3 grid((unsigned)((n + kBlock / kGroup - 1) / (kBlock / kGroup)));
     if (f->n_run <= kGroup) hipLaunchKernelGGL((k_select<kMigrate, 1>), grid, dim3(kBlock), 0, s, a);
     else if (f->n_run <= 2 * kGroup) hipLaunchKernelGGL((k_select<kMigrate, 2>), grid, dim3(kBlock), 0, s, a);
     else hipLaunchKernelGGL((k_select<kMigrate, 4>), grid, dim3(kBlock), 0, s, a);
@@ -1233,8 +1267,7 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     }
     if (with_order) f->ranks_current = true;
     const int64_t max_rows = n < f->bins ? n : f->bins;
-    // Classes first in large batches on fleets of many runs.  (A blend gives every instance its own
-    // prefill rate: the bounds of the runs have to do.)  Whole routing call, us, a group of lanes per
+    // Classes first in large batches on fleets of many runs.  Whole routing call, us, a group of lanes per
     // request / classes first; in brackets with deadlines that most requests can meet, where
     // the classes only say which runs to look at:
     //   instances   65 536 requests          262 144 requests
@@ -1243,8 +1276,14 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     //    4 096      54.6 / 51.6 (55.2 / 55.6)    126 / 89.9  (133 / 109)
     // A risk scan's requests are late where they are, and few can be served in time elsewhere:
     // 512 x 512 requests 57.6 / 41.2 (42.0 / 42.0), 4 096 x 512 544 / 110 (278 / 137).
-    const bool by_class = f->lam_built == 0.0 && n >= kByClassMin && f->n_class <= kGroup && f->n_run >= 4 * f->n_class &&
-                          f->n_run >= (migrate ? 2 * kGroup : 4 * kGroup);
+    // With a blend the classes only rule out whole classes: 4 096 x 400 435 / 372 (221 / 195), and nothing
+    // is won where a group reads all runs at once (64).
+    const bool by_class = n >= kByClassMin && f->n_class <= kGroup && f->n_run >= 4 * f->n_class &&
+                          f->n_run >= (f->lam_built != 0.0 ? 8 * kGroup : migrate ? 2 * kGroup : 4 * kGroup);
+    // The runs' minima in blocks of rows where few requests get as far as the runs (6 us less for the
+    // table of 7 061 rows x 4 096 instances); row by row where many may: a request's 16 lanes then read 16
+    // runs from one cache line, not from sixteen.
+    const bool blocks = by_class && migrate && f->lam_built == 0.0;
     {
         MemoArgs m{};
         m.totals = f->totals; m.row_len = f->row_len; m.len_row = f->len_row; m.order = f->order; m.instK = f->instK;
@@ -1258,22 +1297,24 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
 #define GR_LAUNCH_MEMO(B) do { \
         if (f->cap > 512) hipLaunchKernelGGL((k_memo<true, B>), grid, dim3(kBlock), 0, s, m); \
         else hipLaunchKernelGGL((k_memo<false, B>), grid, dim3(kBlock), 0, s, m); } while (0)
-        if (by_class) GR_LAUNCH_MEMO(true);
+        if (blocks) GR_LAUNCH_MEMO(true);
         else GR_LAUNCH_MEMO(false);
 #undef GR_LAUNCH_MEMO
     }
     if (by_class) {
         ClassArgs c{};
         c.totals = f->totals; c.cls_run = f->cls_run; c.order = f->order; c.memo = f->memo; c.grp_min = f->grp_min;
-        c.run_k = f->run_k; c.class_min = f->class_min; c.class_next = f->class_next;
+        c.run_k = f->run_k; c.class_min = f->class_min; c.class_next = f->class_next; c.cls_bound = f->cls_bound;
         c.n_class = f->n_class; c.c_pad = f->c_pad; c.m_pos = f->m_pos; c.run_pad = f->run_pad;
         ProfScope ps(f, kClassRoute + off, s);
-        hipLaunchKernelGGL(k_class, dim3((unsigned)((max_rows + kWave - 1) / kWave * f->n_class)), dim3(kBlock), 0, s, c);
+        const dim3 grid((unsigned)((max_rows + kWave - 1) / kWave * f->n_class));
+        if (blocks) hipLaunchKernelGGL(k_class<true>, grid, dim3(kBlock), 0, s, c);
+        else hipLaunchKernelGGL(k_class<false>, grid, dim3(kBlock), 0, s, c);
     }
     {
         SelectArgs a{};
         a.s = src; a.len_row = f->len_row; a.order = f->order; a.memo = f->memo; a.grp_min = f->grp_min; a.run_k = f->run_k;
-        a.posK = f->posK; a.posKey = f->posKey; a.run_head = f->run_head; a.cls_run = f->cls_run; a.class_min = f->class_min; a.class_next = f->class_next; a.clsK = f->clsK;
+        a.posK = f->posK; a.posKey = f->posKey; a.run_head = f->run_head; a.cls_run = f->cls_run; a.class_min = f->class_min; a.class_next = f->class_next; a.clsK = f->clsK; a.cls_bound = f->cls_bound;
         a.out_inst = out.inst; a.out_slack = out.slack; a.out_fallback = out.fallback;
         a.m_pos = f->m_pos; a.run_pad = f->run_pad; a.n_run = f->n_run; a.n_class = f->n_class; a.c_pad = f->c_pad;
         a.max_len = f->max_len;

@@ -97,3 +97,8 @@ def test_blended(n_inst, blend):
 @pytest.mark.parametrize("n_req,n_class", [((1 << 17) - 1, 3), (1 << 17, 3), ((1 << 17) + 37, 16), ((1 << 19) + 5, 4)])
 def test_classes_first(n_req, n_class, kind):
     _check(_fleet(1300, n_class, n_req, kind))
+
+
+@pytest.mark.parametrize("blend", [0.5, 1.0])
+def test_classes_first_blended(blend):
+    _check(_fleet(2200, 3, (1 << 17) + 3, "mixed"), blend=blend)
