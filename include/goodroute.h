@@ -38,7 +38,9 @@
  * no synchronisation), so a sequence of them can be recorded into a HIP graph
  * and replayed on the same buffers.  What the host decides at call time is
  * recorded with it: sizes, the blend weight and caps in force, and how a
- * batch is scored (gr_set_small_batch_pairs).  gr_create, gr_destroy, the
+ * batch is scored (gr_set_small_batch_pairs).  Direct calls on the same handle
+ * before, between and after replays work on the tables as the last call or
+ * replay on the device left them.  gr_create, gr_destroy, the
  * gr_set_* calls, gr_profile_* and gr_device_status copy or synchronise and
  * are not for use inside a capture.
  *

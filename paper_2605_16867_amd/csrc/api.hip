@@ -163,6 +163,13 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     clear(f->seen, seen_bytes);
     clear(f->slot_key, sizeof(unsigned long long) * f->m_pos);
     clear(f->totals, sizeof(int) * 4);
+    // tables without an entry, as far as the reads go: a status build may be recorded first, and a direct call
+    // come before its first replay
+    sent = sent && hipMemset(f->tabR, 0xFF, tab * sizeof(uint16_t)) == hipSuccess &&
+           hipMemset(f->tabS, 0xFF, (size_t)n_inst * f->n_split * sizeof(uint16_t)) == hipSuccess;
+    clear(f->tabGH, (size_t)n_inst * (f->cap + 2) * sizeof(float2));
+    clear(f->instK, sizeof(float4) * n_inst);
+    clear(f->hD, sizeof(double) * n_inst);
     clear(f->pend_cnt, sizeof(int) * n_inst);
     clear(f->pend_touched, sizeof(int) * n_inst);
     clear(f->commit_mark, sizeof(int) * n_inst);
@@ -293,6 +300,9 @@ int gr_route_feedback(gr_fleet* f, int64_t n_req, int64_t chunk, const int32_t* 
     in.use_pending = 1;
     in.act_budget = nullptr; in.out_flag = nullptr;
     in.out_act_finish = f->scratch_finish; in.out_q_finish = nullptr; in.out_d = nullptr; in.out_rank = nullptr;
+    // Instances that were given nothing keep their tables, unless those may be from an earlier blend
+    // weight or earlier caps: then the first rebuild takes every instance.
+    bool current = TableAccount(f, s).view(f).current;
     for (int64_t s0 = 0; s0 < n_req; s0 += chunk) {
         const int64_t n = n_req - s0 < chunk ? n_req - s0 : chunk;
         ReqSrc src{};
@@ -308,11 +318,10 @@ int gr_route_feedback(gr_fleet* f, int64_t n_req, int64_t chunk, const int32_t* 
         in.chunk_n = in_build ? (int)n : 0;
         in.chunk_inst = out_inst + s0; in.chunk_ctx0 = ctx0 + s0; in.chunk_len = pred_len + s0;
         if (rc == GR_OK && !in_build) rc = launch_commit(f, n, out_inst + s0, ctx0 + s0, pred_len + s0, s);
-        // instances that were given nothing keep their tables, unless those are from an earlier blend
-        // weight or earlier caps
-        in.only_touched = f->tables_current ? 1 : 0;
+        in.only_touched = current ? 1 : 0;
         if (rc == GR_OK) rc = launch_status(f, in, s);
         if (rc != GR_OK) return rc;
+        current = true;
     }
     return GR_OK;
 }
@@ -353,7 +362,9 @@ int gr_observe(gr_fleet* f, double weight, const float* obs_wait, const float* o
 {
     if (!f || !(weight >= 0.0 && weight <= 1.0)) return GR_ERR_INVALID_ARG;
     if (!obs_wait && !obs_prefill && !obs_decode) return GR_OK;
-    f->tables_current = false;      // (a blended table holds the smoothed status)
+    const TableAccount account(f, static_cast<hipStream_t>(hip_stream));
+    account.v->current = false;      // (a blended table holds the smoothed status)
+    f->recorded |= account.capturing;
     return launch_ema(f, weight, obs_wait, obs_prefill, obs_decode, static_cast<hipStream_t>(hip_stream));
 }
 
@@ -362,7 +373,7 @@ int gr_set_blend(gr_fleet* f, double black_box_weight)
     if (!f || !(black_box_weight >= 0.0 && black_box_weight <= 1.0)) return GR_ERR_INVALID_ARG;
     if (black_box_weight > 0.0 && !(f->have_q && f->have_p && f->have_d)) return GR_ERR_NO_STATUS;
     f->lam = black_box_weight;
-    f->tables_current = false;
+    f->now.current = f->rec.current = false;
     return GR_OK;
 }
 
@@ -376,7 +387,7 @@ int gr_set_small_batch_pairs(gr_fleet* f, int64_t max_pairs)
 int gr_set_batch_cap(gr_fleet* f, const int32_t* cap)
 {
     if (!f) return GR_ERR_INVALID_ARG;
-    f->tables_current = false;
+    f->now.current = f->rec.current = false;
     if (!cap) { f->has_cap = false; return GR_OK; }
     for (int g = 0; g < f->n_inst; ++g)
         if (cap[g] < 1) return GR_ERR_INVALID_ARG;

@@ -109,6 +109,13 @@ struct StatusIn {
     const int *chunk_inst = nullptr, *chunk_ctx0 = nullptr, *chunk_len = nullptr;
 };
 
+// What is known of the instance tables at a call.
+struct TableView {
+    bool current = false;    // every instance's table is from the last inputs, blend weight and caps
+    bool ordered = false;    // the class order belongs to the d_g (else the next scoring pass makes it)
+    bool blended = false;    // the tables may hold a blend with the smoothed status
+};
+
 }  // namespace gr
 
 struct gr_fleet {
@@ -131,7 +138,6 @@ struct gr_fleet {
     bool has_status = false;
     // smoothed black-box status (Sec. 3.3) and the weight it is blended in with
     double lam = 0.0;        // as set; takes effect at the next status build
-    double lam_built = 0.0;  // the weight the current tables were built with
     bool have_q = false, have_p = false, have_d = false;
     double *emaQ = nullptr, *emaP = nullptr, *emaD = nullptr;   // [M] each
     // device memory: fleet description
@@ -186,8 +192,13 @@ struct gr_fleet {
     float* class_min = nullptr;  // [row_cap][c_pad] least E of each class, per row
     float4* cls_bound = nullptr; // [n_class] least delta of the class, gamma, largest delta
     uint2* class_next = nullptr; // [row_cap][n_class] next larger E of the class (bits), lowest instance that has the least
-    bool tables_current = false;   // every instance's table is from the last inputs, blend weight and caps
-    bool ranks_current = false;    // the class order belongs to the current d_g (else the next scoring pass makes it)
+    // What the host knows of the tables.  A call that is being recorded runs nothing, and what it records
+    // changes the tables at every replay without the host: calls of a capture keep an account of their
+    // own (`rec`, of capture `rec_id`), and once one of them may change the tables, or what they are made
+    // from, the direct calls no longer rely on theirs (`recorded`; `blend_recorded`: one with a blend).
+    gr::TableView now, rec;
+    unsigned long long rec_id = ~0ull;
+    bool recorded = false, blend_recorded = false;
     int* pend_touched = nullptr;   // [M] 1: given requests since its table was built
     int64_t small_batch_pairs = int64_t(1) << 18;   // largest batch, in pairs, scored pair by pair
     gr::DirectPart* direct_part = nullptr;       // [kDirectParts] selections of the parts of a wide fleet, scored pair by pair
@@ -213,6 +224,32 @@ struct ProfScope {
     }
 };
 
+
+// The account of the tables that a call on stream `s` reads and keeps up to date (see gr_fleet).
+struct TableAccount {
+    bool ok = true;          // false: the stream may not be asked (a default stream next to a capture)
+    bool capturing = false;
+    TableView* v;
+
+    TableAccount(gr_fleet* f, hipStream_t s) : v(&f->now)
+    {
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        unsigned long long id = 0;
+        ok = hipStreamGetCaptureInfo(s, &status, &id) == hipSuccess;
+        if (!ok) { (void)hipGetLastError(); return; }
+        capturing = status != hipStreamCaptureStatusNone;
+        if (!capturing) return;
+        if (f->rec_id != id) { f->rec_id = id; f->rec = view(f); }
+        v = &f->rec;
+    }
+
+    // what may be relied upon
+    TableView view(const gr_fleet* f) const
+    {
+        if (v == &f->rec) return {v->current, false, v->blended};      // (replayed after whatever: the order is made)
+        return {v->current && !f->recorded, v->ordered && !f->recorded, v->blended || f->blend_recorded};
+    }
+};
 
 // What the class order needs (see gr_fleet).
 struct OrderArgs {

@@ -1201,21 +1201,12 @@ constexpr int64_t kByClassMin = int64_t(1) << 17;      // requests from which th
 // 38 us, with 512 33)
 constexpr int64_t kByClassMany = int64_t(1) << 19;
 
-// Whether a scoring pass on stream `s` has to make the class order first.
-static int order_needed(const gr_fleet* f, hipStream_t s, bool* needed)
-{
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &capturing) != hipSuccess) return GR_ERR_HIP;
-    *needed = !f->ranks_current || capturing != hipStreamCaptureStatusNone;
-    return GR_OK;
-}
-
 template <bool kMigrate>
-static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, hipStream_t s)
+static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, bool blended, hipStream_t s)
 {
     const int64_t n = a.s.n;
     const dim3 grid((unsigned)((n + kBlock / kGroup - 1) / (kBlock / kGroup)));
-    if (by_class && f->lam_built != 0.0) {
+    if (by_class && blended) {
         hipLaunchKernelGGL(k_select_blended<kMigrate>, grid, dim3(kBlock), 0, s, a);
         return;
     }
@@ -1244,11 +1235,13 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     }
     if (small_batch_ok && !migrate && n <= kDirectMax && n * f->m_pad <= f->small_batch_pairs)
         return launch_direct(f, src, out, s);
-    // The class order of the current status, if nobody has made it yet, comes first.  While
-    // the stream is being captured it always does: a recorded pass may be replayed after a status
-    // build that was recorded elsewhere.
-    bool with_order = false;
-    if (order_needed(f, s, &with_order) != GR_OK) return GR_ERR_HIP;
+    // The class order of the current status, if nobody is known to have made it, comes first: always while
+    // the stream is being captured (a recorded pass may be replayed after a status build that was
+    // recorded elsewhere), and always once a status build has been recorded.
+    const TableAccount account(f, s);
+    if (!account.ok) return GR_ERR_HIP;
+    const TableView view = account.view(f);
+    const bool with_order = !view.ordered, blended = view.blended;
     const int off = migrate ? kScanMigrate - kScanRoute : 0;
     if (!migrate) {
         ProfScope ps(f, kMarkRoute, s);
@@ -1265,7 +1258,7 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         ProfScope ps(f, kScanRoute + off, s);
         hipLaunchKernelGGL(k_scan, dim3(kScanGroups + (with_order ? order_blocks(f->m_pos, kScanBlock) : 0)), dim3(kScanBlock), 0, s, sc, o);
     }
-    if (with_order) f->ranks_current = true;
+    account.v->ordered = true;
     const int64_t max_rows = n < f->bins ? n : f->bins;
     // Classes first in large batches on fleets of many runs.  Whole routing call, us, a group of lanes per
     // request / classes first; in brackets with deadlines that most requests can meet, where
@@ -1279,11 +1272,11 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     // With a blend the classes only rule out whole classes: 4 096 x 400 435 / 372 (221 / 195), and nothing
     // is won where a group reads all runs at once (64).
     const bool by_class = n >= kByClassMin && f->n_class <= kGroup && f->n_run >= 4 * f->n_class &&
-                          f->n_run >= (f->lam_built != 0.0 ? 8 * kGroup : migrate ? 2 * kGroup : 4 * kGroup);
+                          f->n_run >= (blended ? 8 * kGroup : migrate ? 2 * kGroup : 4 * kGroup);
     // The runs' minima in blocks of rows where few requests get as far as the runs (6 us less for the
     // table of 7 061 rows x 4 096 instances); row by row where many may: a request's 16 lanes then read 16
     // runs from one cache line, not from sixteen.
-    const bool blocks = by_class && migrate && f->lam_built == 0.0;
+    const bool blocks = by_class && migrate && !blended;
     {
         MemoArgs m{};
         m.totals = f->totals; m.row_len = f->row_len; m.len_row = f->len_row; m.order = f->order; m.instK = f->instK;
@@ -1319,8 +1312,8 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         a.m_pos = f->m_pos; a.run_pad = f->run_pad; a.n_run = f->n_run; a.n_class = f->n_class; a.c_pad = f->c_pad;
         a.max_len = f->max_len;
         ProfScope ps(f, kSelectRoute + off, s);
-        if (migrate) launch_select<true>(f, a, by_class, s);
-        else launch_select<false>(f, a, by_class, s);
+        if (migrate) launch_select<true>(f, a, by_class, blended, s);
+        else launch_select<false>(f, a, by_class, blended, s);
     }
     if (out.T) {
         PairsArgs p{};

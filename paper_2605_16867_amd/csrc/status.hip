@@ -1468,16 +1468,20 @@ int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s)
         }
     }
     if (in.act_budget) f->late_parts = parts;
-    // the class order is made by the next scoring pass that needs it
-    f->ranks_current = false;
-    f->lam_built = f->lam;
+    // (the class order is made by the next scoring pass that needs it)
+    const TableAccount account(f, s);
+    *account.v = TableView{false, false, f->lam != 0.0};
+    if (account.capturing) {
+        f->recorded = true;
+        f->blend_recorded |= f->lam != 0.0;
+    }
     if (in.out_rank) {
         const int rc = launch_ranks(f, in.out_rank, s);
         if (rc != GR_OK) return rc;
     }
     if (hipGetLastError() != hipSuccess) return GR_ERR_HIP;
     f->has_status = true;
-    f->tables_current = true;
+    account.v->current = true;
     if (!in.use_pending) f->last_in = in;     // what a later feedback routing rebuilds from
     return GR_OK;
 }
