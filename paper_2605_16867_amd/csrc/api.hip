@@ -351,6 +351,7 @@ int gr_risk_scan(gr_fleet* f, const int32_t* act_off, const int32_t* act_prompt,
     ReqSrc src{};
     src.act_prompt = act_prompt; src.act_gen = act_gen; src.act_rem = act_rem_refreshed;
     src.act_inst = f->act_inst; src.flag = out_flag; src.act_budget = act_budget;
+    src.act_off = act_off;
     src.n = n_active;
     ScoreOut o{};
     o.inst = out_target; o.slack = out_target_slack; o.n_selected = out_n_flagged;

@@ -62,6 +62,7 @@ struct ReqSrc {
     const int *act_prompt, *act_gen, *act_rem, *act_inst;
     const uint8_t* flag;
     const float* act_budget;
+    const int* act_off;
     int64_t n;
 };
 
@@ -185,7 +186,7 @@ struct gr_fleet {
     int late_parts = 0;
     int* row_len = nullptr;   // [row_cap] the distinct lengths ("rows"), ascending
     uint16_t* len_row = nullptr;  // [bins] rows shorter than each length = its row if it has one
-    int* totals = nullptr;    // [4] -, distinct lengths
+    int* totals = nullptr;    // [4] -, distinct lengths, 1: flags that the risk scan's build has not set (zero between calls)
     float* memo = nullptr;       // [row_cap / kMemoU][m_pos][kMemoU] E per distinct length and position
     float* grp_min = nullptr;    // [row_cap][run_pad] least E of each run, per row (see runs_at)
     float4* run_k = nullptr;     // [n_run] least delta of the run, gamma, largest delta, lowest instance (int bits)

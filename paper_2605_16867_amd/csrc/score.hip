@@ -47,19 +47,27 @@ constexpr int kScanChunks = 2;      // blocks of 64 lengths per wave
 static_assert(kMaxLen + 1 <= kWave * kScanChunks * kScanWaves * kScanGroups, "every length has a lane of some wave");
 
 struct ScanArgs {
-    const uint8_t* seen;
+    uint8_t* seen;
     int* row_len;
     uint16_t* len_row;
     int* totals;
     const int* late_cnt;    // flagged requests, n_late counts
     int* out_n;             // may be null
-    int bins, n_late;
+    // a risk scan's running requests (null: a routing batch)
+    const uint8_t* flag;
+    const int *act_rem, *act_off;
+    int64_t n;
+    int bins, n_late, n_inst;
 };
 
 // The list of lengths present ("rows", ascending) and, per length, the number of rows that are
 // shorter.  A wave owns one or two blocks of 64 consecutive lengths (lane = length within the
 // block); instead of passing sums from workgroup to workgroup each workgroup counts everything
 // before its own lengths itself (the bytes sit in L2); the last one also has the total.
+//
+// The migration pass goes by the flags as they are, and a flag that no instance sets is the caller's own:
+// of running entries in nobody's slice, and of those the build passes over (totals[2]).  With such entries the
+// lengths and the count are taken from the flags, by each workgroup for itself.
 //
 // Workgroups past the first kScanGroups place the instances in class order, which the next kernel
 // needs as well and which would cost a launch of its own otherwise.
@@ -77,25 +85,38 @@ __global__ __launch_bounds__(kScanBlock) void k_scan(ScanArgs a, OrderArgs order
     const int first = min((int)blockIdx.x * kScanWaves * per * kWave, a.bins);    // first length of this workgroup
     const auto wave_total = [](int v) { return __builtin_amdgcn_readlane(wave_incl_scan_i32(v), kWave - 1); };
 
-    // everything before this workgroup's lengths, 16 at a time (`first` is a
-    // multiple of 64 or the end, and behind the end are zeros)
-    int before = 0;
-    for (int i = threadIdx.x; i < (first + 15) / 16; i += kScanBlock) {
-        const uint4 v = reinterpret_cast<const uint4*>(a.seen)[i];
-        before += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
-    }
-    // this wave's own lengths
+    bool unset = false;
+    if (a.flag) unset = a.totals[2] != 0 || a.act_off[0] > 0 || a.act_off[a.n_inst] < a.n;
+
     bool here[kScanChunks];
-    int own = 0;
+    int n_flags = 0;
+    for (int pass = 0;; ++pass) {
+        // everything before this workgroup's lengths, 16 at a time (`first` is a
+        // multiple of 64 or the end, and behind the end are zeros)
+        int before = 0;
+        for (int i = threadIdx.x; i < (first + 15) / 16; i += kScanBlock) {
+            const uint4 v = reinterpret_cast<const uint4*>(a.seen)[i];
+            before += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+        }
+        // this wave's own lengths
+        int own = 0;
 #pragma unroll
-    for (int k = 0; k < kScanChunks; ++k) {
-        const int i = first + (wave * per + k) * kWave + lane;
-        here[k] = k < per && i < a.bins && a.seen[i] != 0;
-        own += __popcll(__ballot(here[k]));
+        for (int k = 0; k < kScanChunks; ++k) {
+            const int i = first + (wave * per + k) * kWave + lane;
+            here[k] = k < per && i < a.bins && a.seen[i] != 0;
+            own += __popcll(__ballot(here[k]));
+        }
+        before = wave_total(before);
+        if (lane == 0) { w_rows[0][wave] = before; w_rows[1][wave] = own; }
+        __syncthreads();
+        if (!unset || pass) break;
+        for (int64_t i = threadIdx.x; i < a.n; i += kScanBlock) {
+            if (!a.flag[i]) continue;
+            a.seen[min(max(a.act_rem[i], 0), a.bins - 1)] = 1;
+            ++n_flags;
+        }
+        __syncthreads();
     }
-    before = wave_total(before);
-    if (lane == 0) { w_rows[0][wave] = before; w_rows[1][wave] = own; }
-    __syncthreads();
     int u = 0, all = 0;
 #pragma unroll
     for (int w = 0; w < kScanWaves; ++w) {
@@ -117,8 +138,8 @@ __global__ __launch_bounds__(kScanBlock) void k_scan(ScanArgs a, OrderArgs order
     if (blockIdx.x != kScanGroups - 1) return;
     if (threadIdx.x == 0) a.totals[1] = all;        // the last workgroup has seen every length
     if (a.out_n) {
-        int n = 0;
-        for (int i = threadIdx.x; i < a.n_late; i += kScanBlock) n += a.late_cnt[i];
+        int n = n_flags;
+        for (int i = threadIdx.x; !unset && i < a.n_late; i += kScanBlock) n += a.late_cnt[i];
         n = wave_total(n);
         if (lane == 0) sums[wave] = n;
         __syncthreads();
@@ -141,7 +162,8 @@ __device__ inline int count_upto(const uint4& w, uint32_t L)
 
 // ------------------------------------------------------------------ E per length and position
 struct MemoArgs {
-    const int *totals, *row_len, *order;
+    int* totals;
+    const int *row_len, *order;
     const uint16_t* len_row;
     const float4* instK;
     const uint16_t *tabR, *tabS;
@@ -150,7 +172,7 @@ struct MemoArgs {
     float* grp_min;        // see runs_at
     float4* run_k;         // [n_run]
     const float2* posK;
-    uint4* seen;           // cleared here for the next batch (its reader is done)
+    uint4* seen;           // cleared here for the next batch (its reader is done), as is totals[2]
     int seen_words;        // of 16 bytes
     int n_run, m_pos, run_pad, cap;
 };
@@ -206,6 +228,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 7))) 
     __shared__ float min_lds[kMemoWaves][kMemoU];
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < a.seen_words; i += gridDim.x * kBlock)
         a.seen[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.totals[2] = 0;
     const int U = a.totals[1];
     const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int pass = blockIdx.x / a.n_run, run = blockIdx.x % a.n_run;
@@ -1252,6 +1275,7 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         ScanArgs sc{};
         sc.seen = f->seen; sc.row_len = f->row_len; sc.len_row = f->len_row; sc.totals = f->totals; sc.bins = f->bins;
         sc.late_cnt = f->late_cnt; sc.n_late = migrate ? f->n_inst * f->late_parts : 0; sc.out_n = out.n_selected;
+        sc.flag = src.flag; sc.act_rem = src.act_rem; sc.act_off = src.act_off; sc.n = n; sc.n_inst = f->n_inst;
         OrderArgs o{};
         o.key = f->slot_key; o.instK = f->instK; o.slot_inst = f->slot_inst; o.run_cls = f->run_cls;
         o.order = f->order; o.pos_of = f->pos_of; o.posK = f->posK; o.posKey = f->posKey; o.run_head = f->run_head; o.m_pos = f->m_pos;

@@ -43,6 +43,7 @@ struct BuildArgs {
     // for the migration pass of a risk scan: which lengths flagged requests have, and how many are flagged
     uint8_t* seen;
     int* late_cnt;
+    int* unset;          // 1: some running entry's flag is not set here (read by k_scan)
     // requests routed since the caller's status (feedback routing): per instance, queued behind the queue
     int* pend_cnt;
     int *pend_prompt, *pend_len;
@@ -342,6 +343,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
     for (int r = 0; r < kEPL; ++r)
         if (r * kWave + lane < A) a.act_inst[a0 + r * kWave + lane] = g;
     if (status) atomicOr(&a.counters[0], status);
+    if (a.act_budget && (status & GR_DEV_ENTRIES_DROPPED)) *a.unset = 1;
     if (Q + P > 0) qsum = wave_sum_i64(qsum);   // Q and P are the same in every lane
     double q = cc.delta * (double)qsum;
 
@@ -359,6 +361,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
         for (int r = 0; r < kEPL; ++r) {
             const int i = r * kWave + lane;
             double fin = fin_lds[i];
+            if (a.act_budget && i < A && fin == kNoFinish) *a.unset = 1;      // (no token left to decode)
             if (i >= A + Q || fin == kNoFinish) continue;
             // (length and prompt as given are read again: kept through the events they would spill)
             const float bud = a.act_budget && i < A ? a.act_budget[a0 + i] : 0.f;
@@ -873,7 +876,10 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
         for (int r = 0; r < kEPL; ++r) stage[first + r * kWave + lane] = __int_as_float(bud_in[r]);
     }
     if (__ballot(bad)) status |= GR_DEV_LEN_CLAMPED;
-    if (status && lane == 0) atomicOr(&a.counters[0], status);
+    if (status && lane == 0) {
+        atomicOr(&a.counters[0], status);
+        if (a.act_budget && (status & GR_DEV_ENTRIES_DROPPED)) *a.unset = 1;
+    }
     if (a.act_budget) {      // the instance of each running request, for the migration pass of a risk scan
         const __amdgpu_buffer_rsrc_t b_inst = slice(a.act_inst, 4);
 #pragma unroll
@@ -1447,7 +1453,7 @@ int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s)
     b.instK = f->instK; b.tabS = f->tabS; b.slot_of = f->slot_of; b.slot_key = f->slot_key; b.counters = f->counters;
     b.n_active = in.n_active; b.n_queued = in.n_queued;
     b.n_inst = f->n_inst; b.max_entries = f->max_entries; b.max_len = f->max_len;
-    b.seen = f->seen; b.late_cnt = f->late_cnt;
+    b.seen = f->seen; b.late_cnt = f->late_cnt; b.unset = f->totals + 2;
     b.pend_cnt = f->pend_cnt; b.pend_prompt = f->pend_prompt; b.pend_len = f->pend_len;
     b.use_pending = in.use_pending;
     b.pend_touched = f->pend_touched; b.only_touched = in.use_pending && in.only_touched;
