@@ -15,6 +15,7 @@
 //
 // A batch of a few requests skips the table: a thread per pair with its own
 // two-step search (k_direct).
+#include <algorithm>
 #include <cfloat>
 
 #include "common.h"
@@ -542,6 +543,7 @@ struct SelectArgs {
     uint8_t* out_fallback;
     int m_pos, run_pad, n_run, n_class, c_pad, max_len;
     int segments;      // by classes first: workgroups of the launch
+    int64_t first;     // a group of lanes per request: the launch's first request
 };
 
 struct Request {
@@ -736,7 +738,7 @@ template <bool kMigrate, int kChunks>
 __global__ __launch_bounds__(kBlock) void k_select(SelectArgs a)
 {
     const int sub = threadIdx.x % kGroup;
-    const int64_t i = (int64_t)blockIdx.x * (kBlock / kGroup) + threadIdx.x / kGroup;
+    const int64_t i = a.first + (int64_t)blockIdx.x * (kBlock / kGroup) + threadIdx.x / kGroup;
     if (i >= a.s.n) return;
     const Request q = fetch<kMigrate>(a.s, i, a.max_len);
     if (!q.scored) {
@@ -794,7 +796,7 @@ template <bool kMigrate>
 __global__ __launch_bounds__(kBlock) void k_select_blended(SelectArgs a)
 {
     const int sub = threadIdx.x % kGroup;
-    const int64_t i = (int64_t)blockIdx.x * (kBlock / kGroup) + threadIdx.x / kGroup;
+    const int64_t i = a.first + (int64_t)blockIdx.x * (kBlock / kGroup) + threadIdx.x / kGroup;
     if (i >= a.s.n) return;
     const Request q = fetch<kMigrate>(a.s, i, a.max_len);
     if (!q.scored) {
@@ -896,13 +898,14 @@ struct PairsArgs {
     const float* memo;
     const float2* posK;
     float* out_T;
+    int64_t first;     // the launch's first request
     int n_inst, m_pos, max_len;
 };
 
 // Every pair's latency, for checking: the same arithmetic, exclusions not applied.
 __global__ __launch_bounds__(kBlock) void k_pairs(PairsArgs a)
 {
-    const int64_t r = blockIdx.x;
+    const int64_t r = a.first + blockIdx.x;
     const int L = min(max(a.pred_len[r], 0), a.max_len);
     const float c0 = (float)a.ctx0[r], Lf = (float)L;
     const float* __restrict__ E = a.memo + memo_at(a.len_row[L], 0, a.m_pos);
@@ -1224,16 +1227,15 @@ constexpr int64_t kByClassMin = int64_t(1) << 17;      // requests from which th
 // 38 us, with 512 33)
 constexpr int64_t kByClassMany = int64_t(1) << 19;
 
+// A launch has fewer than 2^32 threads: kernels that take many threads per request go through larger batches
+// (2^28 requests at 16 lanes each, 2^24 at a workgroup each) a part at a time.
+constexpr int64_t kLaunchThreads = int64_t(1) << 31;
+
 template <bool kMigrate>
 static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, bool blended, hipStream_t s)
 {
     const int64_t n = a.s.n;
-    const dim3 grid((unsigned)((n + kBlock / kGroup - 1) / (kBlock / kGroup)));
-    if (by_class && blended) {
-        hipLaunchKernelGGL(k_select_blended<kMigrate>, grid, dim3(kBlock), 0, s, a);
-        return;
-    }
-    if (by_class) {
+    if (by_class && !blended) {
         // large batches: two requests per lane of a whole workgroup; else a wave's worth per workgroup,
         // so that the second half has the lanes when many requests need it
         const bool many = n >= kByClassMany;
@@ -1243,9 +1245,14 @@ static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, bool b
         else hipLaunchKernelGGL((k_select_by_class<kMigrate, kWave, 1>), dim3(a.segments), dim3(kBlock), 0, s, a);
         return;
     }
-    if (f->n_run <= kGroup) hipLaunchKernelGGL((k_select<kMigrate, 1>), grid, dim3(kBlock), 0, s, a);
-    else if (f->n_run <= 2 * kGroup) hipLaunchKernelGGL((k_select<kMigrate, 2>), grid, dim3(kBlock), 0, s, a);
-    else hipLaunchKernelGGL((k_select<kMigrate, 4>), grid, dim3(kBlock), 0, s, a);
+    for (a.first = 0; a.first < n; a.first += kLaunchThreads / kGroup) {
+        const int64_t here = std::min(n - a.first, kLaunchThreads / kGroup);
+        const dim3 grid((unsigned)((here + kBlock / kGroup - 1) / (kBlock / kGroup)));
+        if (by_class) hipLaunchKernelGGL(k_select_blended<kMigrate>, grid, dim3(kBlock), 0, s, a);
+        else if (f->n_run <= kGroup) hipLaunchKernelGGL((k_select<kMigrate, 1>), grid, dim3(kBlock), 0, s, a);
+        else if (f->n_run <= 2 * kGroup) hipLaunchKernelGGL((k_select<kMigrate, 2>), grid, dim3(kBlock), 0, s, a);
+        else hipLaunchKernelGGL((k_select<kMigrate, 4>), grid, dim3(kBlock), 0, s, a);
+    }
 }
 
 int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& out, hipStream_t s,
@@ -1344,7 +1351,8 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         p.ctx0 = src.ctx0; p.pred_len = src.pred_len; p.len_row = f->len_row; p.order = f->order; p.memo = f->memo;
         p.posK = f->posK; p.out_T = out.T; p.n_inst = f->n_inst; p.m_pos = f->m_pos; p.max_len = f->max_len;
         ProfScope ps(f, kPairsRoute, s);
-        hipLaunchKernelGGL(k_pairs, dim3((unsigned)n), dim3(kBlock), 0, s, p);
+        for (p.first = 0; p.first < n; p.first += kLaunchThreads / kBlock)
+            hipLaunchKernelGGL(k_pairs, dim3((unsigned)std::min(n - p.first, kLaunchThreads / kBlock)), dim3(kBlock), 0, s, p);
     }
     return hipGetLastError() == hipSuccess ? GR_OK : GR_ERR_HIP;
 }
