@@ -125,6 +125,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     f->row_cap = f->req_cap < f->bins ? f->req_cap : f->bins;
     f->row_cap = (f->row_cap + kMemoU - 1) / kMemoU * kMemoU;
     if (f->row_cap < kMemoU) f->row_cap = kMemoU;
+    f->turned_rows = (int)std::min<int64_t>(f->row_cap, std::max<int64_t>(kTurnedBytes / ((int64_t)n_inst * 4 * kMemoU), 1) * kMemoU);
     if (hipGetDevice(&f->device) != hipSuccess) { delete f; return GR_ERR_HIP; }
 
     const size_t tab = (size_t)n_inst * f->cap, seen_bytes = (size_t)(f->bins + 15) / 16 * 16;
@@ -144,7 +145,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
         dev_alloc(&f->memo, (size_t)f->row_cap * f->m_pos) && dev_alloc(&f->grp_min, (size_t)f->row_cap * f->run_pad) &&
         dev_alloc(&f->run_k, f->n_run) && dev_alloc(&f->class_min, (size_t)f->row_cap * f->c_pad) &&
         dev_alloc(&f->cls_bound, n_class) && dev_alloc(&f->class_next, (size_t)f->row_cap * n_class) &&
-        dev_alloc(&f->direct_part, (size_t)kDirectParts);
+        dev_alloc(&f->turned, (size_t)f->turned_rows * n_inst) && dev_alloc(&f->direct_part, (size_t)kDirectParts);
     if (!ok) { gr_destroy(f); return GR_ERR_NOMEM; }
 
     bool sent = true;
@@ -189,7 +190,7 @@ int gr_destroy(gr_fleet* f)
     void* ptrs[] = {f->cls, f->inst_class, f->tabR, f->tabGH, f->hN, f->hD, f->emaQ, f->emaP, f->emaD, f->instK, f->tabS,
                     f->clsK, f->slot_inst, f->slot_of, f->slot_key, f->run_cls, f->cls_run, f->order, f->pos_of, f->posK, f->posKey, f->run_head, f->act_inst, f->pend_cnt, f->commit_mark, f->pend_touched, f->pend_prompt, f->pend_len,
                     f->scratch_finish, f->batch_cap, f->counters, f->seen, f->late_cnt, f->row_len,
-                    f->len_row, f->totals, f->memo, f->grp_min, f->run_k, f->class_min, f->cls_bound, f->class_next, f->direct_part};
+                    f->len_row, f->totals, f->memo, f->grp_min, f->run_k, f->class_min, f->cls_bound, f->class_next, f->turned, f->direct_part};
     int rc = GR_OK;
     for (void* p : ptrs)
         if (p && hipFree(p) != hipSuccess) rc = GR_ERR_HIP;

@@ -41,6 +41,7 @@ constexpr int kDirectMax = 4096;   // most requests of a batch scored pair by pa
 constexpr int kDirectSpan = 4096;  // instances that one workgroup takes of a request scored pair by pair
 constexpr int kDirectParts = 16384;  // room for the selections of such parts
 constexpr int kMemoP = 16;         // positions of a run of the class order
+constexpr int64_t kTurnedBytes = int64_t(64) << 20;   // room for rows of the table over the instances, where 256 rows fit
 
 // Splitters of an instance's sorted lengths, by table size (strides of 8, 8, 16, 32, 32, 64 lengths).
 constexpr int split_count(int cap) { return cap <= 64 ? 8 : cap <= 512 ? 16 : 32; }
@@ -192,6 +193,8 @@ struct gr_fleet {
     float4* run_k = nullptr;     // [n_run] least delta of the run, gamma, largest delta, lowest instance (int bits)
     float* class_min = nullptr;  // [row_cap][c_pad] least E of each class, per row
     float4* cls_bound = nullptr; // [n_class] least delta of the class, gamma, largest delta
+    float* turned = nullptr;     // [turned_rows][M] a part of memo with a row's values together, for out_T
+    int turned_rows = 0;         // multiple of kMemoU
     uint2* class_next = nullptr; // [row_cap][n_class] next larger E of the class (bits), lowest instance that has the least
     // What the host knows of the tables.  A call that is being recorded runs nothing, and what it records
     // changes the tables at every replay without the host: calls of a capture keep an account of their

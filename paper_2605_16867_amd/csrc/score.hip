@@ -891,30 +891,6 @@ __global__ __launch_bounds__(kBlock) void k_select_by_class(SelectArgs a)
     }
 }
 
-struct PairsArgs {
-    const int *ctx0, *pred_len;
-    const uint16_t* len_row;
-    const int* order;
-    const float* memo;
-    const float2* posK;
-    float* out_T;
-    int64_t first;     // the launch's first request
-    int n_inst, m_pos, max_len;
-};
-
-// Every pair's latency, for checking: the same arithmetic, exclusions not applied.
-__global__ __launch_bounds__(kBlock) void k_pairs(PairsArgs a)
-{
-    const int64_t r = a.first + blockIdx.x;
-    const int L = min(max(a.pred_len[r], 0), a.max_len);
-    const float c0 = (float)a.ctx0[r], Lf = (float)L;
-    const float* __restrict__ E = a.memo + memo_at(a.len_row[L], 0, a.m_pos);
-    for (int p = threadIdx.x; p < a.m_pos; p += kBlock) {
-        const int g = a.order[p];
-        if (g >= 0) a.out_T[(size_t)r * a.n_inst + g] = fmaf(c0, kappa_of(a.posK[p], Lf), E[(size_t)p * kMemoU]);
-    }
-}
-
 // ------------------------------------------------------------------ cached prefixes
 struct HitArgs {
     const int *ctx0, *pred_len;
@@ -1180,6 +1156,136 @@ __global__ __launch_bounds__(kBlock) void k_direct_merge(DirectArgs a)
     if (lane_id() == 0) direct_answer(a, r, best);
 }
 
+// ------------------------------------------------------------------ every pair's latency (out_T)
+// The table keeps a position's values of 256 rows together, a request wants one row of every instance: read
+// as it is, every 4-byte value is a cache line of its own (65 536 requests x 256 instances 60 us, 262 144 x 64
+// 105 us, written at 1.1 and 0.6 TB/s).  So `rows` lengths at a time the table is first turned into rows over the
+// instances (k_rows, as much as the lengths, not the requests), and the latencies are then a
+// stream over those (k_pairs).
+struct PairsArgs {
+    const int *ctx0, *pred_len, *totals;
+    const float* budget;
+    const int* exclude;
+    const double* hD;
+    int* out_inst;
+    float* out_slack;
+    uint8_t* out_fallback;
+    const uint16_t* len_row;
+    const int* order;
+    const float* memo;
+    const float4* instK;
+    float* turned;     // [rows][n_inst]
+    float* out_T;
+    int64_t n, first;  // requests; the launch's first one
+    int row0, rows;    // the part of the table at hand
+    int n_inst, m_pos, max_len;
+};
+
+// Requests that a group of lanes takes together (with the selections, which take six registers each: fewer).
+constexpr int pairs_requests(bool select) { return select ? 4 : 8; }
+
+__global__ __launch_bounds__(kBlock) void k_rows(PairsArgs a)
+{
+    __shared__ float tile[kWave][kWave + 1];
+    const int blocks = (a.m_pos + kWave - 1) / kWave;
+    const int p0 = (int)(blockIdx.x % blocks) * kWave, u0 = (int)(blockIdx.x / blocks) * kWave;   // row u0 of the part
+    if (a.row0 + u0 >= a.totals[1]) return;
+    const int lane = lane_id(), wave = threadIdx.x / kWave;
+    constexpr int kPer = kWave / (kBlock / kWave);
+    float v[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+        v[i] = a.memo[memo_at(a.row0 + u0, min(p0 + wave * kPer + i, a.m_pos - 1), a.m_pos) + lane];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) tile[wave * kPer + i][lane] = v[i];
+    __syncthreads();
+    const int g = p0 + lane < a.m_pos ? a.order[p0 + lane] : -1;
+    if (g < 0) return;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) a.turned[(size_t)(u0 + wave * kPer + i) * a.n_inst + g] = tile[lane][wave * kPer + i];
+}
+
+// The same arithmetic as the selection's, exclusions not applied.  kLanes lanes take kReq requests together (one
+// request is a chain of three reads and, on a small fleet, one store), kVec instances each.
+//
+// kSelect: with every latency of a request in its lanes' registers, Alg. 1 is decided here as well and the
+// selection over runs is not launched.  On a small fleet that took longer than the latencies
+// themselves: whole call on 262 144 requests x 64 instances 59 us with it, 46 without; 100 000 x 128 without it 40 us, x 129
+// with it 50 (a row of lanes per request is kept up to 128 instances: eight of them per lane).
+template <int kLanes, int kVec, bool kSelect>
+__global__ __launch_bounds__(kBlock) void k_pairs(PairsArgs a)
+{
+    constexpr int kReq = pairs_requests(kSelect);
+    static_assert(!kSelect || kLanes == 16, "a request's lanes are a row of a wave");
+    if (a.row0 >= a.totals[1]) return;
+    const int sub = threadIdx.x % kLanes;
+    const int64_t r0 = a.first + ((int64_t)blockIdx.x * (kBlock / kLanes) + threadIdx.x / kLanes) * kReq;
+    if (r0 >= a.n) return;
+    int L[kReq], row[kReq], ex[kReq];
+    float c0[kReq], D[kReq];
+    // the lane's selections (its instances come in ascending order, so of equal ones the first stays)
+    float anyT[kReq], feasT[kReq];
+    int anyG[kReq], feasG[kReq];
+    unsigned long long feasKey[kReq];
+#pragma unroll
+    for (int j = 0; j < kReq; ++j) {
+        const int64_t r = min(r0 + j, a.n - 1);
+        L[j] = min(max(a.pred_len[r], 0), a.max_len);
+        c0[j] = (float)a.ctx0[r];
+        if (kSelect) { D[j] = a.budget[r]; ex[j] = a.exclude ? a.exclude[r] : -1; }
+        anyT[j] = __builtin_inff(); feasT[j] = 0.f; anyG[j] = feasG[j] = -1; feasKey[j] = ~0ull;
+    }
+#pragma unroll
+    for (int j = 0; j < kReq; ++j) {
+        row[j] = a.len_row[L[j]] - a.row0;
+        if (r0 + j >= a.n || (unsigned)row[j] >= (unsigned)a.rows) row[j] = -1;
+    }
+    struct alignas(4 * kVec) Values { float v[kVec]; };
+    for (int g = sub * kVec; g < a.n_inst; g += kLanes * kVec) {
+        float2 K[kVec];
+        unsigned long long key[kVec];
+#pragma unroll
+        for (int i = 0; i < kVec; ++i) {
+            const float4 k = a.instK[g + i];
+            K[i] = make_float2(k.x, k.y);
+            if (kSelect) key[i] = falling_bits(a.hD[g + i]);
+        }
+        Values E[kReq];
+#pragma unroll
+        for (int j = 0; j < kReq; ++j) E[j] = *reinterpret_cast<const Values*>(a.turned + (size_t)max(row[j], 0) * a.n_inst + g);
+#pragma unroll
+        for (int j = 0; j < kReq; ++j) {
+            if (row[j] < 0) continue;
+            const float Dc = D[j] > FLT_MAX ? FLT_MAX : D[j];
+#pragma unroll
+            for (int i = 0; i < kVec; ++i) {
+                const float T = fmaf(c0[j], kappa_of(K[i], (float)L[j]), E[j].v[i]);
+                E[j].v[i] = T;
+                if (!kSelect) continue;
+                const float mine = g + i == ex[j] ? __builtin_inff() : T;      // (an infinite latency is none, as in the selection over runs)
+                const bool less = mine < anyT[j], better = mine <= Dc && key[i] < feasKey[j];
+                anyT[j] = less ? mine : anyT[j]; anyG[j] = less ? g + i : anyG[j];
+                feasKey[j] = better ? key[i] : feasKey[j]; feasG[j] = better ? g + i : feasG[j]; feasT[j] = better ? mine : feasT[j];
+            }
+            *reinterpret_cast<Values*>(a.out_T + (size_t)(r0 + j) * a.n_inst + g) = E[j];
+        }
+    }
+    if constexpr (kSelect) {
+#pragma unroll
+        for (int j = 0; j < kReq; ++j) {
+            const DirectPart b = best_over<true>(DirectPart{anyG[j] >= 0 ? ordered_bits(anyT[j]) : ~0u, (uint32_t)anyG[j],
+                                                            (uint32_t)(feasKey[j] >> 32), (uint32_t)feasKey[j], (uint32_t)feasG[j],
+                                                            feasG[j] >= 0 ? ordered_bits(feasT[j]) : ~0u});
+            if (sub != 0 || row[j] < 0) continue;
+            const bool found = b.g != ~0u;
+            const int g = (int)(found ? b.g : b.any_g);          // (-1: nobody is allowed)
+            a.out_inst[r0 + j] = g;
+            a.out_slack[r0 + j] = g >= 0 ? D[j] - from_ordered_bits(found ? b.T : b.any_T) : 0.f;
+            if (a.out_fallback) a.out_fallback[r0 + j] = !found;
+        }
+    }
+}
+
 __global__ void k_set_int(int* p, int v) { *p = v; }
 
 }  // namespace
@@ -1255,6 +1361,51 @@ static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, bool b
     }
 }
 
+// How the latencies of out_T are written: four instances per lane where every row begins at a multiple of 16
+// bytes; few lanes per request on a small fleet, whose rows are short; and whether Alg. 1 is decided there.
+struct PairsPlan {
+    bool four, select;
+    int lanes;
+
+    PairsPlan(const gr_fleet* f, const float* out_T)
+    {
+        const int M = f->n_inst;
+        four = M % 4 == 0 && M >= 64 && reinterpret_cast<uintptr_t>(out_T) % 16 == 0;
+        select = M <= 128;
+        lanes = select ? 16 : M <= 512 ? kWave : kBlock;
+    }
+};
+
+static void launch_pairs(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, const PairsPlan& plan, int64_t max_rows,
+                         hipStream_t s)
+{
+    PairsArgs p{};
+    p.ctx0 = src.ctx0; p.pred_len = src.pred_len; p.budget = src.budget; p.exclude = src.exclude;
+    p.totals = f->totals; p.len_row = f->len_row; p.order = f->order; p.memo = f->memo; p.instK = f->instK; p.hD = f->hD;
+    p.turned = f->turned; p.out_T = out.T; p.out_inst = out.inst; p.out_slack = out.slack; p.out_fallback = out.fallback;
+    p.n = src.n; p.rows = f->turned_rows; p.n_inst = f->n_inst; p.m_pos = f->m_pos; p.max_len = f->max_len;
+    const int64_t per = kBlock / plan.lanes * pairs_requests(plan.select), most = kLaunchThreads / kBlock * per;
+    // (parts for as many rows as there may be; those past the last row end at once)
+    for (p.row0 = 0; p.row0 < max_rows; p.row0 += p.rows) {
+        {
+            const int64_t rows = std::min<int64_t>(max_rows - p.row0, p.rows);
+            ProfScope ps(f, kPairsRoute, s);
+            hipLaunchKernelGGL(k_rows, dim3((unsigned)((rows + kWave - 1) / kWave * ((f->m_pos + kWave - 1) / kWave))), dim3(kBlock), 0, s, p);
+        }
+        for (p.first = 0; p.first < p.n; p.first += most) {
+            const dim3 grid((unsigned)((std::min(p.n - p.first, most) + per - 1) / per));
+            ProfScope ps(f, kPairsRoute, s);
+#define GR_LAUNCH_PAIRS(N, S) do { \
+            if (plan.four) hipLaunchKernelGGL((k_pairs<N, 4, S>), grid, dim3(kBlock), 0, s, p); \
+            else hipLaunchKernelGGL((k_pairs<N, 1, S>), grid, dim3(kBlock), 0, s, p); } while (0)
+            if (plan.lanes == 16) GR_LAUNCH_PAIRS(16, true);
+            else if (plan.lanes == kWave) GR_LAUNCH_PAIRS(kWave, false);
+            else GR_LAUNCH_PAIRS(kBlock, false);
+#undef GR_LAUNCH_PAIRS
+        }
+    }
+}
+
 int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& out, hipStream_t s,
                  bool small_batch_ok)
 {
@@ -1302,7 +1453,9 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     // 512 x 512 requests 57.6 / 41.2 (42.0 / 42.0), 4 096 x 512 544 / 110 (278 / 137).
     // With a blend the classes only rule out whole classes: 4 096 x 400 435 / 372 (221 / 195), and nothing
     // is won where a group reads all runs at once (64).
-    const bool by_class = n >= kByClassMin && f->n_class <= kGroup && f->n_run >= 4 * f->n_class &&
+    const PairsPlan pairs(f, out.T);
+    const bool select = !(out.T && pairs.select);
+    const bool by_class = select && n >= kByClassMin && f->n_class <= kGroup && f->n_run >= 4 * f->n_class &&
                           f->n_run >= (blended ? 8 * kGroup : migrate ? 2 * kGroup : 4 * kGroup);
     // The runs' minima in blocks of rows where few requests get as far as the runs (6 us less for the
     // table of 7 061 rows x 4 096 instances); row by row where many may: a request's 16 lanes then read 16
@@ -1335,7 +1488,7 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         if (blocks) hipLaunchKernelGGL(k_class<true>, grid, dim3(kBlock), 0, s, c);
         else hipLaunchKernelGGL(k_class<false>, grid, dim3(kBlock), 0, s, c);
     }
-    {
+    if (select) {
         SelectArgs a{};
         a.s = src; a.len_row = f->len_row; a.order = f->order; a.memo = f->memo; a.grp_min = f->grp_min; a.run_k = f->run_k;
         a.posK = f->posK; a.posKey = f->posKey; a.run_head = f->run_head; a.cls_run = f->cls_run; a.class_min = f->class_min; a.class_next = f->class_next; a.clsK = f->clsK; a.cls_bound = f->cls_bound;
@@ -1346,14 +1499,7 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         if (migrate) launch_select<true>(f, a, by_class, blended, s);
         else launch_select<false>(f, a, by_class, blended, s);
     }
-    if (out.T) {
-        PairsArgs p{};
-        p.ctx0 = src.ctx0; p.pred_len = src.pred_len; p.len_row = f->len_row; p.order = f->order; p.memo = f->memo;
-        p.posK = f->posK; p.out_T = out.T; p.n_inst = f->n_inst; p.m_pos = f->m_pos; p.max_len = f->max_len;
-        ProfScope ps(f, kPairsRoute, s);
-        for (p.first = 0; p.first < n; p.first += kLaunchThreads / kBlock)
-            hipLaunchKernelGGL(k_pairs, dim3((unsigned)std::min(n - p.first, kLaunchThreads / kBlock)), dim3(kBlock), 0, s, p);
-    }
+    if (out.T) launch_pairs(f, src, out, pairs, max_rows, s);
     return hipGetLastError() == hipSuccess ? GR_OK : GR_ERR_HIP;
 }
 
