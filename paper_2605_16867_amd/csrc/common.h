@@ -190,6 +190,8 @@ struct gr_fleet {
     int* totals = nullptr;    // [4] -, distinct lengths, 1: flags that the risk scan's build has not set (zero between calls)
     float* memo = nullptr;       // [row_cap / kMemoU][m_pos][kMemoU] E per distinct length and position
     float* grp_min = nullptr;    // [row_cap][run_pad] least E of each run, per row (see runs_at)
+    uint32_t* run_rank = nullptr;   // [n_run] runs whose first instance is more capable than the run's first
+    uint32_t* pos_thr = nullptr;    // [m_pos] runs whose first instance is more capable than the position's
     float4* run_k = nullptr;     // [n_run] least delta of the run, gamma, largest delta, lowest instance (int bits)
     float* class_min = nullptr;  // [row_cap][c_pad] least E of each class, per row
     float4* cls_bound = nullptr; // [n_class] least delta of the class, gamma, largest delta

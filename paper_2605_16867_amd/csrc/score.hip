@@ -172,7 +172,10 @@ struct MemoArgs {
     float* memo;           // see memo_at
     float* grp_min;        // see runs_at
     float4* run_k;         // [n_run]
+    uint32_t *run_rank, *pos_thr;   // [n_run], [m_pos], see gr_fleet
     const float2* posK;
+    const unsigned long long* posKey;
+    const uint4* run_head;
     uint4* seen;           // cleared here for the next batch (its reader is done), as is totals[2]
     int seen_words;        // of 16 bytes
     int n_run, m_pos, run_pad, cap;
@@ -221,6 +224,33 @@ constexpr int kMemoWaves = kBlock / kWave;
 constexpr int kMemoInst = kMemoP / kMemoWaves;      // instances of a wave
 static_assert(kMemoU == 4 * kWave, "a lane owns four consecutive rows");
 
+// For each position of a run, how many runs begin with a more capable instance: 16 lanes each.
+__device__ __forceinline__ void rank_run(const MemoArgs& a, int run)
+{
+    static_assert(kBlock == kMemoP * kMemoP, "16 lanes per position of the run");
+    const int p = run * kMemoP + threadIdx.x / kMemoP, sub = threadIdx.x % kMemoP;
+    const unsigned long long key = a.posKey[p];
+    const int g = a.order[p];
+    uint32_t n = 0;
+    constexpr int kAhead = 8;
+    for (int r0 = sub; r0 < a.n_run; r0 += kAhead * kMemoP) {
+        uint4 h[kAhead];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) h[i] = a.run_head[min(r0 + i * kMemoP, a.n_run - 1)];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+            const unsigned long long hk = ((unsigned long long)h[i].y << 32) | h[i].x;
+            n += r0 + i * kMemoP < a.n_run && (hk < key || (hk == key && (int)h[i].z < g));
+        }
+    }
+#pragma unroll
+    for (int d = 1; d < kMemoP; d <<= 1) n += __shfl_xor(n, d, kMemoP);
+    if (sub == 0) {
+        a.pos_thr[p] = n;
+        if (threadIdx.x == 0) a.run_rank[run] = n;
+    }
+}
+
 template <bool kLargeTab, bool kBlocks>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 7))) void k_memo(MemoArgs a)
 {
@@ -230,9 +260,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 7))) 
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < a.seen_words; i += gridDim.x * kBlock)
         a.seen[i] = make_uint4(0u, 0u, 0u, 0u);
     if (blockIdx.x == 0 && threadIdx.x == 0) a.totals[2] = 0;
+    // (the first n_run workgroups rank the runs for the selection: next to the others, not behind them)
+    if ((int)blockIdx.x < a.n_run) return rank_run(a, blockIdx.x);
     const int U = a.totals[1];
     const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int pass = blockIdx.x / a.n_run, run = blockIdx.x % a.n_run;
+    const int pass = blockIdx.x / a.n_run - 1, run = blockIdx.x % a.n_run;
     const int ub = pass * kMemoU, ue = min(ub + kMemoU, U);
     if (ub >= ue) return;
     const int p0 = run * kMemoP + wave * kMemoInst;
@@ -532,7 +564,7 @@ struct SelectArgs {
     const float4* run_k;
     const float2* posK;
     const unsigned long long* posKey;
-    const uint4* run_head;
+    const uint32_t *run_rank, *pos_thr;
     const int2* cls_run;
     const float* class_min;
     const uint2* class_next;
@@ -579,7 +611,9 @@ __device__ __forceinline__ void answer(const SelectArgs& a, int64_t i, int g, fl
 //
 // Feasible choice (scan<true, .>): of every run whose bound meets the deadline and whose most capable
 // instance would be an improvement, the first feasible position (a run's positions are in
-// capability order, and classes of slow steps come first).  Least latency (scan<., true>, then
+// capability order, and classes of slow steps come first).  The improvement is one comparison: the runs are
+// ranked by their first instances, and every position knows how many runs begin with a better one (with
+// the d_g themselves, 64 bits and the index on ties, the search took half of the selection's instructions).  Least latency (scan<., true>, then
 // settle): the run with the least bound is looked at, then every other run whose bound does not
 // exceed the least latency at hand (equal ones only if they hold a lower instance).  kChunks x
 // kGroup runs are read together: the reads of the runs' values are what a request waits for.
@@ -594,6 +628,7 @@ struct Selection {
     unsigned long long feasKey = ~0ull;
     int feasG = -1;
     float feasT = 0.f;
+    uint32_t feasThr = ~0u;      // runs of a smaller rank may hold a better one
     // the least latency so far
     float bestT = __builtin_inff();
     int bestG = -1;
@@ -611,11 +646,6 @@ struct Selection {
         return fmaf(c0, kappa_of(make_float2(c0 >= 0.f ? k.x : k.z, k.y), Lf), e);
     }
 
-    __device__ __forceinline__ bool improves(unsigned long long key, int g) const
-    {
-        return feasG < 0 || key < feasKey || (key == feasKey && g < feasG);
-    }
-
     template <bool kFeasible, bool kLeast>
     __device__ __forceinline__ void scan(int first, int n)
     {
@@ -624,15 +654,15 @@ struct Selection {
         for (int r0 = 0; r0 < n; r0 += kChunks * kGroup) {
             float b[kChunks];
             float4 k[kChunks];
-            uint4 head[kChunks];      // (read with the rest where a feasible run is known to be there)
+            uint32_t rank[kChunks];      // (read with the rest where a feasible run is known to be there)
 #pragma unroll
             for (int j = 0; j < kChunks; ++j) {
                 const int r = first + min(r0 + j * kGroup + sub, n - 1);
-                if (!kLeast) head[j] = a.run_head[r];
+                if (!kLeast) rank[j] = a.run_rank[r];
                 b[j] = runs[(size_t)r * kRunStride<kBlocks>];
                 k[j] = a.run_k[r];
             }
-            uint32_t any = 0;
+            bool any = false;
 #pragma unroll
             for (int j = 0; j < kChunks; ++j) {
                 const int r = r0 + j * kGroup + sub;
@@ -641,30 +671,25 @@ struct Selection {
                     if (b[j] < m1) { m2 = m1; m1 = b[j]; r1 = first + r; }
                     else m2 = fminf(m2, b[j]);
                 }
-                if (kFeasible) any |= group_ballot(b[j] <= Dc);
+                if (kFeasible) any = any || b[j] <= Dc;
             }
-            if (!kFeasible || !any) continue;
-            bool in[kChunks];
+            if (!kFeasible || !__any(any)) continue;
 #pragma unroll
             for (int j = 0; j < kChunks; ++j) {
-                if (kLeast) head[j] = a.run_head[first + min(r0 + j * kGroup + sub, n - 1)];
-                in[j] = b[j] <= Dc;
+                if (kLeast) rank[j] = a.run_rank[first + min(r0 + j * kGroup + sub, n - 1)];
+                if (!(b[j] <= Dc)) rank[j] = ~0u;      // (not, or no longer, in question)
             }
             for (;;) {
-                int run = -1;       // the first run in question
+                uint32_t at = ~0u;       // the first run in question
 #pragma unroll
-                for (int j = 0; j < kChunks; ++j) {
-                    const unsigned long long key = ((unsigned long long)head[j].y << 32) | head[j].x;
-                    const uint32_t mask = group_ballot(in[j] && improves(key, (int)head[j].z));
-                    const int l = __ffs(mask) - 1;
-                    if (run < 0 && mask) {
-                        run = first + r0 + j * kGroup + l;
-                        in[j] = in[j] && sub != l;
-                    }
-                }
-                if (run < 0) break;
-                const int p = run * kMemoP + sub, g = a.order[p];
+                for (int j = kChunks - 1; j >= 0; --j) at = rank[j] < feasThr ? j * kGroup + sub : at;
+                at = min_over<true>(at);
+                if (at == ~0u) break;
+#pragma unroll
+                for (int j = 0; j < kChunks; ++j) rank[j] = at == (uint32_t)(j * kGroup + sub) ? ~0u : rank[j];
+                const int p = (first + r0 + (int)at) * kMemoP + sub, g = a.order[p];
                 const unsigned long long pk = a.posKey[p];
+                const uint32_t thr = a.pos_thr[p];
                 const float T = fmaf(c0, kappa_of(a.posK[p], Lf), E[(size_t)p * kMemoU]);
                 const uint32_t hit = group_ballot(T <= Dc && g >= 0 && g != ex);
                 if (!hit) continue;
@@ -672,7 +697,10 @@ struct Selection {
                 const unsigned long long hk = group_lane(pk, h);
                 const int hg = group_lane(g, h);
                 const float hT = group_lane(T, h);
-                if (improves(hk, hg)) { feasKey = hk; feasG = hg; feasT = hT; }
+                const uint32_t ht = group_lane(thr, h);
+                if (feasG < 0 || hk < feasKey || (hk == feasKey && hg < feasG)) {
+                    feasKey = hk; feasG = hg; feasT = hT; feasThr = ht;
+                }
             }
         }
     }
@@ -761,17 +789,14 @@ __device__ __forceinline__ void select_by_class(const SelectArgs& a, int64_t i, 
     const int c = min(sub, a.n_class - 1);
     const float e = a.class_min[(size_t)row * a.c_pad + c];
     const int2 range = a.cls_run[c];
-    const uint4 head = a.run_head[min(range.x, a.n_run - 1)];
-    const unsigned long long key = ((unsigned long long)head.y << 32) | head.x;
+    const uint32_t rank = a.run_rank[min(range.x, a.n_run - 1)];      // (of the class's most capable instance)
     const float T = sub < a.n_class && e < inf ? sel.bound(e, a.cls_bound[c]) : inf;      // (none of the class's is less)
-    bool feasible = T <= sel.Dc;
+    uint32_t left_rank = T <= sel.Dc ? rank : ~0u;
     for (;;) {
-        const bool in = feasible && sel.improves(key, (int)head.z);
-        if (!group_ballot(in)) break;
-        const uint32_t hi = min_over<true>(in ? head.y : ~0u);
-        const uint32_t lo = min_over<true>(in && head.y == hi ? head.x : ~0u);
-        const int l = __ffs(group_ballot(in && head.y == hi && head.x == lo)) - 1;      // the most capable of them
-        feasible = feasible && sub != l;
+        const uint32_t least = min_over<true>(left_rank < sel.feasThr ? left_rank : ~0u);      // the most capable of them
+        if (least == ~0u) break;
+        const int l = __ffs(group_ballot(left_rank == least)) - 1;
+        if (sub == l) left_rank = ~0u;
         sel.template scan<true, false>(group_lane(range.x, l), group_lane(range.y, l));
     }
     if (sel.feasG < 0) {
@@ -1351,13 +1376,20 @@ static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, bool b
         else hipLaunchKernelGGL((k_select_by_class<kMigrate, kWave, 1>), dim3(a.segments), dim3(kBlock), 0, s, a);
         return;
     }
+    // 16 runs per lane group and chunk: as few rounds as five chunks make, and no more chunks than fill them
+    // (1 024 instances of three classes are 66 runs: two rounds of four chunks for two runs more than one)
+    const int all = (f->n_run + kGroup - 1) / kGroup, rounds = (all + 4) / 5, chunks = (all + rounds - 1) / rounds;
     for (a.first = 0; a.first < n; a.first += kLaunchThreads / kGroup) {
         const int64_t here = std::min(n - a.first, kLaunchThreads / kGroup);
         const dim3 grid((unsigned)((here + kBlock / kGroup - 1) / (kBlock / kGroup)));
         if (by_class) hipLaunchKernelGGL(k_select_blended<kMigrate>, grid, dim3(kBlock), 0, s, a);
-        else if (f->n_run <= kGroup) hipLaunchKernelGGL((k_select<kMigrate, 1>), grid, dim3(kBlock), 0, s, a);
-        else if (f->n_run <= 2 * kGroup) hipLaunchKernelGGL((k_select<kMigrate, 2>), grid, dim3(kBlock), 0, s, a);
-        else hipLaunchKernelGGL((k_select<kMigrate, 4>), grid, dim3(kBlock), 0, s, a);
+        else switch (chunks) {
+            case 1: hipLaunchKernelGGL((k_select<kMigrate, 1>), grid, dim3(kBlock), 0, s, a); break;
+            case 2: hipLaunchKernelGGL((k_select<kMigrate, 2>), grid, dim3(kBlock), 0, s, a); break;
+            case 3: hipLaunchKernelGGL((k_select<kMigrate, 3>), grid, dim3(kBlock), 0, s, a); break;
+            case 4: hipLaunchKernelGGL((k_select<kMigrate, 4>), grid, dim3(kBlock), 0, s, a); break;
+            default: hipLaunchKernelGGL((k_select<kMigrate, 5>), grid, dim3(kBlock), 0, s, a);
+        }
     }
 }
 
@@ -1465,11 +1497,12 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         MemoArgs m{};
         m.totals = f->totals; m.row_len = f->row_len; m.len_row = f->len_row; m.order = f->order; m.instK = f->instK;
         m.tabR = f->tabR; m.tabS = f->tabS; m.tabGH = f->tabGH; m.memo = f->memo; m.grp_min = f->grp_min;
-        m.run_k = f->run_k; m.posK = f->posK;
+        m.run_k = f->run_k; m.run_rank = f->run_rank; m.pos_thr = f->pos_thr; m.posK = f->posK; m.posKey = f->posKey;
+        m.run_head = f->run_head;
         m.seen = reinterpret_cast<uint4*>(f->seen); m.seen_words = (f->bins + 15) / 16;
         m.n_run = f->n_run; m.m_pos = f->m_pos; m.run_pad = f->run_pad; m.cap = f->cap;
         // (workgroups for as many rows as there may be; those past the last row end at once)
-        const dim3 grid((unsigned)(f->n_run * ((max_rows + kMemoU - 1) / kMemoU)));
+        const dim3 grid((unsigned)(f->n_run * (1 + (max_rows + kMemoU - 1) / kMemoU)));
         ProfScope ps(f, kMemoRoute + off, s);
 #define GR_LAUNCH_MEMO(B) do { \
         if (f->cap > 512) hipLaunchKernelGGL((k_memo<true, B>), grid, dim3(kBlock), 0, s, m); \
@@ -1491,7 +1524,7 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     if (select) {
         SelectArgs a{};
         a.s = src; a.len_row = f->len_row; a.order = f->order; a.memo = f->memo; a.grp_min = f->grp_min; a.run_k = f->run_k;
-        a.posK = f->posK; a.posKey = f->posKey; a.run_head = f->run_head; a.cls_run = f->cls_run; a.class_min = f->class_min; a.class_next = f->class_next; a.clsK = f->clsK; a.cls_bound = f->cls_bound;
+        a.posK = f->posK; a.posKey = f->posKey; a.run_rank = f->run_rank; a.pos_thr = f->pos_thr; a.cls_run = f->cls_run; a.class_min = f->class_min; a.class_next = f->class_next; a.clsK = f->clsK; a.cls_bound = f->cls_bound;
         a.out_inst = out.inst; a.out_slack = out.slack; a.out_fallback = out.fallback;
         a.m_pos = f->m_pos; a.run_pad = f->run_pad; a.n_run = f->n_run; a.n_class = f->n_class; a.c_pad = f->c_pad;
         a.max_len = f->max_len;
