@@ -41,6 +41,11 @@ constexpr int kDirectMax = 4096;   // most requests of a batch scored pair by pa
 constexpr int kDirectSpan = 4096;  // instances that one workgroup takes of a request scored pair by pair
 constexpr int kDirectParts = 16384;  // room for the selections of such parts
 constexpr int kMemoP = 16;         // positions of a run of the class order
+constexpr int kRanges = 4;         // ranges of prompt lengths that a length's possible least latencies are looked up for
+constexpr int kRestParts = 64;     // lists of requests that those do not decide
+constexpr int kRestStride = 16;    // ints from one list's counter to the next: a cache line each
+constexpr int kRestItems = 2;      // requests per thread that append to a list
+constexpr int kRestRuns = 1024;    // most runs of a fleet whose requests are decided that way
 constexpr int64_t kTurnedBytes = int64_t(64) << 20;   // room for rows of the table over the instances, where 256 rows fit
 
 // Splitters of an instance's sorted lengths, by table size (strides of 8, 8, 16, 32, 32, 64 lengths).
@@ -83,8 +88,8 @@ struct DirectPart {
 };
 
 enum KernelId {
-    kBuild = 0, kRank, kMarkRoute, kScanRoute, kMemoRoute, kClassRoute, kSelectRoute,
-    kScanMigrate, kMemoMigrate, kClassMigrate, kSelectMigrate, kHitsRoute, kPairsRoute, kDirect, kDirectMerge,
+    kBuild = 0, kRank, kMarkRoute, kScanRoute, kMemoRoute, kClassRoute, kLinesRoute, kSelectRoute,
+    kScanMigrate, kMemoMigrate, kClassMigrate, kLinesMigrate, kSelectMigrate, kHitsRoute, kPairsRoute, kDirect, kDirectMerge,
     kNumKernels
 };
 
@@ -177,7 +182,7 @@ struct gr_fleet {
     int* commit_mark = nullptr;   // [M] 1: chosen by a request of the chunk being committed (all zero between commits)
     int* pend_prompt = nullptr;   // [M][cap]
     int* pend_len = nullptr;      // [M][cap]
-    float* scratch_finish = nullptr;  // [max_active] finish times of rebuilds nobody asked to see
+    float* scratch_finish = nullptr;  // [max_active + kBlock * kRestItems] finish times of rebuilds nobody asked to see
     int* batch_cap = nullptr;     // [M] requests that may decode together on each instance
     bool has_cap = false;
     int* counters = nullptr; // [1] GR_DEV_* bits
@@ -191,10 +196,13 @@ struct gr_fleet {
     float* memo = nullptr;       // [row_cap / kMemoU][m_pos][kMemoU] E per distinct length and position
     float* grp_min = nullptr;    // [row_cap][run_pad] least E of each run, per row (see runs_at)
     uint32_t* run_rank = nullptr;   // [n_run] runs whose first instance is more capable than the run's first
+    int* run_at = nullptr;          // [n_run] the run of each rank
     uint32_t* pos_thr = nullptr;    // [m_pos] runs whose first instance is more capable than the position's
     float4* run_k = nullptr;     // [n_run] least delta of the run, gamma, largest delta, lowest instance (int bits)
     float* class_min = nullptr;  // [row_cap][c_pad] least E of each class, per row
     float4* cls_bound = nullptr; // [n_class] least delta of the class, gamma, largest delta
+    float4* lines = nullptr;     // [row_cap][kRanges][2] with a blend: the instances that can have the least latency, see k_lines
+    int* rest_cnt = nullptr;     // [kRestParts][kRestStride] length of each list (the lists themselves: scratch_finish)
     float* turned = nullptr;     // [turned_rows][M] a part of memo with a row's values together, for out_T
     int turned_rows = 0;         // multiple of kMemoU
     uint2* class_next = nullptr; // [row_cap][n_class] next larger E of the class (bits), lowest instance that has the least

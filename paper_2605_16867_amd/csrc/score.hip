@@ -11,7 +11,8 @@
 // also holds after rounding; without a blend it is the least latency itself.
 // A request then looks at the runs first and at the positions of a run only
 // where the bound leaves the run in question (k_select), and large batches look
-// at the classes before the runs.  The choice is Alg. 1's over all pairs, bit for bit.
+// at the classes before the runs, or at the few instances that can have the least
+// latency at a length (k_lines).  The choice is Alg. 1's over all pairs, bit for bit.
 //
 // A batch of a few requests skips the table: a thread per pair with its own
 // two-step search (k_direct).
@@ -173,6 +174,7 @@ struct MemoArgs {
     float* grp_min;        // see runs_at
     float4* run_k;         // [n_run]
     uint32_t *run_rank, *pos_thr;   // [n_run], [m_pos], see gr_fleet
+    int* run_at;                    // [n_run]
     const float2* posK;
     const unsigned long long* posKey;
     const uint4* run_head;
@@ -247,7 +249,7 @@ __device__ __forceinline__ void rank_run(const MemoArgs& a, int run)
     for (int d = 1; d < kMemoP; d <<= 1) n += __shfl_xor(n, d, kMemoP);
     if (sub == 0) {
         a.pos_thr[p] = n;
-        if (threadIdx.x == 0) a.run_rank[run] = n;
+        if (threadIdx.x == 0) { a.run_rank[run] = n; a.run_at[n] = run; }
     }
 }
 
@@ -565,16 +567,20 @@ struct SelectArgs {
     const float2* posK;
     const unsigned long long* posKey;
     const uint32_t *run_rank, *pos_thr;
+    const int* run_at;
     const int2* cls_run;
     const float* class_min;
     const uint2* class_next;
     const float2* clsK;
     const float4* cls_bound;
+    float4* lines;           // see k_lines
+    int *rest, *rest_cnt;    // see k_select_lines
+    const int *totals, *row_len, *pos_of;
     int* out_inst;
     float* out_slack;
     uint8_t* out_fallback;
     int m_pos, run_pad, n_run, n_class, c_pad, max_len;
-    int segments;      // by classes first: workgroups of the launch
+    int segments;      // by classes or lines first: workgroups of the launch
     int64_t first;     // a group of lanes per request: the launch's first request
 };
 
@@ -623,6 +629,8 @@ struct Selection {
     const int sub, ex;
     const float* __restrict__ runs;
     const float* __restrict__ E;
+    const int* run_at;          // (of a, or a copy in LDS)
+    const float4* run_k;
     const float Lf, c0, Dc;
     // the feasible choice so far
     unsigned long long feasKey = ~0ull;
@@ -638,7 +646,7 @@ struct Selection {
 
     __device__ __forceinline__ Selection(const SelectArgs& args, const Request& q, int row, int sub_)
         : a(args), sub(sub_), ex(q.ex), runs(args.grp_min + runs_at<kBlocks>(row, args.run_pad)),
-          E(args.memo + memo_at(row, 0, args.m_pos)), Lf((float)q.L), c0((float)q.c0),
+          E(args.memo + memo_at(row, 0, args.m_pos)), run_at(args.run_at), run_k(args.run_k), Lf((float)q.L), c0((float)q.c0),
           Dc(q.D > FLT_MAX ? FLT_MAX : q.D) {}
 
     __device__ __forceinline__ float bound(float e, const float4& k) const
@@ -646,29 +654,38 @@ struct Selection {
         return fmaf(c0, kappa_of(make_float2(c0 >= 0.f ? k.x : k.z, k.y), Lf), e);
     }
 
-    template <bool kFeasible, bool kLeast>
+    // kRanked (all runs): by rank, not in class order, so that the search ends where no run can improve the choice;
+    // for requests that can be served in time (the runs of a rank lie anywhere in a row: a search that goes
+    // through all of them takes 29 us by rank and 23 in class order, 65 536 requests x 4 096 instances).
+    template <bool kFeasible, bool kLeast, bool kRanked>
     __device__ __forceinline__ void scan(int first, int n)
     {
         const float inf = __builtin_inff();
         m1 = inf; m2 = inf; r1 = -1;
         for (int r0 = 0; r0 < n; r0 += kChunks * kGroup) {
+            if (kRanked && (uint32_t)r0 >= feasThr) break;
             float b[kChunks];
             float4 k[kChunks];
+            int run[kChunks];
             uint32_t rank[kChunks];      // (read with the rest where a feasible run is known to be there)
 #pragma unroll
             for (int j = 0; j < kChunks; ++j) {
-                const int r = first + min(r0 + j * kGroup + sub, n - 1);
-                if (!kLeast) rank[j] = a.run_rank[r];
-                b[j] = runs[(size_t)r * kRunStride<kBlocks>];
-                k[j] = a.run_k[r];
+                const int i = min(r0 + j * kGroup + sub, n - 1);
+                run[j] = kRanked ? run_at[i] : first + i;
+                if (kRanked) rank[j] = (uint32_t)i;
+            }
+#pragma unroll
+            for (int j = 0; j < kChunks; ++j) {
+                if (!kRanked && !kLeast) rank[j] = a.run_rank[run[j]];
+                b[j] = runs[(size_t)run[j] * kRunStride<kBlocks>];
+                k[j] = run_k[run[j]];
             }
             bool any = false;
 #pragma unroll
             for (int j = 0; j < kChunks; ++j) {
-                const int r = r0 + j * kGroup + sub;
-                b[j] = r < n ? bound(b[j], k[j]) : inf;
+                b[j] = r0 + j * kGroup + sub < n ? bound(b[j], k[j]) : inf;
                 if (kLeast) {
-                    if (b[j] < m1) { m2 = m1; m1 = b[j]; r1 = first + r; }
+                    if (b[j] < m1) { m2 = m1; m1 = b[j]; r1 = run[j]; }
                     else m2 = fminf(m2, b[j]);
                 }
                 if (kFeasible) any = any || b[j] <= Dc;
@@ -676,7 +693,7 @@ struct Selection {
             if (!kFeasible || !__any(any)) continue;
 #pragma unroll
             for (int j = 0; j < kChunks; ++j) {
-                if (kLeast) rank[j] = a.run_rank[first + min(r0 + j * kGroup + sub, n - 1)];
+                if (!kRanked && kLeast) rank[j] = a.run_rank[run[j]];
                 if (!(b[j] <= Dc)) rank[j] = ~0u;      // (not, or no longer, in question)
             }
             for (;;) {
@@ -685,9 +702,14 @@ struct Selection {
                 for (int j = kChunks - 1; j >= 0; --j) at = rank[j] < feasThr ? j * kGroup + sub : at;
                 at = min_over<true>(at);
                 if (at == ~0u) break;
+                int r = run[0];
 #pragma unroll
-                for (int j = 0; j < kChunks; ++j) rank[j] = at == (uint32_t)(j * kGroup + sub) ? ~0u : rank[j];
-                const int p = (first + r0 + (int)at) * kMemoP + sub, g = a.order[p];
+                for (int j = 0; j < kChunks; ++j) {
+                    if (kRanked) r = at / kGroup == (uint32_t)j ? run[j] : r;
+                    rank[j] = at == (uint32_t)(j * kGroup + sub) ? ~0u : rank[j];
+                }
+                r = kRanked ? group_lane(r, at % kGroup) : first + r0 + (int)at;
+                const int p = r * kMemoP + sub, g = a.order[p];
                 const unsigned long long pk = a.posKey[p];
                 const uint32_t thr = a.pos_thr[p];
                 const float T = fmaf(c0, kappa_of(a.posK[p], Lf), E[(size_t)p * kMemoU]);
@@ -774,7 +796,7 @@ __global__ __launch_bounds__(kBlock) void k_select(SelectArgs a)
         return;
     }
     Selection<kChunks, false> sel(a, q, a.len_row[q.L], sub);
-    sel.template scan<true, true>(0, a.n_run);
+    sel.template scan<true, true, false>(0, a.n_run);
     if (sel.feasG < 0) sel.settle(0, a.n_run);
     sel.template report<kMigrate>(i, q.D);
 }
@@ -797,7 +819,7 @@ __device__ __forceinline__ void select_by_class(const SelectArgs& a, int64_t i, 
         if (least == ~0u) break;
         const int l = __ffs(group_ballot(left_rank == least)) - 1;
         if (sub == l) left_rank = ~0u;
-        sel.template scan<true, false>(group_lane(range.x, l), group_lane(range.y, l));
+        sel.template scan<true, false, false>(group_lane(range.x, l), group_lane(range.y, l));
     }
     if (sel.feasG < 0) {
         float left = T;
@@ -808,27 +830,132 @@ __device__ __forceinline__ void select_by_class(const SelectArgs& a, int64_t i, 
             const int l = __ffs(mask) - 1;
             if (sub == l) left = inf;
             const int first = group_lane(range.x, l), n = group_lane(range.y, l);
-            sel.template scan<false, true>(first, n);
+            sel.template scan<false, true, false>(first, n);
             sel.settle(first, n);
         }
     }
     sel.template report<kMigrate>(i, q.D);
 }
 
-// A group of lanes per request, over the classes first (a blend gives every instance its own prefill
-// rate: no class minimum decides a request by itself).
-template <bool kMigrate>
-__global__ __launch_bounds__(kBlock) void k_select_blended(SelectArgs a)
+// With a blend every instance has its own prefill rate, and no least E decides a request.  But for a length and a
+// range of prompts hardly ever more than one instance can have the least latency: T is linear in c0, the
+// least latency a lower envelope of lines, and the lines cross seldom.  So for every row and each of
+// kRanges ranges of c0 the instances that could be least somewhere in it are looked up once, and a request compares those.
+//
+// With any lines a, b and any c in a range lo .. hi, an instance g whose line is above a's at lo and c and above b's at c
+// and hi is above the lesser of the two in all of the range (everything is linear): only the others count.
+// a and b are the least of the run with the least bound at lo and at hi, c is where they cross.  "Above" is by 2^-20 of the largest
+// value: T as a request forms it is off by 2^-24, so none of those left out can come out less, or equal.
+//
+// A wave per row and range: on up to 320 runs the bounds are read once, and what is waited for is those, the two
+// runs, and the runs in question four at a time (4 096 instances, 4 000 rows: 14 us between events; a group of
+// lanes that goes through the runs 64 at a time, three times over, for five ranges: 30).
+__device__ constexpr float kRangeEnd[kRanges + 1] = {0.f, 1024.f, 4096.f, 16384.f, 131072.f};
+
+// [row][range][2]: E, kappa (at the row's length), instance; the first one's fourth word: how many there are, 3 for more
+// than two and 0 where some value is not finite
+__device__ inline size_t lines_at(int64_t row, int range) { return ((size_t)row * kRanges + range) * 2; }
+
+template <int kChunks>
+__global__ __launch_bounds__(kBlock) void k_lines(SelectArgs a)
 {
-    const int sub = threadIdx.x % kGroup;
-    const int64_t i = a.first + (int64_t)blockIdx.x * (kBlock / kGroup) + threadIdx.x / kGroup;
-    if (i >= a.s.n) return;
-    const Request q = fetch<kMigrate>(a.s, i, a.max_len);
-    if (!q.scored) {
-        if (sub == 0) answer<kMigrate>(a, i, -1, 0.f, false);      // not flagged: no migration target
-        return;
+    if (blockIdx.x == 0 && threadIdx.x < kRestParts) a.rest_cnt[threadIdx.x * kRestStride] = 0;      // (for the kernel behind)
+    const int lane = lane_id();
+    const int i = __builtin_amdgcn_readfirstlane(blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave);
+    const int row = i / kRanges, range = i % kRanges;
+    if (row >= a.totals[1]) return;
+    const float inf = __builtin_inff(), lo = kRangeEnd[range], hi = kRangeEnd[range + 1];
+    const float Lf = (float)a.row_len[row];
+    const float* __restrict__ runs = a.grp_min + runs_at<false>(row, a.run_pad);
+    const float* __restrict__ E = a.memo + memo_at(row, 0, a.m_pos);
+
+    float e[kChunks], kappa[kChunks];       // least E of a run, its least kappa (no run: infinite)
+    const auto read = [&](int r0) {
+        float4 k[kChunks];
+#pragma unroll
+        for (int j = 0; j < kChunks; ++j) {
+            const int r = min(r0 + j * kWave + lane, a.n_run - 1);
+            e[j] = runs[r];
+            k[j] = a.run_k[r];
+        }
+#pragma unroll
+        for (int j = 0; j < kChunks; ++j) {
+            kappa[j] = kappa_of(make_float2(k[j].x, k[j].y), Lf);
+            if (r0 + j * kWave + lane >= a.n_run) e[j] = inf;
+        }
+    };
+    // the run with the least bound at either end
+    uint32_t least_lo = ~0u, least_hi = ~0u;
+    int run_lo = 0, run_hi = 0;
+    for (int r0 = 0; r0 < a.n_run; r0 += kChunks * kWave) {
+        read(r0);
+#pragma unroll
+        for (int j = 0; j < kChunks; ++j) {
+            const uint32_t l = ordered_bits(fmaf(lo, kappa[j], e[j])), h = ordered_bits(fmaf(hi, kappa[j], e[j]));
+            if (l < least_lo) { least_lo = l; run_lo = r0 + j * kWave + lane; }
+            if (h < least_hi) { least_hi = h; run_hi = r0 + j * kWave + lane; }
+        }
     }
-    select_by_class<kMigrate, 4, false>(a, i, q, a.len_row[q.L], sub);
+    const auto run_of_least = [&](uint32_t v, int run) {
+        const uint32_t least = min_over<false>(v);
+        return __builtin_amdgcn_readlane(run, __ffsll((long long)__ballot(v == least)) - 1);
+    };
+    run_lo = min(run_of_least(least_lo, run_lo), a.n_run - 1);
+    run_hi = min(run_of_least(least_hi, run_hi), a.n_run - 1);
+
+    // a, b: lanes 0 .. 15 look at the one run, lanes 16 .. 31 at the other
+    float Ea, Eb, ka, kb, Ta_lo, Tb_hi;
+    {
+        const int p = (lane & kGroup ? run_hi : run_lo) * kMemoP + lane % kGroup;
+        const float Ep = E[(size_t)p * kMemoU], kp = kappa_of(a.posK[p], Lf);
+        const float T = fmaf(lane & kGroup ? hi : lo, kp, Ep);
+        const uint32_t v = a.order[p] >= 0 && T < inf ? ordered_bits(T) : ~0u;      // (also not a NaN)
+        const unsigned long long best = __ballot(v == min_over<true>(v));
+        const int la = __ffsll((long long)best) - 1, lb = __ffsll((long long)(best & 0xFFFF0000ull)) - 1;
+        const auto at = [&](float x, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)); };
+        Ea = at(Ep, la); ka = at(kp, la); Ta_lo = at(T, la);
+        Eb = at(Ep, lb); kb = at(kp, lb); Tb_hi = at(T, lb);
+    }
+    const float cross = (Eb - Ea) / (ka - kb), c = cross > lo && cross < hi ? cross : hi;
+    const float Ta = fmaf(c, ka, Ea), Tb = fmaf(c, kb, Eb);
+    const float margin = 0x1p-20f * fmaxf(fmaxf(fabsf(Ta_lo), fabsf(Tb_hi)), fmaxf(fabsf(Ta), fabsf(Tb)));
+    const float at_lo = Ta_lo + margin, at_c = fmaxf(Ta, Tb) + margin, at_hi = Tb_hi + margin;
+    const bool fine = fabsf(Ta_lo) < inf && fabsf(Tb_hi) < inf && fabsf(Ta) < inf && fabsf(Tb) < inf;
+    const auto counts = [&](float Ev, float kv) {
+        return fmaf(lo, kv, Ev) <= at_lo || fmaf(c, kv, Ev) <= at_c || fmaf(hi, kv, Ev) <= at_hi;
+    };
+
+    float4 found[2] = {make_float4(0.f, 0.f, 0.f, 0.f), make_float4(0.f, 0.f, 0.f, 0.f)};
+    int n = 0;
+    for (int r0 = 0; fine && n <= 2 && r0 < a.n_run; r0 += kChunks * kWave) {      // (more than two are not told apart)
+        if (a.n_run > kChunks * kWave) read(r0);
+#pragma unroll
+        for (int j = 0; j < kChunks; ++j) {
+            unsigned long long open = __ballot(counts(e[j], kappa[j]));
+            while (open && n <= 2) {
+                int run = -1;       // four at a time, 16 lanes each
+#pragma unroll
+                for (int t = 0; t < kWave / kGroup; ++t) {
+                    if (lane / kGroup == t && open) run = r0 + j * kWave + __ffsll((long long)open) - 1;
+                    open &= open - 1;
+                }
+                const int p = max(run, 0) * kMemoP + lane % kGroup, g = a.order[p];
+                const float Ep = E[(size_t)p * kMemoU], kp = kappa_of(a.posK[p], Lf);
+                for (unsigned long long take = __ballot(run >= 0 && g >= 0 && counts(Ep, kp)); take && n <= 2; take &= take - 1, ++n) {
+                    const int l = __ffsll((long long)take) - 1;
+                    const float4 line = make_float4(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(Ep), l)),
+                                                    __int_as_float(__builtin_amdgcn_readlane(__float_as_int(kp), l)),
+                                                    __int_as_float(__builtin_amdgcn_readlane(g, l)), 0.f);
+                    if (n == 0) found[0] = line;
+                    else if (n == 1) found[1] = line;
+                }
+            }
+        }
+    }
+    if (lane != 0) return;
+    found[0].w = __int_as_float(min(n, 3));
+    a.lines[lines_at(row, range)] = found[0];
+    a.lines[lines_at(row, range) + 1] = found[1];
 }
 
 // A lane per request over the classes first; what that does not decide (a deadline that somebody
@@ -913,6 +1040,158 @@ __global__ __launch_bounds__(kBlock) void k_select_by_class(SelectArgs a)
     for (int k = tid / kGroup; k < n; k += kBlock / kGroup) {
         const Left& t = todo[k];
         select_by_class<kMigrate, 4, kMigrate>(a, index(t.index / kLanes, t.index % kLanes), t.q, t.row, tid % kGroup);
+    }
+}
+
+// Alg. 1 for a request from the lines that can be least at its length and prompt (k_lines).  Not decided: a deadline that
+// somebody meets, the least latency on the excluded instance, more than two lines.
+struct LineChoice {
+    float T;
+    int g;
+    bool decided;
+};
+
+// Where the lines of a request are.
+__device__ __forceinline__ const float4* lines_of(const SelectArgs& a, const Request& q, int row)
+{
+    int range = 0;
+#pragma unroll
+    for (int k = 1; k < kRanges; ++k) range += q.c0 >= (int)kRangeEnd[k];
+    return a.lines + lines_at(row, range);
+}
+
+__device__ __forceinline__ LineChoice choose_line(const Request& q, const float4& one, const float4& two)
+{
+    const int n = __float_as_int(one.w), g2 = __float_as_int(two.z);
+    const float c0 = (float)q.c0, D = q.D, T2 = fmaf(c0, two.y, two.x);
+    LineChoice r;
+    r.T = fmaf(c0, one.y, one.x);
+    r.g = __float_as_int(one.z);
+    if (n == 2 && (T2 < r.T || (T2 == r.T && g2 < r.g))) { r.T = T2; r.g = g2; }
+    r.decided = (n == 1 || n == 2) && q.c0 >= 0 && q.c0 <= (int)kRangeEnd[kRanges] && r.T < __builtin_inff() && r.g != q.ex &&
+                !(r.T <= (D > FLT_MAX ? FLT_MAX : D));
+    return r;
+}
+
+// What the lines leave open, by a group of lanes: mostly requests that can be served in time, so the least
+// latency is not looked for along the way.
+template <bool kMigrate>
+__device__ __forceinline__ void select_rest(const SelectArgs& a, int64_t i, const Request& q, Selection<4, false>& sel)
+{
+    sel.template scan<true, false, true>(0, a.n_run);
+    if (sel.feasG < 0) {
+        sel.template scan<false, true, false>(0, a.n_run);
+        sel.settle(0, a.n_run);
+    }
+    sel.template report<kMigrate>(i, q.D);
+}
+
+// A group of lanes per request, its lines first.
+template <bool kMigrate>
+__global__ __launch_bounds__(kBlock) void k_select_lines(SelectArgs a)
+{
+    const int sub = threadIdx.x % kGroup;
+    const int64_t i = a.first + (int64_t)blockIdx.x * (kBlock / kGroup) + threadIdx.x / kGroup;
+    if (i >= a.s.n) return;
+    const Request q = fetch<kMigrate>(a.s, i, a.max_len);
+    if (!q.scored) {
+        if (sub == 0) answer<kMigrate>(a, i, -1, 0.f, false);      // not flagged: no migration target
+        return;
+    }
+    const int row = a.len_row[q.L];
+    const float4* at = lines_of(a, q, row);
+    const LineChoice c = choose_line(q, at[0], at[1]);
+    if (c.decided) {
+        if (sub == 0) answer<kMigrate>(a, i, c.g, q.D - c.T, false);
+        return;
+    }
+    Selection<4, false> sel(a, q, row, sub);
+    select_rest<kMigrate>(a, i, q, sel);
+}
+
+constexpr int kRestBlocks = 24;      // workgroups per list: six on every compute unit, so that all are there at once
+
+// First entry of list `part` where workgroup b of `blocks` appends at most `per` requests to list b % kRestParts.
+__device__ inline int64_t rest_begin(int part, int blocks, int per)
+{
+    return (int64_t)per * ((blocks / kRestParts) * part + min(part, blocks % kRestParts));
+}
+
+// A large risk scan, of which any share of the requests may be late, first half: a lane per request and its lines.
+// What those leave open goes on a list for the second half; kRestParts lists, so that the workgroups do not
+// wait for each other at one counter.
+template <int kItems>
+__global__ __launch_bounds__(kBlock) void k_late_lines(SelectArgs a)
+{
+    __shared__ int todo[kBlock * kItems];
+    __shared__ int n_todo, at_todo;
+    const int tid = threadIdx.x, part = blockIdx.x % kRestParts;
+    if (tid == 0) n_todo = 0;
+    __syncthreads();
+    Request q[kItems];
+    int row[kItems];
+    float4 one[kItems], two[kItems];
+    const int64_t i0 = (int64_t)blockIdx.x * (kBlock * kItems) + tid;
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) q[it] = fetch<true>(a.s, min(i0 + it * kBlock, a.s.n - 1), a.max_len);
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) row[it] = a.len_row[q[it].L];
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) {
+        const float4* __restrict__ at = lines_of(a, q[it], row[it]);
+        one[it] = at[0];
+        two[it] = at[1];
+    }
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) {
+        const int64_t i = i0 + it * kBlock;
+        const LineChoice c = choose_line(q[it], one[it], two[it]);
+        const bool in = i < a.s.n, later = in && q[it].scored && !c.decided;
+        if (in && !later) answer<true>(a, i, q[it].scored ? c.g : -1, q[it].scored ? q[it].D - c.T : 0.f, false);
+        const unsigned long long m = __ballot(later);
+        if (!m) continue;
+        int at = 0;
+        if (lane_id() == 0) at = atomicAdd(&n_todo, __popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (later) todo[at + __popcll(m & ((1ull << lane_id()) - 1ull))] = (int)i;
+    }
+    __syncthreads();
+    if (tid == 0 && n_todo) at_todo = atomicAdd(&a.rest_cnt[part * kRestStride], n_todo);
+    __syncthreads();
+    int* __restrict__ list = a.rest + rest_begin(part, a.segments, kBlock * kItems);
+    for (int k = tid; k < n_todo; k += kBlock) list[at_todo + k] = todo[k];
+}
+
+// Second half: a group of lanes per listed request.  What it takes is the chain of reads of a request, so
+// what all requests need of the runs is in LDS, and the next requests are on their way: per request its runs
+// are waited for, and the runs looked at (147 000 requests of 1.6 M on 4 096 instances 60 us between events; without either 71).
+__global__ __launch_bounds__(kBlock, 6) void k_late_rest(SelectArgs a, int wg_requests)
+{
+    __shared__ float4 lds_k[kRestRuns];
+    __shared__ int lds_at[kRestRuns];
+    for (int r = threadIdx.x; r < a.n_run; r += kBlock) { lds_k[r] = a.run_k[r]; lds_at[r] = a.run_at[r]; }
+    __syncthreads();
+    const int sub = threadIdx.x % kGroup, part = blockIdx.x % kRestParts;
+    const int n = a.rest_cnt[part * kRestStride];
+    const int* __restrict__ list = a.rest + rest_begin(part, a.segments, wg_requests);
+    constexpr int kStep = kRestBlocks * (kBlock / kGroup);
+    int k = blockIdx.x / kRestParts * (kBlock / kGroup) + threadIdx.x / kGroup;
+    if (k >= n) return;
+    // the request at hand and its row; the next one; the one after that by its index
+    const auto index = [&](int k) { return list[min(k, n - 1)]; };
+    int i = index(k), i1 = index(k + kStep), i2 = index(k + 2 * kStep);
+    Request q = fetch<true>(a.s, i, a.max_len), q1 = fetch<true>(a.s, i1, a.max_len);
+    int row = a.len_row[q.L];
+    for (; k < n; k += kStep) {
+        const int i3 = index(k + 3 * kStep), row1 = a.len_row[q1.L];
+        const Request q2 = fetch<true>(a.s, i2, a.max_len);
+        Selection<4, false> sel(a, q, row, sub);
+        sel.run_at = lds_at;
+        sel.run_k = lds_k;
+        select_rest<true>(a, i, q, sel);
+        i = i1; i1 = i2; i2 = i3;
+        q = q1; q1 = q2;
+        row = row1;
     }
 }
 
@@ -1363,10 +1642,10 @@ constexpr int64_t kByClassMany = int64_t(1) << 19;
 constexpr int64_t kLaunchThreads = int64_t(1) << 31;
 
 template <bool kMigrate>
-static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, bool blended, hipStream_t s)
+static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, bool by_lines, hipStream_t s)
 {
     const int64_t n = a.s.n;
-    if (by_class && !blended) {
+    if (by_class) {
         // large batches: two requests per lane of a whole workgroup; else a wave's worth per workgroup,
         // so that the second half has the lanes when many requests need it
         const bool many = n >= kByClassMany;
@@ -1382,14 +1661,14 @@ static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, bool b
     for (a.first = 0; a.first < n; a.first += kLaunchThreads / kGroup) {
         const int64_t here = std::min(n - a.first, kLaunchThreads / kGroup);
         const dim3 grid((unsigned)((here + kBlock / kGroup - 1) / (kBlock / kGroup)));
-        if (by_class) hipLaunchKernelGGL(k_select_blended<kMigrate>, grid, dim3(kBlock), 0, s, a);
-        else switch (chunks) {
-            case 1: hipLaunchKernelGGL((k_select<kMigrate, 1>), grid, dim3(kBlock), 0, s, a); break;
-            case 2: hipLaunchKernelGGL((k_select<kMigrate, 2>), grid, dim3(kBlock), 0, s, a); break;
-            case 3: hipLaunchKernelGGL((k_select<kMigrate, 3>), grid, dim3(kBlock), 0, s, a); break;
-            case 4: hipLaunchKernelGGL((k_select<kMigrate, 4>), grid, dim3(kBlock), 0, s, a); break;
-            default: hipLaunchKernelGGL((k_select<kMigrate, 5>), grid, dim3(kBlock), 0, s, a);
-        }
+#define GR_LAUNCH_SELECT(C) hipLaunchKernelGGL((k_select<kMigrate, C>), grid, dim3(kBlock), 0, s, a)
+        if (by_lines) hipLaunchKernelGGL(k_select_lines<kMigrate>, grid, dim3(kBlock), 0, s, a);
+        else if (chunks == 1) GR_LAUNCH_SELECT(1);
+        else if (chunks == 2) GR_LAUNCH_SELECT(2);
+        else if (chunks == 3) GR_LAUNCH_SELECT(3);
+        else if (chunks == 4) GR_LAUNCH_SELECT(4);
+        else GR_LAUNCH_SELECT(5);
+#undef GR_LAUNCH_SELECT
     }
 }
 
@@ -1483,21 +1762,29 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     //    4 096      54.6 / 51.6 (55.2 / 55.6)    126 / 89.9  (133 / 109)
     // A risk scan's requests are late where they are, and few can be served in time elsewhere:
     // 512 x 512 requests 57.6 / 41.2 (42.0 / 42.0), 4 096 x 512 544 / 110 (278 / 137).
-    // With a blend the classes only rule out whole classes: 4 096 x 400 435 / 372 (221 / 195), and nothing
-    // is won where a group reads all runs at once (64).
     const PairsPlan pairs(f, out.T);
     const bool select = !(out.T && pairs.select);
-    const bool by_class = select && n >= kByClassMin && f->n_class <= kGroup && f->n_run >= 4 * f->n_class &&
-                          f->n_run >= (blended ? 8 * kGroup : migrate ? 2 * kGroup : 4 * kGroup);
+    const bool by_class = select && !blended && n >= kByClassMin && f->n_class <= kGroup && f->n_run >= 4 * f->n_class &&
+                          f->n_run >= (migrate ? 2 * kGroup : 4 * kGroup);
+    // The lines first where no class decides a request: with a blend (every instance has its own prefill rate), and where
+    // there are more classes than a group has lanes.  Whole calls, us, a group of lanes per request over the runs / lines
+    // first (weight 1; in brackets deadlines that many instances meet):
+    //   262 144 requests on 4 096 instances  92 / 61 (114 / 103), on 1 024 of 64 classes, no blend, 68 / 54 (57 / 69)
+    //   a scan of 1 024 x 1 000             164 / 70 (179 / 131)   4 096 x 400  355 / 107 (226 / 147)
+    // Below 2^17 requests the lookup (10 to 14 us) is not won back; below 81 runs a group reads all of them at once.
+    // A large scan takes a lane per request and lists the rest, as most of it may not be late at all.
+    const bool by_lines = select && (blended || f->n_class > kGroup) && n >= kByClassMin &&
+                          f->n_run > (migrate && n >= kByClassMany ? 2 : 5) * kGroup;
+    const bool listed = by_lines && migrate && n >= kByClassMany && f->n_run <= kRestRuns;
     // The runs' minima in blocks of rows where few requests get as far as the runs (6 us less for the
     // table of 7 061 rows x 4 096 instances); row by row where many may: a request's 16 lanes then read 16
     // runs from one cache line, not from sixteen.
-    const bool blocks = by_class && migrate && !blended;
+    const bool blocks = by_class && migrate;
     {
         MemoArgs m{};
         m.totals = f->totals; m.row_len = f->row_len; m.len_row = f->len_row; m.order = f->order; m.instK = f->instK;
         m.tabR = f->tabR; m.tabS = f->tabS; m.tabGH = f->tabGH; m.memo = f->memo; m.grp_min = f->grp_min;
-        m.run_k = f->run_k; m.run_rank = f->run_rank; m.pos_thr = f->pos_thr; m.posK = f->posK; m.posKey = f->posKey;
+        m.run_k = f->run_k; m.run_rank = f->run_rank; m.pos_thr = f->pos_thr; m.run_at = f->run_at; m.posK = f->posK; m.posKey = f->posKey;
         m.run_head = f->run_head;
         m.seen = reinterpret_cast<uint4*>(f->seen); m.seen_words = (f->bins + 15) / 16;
         m.n_run = f->n_run; m.m_pos = f->m_pos; m.run_pad = f->run_pad; m.cap = f->cap;
@@ -1524,13 +1811,34 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     if (select) {
         SelectArgs a{};
         a.s = src; a.len_row = f->len_row; a.order = f->order; a.memo = f->memo; a.grp_min = f->grp_min; a.run_k = f->run_k;
-        a.posK = f->posK; a.posKey = f->posKey; a.run_rank = f->run_rank; a.pos_thr = f->pos_thr; a.cls_run = f->cls_run; a.class_min = f->class_min; a.class_next = f->class_next; a.clsK = f->clsK; a.cls_bound = f->cls_bound;
+        a.posK = f->posK; a.posKey = f->posKey; a.run_rank = f->run_rank; a.pos_thr = f->pos_thr; a.run_at = f->run_at; a.cls_run = f->cls_run; a.class_min = f->class_min; a.class_next = f->class_next; a.clsK = f->clsK; a.cls_bound = f->cls_bound;
         a.out_inst = out.inst; a.out_slack = out.slack; a.out_fallback = out.fallback;
         a.m_pos = f->m_pos; a.run_pad = f->run_pad; a.n_run = f->n_run; a.n_class = f->n_class; a.c_pad = f->c_pad;
         a.max_len = f->max_len;
-        ProfScope ps(f, kSelectRoute + off, s);
-        if (migrate) launch_select<true>(f, a, by_class, blended, s);
-        else launch_select<false>(f, a, by_class, blended, s);
+        a.lines = f->lines; a.totals = f->totals; a.row_len = f->row_len; a.pos_of = f->pos_of;
+        a.rest_cnt = f->rest_cnt;
+        if (by_lines) {
+            constexpr int per = kBlock / kWave;
+            const dim3 grid((unsigned)((max_rows * kRanges + per - 1) / per));
+            ProfScope ps(f, kLinesRoute + off, s);
+            if (f->n_run <= 2 * kWave) hipLaunchKernelGGL(k_lines<2>, grid, dim3(kBlock), 0, s, a);
+            else hipLaunchKernelGGL(k_lines<5>, grid, dim3(kBlock), 0, s, a);      // (4 096 instances of three classes are 258 runs)
+        }
+        if (listed) {
+            // (the lists use the room for finish times of feedback routing, a word per running request)
+            a.rest = reinterpret_cast<int*>(f->scratch_finish);
+            a.segments = (int)((n + kBlock * kRestItems - 1) / (kBlock * kRestItems));
+            {
+                ProfScope ps(f, kSelectMigrate, s);
+                hipLaunchKernelGGL(k_late_lines<kRestItems>, dim3(a.segments), dim3(kBlock), 0, s, a);
+            }
+            ProfScope ps(f, kSelectMigrate, s);
+            hipLaunchKernelGGL(k_late_rest, dim3(kRestParts * kRestBlocks), dim3(kBlock), 0, s, a, kBlock * kRestItems);
+        } else {
+            ProfScope ps(f, kSelectRoute + off, s);
+            if (migrate) launch_select<true>(f, a, by_class, by_lines, s);
+            else launch_select<false>(f, a, by_class, by_lines, s);
+        }
     }
     if (out.T) launch_pairs(f, src, out, pairs, max_rows, s);
     return hipGetLastError() == hipSuccess ? GR_OK : GR_ERR_HIP;
