@@ -132,7 +132,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     const bool ok =
         dev_alloc(&f->cls, n_class) && dev_alloc(&f->inst_class, n_inst) &&
         dev_alloc(&f->tabR, tab) && dev_alloc(&f->tabGH, (size_t)n_inst * (f->cap + 2)) &&
-        dev_alloc(&f->hN, n_inst) && dev_alloc(&f->hD, n_inst) &&
+        dev_alloc(&f->hD, n_inst) &&
         dev_alloc(&f->emaQ, n_inst) && dev_alloc(&f->emaP, n_inst) && dev_alloc(&f->emaD, n_inst) &&
         dev_alloc(&f->instK, n_inst) && dev_alloc(&f->tabS, (size_t)n_inst * f->n_split) &&
         dev_alloc(&f->clsK, n_class) && dev_alloc(&f->slot_inst, f->m_pos) && dev_alloc(&f->slot_of, n_inst) && dev_alloc(&f->slot_key, f->m_pos) && dev_alloc(&f->run_cls, f->n_run) && dev_alloc(&f->cls_run, n_class) &&
@@ -187,7 +187,7 @@ int gr_destroy(gr_fleet* f)
 {
     if (!f) return GR_OK;
     (void)hipDeviceSynchronize();
-    void* ptrs[] = {f->cls, f->inst_class, f->tabR, f->tabGH, f->hN, f->hD, f->emaQ, f->emaP, f->emaD, f->instK, f->tabS,
+    void* ptrs[] = {f->cls, f->inst_class, f->tabR, f->tabGH, f->hD, f->emaQ, f->emaP, f->emaD, f->instK, f->tabS,
                     f->clsK, f->slot_inst, f->slot_of, f->slot_key, f->run_cls, f->cls_run, f->order, f->pos_of, f->posK, f->posKey, f->run_head, f->act_inst, f->pend_cnt, f->commit_mark, f->pend_touched, f->pend_prompt, f->pend_len,
                     f->scratch_finish, f->batch_cap, f->counters, f->seen, f->late_cnt, f->row_len,
                     f->len_row, f->totals, f->memo, f->grp_min, f->run_k, f->run_rank, f->run_at, f->pos_thr, f->class_min, f->cls_bound, f->class_next, f->rest_cnt, f->lines, f->turned, f->direct_part};

@@ -32,7 +32,6 @@ namespace gr {
 
 constexpr int kBlock = 256;
 constexpr int kWave = 64;
-constexpr int kWaves = kBlock / kWave;
 constexpr int kMaxEntries = 2048;
 constexpr int kMaxClasses = 64;
 constexpr int kMaxLen = 32767;     // lengths and row numbers are kept in 16 bits
@@ -134,7 +133,7 @@ struct gr_fleet {
     int epl = 0;           // sort words per lane of the status build: 1, 2, 4 .. 32
     int cap = 0;           // 64 * epl >= max_entries: table entries per instance
     int n_split = 0;       // splitters per instance: 8 (cap 64), 16 (to 512), 32
-    int m_pad = 0;         // instances rounded up to a multiple of 128 (two blocks of 64 positions)
+    int m_pad = 0;         // instances rounded up to a multiple of 128, for the size of a small batch (gr_set_small_batch_pairs)
     int m_pos = 0;         // positions of the class order: every class rounded up to whole runs of kMemoP
     int n_run = 0;         // m_pos / kMemoP
     int run_pad = 0;       // n_run rounded up to whole runs of kMemoP: row length of grp_min
@@ -154,7 +153,6 @@ struct gr_fleet {
     // E_g(L) = Gq + L*H + tri(L)*gamma*(n+1) on the segment after the k shortest requests (n still running)
     uint16_t* tabR = nullptr; // [M][cap] remaining lengths, ascending; 0xFFFF past the last entry
     float2* tabGH = nullptr;  // [M][cap + 2] (Gq, H) of segment k, see gh_at; segment 0 is (q_g, alpha + beta*(N+1) + gamma*sum of contexts)
-    int* hN = nullptr;       // [M] entries per instance
     double* hD = nullptr;    // [M] d_g
     // [M] what a pair needs of its instance besides the tables: (delta, gamma) of the latency's prefill
     // part T = E + c0 * (delta + gamma * L), blended as the tables are; the curvature gamma of E; entries (int bits)
@@ -300,18 +298,6 @@ __device__ inline T wave_sum(T v)
 {
 #pragma unroll
     for (int d = kWave / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, kWave);
-    return v;
-}
-
-template <typename T>
-__device__ inline T wave_incl_scan(T v)
-{
-    const int lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        T o = __shfl_up(v, d, kWave);
-        if (lane >= d) v += o;
-    }
     return v;
 }
 

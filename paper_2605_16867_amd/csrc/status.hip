@@ -30,7 +30,7 @@ struct BuildArgs {
     const int* inst_class;
     uint16_t* tabR;
     float2* tabGH;
-    int* hN;
+    int* unset;          // 1: some running entry's flag is not set here (read by k_scan)
     double* hD;
     int* act_inst;
     float4* instK;
@@ -43,7 +43,6 @@ struct BuildArgs {
     // for the migration pass of a risk scan: which lengths flagged requests have, and how many are flagged
     uint8_t* seen;
     int* late_cnt;
-    int* unset;          // 1: some running entry's flag is not set here (read by k_scan)
     // requests routed since the caller's status (feedback routing): per instance, queued behind the queue
     int* pend_cnt;
     int *pend_prompt, *pend_len;
@@ -338,10 +337,13 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
         fin_lds[i] = kNoFinish;
         key[r] = word;
     }
+    // the instance of each running request, for the migration pass of a risk scan
     // (stores on their own: a store between two uses of loaded words would make the second wait for it)
+    if (a.act_budget) {
 #pragma unroll
-    for (int r = 0; r < kEPL; ++r)
-        if (r * kWave + lane < A) a.act_inst[a0 + r * kWave + lane] = g;
+        for (int r = 0; r < kEPL; ++r)
+            if (r * kWave + lane < A) a.act_inst[a0 + r * kWave + lane] = g;
+    }
     if (status) atomicOr(&a.counters[0], status);
     if (a.act_budget && (status & GR_DEV_ENTRIES_DROPPED)) *a.unset = 1;
     if (Q + P > 0) qsum = wave_sum_i64(qsum);   // Q and P are the same in every lane
@@ -631,7 +633,6 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
                 double Gq0 = q_adm, H0 = cc.alpha + (cc.beta * (double)(Nleft + 1) + cc.gamma * Cd);
                 if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
                 a.tabGH[gh_at(g, 0, kCap)] = make_float2((float)Gq0, (float)H0);
-                a.hN[g] = Nleft;
                 a.instK[g] = inst_coef(a, cc, bp, Nleft);
                 if (!a.use_pending) a.pend_cnt[g] = 0;
                 // the next decode step that runs: the first one played above, else the batch as it stands
@@ -704,7 +705,6 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
         double Gq0 = q, H0 = cc.alpha + (cc.beta * (double)(Nrun + 1) + cc.gamma * Cd);
         if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
         a.tabGH[gh_at(g, 0, kCap)] = make_float2((float)Gq0, (float)H0);
-        a.hN[g] = Nrun;
         a.instK[g] = inst_coef(a, cc, bp, Nrun);
         if (!a.use_pending) a.pend_cnt[g] = 0;
         // the next decode step that runs: the first one played above, else the batch as it stands
@@ -1061,7 +1061,6 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
         double Gq0 = q, H0 = fma(cc.gamma, Ctot, fma(cc.beta, (double)(N + 1), cc.alpha));
         if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
         a.tabGH[gh_at(g, 0, kTab)] = make_float2((float)Gq0, (float)H0);
-        a.hN[g] = N;
         a.instK[g] = inst_coef(a, cc, bp, N);
         a.pend_touched[g] = 0;
         if (!a.use_pending) a.pend_cnt[g] = 0;
@@ -1409,7 +1408,8 @@ int launch_ema(gr_fleet* f, double w, const float* s_q, const float* s_p, const 
     return GR_OK;
 }
 
-// Dynamic LDS limits of the build kernels, set to what each needs at most (see score_prepare).
+// Dynamic LDS limits of the build kernels, set to what each needs at most: the attribute belongs to the kernel, not to
+// a handle, so a smaller handle must not lower it for a live, larger one.
 int status_prepare()
 {
     bool ok = true;
@@ -1449,7 +1449,7 @@ int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s)
     b.out_d = in.out_d; b.out_flag = in.out_flag;
     b.cls = f->cls; b.inst_class = f->inst_class;
     b.tabR = f->tabR; b.tabGH = f->tabGH;
-    b.hN = f->hN; b.hD = f->hD; b.act_inst = f->act_inst;
+    b.hD = f->hD; b.act_inst = f->act_inst;
     b.instK = f->instK; b.tabS = f->tabS; b.slot_of = f->slot_of; b.slot_key = f->slot_key; b.counters = f->counters;
     b.n_active = in.n_active; b.n_queued = in.n_queued;
     b.n_inst = f->n_inst; b.max_entries = f->max_entries; b.max_len = f->max_len;

@@ -76,7 +76,7 @@ def _scan(n_inst, held, n_class, late, blend=0.0, obs="many", clones=False, seed
 # the classes first: 2^17 requests and more, 2^19 and more
 @pytest.mark.parametrize("clones", [False, True])
 @pytest.mark.parametrize("late", ["all", "some"])
-@pytest.mark.parametrize("n_inst,held,n_class", [(520, 257, 3), (700, 190, 16), (530, 1001, 4)])
+@pytest.mark.parametrize("n_inst,held,n_class", [(520, 257, 3), (1100, 121, 16), (530, 1001, 4)])
 def test_scan_classes_first(n_inst, held, n_class, late, clones):
     na, share, _ = _scan(n_inst, held, n_class, late, clones=clones)
     assert na >= 1 << 17 and share > 0.01
@@ -96,6 +96,14 @@ def test_scan_lines_first(late, obs):
 @pytest.mark.parametrize("n_inst,held", [(530, 1001), (2100, 251)])
 def test_scan_lines_and_list(n_inst, held, late, blend, obs):
     na, share, _ = _scan(n_inst, held, 3, late, blend=blend, obs=obs)
+    assert na >= (1 << 19) and share > 0.001
+
+
+# more runs than a wave reads at once (320), and than the list's kernel keeps in LDS (1 024)
+@pytest.mark.parametrize("late", ["all", "few"])
+@pytest.mark.parametrize("n_inst,held", [(5300, 100), (17000, 31)])
+def test_scan_of_wide_fleets(n_inst, held, late):
+    na, share, _ = _scan(n_inst, held, 3, late, blend=1.0)
     assert na >= (1 << 19) and share > 0.001
 
 
