@@ -171,8 +171,8 @@ def max_len_of(fl) -> int:
 
 
 # How the handles of the checks below score a batch: None = the library's own choice (small
-# batches pair by pair, large ones grouped by length), 0 = always grouped.  tests/conftest.py
-# runs the GPU tests of the edge cases once each way.
+# batches pair by pair, large ones through the table of their lengths), 0 = always through the table.
+# The tests of the edge cases and of the whole path run once each way.
 SMALL_BATCH_PAIRS: Optional[int] = None
 
 

@@ -13,27 +13,28 @@ pytestmark = pytest.mark.gpu
 
 
 def _route_all(fl, max_entries, exclude=None):
-    """The batch through gr_score_route pair by pair and through gr_score_route_noalloc: equal bit for
-    bit, every choice against the reference."""
+    """The batch through gr_score_route pair by pair, through gr_score_route_noalloc and through the table
+    pass: equal bit for bit, every choice against the reference."""
     import torch
     dev = "cuda:0"
     d = parity.upload(fl, dev)
     h = parity.make_handle(fl, max_entries=max_entries)
-    h.gr_set_small_batch_pairs(1 << 40)
     fin = torch.zeros(len(fl.act_prompt), dtype=torch.float32, device=dev)
     h.gr_build_status(d["act_off"], d["act_prompt"], d["act_gen"], d["act_rem"], d["q_off"], d["q_prompt"], d["q_len"], fin)
     R = len(fl.in_prompt)
     ex = None if exclude is None else torch.from_numpy(exclude).to(dev)
     got = []
-    for call in (h.gr_score_route, h.gr_score_route_noalloc):
+    for call, pairs in ((h.gr_score_route, 1 << 40), (h.gr_score_route_noalloc, 1 << 40), (h.gr_score_route, 0)):
+        h.gr_set_small_batch_pairs(pairs)
         inst = torch.full((R,), -7, dtype=torch.int32, device=dev)
         slack = torch.full((R,), float("nan"), dtype=torch.float32, device=dev)
         fb = torch.full((R,), 9, dtype=torch.uint8, device=dev)
         call(d["in_prompt"], d["in_len"], d["in_budget"], inst, slack, exclude_inst=ex, out_fallback=fb)
         torch.cuda.synchronize()
         got.append((inst.cpu().numpy(), slack.cpu().numpy(), fb.cpu().numpy()))
-    for a, b in zip(*got):
-        assert np.array_equal(a, b)
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
+            assert np.array_equal(a, b)
     rep = {}
     parity.check_choices_all("direct", oracle.simulate(fl), fl.in_prompt, fl.in_len, fl.in_budget.astype(np.float64),
                              exclude, None, got[0][0].astype(np.int64), got[0][1], rep, fallback=got[0][2])
@@ -53,6 +54,16 @@ def test_fleet_sizes(n_inst):
     for me in (8, 1024):
         _route_all(fl, me)
         _route_all(fl, me, exclude=rng.integers(-1, n_inst, n).astype(np.int32))
+
+
+@pytest.mark.parametrize("n", [3276, 3277, 4096])
+def test_more_parts_than_there_is_room_for(n):
+    """Five parts of 4 096 instances per request: 16 384 selections are kept at most, and beyond that one
+    workgroup takes all instances of a request."""
+    rng = np.random.default_rng(n)
+    acts = [rand_entries(rng, int(k)) for k in rng.integers(0, 3, 17000)]
+    inc = np.stack([rng.integers(128, 2049, n), rng.choice([1, 3, 50, 400, 2000], n)], 1)
+    _route_all(fleet(rng.integers(0, 3, 17000), acts, [[]] * 17000, inc, rng.uniform(0.8, 6, n) * solo(inc[:, 0], inc[:, 1])), 8)
 
 
 @pytest.mark.parametrize("cap", [64, 128, 256, 512, 1024, 2048])

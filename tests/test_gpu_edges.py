@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 @pytest.fixture(autouse=True, params=["auto", "grouped"])
 def scoring_layout(request):
     """Every test here runs twice: with the library choosing how a batch is scored
-    (few pairs: a thread per pair; many: grouped by length), and always grouped."""
+    (few pairs: pair by pair; many: through the table of its lengths), and always through the table."""
     parity.SMALL_BATCH_PAIRS = None if request.param == "auto" else 0
     yield
     parity.SMALL_BATCH_PAIRS = None
@@ -116,10 +116,9 @@ def test_one_length_many_requests_and_all_lengths_distinct():
     parity.run_and_check(fl)
 
 
-def test_every_tile_filling():
-    """Lengths with 1 .. 70 requests each: tiles of every filling (the main pass
-    runs over the requests a tile has, in eights; small tiles and full tiles
-    take their minima differently), with deadlines on both sides of feasible."""
+def test_every_number_of_requests_per_length():
+    """Lengths with 1 .. 70 requests each (requests of one length share a row of the table), with
+    deadlines on both sides of feasible."""
     rng = np.random.default_rng(11)
     acts = [rand_entries(rng, int(n)) for n in rng.integers(0, 120, 200)]
     cls = rng.integers(0, 3, 200)
@@ -133,10 +132,10 @@ def test_every_tile_filling():
         parity.run_and_check(fl)
 
 
-@pytest.mark.parametrize("n_inst", [6208, 8320])
+@pytest.mark.parametrize("n_inst", [4096, 4097, 6208, 8320])
 def test_wide_fleets(n_inst):
-    """More instances than the scoring kernel's small-workgroup variant keeps
-    coefficient pairs for in LDS (larger workgroups, then global memory)."""
+    """At and beyond the instances that one workgroup takes of a request scored pair by pair (4 096: two
+    parts, three), and hundreds of runs in the table pass."""
     rng = np.random.default_rng(n_inst)
     acts = [rand_entries(rng, int(n)) for n in rng.integers(0, 7, n_inst)]
     cls = rng.integers(0, 3, n_inst)

@@ -1,7 +1,7 @@
 """GPU parity at the full sizes of the large configurations, in the launch shapes the
 benchmark times: the three library calls, through the C interface, against the CPU
 reference on the same seeded inputs (bars in tests/parity.py).  Batches of these sizes are
-always scored grouped by length, so each test runs once."""
+always scored through the table of their lengths, so each test runs once."""
 import numpy as np
 import pytest
 

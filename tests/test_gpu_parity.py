@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 @pytest.fixture(autouse=True, params=["auto", "grouped"])
 def scoring_layout(request):
     """Every test here runs twice: with the library choosing how a batch is scored
-    (few pairs: a thread per pair; many: grouped by length), and always grouped."""
+    (few pairs: pair by pair; many: through the table of its lengths), and always through the table."""
     parity.SMALL_BATCH_PAIRS = None if request.param == "auto" else 0
     yield
     parity.SMALL_BATCH_PAIRS = None

@@ -1,8 +1,7 @@
-"""gr_score_route_noalloc (the entry point for callers that cannot allocate: its running
-selections live in a fixed array of the library's device image) against gr_score_route,
-through the C interface: the same inputs must give the same instances, fallback bits and
-slacks bit for bit, on two calls in a row, the second with a smaller batch, and again after
-the first handle is gone (the array outlives handles)."""
+"""gr_score_route_noalloc (the pair-by-pair pass for callers that want the same work queued whatever
+the batch) against gr_score_route through the table pass, which shares none of it: the same inputs must
+give the same instances, fallback bits and slacks bit for bit, on two calls in a row, the second
+with a smaller batch, and on a second handle after the first is gone."""
 import numpy as np
 import pytest
 
@@ -38,7 +37,7 @@ def test_noalloc_entry_point_matches_gr_score_route_on_two_calls_in_a_row():
     fl = workloads.make_fleet(workloads.spec("mid", slo_scale=3.0, occupancy_jitter=True, seed=61))
     d = parity.upload(fl, dev)
     h = parity.make_handle(fl)
-    h.gr_set_small_batch_pairs(1 << 40)          # gr_score_route pair by pair as well: same arithmetic
+    h.gr_set_small_batch_pairs(0)                # gr_score_route through the table, whatever the batch
     fin = torch.empty(len(fl.act_prompt), dtype=torch.float32, device=dev)
     h.gr_build_status(d["act_off"], d["act_prompt"], d["act_gen"], d["act_rem"], d["q_off"], d["q_prompt"],
                       d["q_len"], fin)
@@ -70,8 +69,8 @@ def test_noalloc_entry_point_matches_gr_score_route_on_two_calls_in_a_row():
             d["in_prompt"][:4], d["in_len"][:4], d["in_budget"][:4],
             torch.zeros(4, dtype=torch.int32, device=dev), torch.zeros(4, dtype=torch.float32, device=dev))
     assert e.value.code == -4
-    # a second handle on the same GPU uses the same array
-    h2.gr_set_small_batch_pairs(1 << 40)
+    # a second handle on the same GPU
+    h2.gr_set_small_batch_pairs(0)
     h2.gr_build_status(d["act_off"], d["act_prompt"], d["act_gen"], d["act_rem"], d["q_off"], d["q_prompt"],
                        d["q_len"], fin)
     ref4, got4 = _route_both(h2, d, 300)
