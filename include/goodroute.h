@@ -49,7 +49,9 @@
  * instance <= max_entries_per_inst; CSR offsets non-decreasing, starting at 0.
  * Kernels stay in bounds when the contract is broken (lengths are clamped,
  * surplus entries dropped) and raise a sticky bit readable with
- * gr_device_status.
+ * gr_device_status.  gr_risk_scan writes no finish time and no flag for running
+ * entries that it drops or that no instance's offsets cover; a target is looked
+ * for wherever out_flag then reads nonzero.
  */
 #ifndef GOODROUTE_H
 #define GOODROUTE_H
@@ -88,14 +90,18 @@ enum {
  * Hard limits: max_entries_per_inst <= 2048; max_len <= 32767.
  * Device memory held by the handle until gr_destroy, all of it allocated here: with
  * cap = max_entries_per_inst rounded up to 64, 128, .. 2048, M' = the instances of every class
- * rounded up to a multiple of 16 and added up, and N = max(max_requests, n_inst * max_entries_per_inst),
+ * rounded up to a multiple of 16 and added up, N = max(max_requests, n_inst * max_entries_per_inst) and
+ * rows = min(max_len + 1, N) rounded up to a multiple of 256,
  *   18 * n_inst * cap bytes          instance tables and the lists of feedback routing,
  *   8 * n_inst * max_entries_per_inst bytes   per held request (its instance, a spare finish time),
- *   (4.25 * M' + 12 * n_class) * min(max_len + 1, N) bytes   the per-(distinct length, instance) table
- *                                    of a scoring pass with its minima, reserved for the worst case
- *                                    whatever the batches turn out to be (290 MB for 4 096 instances of
- *                                    6 classes and max_len 16 384),
- * plus a few arrays of n_inst or max_len + 1 words.
+ *   rows * (4 * M' + 4 * [M' / 16 rounded up to 16] + 4 * [n_class rounded up to 4] + 8 * n_class + 128) bytes
+ *                                    the per-(distinct length, instance) table of a scoring pass, its minima
+ *                                    over runs and classes, and the instances that can be least, reserved for the
+ *                                    worst case whatever the batches turn out to be (296 MB for 4 096
+ *                                    instances of 6 classes and max_len 16 384),
+ *   at most 64 MB, or 1 024 * n_inst bytes if that is more   rows of that table for out_T,
+ *   0.4 MB                           selections of small batches on fleets of more than 4 096 instances,
+ * plus a few arrays of n_inst, M' or max_len + 1 words.
  */
 int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
               const double* delta, const double* alpha, const double* beta, const double* gamma,
