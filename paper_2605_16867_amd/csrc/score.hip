@@ -1117,7 +1117,7 @@ __device__ inline int64_t rest_begin(int part, int blocks, int per)
     return (int64_t)per * ((blocks / kRestParts) * part + min(part, blocks % kRestParts));
 }
 
-// A large risk scan, of which any share of the requests may be late, first half: a lane per request and its lines.
+// A risk scan, of which any share of the requests may be late, first half: a lane per request and its lines.
 // What those leave open goes on a list for the second half; kRestParts lists, so that the workgroups do not
 // wait for each other at one counter.
 template <int kItems>
@@ -1636,6 +1636,7 @@ constexpr int64_t kByClassMin = int64_t(1) << 17;      // requests from which th
 // and from which a workgroup takes 512 of them (64 otherwise; kernel time of a scan of 2.1 M with 1 024
 // 38 us, with 512 33)
 constexpr int64_t kByClassMany = int64_t(1) << 19;
+constexpr int64_t kLinesScanMin = int64_t(3) << 16;     // requests of a scan from which the lines are looked at first
 
 // A launch has fewer than 2^32 threads: kernels that take many threads per request go through larger batches
 // (2^28 requests at 16 lanes each, 2^24 at a workgroup each) a part at a time.
@@ -1771,11 +1772,14 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     // first (weight 1; in brackets deadlines that many instances meet):
     //   262 144 requests on 4 096 instances  92 / 61 (114 / 103), on 1 024 of 64 classes, no blend, 68 / 54 (57 / 69)
     //   a scan of 1 024 x 1 000             164 / 70 (179 / 131)   4 096 x 400  355 / 107 (226 / 147)
-    // Below 2^17 requests the lookup (10 to 14 us) is not won back; below 81 runs a group reads all of them at once.
-    // A large scan takes a lane per request and lists the rest, as most of it may not be late at all.
-    const bool by_lines = select && (blended || f->n_class > kGroup) && n >= kByClassMin &&
+    //   a scan of 2 048 x 100                78 / 62 (36 / 37)     1 400 x 99   56 / 49 (31 / 38)
+    // Below 2^17 requests the lookup (10 to 14 us) is not won back, in a scan below 3 * 2^16, of which hardly any may be
+    // late; below 81 runs a group reads all of them at once, so only the largest scans gain.
+    // A scan takes a lane per request and lists the rest, as most of it may not be late at all (3 270 x 130, a
+    // group of lanes per request from the lines on: 125 us, listed 92).
+    const bool by_lines = select && (blended || f->n_class > kGroup) && n >= (migrate ? kLinesScanMin : kByClassMin) &&
                           f->n_run > (migrate && n >= kByClassMany ? 2 : 5) * kGroup;
-    const bool listed = by_lines && migrate && n >= kByClassMany && f->n_run <= kRestRuns;
+    const bool listed = by_lines && migrate && f->n_run <= kRestRuns;
     // The runs' minima in blocks of rows where few requests get as far as the runs (6 us less for the
     // table of 7 061 rows x 4 096 instances); row by row where many may: a request's 16 lanes then read 16
     // runs from one cache line, not from sixteen.

@@ -82,12 +82,13 @@ def test_scan_classes_first(n_inst, held, n_class, late, clones):
     assert na >= 1 << 17 and share > 0.01
 
 
-# the lines first, a group of lanes per request (more than 80 runs, less than 2^19 requests)
+# over the runs (less than 3 * 2^16 requests), and the lines first (more than 80 runs, less than 2^19 requests)
 @pytest.mark.parametrize("obs", ["many", "few", "odd"])
 @pytest.mark.parametrize("late", ["all", "some"])
-def test_scan_lines_first(late, obs):
-    na, share, _ = _scan(1400, 99, 3, late, blend=0.5, obs=obs)
-    assert (1 << 17) <= na < (1 << 19) and share > 0.01
+@pytest.mark.parametrize("n_inst,held", [(1400, 99), (2000, 101)])
+def test_scan_lines_first(n_inst, held, late, obs):
+    na, share, _ = _scan(n_inst, held, 3, late, blend=0.5, obs=obs)
+    assert (1 << 17) <= na < (1 << 19) and (na >= 3 << 16) == (held == 101) and share > 0.01
 
 
 # the lines first, a lane per request and a list of the rest (2^19 requests and more)
