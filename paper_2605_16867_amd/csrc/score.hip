@@ -1475,7 +1475,7 @@ struct PairsArgs {
     float* out_slack;
     uint8_t* out_fallback;
     const uint16_t* len_row;
-    const int* order;
+    const int *order, *pos_of;
     const float* memo;
     const float4* instK;
     float* turned;     // [rows][n_inst]
@@ -1516,12 +1516,12 @@ __global__ __launch_bounds__(kBlock) void k_rows(PairsArgs a)
 // selection over runs is not launched.  On a small fleet that took longer than the latencies
 // themselves: whole call on 262 144 requests x 64 instances 59 us with it, 46 without; 100 000 x 128 without it 40 us, x 129
 // with it 50 (a row of lanes per request is kept up to 128 instances: eight of them per lane).
-template <int kLanes, int kVec, bool kSelect>
-__global__ __launch_bounds__(kBlock) void k_pairs(PairsArgs a)
+template <int kLanes, int kVec, bool kSelect, bool kWrite>
+__device__ __forceinline__ void pairs(const PairsArgs& a)
 {
     constexpr int kReq = pairs_requests(kSelect);
     static_assert(!kSelect || kLanes == 16, "a request's lanes are a row of a wave");
-    if (a.row0 >= a.totals[1]) return;
+    static_assert(kWrite || kVec == 1, "read where they are, an instance's values are on their own");
     const int sub = threadIdx.x % kLanes;
     const int64_t r0 = a.first + ((int64_t)blockIdx.x * (kBlock / kLanes) + threadIdx.x / kLanes) * kReq;
     if (r0 >= a.n) return;
@@ -1541,8 +1541,8 @@ __global__ __launch_bounds__(kBlock) void k_pairs(PairsArgs a)
     }
 #pragma unroll
     for (int j = 0; j < kReq; ++j) {
-        row[j] = a.len_row[L[j]] - a.row0;
-        if (r0 + j >= a.n || (unsigned)row[j] >= (unsigned)a.rows) row[j] = -1;
+        row[j] = a.len_row[L[j]] - (kWrite ? a.row0 : 0);
+        if (r0 + j >= a.n || (kWrite && (unsigned)row[j] >= (unsigned)a.rows)) row[j] = -1;
     }
     struct alignas(4 * kVec) Values { float v[kVec]; };
     for (int g = sub * kVec; g < a.n_inst; g += kLanes * kVec) {
@@ -1556,7 +1556,9 @@ __global__ __launch_bounds__(kBlock) void k_pairs(PairsArgs a)
         }
         Values E[kReq];
 #pragma unroll
-        for (int j = 0; j < kReq; ++j) E[j] = *reinterpret_cast<const Values*>(a.turned + (size_t)max(row[j], 0) * a.n_inst + g);
+        for (int j = 0; j < kReq; ++j)
+            E[j] = *reinterpret_cast<const Values*>(kWrite ? a.turned + (size_t)max(row[j], 0) * a.n_inst + g
+                                                           : a.memo + memo_at(max(row[j], 0), a.pos_of[g], a.m_pos));
 #pragma unroll
         for (int j = 0; j < kReq; ++j) {
             if (row[j] < 0) continue;
@@ -1571,7 +1573,7 @@ __global__ __launch_bounds__(kBlock) void k_pairs(PairsArgs a)
                 anyT[j] = less ? mine : anyT[j]; anyG[j] = less ? g + i : anyG[j];
                 feasKey[j] = better ? key[i] : feasKey[j]; feasG[j] = better ? g + i : feasG[j]; feasT[j] = better ? mine : feasT[j];
             }
-            *reinterpret_cast<Values*>(a.out_T + (size_t)(r0 + j) * a.n_inst + g) = E[j];
+            if (kWrite) *reinterpret_cast<Values*>(a.out_T + (size_t)(r0 + j) * a.n_inst + g) = E[j];
         }
     }
     if constexpr (kSelect) {
@@ -1589,6 +1591,19 @@ __global__ __launch_bounds__(kBlock) void k_pairs(PairsArgs a)
         }
     }
 }
+
+template <int kLanes, int kVec, bool kSelect>
+__global__ __launch_bounds__(kBlock) void k_pairs(PairsArgs a)
+{
+    if (a.row0 >= a.totals[1]) return;
+    pairs<kLanes, kVec, kSelect, true>(a);
+}
+
+// The same decision on a fleet of up to kFewInst instances, where a run holds hardly more than one or two of them and the
+// selection over runs looks at one after the other: every latency of a request from the table as it is.
+// 193 397 requests, selection over runs / this, us a call: 12 instances with a blend 53 / 35 (every pair scored
+// without the table of runs: 47), 16 without 33 / 26, 24 33 / 32, 32 34 / 34, 48 33 / 41.
+__global__ __launch_bounds__(kBlock) void k_select_few(PairsArgs a) { pairs<kGroup, 1, true, false>(a); }
 
 __global__ void k_set_int(int* p, int v) { *p = v; }
 
@@ -1637,6 +1652,8 @@ constexpr int64_t kByClassMin = int64_t(1) << 17;      // requests from which th
 // 38 us, with 512 33)
 constexpr int64_t kByClassMany = int64_t(1) << 19;
 constexpr int64_t kLinesScanMin = int64_t(3) << 16;     // requests of a scan from which the lines are looked at first
+
+constexpr int kFewInst = 16;     // instances up to which a routing batch is decided over all of them
 
 // A launch has fewer than 2^32 threads: kernels that take many threads per request go through larger batches
 // (2^28 requests at 16 lanes each, 2^24 at a workgroup each) a part at a time.
@@ -1688,14 +1705,29 @@ struct PairsPlan {
     }
 };
 
-static void launch_pairs(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, const PairsPlan& plan, int64_t max_rows,
-                         hipStream_t s)
+static PairsArgs pairs_args(const gr_fleet* f, const ReqSrc& src, const ScoreOut& out)
 {
     PairsArgs p{};
     p.ctx0 = src.ctx0; p.pred_len = src.pred_len; p.budget = src.budget; p.exclude = src.exclude;
     p.totals = f->totals; p.len_row = f->len_row; p.order = f->order; p.memo = f->memo; p.instK = f->instK; p.hD = f->hD;
     p.turned = f->turned; p.out_T = out.T; p.out_inst = out.inst; p.out_slack = out.slack; p.out_fallback = out.fallback;
+    p.pos_of = f->pos_of;
     p.n = src.n; p.rows = f->turned_rows; p.n_inst = f->n_inst; p.m_pos = f->m_pos; p.max_len = f->max_len;
+    return p;
+}
+
+static void launch_few(const gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream_t s)
+{
+    PairsArgs p = pairs_args(f, src, out);
+    constexpr int64_t per = kBlock / kGroup * pairs_requests(true), most = kLaunchThreads / kBlock * per;
+    for (p.first = 0; p.first < p.n; p.first += most)
+        hipLaunchKernelGGL(k_select_few, dim3((unsigned)((std::min(p.n - p.first, most) + per - 1) / per)), dim3(kBlock), 0, s, p);
+}
+
+static void launch_pairs(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, const PairsPlan& plan, int64_t max_rows,
+                         hipStream_t s)
+{
+    PairsArgs p = pairs_args(f, src, out);
     const int64_t per = kBlock / plan.lanes * pairs_requests(plan.select), most = kLaunchThreads / kBlock * per;
     // (parts for as many rows as there may be; those past the last row end at once)
     for (p.row0 = 0; p.row0 < max_rows; p.row0 += p.rows) {
@@ -1840,7 +1872,8 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
             hipLaunchKernelGGL(k_late_rest, dim3(kRestParts * kRestBlocks), dim3(kBlock), 0, s, a, kBlock * kRestItems);
         } else {
             ProfScope ps(f, kSelectRoute + off, s);
-            if (migrate) launch_select<true>(f, a, by_class, by_lines, s);
+            if (!migrate && f->n_inst <= kFewInst) launch_few(f, src, out, s);
+            else if (migrate) launch_select<true>(f, a, by_class, by_lines, s);
             else launch_select<false>(f, a, by_class, by_lines, s);
         }
     }
