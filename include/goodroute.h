@@ -328,10 +328,11 @@ int gr_set_batch_cap(gr_fleet* f, const int32_t* cap);
  * arriving request at a time) skips the table: a thread per (request, instance)
  * pair searches the instance's own tables, and the whole call is one kernel.
  *
- *   max_pairs   gr_score_route and gr_route_feedback score a batch (a chunk)
- *               pair by pair when n_req * (n_inst rounded up to 128) is at
- *               most this and n_req <= 4096.  0: never.  Default 262 144.
- * gr_score_route_cached and gr_risk_scan always take the table.
+ *   max_pairs   gr_score_route, gr_route_feedback (its chunks) and gr_risk_scan (its running
+ *               requests) score a batch pair by pair when n * (n_inst rounded up to
+ *               128) is at most this and n <= 4096.  0: never.  If it is never set, the
+ *               number of pairs decides (up to 524 288, with at least 16 per request).
+ * gr_score_route_cached always takes the table.
  * Equal latencies go to the lowest instance index either way.
  */
 int gr_set_small_batch_pairs(gr_fleet* f, int64_t max_pairs);

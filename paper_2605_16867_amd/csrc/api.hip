@@ -356,7 +356,7 @@ int gr_risk_scan(gr_fleet* f, const int32_t* act_off, const int32_t* act_prompt,
     src.n = n_active;
     ScoreOut o{};
     o.inst = out_target; o.slack = out_target_slack; o.n_selected = out_n_flagged;
-    return launch_score(f, src, true, o, s);
+    return launch_score(f, src, true, o, s, true);
 }
 
 int gr_observe(gr_fleet* f, double weight, const float* obs_wait, const float* obs_prefill,

@@ -36,7 +36,9 @@ constexpr int kMaxEntries = 2048;
 constexpr int kMaxClasses = 64;
 constexpr int kMaxLen = 32767;     // lengths and row numbers are kept in 16 bits
 constexpr int kMemoU = 256;        // distinct lengths per block of the table of a scoring pass
-constexpr int kDirectMax = 4096;   // most requests of a batch scored pair by pair, without grouping
+constexpr int kDirectMax = 4096;   // most requests of a batch that a caller has scored pair by pair
+constexpr int64_t kDirectPairs = int64_t(1) << 19;   // pairs of a batch that is where the sizes decide (see pair_by_pair)
+constexpr int64_t kDirectInfinite = int64_t(1) << 18;   // pairs (of whole 128 instances) up to which infinite latencies count there
 constexpr int kDirectSpan = 4096;  // instances that one workgroup takes of a request scored pair by pair
 constexpr int kDirectParts = 16384;  // room for the selections of such parts
 constexpr int kMemoP = 16;         // positions of a run of the class order
@@ -212,7 +214,7 @@ struct gr_fleet {
     unsigned long long rec_id = ~0ull;
     bool recorded = false, blend_recorded = false;
     int* pend_touched = nullptr;   // [M] 1: given requests since its table was built
-    int64_t small_batch_pairs = int64_t(1) << 18;   // largest batch, in pairs, scored pair by pair
+    int64_t small_batch_pairs = -1;   // largest batch, in pairs, scored pair by pair; -1: by the sizes (see pair_by_pair)
     gr::DirectPart* direct_part = nullptr;       // [kDirectParts] selections of the parts of a wide fleet, scored pair by pair
 };
 

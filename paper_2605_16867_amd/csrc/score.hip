@@ -1275,9 +1275,7 @@ __global__ __launch_bounds__(kBlock) void k_hits(HitArgs a)
 
 // ------------------------------------------------------------------ small batches, pair by pair
 struct DirectArgs {
-    const int *ctx0, *pred_len;
-    const float* budget;
-    const int* exclude;
+    ReqSrc s;
     const float4* instK;
     const double* hD;
     const uint16_t *tabR, *tabS;
@@ -1288,6 +1286,12 @@ struct DirectArgs {
     uint8_t* out_fallback;
     float* out_T;
     int n, n_inst, cap, max_len, parts;
+    int finite;              // 1: an infinite latency (or a NaN) is none, as in the pass over the table
+    // a risk scan: what the build left for the table pass (see ScanArgs), put in order by an extra workgroup
+    uint4* seen;
+    int *totals, *out_n;
+    const int* late_cnt;
+    int seen_words, n_late;
 };
 
 __device__ inline DirectPart no_selection() { return DirectPart{~0u, ~0u, ~0u, ~0u, ~0u, ~0u}; }
@@ -1322,15 +1326,37 @@ __device__ inline DirectPart best_over(const DirectPart& b)
     return r;
 }
 
-__device__ inline void direct_answer(const DirectArgs& a, int r, const DirectPart& b)
+__device__ inline void direct_answer(const DirectArgs& a, int r, float D, const DirectPart& b)
 {
     const bool found = b.g != ~0u;
     const uint32_t fg = b.g, ag = b.any_g, fT = b.T, aT = b.any_T;
     const int g = (int)(found ? fg : ag);          // (-1: nobody is allowed)
     const float T = from_ordered_bits(found ? fT : aT);
     a.out_inst[r] = g;
-    a.out_slack[r] = g >= 0 ? a.budget[r] - T : 0.f;
+    a.out_slack[r] = g >= 0 ? D - T : 0.f;
     if (a.out_fallback) a.out_fallback[r] = !found;
+}
+
+// What k_scan and k_memo do for a risk scan besides the table, by one workgroup: the number of flagged
+// requests (where the build has not set every flag: by the flags), and the marks of their lengths, which nobody needs here.
+__device__ void close_scan(const DirectArgs& a)
+{
+    __shared__ int sums[1024 / kWave];
+    const int tid = threadIdx.x, threads = blockDim.x;
+    const bool unset = a.totals[2] != 0 || a.s.act_off[0] > 0 || a.s.act_off[a.n_inst] < a.n;
+    int n = 0;
+    if (a.out_n) {
+        if (unset) for (int i = tid; i < a.n; i += threads) n += a.s.flag[i] != 0;
+        else for (int i = tid; i < a.n_late; i += threads) n += a.late_cnt[i];
+    }
+    for (int i = tid; i < a.seen_words; i += threads) a.seen[i] = make_uint4(0u, 0u, 0u, 0u);
+    n = wave_sum(n);
+    if (lane_id() == 0) sums[tid / kWave] = n;
+    __syncthreads();
+    if (tid != 0) return;
+    for (int w = 1; w < threads / kWave; ++w) n += sums[w];
+    if (a.out_n) *a.out_n = n;
+    a.totals[2] = 0;
 }
 
 // A batch of a few requests (one arriving request is the paper's own case): grouping by length and
@@ -1345,9 +1371,13 @@ __device__ inline void direct_answer(const DirectArgs& a, int r, const DirectPar
 // the lanes are combined in registers and, between the waves of a request, through LDS, so there is
 // no second launch and no workspace.  Fleets of more than kDirectSpan instances take several
 // workgroups per request, combined by k_direct_merge.
-template <int kLanes, int kU, bool kLargeTab>     // kU: instances of a lane in flight together
+//
+// The flagged requests of a small risk scan are taken the same way (kMigrate; a workgroup of its own
+// finishes what the table pass would have).
+template <bool kMigrate, int kLanes, int kU, bool kLargeTab>     // kU: instances of a lane in flight together
 __global__ __launch_bounds__(kLanes <= 64 ? kBlock : kLanes) void k_direct(DirectArgs a)
 {
+    if (kMigrate && blockIdx.x == gridDim.x - 1) return close_scan(a);
     constexpr int kThreads = kLanes <= 64 ? kBlock : kLanes;
     constexpr int kPerGroup = kThreads / kLanes;              // requests per workgroup
     constexpr int kS = kLargeTab ? 4 : 2, kB = kLargeTab ? 8 : 4;   // most 16-byte words of splitters, of a stride
@@ -1361,10 +1391,14 @@ __global__ __launch_bounds__(kLanes <= 64 ? kBlock : kLanes) void k_direct(Direc
     }
     const bool live = r < a.n;
     const int rc = min(r, a.n - 1);
-    const int L = min(max(a.pred_len[rc], 0), a.max_len);
-    const float c0 = (float)a.ctx0[rc], Lf = (float)L, D = a.budget[rc];
+    const Request q = fetch<kMigrate>(a.s, rc, a.max_len);
+    const int L = q.L, ex = q.ex;
+    const float c0 = (float)q.c0, Lf = (float)L, D = q.D;
     const float Dc = D > FLT_MAX ? FLT_MAX : D;
-    const int ex = a.exclude ? a.exclude[rc] : -1;
+    if (kMigrate && !__ballot(q.scored)) {      // not flagged: no migration target (a request is a workgroup's, or all of a wave's are alike)
+        if (sub == 0 && live) { a.out_inst[r] = -1; a.out_slack[r] = 0.f; }
+        return;
+    }
     const float tri = Lf * (Lf - 1.0f) * 0.5f;
     const int n_split = split_count(a.cap), stride = a.cap / n_split, s_words = n_split / 8, b_words = stride / 8;
     const int g_begin = part * kDirectSpan, g_end = a.parts > 1 ? min(g_begin + kDirectSpan, a.n_inst) : a.n_inst;
@@ -1417,7 +1451,7 @@ __global__ __launch_bounds__(kLanes <= 64 ? kBlock : kLanes) void k_direct(Direc
             const float E = fmaf(Lf, gh[u].y, gh[u].x) + tri * (K[u].z * (float)(N - k[u] + 1));
             const float T = fmaf(c0, kappa_of(make_float2(K[u].x, K[u].y), Lf), E);
             if (a.out_T && live) a.out_T[(size_t)r * a.n_inst + g[u]] = T;
-            if (g[u] != ex) {
+            if (g[u] != ex && (!a.finite || T < __builtin_inff())) {
                 const unsigned long long db = falling_bits(d[u]);
                 const uint32_t tb = ordered_bits(T);
                 DirectPart one{tb, (uint32_t)g[u], ~0u, ~0u, ~0u, ~0u};
@@ -1429,7 +1463,7 @@ __global__ __launch_bounds__(kLanes <= 64 ? kBlock : kLanes) void k_direct(Direc
 
     if constexpr (kLanes <= 64) {
         best = best_over<kLanes == 16>(best);
-        if (sub == 0 && live) direct_answer(a, r, best);
+        if (sub == 0 && live) direct_answer(a, r, D, q.scored ? best : no_selection());
     } else {
         constexpr int kN = kLanes / kWave;
         static_assert(kN <= 16, "one row of lanes takes the waves' selections");
@@ -1442,7 +1476,7 @@ __global__ __launch_bounds__(kLanes <= 64 ? kBlock : kLanes) void k_direct(Direc
             if (threadIdx.x < kN) best = waves[threadIdx.x];
             best = best_over<true>(best);
             if (threadIdx.x == 0) {
-                if (a.parts == 1) direct_answer(a, r, best);
+                if (a.parts == 1) direct_answer(a, r, D, best);
                 else a.parts_out[(size_t)r * a.parts + part] = best;
             }
         }
@@ -1457,7 +1491,7 @@ __global__ __launch_bounds__(kBlock) void k_direct_merge(DirectArgs a)
     DirectPart best = no_selection();
     for (int i = lane_id(); i < a.parts; i += kWave) take_better(best, a.parts_out[(size_t)r * a.parts + i]);
     best = best_over<false>(best);
-    if (lane_id() == 0) direct_answer(a, r, best);
+    if (lane_id() == 0) direct_answer(a, r, a.s.budget[r], best);
 }
 
 // ------------------------------------------------------------------ every pair's latency (out_T)
@@ -1609,32 +1643,39 @@ __global__ void k_set_int(int* p, int v) { *p = v; }
 
 }  // namespace
 
-// Alg. 1 pair by pair for up to kDirectMax requests.
-int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream_t s)
+// Alg. 1 pair by pair.
+template <bool kMigrate>
+static int launch_pair_by_pair(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, bool finite, hipStream_t s)
 {
     const int n = (int)src.n, M = f->n_inst;
     if (n == 0) return GR_OK;
-    if (src.n > kDirectMax) return GR_ERR_TOO_LARGE;
+    if (src.n > std::max<int64_t>(kDirectMax, kDirectPairs / kGroup)) return GR_ERR_TOO_LARGE;
     DirectArgs d{};
-    d.ctx0 = src.ctx0; d.pred_len = src.pred_len; d.budget = src.budget; d.exclude = src.exclude;
+    d.s = src;
     d.instK = f->instK; d.hD = f->hD; d.tabR = f->tabR; d.tabS = f->tabS; d.tabGH = f->tabGH;
     d.parts_out = f->direct_part;
     d.out_inst = out.inst; d.out_slack = out.slack; d.out_fallback = out.fallback; d.out_T = out.T;
-    d.n = n; d.n_inst = M; d.cap = f->cap; d.max_len = f->max_len;
-    d.parts = (M + kDirectSpan - 1) / kDirectSpan;
+    d.n = n; d.n_inst = M; d.cap = f->cap; d.max_len = f->max_len; d.finite = finite;
+    d.parts = kMigrate ? 1 : (M + kDirectSpan - 1) / kDirectSpan;
     if ((int64_t)n * d.parts > kDirectParts) d.parts = 1;      // (many requests fill the chip as they are)
+    if (kMigrate) {
+        d.seen = reinterpret_cast<uint4*>(f->seen); d.seen_words = (f->bins + 15) / 16;
+        d.totals = f->totals; d.out_n = out.n_selected; d.late_cnt = f->late_cnt; d.n_late = M * f->late_parts;
+    }
     // lanes per request: an instance each as far as a workgroup goes (few requests: the chain of reads
-    // of one instance is the time of the call); 64 lanes leave the fewest idle on small fleets
-    const int lanes = M <= 16 ? 16 : M <= 64 ? 64 : M <= 512 ? 256 : 1024;
+    // of one instance is the time of the call); 64 lanes leave the fewest idle on small fleets, 16 with two
+    // instances each up to 32 (16 384 requests x 32 instances 6.7 us, 8.9 with 64 lanes)
     {
         ProfScope ps(f, kDirect, s);
 #define GR_LAUNCH_DIRECT(N, U) do { \
-        const dim3 grid(N <= 64 ? (n + kBlock / N - 1) / (kBlock / N) : n * d.parts), block(N <= 64 ? kBlock : N); \
-        if (f->cap > 512) hipLaunchKernelGGL((k_direct<N, (U > 2 ? 2 : U), true>), grid, block, 0, s, d); \
-        else hipLaunchKernelGGL((k_direct<N, U, false>), grid, block, 0, s, d); } while (0)
-        if (lanes == 16) GR_LAUNCH_DIRECT(16, 1);
-        else if (lanes == 64) GR_LAUNCH_DIRECT(64, 1);
-        else if (lanes == 256) GR_LAUNCH_DIRECT(256, 1);
+        constexpr int per = N <= 64 ? kBlock / (N <= 64 ? N : 1) : 1;      /* requests per workgroup */ \
+        const dim3 grid((per > 1 ? (n + per - 1) / per : n * d.parts) + (kMigrate ? 1 : 0)), block(per > 1 ? kBlock : N); \
+        if (f->cap > 512) hipLaunchKernelGGL((k_direct<kMigrate, N, (U > 2 ? 2 : U), true>), grid, block, 0, s, d); \
+        else hipLaunchKernelGGL((k_direct<kMigrate, N, U, false>), grid, block, 0, s, d); } while (0)
+        if (M <= 16) GR_LAUNCH_DIRECT(16, 1);
+        else if (M <= 32) GR_LAUNCH_DIRECT(16, 2);
+        else if (M <= 64) GR_LAUNCH_DIRECT(64, 1);
+        else if (M <= 512) GR_LAUNCH_DIRECT(256, 1);
         else if (M <= 1024) GR_LAUNCH_DIRECT(1024, 1);
         else GR_LAUNCH_DIRECT(1024, 4);
 #undef GR_LAUNCH_DIRECT
@@ -1645,6 +1686,24 @@ int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream
         hipLaunchKernelGGL(k_direct_merge, dim3((n + per - 1) / per), dim3(kBlock), 0, s, d);
     }
     return hipGetLastError() == hipSuccess ? GR_OK : GR_ERR_HIP;
+}
+
+int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream_t s)
+{
+    return launch_pair_by_pair<false>(f, src, out, false, s);
+}
+
+// Whether a batch is scored pair by pair: as the caller says (gr_set_small_batch_pairs), or by the number of pairs.
+// A pass over the table is three or four launches, 15 to 20 us whatever the batch; this is one of 4 us
+// and grows with the pairs.  Routing call, us, table / pairs:
+//   4 096 requests x 32 instances 17.1 / 4.6, x 64 17.8 / 6.5, x 128 18.8 / 10.3; x 256 19.5 / 18.9
+//   2 048 x 256                   19.4 / 11.5   1 024 x 256 19.2 / 7.9;  1 024 x 1 024 20.3 / 24.9
+// and a risk scan with its status build, 32 x 512 requests 23.6 / 11.2, 64 x 128 18.9 / 10.5, 16 x 1 000 29.1 / 13.0.
+// (A request takes 16 lanes at least.)
+static bool pair_by_pair(const gr_fleet* f, int64_t n)
+{
+    if (f->small_batch_pairs >= 0) return n <= kDirectMax && n * f->m_pad <= f->small_batch_pairs;
+    return n * std::max(f->n_inst, kGroup) <= kDirectPairs;
 }
 
 constexpr int64_t kByClassMin = int64_t(1) << 17;      // requests from which the classes are looked at first
@@ -1758,8 +1817,12 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         if (out.n_selected) hipLaunchKernelGGL(k_set_int, dim3(1), dim3(1), 0, s, out.n_selected, 0);
         return hipGetLastError() == hipSuccess ? GR_OK : GR_ERR_HIP;
     }
-    if (small_batch_ok && !migrate && n <= kDirectMax && n * f->m_pad <= f->small_batch_pairs)
-        return launch_direct(f, src, out, s);
+    if (small_batch_ok && pair_by_pair(f, n)) {
+        // (small routing batches have always taken infinite latencies for latencies here)
+        const bool small = n <= kDirectMax && n * f->m_pad <= kDirectInfinite;
+        return migrate ? launch_pair_by_pair<true>(f, src, out, true, s)
+                       : launch_pair_by_pair<false>(f, src, out, f->small_batch_pairs < 0 && !small, s);
+    }
     // The class order of the current status, if nobody is known to have made it, comes first: always while
     // the stream is being captured (a recorded pass may be replayed after a status build that was
     // recorded elsewhere), and always once a status build has been recorded.
