@@ -131,7 +131,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     const size_t tab = (size_t)n_inst * f->cap, seen_bytes = (size_t)(f->bins + 15) / 16 * 16;
     const bool ok =
         dev_alloc(&f->cls, n_class) && dev_alloc(&f->inst_class, n_inst) &&
-        dev_alloc(&f->tabR, tab) && dev_alloc(&f->tabGH, (size_t)n_inst * (f->cap + 2)) &&
+        dev_alloc(&f->tabR, tab + kWave) && dev_alloc(&f->tabGH, (size_t)n_inst * (f->cap + 2)) &&
         dev_alloc(&f->hD, n_inst) &&
         dev_alloc(&f->emaQ, n_inst) && dev_alloc(&f->emaP, n_inst) && dev_alloc(&f->emaD, n_inst) &&
         dev_alloc(&f->instK, n_inst) && dev_alloc(&f->tabS, (size_t)n_inst * f->n_split) &&
@@ -141,7 +141,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
         dev_alloc(&f->pend_cnt, n_inst) && dev_alloc(&f->commit_mark, n_inst) && dev_alloc(&f->pend_touched, n_inst) && dev_alloc(&f->pend_prompt, tab) && dev_alloc(&f->pend_len, tab) &&
         dev_alloc(&f->scratch_finish, f->max_active + kBlock * kRestItems) && dev_alloc(&f->batch_cap, n_inst) &&
         dev_alloc(&f->seen, seen_bytes) && dev_alloc(&f->late_cnt, (size_t)n_inst * 4) &&
-        dev_alloc(&f->row_len, f->row_cap) && dev_alloc(&f->len_row, f->bins) && dev_alloc(&f->totals, 4) &&
+        dev_alloc(&f->row_len, f->row_cap) && dev_alloc(&f->len_row, f->bins + 1) && dev_alloc(&f->totals, 4) &&
         dev_alloc(&f->memo, (size_t)f->row_cap * f->m_pos) && dev_alloc(&f->grp_min, (size_t)f->row_cap * f->run_pad) &&
         dev_alloc(&f->run_k, f->n_run) && dev_alloc(&f->run_rank, f->n_run) && dev_alloc(&f->run_at, f->n_run) && dev_alloc(&f->pos_thr, f->m_pos) && dev_alloc(&f->class_min, (size_t)f->row_cap * f->c_pad) &&
         dev_alloc(&f->cls_bound, n_class) && dev_alloc(&f->class_next, (size_t)f->row_cap * n_class) &&
@@ -166,7 +166,8 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     clear(f->totals, sizeof(int) * 4);
     // tables without an entry, as far as the reads go: a status build may be recorded first, and a direct call
     // come before its first replay
-    sent = sent && hipMemset(f->tabR, 0xFF, tab * sizeof(uint16_t)) == hipSuccess &&
+    sent = sent && hipMemset(f->tabR, 0xFF, (tab + kWave) * sizeof(uint16_t)) == hipSuccess &&
+           hipMemset(f->len_row + f->bins, 0xFF, sizeof(uint16_t)) == hipSuccess &&
            hipMemset(f->tabS, 0xFF, (size_t)n_inst * f->n_split * sizeof(uint16_t)) == hipSuccess;
     clear(f->tabGH, (size_t)n_inst * (f->cap + 2) * sizeof(float2));
     clear(f->instK, sizeof(float4) * n_inst);

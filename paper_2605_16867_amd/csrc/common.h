@@ -32,6 +32,7 @@ namespace gr {
 
 constexpr int kBlock = 256;
 constexpr int kWave = 64;
+constexpr int kSimds = 1024;       // 256 compute units of four
 constexpr int kMaxEntries = 2048;
 constexpr int kMaxClasses = 64;
 constexpr int kMaxLen = 32767;     // lengths and row numbers are kept in 16 bits
@@ -153,7 +154,7 @@ struct gr_fleet {
     int* inst_class = nullptr;
     // per-instance tables written by the status build
     // E_g(L) = Gq + L*H + tri(L)*gamma*(n+1) on the segment after the k shortest requests (n still running)
-    uint16_t* tabR = nullptr; // [M][cap] remaining lengths, ascending; 0xFFFF past the last entry
+    uint16_t* tabR = nullptr; // [M][cap] remaining lengths, ascending; 0xFFFF past the last entry (and room for a wave's reads behind it)
     float2* tabGH = nullptr;  // [M][cap + 2] (Gq, H) of segment k, see gh_at; segment 0 is (q_g, alpha + beta*(N+1) + gamma*sum of contexts)
     double* hD = nullptr;    // [M] d_g
     // [M] what a pair needs of its instance besides the tables: (delta, gamma) of the latency's prefill
@@ -191,9 +192,9 @@ struct gr_fleet {
     int* late_cnt = nullptr;  // [4][M] flagged requests, counted by the build (late_parts counts per instance)
     int late_parts = 0;
     int* row_len = nullptr;   // [row_cap] the distinct lengths ("rows"), ascending
-    uint16_t* len_row = nullptr;  // [bins] rows shorter than each length = its row if it has one
+    uint16_t* len_row = nullptr;  // [bins + 1] rows shorter than each length = its row if it has one; 0xFFFF (past every row) at the end
     int* totals = nullptr;    // [4] -, distinct lengths, 1: flags that the risk scan's build has not set (zero between calls)
-    float* memo = nullptr;       // [row_cap / kMemoU][m_pos][kMemoU] E per distinct length and position
+    float* memo = nullptr;       // [row_cap / kMemoU][n_run][kMemoU][kMemoP] E per distinct length and position
     float* grp_min = nullptr;    // [row_cap][run_pad] least E of each run, per row (see runs_at)
     uint32_t* run_rank = nullptr;   // [n_run] runs whose first instance is more capable than the run's first
     int* run_at = nullptr;          // [n_run] the run of each rank

@@ -168,7 +168,7 @@ struct MemoArgs {
     const int *row_len, *order;
     const uint16_t* len_row;
     const float4* instK;
-    const uint16_t *tabR, *tabS;
+    const uint16_t* tabR;
     const float2* tabGH;
     float* memo;           // see memo_at
     float* grp_min;        // see runs_at
@@ -180,13 +180,17 @@ struct MemoArgs {
     const uint4* run_head;
     uint4* seen;           // cleared here for the next batch (its reader is done), as is totals[2]
     int seen_words;        // of 16 bytes
-    int n_run, m_pos, run_pad, cap;
+    int n_run, run8, run_pad, cap, bins;      // run8: n_run rounded up to a multiple of the XCDs
 };
 
-// The table is cut into blocks of kMemoU rows; in a block a position's values are consecutive.
-__device__ inline size_t memo_at(int64_t row, int pos, int m_pos)
+// The table is cut into blocks of kMemoU rows; a run's part of a block is consecutive, row by row, so that the
+// kMemoP values of a row and run are one piece of 64 bytes: what a request looks at, and what a lane per row
+// reads.  (With a position's values of 256 rows together instead every one of them was a cache line of its own.)
+constexpr int kTile = kMemoU * kMemoP;
+
+__device__ inline size_t memo_at(int64_t row, int run, int n_run)
 {
-    return ((size_t)(row / kMemoU) * m_pos + pos) * kMemoU + (size_t)(row % kMemoU);
+    return ((size_t)(row / kMemoU) * n_run + run) * kTile + (size_t)(row % kMemoU) * kMemoP;
 }
 
 // The runs' least values: row by row where a request's lanes take 16 runs of its row at a time, in
@@ -208,31 +212,44 @@ __device__ inline float min_plain(float a, float b)
     return r;
 }
 
+template <int kCtrl>
+__device__ inline float quad_move(float x)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xf, 0xf, true));
+}
+
 // E of every (distinct length, instance).  A workgroup takes a run of kMemoP positions of the class
 // order and a block of kMemoU consecutive distinct lengths ("rows", ascending), a wave four of the
 // positions, a lane four rows.  The segment of a row is k = #{R_i <= L}.  The instance's lengths R
-// and the rows are both sorted, so the entries up to the block and in it are found with one search
-// each (a lane per instance and end: splitters, then one stride), the entries in the block (a
-// handful) add one each to the counter of the first row that is at least as long, and a prefix
-// sum over the counters gives k for every row.  The four instances of a wave are in flight together.
+// and the rows are both sorted: every eighth length (a lane each) says where the entries of the
+// block begin to within eight, and the entries from there on (a lane each, almost always one read) add one to the counter
+// of the first row that is at least as long; a prefix sum over the counters gives k for every
+// row.  The four instances of a wave are in flight together.
 //
-// A lane keeps its rows' values in registers from the counters to the store and the minimum over
-// positions is a running one, so there is no transpose and one barrier.  Kernel time on 4 096 instances of
-// 512 requests: 2 726 rows 25 us, 7 061 rows 46 us (116 MB written: 2.5 TB/s; the rest is the vector ALU
-// and the chain of reads a workgroup begins with); with the table laid out row by row, a wave per
-// instance, a pass through LDS to turn a block and the minimum taken over lanes, 42 and 65 us.  The runs'
-// minima written row by row cost 4 and 6 us more.  Seven waves per SIMD: at eight the registers spill (65 us).
+// What bounds it is the chain of reads a workgroup begins with (instance; its every eighth length; its entries; their
+// rows; the segments), then the vector ALU and the store.  A lane has four rows of four positions: the values are
+// turned in LDS, so that the store is consecutive, and the least of a run is taken on the way out.  A run's blocks are
+// all on one XCD (every eighth workgroup), whose L2 then has its instances' tables.  Kernel time, us, on 4 096 instances of 512
+// requests 2 726 rows 29, 7 061 rows 41; 1 024 x 1 000, 3 900 rows 15.5; 256 x 512 8.2.  With two searches per instance
+// (splitters, then a stride), 64 entries at a time, 30 / 46 / 18.6 / 11.2, without the XCDs 31 / 43 / 17.5 / 8.5.
+// A workgroup for several blocks, the next one's entries on their way: 104 registers, 27 / 43 / 21.5 / 9.0.
+constexpr int kMemoPerSimd = 7;     // waves per SIMD
 constexpr int kMemoWaves = kBlock / kWave;
 constexpr int kMemoInst = kMemoP / kMemoWaves;      // instances of a wave
 static_assert(kMemoU == 4 * kWave, "a lane owns four consecutive rows");
 
-// For each position of a run, how many runs begin with a more capable instance: 16 lanes each.
+// For each position of a run, how many runs begin with a more capable instance: 16 lanes each.  And what the
+// selection needs of the run: its least and largest delta (gamma is the same for all of a class) and its lowest instance.
 __device__ __forceinline__ void rank_run(const MemoArgs& a, int run)
 {
+    for (int i = run * kBlock + threadIdx.x; i < a.seen_words; i += a.n_run * kBlock) a.seen[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (run == 0 && threadIdx.x == 0) a.totals[2] = 0;
     static_assert(kBlock == kMemoP * kMemoP, "16 lanes per position of the run");
     const int p = run * kMemoP + threadIdx.x / kMemoP, sub = threadIdx.x % kMemoP;
     const unsigned long long key = a.posKey[p];
     const int g = a.order[p];
+    const float2 kk = a.posK[run * kMemoP + sub];
+    const int gi = a.order[run * kMemoP + sub];
     uint32_t n = 0;
     constexpr int kAhead = 8;
     for (int r0 = sub; r0 < a.n_run; r0 += kAhead * kMemoP) {
@@ -245,106 +262,117 @@ __device__ __forceinline__ void rank_run(const MemoArgs& a, int run)
             n += r0 + i * kMemoP < a.n_run && (hk < key || (hk == key && (int)h[i].z < g));
         }
     }
+    float lo = kk.x, hi = gi >= 0 ? kk.x : -__builtin_inff();
+    float gm = gi >= 0 ? kk.y : 0.f;
+    int low = gi >= 0 ? gi : 0x7fffffff;
 #pragma unroll
-    for (int d = 1; d < kMemoP; d <<= 1) n += __shfl_xor(n, d, kMemoP);
+    for (int d = 1; d < kMemoP; d <<= 1) {
+        n += __shfl_xor(n, d, kMemoP);
+        lo = fminf(lo, __shfl_xor(lo, d, kMemoP));
+        hi = fmaxf(hi, __shfl_xor(hi, d, kMemoP));
+        gm = fmaxf(gm, __shfl_xor(gm, d, kMemoP));
+        low = min(low, __shfl_xor(low, d, kMemoP));
+    }
     if (sub == 0) {
         a.pos_thr[p] = n;
-        if (threadIdx.x == 0) { a.run_rank[run] = n; a.run_at[n] = run; }
+        if (threadIdx.x == 0) {
+            a.run_rank[run] = n;
+            a.run_at[n] = run;
+            a.run_k[run] = make_float4(lo, gm, hi, __int_as_float(low));
+        }
     }
 }
 
-template <bool kLargeTab, bool kBlocks>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 7))) void k_memo(MemoArgs a)
-{
-    constexpr int kS = kLargeTab ? 4 : 2, kB = kLargeTab ? 8 : 4;   // most 16-byte words of splitters, of a stride
-    __shared__ int cnt_lds[kMemoWaves][kMemoInst][kMemoU];
-    __shared__ float min_lds[kMemoWaves][kMemoU];
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < a.seen_words; i += gridDim.x * kBlock)
-        a.seen[i] = make_uint4(0u, 0u, 0u, 0u);
-    if (blockIdx.x == 0 && threadIdx.x == 0) a.totals[2] = 0;
-    // (the first n_run workgroups rank the runs for the selection: next to the others, not behind them)
-    if ((int)blockIdx.x < a.n_run) return rank_run(a, blockIdx.x);
-    const int U = a.totals[1];
-    const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int pass = blockIdx.x / a.n_run - 1, run = blockIdx.x % a.n_run;
-    const int ub = pass * kMemoU, ue = min(ub + kMemoU, U);
-    if (ub >= ue) return;
-    const int p0 = run * kMemoP + wave * kMemoInst;
+// Rows of the tile in LDS are kTileRow words apart, and a row's four pieces change places every 16 rows: the lanes'
+// writes (four rows of 16 bytes each, 80 words from lane to lane) and the consecutive reads both spread over the banks.
+constexpr int kTileRow = kMemoP + 4;
+__device__ inline int tile_at(int row, int piece) { return row * kTileRow + 4 * (piece ^ ((row >> 4) & 3)); }
 
-    // this lane's rows (past the last one: length 0, never read)
+template <int kEighths, bool kBlocks>     // kEighths x 64 eighths of an instance's lengths at most
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMemoPerSimd, kMemoPerSimd))) void k_memo(MemoArgs a)
+{
+    __shared__ __align__(16) int lds[kMemoU * kTileRow];       // the counters, then the tile
+    static_assert(kMemoU * kTileRow >= kMemoWaves * kMemoInst * kMemoU, "room for the counters");
+    // (the first workgroups rank the runs for the selection: next to the others, not behind them)
+    const int pass = blockIdx.x / a.run8 - 1, run = blockIdx.x % a.run8;
+    if (run >= a.n_run) return;
+    if (pass < 0) return rank_run(a, run);
+    const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int ub = pass * kMemoU, p0 = run * kMemoP + wave * kMemoInst;
+
+    // this lane's rows, the length before the block, the wave's instances: one trip, and the number of rows with it
+    int4 r = *reinterpret_cast<const int4*>(a.row_len + ub + 4 * lane);
+    const int L_before = ub > 0 ? a.row_len[ub - 1] : -1;
+    int g[kMemoInst], gs[kMemoInst];
+#pragma unroll
+    for (int j = 0; j < kMemoInst; ++j) g[j] = a.order[p0 + j];
+    const int U = a.totals[1];
+    asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w));
+    if (ub >= U) return;
+    const int ue = ub + kMemoU;
+
+    float4 K[kMemoInst];
+    int eighth[kMemoInst][kEighths];
+    const uint16_t* R[kMemoInst];
+#pragma unroll
+    for (int j = 0; j < kMemoInst; ++j) {
+        gs[j] = max(g[j], 0);
+        K[j] = a.instK[gs[j]];
+        R[j] = a.tabR + (size_t)gs[j] * a.cap;
+#pragma unroll
+        for (int c = 0; c < kEighths; ++c) eighth[j][c] = R[j][(unsigned)min(8 * (lane + c * kWave) + 7, a.cap - 1)];      // (past the table: the last one again)
+    }
+    int* const cnt = lds + wave * kMemoInst * kMemoU;
+#pragma unroll
+    for (int j = 0; j < kMemoInst; ++j) reinterpret_cast<int4*>(cnt + j * kMemoU)[lane] = make_int4(0, 0, 0, 0);
+
+    // Of each instance the 64 entries from kb on, this lane's: its row (the first one at least as long).  kb: entries before
+    // the block, less up to seven.  (What lies behind the instance's table is read as well, and masked.)
+    int kb[kMemoInst], er[kMemoInst];
+    unsigned long long valid[kMemoInst];
+#pragma unroll
+    for (int j = 0; j < kMemoInst; ++j) {
+        int n = 0;
+#pragma unroll
+        for (int c = 0; c < kEighths; ++c) n += __popcll(__ballot(eighth[j][c] <= L_before));
+        kb[j] = min(8 * n, a.cap);
+        valid[j] = a.cap - kb[j] >= kWave ? ~0ull : (1ull << (a.cap - kb[j])) - 1ull;
+        er[j] = R[j][(unsigned)(kb[j] + lane)];
+    }
+#pragma unroll
+    for (int j = 0; j < kMemoInst; ++j) er[j] = a.len_row[(unsigned)min(er[j], a.bins)];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int j = 0; j < kMemoInst; ++j) {
+        const bool in = ((valid[j] >> lane) & 1ull) && (unsigned)(er[j] - ub) < (unsigned)kMemoU;
+        if (in) atomicAdd(&cnt[j * kMemoU + er[j] - ub], 1);
+        const int from = kb[j] + kWave;
+        kb[j] += __popcll(__ballot(er[j] < ub) & valid[j]);
+        // more than 64 are in the block (the shortest lengths): 512 at a time
+        if (!(__ballot(in) >> (kWave - 1))) continue;
+        for (int e0 = from; e0 < a.cap; e0 += 8 * kWave) {
+            const int e = e0 + 8 * lane;
+            uint4 w = make_uint4(~0u, ~0u, ~0u, ~0u);
+            if (e < a.cap) w = *reinterpret_cast<const uint4*>(R[j] + (unsigned)e);
+            const uint32_t words[4] = {w.x, w.y, w.z, w.w};
+            int row[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) row[i] = a.len_row[min(i % 2 ? words[i / 2] >> 16 : words[i / 2] & 0xFFFFu, (uint32_t)a.bins)];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (row[i] < ue) atomicAdd(&cnt[j * kMemoU + row[i] - ub], 1);       // (in order: none is before the block)
+            if (__builtin_amdgcn_readlane(row[7], kWave - 1) >= ue) break;
+        }
+    }
     float Lf[4], tri[4];
     {
-        const int4 r = *reinterpret_cast<const int4*>(a.row_len + ub + 4 * lane);
-        const int u = ub + 4 * lane;
-        const int L[4] = {u < U ? r.x : 0, u + 1 < U ? r.y : 0, u + 2 < U ? r.z : 0, u + 3 < U ? r.w : 0};
+        const int L[4] = {r.x, r.y, r.z, r.w};        // (past the last row: whatever is there, never read)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             Lf[i] = (float)L[i];
             tri[i] = Lf[i] * (Lf[i] - 1.0f) * 0.5f;
-        }
-    }
-
-    // entries up to the block's first row (lanes 0 .. 3: exclusive) and up to its last (lanes 4 .. 7)
-    int my_g, my_k = 0;
-    float4 my_K{};
-    {
-        const bool last = lane & kMemoInst;
-        my_g = a.order[p0 + lane % kMemoInst];
-        const int g = max(my_g, 0);
-        const uint32_t L = (uint32_t)(last ? a.row_len[ue - 1] : ub > 0 ? a.row_len[ub - 1] : 0);
-        const int n_split = split_count(a.cap), stride = a.cap / n_split, s_words = n_split / 8, b_words = stride / 8;
-        my_K = a.instK[g];
-        uint4 w[kB];
-        const uint4* __restrict__ S = reinterpret_cast<const uint4*>(a.tabS + (size_t)g * n_split);
-#pragma unroll
-        for (int i = 0; i < kS; ++i)
-            if (i < s_words) w[i] = S[i];
-        int b = 0;
-#pragma unroll
-        for (int i = 0; i < kS; ++i)
-            if (i < s_words) b += count_upto(w[i], L);
-        my_k = min(b, n_split - 1) * stride;
-        const uint4* __restrict__ R = reinterpret_cast<const uint4*>(a.tabR + (size_t)g * a.cap + my_k);
-#pragma unroll
-        for (int i = 0; i < kB; ++i)
-            if (i < b_words) w[i] = R[i];
-#pragma unroll
-        for (int i = 0; i < kB; ++i)
-            if (i < b_words) my_k += count_upto(w[i], L);
-        if (!last && ub == 0) my_k = 0;
-    }
-
-    int g[kMemoInst], kb[kMemoInst], ke[kMemoInst];
-#pragma unroll
-    for (int j = 0; j < kMemoInst; ++j) {
-        g[j] = __builtin_amdgcn_readlane(my_g, j);
-        kb[j] = __builtin_amdgcn_readlane(my_k, j);
-        ke[j] = g[j] >= 0 ? __builtin_amdgcn_readlane(my_k, j + kMemoInst) : kb[j];
-    }
-    int* const cnt = &cnt_lds[wave][0][0];
-#pragma unroll
-    for (int j = 0; j < kMemoInst; ++j) reinterpret_cast<int4*>(cnt + j * kMemoU)[lane] = make_int4(0, 0, 0, 0);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    {   // 64 entries of each instance at a time; almost always that is all there are
-        int done = 0, most = 0;
-#pragma unroll
-        for (int j = 0; j < kMemoInst; ++j) most = max(most, ke[j] - kb[j]);
-        for (; done < most; done += kWave) {
-            int row[kMemoInst];
-#pragma unroll
-            for (int j = 0; j < kMemoInst; ++j) {
-                const int e = kb[j] + done + lane;
-                row[j] = -1;
-                if (e < ke[j]) row[j] = a.tabR[(size_t)g[j] * a.cap + (unsigned)e];
-            }
-#pragma unroll
-            for (int j = 0; j < kMemoInst; ++j)
-                if (row[j] >= 0) row[j] = a.len_row[row[j]];
-#pragma unroll
-            for (int j = 0; j < kMemoInst; ++j)
-                if (row[j] >= 0) atomicAdd(&cnt[j * kMemoU + ((row[j] - ub) & (kMemoU - 1))], 1);
         }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -354,57 +382,43 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(7, 7))) 
     float2 gh[kMemoInst][4];
 #pragma unroll
     for (int j = 0; j < kMemoInst; ++j) {
-        int4 c = make_int4(0, 0, 0, 0);
-        if (ke[j] > kb[j]) {
-            c = reinterpret_cast<const int4*>(cnt + j * kMemoU)[lane];
-            c.y += c.x; c.z += c.y; c.w += c.z;
-            const int before = wave_incl_scan_i32(c.w) - c.w;
-            c.x += before; c.y += before; c.z += before; c.w += before;
-        }
-        k[j][0] = kb[j] + c.x; k[j][1] = kb[j] + c.y; k[j][2] = kb[j] + c.z; k[j][3] = kb[j] + c.w;
-        const char* __restrict__ GH = reinterpret_cast<const char*>(a.tabGH + gh_at(max(g[j], 0), 0, a.cap));
+        int4 c = reinterpret_cast<const int4*>(cnt + j * kMemoU)[lane];
+        c.y += c.x; c.z += c.y; c.w += c.z;
+        const int before = kb[j] + wave_incl_scan_i32(c.w) - c.w;
+        k[j][0] = before + c.x; k[j][1] = before + c.y; k[j][2] = before + c.z; k[j][3] = before + c.w;
+        const char* __restrict__ GH = reinterpret_cast<const char*>(a.tabGH + gh_at(gs[j], 0, a.cap));
 #pragma unroll
         for (int i = 0; i < 4; ++i) gh[j][i] = *reinterpret_cast<const float2*>(GH + (unsigned)k[j][i] * (unsigned)sizeof(float2));
     }
-    float least[4] = {__builtin_inff(), __builtin_inff(), __builtin_inff(), __builtin_inff()};
+    float E[4][kMemoInst];
 #pragma unroll
     for (int j = 0; j < kMemoInst; ++j) {
-        if (g[j] < 0) continue;
-        const float gam = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_K.z), j));
-        const int N = __builtin_amdgcn_readlane(__float_as_int(my_K.w), j);
-        float E[4];
+        const int N1 = __float_as_int(K[j].w) + 1;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            E[i] = fmaf(Lf[i], gh[j][i].y, gh[j][i].x) + tri[i] * (gam * (float)(N - k[j][i] + 1));
-            least[i] = min_plain(least[i], E[i]);
-        }
-        *reinterpret_cast<float4*>(a.memo + ((size_t)pass * a.m_pos + p0 + j) * kMemoU + 4 * lane) = make_float4(E[0], E[1], E[2], E[3]);
+        for (int i = 0; i < 4; ++i) E[i][j] = fmaf(Lf[i], gh[j][i].y, gh[j][i].x) + tri[i] * (K[j].z * (float)(N1 - k[j][i]));
     }
-    reinterpret_cast<float4*>(min_lds[wave])[lane] = make_float4(least[0], least[1], least[2], least[3]);
+    __syncthreads();        // (every wave has its counters)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<float4*>(lds + tile_at(4 * lane + i, wave)) = make_float4(E[i][0], E[i][1], E[i][2], E[i][3]);
     __syncthreads();
-    {
-        float m = min_lds[0][tid];
+    // (positions without an instance, at the end of a class: infinite)
+    const int4 at = *reinterpret_cast<const int4*>(a.order + run * kMemoP + 4 * (lane % 4));
+    const bool padded = __any(min(min(at.x, at.y), min(at.z, at.w)) < 0);
+    float* __restrict__ out = a.memo + memo_at(ub, run, a.n_run);
 #pragma unroll
-        for (int w = 1; w < kMemoWaves; ++w) m = min_plain(m, min_lds[w][tid]);
-        if (ub + tid < ue) a.grp_min[runs_at<kBlocks>(ub + tid, a.run_pad) + (size_t)run * kRunStride<kBlocks>] = m;
-    }
-
-    // what the selection needs of the run: its least and largest delta (gamma is the same for all of
-    // a class) and its lowest instance
-    if (pass == 0 && tid < kMemoP) {
-        const float2 kk = a.posK[run * kMemoP + tid];
-        const int gi = a.order[run * kMemoP + tid];
-        float lo = kk.x, hi = gi >= 0 ? kk.x : -__builtin_inff();
-        float gm = gi >= 0 ? kk.y : 0.f;
-        int low = gi >= 0 ? gi : 0x7fffffff;
-#pragma unroll
-        for (int d = 1; d < kMemoP; d <<= 1) {
-            lo = fminf(lo, __shfl_xor(lo, d, kMemoP));
-            hi = fmaxf(hi, __shfl_xor(hi, d, kMemoP));
-            gm = fmaxf(gm, __shfl_xor(gm, d, kMemoP));
-            low = min(low, __shfl_xor(low, d, kMemoP));
+    for (int i = 0; i < 4; ++i) {
+        const int c = tid + i * kBlock, row = c / 4;
+        float4 e = *reinterpret_cast<const float4*>(lds + tile_at(row, c % 4));
+        if (padded) {
+            const float inf = __builtin_inff();
+            e = make_float4(at.x < 0 ? inf : e.x, at.y < 0 ? inf : e.y, at.z < 0 ? inf : e.z, at.w < 0 ? inf : e.w);
         }
-        if (tid == 0) a.run_k[run] = make_float4(lo, gm, hi, __int_as_float(low));
+        reinterpret_cast<float4*>(out)[c] = e;
+        float m = min_plain(min_plain(e.x, e.y), min_plain(e.z, e.w));
+        m = min_plain(m, quad_move<0xB1>(m));      // quad_perm [1,0,3,2], [2,3,0,1]
+        m = min_plain(m, quad_move<0x4E>(m));
+        if (c % 4 == 0 && ub + row < U) a.grp_min[runs_at<kBlocks>(ub + row, a.run_pad) + (size_t)run * kRunStride<kBlocks>] = m;
     }
 }
 
@@ -446,7 +460,7 @@ struct ClassArgs {
     float* class_min;
     uint2* class_next;
     float4* cls_bound;
-    int n_class, c_pad, m_pos, run_pad;
+    int n_class, c_pad, n_run, run_pad;
 };
 
 // Per row and class: the least E, the lowest instance that has it, and the least E above it among
@@ -481,7 +495,7 @@ __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
         if (lane == 0) a.cls_bound[c] = k;
     }
     const float* __restrict__ runs = a.grp_min + runs_at<kBlocks>(min(u, (int64_t)U - 1), a.run_pad) + (size_t)cr.x * kRunStride<kBlocks>;
-    const float* __restrict__ E = a.memo + memo_at(u, cr.x * kMemoP, a.m_pos);
+    const float* __restrict__ E = a.memo + memo_at(u, cr.x, a.n_run);
     const int* __restrict__ order = a.order + cr.x * kMemoP;
 
     float m1 = inf, m2 = inf;       // of this wave's runs: the least, the least of the others
@@ -516,17 +530,18 @@ __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
     }
     const bool any = u < U && E1 < inf;
     int low = 0x7fffffff;
-    const auto take = [&](int p) {
-        const float v = E[(size_t)p * kMemoU];
-        const int g = order[p];
-        if (g < 0) return;
-        if (v > E1) above = fminf(above, v);
-        else if (v == E1) low = min(low, g);
+    const auto take = [&](int r, int piece) {      // four positions of a run
+        const float4 v = *reinterpret_cast<const float4*>(E + (size_t)r * kTile + 4 * piece);
+        const int4 g = *reinterpret_cast<const int4*>(order + r * kMemoP + 4 * piece);
+        const auto one = [&](float v, int g) {
+            if (g < 0) return;
+            if (v > E1) above = fminf(above, v);
+            else if (v == E1) low = min(low, g);
+        };
+        one(v.x, g.x); one(v.y, g.y); one(v.z, g.z); one(v.w, g.w);
     };
-    if (any) {
-#pragma unroll
-        for (int k = 0; k < kMemoP / kW; ++k) take(r1 * kMemoP + w * (kMemoP / kW) + k);
-    }
+    static_assert(kMemoP == 4 * kW, "four positions per wave");
+    if (any) take(r1, w);
     low_lds[w][lane] = low;
     if (__syncthreads_or(any && tied > 1)) {
         // Several runs hold the least E: those are looked at as well, unless all of a run's instances
@@ -540,7 +555,7 @@ __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
                 const float e = runs[(size_t)r * kRunStride<kBlocks>];
                 if (e > E1) above = fminf(above, e);
                 else if (r != r1 && __float_as_int(a.run_k[cr.x + r].w) < low1)
-                    for (int p = r * kMemoP; p < (r + 1) * kMemoP; ++p) take(p);
+                    for (int q = 0; q < kW; ++q) take(r, q);
             }
         }
         __syncthreads();
@@ -579,7 +594,7 @@ struct SelectArgs {
     int* out_inst;
     float* out_slack;
     uint8_t* out_fallback;
-    int m_pos, run_pad, n_run, n_class, c_pad, max_len;
+    int run_pad, n_run, n_class, c_pad, max_len;
     int segments;      // by classes or lines first: workgroups of the launch
     int64_t first;     // a group of lanes per request: the launch's first request
 };
@@ -628,7 +643,7 @@ struct Selection {
     const SelectArgs& a;
     const int sub, ex;
     const float* __restrict__ runs;
-    const float* __restrict__ E;
+    const float* __restrict__ E;      // (this lane's position)
     const int* run_at;          // (of a, or a copy in LDS)
     const float4* run_k;
     const float Lf, c0, Dc;
@@ -646,7 +661,7 @@ struct Selection {
 
     __device__ __forceinline__ Selection(const SelectArgs& args, const Request& q, int row, int sub_)
         : a(args), sub(sub_), ex(q.ex), runs(args.grp_min + runs_at<kBlocks>(row, args.run_pad)),
-          E(args.memo + memo_at(row, 0, args.m_pos)), run_at(args.run_at), run_k(args.run_k), Lf((float)q.L), c0((float)q.c0),
+          E(args.memo + memo_at(row, 0, args.n_run) + sub_), run_at(args.run_at), run_k(args.run_k), Lf((float)q.L), c0((float)q.c0),
           Dc(q.D > FLT_MAX ? FLT_MAX : q.D) {}
 
     __device__ __forceinline__ float bound(float e, const float4& k) const
@@ -712,7 +727,7 @@ struct Selection {
                 const int p = r * kMemoP + sub, g = a.order[p];
                 const unsigned long long pk = a.posKey[p];
                 const uint32_t thr = a.pos_thr[p];
-                const float T = fmaf(c0, kappa_of(a.posK[p], Lf), E[(size_t)p * kMemoU]);
+                const float T = fmaf(c0, kappa_of(a.posK[p], Lf), E[(size_t)r * kTile]);
                 const uint32_t hit = group_ballot(T <= Dc && g >= 0 && g != ex);
                 if (!hit) continue;
                 const int h = __ffs(hit) - 1;
@@ -730,7 +745,7 @@ struct Selection {
     __device__ __forceinline__ void look(int run)
     {
         const int p = run * kMemoP + sub, g = a.order[p];
-        const float T = fmaf(c0, kappa_of(a.posK[p], Lf), E[(size_t)p * kMemoU]);
+        const float T = fmaf(c0, kappa_of(a.posK[p], Lf), E[(size_t)run * kTile]);
         const bool in = g >= 0 && g != ex && T < __builtin_inff();
         const float least = from_ordered_bits(min_over<true>(in ? ordered_bits(T) : ~0u));
         if (!group_ballot(in) || least > bestT) return;
@@ -867,7 +882,7 @@ __global__ __launch_bounds__(kBlock) void k_lines(SelectArgs a)
     const float inf = __builtin_inff(), lo = kRangeEnd[range], hi = kRangeEnd[range + 1];
     const float Lf = (float)a.row_len[row];
     const float* __restrict__ runs = a.grp_min + runs_at<false>(row, a.run_pad);
-    const float* __restrict__ E = a.memo + memo_at(row, 0, a.m_pos);
+    const float* __restrict__ E = a.memo + memo_at(row, 0, a.n_run);
 
     float e[kChunks], kappa[kChunks];       // least E of a run, its least kappa (no run: infinite)
     const auto read = [&](int r0) {
@@ -906,8 +921,8 @@ __global__ __launch_bounds__(kBlock) void k_lines(SelectArgs a)
     // a, b: lanes 0 .. 15 look at the one run, lanes 16 .. 31 at the other
     float Ea, Eb, ka, kb, Ta_lo, Tb_hi;
     {
-        const int p = (lane & kGroup ? run_hi : run_lo) * kMemoP + lane % kGroup;
-        const float Ep = E[(size_t)p * kMemoU], kp = kappa_of(a.posK[p], Lf);
+        const int run = lane & kGroup ? run_hi : run_lo, p = run * kMemoP + lane % kGroup;
+        const float Ep = E[(size_t)run * kTile + lane % kGroup], kp = kappa_of(a.posK[p], Lf);
         const float T = fmaf(lane & kGroup ? hi : lo, kp, Ep);
         const uint32_t v = a.order[p] >= 0 && T < inf ? ordered_bits(T) : ~0u;      // (also not a NaN)
         const unsigned long long best = __ballot(v == min_over<true>(v));
@@ -940,7 +955,7 @@ __global__ __launch_bounds__(kBlock) void k_lines(SelectArgs a)
                     open &= open - 1;
                 }
                 const int p = max(run, 0) * kMemoP + lane % kGroup, g = a.order[p];
-                const float Ep = E[(size_t)p * kMemoU], kp = kappa_of(a.posK[p], Lf);
+                const float Ep = E[(size_t)max(run, 0) * kTile + lane % kGroup], kp = kappa_of(a.posK[p], Lf);
                 for (unsigned long long take = __ballot(run >= 0 && g >= 0 && counts(Ep, kp)); take && n <= 2; take &= take - 1, ++n) {
                     const int l = __ffsll((long long)take) - 1;
                     const float4 line = make_float4(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(Ep), l)),
@@ -1211,7 +1226,7 @@ struct HitArgs {
     uint8_t* out_fallback;
     float* out_T;
     int64_t n, n_hits;
-    int n_inst, m_pos, max_len;
+    int n_inst, n_run, max_len;
 };
 
 // Eq. 2's hit prefix H_{r,g}, after the pass without it: a cached prefix of h
@@ -1234,7 +1249,8 @@ __global__ __launch_bounds__(kBlock) void k_hits(HitArgs a)
     const float c0 = (float)ci, Lf = (float)L, D = a.budget[r];
     const float Dc = D > FLT_MAX ? FLT_MAX : D;
     const int ex = a.exclude ? a.exclude[r] : -1;
-    const float* __restrict__ rowE = a.memo + memo_at(a.len_row[L], 0, a.m_pos);
+    const float* __restrict__ rowE = a.memo + memo_at(a.len_row[L], 0, a.n_run);
+    const auto E_at = [&](int p) { return rowE[(size_t)(p / kMemoP) * kTile + p % kMemoP]; };
 
     unsigned long long feasKey = ~0ull;
     int feasG = -1, anyG = -1;
@@ -1242,7 +1258,7 @@ __global__ __launch_bounds__(kBlock) void k_hits(HitArgs a)
     const int g0 = a.out_inst[r];
     if (g0 >= 0) {
         const int p0 = a.pos_of[g0];
-        const float T0 = fmaf(c0, kappa_of(a.posK[p0], Lf), rowE[(size_t)p0 * kMemoU]);
+        const float T0 = fmaf(c0, kappa_of(a.posK[p0], Lf), E_at(p0));
         if (T0 <= Dc) { feasKey = a.posKey[p0]; feasG = g0; feasT = T0; }
         anyG = g0; anyT = T0;
     }
@@ -1252,7 +1268,7 @@ __global__ __launch_bounds__(kBlock) void k_hits(HitArgs a)
         const int h = min(max(a.hit_len[k], 0), max(ci, 0));
         const int p = a.pos_of[g];
         const float2 dg = a.posK[p];
-        const float T = fmaf(-(float)h, dg.x, fmaf(c0, kappa_of(dg, Lf), rowE[(size_t)p * kMemoU]));
+        const float T = fmaf(-(float)h, dg.x, fmaf(c0, kappa_of(dg, Lf), E_at(p)));
         if (a.out_T) {          // (an instance named twice: the longer prefix, i.e. the smaller T, stays)
             float* t = a.out_T + (size_t)r * a.n_inst + g;
             *t = fminf(*t, T);
@@ -1495,11 +1511,9 @@ __global__ __launch_bounds__(kBlock) void k_direct_merge(DirectArgs a)
 }
 
 // ------------------------------------------------------------------ every pair's latency (out_T)
-// The table keeps a position's values of 256 rows together, a request wants one row of every instance: read
-// as it is, every 4-byte value is a cache line of its own (65 536 requests x 256 instances 60 us, 262 144 x 64
-// 105 us, written at 1.1 and 0.6 TB/s).  So `rows` lengths at a time the table is first turned into rows over the
-// instances (k_rows, as much as the lengths, not the requests), and the latencies are then a
-// stream over those (k_pairs).
+// The table keeps the values of a run together, in class order, a request wants every instance in index order.  So
+// `rows` lengths at a time the table is first turned into rows over the instances (k_rows, as much as the
+// lengths, not the requests), and the latencies are then a stream over those (k_pairs).
 struct PairsArgs {
     const int *ctx0, *pred_len, *totals;
     const float* budget;
@@ -1524,23 +1538,19 @@ constexpr int pairs_requests(bool select) { return select ? 4 : 8; }
 
 __global__ __launch_bounds__(kBlock) void k_rows(PairsArgs a)
 {
-    __shared__ float tile[kWave][kWave + 1];
     const int blocks = (a.m_pos + kWave - 1) / kWave;
     const int p0 = (int)(blockIdx.x % blocks) * kWave, u0 = (int)(blockIdx.x / blocks) * kWave;   // row u0 of the part
     if (a.row0 + u0 >= a.totals[1]) return;
     const int lane = lane_id(), wave = threadIdx.x / kWave;
     constexpr int kPer = kWave / (kBlock / kWave);
+    const int p = min(p0 + lane, a.m_pos - 1);
     float v[kPer];
 #pragma unroll
-    for (int i = 0; i < kPer; ++i)
-        v[i] = a.memo[memo_at(a.row0 + u0, min(p0 + wave * kPer + i, a.m_pos - 1), a.m_pos) + lane];
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) tile[wave * kPer + i][lane] = v[i];
-    __syncthreads();
-    const int g = p0 + lane < a.m_pos ? a.order[p0 + lane] : -1;
+    for (int i = 0; i < kPer; ++i) v[i] = a.memo[memo_at(a.row0 + u0 + wave * kPer + i, p / kMemoP, a.m_pos / kMemoP) + p % kMemoP];
+    const int g = p0 + lane < a.m_pos ? a.order[p] : -1;
     if (g < 0) return;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) a.turned[(size_t)(u0 + wave * kPer + i) * a.n_inst + g] = tile[lane][wave * kPer + i];
+    for (int i = 0; i < kPer; ++i) a.turned[(size_t)(u0 + wave * kPer + i) * a.n_inst + g] = v[i];
 }
 
 // The same arithmetic as the selection's, exclusions not applied.  kLanes lanes take kReq requests together (one
@@ -1591,8 +1601,9 @@ __device__ __forceinline__ void pairs(const PairsArgs& a)
         Values E[kReq];
 #pragma unroll
         for (int j = 0; j < kReq; ++j)
-            E[j] = *reinterpret_cast<const Values*>(kWrite ? a.turned + (size_t)max(row[j], 0) * a.n_inst + g
-                                                           : a.memo + memo_at(max(row[j], 0), a.pos_of[g], a.m_pos));
+            E[j] = *reinterpret_cast<const Values*>(
+                kWrite ? a.turned + (size_t)max(row[j], 0) * a.n_inst + g
+                       : a.memo + memo_at(max(row[j], 0), a.pos_of[g] / kMemoP, a.m_pos / kMemoP) + a.pos_of[g] % kMemoP);
 #pragma unroll
         for (int j = 0; j < kReq; ++j) {
             if (row[j] < 0) continue;
@@ -1882,17 +1893,18 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     {
         MemoArgs m{};
         m.totals = f->totals; m.row_len = f->row_len; m.len_row = f->len_row; m.order = f->order; m.instK = f->instK;
-        m.tabR = f->tabR; m.tabS = f->tabS; m.tabGH = f->tabGH; m.memo = f->memo; m.grp_min = f->grp_min;
+        m.tabR = f->tabR; m.tabGH = f->tabGH; m.memo = f->memo; m.grp_min = f->grp_min;
         m.run_k = f->run_k; m.run_rank = f->run_rank; m.pos_thr = f->pos_thr; m.run_at = f->run_at; m.posK = f->posK; m.posKey = f->posKey;
         m.run_head = f->run_head;
         m.seen = reinterpret_cast<uint4*>(f->seen); m.seen_words = (f->bins + 15) / 16;
-        m.n_run = f->n_run; m.m_pos = f->m_pos; m.run_pad = f->run_pad; m.cap = f->cap;
+        m.n_run = f->n_run; m.run8 = (f->n_run + 7) / 8 * 8; m.bins = f->bins; m.run_pad = f->run_pad; m.cap = f->cap;
         // (workgroups for as many rows as there may be; those past the last row end at once)
-        const dim3 grid((unsigned)(f->n_run * (1 + (max_rows + kMemoU - 1) / kMemoU)));
+        const dim3 grid((unsigned)(m.run8 * (1 + (max_rows + kMemoU - 1) / kMemoU)));
         ProfScope ps(f, kMemoRoute + off, s);
 #define GR_LAUNCH_MEMO(B) do { \
-        if (f->cap > 512) hipLaunchKernelGGL((k_memo<true, B>), grid, dim3(kBlock), 0, s, m); \
-        else hipLaunchKernelGGL((k_memo<false, B>), grid, dim3(kBlock), 0, s, m); } while (0)
+        if (f->cap > 1024) hipLaunchKernelGGL((k_memo<4, B>), grid, dim3(kBlock), 0, s, m); \
+        else if (f->cap > 512) hipLaunchKernelGGL((k_memo<2, B>), grid, dim3(kBlock), 0, s, m); \
+        else hipLaunchKernelGGL((k_memo<1, B>), grid, dim3(kBlock), 0, s, m); } while (0)
         if (blocks) GR_LAUNCH_MEMO(true);
         else GR_LAUNCH_MEMO(false);
 #undef GR_LAUNCH_MEMO
@@ -1901,7 +1913,7 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         ClassArgs c{};
         c.totals = f->totals; c.cls_run = f->cls_run; c.order = f->order; c.memo = f->memo; c.grp_min = f->grp_min;
         c.run_k = f->run_k; c.class_min = f->class_min; c.class_next = f->class_next; c.cls_bound = f->cls_bound;
-        c.n_class = f->n_class; c.c_pad = f->c_pad; c.m_pos = f->m_pos; c.run_pad = f->run_pad;
+        c.n_class = f->n_class; c.c_pad = f->c_pad; c.n_run = f->n_run; c.run_pad = f->run_pad;
         ProfScope ps(f, kClassRoute + off, s);
         const dim3 grid((unsigned)((max_rows + kWave - 1) / kWave * f->n_class));
         if (blocks) hipLaunchKernelGGL(k_class<true>, grid, dim3(kBlock), 0, s, c);
@@ -1912,7 +1924,7 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         a.s = src; a.len_row = f->len_row; a.order = f->order; a.memo = f->memo; a.grp_min = f->grp_min; a.run_k = f->run_k;
         a.posK = f->posK; a.posKey = f->posKey; a.run_rank = f->run_rank; a.pos_thr = f->pos_thr; a.run_at = f->run_at; a.cls_run = f->cls_run; a.class_min = f->class_min; a.class_next = f->class_next; a.clsK = f->clsK; a.cls_bound = f->cls_bound;
         a.out_inst = out.inst; a.out_slack = out.slack; a.out_fallback = out.fallback;
-        a.m_pos = f->m_pos; a.run_pad = f->run_pad; a.n_run = f->n_run; a.n_class = f->n_class; a.c_pad = f->c_pad;
+        a.run_pad = f->run_pad; a.n_run = f->n_run; a.n_class = f->n_class; a.c_pad = f->c_pad;
         a.max_len = f->max_len;
         a.lines = f->lines; a.totals = f->totals; a.row_len = f->row_len; a.pos_of = f->pos_of;
         a.rest_cnt = f->rest_cnt;
@@ -1953,7 +1965,7 @@ int launch_hits(gr_fleet* f, const ReqSrc& src, const int* hit_off, const int* h
     h.hit_off = hit_off; h.hit_inst = hit_inst; h.hit_len = hit_len;
     h.len_row = f->len_row; h.pos_of = f->pos_of; h.memo = f->memo; h.posK = f->posK; h.posKey = f->posKey;
     h.out_inst = out.inst; h.out_slack = out.slack; h.out_fallback = out.fallback; h.out_T = out.T;
-    h.n = src.n; h.n_hits = n_hits; h.n_inst = f->n_inst; h.m_pos = f->m_pos; h.max_len = f->max_len;
+    h.n = src.n; h.n_hits = n_hits; h.n_inst = f->n_inst; h.n_run = f->n_run; h.max_len = f->max_len;
     ProfScope ps(f, kHitsRoute, s);
     hipLaunchKernelGGL(k_hits, dim3((unsigned)((src.n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, h);
     return hipGetLastError() == hipSuccess ? GR_OK : GR_ERR_HIP;

@@ -1335,8 +1335,6 @@ constexpr size_t split_lds()
 template <int kEPL>
 constexpr size_t lean_lds() { return (size_t)kBuildWaves * lean_inst_words(kWave * kEPL) * sizeof(int); }
 
-constexpr int kSimds = 1024;      // 256 compute units of four
-
 // Whether instances pick the number of sort words by what they hold: where half of the words would do
 // for the average one, and in feedback routing, whose handles are made with room for what is routed
 // (256 instances of 512 to 560 requests in tables for 2 048: 8.5 us instead of 10.0).  Elsewhere the
