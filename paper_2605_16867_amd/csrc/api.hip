@@ -122,6 +122,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     f->run_pad = (f->n_run + kMemoP - 1) / kMemoP * kMemoP;
     f->c_pad = (n_class + 3) / 4 * 4;
     f->bins = max_len + 1;
+    for (const int2 r : tab_h.run_cls) f->most_of_class = std::max(f->most_of_class, r.y);
     f->row_cap = f->req_cap < f->bins ? f->req_cap : f->bins;
     f->row_cap = (f->row_cap + kMemoU - 1) / kMemoU * kMemoU;
     if (f->row_cap < kMemoU) f->row_cap = kMemoU;
@@ -141,7 +142,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
         dev_alloc(&f->pend_cnt, n_inst) && dev_alloc(&f->commit_mark, n_inst) && dev_alloc(&f->pend_touched, n_inst) && dev_alloc(&f->pend_prompt, tab) && dev_alloc(&f->pend_len, tab) &&
         dev_alloc(&f->scratch_finish, f->max_active + kBlock * kRestItems) && dev_alloc(&f->batch_cap, n_inst) &&
         dev_alloc(&f->seen, seen_bytes) && dev_alloc(&f->late_cnt, (size_t)n_inst * 4) &&
-        dev_alloc(&f->row_len, f->row_cap) && dev_alloc(&f->len_row, f->bins + 1) && dev_alloc(&f->totals, 4) &&
+        dev_alloc(&f->row_len, f->row_cap) && dev_alloc(&f->len_row, f->bins + 1) && dev_alloc(&f->totals, 4) && dev_alloc(&f->dense_totals, 2) &&
         dev_alloc(&f->memo, (size_t)f->row_cap * f->m_pos) && dev_alloc(&f->grp_min, (size_t)f->row_cap * f->run_pad) &&
         dev_alloc(&f->run_k, f->n_run) && dev_alloc(&f->run_rank, f->n_run) && dev_alloc(&f->run_at, f->n_run) && dev_alloc(&f->pos_thr, f->m_pos) && dev_alloc(&f->class_min, (size_t)f->row_cap * f->c_pad) &&
         dev_alloc(&f->cls_bound, n_class) && dev_alloc(&f->class_next, (size_t)f->row_cap * n_class) &&
@@ -159,6 +160,8 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     send(f->run_cls, tab_h.run_cls.data(), sizeof(int2) * f->n_run);
     send(f->slot_inst, tab_h.slot.data(), sizeof(int) * f->m_pos);
     send(f->slot_of, tab_h.slot_of.data(), sizeof(int) * n_inst);
+    const int dense[2] = {0, f->bins};
+    send(f->dense_totals, dense, sizeof dense);
     send(f->inst_class, inst_class, sizeof(int) * n_inst);
     clear(f->counters, sizeof(int));
     clear(f->seen, seen_bytes);
@@ -191,7 +194,7 @@ int gr_destroy(gr_fleet* f)
     void* ptrs[] = {f->cls, f->inst_class, f->tabR, f->tabGH, f->hD, f->emaQ, f->emaP, f->emaD, f->instK, f->tabS,
                     f->clsK, f->slot_inst, f->slot_of, f->slot_key, f->run_cls, f->cls_run, f->order, f->pos_of, f->posK, f->posKey, f->run_head, f->act_inst, f->pend_cnt, f->commit_mark, f->pend_touched, f->pend_prompt, f->pend_len,
                     f->scratch_finish, f->batch_cap, f->counters, f->seen, f->late_cnt, f->row_len,
-                    f->len_row, f->totals, f->memo, f->grp_min, f->run_k, f->run_rank, f->run_at, f->pos_thr, f->class_min, f->cls_bound, f->class_next, f->rest_cnt, f->lines, f->turned, f->direct_part};
+                    f->len_row, f->totals, f->dense_totals, f->memo, f->grp_min, f->run_k, f->run_rank, f->run_at, f->pos_thr, f->class_min, f->cls_bound, f->class_next, f->rest_cnt, f->lines, f->turned, f->direct_part};
     int rc = GR_OK;
     for (void* p : ptrs)
         if (p && hipFree(p) != hipSuccess) rc = GR_ERR_HIP;
@@ -348,6 +351,7 @@ int gr_risk_scan(gr_fleet* f, const int32_t* act_off, const int32_t* act_prompt,
     in.act_budget = act_budget;
     in.n_active = n_active; in.n_queued = n_queued;
     in.out_act_finish = out_finish; in.out_flag = out_flag;
+    in.mark = needs_marks(f, n_active);
     rc = launch_status(f, in, s);
     if (rc != GR_OK) return rc;
     ReqSrc src{};

@@ -42,6 +42,7 @@ constexpr int64_t kDirectPairs = int64_t(1) << 19;   // pairs of a batch that is
 constexpr int64_t kDirectInfinite = int64_t(1) << 18;   // pairs (of whole 128 instances) up to which infinite latencies count there
 constexpr int kDirectSpan = 4096;  // instances that one workgroup takes of a request scored pair by pair
 constexpr int kDirectParts = 16384;  // room for the selections of such parts
+constexpr int64_t kDenseValues = int64_t(1) << 23;   // values of a table that has a row for every length
 constexpr int kMemoP = 16;         // positions of a run of the class order
 constexpr int kRanges = 4;         // ranges of prompt lengths that a length's possible least latencies are looked up for
 constexpr int kRestParts = 64;     // lists of requests that those do not decide
@@ -111,6 +112,7 @@ struct StatusIn {
     double* out_d;
     int* out_rank;
     uint8_t* out_flag;
+    int mark = 0;             // with flags: leave the lengths of flagged requests for the table pass
     int use_pending = 0;      // count the requests routed since the caller's status (feedback routing)
     int only_touched = 0;     // rebuild only the instances that have been given requests since the last build
     // a chunk just decided, to be taken into the lists by the build (see BuildArgs); 0: none
@@ -142,6 +144,7 @@ struct gr_fleet {
     int run_pad = 0;       // n_run rounded up to whole runs of kMemoP: row length of grp_min
     int c_pad = 0;         // n_class rounded up to a multiple of 4: row length of class_min
     int bins = 0;          // max_len + 1
+    int most_of_class = 0; // instances of the largest class
     int64_t row_cap = 0;   // rows of the memo table, rounded up to whole blocks of kMemoU
     int device = 0;
     bool has_status = false;
@@ -193,6 +196,7 @@ struct gr_fleet {
     int late_parts = 0;
     int* row_len = nullptr;   // [row_cap] the distinct lengths ("rows"), ascending
     uint16_t* len_row = nullptr;  // [bins + 1] rows shorter than each length = its row if it has one; 0xFFFF (past every row) at the end
+    int* dense_totals = nullptr;   // [2] -, bins: the rows of a table that has one for every length
     int* totals = nullptr;    // [4] -, distinct lengths, 1: flags that the risk scan's build has not set (zero between calls)
     float* memo = nullptr;       // [row_cap / kMemoU][n_run][kMemoU][kMemoP] E per distinct length and position
     float* grp_min = nullptr;    // [row_cap][run_pad] least E of each run, per row (see runs_at)
@@ -289,6 +293,7 @@ int launch_ema(gr_fleet* f, double w, const float* s_q, const float* s_p, const 
 // score.hip
 int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& out, hipStream_t s,
                  bool small_batch_ok = false);
+bool needs_marks(const gr_fleet* f, int64_t n);      // a risk scan's table pass makes a list of lengths
 int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream_t s);
 int launch_hits(gr_fleet* f, const ReqSrc& src, const int* hit_off, const int* hit_inst, const int* hit_len,
                 int64_t n_hits, const ScoreOut& out, hipStream_t s);

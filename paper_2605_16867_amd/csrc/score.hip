@@ -152,6 +152,37 @@ __global__ __launch_bounds__(kScanBlock) void k_scan(ScanArgs a, OrderArgs order
     }
 }
 
+// The flagged requests of a risk scan, counted by one workgroup where k_scan does not: by the build's counts, or by the
+// flags where the build has not set every one (see ScanArgs).
+struct CountArgs {
+    int *totals, *out_n;      // totals null: no risk scan
+    const int *late_cnt, *act_off;
+    const uint8_t* flag;
+    int64_t n;
+    int n_late, n_inst;
+};
+
+__device__ __forceinline__ void count_flagged(const CountArgs& a, int threads, int* sums)
+{
+    const int tid = threadIdx.x;
+    const bool unset = a.totals[2] != 0 || a.act_off[0] > 0 || a.act_off[a.n_inst] < a.n;
+    int n = 0;
+    if (a.out_n) {
+        if (unset) for (int64_t i = tid; i < a.n; i += threads) n += a.flag[i] != 0;
+        else for (int i = tid; i < a.n_late; i += threads) n += a.late_cnt[i];
+    }
+    n = wave_sum(n);
+    if (lane_id() == 0) sums[tid / kWave] = n;
+    __syncthreads();
+    if (tid != 0) return;
+    for (int w = 1; w < threads / kWave; ++w) n += sums[w];
+    if (a.out_n) *a.out_n = n;
+    a.totals[2] = 0;
+}
+
+// The row of a length: its place in the list, or the length itself where every length has a row.
+__device__ inline int row_at(const uint16_t* len_row, int L) { return len_row ? (int)len_row[L] : L; }
+
 // how many of the 16-bit lengths in `w` are at most L
 __device__ inline int count_upto(const uint4& w, uint32_t L)
 {
@@ -180,7 +211,10 @@ struct MemoArgs {
     const uint4* run_head;
     uint4* seen;           // cleared here for the next batch (its reader is done), as is totals[2]
     int seen_words;        // of 16 bytes
-    int n_run, run8, run_pad, cap, bins;      // run8: n_run rounded up to a multiple of the XCDs
+    int n_run, run_pad, cap, bins;
+    const int2* run_cls;
+    CountArgs count;       // of a risk scan, where every length has a row
+    OrderArgs own;         // the class order, made here (small classes)
 };
 
 // The table is cut into blocks of kMemoU rows; a run's part of a block is consecutive, row by row, so that the
@@ -238,20 +272,121 @@ constexpr int kMemoWaves = kBlock / kWave;
 constexpr int kMemoInst = kMemoP / kMemoWaves;      // instances of a wave
 static_assert(kMemoU == 4 * kWave, "a lane owns four consecutive rows");
 
+// The class order by each workgroup itself, on fleets small enough for that (dense_rows; a launch of its own takes 5 us,
+// this 2): everything a workgroup needs comes with one read, a thread then counts for one of the class's
+// instances over a share of the others.
+constexpr int kOwnClass = 128;       // most instances of a class
+constexpr int kOwnSlots = 2 * kBlock;    // most positions of the fleet
+
+struct OwnLds {
+    uint32_t rough[kOwnSlots];           // the keys as single precision: in the same order or equal; all ones where there is no instance
+    unsigned long long key[kOwnSlots];
+    int inst[kOwnSlots];
+    int rank[kOwnClass];
+    int slot[kMemoP];      // the slot of each of the run's positions, -1: none
+};
+
+// a key (falling_bits) to single precision
+__device__ inline uint32_t rough_key(unsigned long long key)
+{
+    const unsigned long long b = (key >> 63) ? key : ~key ^ 0x8000000000000000ull;
+    const uint32_t f = __float_as_uint((float)__longlong_as_double((long long)b));
+    return ~(f ^ ((f >> 31) ? 0xFFFFFFFFu : 0x80000000u));
+}
+
+__device__ __forceinline__ void own_order(const OrderArgs& a, int run, OwnLds& l)
+{
+    const int tid = threadIdx.x;
+    const int2 rc = a.run_cls[run];      // first position, instances of the class
+#pragma unroll
+    for (int s = tid; s < kOwnSlots; s += kBlock) {
+        const unsigned long long k = a.key[min(s, a.m_pos - 1)];
+        const int g = a.slot_inst[min(s, a.m_pos - 1)];
+        l.key[s] = k;
+        l.inst[s] = g;
+        l.rough[s] = g >= 0 ? rough_key(k) : ~0u;
+    }
+    if (tid < kOwnClass) l.rank[tid] = 0;
+    if (tid < kMemoP) l.slot[tid] = -1;
+    __syncthreads();
+    // by the keys in single precision; hardly any two are equal, or all of them are (idle instances)
+    const int n = rc.y, per = n <= kWave ? kWave : kOwnClass, parts = kBlock / per;
+    const int me = min(tid % per, n - 1), step = ((n + parts - 1) / parts + 3) & ~3, h0 = tid / per * step, h1 = min(h0 + step, n);
+    const uint32_t own = l.rough[rc.x + me];
+    int less = 0, same = 0;
+#pragma unroll 4
+    for (int h = h0; h < h1; h += 4) {      // (a class is padded to 16 slots)
+        const uint4 k = *reinterpret_cast<const uint4*>(l.rough + rc.x + h);
+        less += (k.x < own) + (k.y < own) + (k.z < own) + (k.w < own);
+        same += (k.x == own) + (k.y == own) + (k.z == own) + (k.w == own);
+    }
+    if (__any(same > (me >= h0 && me < h1))) {
+        const unsigned long long mine = l.key[rc.x + me];
+#pragma unroll 4
+        for (int h = h0; h < h1; ++h) {
+            const unsigned long long k = l.key[rc.x + h];
+            less += l.rough[rc.x + h] == own && (k < mine || (k == mine && h < me));
+        }
+    }
+    if (tid % per < n && less) atomicAdd(&l.rank[me], less);
+    __syncthreads();
+    if (tid < n) {
+        const int p = l.rank[tid] + rc.x - run * kMemoP;
+        if (p >= 0 && p < kMemoP) l.slot[p] = rc.x + tid;
+    }
+    __syncthreads();
+}
+
 // For each position of a run, how many runs begin with a more capable instance: 16 lanes each.  And what the
 // selection needs of the run: its least and largest delta (gamma is the same for all of a class) and its lowest instance.
-__device__ __forceinline__ void rank_run(const MemoArgs& a, int run)
+//
+// Where the workgroups make the class order themselves (kOwn), this one writes it down for the selection, and
+// counts instances instead of runs' first ones: of a run and a choice, either says whether the run begins with a better one.
+template <bool kOwn>
+__device__ __forceinline__ void rank_run(const MemoArgs& a, int run, int* lds)
 {
     for (int i = run * kBlock + threadIdx.x; i < a.seen_words; i += a.n_run * kBlock) a.seen[i] = make_uint4(0u, 0u, 0u, 0u);
     if (run == 0 && threadIdx.x == 0) a.totals[2] = 0;
     static_assert(kBlock == kMemoP * kMemoP, "16 lanes per position of the run");
+    if (run == 0 && a.count.totals) count_flagged(a.count, kBlock, lds);
     const int p = run * kMemoP + threadIdx.x / kMemoP, sub = threadIdx.x % kMemoP;
-    const unsigned long long key = a.posKey[p];
-    const int g = a.order[p];
-    const float2 kk = a.posK[run * kMemoP + sub];
-    const int gi = a.order[run * kMemoP + sub];
+    unsigned long long key;
+    int g, gi;
+    float2 kk;
     uint32_t n = 0;
     constexpr int kAhead = 8;
+    if constexpr (kOwn) {
+        __syncthreads();
+        OwnLds& l = *reinterpret_cast<OwnLds*>(lds);
+        own_order(a.own, run, l);
+        const int s = l.slot[threadIdx.x / kMemoP], si = l.slot[sub];
+        g = s >= 0 ? l.inst[s] : -1;
+        gi = si >= 0 ? l.inst[si] : -1;
+        key = s >= 0 ? l.key[s] : ~0ull;
+        kk = make_float2(__builtin_inff(), 0.f);
+        if (gi >= 0) { const float4 k = a.instK[gi]; kk = make_float2(k.x, k.y); }
+        for (int s0 = sub; s0 < a.own.m_pos; s0 += kAhead * kMemoP) {
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) {
+                const int h = s0 + i * kMemoP;
+                if (h >= kOwnSlots) break;
+                const unsigned long long hk = l.key[h];
+                const int hg = l.inst[h];
+                n += h < a.own.m_pos && hg >= 0 && (hk < key || (hk == key && hg < g));
+            }
+        }
+        if (sub == 0) {
+            a.own.order[p] = g;
+            a.own.posKey[p] = key;
+            if (g >= 0) a.own.pos_of[g] = p;
+            if (p % kMemoP == 0) a.own.run_head[run] = make_uint4((uint32_t)key, (uint32_t)(key >> 32), (uint32_t)g, 0u);
+        }
+        if (threadIdx.x < kMemoP) a.own.posK[run * kMemoP + sub] = kk;
+    } else {
+        key = a.posKey[p];
+        g = a.order[p];
+        kk = a.posK[run * kMemoP + sub];
+        gi = a.order[run * kMemoP + sub];
     for (int r0 = sub; r0 < a.n_run; r0 += kAhead * kMemoP) {
         uint4 h[kAhead];
 #pragma unroll
@@ -261,6 +396,7 @@ __device__ __forceinline__ void rank_run(const MemoArgs& a, int run)
             const unsigned long long hk = ((unsigned long long)h[i].y << 32) | h[i].x;
             n += r0 + i * kMemoP < a.n_run && (hk < key || (hk == key && (int)h[i].z < g));
         }
+    }
     }
     float lo = kk.x, hi = gi >= 0 ? kk.x : -__builtin_inff();
     float gm = gi >= 0 ? kk.y : 0.f;
@@ -277,7 +413,7 @@ __device__ __forceinline__ void rank_run(const MemoArgs& a, int run)
         a.pos_thr[p] = n;
         if (threadIdx.x == 0) {
             a.run_rank[run] = n;
-            a.run_at[n] = run;
+            if (!kOwn) a.run_at[n] = run;
             a.run_k[run] = make_float4(lo, gm, hi, __int_as_float(low));
         }
     }
@@ -288,27 +424,49 @@ __device__ __forceinline__ void rank_run(const MemoArgs& a, int run)
 constexpr int kTileRow = kMemoP + 4;
 __device__ inline int tile_at(int row, int piece) { return row * kTileRow + 4 * (piece ^ ((row >> 4) & 3)); }
 
-template <int kEighths, bool kBlocks>     // kEighths x 64 eighths of an instance's lengths at most
+//
+// kDense: every length up to the largest has a row (see dense_rows): no list, no row numbers to look up.
+template <int kEighths, bool kBlocks, bool kDense, bool kOwn>     // kEighths x 64 eighths of an instance's lengths at most
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMemoPerSimd, kMemoPerSimd))) void k_memo(MemoArgs a)
 {
     __shared__ __align__(16) int lds[kMemoU * kTileRow];       // the counters, then the tile
     static_assert(kMemoU * kTileRow >= kMemoWaves * kMemoInst * kMemoU, "room for the counters");
     // (the first workgroups rank the runs for the selection: next to the others, not behind them)
-    const int pass = blockIdx.x / a.run8 - 1, run = blockIdx.x % a.run8;
+    const int pass = (int)blockIdx.y - 1, run = blockIdx.x;
     if (run >= a.n_run) return;
-    if (pass < 0) return rank_run(a, run);
+    if (pass < 0) return rank_run<kOwn>(a, run, lds);
     const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int ub = pass * kMemoU, p0 = run * kMemoP + wave * kMemoInst;
 
-    // this lane's rows, the length before the block, the wave's instances: one trip, and the number of rows with it
-    int4 r = *reinterpret_cast<const int4*>(a.row_len + ub + 4 * lane);
-    const int L_before = ub > 0 ? a.row_len[ub - 1] : -1;
     int g[kMemoInst], gs[kMemoInst];
+    if constexpr (kOwn) {
+        static_assert(sizeof(OwnLds) <= sizeof lds, "the order is made where the counters will be");
+        OwnLds& l = *reinterpret_cast<OwnLds*>(lds);
+        own_order(a.own, run, l);
 #pragma unroll
-    for (int j = 0; j < kMemoInst; ++j) g[j] = a.order[p0 + j];
-    const int U = a.totals[1];
-    asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w));
-    if (ub >= U) return;
+        for (int j = 0; j < kMemoInst; ++j) {
+            const int s = __builtin_amdgcn_readfirstlane(l.slot[wave * kMemoInst + j]);
+            g[j] = s >= 0 ? __builtin_amdgcn_readfirstlane(l.inst[s]) : -1;
+        }
+        __syncthreads();
+    } else {
+#pragma unroll
+        for (int j = 0; j < kMemoInst; ++j) g[j] = a.order[p0 + j];
+    }
+    // this lane's rows, the length before the block, the wave's instances: one trip, and the number of rows with it
+    int4 r;
+    int L_before = ub - 1, U = a.bins;
+    if constexpr (kDense) {
+        r = make_int4(ub + 4 * lane, ub + 4 * lane + 1, ub + 4 * lane + 2, ub + 4 * lane + 3);
+    } else {
+        r = *reinterpret_cast<const int4*>(a.row_len + ub + 4 * lane);
+        if (ub > 0) L_before = a.row_len[ub - 1];
+        U = a.totals[1];
+        asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w));
+        if (ub >= U) return;
+    }
+    const int2 rc = a.run_cls[run];
+    const int here = rc.x + rc.y - run * kMemoP;      // positions of the run that have an instance (or more)
     const int ue = ub + kMemoU;
 
     float4 K[kMemoInst];
@@ -340,7 +498,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMemoPer
         er[j] = R[j][(unsigned)(kb[j] + lane)];
     }
 #pragma unroll
-    for (int j = 0; j < kMemoInst; ++j) er[j] = a.len_row[(unsigned)min(er[j], a.bins)];
+    for (int j = 0; j < kMemoInst; ++j)
+        if (!kDense) er[j] = a.len_row[(unsigned)min(er[j], a.bins)];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -359,7 +518,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMemoPer
             const uint32_t words[4] = {w.x, w.y, w.z, w.w};
             int row[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) row[i] = a.len_row[min(i % 2 ? words[i / 2] >> 16 : words[i / 2] & 0xFFFFu, (uint32_t)a.bins)];
+            for (int i = 0; i < 8; ++i) {
+                row[i] = (int)(i % 2 ? words[i / 2] >> 16 : words[i / 2] & 0xFFFFu);
+                if (!kDense) row[i] = a.len_row[(unsigned)min(row[i], a.bins)];
+            }
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 if (row[i] < ue) atomicAdd(&cnt[j * kMemoU + row[i] - ub], 1);       // (in order: none is before the block)
@@ -395,24 +557,22 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMemoPer
     for (int j = 0; j < kMemoInst; ++j) {
         const int N1 = __float_as_int(K[j].w) + 1;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) E[i][j] = fmaf(Lf[i], gh[j][i].y, gh[j][i].x) + tri[i] * (K[j].z * (float)(N1 - k[j][i]));
+        for (int i = 0; i < 4; ++i) E[i][j] = fmaf(tri[i], K[j].z * (float)(N1 - k[j][i]), fmaf(Lf[i], gh[j][i].y, gh[j][i].x));
     }
     __syncthreads();        // (every wave has its counters)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
         *reinterpret_cast<float4*>(lds + tile_at(4 * lane + i, wave)) = make_float4(E[i][0], E[i][1], E[i][2], E[i][3]);
     __syncthreads();
-    // (positions without an instance, at the end of a class: infinite)
-    const int4 at = *reinterpret_cast<const int4*>(a.order + run * kMemoP + 4 * (lane % 4));
-    const bool padded = __any(min(min(at.x, at.y), min(at.z, at.w)) < 0);
     float* __restrict__ out = a.memo + memo_at(ub, run, a.n_run);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int c = tid + i * kBlock, row = c / 4;
         float4 e = *reinterpret_cast<const float4*>(lds + tile_at(row, c % 4));
-        if (padded) {
+        if (here < kMemoP) {      // (the end of a class)
             const float inf = __builtin_inff();
-            e = make_float4(at.x < 0 ? inf : e.x, at.y < 0 ? inf : e.y, at.z < 0 ? inf : e.z, at.w < 0 ? inf : e.w);
+            const int q = 4 * (c % 4);
+            e = make_float4(q < here ? e.x : inf, q + 1 < here ? e.y : inf, q + 2 < here ? e.z : inf, q + 3 < here ? e.w : inf);
         }
         reinterpret_cast<float4*>(out)[c] = e;
         float m = min_plain(min_plain(e.x, e.y), min_plain(e.z, e.w));
@@ -461,6 +621,7 @@ struct ClassArgs {
     uint2* class_next;
     float4* cls_bound;
     int n_class, c_pad, n_run, run_pad;
+    int dense;         // 1: row 0 is the length 0, at which instances without a queue all tie
 };
 
 // Per row and class: the least E, the lowest instance that has it, and the least E above it among
@@ -529,6 +690,7 @@ __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
         if (y > E1) above = fminf(above, y);
     }
     const bool any = u < U && E1 < inf;
+    if (a.dense && u == 0) { tied = 1; above = E1; }      // (left to the runs: nobody is decided by a next larger E that is no larger)
     int low = 0x7fffffff;
     const auto take = [&](int r, int piece) {      // four positions of a run
         const float4 v = *reinterpret_cast<const float4*>(E + (size_t)r * kTile + 4 * piece);
@@ -810,7 +972,7 @@ __global__ __launch_bounds__(kBlock) void k_select(SelectArgs a)
         if (sub == 0) answer<kMigrate>(a, i, -1, 0.f, false);      // not flagged: no migration target
         return;
     }
-    Selection<kChunks, false> sel(a, q, a.len_row[q.L], sub);
+    Selection<kChunks, false> sel(a, q, row_at(a.len_row, q.L), sub);
     sel.template scan<true, true, false>(0, a.n_run);
     if (sel.feasG < 0) sel.settle(0, a.n_run);
     sel.template report<kMigrate>(i, q.D);
@@ -880,7 +1042,7 @@ __global__ __launch_bounds__(kBlock) void k_lines(SelectArgs a)
     const int row = i / kRanges, range = i % kRanges;
     if (row >= a.totals[1]) return;
     const float inf = __builtin_inff(), lo = kRangeEnd[range], hi = kRangeEnd[range + 1];
-    const float Lf = (float)a.row_len[row];
+    const float Lf = (float)(a.row_len ? a.row_len[row] : row);
     const float* __restrict__ runs = a.grp_min + runs_at<false>(row, a.run_pad);
     const float* __restrict__ E = a.memo + memo_at(row, 0, a.n_run);
 
@@ -1008,7 +1170,7 @@ __global__ __launch_bounds__(kBlock) void k_select_by_class(SelectArgs a)
             best[it] = inf; cls[it] = 0; tie[it] = false;
         }
 #pragma unroll
-        for (int it = 0; it < kItems; ++it) row[it] = a.len_row[q[it].L];
+        for (int it = 0; it < kItems; ++it) row[it] = row_at(a.len_row, q[it].L);
         for (int c0 = 0; c0 < a.n_class; c0 += 4) {
             float4 e[kItems];
 #pragma unroll
@@ -1113,7 +1275,7 @@ __global__ __launch_bounds__(kBlock) void k_select_lines(SelectArgs a)
         if (sub == 0) answer<kMigrate>(a, i, -1, 0.f, false);      // not flagged: no migration target
         return;
     }
-    const int row = a.len_row[q.L];
+    const int row = row_at(a.len_row, q.L);
     const float4* at = lines_of(a, q, row);
     const LineChoice c = choose_line(q, at[0], at[1]);
     if (c.decided) {
@@ -1150,7 +1312,7 @@ __global__ __launch_bounds__(kBlock) void k_late_lines(SelectArgs a)
 #pragma unroll
     for (int it = 0; it < kItems; ++it) q[it] = fetch<true>(a.s, min(i0 + it * kBlock, a.s.n - 1), a.max_len);
 #pragma unroll
-    for (int it = 0; it < kItems; ++it) row[it] = a.len_row[q[it].L];
+    for (int it = 0; it < kItems; ++it) row[it] = row_at(a.len_row, q[it].L);
 #pragma unroll
     for (int it = 0; it < kItems; ++it) {
         const float4* __restrict__ at = lines_of(a, q[it], row[it]);
@@ -1196,9 +1358,9 @@ __global__ __launch_bounds__(kBlock, 6) void k_late_rest(SelectArgs a, int wg_re
     const auto index = [&](int k) { return list[min(k, n - 1)]; };
     int i = index(k), i1 = index(k + kStep), i2 = index(k + 2 * kStep);
     Request q = fetch<true>(a.s, i, a.max_len), q1 = fetch<true>(a.s, i1, a.max_len);
-    int row = a.len_row[q.L];
+    int row = row_at(a.len_row, q.L);
     for (; k < n; k += kStep) {
-        const int i3 = index(k + 3 * kStep), row1 = a.len_row[q1.L];
+        const int i3 = index(k + 3 * kStep), row1 = row_at(a.len_row, q1.L);
         const Request q2 = fetch<true>(a.s, i2, a.max_len);
         Selection<4, false> sel(a, q, row, sub);
         sel.run_at = lds_at;
@@ -1249,7 +1411,7 @@ __global__ __launch_bounds__(kBlock) void k_hits(HitArgs a)
     const float c0 = (float)ci, Lf = (float)L, D = a.budget[r];
     const float Dc = D > FLT_MAX ? FLT_MAX : D;
     const int ex = a.exclude ? a.exclude[r] : -1;
-    const float* __restrict__ rowE = a.memo + memo_at(a.len_row[L], 0, a.n_run);
+    const float* __restrict__ rowE = a.memo + memo_at(row_at(a.len_row, L), 0, a.n_run);
     const auto E_at = [&](int p) { return rowE[(size_t)(p / kMemoP) * kTile + p % kMemoP]; };
 
     unsigned long long feasKey = ~0ull;
@@ -1303,11 +1465,7 @@ struct DirectArgs {
     float* out_T;
     int n, n_inst, cap, max_len, parts;
     int finite;              // 1: an infinite latency (or a NaN) is none, as in the pass over the table
-    // a risk scan: what the build left for the table pass (see ScanArgs), put in order by an extra workgroup
-    uint4* seen;
-    int *totals, *out_n;
-    const int* late_cnt;
-    int seen_words, n_late;
+    CountArgs count;         // a risk scan: by an extra workgroup
 };
 
 __device__ inline DirectPart no_selection() { return DirectPart{~0u, ~0u, ~0u, ~0u, ~0u, ~0u}; }
@@ -1353,28 +1511,6 @@ __device__ inline void direct_answer(const DirectArgs& a, int r, float D, const 
     if (a.out_fallback) a.out_fallback[r] = !found;
 }
 
-// What k_scan and k_memo do for a risk scan besides the table, by one workgroup: the number of flagged
-// requests (where the build has not set every flag: by the flags), and the marks of their lengths, which nobody needs here.
-__device__ void close_scan(const DirectArgs& a)
-{
-    __shared__ int sums[1024 / kWave];
-    const int tid = threadIdx.x, threads = blockDim.x;
-    const bool unset = a.totals[2] != 0 || a.s.act_off[0] > 0 || a.s.act_off[a.n_inst] < a.n;
-    int n = 0;
-    if (a.out_n) {
-        if (unset) for (int i = tid; i < a.n; i += threads) n += a.s.flag[i] != 0;
-        else for (int i = tid; i < a.n_late; i += threads) n += a.late_cnt[i];
-    }
-    for (int i = tid; i < a.seen_words; i += threads) a.seen[i] = make_uint4(0u, 0u, 0u, 0u);
-    n = wave_sum(n);
-    if (lane_id() == 0) sums[tid / kWave] = n;
-    __syncthreads();
-    if (tid != 0) return;
-    for (int w = 1; w < threads / kWave; ++w) n += sums[w];
-    if (a.out_n) *a.out_n = n;
-    a.totals[2] = 0;
-}
-
 // A batch of a few requests (one arriving request is the paper's own case): grouping by length and
 // a table of per-length values would cost more than they save, so kLanes lanes take a request, each
 // an instance (or a few), and form T = E + c0 * kappa with E from the instance's own tables (the
@@ -1393,8 +1529,9 @@ __device__ void close_scan(const DirectArgs& a)
 template <bool kMigrate, int kLanes, int kU, bool kLargeTab>     // kU: instances of a lane in flight together
 __global__ __launch_bounds__(kLanes <= 64 ? kBlock : kLanes) void k_direct(DirectArgs a)
 {
-    if (kMigrate && blockIdx.x == gridDim.x - 1) return close_scan(a);
     constexpr int kThreads = kLanes <= 64 ? kBlock : kLanes;
+    __shared__ int sums[kThreads / kWave];
+    if (kMigrate && blockIdx.x == gridDim.x - 1) return count_flagged(a.count, kThreads, sums);
     constexpr int kPerGroup = kThreads / kLanes;              // requests per workgroup
     constexpr int kS = kLargeTab ? 4 : 2, kB = kLargeTab ? 8 : 4;   // most 16-byte words of splitters, of a stride
     const int sub = threadIdx.x % kLanes;
@@ -1464,7 +1601,7 @@ __global__ __launch_bounds__(kLanes <= 64 ? kBlock : kLanes) void k_direct(Direc
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             const int N = __float_as_int(K[u].w);
-            const float E = fmaf(Lf, gh[u].y, gh[u].x) + tri * (K[u].z * (float)(N - k[u] + 1));
+            const float E = fmaf(tri, K[u].z * (float)(N - k[u] + 1), fmaf(Lf, gh[u].y, gh[u].x));
             const float T = fmaf(c0, kappa_of(make_float2(K[u].x, K[u].y), Lf), E);
             if (a.out_T && live) a.out_T[(size_t)r * a.n_inst + g[u]] = T;
             if (g[u] != ex && (!a.finite || T < __builtin_inff())) {
@@ -1585,7 +1722,7 @@ __device__ __forceinline__ void pairs(const PairsArgs& a)
     }
 #pragma unroll
     for (int j = 0; j < kReq; ++j) {
-        row[j] = a.len_row[L[j]] - (kWrite ? a.row0 : 0);
+        row[j] = row_at(a.len_row, L[j]) - (kWrite ? a.row0 : 0);
         if (r0 + j >= a.n || (kWrite && (unsigned)row[j] >= (unsigned)a.rows)) row[j] = -1;
     }
     struct alignas(4 * kVec) Values { float v[kVec]; };
@@ -1654,6 +1791,11 @@ __global__ void k_set_int(int* p, int v) { *p = v; }
 
 }  // namespace
 
+static CountArgs count_args(const gr_fleet* f, const ReqSrc& src, const ScoreOut& out)
+{
+    return CountArgs{f->totals, out.n_selected, f->late_cnt, src.act_off, src.flag, src.n, f->n_inst * f->late_parts, f->n_inst};
+}
+
 // Alg. 1 pair by pair.
 template <bool kMigrate>
 static int launch_pair_by_pair(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, bool finite, hipStream_t s)
@@ -1669,10 +1811,7 @@ static int launch_pair_by_pair(gr_fleet* f, const ReqSrc& src, const ScoreOut& o
     d.n = n; d.n_inst = M; d.cap = f->cap; d.max_len = f->max_len; d.finite = finite;
     d.parts = kMigrate ? 1 : (M + kDirectSpan - 1) / kDirectSpan;
     if ((int64_t)n * d.parts > kDirectParts) d.parts = 1;      // (many requests fill the chip as they are)
-    if (kMigrate) {
-        d.seen = reinterpret_cast<uint4*>(f->seen); d.seen_words = (f->bins + 15) / 16;
-        d.totals = f->totals; d.out_n = out.n_selected; d.late_cnt = f->late_cnt; d.n_late = M * f->late_parts;
-    }
+    if (kMigrate) d.count = count_args(f, src, out);
     // lanes per request: an instance each as far as a workgroup goes (few requests: the chain of reads
     // of one instance is the time of the call); 64 lanes leave the fewest idle on small fleets, 16 with two
     // instances each up to 32 (16 384 requests x 32 instances 6.7 us, 8.9 with 64 lanes)
@@ -1775,11 +1914,41 @@ struct PairsPlan {
     }
 };
 
+// Whether the table of a pass has a row for every length there may be, so that the list of those that there are is not
+// made, and the class order is made by the table's workgroups: two launches less (three in a routing call), two
+// dependent reads less, for a table that may be larger.  On fleets so small that the workgroups fit the chip at once
+// and a class's order is quickly made.  Control interval of 256 x 512, 65 536 arrivals: 64.7 us with the list, 54.5 without
+// (the table 10.2 us with its order, before 8.2 behind 5.1 for list and order and, routing, 2.4 for the marks).  On larger fleets the
+// order takes a launch of its own and the table's workgroups outnumber what the chip holds at once: 777 instances, 20 011 requests, 29.2 / 29.3;
+// 1 024 x 200, 32 768 requests 66.7 / 66.9.
+static bool dense_rows(const gr_fleet* f)
+{
+    return f->req_cap >= f->bins && f->most_of_class <= kOwnClass && f->m_pos <= kOwnSlots &&
+           (int64_t)f->bins * f->m_pos <= kDenseValues;
+}
+
+bool needs_marks(const gr_fleet* f, int64_t n) { return !pair_by_pair(f, n) && !dense_rows(f); }
+
+// How the rows of a pass are found.
+struct RowsOf {
+    const int* totals;
+    const int* row_len;          // null: a row per length
+    const uint16_t* len_row;
+    int64_t most;
+};
+
+static RowsOf rows_of(const gr_fleet* f, int64_t n)
+{
+    if (dense_rows(f)) return {f->dense_totals, nullptr, nullptr, f->bins};
+    return {f->totals, f->row_len, f->len_row, std::min<int64_t>(n, f->bins)};
+}
+
 static PairsArgs pairs_args(const gr_fleet* f, const ReqSrc& src, const ScoreOut& out)
 {
+    const RowsOf rows = rows_of(f, src.n);
     PairsArgs p{};
     p.ctx0 = src.ctx0; p.pred_len = src.pred_len; p.budget = src.budget; p.exclude = src.exclude;
-    p.totals = f->totals; p.len_row = f->len_row; p.order = f->order; p.memo = f->memo; p.instK = f->instK; p.hD = f->hD;
+    p.totals = rows.totals; p.len_row = rows.len_row; p.order = f->order; p.memo = f->memo; p.instK = f->instK; p.hD = f->hD;
     p.turned = f->turned; p.out_T = out.T; p.out_inst = out.inst; p.out_slack = out.slack; p.out_fallback = out.fallback;
     p.pos_of = f->pos_of;
     p.n = src.n; p.rows = f->turned_rows; p.n_inst = f->n_inst; p.m_pos = f->m_pos; p.max_len = f->max_len;
@@ -1842,24 +2011,26 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     const TableView view = account.view(f);
     const bool with_order = !view.ordered, blended = view.blended;
     const int off = migrate ? kScanMigrate - kScanRoute : 0;
-    if (!migrate) {
+    const bool dense = dense_rows(f);
+    const RowsOf rows = rows_of(f, n);
+    OrderArgs o{};
+    o.key = f->slot_key; o.instK = f->instK; o.slot_inst = f->slot_inst; o.run_cls = f->run_cls;
+    o.order = f->order; o.pos_of = f->pos_of; o.posK = f->posK; o.posKey = f->posKey; o.run_head = f->run_head; o.m_pos = f->m_pos;
+    if (!migrate && !dense) {
         ProfScope ps(f, kMarkRoute, s);
         constexpr int per = kBlock * kMarkItems;
         hipLaunchKernelGGL(k_mark, dim3((unsigned)((n + per - 1) / per)), dim3(kBlock), 0, s, src.pred_len, n, f->seen, f->max_len);
     }
-    {
+    if (!dense) {
         ScanArgs sc{};
         sc.seen = f->seen; sc.row_len = f->row_len; sc.len_row = f->len_row; sc.totals = f->totals; sc.bins = f->bins;
         sc.late_cnt = f->late_cnt; sc.n_late = migrate ? f->n_inst * f->late_parts : 0; sc.out_n = out.n_selected;
         sc.flag = src.flag; sc.act_rem = src.act_rem; sc.act_off = src.act_off; sc.n = n; sc.n_inst = f->n_inst;
-        OrderArgs o{};
-        o.key = f->slot_key; o.instK = f->instK; o.slot_inst = f->slot_inst; o.run_cls = f->run_cls;
-        o.order = f->order; o.pos_of = f->pos_of; o.posK = f->posK; o.posKey = f->posKey; o.run_head = f->run_head; o.m_pos = f->m_pos;
         ProfScope ps(f, kScanRoute + off, s);
         hipLaunchKernelGGL(k_scan, dim3(kScanGroups + (with_order ? order_blocks(f->m_pos, kScanBlock) : 0)), dim3(kScanBlock), 0, s, sc, o);
     }
     account.v->ordered = true;
-    const int64_t max_rows = n < f->bins ? n : f->bins;
+    const int64_t max_rows = rows.most;
     // Classes first in large batches on fleets of many runs.  Whole routing call, us, a group of lanes per
     // request / classes first; in brackets with deadlines that most requests can meet, where
     // the classes only say which runs to look at:
@@ -1890,30 +2061,38 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     // table of 7 061 rows x 4 096 instances); row by row where many may: a request's 16 lanes then read 16
     // runs from one cache line, not from sixteen.
     const bool blocks = by_class && migrate;
+    const bool own = dense && with_order;
     {
         MemoArgs m{};
+        m.own = o; m.run_cls = f->run_cls;
+        if (dense && migrate) m.count = count_args(f, src, out);
         m.totals = f->totals; m.row_len = f->row_len; m.len_row = f->len_row; m.order = f->order; m.instK = f->instK;
         m.tabR = f->tabR; m.tabGH = f->tabGH; m.memo = f->memo; m.grp_min = f->grp_min;
         m.run_k = f->run_k; m.run_rank = f->run_rank; m.pos_thr = f->pos_thr; m.run_at = f->run_at; m.posK = f->posK; m.posKey = f->posKey;
         m.run_head = f->run_head;
-        m.seen = reinterpret_cast<uint4*>(f->seen); m.seen_words = (f->bins + 15) / 16;
-        m.n_run = f->n_run; m.run8 = (f->n_run + 7) / 8 * 8; m.bins = f->bins; m.run_pad = f->run_pad; m.cap = f->cap;
+        m.seen = reinterpret_cast<uint4*>(f->seen); m.seen_words = dense ? 0 : (f->bins + 15) / 16;
+        m.n_run = f->n_run; m.bins = f->bins; m.run_pad = f->run_pad; m.cap = f->cap;
         // (workgroups for as many rows as there may be; those past the last row end at once)
-        const dim3 grid((unsigned)(m.run8 * (1 + (max_rows + kMemoU - 1) / kMemoU)));
+        // (a run's workgroups on one XCD: the runs rounded up to a multiple of the XCDs)
+        const dim3 grid((unsigned)((f->n_run + 7) / 8 * 8), (unsigned)(1 + (max_rows + kMemoU - 1) / kMemoU));
         ProfScope ps(f, kMemoRoute + off, s);
-#define GR_LAUNCH_MEMO(B) do { \
-        if (f->cap > 1024) hipLaunchKernelGGL((k_memo<4, B>), grid, dim3(kBlock), 0, s, m); \
-        else if (f->cap > 512) hipLaunchKernelGGL((k_memo<2, B>), grid, dim3(kBlock), 0, s, m); \
-        else hipLaunchKernelGGL((k_memo<1, B>), grid, dim3(kBlock), 0, s, m); } while (0)
-        if (blocks) GR_LAUNCH_MEMO(true);
-        else GR_LAUNCH_MEMO(false);
+#define GR_LAUNCH_MEMO(B, D, O) do { \
+        if (f->cap > 1024) hipLaunchKernelGGL((k_memo<4, B, D, O>), grid, dim3(kBlock), 0, s, m); \
+        else if (f->cap > 512) hipLaunchKernelGGL((k_memo<2, B, D, O>), grid, dim3(kBlock), 0, s, m); \
+        else hipLaunchKernelGGL((k_memo<1, B, D, O>), grid, dim3(kBlock), 0, s, m); } while (0)
+        if (blocks && own) GR_LAUNCH_MEMO(true, true, true);
+        else if (blocks && dense) GR_LAUNCH_MEMO(true, true, false);
+        else if (blocks) GR_LAUNCH_MEMO(true, false, false);
+        else if (own) GR_LAUNCH_MEMO(false, true, true);
+        else if (dense) GR_LAUNCH_MEMO(false, true, false);
+        else GR_LAUNCH_MEMO(false, false, false);
 #undef GR_LAUNCH_MEMO
     }
     if (by_class) {
         ClassArgs c{};
-        c.totals = f->totals; c.cls_run = f->cls_run; c.order = f->order; c.memo = f->memo; c.grp_min = f->grp_min;
+        c.totals = rows.totals; c.cls_run = f->cls_run; c.order = f->order; c.memo = f->memo; c.grp_min = f->grp_min;
         c.run_k = f->run_k; c.class_min = f->class_min; c.class_next = f->class_next; c.cls_bound = f->cls_bound;
-        c.n_class = f->n_class; c.c_pad = f->c_pad; c.n_run = f->n_run; c.run_pad = f->run_pad;
+        c.n_class = f->n_class; c.c_pad = f->c_pad; c.n_run = f->n_run; c.run_pad = f->run_pad; c.dense = dense;
         ProfScope ps(f, kClassRoute + off, s);
         const dim3 grid((unsigned)((max_rows + kWave - 1) / kWave * f->n_class));
         if (blocks) hipLaunchKernelGGL(k_class<true>, grid, dim3(kBlock), 0, s, c);
@@ -1921,12 +2100,12 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     }
     if (select) {
         SelectArgs a{};
-        a.s = src; a.len_row = f->len_row; a.order = f->order; a.memo = f->memo; a.grp_min = f->grp_min; a.run_k = f->run_k;
+        a.s = src; a.len_row = rows.len_row; a.order = f->order; a.memo = f->memo; a.grp_min = f->grp_min; a.run_k = f->run_k;
         a.posK = f->posK; a.posKey = f->posKey; a.run_rank = f->run_rank; a.pos_thr = f->pos_thr; a.run_at = f->run_at; a.cls_run = f->cls_run; a.class_min = f->class_min; a.class_next = f->class_next; a.clsK = f->clsK; a.cls_bound = f->cls_bound;
         a.out_inst = out.inst; a.out_slack = out.slack; a.out_fallback = out.fallback;
         a.run_pad = f->run_pad; a.n_run = f->n_run; a.n_class = f->n_class; a.c_pad = f->c_pad;
         a.max_len = f->max_len;
-        a.lines = f->lines; a.totals = f->totals; a.row_len = f->row_len; a.pos_of = f->pos_of;
+        a.lines = f->lines; a.totals = rows.totals; a.row_len = rows.row_len; a.pos_of = f->pos_of;
         a.rest_cnt = f->rest_cnt;
         if (by_lines) {
             constexpr int per = kBlock / kWave;
@@ -1963,7 +2142,7 @@ int launch_hits(gr_fleet* f, const ReqSrc& src, const int* hit_off, const int* h
     HitArgs h{};
     h.ctx0 = src.ctx0; h.pred_len = src.pred_len; h.budget = src.budget; h.exclude = src.exclude;
     h.hit_off = hit_off; h.hit_inst = hit_inst; h.hit_len = hit_len;
-    h.len_row = f->len_row; h.pos_of = f->pos_of; h.memo = f->memo; h.posK = f->posK; h.posKey = f->posKey;
+    h.len_row = rows_of(f, src.n).len_row; h.pos_of = f->pos_of; h.memo = f->memo; h.posK = f->posK; h.posKey = f->posKey;
     h.out_inst = out.inst; h.out_slack = out.slack; h.out_fallback = out.fallback; h.out_T = out.T;
     h.n = src.n; h.n_hits = n_hits; h.n_inst = f->n_inst; h.n_run = f->n_run; h.max_len = f->max_len;
     ProfScope ps(f, kHitsRoute, s);

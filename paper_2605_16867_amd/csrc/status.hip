@@ -41,7 +41,7 @@ struct BuildArgs {
     int64_t n_active, n_queued;
     int n_inst, max_entries, max_len;
     // for the migration pass of a risk scan: which lengths flagged requests have, and how many are flagged
-    uint8_t* seen;
+    uint8_t* seen;       // null: nobody asks for the lengths
     int* late_cnt;
     // requests routed since the caller's status (feedback routing): per instance, queued behind the queue
     int* pend_cnt;
@@ -377,7 +377,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
                 if (a.act_budget) {
                     const bool late = fin > (double)bud;
                     a.out_flag[a0 + i] = late;
-                    if (late) { a.seen[rem] = 1; ++n_late; }
+                    if (late) { if (a.seen) a.seen[rem] = 1; ++n_late; }
                 }
             } else if (a.out_q_finish) {
                 a.out_q_finish[q0 + i - A] = (float)fin;
@@ -996,10 +996,12 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
 #pragma unroll
         for (int r = 0; r < kEPL; ++r) mig |= (unsigned)(r < mine && idx[r] < A) << r;
         mig &= late;
+        if (a.seen) {
 #pragma unroll
-        for (int r = 0; r < kEPL; ++r) {
-            const bool again = r + 1 < kEPL && ((mig >> (r + 1)) & 1u) && Ri[r + 1 < kEPL ? r + 1 : r] == Ri[r];
-            if (((mig >> r) & 1u) && !again) a.seen[Ri[r]] = 1;
+            for (int r = 0; r < kEPL; ++r) {
+                const bool again = r + 1 < kEPL && ((mig >> (r + 1)) & 1u) && Ri[r + 1 < kEPL ? r + 1 : r] == Ri[r];
+                if (((mig >> r) & 1u) && !again) a.seen[Ri[r]] = 1;
+            }
         }
         const int n_late = wave_incl_scan_i32(__popc(mig));
         if (lane == kWave - 1) a.late_cnt[part * a.n_inst + g] = n_late;
@@ -1451,7 +1453,7 @@ int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s)
     b.instK = f->instK; b.tabS = f->tabS; b.slot_of = f->slot_of; b.slot_key = f->slot_key; b.counters = f->counters;
     b.n_active = in.n_active; b.n_queued = in.n_queued;
     b.n_inst = f->n_inst; b.max_entries = f->max_entries; b.max_len = f->max_len;
-    b.seen = f->seen; b.late_cnt = f->late_cnt; b.unset = f->totals + 2;
+    b.seen = in.mark ? f->seen : nullptr; b.late_cnt = f->late_cnt; b.unset = f->totals + 2;
     b.pend_cnt = f->pend_cnt; b.pend_prompt = f->pend_prompt; b.pend_len = f->pend_len;
     b.use_pending = in.use_pending;
     b.pend_touched = f->pend_touched; b.only_touched = in.use_pending && in.only_touched;
