@@ -1813,8 +1813,9 @@ static int launch_pair_by_pair(gr_fleet* f, const ReqSrc& src, const ScoreOut& o
     if ((int64_t)n * d.parts > kDirectParts) d.parts = 1;      // (many requests fill the chip as they are)
     if (kMigrate) d.count = count_args(f, src, out);
     // lanes per request: an instance each as far as a workgroup goes (few requests: the chain of reads
-    // of one instance is the time of the call); 64 lanes leave the fewest idle on small fleets, 16 with two
-    // instances each up to 32 (16 384 requests x 32 instances 6.7 us, 8.9 with 64 lanes)
+    // of one instance is the time of the call); 64 lanes leave the fewest idle on small fleets, and
+    // where there are requests enough, 16 with two instances each up to 32 (16 384 requests x 32 instances
+    // 6.7 us, 8.9 with 64 lanes; 110 x 17 a microsecond more)
     {
         ProfScope ps(f, kDirect, s);
 #define GR_LAUNCH_DIRECT(N, U) do { \
@@ -1823,7 +1824,7 @@ static int launch_pair_by_pair(gr_fleet* f, const ReqSrc& src, const ScoreOut& o
         if (f->cap > 512) hipLaunchKernelGGL((k_direct<kMigrate, N, (U > 2 ? 2 : U), true>), grid, block, 0, s, d); \
         else hipLaunchKernelGGL((k_direct<kMigrate, N, U, false>), grid, block, 0, s, d); } while (0)
         if (M <= 16) GR_LAUNCH_DIRECT(16, 1);
-        else if (M <= 32) GR_LAUNCH_DIRECT(16, 2);
+        else if (M <= 32 && n > kDirectMax) GR_LAUNCH_DIRECT(16, 2);
         else if (M <= 64) GR_LAUNCH_DIRECT(64, 1);
         else if (M <= 512) GR_LAUNCH_DIRECT(256, 1);
         else if (M <= 1024) GR_LAUNCH_DIRECT(1024, 1);
