@@ -284,6 +284,7 @@ struct OwnLds {
     int inst[kOwnSlots];
     int rank[kOwnClass];
     int slot[kMemoP];      // the slot of each of the run's positions, -1: none
+    uint4 head[kOwnSlots / kMemoP];      // as gr_fleet::run_head
 };
 
 // a key (falling_bits) to single precision
@@ -337,11 +338,37 @@ __device__ __forceinline__ void own_order(const OrderArgs& a, int run, OwnLds& l
     __syncthreads();
 }
 
+// The first instance of every run, from the ranks of all instances in their classes (of the workgroups that write
+// the order down; own_order has read the keys).
+__device__ __forceinline__ void own_heads(const OrderArgs& a, OwnLds& l)
+{
+#pragma unroll
+    for (int s = threadIdx.x; s < kOwnSlots; s += kBlock) {
+        if (s >= a.m_pos || l.inst[s] < 0) continue;
+        const int2 rc = a.run_cls[s / kMemoP];
+        const uint32_t own = l.rough[s];
+        int less = 0, same = 0;
+#pragma unroll 4
+        for (int h = 0; h < rc.y; h += 4) {
+            const uint4 k = *reinterpret_cast<const uint4*>(l.rough + rc.x + h);
+            less += (k.x < own) + (k.y < own) + (k.z < own) + (k.w < own);
+            same += (k.x == own) + (k.y == own) + (k.z == own) + (k.w == own);
+        }
+        if (same > 1) {
+            const unsigned long long mine = l.key[s];
+#pragma unroll 4
+            for (int h = rc.x; h < rc.x + rc.y; ++h) less += l.rough[h] == own && (l.key[h] < mine || (l.key[h] == mine && h < s));
+        }
+        if (less % kMemoP == 0)
+            l.head[(rc.x + less) / kMemoP] = make_uint4((uint32_t)l.key[s], (uint32_t)(l.key[s] >> 32), (uint32_t)l.inst[s], 0u);
+    }
+    __syncthreads();
+}
+
 // For each position of a run, how many runs begin with a more capable instance: 16 lanes each.  And what the
 // selection needs of the run: its least and largest delta (gamma is the same for all of a class) and its lowest instance.
 //
-// Where the workgroups make the class order themselves (kOwn), this one writes it down for the selection, and
-// counts instances instead of runs' first ones: of a run and a choice, either says whether the run begins with a better one.
+// Where the workgroups make the class order themselves (kOwn), this one writes it down for the selection.
 template <bool kOwn>
 __device__ __forceinline__ void rank_run(const MemoArgs& a, int run, int* lds)
 {
@@ -365,15 +392,12 @@ __device__ __forceinline__ void rank_run(const MemoArgs& a, int run, int* lds)
         key = s >= 0 ? l.key[s] : ~0ull;
         kk = make_float2(__builtin_inff(), 0.f);
         if (gi >= 0) { const float4 k = a.instK[gi]; kk = make_float2(k.x, k.y); }
-        for (int s0 = sub; s0 < a.own.m_pos; s0 += kAhead * kMemoP) {
+        own_heads(a.own, l);
 #pragma unroll
-            for (int i = 0; i < kAhead; ++i) {
-                const int h = s0 + i * kMemoP;
-                if (h >= kOwnSlots) break;
-                const unsigned long long hk = l.key[h];
-                const int hg = l.inst[h];
-                n += h < a.own.m_pos && hg >= 0 && (hk < key || (hk == key && hg < g));
-            }
+        for (int r = sub; r < kOwnSlots / kMemoP; r += kMemoP) {
+            const uint4 h = l.head[r];
+            const unsigned long long hk = ((unsigned long long)h.y << 32) | h.x;
+            n += r < a.n_run && (hk < key || (hk == key && (int)h.z < g));
         }
         if (sub == 0) {
             a.own.order[p] = g;
@@ -413,7 +437,7 @@ __device__ __forceinline__ void rank_run(const MemoArgs& a, int run, int* lds)
         a.pos_thr[p] = n;
         if (threadIdx.x == 0) {
             a.run_rank[run] = n;
-            if (!kOwn) a.run_at[n] = run;
+            a.run_at[n] = run;
             a.run_k[run] = make_float4(lo, gm, hi, __int_as_float(low));
         }
     }
@@ -756,7 +780,7 @@ struct SelectArgs {
     int* out_inst;
     float* out_slack;
     uint8_t* out_fallback;
-    int run_pad, n_run, n_class, c_pad, max_len;
+    int run_pad, n_run, n_class, c_pad, max_len, n_inst;
     int segments;      // by classes or lines first: workgroups of the launch
     int64_t first;     // a group of lanes per request: the launch's first request
 };
@@ -976,6 +1000,159 @@ __global__ __launch_bounds__(kBlock) void k_select(SelectArgs a)
     sel.template scan<true, true, false>(0, a.n_run);
     if (sel.feasG < 0) sel.settle(0, a.n_run);
     sel.template report<kMigrate>(i, q.D);
+}
+
+// Four lanes per request on fleets of up to kLaneRuns runs.  The bounds of the runs of a request's row stay in
+// registers, and a run is looked at by the same lanes, its 16 values being one piece of 64 bytes: about a quarter of the vector
+// instructions that 16 lanes per request take, which is what batches of many requests wait for.  Whole calls, us, 16 lanes /
+// four / one (fewer instructions still, but a wave for every SIMD at 65 536 requests, and nothing to hide its reads behind):
+//   route 256 instances: 32 768 requests 14.9 / 14.3 / 17.4, 65 536 16.9 / 13.6 / 16.2, 262 144 31.8 / 18.3 / 20.6
+//   (16 384 13.7 / 14.1 / 17.3); 480: 262 144 45.0 / 28.7 / 31.3, blended 48.3 / 30.3 / 33.5
+//   scan 256 x 512 30.4 / 24.8 / 30.8, blended 33.8 / 25.0 / 28.1, 400 x 1 000 70.4 / 47.9 / 53.7
+// The answers are Selection's.
+constexpr int kLaneRuns = 32;
+constexpr int kLanes = 4;
+
+// over the lanes of a request
+__device__ __forceinline__ uint32_t lanes_min(uint32_t v)
+{
+    return min_dpp<0x4E, 0xf>(min_dpp<0xB1, 0xf>(v));      // quad_perm [1,0,3,2], [2,3,0,1]
+}
+
+__device__ __forceinline__ uint32_t lanes_or(uint32_t v)
+{
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, false);
+    return v | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, false);
+}
+
+template <bool kMigrate, int kRuns, bool kBlend>
+__global__ __launch_bounds__(kBlock) void k_select_lanes(SelectArgs a)
+{
+    // of each run: its least delta, gamma, largest delta, its rank as a bit; the run of each rank; delta and gamma by position
+    __shared__ float4 of_run[kRuns];
+    __shared__ int at_rank[kRuns];
+    __shared__ float2 of_pos[kBlend ? kRuns * kMemoP : 1];
+    const int tid = threadIdx.x, sub = tid % kLanes;
+    if (tid < a.n_run) {
+        float4 k = a.run_k[tid];
+        k.w = __uint_as_float(1u << a.run_rank[tid]);
+        of_run[tid] = k;
+        at_rank[tid] = a.run_at[tid];
+    }
+    if (kBlend)
+        for (int p = tid; p < a.n_run * kMemoP; p += kBlock) of_pos[p] = a.posK[p];
+    const int64_t i = a.first + ((int64_t)blockIdx.x * kBlock + tid) / kLanes;
+    const Request q = fetch<kMigrate>(a.s, min(i, a.s.n - 1), a.max_len);
+    const int row = row_at(a.len_row, q.L);
+    const int ex_at = q.ex >= 0 && q.ex < a.n_inst ? a.pos_of[q.ex] : -1;
+    __syncthreads();
+    if (i >= a.s.n) return;
+    const auto reply = [&](int g, float slack, bool found) { if (sub == 0) answer<kMigrate>(a, i, g, slack, found); };
+    if (!q.scored) return reply(-1, 0.f, false);      // not flagged: no migration target
+
+    // a lane's runs of a row, and its positions of a run: four together, then the other lanes' four
+    const auto nth = [&](int x) { return x / 4 * (4 * kLanes) + 4 * sub + x % 4; };
+    constexpr int kMine = kRuns / kLanes, kAt = kMemoP / kLanes;
+    const float inf = __builtin_inff();
+    const float c0 = (float)q.c0, Lf = (float)q.L, Dc = q.D > FLT_MAX ? FLT_MAX : q.D;
+    const float* __restrict__ E = a.memo + memo_at(row, 0, a.n_run);
+    float b[kMine];
+    {
+        const float* __restrict__ runs = a.grp_min + (size_t)row * a.run_pad;      // (a row's length is a multiple of 16)
+#pragma unroll
+        for (int x = 0; x < kMine; x += 4) {
+            float4 e = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (x / 4 * (4 * kLanes) < a.n_run) e = *reinterpret_cast<const float4*>(runs + nth(x));
+            b[x] = e.x; b[x + 1] = e.y; b[x + 2] = e.z; b[x + 3] = e.w;
+        }
+    }
+    float least = inf;
+    int least_run = -1;
+    uint32_t open = 0;       // by rank: the runs that may hold a feasible instance
+#pragma unroll
+    for (int x = 0; x < kMine; ++x) {
+        const int r = nth(x);
+        if (r < a.n_run) {
+            const float4 k = of_run[r];
+            b[x] = fmaf(c0, kappa_of(make_float2(!kBlend || c0 >= 0.f ? k.x : k.z, k.y), Lf), b[x]);
+            if (b[x] < least) { least = b[x]; least_run = r; }
+            open |= b[x] <= Dc ? __float_as_uint(k.w) : 0u;
+        } else {
+            b[x] = inf;
+        }
+    }
+    open = lanes_or(open);
+    // every latency of a run, that of the excluded instance infinite
+    const auto latencies = [&](int run, float (&T)[kAt]) {
+        const float* __restrict__ line = E + (size_t)run * kTile;
+#pragma unroll
+        for (int x = 0; x < kAt; x += 4) {
+            const float4 e = *reinterpret_cast<const float4*>(line + nth(x));
+            T[x] = e.x; T[x + 1] = e.y; T[x + 2] = e.z; T[x + 3] = e.w;
+        }
+        const float4 k = of_run[run];
+        const float kappa = kappa_of(make_float2(k.x, k.y), Lf);
+        const int ex = ex_at - run * kMemoP;
+#pragma unroll
+        for (int x = 0; x < kAt; ++x) {
+            T[x] = fmaf(c0, kBlend ? kappa_of(of_pos[run * kMemoP + nth(x)], Lf) : kappa, T[x]);
+            T[x] = nth(x) == ex ? inf : T[x];
+        }
+    };
+    int feasG = -1;
+    float feasT = 0.f;
+    unsigned long long feasKey = ~0ull;
+    while (open) {       // the most capable run first
+        const int run = at_rank[__ffs(open) - 1];
+        open &= open - 1;
+        float T[kAt];
+        latencies(run, T);
+        uint32_t hit = kMemoP;
+        float hitT = 0.f;
+#pragma unroll
+        for (int x = kAt - 1; x >= 0; --x)
+            if (T[x] <= Dc) { hit = nth(x); hitT = T[x]; }
+        const uint32_t first = lanes_min(hit);
+        if (first == kMemoP) continue;
+        const int p = run * kMemoP + (int)first, g = a.order[p];
+        const unsigned long long key = a.posKey[p];
+        const uint32_t thr = a.pos_thr[p];
+        hitT = from_ordered_bits(lanes_min(hit == first ? ordered_bits(hitT) : ~0u));
+        if (feasG < 0 || key < feasKey || (key == feasKey && g < feasG)) {
+            feasKey = key; feasG = g; feasT = hitT;
+            if (thr < 32) open &= (1u << thr) - 1u;      // (the others begin with nobody better)
+        }
+    }
+    if (feasG >= 0) return reply(feasG, q.D - feasT, true);
+
+    float bestT = inf;
+    int bestG = -1;
+    const auto look = [&](int run) {
+        float T[kAt];
+        latencies(run, T);
+        float m = inf;
+#pragma unroll
+        for (int x = 0; x < kAt; ++x) m = min_plain(m, T[x]);
+        m = from_ordered_bits(lanes_min(ordered_bits(m)));
+        if (!(m < inf) || m > bestT) return;
+        uint32_t equal = 0;
+#pragma unroll
+        for (int x = 0; x < kAt; ++x) equal |= T[x] == m ? 1u << nth(x) : 0u;
+        int low = 0x7fffffff;
+        for (equal = lanes_or(equal); equal; equal &= equal - 1) low = min(low, a.order[run * kMemoP + __ffs(equal) - 1]);
+        if (m < bestT || low < bestG) { bestT = m; bestG = low; }
+    };
+    // the least bound, of equal ones that of the first run
+    const uint32_t all_least = lanes_min(ordered_bits(least));
+    least_run = (int)lanes_min(least_run >= 0 && ordered_bits(least) == all_least ? (uint32_t)least_run : 0x7fffffffu);
+    if (least_run != 0x7fffffff) {
+        look(least_run);
+        uint32_t others = 0;
+#pragma unroll
+        for (int x = 0; x < kMine; ++x) others |= b[x] <= bestT && b[x] < inf && nth(x) != least_run ? 1u << nth(x) : 0u;
+        for (others = lanes_or(others); others; others &= others - 1) look(__ffs(others) - 1);
+    }
+    reply(bestG, bestG >= 0 ? q.D - bestT : 0.f, false);
 }
 
 // The same where the least E of every class is known: the runs of one class after the other, as long
@@ -1863,6 +2040,8 @@ constexpr int64_t kByClassMin = int64_t(1) << 17;      // requests from which th
 constexpr int64_t kByClassMany = int64_t(1) << 19;
 constexpr int64_t kLinesScanMin = int64_t(3) << 16;     // requests of a scan from which the lines are looked at first
 
+constexpr int64_t kLaneMin = 1 << 15;      // requests from which four lanes take one, on fleets of few runs (see k_select_lanes)
+
 constexpr int kFewInst = 16;     // instances up to which a routing batch is decided over all of them
 
 // A launch has fewer than 2^32 threads: kernels that take many threads per request go through larger batches
@@ -1870,7 +2049,7 @@ constexpr int kFewInst = 16;     // instances up to which a routing batch is dec
 constexpr int64_t kLaunchThreads = int64_t(1) << 31;
 
 template <bool kMigrate>
-static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, bool by_lines, hipStream_t s)
+static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, bool by_lines, bool blended, hipStream_t s)
 {
     const int64_t n = a.s.n;
     if (by_class) {
@@ -1881,6 +2060,19 @@ static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, bool b
         a.segments = (int)((n + per - 1) / per);
         if (many) hipLaunchKernelGGL((k_select_by_class<kMigrate, kBlock, 2>), dim3(a.segments), dim3(kBlock), 0, s, a);
         else hipLaunchKernelGGL((k_select_by_class<kMigrate, kWave, 1>), dim3(a.segments), dim3(kBlock), 0, s, a);
+        return;
+    }
+    if (!by_lines && f->n_run <= kLaneRuns && n >= kLaneMin) {
+        for (a.first = 0; a.first < n; a.first += kLaunchThreads / kLanes) {
+            const int64_t here = std::min(n - a.first, kLaunchThreads / kLanes);
+            const dim3 grid((unsigned)((here * kLanes + kBlock - 1) / kBlock));
+#define GR_LAUNCH_LANES(R) do { \
+            if (blended) hipLaunchKernelGGL((k_select_lanes<kMigrate, R, true>), grid, dim3(kBlock), 0, s, a); \
+            else hipLaunchKernelGGL((k_select_lanes<kMigrate, R, false>), grid, dim3(kBlock), 0, s, a); } while (0)
+            if (f->n_run <= 16) GR_LAUNCH_LANES(16);
+            else GR_LAUNCH_LANES(32);
+#undef GR_LAUNCH_LANES
+        }
         return;
     }
     // 16 runs per lane group and chunk: as few rounds as five chunks make, and no more chunks than fill them
@@ -2105,7 +2297,7 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         a.posK = f->posK; a.posKey = f->posKey; a.run_rank = f->run_rank; a.pos_thr = f->pos_thr; a.run_at = f->run_at; a.cls_run = f->cls_run; a.class_min = f->class_min; a.class_next = f->class_next; a.clsK = f->clsK; a.cls_bound = f->cls_bound;
         a.out_inst = out.inst; a.out_slack = out.slack; a.out_fallback = out.fallback;
         a.run_pad = f->run_pad; a.n_run = f->n_run; a.n_class = f->n_class; a.c_pad = f->c_pad;
-        a.max_len = f->max_len;
+        a.max_len = f->max_len; a.n_inst = f->n_inst;
         a.lines = f->lines; a.totals = rows.totals; a.row_len = rows.row_len; a.pos_of = f->pos_of;
         a.rest_cnt = f->rest_cnt;
         if (by_lines) {
@@ -2128,8 +2320,8 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         } else {
             ProfScope ps(f, kSelectRoute + off, s);
             if (!migrate && f->n_inst <= kFewInst) launch_few(f, src, out, s);
-            else if (migrate) launch_select<true>(f, a, by_class, by_lines, s);
-            else launch_select<false>(f, a, by_class, by_lines, s);
+            else if (migrate) launch_select<true>(f, a, by_class, by_lines, blended, s);
+            else launch_select<false>(f, a, by_class, by_lines, blended, s);
         }
     }
     if (out.T) launch_pairs(f, src, out, pairs, max_rows, s);
