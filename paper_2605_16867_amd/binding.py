@@ -1,5 +1,5 @@
-"""ctypes binding of libgoodroute: same names as the C interface, argument
-marshalling only.  Tensors are torch tensors on the GPU (device memory and the
+"""Binding of libgoodroute: same names as the C interface, argument
+marshalling only (ctypes; natively, by csrc/marshal.cpp, for the calls of a serving loop).  Tensors are torch tensors on the GPU (device memory and the
 current stream come from torch; every step of the path runs in the library's
 kernels).  There is no fallback: without the built library every call raises.
 """
@@ -11,6 +11,7 @@ from typing import Optional
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "csrc", "libgoodroute.so")
+MARSHAL_PATH = os.path.join(_HERE, "csrc", "goodroute_marshal.so")
 
 EXPORTS = ("gr_create", "gr_destroy", "gr_build_status", "gr_score_route", "gr_score_route_noalloc", "gr_score_route_cached", "gr_route_feedback",
            "gr_risk_scan", "gr_observe", "gr_set_blend", "gr_set_batch_cap", "gr_set_small_batch_pairs",
@@ -18,6 +19,7 @@ EXPORTS = ("gr_create", "gr_destroy", "gr_build_status", "gr_score_route", "gr_s
            "gr_profile_read_launches", "gr_profile_kernel_count", "gr_profile_kernel_name")
 
 _lib = None
+_marshal = None
 
 
 class GoodRouteError(RuntimeError):
@@ -78,6 +80,34 @@ def lib() -> C.CDLL:
     return _lib
 
 
+def marshal():
+    """The native marshalling, connected to the library's entry points."""
+    global _marshal
+    if _marshal is None:
+        l = lib()
+        if not os.path.exists(MARSHAL_PATH):
+            raise ImportError(f"{MARSHAL_PATH} is not built; run `python -m paper_2605_16867_amd.build`")
+        import importlib.machinery
+        import importlib.util
+
+        import torch  # noqa: F401  (its libraries come first)
+        loader = importlib.machinery.ExtensionFileLoader("goodroute_marshal", MARSHAL_PATH)
+        m = importlib.util.module_from_spec(importlib.util.spec_from_loader("goodroute_marshal", loader))
+        loader.exec_module(m)
+        m.connect(_check_slowly, *[C.cast(getattr(l, n), C.c_void_p).value for n in (
+            "gr_build_status", "gr_score_route", "gr_score_route_noalloc", "gr_score_route_cached", "gr_route_feedback",
+            "gr_risk_scan")])
+        _marshal = m
+    return _marshal
+
+
+def _check_slowly(t, code, name, n):
+    """What the native marshalling asks about a tensor that is not plainly right: its address, or an error."""
+    import torch
+    p = _dev(t, {"i": torch.int32, "f": torch.float32, "d": torch.float64, "B": torch.uint8}[code], name, n)
+    return None if p is None else p.value
+
+
 def strerror(code: int) -> str:
     return lib().gr_strerror(int(code)).decode()
 
@@ -109,7 +139,8 @@ class Fleet:
     def __init__(self, delta, alpha, beta, gamma, inst_class, max_entries_per_inst: int,
                  max_len: int, max_requests: int):
         import numpy as np
-        self._h = C.c_void_p()
+        self._h, self._at = C.c_void_p(), None
+        self._m = marshal()
         co = [np.ascontiguousarray(x, dtype=np.float64) for x in (delta, alpha, beta, gamma)]
         ic = np.ascontiguousarray(inst_class, dtype=np.int32)
         self.n_inst = int(ic.shape[0])
@@ -117,10 +148,11 @@ class Fleet:
                                *[c.ctypes.data_as(C.c_void_p) for c in co],
                                ic.ctypes.data_as(C.c_void_p), int(max_entries_per_inst),
                                int(max_len), int(max_requests)), "gr_create")
+        self._at = self._h.value
 
     def close(self) -> None:
         if self._h:
-            h, self._h = self._h, C.c_void_p()
+            h, self._h, self._at = self._h, C.c_void_p(), None
             _check(lib().gr_destroy(h), "gr_destroy")
 
     def __del__(self):
@@ -131,81 +163,45 @@ class Fleet:
 
     def gr_build_status(self, act_off, act_prompt, act_gen, act_rem, q_off, q_prompt, q_len,
                         out_act_finish, out_q_finish=None, out_d=None, out_rank=None) -> None:
-        import torch
-        i32, f32 = torch.int32, torch.float32
-        na, nq, M = act_prompt.numel(), q_prompt.numel(), self.n_inst
-        _check(lib().gr_build_status(
-            self._h, _dev(act_off, i32, "act_off", M + 1), _dev(act_prompt, i32, "act_prompt"),
-            _dev(act_gen, i32, "act_gen", na), _dev(act_rem, i32, "act_rem", na), na,
-            _dev(q_off, i32, "q_off", M + 1), _dev(q_prompt, i32, "q_prompt"),
-            _dev(q_len, i32, "q_len", nq), nq,
-            _dev(out_act_finish, f32, "out_act_finish", na), _dev(out_q_finish, f32, "out_q_finish", nq),
-            _dev(out_d, torch.float64, "out_d", M), _dev(out_rank, i32, "out_rank", M),
-            _stream()), "gr_build_status")
+        rc = self._m.build_status(self._at, self.n_inst, act_off, act_prompt, act_gen, act_rem, q_off, q_prompt, q_len,
+                                  out_act_finish, out_q_finish, out_d, out_rank)
+        if rc:
+            _check(rc, "gr_build_status")
 
     def gr_score_route(self, ctx0, pred_len, budget, out_inst, out_slack, exclude_inst=None,
                        out_fallback=None, out_T=None) -> None:
-        import torch
-        i32, f32 = torch.int32, torch.float32
-        n = ctx0.numel()
-        _check(lib().gr_score_route(
-            self._h, n, _dev(ctx0, i32, "ctx0"), _dev(pred_len, i32, "pred_len", n),
-            _dev(budget, f32, "budget", n), _dev(exclude_inst, i32, "exclude_inst", n),
-            _dev(out_inst, i32, "out_inst", n), _dev(out_slack, f32, "out_slack", n),
-            _dev(out_fallback, torch.uint8, "out_fallback", n),
-            _dev(out_T, f32, "out_T", n * self.n_inst), _stream()), "gr_score_route")
+        rc = self._m.score_route(self._at, self.n_inst, ctx0, pred_len, budget, exclude_inst, out_inst, out_slack,
+                                 out_fallback, out_T)
+        if rc:
+            _check(rc, "gr_score_route")
 
     def gr_score_route_noalloc(self, ctx0, pred_len, budget, out_inst, out_slack, exclude_inst=None,
                                out_fallback=None) -> None:
-        import torch
-        i32, f32 = torch.int32, torch.float32
-        n = ctx0.numel()
-        _check(lib().gr_score_route_noalloc(
-            self._h, n, _dev(ctx0, i32, "ctx0"), _dev(pred_len, i32, "pred_len", n),
-            _dev(budget, f32, "budget", n), _dev(exclude_inst, i32, "exclude_inst", n),
-            _dev(out_inst, i32, "out_inst", n), _dev(out_slack, f32, "out_slack", n),
-            _dev(out_fallback, torch.uint8, "out_fallback", n), _stream()), "gr_score_route_noalloc")
+        rc = self._m.score_route_noalloc(self._at, ctx0, pred_len, budget, exclude_inst, out_inst, out_slack, out_fallback)
+        if rc:
+            _check(rc, "gr_score_route_noalloc")
 
     def gr_score_route_cached(self, ctx0, pred_len, budget, hit_off, hit_inst, hit_len, out_inst, out_slack,
                               exclude_inst=None, out_fallback=None, out_T=None) -> None:
-        import torch
-        i32, f32 = torch.int32, torch.float32
-        n, nh = ctx0.numel(), hit_inst.numel()
-        _check(lib().gr_score_route_cached(
-            self._h, n, _dev(ctx0, i32, "ctx0"), _dev(pred_len, i32, "pred_len", n),
-            _dev(budget, f32, "budget", n), _dev(exclude_inst, i32, "exclude_inst", n),
-            _dev(hit_off, i32, "hit_off", n + 1), _dev(hit_inst, i32, "hit_inst"),
-            _dev(hit_len, i32, "hit_len", nh), nh,
-            _dev(out_inst, i32, "out_inst", n), _dev(out_slack, f32, "out_slack", n),
-            _dev(out_fallback, torch.uint8, "out_fallback", n),
-            _dev(out_T, f32, "out_T", n * self.n_inst), _stream()), "gr_score_route_cached")
+        rc = self._m.score_route_cached(self._at, self.n_inst, ctx0, pred_len, budget, exclude_inst, hit_off, hit_inst,
+                                        hit_len, out_inst, out_slack, out_fallback, out_T)
+        if rc:
+            _check(rc, "gr_score_route_cached")
 
     def gr_route_feedback(self, chunk: int, ctx0, pred_len, budget, out_inst, out_slack, exclude_inst=None,
                           out_fallback=None) -> None:
-        import torch
-        i32, f32 = torch.int32, torch.float32
-        n = ctx0.numel()
-        _check(lib().gr_route_feedback(
-            self._h, n, int(chunk), _dev(ctx0, i32, "ctx0"), _dev(pred_len, i32, "pred_len", n),
-            _dev(budget, f32, "budget", n), _dev(exclude_inst, i32, "exclude_inst", n),
-            _dev(out_inst, i32, "out_inst", n), _dev(out_slack, f32, "out_slack", n),
-            _dev(out_fallback, torch.uint8, "out_fallback", n), _stream()), "gr_route_feedback")
+        rc = self._m.route_feedback(self._at, int(chunk), ctx0, pred_len, budget, exclude_inst, out_inst, out_slack,
+                                    out_fallback)
+        if rc:
+            _check(rc, "gr_route_feedback")
 
     def gr_risk_scan(self, act_off, act_prompt, act_gen, act_rem_refreshed, q_off, q_prompt, q_len,
                      act_budget, out_flag, out_finish, out_target, out_target_slack,
                      out_n_flagged=None) -> None:
-        import torch
-        i32, f32 = torch.int32, torch.float32
-        na, nq, M = act_prompt.numel(), q_prompt.numel(), self.n_inst
-        _check(lib().gr_risk_scan(
-            self._h, _dev(act_off, i32, "act_off", M + 1), _dev(act_prompt, i32, "act_prompt"),
-            _dev(act_gen, i32, "act_gen", na), _dev(act_rem_refreshed, i32, "act_rem_refreshed", na), na,
-            _dev(q_off, i32, "q_off", M + 1), _dev(q_prompt, i32, "q_prompt"),
-            _dev(q_len, i32, "q_len", nq), nq,
-            _dev(act_budget, f32, "act_budget", na), _dev(out_flag, torch.uint8, "out_flag", na),
-            _dev(out_finish, f32, "out_finish", na), _dev(out_target, i32, "out_target", na),
-            _dev(out_target_slack, f32, "out_target_slack", na),
-            _dev(out_n_flagged, i32, "out_n_flagged", 1), _stream()), "gr_risk_scan")
+        rc = self._m.risk_scan(self._at, self.n_inst, act_off, act_prompt, act_gen, act_rem_refreshed, q_off, q_prompt, q_len,
+                               act_budget, out_flag, out_finish, out_target, out_target_slack, out_n_flagged)
+        if rc:
+            _check(rc, "gr_risk_scan")
 
     def gr_observe(self, weight: float, obs_wait=None, obs_prefill=None, obs_decode=None) -> None:
         import torch

@@ -28,6 +28,25 @@ def build_library(verbose: bool = False) -> str:
     return LIB
 
 
+MARSHAL = os.path.join(CSRC, "goodroute_marshal.so")
+
+
+def build_marshal(verbose: bool = False) -> str:
+    """The binding's argument marshalling (host code only, against torch's headers)."""
+    import sysconfig
+
+    import torch
+    at = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-D__HIP_PLATFORM_AMD__=1", "-I", sysconfig.get_path("include"), "-I", os.path.join(at, "include"),
+           "-I", os.path.join(at, "include", "torch", "csrc", "api", "include"), "-I", "/opt/rocm/include",
+           "-o", MARSHAL, os.path.join(CSRC, "marshal.cpp"), "-L", os.path.join(at, "lib"), "-ltorch_python", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return MARSHAL
+
+
 PROBE = os.path.join(CSRC, "probe_valu_issue")
 
 
@@ -42,4 +61,5 @@ def build_probe(verbose: bool = False) -> str:
 
 if __name__ == "__main__":
     build_library(verbose=True)
+    build_marshal(verbose=True)
     build_probe(verbose=True)
