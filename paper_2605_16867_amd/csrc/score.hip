@@ -1571,60 +1571,99 @@ struct HitArgs {
 // Eq. 2's hit prefix H_{r,g}, after the pass without it: a cached prefix of h
 // tokens on instance g takes delta_g * h off T(r,g) and changes nothing else,
 // so Alg. 1's answer can only move to an instance the request has a prefix on.
-// One thread per request that has any: the choice made without prefixes
+// kLanes threads per request that has any: the choice made without prefixes
 // against the request's own short list.  Feasible set: the earlier position in
 // capability order wins; otherwise the smallest T, ties to the lowest index
 // (the minimum over all instances is either the old one or among the hits,
 // because a hit only lowers its own pair).
+//
+// What bounds it is the chain of dependent reads: offsets, hit, position, value.  Every lane reads the
+// choice as it stands along with its own hit, so the two chains run side by side, and the hits of a
+// request run side by side too.  Status build and routing of 32 768 requests with two hits on average,
+// 1 024 instances: 69.0 us with a thread per request that takes the choice and its hits one after the other, 64.4 this way.
+// With out_T one thread takes a request: an instance named twice is written twice.
+constexpr int kHitLanes = 4;
+
+template <int kLanes>
 __global__ __launch_bounds__(kBlock) void k_hits(HitArgs a)
 {
-    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t r = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kLanes;
     if (r >= a.n) return;
     const int64_t h0 = min(max((int64_t)a.hit_off[r], (int64_t)0), a.n_hits);
     const int64_t h1 = min(max((int64_t)a.hit_off[r + 1], h0), a.n_hits);
-    if (h0 >= h1) return;
+    const int g0 = a.out_inst[r];
     const int L = min(max(a.pred_len[r], 0), a.max_len);
     const int ci = a.ctx0[r];
     const float c0 = (float)ci, Lf = (float)L, D = a.budget[r];
     const float Dc = D > FLT_MAX ? FLT_MAX : D;
     const int ex = a.exclude ? a.exclude[r] : -1;
+    if (h0 >= h1) return;
+    int64_t k = h0 + threadIdx.x % kLanes;
+    const auto hit = [&](int64_t at, int& g, int& h) {
+        const int64_t i = min(at, h1 - 1);
+        g = a.hit_inst[i];
+        h = min(max(a.hit_len[i], 0), max(ci, 0));
+    };
+    const auto place = [&](int g) { return a.pos_of[min(max(g, 0), a.n_inst - 1)]; };
     const float* __restrict__ rowE = a.memo + memo_at(row_at(a.len_row, L), 0, a.n_run);
-    const auto E_at = [&](int p) { return rowE[(size_t)(p / kMemoP) * kTile + p % kMemoP]; };
+    struct Pair { float2 K; unsigned long long key; float E; };
+    const auto pair_at = [&](int p) {
+        return Pair{a.posK[p], a.posKey[p], rowE[(size_t)(p / kMemoP) * kTile + p % kMemoP]};
+    };
+
+    int g, h;
+    hit(k, g, h);
+    const int p0 = place(g0);
+    int p = place(g);
+    const Pair b = pair_at(p0);
+    Pair v = pair_at(p);
 
     unsigned long long feasKey = ~0ull;
     int feasG = -1, anyG = -1;
     float feasT = 0.f, anyT = __builtin_inff();
-    const int g0 = a.out_inst[r];
     if (g0 >= 0) {
-        const int p0 = a.pos_of[g0];
-        const float T0 = fmaf(c0, kappa_of(a.posK[p0], Lf), E_at(p0));
-        if (T0 <= Dc) { feasKey = a.posKey[p0]; feasG = g0; feasT = T0; }
+        const float T0 = fmaf(c0, kappa_of(b.K, Lf), b.E);
+        if (T0 <= Dc) { feasKey = b.key; feasG = g0; feasT = T0; }
         anyG = g0; anyT = T0;
     }
-    for (int64_t k = h0; k < h1; ++k) {
-        const int g = a.hit_inst[k];
-        if (g < 0 || g >= a.n_inst) continue;
-        const int h = min(max(a.hit_len[k], 0), max(ci, 0));
-        const int p = a.pos_of[g];
-        const float2 dg = a.posK[p];
-        const float T = fmaf(-(float)h, dg.x, fmaf(c0, kappa_of(dg, Lf), E_at(p)));
-        if (a.out_T) {          // (an instance named twice: the longer prefix, i.e. the smaller T, stays)
-            float* t = a.out_T + (size_t)r * a.n_inst + g;
-            *t = fminf(*t, T);
-        }
-        if (g == ex) continue;
-        if (T <= Dc) {
-            const unsigned long long key = a.posKey[p];
-            if (feasG < 0 || key < feasKey || (key == feasKey && (g < feasG || (g == feasG && T < feasT)))) {
-                feasKey = key; feasG = g; feasT = T;
+    while (k < h1) {
+        const float T = fmaf(-(float)h, v.K.x, fmaf(c0, kappa_of(v.K, Lf), v.E));
+        const bool there = g >= 0 && g < a.n_inst;
+        if constexpr (kLanes == 1) {
+            if (a.out_T && there) {          // (an instance named twice: the longer prefix, i.e. the smaller T, stays)
+                float* t = a.out_T + (size_t)r * a.n_inst + g;
+                *t = fminf(*t, T);
             }
         }
-        if (T < anyT || (T == anyT && g < anyG)) { anyT = T; anyG = g; }
+        if (there && g != ex) {
+            if (T <= Dc &&
+                (feasG < 0 || v.key < feasKey || (v.key == feasKey && (g < feasG || (g == feasG && T < feasT))))) {
+                feasKey = v.key; feasG = g; feasT = T;
+            }
+            if (T < anyT || (T == anyT && g < anyG)) { anyT = T; anyG = g; }
+        }
+        k += kLanes;
+        if (k < h1) {
+            hit(k, g, h);
+            v = pair_at(place(g));
+        }
     }
+    // the lanes started from the same choice: the least of them in the same order
+#pragma unroll
+    for (int d = 1; d < kLanes; d *= 2) {
+        const unsigned long long key = __shfl_xor(feasKey, d);
+        const int fg = __shfl_xor(feasG, d), ag = __shfl_xor(anyG, d);
+        const float fT = __shfl_xor(feasT, d), aT = __shfl_xor(anyT, d);
+        if (fg >= 0 && (feasG < 0 || key < feasKey || (key == feasKey && (fg < feasG || (fg == feasG && fT < feasT))))) {
+            feasKey = key; feasG = fg; feasT = fT;
+        }
+        if (aT < anyT || (aT == anyT && ag < anyG)) { anyT = aT; anyG = ag; }
+    }
+    if (threadIdx.x % kLanes) return;
     const bool found = feasG >= 0;
-    const int g = found ? feasG : anyG;
-    a.out_inst[r] = g;
-    a.out_slack[r] = g >= 0 ? D - (found ? feasT : anyT) : 0.f;
+    const int best = found ? feasG : anyG;
+    a.out_inst[r] = best;
+    a.out_slack[r] = best >= 0 ? D - (found ? feasT : anyT) : 0.f;
     if (a.out_fallback) a.out_fallback[r] = !found;
 }
 
@@ -2339,7 +2378,9 @@ int launch_hits(gr_fleet* f, const ReqSrc& src, const int* hit_off, const int* h
     h.out_inst = out.inst; h.out_slack = out.slack; h.out_fallback = out.fallback; h.out_T = out.T;
     h.n = src.n; h.n_hits = n_hits; h.n_inst = f->n_inst; h.n_run = f->n_run; h.max_len = f->max_len;
     ProfScope ps(f, kHitsRoute, s);
-    hipLaunchKernelGGL(k_hits, dim3((unsigned)((src.n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, h);
+    const auto groups = [&](int lanes) { return dim3((unsigned)((src.n * lanes + kBlock - 1) / kBlock)); };
+    if (out.T || src.n > kLaunchThreads / kHitLanes) hipLaunchKernelGGL(k_hits<1>, groups(1), dim3(kBlock), 0, s, h);
+    else hipLaunchKernelGGL(k_hits<kHitLanes>, groups(kHitLanes), dim3(kBlock), 0, s, h);
     return hipGetLastError() == hipSuccess ? GR_OK : GR_ERR_HIP;
 }
 
