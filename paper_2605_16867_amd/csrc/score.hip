@@ -1787,6 +1787,7 @@ __global__ __launch_bounds__(kLanes <= 64 ? kBlock : kLanes) void k_direct(Direc
             for (int i = 0; i < kS; ++i)
                 if (i < s_words) w[u][i] = S[i];
             K[u] = a.instK[g[u]];
+            d[u] = a.hD[g[u]];
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
@@ -1812,7 +1813,6 @@ __global__ __launch_bounds__(kLanes <= 64 ? kBlock : kLanes) void k_direct(Direc
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             gh[u] = a.tabGH[gh_at(g[u], k[u], a.cap)];
-            d[u] = a.hD[g[u]];
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
