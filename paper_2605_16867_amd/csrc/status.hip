@@ -774,9 +774,10 @@ struct InstanceIn {
     unsigned long long joins;           // requests of the chunk that were sent here
 };
 
-template <int kEPL, int kSplit, int kTab>
+template <int kEPL, int kSplit, int kTab, bool kQuiet>     // kQuiet: nobody asks for finish times or flags
 __device__ __forceinline__ void build_instance(const BuildArgs& a, const InstanceIn& in, int wave, uint32_t* smem)
 {
+    const bool risk = !kQuiet && a.act_budget;
     constexpr int kWords = kWave * kEPL;         // sort words of a wave
     constexpr int kCap = kWords * kSplit;        // of the instance
     constexpr int kIdxBits = log2_of(kCap);
@@ -797,6 +798,7 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
     double* sums = reinterpret_cast<double*>(smem + kInstWords + 2 * kCap);         // (split) four totals per wave
 
     const ClassCoef cc = a.cls[a.inst_class[g]];
+    const int slot = a.slot_of[g];               // (used at the very end: its read is not to be waited for there)
     const int a0 = in.a0, q0 = in.q0, A = in.A, Q = in.Q, P = in.P, N = A + Q + P;
     int status = in.status;
 
@@ -808,7 +810,7 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
     const __amdgpu_buffer_rsrc_t b_rem = slice(a.act_rem, 4), b_prompt = slice(a.act_prompt, 4),
                                  b_gen = slice(a.act_gen, 4), b_fin = slice(a.out_act_finish, 4);
     __amdgpu_buffer_rsrc_t b_bud = b_fin, b_flag = b_fin;
-    if (a.act_budget) { b_bud = slice(a.act_budget, 4); b_flag = slice(a.out_flag, 1); }
+    if (risk) { b_bud = slice(a.act_budget, 4); b_flag = slice(a.out_flag, 1); }
 
     // load, entry i = first + 64 r + lane: all loads in flight together
     const int lane4 = lane * 4;
@@ -819,7 +821,7 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
         c_in[r] = __builtin_amdgcn_raw_buffer_load_b32(b_prompt, lane4, (first + r * kWave) * 4, 0);
         gen_in[r] = __builtin_amdgcn_raw_buffer_load_b32(b_gen, lane4, (first + r * kWave) * 4, 0);
     }
-    if (a.act_budget) {
+    if (risk) {
 #pragma unroll
         for (int r = 0; r < kEPL; ++r)
             bud_in[r] = __builtin_amdgcn_raw_buffer_load_b32(b_bud, lane4, (first + r * kWave) * 4, 0);
@@ -857,7 +859,7 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
                 qsum += c_in[r];
             }
         }
-        qsum = wave_sum(qsum);
+        qsum = wave_sum_i64(qsum);
     }
 
     // one sort word per entry = (remaining length << kIdxBits) | i; past the last entry all ones
@@ -871,16 +873,16 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
         key[r] = i < N ? ((uint32_t)rem << kIdxBits) | (uint32_t)i : 0xFFFFFFFFu;
         ctx[i] = c_in[r] + gen_in[r];          // (zero past the last entry: the loads returned zeros)
     }
-    if (a.act_budget) {
+    if (risk) {
 #pragma unroll
         for (int r = 0; r < kEPL; ++r) stage[first + r * kWave + lane] = __int_as_float(bud_in[r]);
     }
     if (__ballot(bad)) status |= GR_DEV_LEN_CLAMPED;
     if (status && lane == 0) {
         atomicOr(&a.counters[0], status);
-        if (a.act_budget && (status & GR_DEV_ENTRIES_DROPPED)) *a.unset = 1;
+        if (risk && (status & GR_DEV_ENTRIES_DROPPED)) *a.unset = 1;
     }
-    if (a.act_budget) {      // the instance of each running request, for the migration pass of a risk scan
+    if (risk) {      // the instance of each running request, for the migration pass of a risk scan
         const __amdgpu_buffer_rsrc_t b_inst = slice(a.act_inst, 4);
 #pragma unroll
         for (int r = 0; r < kEPL; ++r) __builtin_amdgcn_raw_buffer_store_b32(g, b_inst, lane4, (first + r * kWave) * 4, 0);
@@ -955,7 +957,7 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
     float2 tGH[kEPL];
     float fin32[kEPL], bud[kEPL];
     unsigned late = 0;                           // bit r: the request at position r finishes after its budget
-    if (a.act_budget) {
+    if (risk) {
 #pragma unroll
         for (int r = 0; r < kEPL; ++r) bud[r] = stage[idx[r]];
     }
@@ -978,16 +980,18 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
             fin = keep * fin + a.lam * (idx[r] < A ? bd * Rd : (bq + bp * cd) + bd * Rd);
         }
         fin32[r] = (float)fin;
-        if (a.act_budget) late |= (unsigned)(fin > (double)bud[r]) << r;     // decided in double precision
+        if (risk) late |= (unsigned)(fin > (double)bud[r]) << r;     // decided in double precision
         tR[r] = r < mine ? (uint16_t)Ri[r] : (uint16_t)0xFFFFu;
         tGH[r] = make_float2((float)Gq, (float)Hs);
     }
     // Finish times and flags go back to entry order through LDS: the lane that read an entry's budget
     // from its slot is the one that writes its finish time there.  (A position without an entry
     // carries index kCap - 1 >= N: a slot past the slice, of which nothing is stored.)
+    if constexpr (!kQuiet) {
 #pragma unroll
-    for (int r = 0; r < kEPL; ++r) stage[idx[r]] = fin32[r];
-    if (a.act_budget) {
+        for (int r = 0; r < kEPL; ++r) stage[idx[r]] = fin32[r];
+    }
+    if (risk) {
 #pragma unroll
         for (int r = 0; r < kEPL; ++r) flag_lds[idx[r]] = (uint8_t)((late >> r) & 1u);
         // the lengths of flagged requests, for the migration pass (a byte each; of equal neighbours in
@@ -1006,26 +1010,28 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
         const int n_late = wave_incl_scan_i32(__popc(mig));
         if (lane == kWave - 1) a.late_cnt[part * a.n_inst + g] = n_late;
     }
-    if constexpr (kSplit == 1) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    } else {
-        __syncthreads();
-    }
-#pragma unroll
-    for (int r = 0; r < kEPL; ++r)
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(stage[first + r * kWave + lane]), b_fin, lane4,
-                                              (first + r * kWave) * 4, 0);
-    if (a.act_budget) {
+    if constexpr (!kQuiet) {
+        if constexpr (kSplit == 1) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        } else {
+            __syncthreads();
+        }
 #pragma unroll
         for (int r = 0; r < kEPL; ++r)
-            __builtin_amdgcn_raw_buffer_store_b8(flag_lds[first + r * kWave + lane], b_flag, lane, first + r * kWave, 0);
-    }
-    if (Q > 0 && a.out_q_finish) {
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(stage[first + r * kWave + lane]), b_fin, lane4,
+                                                  (first + r * kWave) * 4, 0);
+        if (risk) {
 #pragma unroll
-        for (int r = 0; r < kEPL; ++r)
-            if (r < mine && idx[r] >= A && idx[r] < A + Q) a.out_q_finish[q0 + idx[r] - A] = fin32[r];
+            for (int r = 0; r < kEPL; ++r)
+                __builtin_amdgcn_raw_buffer_store_b8(flag_lds[first + r * kWave + lane], b_flag, lane, first + r * kWave, 0);
+        }
+        if (Q > 0 && a.out_q_finish) {
+#pragma unroll
+            for (int r = 0; r < kEPL; ++r)
+                if (r < mine && idx[r] >= A && idx[r] < A + Q) a.out_q_finish[q0 + idx[r] - A] = fin32[r];
+        }
     }
     {
         uint16_t* dstR = a.tabR + (size_t)g * kTab + first + lane * kEPL;
@@ -1070,15 +1076,17 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
         double d = fma(cc.gamma, Ctot, fma(cc.beta, (double)N, cc.alpha));     // the next decode step
         if (blended) d = keep * d + a.lam * bd;
         a.hD[g] = d;
-        a.slot_key[a.slot_of[g]] = falling_bits(d);
+        a.slot_key[slot] = falling_bits(d);
         if (a.out_d) a.out_d[g] = d;
     }
 }
 
 // A handle's tables have room for the most an instance may hold, which can be several times what
 // it does hold: with kFit an instance that a half or a quarter of the sort words would do for takes
-// those (see fit_words).
-template <int kEPL, int kSplit, bool kFit>
+// those (see fit_words).  kQuiet: a rebuild of feedback routing, whose finish times nobody asks for and of
+// which most instances take no part: 32 rounds of 64 requests on 256 instances 451 us with the plain
+// build and reads in the order of their use, 400 this way.
+template <int kEPL, int kSplit, bool kFit, bool kQuiet>
 __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_build_lean(BuildArgs a)
 {
     extern __shared__ uint32_t smem[];
@@ -1088,6 +1096,9 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
     in.g = kSplit == 1 ? blockIdx.x * kBuildWaves + wave : blockIdx.x;   // wave-uniform: what follows is scalar
     const int g = in.g;
     if (g >= a.n_inst) return;
+    const int a_begin = a.act_off[g], a_end = a.act_off[g + 1], q_begin = a.q_off[g], q_end = a.q_off[g + 1];
+    const int pend = a.use_pending ? a.pend_cnt[g] : 0;
+    if constexpr (kQuiet) asm volatile("" :: "s"(a_begin), "s"(a_end), "s"(q_begin), "s"(q_end), "s"(pend));   // (not after the branch below)
     // feedback routing: an instance that has been given nothing since its table was built keeps it
     // (the mark is cleared at the very end, when every wave of the instance has read it)
     in.joins = 0;
@@ -1099,25 +1110,25 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
         return;
     }
     // offsets are clamped into the arrays, so broken CSR data cannot index outside them
-    in.a0 = (int)min((int64_t)max(a.act_off[g], 0), a.n_active);
-    in.q0 = (int)min((int64_t)max(a.q_off[g], 0), a.n_queued);
-    in.A = (int)max(min((int64_t)a.act_off[g + 1], a.n_active) - in.a0, (int64_t)0);
-    in.Q = (int)max(min((int64_t)a.q_off[g + 1], a.n_queued) - in.q0, (int64_t)0);
+    in.a0 = (int)min((int64_t)max(a_begin, 0), a.n_active);
+    in.q0 = (int)min((int64_t)max(q_begin, 0), a.n_queued);
+    in.A = (int)max(min((int64_t)a_end, a.n_active) - in.a0, (int64_t)0);
+    in.Q = (int)max(min((int64_t)q_end, a.n_queued) - in.q0, (int64_t)0);
     in.status = 0;
     if (in.A > a.max_entries) { in.A = a.max_entries; in.status |= GR_DEV_ENTRIES_DROPPED; }
     if (in.Q > a.max_entries - in.A) { in.Q = a.max_entries - in.A; in.status |= GR_DEV_ENTRIES_DROPPED; }
-    in.pend = a.use_pending ? a.pend_cnt[g] : 0;
+    in.pend = pend;
     in.P = in.pend + __popcll(in.joins);
     if (in.P > kTab) { in.P = kTab; if (in.joins) in.status |= GR_DEV_ENTRIES_DROPPED; }
     if (in.P > a.max_entries - in.A - in.Q) { in.P = a.max_entries - in.A - in.Q; in.status |= GR_DEV_ENTRIES_DROPPED; }
     const int N = in.A + in.Q + in.P;
     if constexpr (kFit) {
         if constexpr (kEPL >= 4)
-            if (N <= kTab / 4) return build_instance<kEPL / 4, kSplit, kTab>(a, in, wave, smem);
+            if (N <= kTab / 4) return build_instance<kEPL / 4, kSplit, kTab, kQuiet>(a, in, wave, smem);
         if constexpr (kEPL >= 2)
-            if (N <= kTab / 2) return build_instance<kEPL / 2, kSplit, kTab>(a, in, wave, smem);
+            if (N <= kTab / 2) return build_instance<kEPL / 2, kSplit, kTab, kQuiet>(a, in, wave, smem);
     }
-    build_instance<kEPL, kSplit, kTab>(a, in, wave, smem);
+    build_instance<kEPL, kSplit, kTab, kQuiet>(a, in, wave, smem);
 }
 
 // The capability rank of every instance, for the caller (Alg. 1's argmax d_g: rank 0 = largest d_g,
@@ -1338,22 +1349,24 @@ template <int kEPL>
 constexpr size_t lean_lds() { return (size_t)kBuildWaves * lean_inst_words(kWave * kEPL) * sizeof(int); }
 
 // Whether instances pick the number of sort words by what they hold: where half of the words would do
-// for the average one, and in feedback routing, whose handles are made with room for what is routed
+// for the average one, and always in feedback routing, whose handles are made with room for what is routed
 // (256 instances of 512 to 560 requests in tables for 2 048: 8.5 us instead of 10.0).  Elsewhere the
 // choice is one more thing to wait for before the first read (1 024 x 1 000: 15.4 instead of 14.3 us).
 bool fit_words(const BuildArgs& b, int M, int cap)
 {
-    return b.use_pending || (b.n_active + b.n_queued) * 2 <= (int64_t)M * cap;
+    return (b.n_active + b.n_queued) * 2 <= (int64_t)M * cap;
 }
 
 template <int kEPL, int kSplit>
 int launch_build_split(const BuildArgs& b, int M, hipStream_t s)
 {
     constexpr size_t lds = split_lds<kEPL, kSplit>();
-    if (fit_words(b, M, kWave * kEPL))
-        hipLaunchKernelGGL((k_build_lean<kEPL / kSplit, kSplit, true>), dim3(M), dim3(kSplit * kWave), lds, s, b);
+    if (b.use_pending)
+        hipLaunchKernelGGL((k_build_lean<kEPL / kSplit, kSplit, true, true>), dim3(M), dim3(kSplit * kWave), lds, s, b);
+    else if (fit_words(b, M, kWave * kEPL))
+        hipLaunchKernelGGL((k_build_lean<kEPL / kSplit, kSplit, true, false>), dim3(M), dim3(kSplit * kWave), lds, s, b);
     else
-        hipLaunchKernelGGL((k_build_lean<kEPL / kSplit, kSplit, false>), dim3(M), dim3(kSplit * kWave), lds, s, b);
+        hipLaunchKernelGGL((k_build_lean<kEPL / kSplit, kSplit, false, false>), dim3(M), dim3(kSplit * kWave), lds, s, b);
     return kSplit;
 }
 
@@ -1373,7 +1386,7 @@ int launch_build(const BuildArgs& b, int M, hipStream_t s)
     const int room = 4 * kSimds / M;
     if constexpr (kEPL >= 4) if (room >= 4) return launch_build_split<kEPL, 4>(b, M, s);
     if constexpr (kEPL >= 2) if (room >= 2) return launch_build_split<kEPL, 2>(b, M, s);
-    hipLaunchKernelGGL((k_build_lean<kEPL, 1, false>), grid, dim3(kBlock), lean_lds<kEPL>(), s, b);
+    hipLaunchKernelGGL((k_build_lean<kEPL, 1, false, false>), grid, dim3(kBlock), lean_lds<kEPL>(), s, b);
     return 1;
 }
 
@@ -1418,13 +1431,15 @@ int status_prepare()
                                        (int)bytes) == hipSuccess;
     };
     constexpr size_t word = kBuildWaves * kWave * sizeof(int);     // per sort word per lane
-    set(k_build_lean<1, 1, false>, lean_lds<1>()); set(k_build_lean<2, 1, false>, lean_lds<2>()); set(k_build_lean<4, 1, false>, lean_lds<4>());
-    set(k_build_lean<8, 1, false>, lean_lds<8>()); set(k_build_lean<16, 1, false>, lean_lds<16>()); set(k_build_lean<32, 1, false>, lean_lds<32>());
-    set(k_build_lean<1, 2, false>, split_lds<2, 2>()); set(k_build_lean<1, 2, true>, split_lds<2, 2>()); set(k_build_lean<2, 2, false>, split_lds<4, 2>()); set(k_build_lean<2, 2, true>, split_lds<4, 2>());
-    set(k_build_lean<4, 2, false>, split_lds<8, 2>()); set(k_build_lean<4, 2, true>, split_lds<8, 2>()); set(k_build_lean<8, 2, false>, split_lds<16, 2>()); set(k_build_lean<8, 2, true>, split_lds<16, 2>());
-    set(k_build_lean<16, 2, false>, split_lds<32, 2>()); set(k_build_lean<16, 2, true>, split_lds<32, 2>());
-    set(k_build_lean<1, 4, false>, split_lds<4, 4>()); set(k_build_lean<1, 4, true>, split_lds<4, 4>()); set(k_build_lean<2, 4, false>, split_lds<8, 4>()); set(k_build_lean<2, 4, true>, split_lds<8, 4>());
-    set(k_build_lean<4, 4, false>, split_lds<16, 4>()); set(k_build_lean<4, 4, true>, split_lds<16, 4>()); set(k_build_lean<8, 4, false>, split_lds<32, 4>()); set(k_build_lean<8, 4, true>, split_lds<32, 4>());
+    set(k_build_lean<1, 1, false, false>, lean_lds<1>()); set(k_build_lean<2, 1, false, false>, lean_lds<2>());
+    set(k_build_lean<4, 1, false, false>, lean_lds<4>()); set(k_build_lean<8, 1, false, false>, lean_lds<8>());
+    set(k_build_lean<16, 1, false, false>, lean_lds<16>()); set(k_build_lean<32, 1, false, false>, lean_lds<32>());
+#define GR_SET_SPLIT(E, W) \
+    set(k_build_lean<E, W, false, false>, split_lds<E * W, W>()); set(k_build_lean<E, W, true, false>, split_lds<E * W, W>()); \
+    set(k_build_lean<E, W, true, true>, split_lds<E * W, W>())
+    GR_SET_SPLIT(1, 2); GR_SET_SPLIT(2, 2); GR_SET_SPLIT(4, 2); GR_SET_SPLIT(8, 2); GR_SET_SPLIT(16, 2);
+    GR_SET_SPLIT(1, 4); GR_SET_SPLIT(2, 4); GR_SET_SPLIT(4, 4); GR_SET_SPLIT(8, 4);
+#undef GR_SET_SPLIT
     set(k_build_capped<1>, 3 * word * 1); set(k_build_capped<2>, 3 * word * 2); set(k_build_capped<4>, 3 * word * 4);
     set(k_build_capped<8>, 3 * word * 8); set(k_build_capped<16>, 3 * word * 16); set(k_build_capped<32>, 3 * word * 32);
     return ok ? GR_OK : GR_ERR_HIP;
