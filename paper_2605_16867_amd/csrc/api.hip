@@ -12,7 +12,7 @@ const char* const kKernelNames[kNumKernels] = {
     "k_build", "k_rank",
     "k_mark<route>", "k_scan<route>", "k_memo<route>", "k_class<route>", "k_lines<route>", "k_select<route>",
     "k_scan<migrate>", "k_memo<migrate>", "k_class<migrate>", "k_lines<migrate>", "k_select<migrate>",
-    "k_hits<route>", "k_pairs<route>", "k_direct", "k_direct_merge"};
+    "k_hits<route>", "k_pairs<route>", "k_direct", "k_direct_merge", "k_feedback"};
 
 template <typename T>
 bool dev_alloc(T** p, size_t n)
@@ -146,7 +146,9 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
         dev_alloc(&f->memo, (size_t)f->row_cap * f->m_pos) && dev_alloc(&f->grp_min, (size_t)f->row_cap * f->run_pad) &&
         dev_alloc(&f->run_k, f->n_run) && dev_alloc(&f->run_rank, f->n_run) && dev_alloc(&f->run_at, f->n_run) && dev_alloc(&f->pos_thr, f->m_pos) && dev_alloc(&f->class_min, (size_t)f->row_cap * f->c_pad) &&
         dev_alloc(&f->cls_bound, n_class) && dev_alloc(&f->class_next, (size_t)f->row_cap * n_class) &&
-        dev_alloc(&f->rest_cnt, kRestParts * kRestStride) && dev_alloc(&f->lines, (size_t)f->row_cap * kRanges * 2) && dev_alloc(&f->turned, (size_t)f->turned_rows * n_inst) && dev_alloc(&f->direct_part, (size_t)kDirectParts);
+        dev_alloc(&f->rest_cnt, kRestParts * kRestStride) && dev_alloc(&f->lines, (size_t)f->row_cap * kRanges * 2) && dev_alloc(&f->turned, (size_t)f->turned_rows * n_inst) && dev_alloc(&f->direct_part, (size_t)kDirectParts) &&
+        (n_inst > kFeedInst || (dev_alloc(&f->feed_T, (size_t)2 * n_inst * kWave) && dev_alloc(&f->feed_met, (size_t)2 * n_inst) &&
+                                dev_alloc(&f->feed_key, (size_t)2 * n_inst)));
     if (!ok) { gr_destroy(f); return GR_ERR_NOMEM; }
 
     bool sent = true;
@@ -194,7 +196,7 @@ int gr_destroy(gr_fleet* f)
     void* ptrs[] = {f->cls, f->inst_class, f->tabR, f->tabGH, f->hD, f->emaQ, f->emaP, f->emaD, f->instK, f->tabS,
                     f->clsK, f->slot_inst, f->slot_of, f->slot_key, f->run_cls, f->cls_run, f->order, f->pos_of, f->posK, f->posKey, f->run_head, f->act_inst, f->pend_cnt, f->commit_mark, f->pend_touched, f->pend_prompt, f->pend_len,
                     f->scratch_finish, f->batch_cap, f->counters, f->seen, f->late_cnt, f->row_len,
-                    f->len_row, f->totals, f->dense_totals, f->memo, f->grp_min, f->run_k, f->run_rank, f->run_at, f->pos_thr, f->class_min, f->cls_bound, f->class_next, f->rest_cnt, f->lines, f->turned, f->direct_part};
+                    f->len_row, f->totals, f->dense_totals, f->memo, f->grp_min, f->run_k, f->run_rank, f->run_at, f->pos_thr, f->class_min, f->cls_bound, f->class_next, f->rest_cnt, f->lines, f->turned, f->feed_T, f->feed_met, f->feed_key, f->direct_part};
     int rc = GR_OK;
     for (void* p : ptrs)
         if (p && hipFree(p) != hipSuccess) rc = GR_ERR_HIP;
@@ -308,6 +310,14 @@ int gr_route_feedback(gr_fleet* f, int64_t n_req, int64_t chunk, const int32_t* 
     // Instances that were given nothing keep their tables, unless those may be from an earlier blend
     // weight or earlier caps: then the first rebuild takes every instance.
     bool current = TableAccount(f, s).view(f).current;
+    if (feedback_by_round(f, std::min(chunk, n_req))) {
+        FeedbackIn r{};
+        r.n = n_req; r.chunk = (int)std::min(chunk, n_req);
+        r.ctx0 = ctx0; r.pred_len = pred_len; r.exclude = exclude_inst; r.budget = budget;
+        r.out_inst = out_inst; r.out_slack = out_slack; r.out_fallback = out_fallback;
+        r.current = current;
+        return launch_feedback(f, in, r, s);
+    }
     for (int64_t s0 = 0; s0 < n_req; s0 += chunk) {
         const int64_t n = n_req - s0 < chunk ? n_req - s0 : chunk;
         ReqSrc src{};

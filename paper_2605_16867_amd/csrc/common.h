@@ -41,6 +41,7 @@ constexpr int kDirectMax = 4096;   // most requests of a batch that a caller has
 constexpr int64_t kDirectPairs = int64_t(1) << 19;   // pairs of a batch that is where the sizes decide (see pair_by_pair)
 constexpr int64_t kDirectInfinite = int64_t(1) << 18;   // pairs (of whole 128 instances) up to which infinite latencies count there
 constexpr int kDirectSpan = 4096;  // instances that one workgroup takes of a request scored pair by pair
+constexpr int kFeedInst = 512;     // most instances of a fleet whose feedback routing is a launch per round
 constexpr int kDirectParts = 16384;  // room for the selections of such parts
 constexpr int64_t kDenseValues = int64_t(1) << 23;   // values of a table that has a row for every length
 constexpr int kMemoP = 16;         // positions of a run of the class order
@@ -92,7 +93,7 @@ struct DirectPart {
 
 enum KernelId {
     kBuild = 0, kRank, kMarkRoute, kScanRoute, kMemoRoute, kClassRoute, kLinesRoute, kSelectRoute,
-    kScanMigrate, kMemoMigrate, kClassMigrate, kLinesMigrate, kSelectMigrate, kHitsRoute, kPairsRoute, kDirect, kDirectMerge,
+    kScanMigrate, kMemoMigrate, kClassMigrate, kLinesMigrate, kSelectMigrate, kHitsRoute, kPairsRoute, kDirect, kDirectMerge, kFeedback,
     kNumKernels
 };
 
@@ -220,6 +221,11 @@ struct gr_fleet {
     bool recorded = false, blend_recorded = false;
     int* pend_touched = nullptr;   // [M] 1: given requests since its table was built
     int64_t small_batch_pairs = -1;   // largest batch, in pairs, scored pair by pair; -1: by the sizes (see pair_by_pair)
+    // feedback routing, a launch per round (null on fleets of more than kFeedInst instances), two of each in turn: what
+    // every instance offers the requests of a chunk
+    uint32_t* feed_T = nullptr;             // [2][M][kWave] latency as an integer of the same order; all ones: not allowed
+    unsigned long long* feed_met = nullptr; // [2][M] bit j: request j's deadline is met
+    unsigned long long* feed_key = nullptr; // [2][M] d_g as an integer that falls with it
     gr::DirectPart* direct_part = nullptr;       // [kDirectParts] selections of the parts of a wide fleet, scored pair by pair
 };
 
@@ -287,6 +293,20 @@ struct OrderArgs {
 int status_prepare();
 int launch_ranks(gr_fleet* f, int* out_rank, hipStream_t s);
 int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s);
+// A whole feedback routing in chunks of up to kWave requests, a launch per round (see k_feedback).  `in`: the status inputs to
+// rebuild from; `current`: instances that are given nothing keep their tables.
+struct FeedbackIn {
+    int64_t n;
+    int chunk;
+    const int *ctx0, *pred_len, *exclude;
+    const float* budget;
+    int* out_inst;
+    float* out_slack;
+    uint8_t* out_fallback;
+    bool current, finite;
+};
+bool feedback_by_round(const gr_fleet* f, int64_t chunk);
+int launch_feedback(gr_fleet* f, const StatusIn& in, const FeedbackIn& r, hipStream_t s);
 int launch_commit(gr_fleet* f, int64_t n, const int* inst, const int* ctx0, const int* pred_len, hipStream_t s);
 int launch_ema(gr_fleet* f, double w, const float* s_q, const float* s_p, const float* s_d, hipStream_t s);
 
@@ -294,6 +314,8 @@ int launch_ema(gr_fleet* f, double w, const float* s_q, const float* s_p, const 
 int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& out, hipStream_t s,
                  bool small_batch_ok = false);
 bool needs_marks(const gr_fleet* f, int64_t n);      // a risk scan's table pass makes a list of lengths
+bool pair_by_pair(const gr_fleet* f, int64_t n);
+bool pairs_finite(const gr_fleet* f, int64_t n);     // pair by pair an infinite latency of a routing batch is none
 int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream_t s);
 int launch_hits(gr_fleet* f, const ReqSrc& src, const int* hit_off, const int* hit_inst, const int* hit_len,
                 int64_t n_hits, const ScoreOut& out, hipStream_t s);
@@ -355,6 +377,43 @@ __device__ inline unsigned long long falling_bits(double v)
 {
     const unsigned long long b = (unsigned long long)__double_as_longlong(v + 0.0);
     return ~(b ^ ((b >> 63) ? ~0ull : 0x8000000000000000ull));
+}
+
+// how many of the 16-bit lengths in `w` are at most L
+__device__ inline int count_upto(const uint4& w, uint32_t L)
+{
+    const uint32_t lim = (L << 16) | 0xFFFFu;
+    int c = 0;
+    c += ((w.x & 0xFFFFu) <= L) + (w.x <= lim) + ((w.y & 0xFFFFu) <= L) + (w.y <= lim);
+    c += ((w.z & 0xFFFFu) <= L) + (w.z <= lim) + ((w.w & 0xFFFFu) <= L) + (w.w <= lim);
+    return c;
+}
+
+// a float as an unsigned integer of the same order
+__device__ inline uint32_t ordered_bits(float v)
+{
+    const uint32_t b = __float_as_uint(v);
+    return b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u);
+}
+
+__device__ inline float from_ordered_bits(uint32_t u)
+{
+    return __uint_as_float(u ^ ((u >> 31) ? 0x80000000u : 0xFFFFFFFFu));
+}
+
+// kappa = delta + gamma * L, the same instruction wherever a pair's latency is formed
+__device__ inline float kappa_of(float2 dg, float Lf) { return fmaf(dg.y, Lf, dg.x); }
+
+__device__ inline DirectPart no_selection() { return DirectPart{~0u, ~0u, ~0u, ~0u, ~0u, ~0u}; }
+
+__device__ inline void take_better(DirectPart& b, const DirectPart& o)
+{
+    // (values, not references: a choice between two structs' members keeps both in memory)
+    const uint32_t oT = o.any_T, og = o.any_g, oh = o.d_hi, ol = o.d_lo, ofg = o.g, ofT = o.T;
+    const uint32_t bT = b.any_T, bg = b.any_g, bh = b.d_hi, bl = b.d_lo, bfg = b.g, bfT = b.T;
+    const bool less = oT < bT || (oT == bT && og < bg);
+    const bool better = oh < bh || (oh == bh && (ol < bl || (ol == bl && ofg < bfg)));
+    b = DirectPart{less ? oT : bT, less ? og : bg, better ? oh : bh, better ? ol : bl, better ? ofg : bfg, better ? ofT : bfT};
 }
 
 constexpr int kRankPer = 8;      // instances that kRankWaves waves rank together

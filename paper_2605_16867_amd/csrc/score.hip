@@ -183,16 +183,6 @@ __device__ __forceinline__ void count_flagged(const CountArgs& a, int threads, i
 // The row of a length: its place in the list, or the length itself where every length has a row.
 __device__ inline int row_at(const uint16_t* len_row, int L) { return len_row ? (int)len_row[L] : L; }
 
-// how many of the 16-bit lengths in `w` are at most L
-__device__ inline int count_upto(const uint4& w, uint32_t L)
-{
-    const uint32_t lim = (L << 16) | 0xFFFFu;
-    int c = 0;
-    c += ((w.x & 0xFFFFu) <= L) + (w.x <= lim) + ((w.y & 0xFFFFu) <= L) + (w.y <= lim);
-    c += ((w.z & 0xFFFFu) <= L) + (w.z <= lim) + ((w.w & 0xFFFFu) <= L) + (w.w <= lim);
-    return c;
-}
-
 // ------------------------------------------------------------------ E per length and position
 struct MemoArgs {
     int* totals;
@@ -606,22 +596,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMemoPer
     }
 }
 
-// a float as an unsigned integer of the same order
-__device__ inline uint32_t ordered_bits(float v)
-{
-    const uint32_t b = __float_as_uint(v);
-    return b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u);
-}
-
-__device__ inline float from_ordered_bits(uint32_t u)
-{
-    return __uint_as_float(u ^ ((u >> 31) ? 0x80000000u : 0xFFFFFFFFu));
-}
-
 // ------------------------------------------------------------------ Alg. 1, runs first
-// kappa = delta + gamma * L, the same instruction wherever a pair's latency is formed
-__device__ inline float kappa_of(float2 dg, float Lf) { return fmaf(dg.y, Lf, dg.x); }
-
 constexpr int kGroup = 16;       // lanes that take a request together: a run's positions, or 16 runs
 static_assert(kGroup == kMemoP, "a lane per position of a run");
 
@@ -1684,18 +1659,6 @@ struct DirectArgs {
     CountArgs count;         // a risk scan: by an extra workgroup
 };
 
-__device__ inline DirectPart no_selection() { return DirectPart{~0u, ~0u, ~0u, ~0u, ~0u, ~0u}; }
-
-__device__ inline void take_better(DirectPart& b, const DirectPart& o)
-{
-    // (values, not references: a choice between two structs' members keeps both in memory)
-    const uint32_t oT = o.any_T, og = o.any_g, oh = o.d_hi, ol = o.d_lo, ofg = o.g, ofT = o.T;
-    const uint32_t bT = b.any_T, bg = b.any_g, bh = b.d_hi, bl = b.d_lo, bfg = b.g, bfT = b.T;
-    const bool less = oT < bT || (oT == bT && og < bg);
-    const bool better = oh < bh || (oh == bh && (ol < bl || (ol == bl && ofg < bfg)));
-    b = DirectPart{less ? oT : bT, less ? og : bg, better ? oh : bh, better ? ol : bl, better ? ofg : bfg, better ? ofT : bfT};
-}
-
 // The best of the lanes' selections, word by word: a minimum and, among the lanes that hold it, the
 // least of the next word (a minimum through DPP is one instruction per step; comparing whole
 // selections pairwise takes twenty).
@@ -2067,10 +2030,17 @@ int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream
 //   2 048 x 256                   19.4 / 11.5   1 024 x 256 19.2 / 7.9;  1 024 x 1 024 20.3 / 24.9
 // and a risk scan with its status build, 32 x 512 requests 23.6 / 11.2, 64 x 128 18.9 / 10.5, 16 x 1 000 29.1 / 13.0.
 // (A request takes 16 lanes at least.)
-static bool pair_by_pair(const gr_fleet* f, int64_t n)
+bool pair_by_pair(const gr_fleet* f, int64_t n)
 {
     if (f->small_batch_pairs >= 0) return n <= kDirectMax && n * f->m_pad <= f->small_batch_pairs;
     return n * std::max(f->n_inst, kGroup) <= kDirectPairs;
+}
+
+// (small routing batches have always taken infinite latencies for latencies)
+bool pairs_finite(const gr_fleet* f, int64_t n)
+{
+    const bool small = n <= kDirectMax && n * f->m_pad <= kDirectInfinite;
+    return f->small_batch_pairs < 0 && !small;
 }
 
 constexpr int64_t kByClassMin = int64_t(1) << 17;      // requests from which the classes are looked at first
@@ -2230,10 +2200,8 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         return hipGetLastError() == hipSuccess ? GR_OK : GR_ERR_HIP;
     }
     if (small_batch_ok && pair_by_pair(f, n)) {
-        // (small routing batches have always taken infinite latencies for latencies here)
-        const bool small = n <= kDirectMax && n * f->m_pad <= kDirectInfinite;
         return migrate ? launch_pair_by_pair<true>(f, src, out, true, s)
-                       : launch_pair_by_pair<false>(f, src, out, f->small_batch_pairs < 0 && !small, s);
+                       : launch_pair_by_pair<false>(f, src, out, pairs_finite(f, n), s);
     }
     // The class order of the current status, if nobody is known to have made it, comes first: always while
     // the stream is being captured (a recorded pass may be replayed after a status build that was

@@ -14,6 +14,10 @@
 // and keep the smaller or the larger of the two with one median-of-three
 // against 0 or 0xFFFFFFFF.  No atomics; barriers only between the waves that
 // share an instance.
+#include <algorithm>
+#include <cfloat>
+#include <type_traits>
+
 #include "common.h"
 
 namespace gr {
@@ -768,14 +772,32 @@ constexpr int lean_inst_words(int cap) { return 2 * cap + cap / 4; }
 // chains and more waves to overlap them.
 //
 // The work is that of kEPL * 64 * kSplit words; the tables have room for kTab >= that many entries.
+// T of a request on segment k of an instance, as k_direct forms it
+__device__ __forceinline__ float latency_at(float c0, int L, const float4& K, const float2& gh, int k)
+{
+    const float Lf = (float)L, tri = Lf * (Lf - 1.0f) * 0.5f;
+    const int N = __float_as_int(K.w);
+    const float E = fmaf(tri, K.z * (float)(N - k + 1), fmaf(Lf, gh.y, gh.x));
+    return fmaf(c0, kappa_of(make_float2(K.x, K.y), Lf), E);
+}
+
 struct InstanceIn {
     int g, a0, q0, A, Q, P, status;     // the instance, its slices of the caller's arrays and their lengths, GR_DEV_* bits
     int pend;                           // entries in its list, not counting those of the chunk
     unsigned long long joins;           // requests of the chunk that were sent here
 };
 
-template <int kEPL, int kSplit, int kTab, bool kQuiet>     // kQuiet: nobody asks for finish times or flags
-__device__ __forceinline__ void build_instance(const BuildArgs& a, const InstanceIn& in, int wave, uint32_t* smem)
+// What the instance offers a request of the next decision round, a lane each (see k_feedback).
+struct Offer {
+    int L;
+    float c0, T;
+    unsigned long long key;     // d_g as an integer that falls with it
+};
+
+// kQuiet: nobody asks for finish times or flags.  With an `offer` (of the instance's first wave) the latency of its
+// request is formed from the new table, as k_direct would.
+template <int kEPL, int kSplit, int kTab, bool kQuiet, bool kOffer = false>
+__device__ __forceinline__ void build_instance(const BuildArgs& a, const InstanceIn& in, int wave, uint32_t* smem, Offer* offer = nullptr)
 {
     const bool risk = !kQuiet && a.act_budget;
     constexpr int kWords = kWave * kEPL;         // sort words of a wave
@@ -1065,20 +1087,61 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
             }
         }
     }
+    double Gq0 = q, H0 = fma(cc.gamma, Ctot, fma(cc.beta, (double)(N + 1), cc.alpha));
+    if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
+    double d = fma(cc.gamma, Ctot, fma(cc.beta, (double)N, cc.alpha));     // the next decode step
+    if (blended) d = keep * d + a.lam * bd;
+    const float4 K = inst_coef(a, cc, bp, N);
     if (lane == 0 && part == 0) {
-        double Gq0 = q, H0 = fma(cc.gamma, Ctot, fma(cc.beta, (double)(N + 1), cc.alpha));
-        if (blended) { Gq0 = keep * Gq0 + a.lam * bq; H0 = keep * H0 + a.lam * bd; }
         a.tabGH[gh_at(g, 0, kTab)] = make_float2((float)Gq0, (float)H0);
-        a.instK[g] = inst_coef(a, cc, bp, N);
+        a.instK[g] = K;
         a.pend_touched[g] = 0;
         if (!a.use_pending) a.pend_cnt[g] = 0;
         else if (in.joins) a.pend_cnt[g] = in.pend + __popcll(in.joins);     // (every wave has read it: the sort's barriers)
-        double d = fma(cc.gamma, Ctot, fma(cc.beta, (double)N, cc.alpha));     // the next decode step
-        if (blended) d = keep * d + a.lam * bd;
         a.hD[g] = d;
         a.slot_key[slot] = falling_bits(d);
         if (a.out_d) a.out_d[g] = d;
     }
+    if constexpr (kOffer) {
+        // the new table in LDS, where the contexts and the sort's exchange were (the last reads of both
+        // are before the barrier of the totals)
+        static_assert(kSplit > 1 && kQuiet && 2 * (kCap + 1) <= kInstWords);
+        float2* const gh = reinterpret_cast<float2*>(smem);
+        uint16_t* const R = reinterpret_cast<uint16_t*>(xch);
+#pragma unroll
+        for (int r = 0; r < kEPL; ++r) {
+            gh[1 + first + lane * kEPL + r] = tGH[r];
+            R[first + lane * kEPL + r] = tR[r];
+        }
+        if (lane == 0 && part == 0) gh[0] = make_float2((float)Gq0, (float)H0);
+        __syncthreads();
+        if (part == 0) {
+            int k = 0;      // entries that are no longer than the request
+#pragma unroll
+            for (int step = kCap / 2; step > 0; step /= 2) k += (int)R[k + step - 1] <= offer->L ? step : 0;
+            k += (int)R[k] <= offer->L;
+            offer->T = latency_at(offer->c0, offer->L, K, gh[k], k);
+            offer->key = falling_bits(d);
+        }
+    }
+}
+
+// The instance's slices and the lengths of its lists, from the caller's offsets.
+template <int kTab>
+__device__ __forceinline__ void clamp_instance(const BuildArgs& a, InstanceIn& in, int a_begin, int a_end, int q_begin, int q_end, int pend)
+{
+    // offsets are clamped into the arrays, so broken CSR data cannot index outside them
+    in.a0 = (int)min((int64_t)max(a_begin, 0), a.n_active);
+    in.q0 = (int)min((int64_t)max(q_begin, 0), a.n_queued);
+    in.A = (int)max(min((int64_t)a_end, a.n_active) - in.a0, (int64_t)0);
+    in.Q = (int)max(min((int64_t)q_end, a.n_queued) - in.q0, (int64_t)0);
+    in.status = 0;
+    if (in.A > a.max_entries) { in.A = a.max_entries; in.status |= GR_DEV_ENTRIES_DROPPED; }
+    if (in.Q > a.max_entries - in.A) { in.Q = a.max_entries - in.A; in.status |= GR_DEV_ENTRIES_DROPPED; }
+    in.pend = pend;
+    in.P = in.pend + __popcll(in.joins);
+    if (in.P > kTab) { in.P = kTab; if (in.joins) in.status |= GR_DEV_ENTRIES_DROPPED; }
+    if (in.P > a.max_entries - in.A - in.Q) { in.P = a.max_entries - in.A - in.Q; in.status |= GR_DEV_ENTRIES_DROPPED; }
 }
 
 // A handle's tables have room for the most an instance may hold, which can be several times what
@@ -1109,18 +1172,7 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
     } else if (a.only_touched && a.pend_touched[g] == 0) {
         return;
     }
-    // offsets are clamped into the arrays, so broken CSR data cannot index outside them
-    in.a0 = (int)min((int64_t)max(a_begin, 0), a.n_active);
-    in.q0 = (int)min((int64_t)max(q_begin, 0), a.n_queued);
-    in.A = (int)max(min((int64_t)a_end, a.n_active) - in.a0, (int64_t)0);
-    in.Q = (int)max(min((int64_t)q_end, a.n_queued) - in.q0, (int64_t)0);
-    in.status = 0;
-    if (in.A > a.max_entries) { in.A = a.max_entries; in.status |= GR_DEV_ENTRIES_DROPPED; }
-    if (in.Q > a.max_entries - in.A) { in.Q = a.max_entries - in.A; in.status |= GR_DEV_ENTRIES_DROPPED; }
-    in.pend = pend;
-    in.P = in.pend + __popcll(in.joins);
-    if (in.P > kTab) { in.P = kTab; if (in.joins) in.status |= GR_DEV_ENTRIES_DROPPED; }
-    if (in.P > a.max_entries - in.A - in.Q) { in.P = a.max_entries - in.A - in.Q; in.status |= GR_DEV_ENTRIES_DROPPED; }
+    clamp_instance<kTab>(a, in, a_begin, a_end, q_begin, q_end, pend);
     const int N = in.A + in.Q + in.P;
     if constexpr (kFit) {
         if constexpr (kEPL >= 4)
@@ -1129,6 +1181,179 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
             if (N <= kTab / 2) return build_instance<kEPL / 2, kSplit, kTab, kQuiet>(a, in, wave, smem);
     }
     build_instance<kEPL, kSplit, kTab, kQuiet>(a, in, wave, smem);
+}
+
+// Feedback routing, a launch per decision round (chunks of up to kWave requests; a workgroup per instance, all
+// of whose waves share it).  Launch k decides the chunk before it from what every instance has offered (every
+// workgroup for itself: a lane per request, the waves share the instances), rebuilds the instances that were
+// chosen, and offers for the next chunk: each request's latency here, whether its deadline is met, and d_g.
+// The launches themselves are the wait of one round for the other.
+//
+// What bounds it is the chain of a round: the offers (64 requests x 256 instances are 64 KB for every workgroup, from
+// L2), the choice, then the rebuild, whose table is still in LDS when the next requests are looked up in it.  A round was
+// two launches, a scoring and a rebuild, each with its own start and its own reads of what the other had just written:
+// 256 instances x 512, 32 rounds of 64, with the status build 400 us, this way 333.  An instance only finds out
+// whether it is chosen itself: looking for everybody's choice took 17 us a round instead of 10.5 (8 bytes of every instance
+// as scalars, one after the other), and 12.3 with those read a lane each.
+struct FeedArgs {
+    BuildArgs b;                        // with the chunk that is decided here
+    const float* budget;
+    int* out_inst;
+    float* out_slack;
+    uint8_t* out_fallback;
+    const int *next_ctx0, *next_len, *next_exclude;     // the chunk to offer for
+    const float* next_budget;
+    const uint32_t* T_in;               // [M][kWave], [M], [M], see gr_fleet
+    const unsigned long long *met_in, *key_in;
+    uint32_t* T_out;
+    unsigned long long *met_out, *key_out;
+    int next_n, finite;
+};
+
+// Segment and latency of a request in the instance's table as it stands, in two steps as k_direct.
+template <int kTab>
+__device__ __forceinline__ float latency_in_table(const BuildArgs& a, int g, float c0, int L)
+{
+    constexpr int kS = split_count(kTab), kStride = kTab / kS;
+    const uint4* __restrict__ S = reinterpret_cast<const uint4*>(a.tabS + (size_t)g * kS);
+    int b = 0;
+#pragma unroll
+    for (int i = 0; i < kS / 8; ++i) b += count_upto(S[i], (uint32_t)L);
+    int k = min(b, kS - 1) * kStride;
+    const uint4* __restrict__ R = reinterpret_cast<const uint4*>(a.tabR + (size_t)g * kTab + k);
+    uint4 w[kStride / 8];
+#pragma unroll
+    for (int i = 0; i < kStride / 8; ++i) w[i] = R[i];
+#pragma unroll
+    for (int i = 0; i < kStride / 8; ++i) k += count_upto(w[i], (uint32_t)L);
+    return latency_at(c0, L, a.instK[g], a.tabGH[gh_at(g, k, kTab)], k);
+}
+
+// The bits of a wave's lanes together (the steps of wave_incl_scan_i32).
+__device__ __forceinline__ uint32_t wave_or_u32(uint32_t v)
+{
+    const auto step = [&](auto ctrl, auto rows) {
+        v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});
+    step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+
+__device__ __forceinline__ unsigned long long wave_or_u64(unsigned long long v)
+{
+    return ((unsigned long long)wave_or_u32((uint32_t)(v >> 32)) << 32) | wave_or_u32((uint32_t)v);
+}
+
+template <int kEPL, int kSplit>
+__global__ __launch_bounds__(kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_feedback(FeedArgs f)
+{
+    extern __shared__ uint32_t smem[];
+    __shared__ uint32_t share[kSplit][kWave];
+    __shared__ unsigned long long met_by[kSplit][2];
+    constexpr int kTab = kWave * kEPL * kSplit;
+    const BuildArgs& a = f.b;
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    InstanceIn in;
+    in.g = blockIdx.x;
+    in.joins = 0;
+    const int g = in.g, M = a.n_inst;
+    const int a_begin = a.act_off[g], a_end = a.act_off[g + 1], q_begin = a.q_off[g], q_end = a.q_off[g + 1];
+    const int pend = a.pend_cnt[g];
+    Offer offer{};
+    float D = 0.f;
+    int ex = -1;
+    if (f.next_n && wave == 0) {
+        const int j = min(lane, f.next_n - 1);
+        offer.L = min(max(f.next_len[j], 0), a.max_len);
+        offer.c0 = (float)f.next_ctx0[j];
+        D = f.next_budget[j];
+        if (f.next_exclude) ex = f.next_exclude[j];
+    }
+
+    if (a.chunk_n) {
+        // Alg. 1 for the instance itself, lane = request: where a deadline can be met, it is met here and by nobody
+        // more capable; else nobody's latency is less, or as little at a lower index
+        const uint32_t own = f.T_in[(size_t)g * kWave + lane];
+        const unsigned long long own_key = f.key_in[g], own_met = f.met_in[g];
+        unsigned long long any = 0, above = 0;         // requests whose deadline is met by somebody, by somebody more capable
+        for (int h = threadIdx.x; h < M; h += kSplit * kWave) {
+            const unsigned long long met = f.met_in[h], key = f.key_in[h];
+            any |= met;
+            above |= key < own_key || (key == own_key && h < g) ? met : 0ull;
+        }
+        // the waves share the latencies; those at lower indices count as one less, so that `own` has to be below them
+        const int per = (M + kSplit - 1) / kSplit, h0 = wave * per, n_here = min(per, M - h0);
+        uint32_t least = ~0u;
+        if (n_here > 0) {
+            constexpr int kAhead = 16;
+            const uint32_t* __restrict__ row = f.T_in + (size_t)h0 * kWave + lane;
+            const int end = n_here * kWave, below = (g - h0) * kWave;
+            uint32_t T[kAhead], T_next[kAhead];
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) T[i] = row[min(i * kWave, end - kWave)];       // (a repeat of the last one changes nothing)
+            for (int at = 0; at < end; at += kAhead * kWave) {
+                if (at + kAhead * kWave < end) {
+#pragma unroll
+                    for (int i = 0; i < kAhead; ++i) T_next[i] = row[min(at + (kAhead + i) * kWave, end - kWave)];
+                }
+#pragma unroll
+                for (int i = 0; i < kAhead; ++i) least = min(least, T[i] - (min(at + i * kWave, end - kWave) < below ? 1u : 0u));
+#pragma unroll
+                for (int i = 0; i < kAhead; ++i) T[i] = T_next[i];
+            }
+        }
+        any = wave_or_u64(any);
+        above = wave_or_u64(above);
+        share[wave][lane] = least;
+        if (lane == 0) { met_by[wave][0] = any; met_by[wave][1] = above; }
+        __syncthreads();
+        any = above = 0;
+#pragma unroll
+        for (int w = 0; w < kSplit; ++w) {
+            least = min(least, share[w][lane]);
+            any |= met_by[w][0];
+            above |= met_by[w][1];
+        }
+        const bool live = lane < a.chunk_n, served = (any >> lane) & 1ull;
+        const bool mine = live && (served ? ((own_met & ~above) >> lane) & 1ull : own != ~0u && own <= least);
+        if (wave == 0 && mine) {
+            f.out_inst[lane] = g;
+            f.out_slack[lane] = f.budget[lane] - from_ordered_bits(own);
+            if (f.out_fallback) f.out_fallback[lane] = !served;
+        }
+        if (g == 0 && wave == 0 && live && !served && least == ~0u) {      // nobody is allowed
+            f.out_inst[lane] = -1;
+            f.out_slack[lane] = 0.f;
+            if (f.out_fallback) f.out_fallback[lane] = 1;
+        }
+        in.joins = __ballot(mine);
+    }
+
+    if (a.chunk_n && (in.joins || !a.only_touched)) {
+        clamp_instance<kTab>(a, in, a_begin, a_end, q_begin, q_end, pend);
+        const int N = in.A + in.Q + in.P;
+        bool built = false;
+        if constexpr (kEPL >= 4)
+            if (N <= kTab / 4) { build_instance<kEPL / 4, kSplit, kTab, true, true>(a, in, wave, smem, &offer); built = true; }
+        if constexpr (kEPL >= 2)
+            if (!built && N <= kTab / 2) { build_instance<kEPL / 2, kSplit, kTab, true, true>(a, in, wave, smem, &offer); built = true; }
+        if (!built) build_instance<kEPL, kSplit, kTab, true, true>(a, in, wave, smem, &offer);
+    } else if (f.next_n && wave == 0) {
+        offer.T = latency_in_table<kTab>(a, g, offer.c0, offer.L);
+        offer.key = falling_bits(a.hD[g]);
+    }
+    if (!f.next_n || wave != 0) return;
+    const float Dc = D > FLT_MAX ? FLT_MAX : D;
+    const bool ok = g != ex && (!f.finite || offer.T < __builtin_inff());
+    const unsigned long long met = __ballot(ok && offer.T <= Dc);
+    f.T_out[(size_t)g * kWave + lane] = ok ? ordered_bits(offer.T) : ~0u;
+    if (lane == 0) { f.met_out[g] = met; f.key_out[g] = offer.key; }
 }
 
 // The capability rank of every instance, for the caller (Alg. 1's argmax d_g: rank 0 = largest d_g,
@@ -1370,6 +1595,16 @@ int launch_build_split(const BuildArgs& b, int M, hipStream_t s)
     return kSplit;
 }
 
+// Waves that share an instance of a fleet of M whose tables take kEPL sort words per lane of one wave (without caps):
+// fewer instances than the chip takes waves at four per SIMD, several waves per instance (measured on 1 024
+// instances x 1 000 requests: 19.8 us with one wave each, 17.7 with two, 16.0 with four, 18.0 with eight, 29 with
+// sixteen; on 256 x 512: 9.2, 8.5, 7.7-8.2, 8.1)
+int waves_per_instance(int epl, int M)
+{
+    const int room = 4 * kSimds / M;
+    return epl >= 4 && room >= 4 ? 4 : epl >= 2 && room >= 2 ? 2 : 1;
+}
+
 // kEPL: sort words per lane if one wave takes an instance.  Returns the waves that share an instance.
 template <int kEPL>
 int launch_build(const BuildArgs& b, int M, hipStream_t s)
@@ -1380,12 +1615,9 @@ int launch_build(const BuildArgs& b, int M, hipStream_t s)
         hipLaunchKernelGGL((k_build_capped<kEPL>), grid, dim3(kBlock), 3 * lds, s, b);
         return 1;
     }
-    // fewer instances than the chip takes waves at four per SIMD: several waves per instance
-    // (measured on 1 024 instances x 1 000 requests: 19.8 us with one wave each, 17.7 with two, 16.0 with
-    // four, 18.0 with eight, 29 with sixteen; on 256 x 512: 9.2, 8.5, 7.7-8.2, 8.1)
-    const int room = 4 * kSimds / M;
-    if constexpr (kEPL >= 4) if (room >= 4) return launch_build_split<kEPL, 4>(b, M, s);
-    if constexpr (kEPL >= 2) if (room >= 2) return launch_build_split<kEPL, 2>(b, M, s);
+    const int waves = waves_per_instance(kEPL, M);
+    if constexpr (kEPL >= 4) if (waves == 4) return launch_build_split<kEPL, 4>(b, M, s);
+    if constexpr (kEPL >= 2) if (waves == 2) return launch_build_split<kEPL, 2>(b, M, s);
     hipLaunchKernelGGL((k_build_lean<kEPL, 1, false, false>), grid, dim3(kBlock), lean_lds<kEPL>(), s, b);
     return 1;
 }
@@ -1440,6 +1672,8 @@ int status_prepare()
     GR_SET_SPLIT(1, 2); GR_SET_SPLIT(2, 2); GR_SET_SPLIT(4, 2); GR_SET_SPLIT(8, 2); GR_SET_SPLIT(16, 2);
     GR_SET_SPLIT(1, 4); GR_SET_SPLIT(2, 4); GR_SET_SPLIT(4, 4); GR_SET_SPLIT(8, 4);
 #undef GR_SET_SPLIT
+    set(k_feedback<1, 2>, split_lds<2, 2>()); set(k_feedback<1, 4>, split_lds<4, 4>()); set(k_feedback<2, 4>, split_lds<8, 4>());
+    set(k_feedback<4, 4>, split_lds<16, 4>()); set(k_feedback<8, 4>, split_lds<32, 4>());
     set(k_build_capped<1>, 3 * word * 1); set(k_build_capped<2>, 3 * word * 2); set(k_build_capped<4>, 3 * word * 4);
     set(k_build_capped<8>, 3 * word * 8); set(k_build_capped<16>, 3 * word * 16); set(k_build_capped<32>, 3 * word * 32);
     return ok ? GR_OK : GR_ERR_HIP;
@@ -1454,7 +1688,7 @@ int launch_ranks(gr_fleet* f, int* out_rank, hipStream_t s)
     return hipGetLastError() == hipSuccess ? GR_OK : GR_ERR_HIP;
 }
 
-int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s)
+static BuildArgs build_args(const gr_fleet* f, const StatusIn& in)
 {
     BuildArgs b{};
     b.act_off = in.act_off; b.act_prompt = in.act_prompt; b.act_gen = in.act_gen; b.act_rem = in.act_rem;
@@ -1475,6 +1709,79 @@ int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s)
     b.chunk_n = in.chunk_n; b.chunk_inst = in.chunk_inst; b.chunk_ctx0 = in.chunk_ctx0; b.chunk_len = in.chunk_len;
     b.batch_cap = f->has_cap ? f->batch_cap : nullptr;
     b.lam = f->lam; b.emaQ = f->emaQ; b.emaP = f->emaP; b.emaD = f->emaD;
+    return b;
+}
+
+// The account of the tables after a build on stream `s`.  (The class order is made by the next scoring pass that needs it.)
+static void tables_built(gr_fleet* f, hipStream_t s)
+{
+    const TableAccount account(f, s);
+    *account.v = TableView{true, false, f->lam != 0.0};
+    if (account.capturing) {
+        f->recorded = true;
+        f->blend_recorded |= f->lam != 0.0;
+    }
+}
+
+static_assert(4 * kSimds / kFeedInst >= 4, "four waves per instance wherever the tables have words for them");
+
+// Where a chunk would be scored pair by pair and would join its instances in the rebuild (no caps), and an instance has two
+// waves or more.  Every workgroup reads all offers, so the gain shrinks as the fleet grows.  A round, us, two launches / one:
+// 64 instances 12.4 / 7.8, 128 10.7 / 7.6, 256 14.0 / 10.6, 400 15.1 / 12.2, 512 16.0 / 13.3 (a rebuild with finish
+// times in the former; without them 1.5 less); wider fleets are not taken.
+bool feedback_by_round(const gr_fleet* f, int64_t chunk)
+{
+    return f->feed_T && !f->has_cap && chunk <= kWave && waves_per_instance(f->epl, f->n_inst) > 1 && pair_by_pair(f, chunk);
+}
+
+int launch_feedback(gr_fleet* f, const StatusIn& in, const FeedbackIn& r, hipStream_t s)
+{
+    FeedArgs a{};
+    a.b = build_args(f, in);
+    const size_t M = f->n_inst;
+    const int64_t rounds = (r.n + r.chunk - 1) / r.chunk;
+    for (int64_t k = 0; k <= rounds; ++k) {       // launch k decides chunk k - 1 and offers for chunk k
+        const int64_t at = k * r.chunk, was = at - r.chunk;
+        a.b.chunk_n = k ? (int)std::min<int64_t>(r.n - was, r.chunk) : 0;
+        a.b.only_touched = r.current || k != 1;
+        if (k) {
+            a.b.chunk_ctx0 = r.ctx0 + was; a.b.chunk_len = r.pred_len + was;
+            a.budget = r.budget + was; a.out_inst = r.out_inst + was; a.out_slack = r.out_slack + was;
+            a.out_fallback = r.out_fallback ? r.out_fallback + was : nullptr;
+        }
+        a.next_n = (int)std::max<int64_t>(0, std::min<int64_t>(r.n - at, r.chunk));
+        if (a.next_n) {
+            a.next_ctx0 = r.ctx0 + at; a.next_len = r.pred_len + at; a.next_budget = r.budget + at;
+            a.next_exclude = r.exclude ? r.exclude + at : nullptr;
+            a.finite = pairs_finite(f, a.next_n);
+        }
+        const size_t out = k & 1, got = out ^ 1;
+        a.T_in = f->feed_T + got * M * kWave; a.met_in = f->feed_met + got * M; a.key_in = f->feed_key + got * M;
+        a.T_out = f->feed_T + out * M * kWave; a.met_out = f->feed_met + out * M; a.key_out = f->feed_key + out * M;
+        ProfScope ps(f, kFeedback, s);
+        const int waves = waves_per_instance(f->epl, f->n_inst);
+#define GR_LAUNCH_FEEDBACK(E, W) \
+        hipLaunchKernelGGL((k_feedback<E / W, W>), dim3((unsigned)M), dim3(W * kWave), (split_lds<E, W>()), s, a); break
+        switch (f->epl * 8 + waves) {
+            case 2 * 8 + 2: GR_LAUNCH_FEEDBACK(2, 2);
+            case 4 * 8 + 4: GR_LAUNCH_FEEDBACK(4, 4);
+            case 8 * 8 + 4: GR_LAUNCH_FEEDBACK(8, 4);
+            case 16 * 8 + 4: GR_LAUNCH_FEEDBACK(16, 4);
+            default: GR_LAUNCH_FEEDBACK(32, 4);
+        }
+#undef GR_LAUNCH_FEEDBACK
+    }
+    if (hipGetLastError() != hipSuccess) {
+        TableAccount(f, s).v->current = false;
+        return GR_ERR_HIP;
+    }
+    tables_built(f, s);
+    return GR_OK;
+}
+
+int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s)
+{
+    const BuildArgs b = build_args(f, in);
     const int M = f->n_inst;
     int parts = 1;
     {
@@ -1489,20 +1796,16 @@ int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s)
         }
     }
     if (in.act_budget) f->late_parts = parts;
-    // (the class order is made by the next scoring pass that needs it)
-    const TableAccount account(f, s);
-    *account.v = TableView{false, false, f->lam != 0.0};
-    if (account.capturing) {
-        f->recorded = true;
-        f->blend_recorded |= f->lam != 0.0;
-    }
+    tables_built(f, s);
     if (in.out_rank) {
         const int rc = launch_ranks(f, in.out_rank, s);
         if (rc != GR_OK) return rc;
     }
-    if (hipGetLastError() != hipSuccess) return GR_ERR_HIP;
+    if (hipGetLastError() != hipSuccess) {
+        TableAccount(f, s).v->current = false;
+        return GR_ERR_HIP;
+    }
     f->has_status = true;
-    account.v->current = true;
     if (!in.use_pending) f->last_in = in;     // what a later feedback routing rebuilds from
     return GR_OK;
 }
