@@ -270,8 +270,11 @@ constexpr int log2_of(int v) { return v <= 1 ? 0 : 1 + log2_of(v / 2); }
 // arrays in entry order at the end, where a budget is also read (in the loop its read stood in
 // the chain).  And as long as
 // nobody can be admitted nothing is played at all.  1 024 instances of 200 running and 40 queued
-// requests, caps of 120 to 288: 94 us, 54 with the shorter turns, 32 without the turns before the
-// first admission.
+// requests, caps of 120 to 288: 94 us, 54 with the shorter turns, 33 without the turns before the
+// first admission, 30.5 with a turn's reductions side by side (one chain of DPP steps fills the waits of another).
+constexpr int kLowBits = 24;     // a lane's sum of contexts is added up over the wave in two parts of 32 bits
+constexpr long long kLowMask = (1ll << kLowBits) - 1;
+
 template <int kEPL>
 __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
 {
@@ -477,30 +480,34 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
                 C += (long long)n * s - wave_sum_i64(goneC);
             }
         }
+        long long left = 0;       // this lane's contexts that left with the last departure, not taken off C yet
         for (int guard = 0; guard <= 2 * N + 2; ++guard) {
-            const int k = min(cap_g - n, N - next_q);
-            if (k > 0) {                   // admit entries next_q .. next_q + k - 1: prefill, then into the batch
-                long long sumP = 0;
-#pragma unroll
-                for (int r = 0; r < kEPL; ++r) {
-                    const int i = r * kWave + lane;
-                    if (i >= next_q && i < next_q + k) {
-                        fstep[r] = s + (int)(key[r] >> kIdxBits);
-                        sumP += cbase[r];
-                        cbase[r] -= s;
-                    }
-                }
-                sumP = wave_sum_i64(sumP);
-                t += cc.delta * (double)sumP;
-                n += k; C += sumP; next_q += k;
-            }
-            if (next_q == N) break;        // the queue is empty: what follows is departures only (below)
-            // next departure
+            // admit entries next_q .. next_q + k - 1: prefill, then into the batch; and the next departure.  The sums and the
+            // minimum are formed side by side (each alone is a chain of steps that wait for one another)
+            const int k = max(min(cap_g - n, N - next_q), 0);
+            long long in_l = 0;
             uint32_t smin = 0x7fffffff;
 #pragma unroll
-            for (int r = 0; r < kEPL; ++r) smin = min(smin, fstep[r] > s ? (uint32_t)fstep[r] : 0x7fffffffu);
+            for (int r = 0; r < kEPL; ++r) {
+                const int i = r * kWave + lane;
+                const bool admitted = i >= next_q && i < next_q + k;
+                fstep[r] = admitted ? s + (int)(key[r] >> kIdxBits) : fstep[r];
+                in_l += admitted ? cbase[r] : 0;
+                cbase[r] -= admitted ? s : 0;
+                smin = min(smin, fstep[r] > s ? (uint32_t)fstep[r] : 0x7fffffffu);
+            }
+            const long long dc_l = in_l - left;
+            const int in_lo = wave_incl_scan_i32((int)(in_l & kLowMask)), in_hi = wave_incl_scan_i32((int)(in_l >> kLowBits));
+            const int dc_lo = wave_incl_scan_i32((int)(dc_l & kLowMask)), dc_hi = wave_incl_scan_i32((int)(dc_l >> kLowBits));
             smin = min_over<false>(smin);
-            if (smin == 0x7fffffffu) break;           // (nobody is running: cannot be, the batch has room then)
+            const auto total = [](int lo, int hi) {
+                return ((long long)__builtin_amdgcn_readlane(hi, kWave - 1) << kLowBits) + __builtin_amdgcn_readlane(lo, kWave - 1);
+            };
+            if (k > 0) t += cc.delta * (double)total(in_lo, in_hi);
+            C += total(dc_lo, dc_hi);
+            n += k; next_q += k;
+            if (next_q == N) break;        // the queue is empty: what follows is departures only (below)
+            if (smin == 0x7fffffff) break;           // (nobody is running: cannot be, the batch has room then)
             const double step_now = fma(cc.gamma, (double)C, fma(cc.beta, (double)n, cc.alpha));
             if (d_first < 0.0) d_first = step_now;
             const long long ks = (int)smin - s;
@@ -509,18 +516,17 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
             C += (long long)n * ks;
             s = (int)smin;
             int gone = 0;
-            long long goneC = 0;
+            left = 0;
 #pragma unroll
             for (int r = 0; r < kEPL; ++r) {
                 const bool leaves = fstep[r] == s;
                 if (leaves) {
-                    goneC += cbase[r] + s;
+                    left += cbase[r] + s;
                     fin_lds[r * kWave + lane] = t;
                 }
                 gone += __popcll(__ballot(leaves));
             }
             n -= gone;
-            C -= wave_sum_i64(goneC);
         }
         // what is left, as of now: the sort words and contexts the closed form is built from
         q = t;
