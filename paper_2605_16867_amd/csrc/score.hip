@@ -364,7 +364,8 @@ template <bool kOwn>
 __device__ __forceinline__ void rank_run(const MemoArgs& a, int run, int* lds)
 {
     for (int i = run * kBlock + threadIdx.x; i < a.seen_words; i += a.n_run * kBlock) a.seen[i] = make_uint4(0u, 0u, 0u, 0u);
-    if (run == 0 && threadIdx.x == 0) a.totals[2] = 0;
+    // (a pass that counts the flagged requests here clears totals[2] when all of the workgroup have read it)
+    if (run == 0 && threadIdx.x == 0 && !a.count.totals) a.totals[2] = 0;
     static_assert(kBlock == kMemoP * kMemoP, "16 lanes per position of the run");
     if (run == 0 && a.count.totals) count_flagged(a.count, kBlock, lds);
     const int p = run * kMemoP + threadIdx.x / kMemoP, sub = threadIdx.x % kMemoP;

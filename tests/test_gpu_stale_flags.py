@@ -61,3 +61,45 @@ def test_flags_that_no_instance_sets(n_inst, held, caps):
         torch.cuda.synchronize()
         assert np.array_equal(T[i], inst.cpu().numpy()) and np.array_equal(S[i], slack.cpu().numpy())
     h.close()
+
+
+@pytest.mark.parametrize("case", ["no room", "no token"])
+@pytest.mark.parametrize("n_inst,held,pairs", [(250, 250, None), (500, 70, None), (40, 20, None), (40, 20, 0), (600, 100, None)])
+def test_offsets_that_cover_every_entry(n_inst, held, pairs, case):
+    """The build alone says that there are entries whose flag it has not set: one instance holds more than the handle
+    has room for, or, under caps, running entries have no token left.  Counted by the workgroups of a table that has
+    a row for every length (250, 500, 40 instances), pair by pair (40), with the list of lengths (600: a class of 200)."""
+    import torch
+    rng = np.random.default_rng([n_inst, held, 1])
+    acts = [rand_entries(rng, held * (2 if case == "no room" and g == n_inst // 3 else 1)) for g in range(n_inst)]
+    all_ = np.concatenate(acts)
+    na = len(all_)
+    fl = fleet(np.arange(n_inst) % 3, acts, [[]] * n_inst, np.ones((8192, 2)), np.ones(8192),
+               act_budget=rng.uniform(0.5, 8, na) * solo(all_[:, 0] + all_[:, 1], all_[:, 2]))
+    d = parity.upload(fl, "cuda:0")
+    h = parity.make_handle(fl, max_entries=held + 1, max_requests=8192)
+    if pairs is not None:
+        h.gr_set_small_batch_pairs(pairs)
+    rem = fl.act_rem_refreshed.copy()
+    if case == "no token":
+        h.gr_set_batch_cap(rng.integers(1, held + 3, n_inst))
+        rem[rng.random(na) < 0.1] = 0
+    z = lambda n, t, v=0: torch.full((n,), v, dtype=t, device="cuda:0")
+    fin, tgt, tsl, nfl = z(na, torch.float32), z(na, torch.int32, -7), z(na, torch.float32, 7), z(1, torch.int32, -7)
+    first = torch.from_numpy((rng.random(na) < 0.5).astype(np.uint8) * 3).cuda()
+    unset = np.zeros(na, bool)
+    if case == "no room":
+        a0 = fl.act_off[n_inst // 3]
+        unset[a0 + held + 1:a0 + 2 * held] = True
+    else:
+        unset = rem == 0
+    for _ in range(2):
+        flag = first.clone()
+        h.gr_risk_scan(d["act_off"], d["act_prompt"], d["act_gen"], torch.from_numpy(rem).cuda(), d["q_off"], d["q_prompt"],
+                       d["q_len"], d["act_budget"], flag, fin, tgt, tsl, nfl)
+        torch.cuda.synchronize()
+        assert (flag.cpu().numpy()[unset] == 3).any()       # (the library sets 0 or 1)
+        off = flag == 0
+        assert int(nfl.item()) == int((~off).sum())
+        assert bool((tgt[off] == -1).all()) and bool((tsl[off] == 0).all())
+    h.close()
