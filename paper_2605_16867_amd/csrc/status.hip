@@ -1368,7 +1368,8 @@ __global__ __launch_bounds__(kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_feedbac
     const float Dc = D > FLT_MAX ? FLT_MAX : D;
     const bool ok = g != ex && (!f.finite || offer.T < __builtin_inff());
     const unsigned long long met = __ballot(ok && offer.T <= Dc);
-    f.T_out[(size_t)g * kWave + lane] = ok ? ordered_bits(offer.T) : ~0u;
+    // (the least and the largest integer are NaNs with every bit set; here nothing is below the one, and the other is not allowed)
+    f.T_out[(size_t)g * kWave + lane] = ok ? min(max(ordered_bits(offer.T), 1u), ~0u - 1u) : ~0u;
     if (lane == 0) { f.met_out[g] = met; f.key_out[g] = offer.key; }
 }
 

@@ -57,3 +57,35 @@ def test_by_round(n_inst, held, entries, chunk, n):
     want = _route(fl, chunk, n, entries, 0, blend, exclude, stale)
     for a, b in zip(got, want):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("who", ["all", "some"])
+@pytest.mark.parametrize("bits", [0x7fc00000, 0x7fffffff, -1, -0x400000])
+def test_observations_that_are_no_numbers(bits, who):
+    """Latencies that are NaNs, of every sign and with every bit set, have their place in the order of the pair-by-pair pass:
+    one instance takes the request.  Tables of 64 entries (a pass and a rebuild per round) against tables of 128."""
+    sp = dataclasses.replace(workloads.spec("mid"), n_inst=9, n_active=20, n_queued=2, n_incoming=21, seed=5)
+    fl = workloads.make_fleet(sp)
+    nan = torch.tensor([bits], dtype=torch.int32).view(torch.float32).cuda().expand(9).contiguous()
+    one = torch.from_numpy(np.linspace(1e-4, 2e-4, 9).astype(np.float32)).cuda()
+    seen = []
+    for entries in (64, 128):
+        h, d = make_handle(fl, max_entries=entries), upload(fl)
+        wait = one * 1e4
+        if who == "some":
+            wait[2:5] = nan[2:5]
+        else:
+            wait = nan
+        h.gr_observe(1.0, wait, one, one * 500)
+        h.gr_set_blend(0.5)
+        fin = torch.zeros(len(fl.act_prompt), device="cuda")
+        h.gr_build_status(d["act_off"], d["act_prompt"], d["act_gen"], d["act_rem"], d["q_off"], d["q_prompt"], d["q_len"], fin)
+        out = [torch.full((21,), -7, dtype=torch.int32, device="cuda"), torch.zeros(21, device="cuda"),
+               torch.zeros(21, dtype=torch.uint8, device="cuda")]
+        ex = torch.arange(21, dtype=torch.int32, device="cuda") % 9
+        h.gr_route_feedback(5, *[d[k] for k in ("in_prompt", "in_len", "in_budget")], out[0], out[1], exclude_inst=ex, out_fallback=out[2])
+        seen.append([x.cpu().numpy() for x in out])
+        h.close()
+    assert (seen[0][0] >= 0).all()
+    for a, b in zip(*seen):
+        assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f")
