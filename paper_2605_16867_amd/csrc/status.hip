@@ -1814,13 +1814,11 @@ int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s)
     }
     if (in.act_budget) f->late_parts = parts;
     tables_built(f, s);
-    if (in.out_rank) {
-        const int rc = launch_ranks(f, in.out_rank, s);
-        if (rc != GR_OK) return rc;
-    }
-    if (hipGetLastError() != hipSuccess) {
+    int rc = in.out_rank ? launch_ranks(f, in.out_rank, s) : GR_OK;
+    if (rc == GR_OK && hipGetLastError() != hipSuccess) rc = GR_ERR_HIP;
+    if (rc != GR_OK) {
         TableAccount(f, s).v->current = false;
-        return GR_ERR_HIP;
+        return rc;
     }
     f->has_status = true;
     if (!in.use_pending) f->last_in = in;     // what a later feedback routing rebuilds from
