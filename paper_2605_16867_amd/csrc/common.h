@@ -43,7 +43,7 @@ constexpr int64_t kDirectInfinite = int64_t(1) << 18;   // pairs (of whole 128 i
 constexpr int kDirectSpan = 4096;  // instances that one workgroup takes of a request scored pair by pair
 constexpr int kFeedInst = 512;     // most instances of a fleet whose feedback routing is a launch per round
 constexpr int kDirectParts = 16384;  // room for the selections of such parts
-constexpr int64_t kDenseValues = int64_t(1) << 23;   // values of a table that has a row for every length
+constexpr int64_t kDenseValues = int64_t(1) << 22;   // values of a table that has a row for every length
 constexpr int kMemoP = 16;         // positions of a run of the class order
 constexpr int kRanges = 4;         // ranges of prompt lengths that a length's possible least latencies are looked up for
 constexpr int kRestParts = 64;     // lists of requests that those do not decide

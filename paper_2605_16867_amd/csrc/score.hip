@@ -2156,11 +2156,16 @@ struct PairsPlan {
 
 // Whether the table of a pass has a row for every length there may be, so that the list of those that there are is not
 // made, and the class order is made by the table's workgroups: two launches less (three in a routing call), two
-// dependent reads less, for a table that may be larger.  On fleets so small that the workgroups fit the chip at once
-// and a class's order is quickly made.  Control interval of 256 x 512, 65 536 arrivals: 64.7 us with the list, 54.5 without
-// (the table 10.2 us with its order, before 8.2 behind 5.1 for list and order and, routing, 2.4 for the marks).  On larger fleets the
-// order takes a launch of its own and the table's workgroups outnumber what the chip holds at once: 777 instances, 20 011 requests, 29.2 / 29.3;
-// 1 024 x 200, 32 768 requests 66.7 / 66.9.
+// dependent reads less, for a table that may be larger.  Where the fleet is so small that a class's order is quickly made, and
+// the table no larger than the list's launches are worth, for one request too (gr_score_route_cached takes
+// the table whatever the batch).  Whole calls, us, with the list / a row per length:
+//   values of the table   1.2 M (256 instances, lengths up to 4 096)   3.9 M (200, 16 384)   4.7 M (256)    7.9 M (480)
+//   routing one request with its prefix       20.4 / 14.4               20.7 / 17.3          20.5 / 20.2    20.5 / 20.9
+//   refresh, x 400, routing 8 192             27.4 / 20.3               27.2 / 22.4          27.0 / 25.7    28.2 / 29.1
+//   risk scan x 128                           25.1 / 21.3               24.4 / 22.1          25.6 / 26.6    24.9 / 28.4
+//   risk scan x 512                           28.5 / 24.7               26.7 / 24.9          27.4 / 28.9    32.8 / 36.2
+// (The workgroups of 2^22 values are 1 024, and one per run: the chip takes 1 792 at once.)  On larger fleets the
+// order takes a launch of its own: 777 instances, 20 011 requests, 29.2 / 29.3; 1 024 x 200, 32 768 requests 66.7 / 66.9.
 static bool dense_rows(const gr_fleet* f)
 {
     return f->req_cap >= f->bins && f->most_of_class <= kOwnClass && f->m_pos <= kOwnSlots &&

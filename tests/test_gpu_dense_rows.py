@@ -4,7 +4,8 @@ most positions and of 16 and 32 runs, exact ties of d_g, lengths that include 0,
 import numpy as np
 import pytest
 
-from tests.fleets import fleet, solo
+from tests import parity
+from tests.fleets import CLASSES, fleet, rand_entries, solo
 from tests.test_gpu_runs import _check, _fleet
 from tests.test_gpu_scan_selection import _scan
 
@@ -36,6 +37,33 @@ def test_lengths_from_nothing(n_len):
 def test_scans(n_inst, held, n_class, late, blend, obs, clones):
     na, share, _ = _scan(n_inst, held, n_class, late, blend=blend, obs=obs, clones=clones)
     assert na >= 1 << 15 and share > 0.01
+
+
+# positions (a class rounded up to 16s) times lengths: 288 x 4 097 = 1.2 M, 240 x 16 385 = 3.9 M, 288 x 16 385 = 4.7 M,
+# 480 x 8 001 = 3.8 M, 480 x 16 385 = 7.9 M; the line is at 2^22 = 4.2 M
+@pytest.mark.parametrize("n_inst,n_class,max_len,listed", [(250, 3, 4096, False), (200, 3, 16384, False), (250, 3, 16384, True),
+                                                           (480, 6, 8000, False), (480, 6, 16384, True)])
+def test_one_request_through_a_table_of_any_size(n_inst, n_class, max_len, listed):
+    """A request with a cached prefix has a row of its own where a row for every length there may be would be a large
+    table (the marks and the list are launched), and the answer is that of the pair-by-pair pass."""
+    import torch
+    rng = np.random.default_rng(n_inst)
+    fl = fleet(np.arange(n_inst) % n_class, [rand_entries(rng, 20) for _ in range(n_inst)], [[]] * n_inst, np.array([[700, max_len]]),
+               np.array([1.0]), classes=[tuple(x * (1 + c / 5) for x in CLASSES[0]) for c in range(n_class)], max_len=max_len)
+    d = parity.upload(fl, "cuda:0")
+    h = parity.make_handle(fl, max_requests=20000)
+    fin = torch.zeros(len(fl.act_prompt), dtype=torch.float32, device="cuda:0")
+    h.gr_build_status(d["act_off"], d["act_prompt"], d["act_gen"], d["act_rem"], d["q_off"], d["q_prompt"], d["q_len"], fin)
+    z = lambda n, t, v=0: torch.full((n,), v, dtype=t, device="cuda:0")
+    got, want = [[z(1, torch.int32, -7), z(1, torch.float32), z(1, torch.uint8, 9)] for _ in range(2)]
+    req = [d[k] for k in ("in_prompt", "in_len", "in_budget")]
+    h.gr_profile_enable(16)
+    h.gr_score_route_cached(*req, z(2, torch.int32), z(0, torch.int32), z(0, torch.int32), got[0], got[1], out_fallback=got[2])
+    ran = {k for k, (_, n) in h.gr_profile_read().items() if n}
+    h.gr_score_route_noalloc(*req, want[0], want[1], out_fallback=want[2])
+    assert ("k_mark<route>" in ran) == listed and "k_memo<route>" in ran
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
+    h.close()
 
 
 @pytest.mark.parametrize("n_inst,n_class", [(2, 1), (64, 1), (65, 1), (128, 1), (250, 3), (440, 4)])
