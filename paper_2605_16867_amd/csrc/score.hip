@@ -658,7 +658,6 @@ struct ClassArgs {
     uint2* class_next;
     float4* cls_bound;
     int n_class, c_pad, n_run, run_pad;
-    int dense;         // 1: row 0 is the length 0, at which instances without a queue all tie
 };
 
 // Per row and class: the least E, the lowest instance that has it, and the least E above it among
@@ -727,7 +726,6 @@ __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
         if (y > E1) above = fminf(above, y);
     }
     const bool any = u < U && E1 < inf;
-    if (a.dense && u == 0) { tied = 1; above = E1; }      // (left to the runs: nobody is decided by a next larger E that is no larger)
     int low = 0x7fffffff;
     const auto take = [&](int r, int piece) {      // four positions of a run
         const float4 v = *reinterpret_cast<const float4*>(E + (size_t)r * kTile + 4 * piece);
@@ -1232,7 +1230,7 @@ __global__ __launch_bounds__(kBlock) void k_lines(SelectArgs a)
     const int row = i / kRanges, range = i % kRanges;
     if (row >= a.totals[1]) return;
     const float inf = __builtin_inff(), lo = kRangeEnd[range], hi = kRangeEnd[range + 1];
-    const float Lf = (float)(a.row_len ? a.row_len[row] : row);
+    const float Lf = (float)a.row_len[row];
     const float* __restrict__ runs = a.grp_min + runs_at<false>(row, a.run_pad);
     const float* __restrict__ E = a.memo + memo_at(row, 0, a.n_run);
 
@@ -1360,7 +1358,7 @@ __global__ __launch_bounds__(kBlock) void k_select_by_class(SelectArgs a)
             best[it] = inf; cls[it] = 0; tie[it] = false;
         }
 #pragma unroll
-        for (int it = 0; it < kItems; ++it) row[it] = row_at(a.len_row, q[it].L);
+        for (int it = 0; it < kItems; ++it) row[it] = a.len_row[q[it].L];
         for (int c0 = 0; c0 < a.n_class; c0 += 4) {
             float4 e[kItems];
 #pragma unroll
@@ -1465,7 +1463,7 @@ __global__ __launch_bounds__(kBlock) void k_select_lines(SelectArgs a)
         if (sub == 0) answer<kMigrate>(a, i, -1, 0.f, false);      // not flagged: no migration target
         return;
     }
-    const int row = row_at(a.len_row, q.L);
+    const int row = a.len_row[q.L];
     const float4* at = lines_of(a, q, row);
     const LineChoice c = choose_line(q, at[0], at[1]);
     if (c.decided) {
@@ -1502,7 +1500,7 @@ __global__ __launch_bounds__(kBlock) void k_late_lines(SelectArgs a)
 #pragma unroll
     for (int it = 0; it < kItems; ++it) q[it] = fetch<true>(a.s, min(i0 + it * kBlock, a.s.n - 1), a.max_len);
 #pragma unroll
-    for (int it = 0; it < kItems; ++it) row[it] = row_at(a.len_row, q[it].L);
+    for (int it = 0; it < kItems; ++it) row[it] = a.len_row[q[it].L];
 #pragma unroll
     for (int it = 0; it < kItems; ++it) {
         const float4* __restrict__ at = lines_of(a, q[it], row[it]);
@@ -1548,9 +1546,9 @@ __global__ __launch_bounds__(kBlock, 6) void k_late_rest(SelectArgs a, int wg_re
     const auto index = [&](int k) { return list[min(k, n - 1)]; };
     int i = index(k), i1 = index(k + kStep), i2 = index(k + 2 * kStep);
     Request q = fetch<true>(a.s, i, a.max_len), q1 = fetch<true>(a.s, i1, a.max_len);
-    int row = row_at(a.len_row, q.L);
+    int row = a.len_row[q.L];
     for (; k < n; k += kStep) {
-        const int i3 = index(k + 3 * kStep), row1 = row_at(a.len_row, q1.L);
+        const int i3 = index(k + 3 * kStep), row1 = a.len_row[q1.L];
         const Request q2 = fetch<true>(a.s, i2, a.max_len);
         Selection<4, false> sel(a, q, row, sub);
         sel.run_at = lds_at;
@@ -2174,18 +2172,18 @@ static bool dense_rows(const gr_fleet* f)
 
 bool needs_marks(const gr_fleet* f, int64_t n) { return !pair_by_pair(f, n) && !dense_rows(f); }
 
-// How the rows of a pass are found.
+// How the rows of a pass are found.  (Lines and classes first are for fleets of more runs than have a row per length.)
 struct RowsOf {
     const int* totals;
-    const int* row_len;          // null: a row per length
-    const uint16_t* len_row;
+    const uint16_t* len_row;     // null: a row per length
     int64_t most;
 };
+static_assert(kOwnSlots / kMemoP <= 2 * kGroup, "a row per length and lines exclude each other");
 
 static RowsOf rows_of(const gr_fleet* f, int64_t n)
 {
-    if (dense_rows(f)) return {f->dense_totals, nullptr, nullptr, f->bins};
-    return {f->totals, f->row_len, f->len_row, std::min<int64_t>(n, f->bins)};
+    if (dense_rows(f)) return {f->dense_totals, nullptr, f->bins};
+    return {f->totals, f->len_row, std::min<int64_t>(n, f->bins)};
 }
 
 static PairsArgs pairs_args(const gr_fleet* f, const ReqSrc& src, const ScoreOut& out)
@@ -2283,9 +2281,11 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     //    4 096      54.6 / 51.6 (55.2 / 55.6)    126 / 89.9  (133 / 109)
     // A risk scan's requests are late where they are, and few can be served in time elsewhere:
     // 512 x 512 requests 57.6 / 41.2 (42.0 / 42.0), 4 096 x 512 544 / 110 (278 / 137).
+    // Fleets with a row per length have four lanes per request as an alternative: four classes of 128, scan of x 300
+    // 29.9 / 35.7 (27.1 / 34.3), x 512 33.1 / 38.7 (31.4 / 40.2).
     const PairsPlan pairs(f, out.T);
     const bool select = !(out.T && pairs.select);
-    const bool by_class = select && !blended && n >= kByClassMin && f->n_class <= kGroup && f->n_run >= 4 * f->n_class &&
+    const bool by_class = select && !dense && !blended && n >= kByClassMin && f->n_class <= kGroup && f->n_run >= 4 * f->n_class &&
                           f->n_run >= (migrate ? 2 * kGroup : 4 * kGroup);
     // The lines first where no class decides a request: with a blend (every instance has its own prefill rate), and where
     // there are more classes than a group has lanes.  Whole calls, us, a group of lanes per request over the runs / lines
@@ -2323,9 +2323,7 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         if (f->cap > 1024) hipLaunchKernelGGL((k_memo<4, B, D, O>), grid, dim3(kBlock), 0, s, m); \
         else if (f->cap > 512) hipLaunchKernelGGL((k_memo<2, B, D, O>), grid, dim3(kBlock), 0, s, m); \
         else hipLaunchKernelGGL((k_memo<1, B, D, O>), grid, dim3(kBlock), 0, s, m); } while (0)
-        if (blocks && own) GR_LAUNCH_MEMO(true, true, true);
-        else if (blocks && dense) GR_LAUNCH_MEMO(true, true, false);
-        else if (blocks) GR_LAUNCH_MEMO(true, false, false);
+        if (blocks) GR_LAUNCH_MEMO(true, false, false);
         else if (own) GR_LAUNCH_MEMO(false, true, true);
         else if (dense) GR_LAUNCH_MEMO(false, true, false);
         else GR_LAUNCH_MEMO(false, false, false);
@@ -2333,9 +2331,9 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     }
     if (by_class) {
         ClassArgs c{};
-        c.totals = rows.totals; c.cls_run = f->cls_run; c.order = f->order; c.memo = f->memo; c.grp_min = f->grp_min;
+        c.totals = f->totals; c.cls_run = f->cls_run; c.order = f->order; c.memo = f->memo; c.grp_min = f->grp_min;
         c.run_k = f->run_k; c.class_min = f->class_min; c.class_next = f->class_next; c.cls_bound = f->cls_bound;
-        c.n_class = f->n_class; c.c_pad = f->c_pad; c.n_run = f->n_run; c.run_pad = f->run_pad; c.dense = dense;
+        c.n_class = f->n_class; c.c_pad = f->c_pad; c.n_run = f->n_run; c.run_pad = f->run_pad;
         ProfScope ps(f, kClassRoute + off, s);
         const dim3 grid((unsigned)((max_rows + kWave - 1) / kWave * f->n_class));
         if (blocks) hipLaunchKernelGGL(k_class<true>, grid, dim3(kBlock), 0, s, c);
@@ -2348,7 +2346,7 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         a.out_inst = out.inst; a.out_slack = out.slack; a.out_fallback = out.fallback;
         a.run_pad = f->run_pad; a.n_run = f->n_run; a.n_class = f->n_class; a.c_pad = f->c_pad;
         a.max_len = f->max_len; a.n_inst = f->n_inst;
-        a.lines = f->lines; a.totals = rows.totals; a.row_len = rows.row_len; a.pos_of = f->pos_of;
+        a.lines = f->lines; a.totals = f->totals; a.row_len = f->row_len; a.pos_of = f->pos_of;
         a.rest_cnt = f->rest_cnt;
         if (by_lines) {
             constexpr int per = kBlock / kWave;

@@ -82,3 +82,10 @@ def test_next_decode_steps_closer_than_single_precision(n_inst, n_class, step):
     budgets = np.exp(rng.uniform(np.log(0.5), np.log(30), n_req)) * solo(inc[:, 0], inc[:, 1])
     share = _check(fleet(np.arange(n_inst) % n_class, acts, [[]] * n_inst, inc, budgets, classes=classes))
     assert share > 0.02
+
+
+@pytest.mark.parametrize("late", ["all", "some"])
+@pytest.mark.parametrize("n_inst,held,n_class", [(470, 300, 5), (458, 300, 6), (476, 300, 5)])      # 32 runs, a row per length
+def test_large_scans_at_the_most_runs(n_inst, held, n_class, late):
+    na, share, _ = _scan(n_inst, held, n_class, late)
+    assert na >= 1 << 17 and share > 0.01
