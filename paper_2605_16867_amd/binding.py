@@ -1,7 +1,8 @@
 """Binding of libgoodroute: same names as the C interface, argument
-marshalling only (ctypes; natively, by csrc/marshal.cpp, for the calls of a serving loop).  Tensors are torch tensors on the GPU (device memory and the
-current stream come from torch; every step of the path runs in the library's
-kernels).  There is no fallback: without the built library every call raises.
+marshalling only (natively, by csrc/marshal.cpp, for the calls of a serving loop; by ctypes for the
+others, and for all of them where that module is not built or is of another torch: 7 to 9 us a call).
+Tensors are torch tensors on the GPU (device memory and the current stream come from torch; every step
+of the path runs in the library's kernels).  There is no fallback for those: without the built library every call raises.
 """
 from __future__ import annotations
 
@@ -81,24 +82,34 @@ def lib() -> C.CDLL:
 
 
 def marshal():
-    """The native marshalling, connected to the library's entry points."""
+    """The marshalling of the serving calls, connected to the library's entry points: native, or by ctypes where the
+    native module is not there."""
     global _marshal
     if _marshal is None:
         l = lib()
-        if not os.path.exists(MARSHAL_PATH):
-            raise ImportError(f"{MARSHAL_PATH} is not built; run `python -m paper_2605_16867_amd.build`")
-        import importlib.machinery
-        import importlib.util
-
-        import torch  # noqa: F401  (its libraries come first)
-        loader = importlib.machinery.ExtensionFileLoader("goodroute_marshal", MARSHAL_PATH)
-        m = importlib.util.module_from_spec(importlib.util.spec_from_loader("goodroute_marshal", loader))
-        loader.exec_module(m)
-        m.connect(_check_slowly, *[C.cast(getattr(l, n), C.c_void_p).value for n in (
-            "gr_build_status", "gr_score_route", "gr_score_route_noalloc", "gr_score_route_cached", "gr_route_feedback",
-            "gr_risk_scan")])
-        _marshal = m
+        try:
+            _marshal = _native(l)
+        except ImportError as e:
+            import warnings
+            warnings.warn(f"arguments are marshalled by ctypes: {e}", RuntimeWarning, stacklevel=2)
+            _marshal = _Ctypes
     return _marshal
+
+
+def _native(l):
+    if not os.path.exists(MARSHAL_PATH):
+        raise ImportError(f"{MARSHAL_PATH} is not built; run `python -m paper_2605_16867_amd.build`")
+    import importlib.machinery
+    import importlib.util
+
+    import torch  # noqa: F401  (its libraries come first)
+    loader = importlib.machinery.ExtensionFileLoader("goodroute_marshal", MARSHAL_PATH)
+    m = importlib.util.module_from_spec(importlib.util.spec_from_loader("goodroute_marshal", loader))
+    loader.exec_module(m)
+    m.connect(_check_slowly, *[C.cast(getattr(l, n), C.c_void_p).value for n in (
+        "gr_build_status", "gr_score_route", "gr_score_route_noalloc", "gr_score_route_cached", "gr_route_feedback",
+        "gr_risk_scan")])
+    return m
 
 
 def _check_slowly(t, code, name, n):
@@ -131,6 +142,76 @@ def _dev(t, dtype, name: str, n: Optional[int] = None):
 def _stream():
     import torch
     return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+
+
+class _Ctypes:
+    """The functions of csrc/marshal.cpp by ctypes: the same arguments, the same refusals."""
+
+    @staticmethod
+    def _lists(M, act_off, act_prompt, act_gen, act_rem, q_off, q_prompt, q_len, rem="act_rem"):
+        import torch
+        i32, na, nq = torch.int32, act_prompt.numel(), q_prompt.numel()
+        return na, nq, (_dev(act_off, i32, "act_off", M + 1), _dev(act_prompt, i32, "act_prompt"),
+                        _dev(act_gen, i32, "act_gen", na), _dev(act_rem, i32, rem, na), na,
+                        _dev(q_off, i32, "q_off", M + 1), _dev(q_prompt, i32, "q_prompt"), _dev(q_len, i32, "q_len", nq), nq)
+
+    @staticmethod
+    def _requests(ctx0, pred_len, budget, exclude):
+        import torch
+        n = ctx0.numel()
+        return n, (_dev(ctx0, torch.int32, "ctx0"), _dev(pred_len, torch.int32, "pred_len", n),
+                   _dev(budget, torch.float32, "budget", n), _dev(exclude, torch.int32, "exclude_inst", n))
+
+    @staticmethod
+    def _choices(n, inst, slack, fallback):
+        import torch
+        return (_dev(inst, torch.int32, "out_inst", n), _dev(slack, torch.float32, "out_slack", n),
+                _dev(fallback, torch.uint8, "out_fallback", n))
+
+    @classmethod
+    def build_status(cls, h, M, *args):
+        import torch
+        finish, q_finish, d, rank = args[7:]
+        na, nq, lists = cls._lists(M, *args[:7])
+        return lib().gr_build_status(h, *lists, _dev(finish, torch.float32, "out_act_finish", na),
+                                     _dev(q_finish, torch.float32, "out_q_finish", nq), _dev(d, torch.float64, "out_d", M),
+                                     _dev(rank, torch.int32, "out_rank", M), _stream())
+
+    @classmethod
+    def score_route(cls, h, M, ctx0, pred_len, budget, exclude, inst, slack, fallback, T):
+        import torch
+        n, requests = cls._requests(ctx0, pred_len, budget, exclude)
+        return lib().gr_score_route(h, n, *requests, *cls._choices(n, inst, slack, fallback),
+                                    _dev(T, torch.float32, "out_T", n * M), _stream())
+
+    @classmethod
+    def score_route_noalloc(cls, h, ctx0, pred_len, budget, exclude, inst, slack, fallback):
+        n, requests = cls._requests(ctx0, pred_len, budget, exclude)
+        return lib().gr_score_route_noalloc(h, n, *requests, *cls._choices(n, inst, slack, fallback), _stream())
+
+    @classmethod
+    def score_route_cached(cls, h, M, ctx0, pred_len, budget, exclude, off, hit_inst, hit_len, inst, slack, fallback, T):
+        import torch
+        i32, nh = torch.int32, hit_inst.numel()
+        n, requests = cls._requests(ctx0, pred_len, budget, exclude)
+        hits = (_dev(off, i32, "hit_off", n + 1), _dev(hit_inst, i32, "hit_inst"), _dev(hit_len, i32, "hit_len", nh), nh)
+        return lib().gr_score_route_cached(h, n, *requests, *hits, *cls._choices(n, inst, slack, fallback),
+                                           _dev(T, torch.float32, "out_T", n * M), _stream())
+
+    @classmethod
+    def route_feedback(cls, h, chunk, ctx0, pred_len, budget, exclude, inst, slack, fallback):
+        n, requests = cls._requests(ctx0, pred_len, budget, exclude)
+        return lib().gr_route_feedback(h, n, chunk, *requests, *cls._choices(n, inst, slack, fallback), _stream())
+
+    @classmethod
+    def risk_scan(cls, h, M, *args):
+        import torch
+        f32, i32 = torch.float32, torch.int32
+        budget, flag, finish, target, slack, n_flagged = args[7:]
+        na, nq, lists = cls._lists(M, *args[:7], rem="act_rem_refreshed")
+        return lib().gr_risk_scan(h, *lists, _dev(budget, f32, "act_budget", na), _dev(flag, torch.uint8, "out_flag", na),
+                                  _dev(finish, f32, "out_finish", na), _dev(target, i32, "out_target", na),
+                                  _dev(slack, f32, "out_target_slack", na), _dev(n_flagged, i32, "out_n_flagged", 1), _stream())
 
 
 class Fleet:
