@@ -303,7 +303,7 @@ struct FeedbackIn {
     int* out_inst;
     float* out_slack;
     uint8_t* out_fallback;
-    bool current, finite;
+    bool current;
 };
 bool feedback_by_round(const gr_fleet* f, int64_t chunk);
 int launch_feedback(gr_fleet* f, const StatusIn& in, const FeedbackIn& r, hipStream_t s);
@@ -315,7 +315,6 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
                  bool small_batch_ok = false);
 bool needs_marks(const gr_fleet* f, int64_t n);      // a risk scan's table pass makes a list of lengths
 bool pair_by_pair(const gr_fleet* f, int64_t n);
-bool pairs_finite(const gr_fleet* f, int64_t n);     // pair by pair an infinite latency of a routing batch is none
 int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream_t s);
 int launch_hits(gr_fleet* f, const ReqSrc& src, const int* hit_off, const int* hit_inst, const int* hit_len,
                 int64_t n_hits, const ScoreOut& out, hipStream_t s);

@@ -2083,8 +2083,9 @@ bool pair_by_pair(const gr_fleet* f, int64_t n)
     return n * std::max(f->n_inst, kGroup) <= kDirectPairs;
 }
 
-// (small routing batches have always taken infinite latencies for latencies)
-bool pairs_finite(const gr_fleet* f, int64_t n)
+// Whether an infinite latency (or a NaN) of a routing batch scored pair by pair is none, as in the pass over the table: small
+// batches have always taken it for a latency.
+static bool pairs_finite(const gr_fleet* f, int64_t n)
 {
     const bool small = n <= kDirectMax && n * f->m_pad <= kDirectInfinite;
     return f->small_batch_pairs < 0 && !small;

@@ -1223,7 +1223,7 @@ struct FeedArgs {
     const unsigned long long *met_in, *key_in;
     uint32_t* T_out;
     unsigned long long *met_out, *key_out;
-    int next_n, finite;
+    int next_n;
 };
 
 // Segment and latency of a request in the instance's table as it stands, in two steps as k_direct.
@@ -1366,7 +1366,7 @@ __global__ __launch_bounds__(kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_feedbac
     }
     if (!f.next_n || wave != 0) return;
     const float Dc = D > FLT_MAX ? FLT_MAX : D;
-    const bool ok = g != ex && (!f.finite || offer.T < __builtin_inff());
+    const bool ok = g != ex;      // (batches of this size take infinite latencies for latencies, see pairs_finite)
     const unsigned long long met = __ballot(ok && offer.T <= Dc);
     // (the least and the largest integer are NaNs with every bit set; here nothing is below the one, and the other is not allowed)
     f.T_out[(size_t)g * kWave + lane] = ok ? min(max(ordered_bits(offer.T), 1u), ~0u - 1u) : ~0u;
@@ -1741,6 +1741,7 @@ static void tables_built(gr_fleet* f, hipStream_t s)
 }
 
 static_assert(4 * kSimds / kFeedInst >= 4, "four waves per instance wherever the tables have words for them");
+static_assert(kWave <= kDirectMax && kWave * kFeedInst <= kDirectInfinite, "an infinite latency is one in every chunk");
 
 // Where a chunk would be scored pair by pair and would join its instances in the rebuild (no caps), and an instance has two
 // waves or more.  Every workgroup reads all offers, so the gain shrinks as the fleet grows.  A round, us, two launches / one:
@@ -1770,7 +1771,6 @@ int launch_feedback(gr_fleet* f, const StatusIn& in, const FeedbackIn& r, hipStr
         if (a.next_n) {
             a.next_ctx0 = r.ctx0 + at; a.next_len = r.pred_len + at; a.next_budget = r.budget + at;
             a.next_exclude = r.exclude ? r.exclude + at : nullptr;
-            a.finite = pairs_finite(f, a.next_n);
         }
         const size_t out = k & 1, got = out ^ 1;
         a.T_in = f->feed_T + got * M * kWave; a.met_in = f->feed_met + got * M; a.key_in = f->feed_key + got * M;
