@@ -172,7 +172,8 @@ int gr_score_route(gr_fleet* f, int64_t n_req,
  * gr_score_route for callers that want the same work queued whatever the batch: code under HIP
  * graph capture, tight serving loops.  Same inputs, outputs and answers as gr_score_route's
  * pair-by-pair pass (whatever gr_set_small_batch_pairs says; no out_T), for at most
- * GR_NOALLOC_MAX_REQUESTS requests per call; more is GR_ERR_TOO_LARGE.  The call queues one
+ * GR_NOALLOC_MAX_REQUESTS requests per call; more is GR_ERR_TOO_LARGE.  (An infinite latency
+ * always counts as one here: see gr_set_small_batch_pairs.)  The call queues one
  * kernel on the stream (two for fleets of more than 4 096 instances) and calls no hipMalloc,
  * hipFree, memset, copy or synchronisation.
  */
@@ -335,6 +336,12 @@ int gr_set_batch_cap(gr_fleet* f, const int32_t* cap);
  *               number of pairs decides (up to 524 288, with at least 16 per request).
  * gr_score_route_cached always takes the table.
  * Equal latencies go to the lowest instance index either way.
+ *
+ * An infinite latency (an infinite observation, see gr_observe) is nobody's in the pass over the table and in
+ * gr_risk_scan: where every latency of a request is infinite, its instance is -1.  It counts as a latency, no less
+ * than any other, and the request goes to the lowest index, in gr_score_route_noalloc, and in gr_score_route and
+ * gr_route_feedback for batches (chunks) that are scored pair by pair and either max_pairs is set or the batch is of
+ * at most 4096 requests and n * (n_inst rounded up to 128) at most 262 144.
  */
 int gr_set_small_batch_pairs(gr_fleet* f, int64_t max_pairs);
 

@@ -88,3 +88,34 @@ def test_the_line(n):
                act_budget=rng.uniform(0.5, 20, n) * solo(all_[:, 0] + all_[:, 1], all_[:, 2]))
     import torch
     _both_ways(fl, torch.from_numpy(fl.act_off).cuda(), None)
+
+
+@pytest.mark.parametrize("n,pairs,inst", [(1, None, 0), (2048, None, 0), (2049, None, -1), (8193, None, -1), (2048, 0, -1), (2049, 1 << 19, 0)])
+def test_infinite_latencies_by_size(n, pairs, inst):
+    """64 instances whose every latency is infinite: a small batch goes to the lowest index (and any batch scored pair by pair that
+    the caller has set the size of), a larger one nowhere, gr_score_route_noalloc always somewhere."""
+    import torch
+    fl = _fleet(64, 2, 10000, 1)
+    d = parity.upload(fl, "cuda:0")
+    h = parity.make_handle(fl)
+    if pairs is not None:
+        h.gr_set_small_batch_pairs(pairs)
+    obs = torch.full((64,), float("inf"), device="cuda:0")
+    h.gr_observe(1.0, obs, obs, obs)
+    h.gr_set_blend(0.5)
+    z = lambda n, t, v=0: torch.full((n,), v, dtype=t, device="cuda:0")
+    h.gr_build_status(d["act_off"], d["act_prompt"], d["act_gen"], d["act_rem"], d["q_off"], d["q_prompt"], d["q_len"],
+                      z(len(fl.act_prompt), torch.float32))
+    got, fb, other = z(n, torch.int32, -7), z(n, torch.uint8, 9), z(n, torch.int32, -7)
+    slack = z(n, torch.float32)
+    req = [d[k][:n] for k in ("in_prompt", "in_len", "in_budget")]
+    h.gr_score_route(*req, got, slack, out_fallback=fb)
+    assert bool((got == inst).all()) and bool((fb == 1).all())
+    assert bool((slack == (0 if inst < 0 else -float("inf"))).all())
+    if n <= 4096:
+        h.gr_score_route_noalloc(*req, other, slack)
+        assert bool((other == 0).all())
+    if inst == 0:
+        h.gr_route_feedback(64, *[x[:64] for x in req], other[:64], slack[:64])
+        assert bool((other[:64] == 0).all())
+    h.close()
