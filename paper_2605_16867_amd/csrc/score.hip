@@ -405,7 +405,6 @@ __device__ __forceinline__ void rank_run(const MemoArgs& a, int run, int* lds)
     int g, gi;
     float2 kk;
     uint32_t n = 0;
-    constexpr int kAhead = 8;
     if constexpr (kOwn) {
         __syncthreads();
         OwnLds& l = *reinterpret_cast<OwnLds*>(lds);
@@ -435,16 +434,17 @@ __device__ __forceinline__ void rank_run(const MemoArgs& a, int run, int* lds)
         g = a.order[p];
         kk = a.posK[run * kMemoP + sub];
         gi = a.order[run * kMemoP + sub];
-    for (int r0 = sub; r0 < a.n_run; r0 += kAhead * kMemoP) {
-        uint4 h[kAhead];
+        constexpr int kAhead = 8;
+        for (int r0 = sub; r0 < a.n_run; r0 += kAhead * kMemoP) {
+            uint4 h[kAhead];
 #pragma unroll
-        for (int i = 0; i < kAhead; ++i) h[i] = a.run_head[min(r0 + i * kMemoP, a.n_run - 1)];
+            for (int i = 0; i < kAhead; ++i) h[i] = a.run_head[min(r0 + i * kMemoP, a.n_run - 1)];
 #pragma unroll
-        for (int i = 0; i < kAhead; ++i) {
-            const unsigned long long hk = ((unsigned long long)h[i].y << 32) | h[i].x;
-            n += r0 + i * kMemoP < a.n_run && (hk < key || (hk == key && (int)h[i].z < g));
+            for (int i = 0; i < kAhead; ++i) {
+                const unsigned long long hk = ((unsigned long long)h[i].y << 32) | h[i].x;
+                n += r0 + i * kMemoP < a.n_run && (hk < key || (hk == key && (int)h[i].z < g));
+            }
         }
-    }
     }
     float lo = kk.x, hi = gi >= 0 ? kk.x : -__builtin_inff();
     float gm = gi >= 0 ? kk.y : 0.f;

@@ -770,14 +770,6 @@ constexpr int kBufferDwords = 0x00020000;   // descriptor word 3: raw buffer of 
 // 32-bit words of LDS per instance of the plain build: contexts, budgets / finish times, flag bytes
 constexpr int lean_inst_words(int cap) { return 2 * cap + cap / 4; }
 
-// kEPL sort words per lane; kSplit waves share an instance (kSplit = 1: a workgroup is four instances, a wave each; 2 or 4:
-// a workgroup is one instance): wave `part` reads entries part * 64 * kEPL onwards, the sort's
-// last levels and the totals of the prefix sums cross the waves through LDS, and the wave ends
-// up with sorted positions part * 64 * kEPL onwards.  The results are the same bit for bit (the
-// sums are exact); a fleet with fewer instances than the chip has SIMDs gets shorter dependent
-// chains and more waves to overlap them.
-//
-// The work is that of kEPL * 64 * kSplit words; the tables have room for kTab >= that many entries.
 // T of a request on segment k of an instance, as k_direct forms it
 __device__ __forceinline__ float latency_at(float c0, int L, const float4& K, const float2& gh, int k)
 {
@@ -800,6 +792,15 @@ struct Offer {
     unsigned long long key;     // d_g as an integer that falls with it
 };
 
+// kEPL sort words per lane; kSplit waves share an instance (kSplit = 1: a workgroup is four instances, a wave each; 2 or 4:
+// a workgroup is one instance): wave `part` reads entries part * 64 * kEPL onwards, the sort's
+// last levels and the totals of the prefix sums cross the waves through LDS, and the wave ends
+// up with sorted positions part * 64 * kEPL onwards.  The results are the same bit for bit (the
+// sums are exact); a fleet with fewer instances than the chip has SIMDs gets shorter dependent
+// chains and more waves to overlap them.
+//
+// The work is that of kEPL * 64 * kSplit words; the tables have room for kTab >= that many entries.
+//
 // kQuiet: nobody asks for finish times or flags.  With an `offer` (of the instance's first wave) the latency of its
 // request is formed from the new table, as k_direct would.
 template <int kEPL, int kSplit, int kTab, bool kQuiet, bool kOffer = false>
