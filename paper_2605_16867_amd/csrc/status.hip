@@ -1212,19 +1212,21 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
 // 256 instances x 512, 32 rounds of 64, with the status build 400 us, this way 333.  An instance only finds out
 // whether it is chosen itself: looking for everybody's choice took 17 us a round instead of 10.5 (8 bytes of every instance
 // as scalars, one after the other), and 12.3 with those read a lane each.
+// (in the order in which they are needed: a launch reads them anew, a line of 64 bytes at a time; the 33 launches of 2 048 requests,
+// 64 at a time, take 338 us this way, 339 with next_n at the end, 345 with it right behind b)
 struct FeedArgs {
     BuildArgs b;                        // with the chunk that is decided here
-    const float* budget;
-    int* out_inst;
-    float* out_slack;
-    uint8_t* out_fallback;
     const int *next_ctx0, *next_len, *next_exclude;     // the chunk to offer for
     const float* next_budget;
+    int next_n;
     const uint32_t* T_in;               // [M][kWave], [M], [M], see gr_fleet
     const unsigned long long *met_in, *key_in;
     uint32_t* T_out;
     unsigned long long *met_out, *key_out;
-    int next_n;
+    const float* budget;
+    int* out_inst;
+    float* out_slack;
+    uint8_t* out_fallback;
 };
 
 // Segment and latency of a request in the instance's table as it stands, in two steps as k_direct.
