@@ -52,7 +52,8 @@ PROBE = os.path.join(CSRC, "probe_valu_issue")
 
 def build_probe(verbose: bool = False) -> str:
     """The stand-alone microbenchmark behind the vector-ALU issue model (not part of the library)."""
-    cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-o", PROBE, PROBE + ".hip"]
+    cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "-o", PROBE, PROBE + ".hip"]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
