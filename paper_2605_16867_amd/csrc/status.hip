@@ -69,6 +69,8 @@ __device__ __forceinline__ float4 inst_coef(const BuildArgs& a, const ClassCoef&
 {
     const double keep = 1.0 - a.lam;
     const float gam = (float)keep * (float)cc.gamma;
+    // the smoothed status alone: every segment is the same (as long as no sum of the white-box part is infinite)
+    if (keep == 0.0 && cc.delta + cc.alpha + cc.beta + cc.gamma < 1e100) n |= kAllAlike;
     return a.lam != 0.0 ? make_float4((float)(keep * cc.delta + a.lam * bp), (float)(keep * cc.gamma), gam, __int_as_float(n))
                         : make_float4((float)cc.delta, (float)cc.gamma, gam, __int_as_float(n));
 }
@@ -774,7 +776,7 @@ constexpr int lean_inst_words(int cap) { return 2 * cap + cap / 4; }
 __device__ __forceinline__ float latency_at(float c0, int L, const float4& K, const float2& gh, int k)
 {
     const float Lf = (float)L, tri = Lf * (Lf - 1.0f) * 0.5f;
-    const int N = __float_as_int(K.w);
+    const int N = entries_of(K);
     const float E = fmaf(tri, K.z * (float)(N - k + 1), fmaf(Lf, gh.y, gh.x));
     return fmaf(c0, kappa_of(make_float2(K.x, K.y), Lf), E);
 }
