@@ -333,7 +333,8 @@ int gr_set_batch_cap(gr_fleet* f, const int32_t* cap);
  *   max_pairs   gr_score_route, gr_route_feedback (its chunks) and gr_risk_scan (its running
  *               requests) score a batch pair by pair when n * (n_inst rounded up to
  *               128) is at most this and n <= 4096.  0: never.  If it is never set, the
- *               number of pairs decides (up to 524 288, with at least 16 per request).
+ *               number of pairs decides (up to 524 288, with at least 16 per request, or up to
+ *               786 432 with more than 32 instances rounded up to whole 64).
  * gr_score_route_cached always takes the table.
  * Equal latencies go to the lowest instance index either way.
  *

@@ -39,7 +39,8 @@ constexpr int kMaxLen = 32767;     // lengths and row numbers are kept in 16 bit
 constexpr int kAllAlike = 1 << 30; // with the entries of an instance (gr_fleet::instK): its segments all have the same (Gq, H) and no curvature
 constexpr int kMemoU = 256;        // distinct lengths per block of the table of a scoring pass
 constexpr int kDirectMax = 4096;   // most requests of a batch that a caller has scored pair by pair
-constexpr int64_t kDirectPairs = int64_t(1) << 19;   // pairs of a batch that is where the sizes decide (see pair_by_pair)
+constexpr int64_t kDirectPairs = int64_t(1) << 19;   // pairs of a batch that is where the sizes decide (see pair_by_pair),
+constexpr int64_t kDirectLanes = int64_t(3) << 18;   // and pairs that its lanes go through
 constexpr int64_t kDirectInfinite = int64_t(1) << 18;   // pairs (of whole 128 instances) up to which infinite latencies count there
 constexpr int kDirectSpan = 4096;  // instances that one workgroup takes of a request scored pair by pair
 constexpr int kFeedInst = 512;     // most instances of a fleet whose feedback routing is a launch per round

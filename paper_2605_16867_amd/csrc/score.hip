@@ -2073,7 +2073,7 @@ static int launch_pair_by_pair(gr_fleet* f, const ReqSrc& src, const ScoreOut& o
 {
     const int n = (int)src.n, M = f->n_inst;
     if (n == 0) return GR_OK;
-    if (src.n > std::max<int64_t>(kDirectMax, kDirectPairs / kGroup)) return GR_ERR_TOO_LARGE;
+    if (src.n > std::max<int64_t>(kDirectMax, kDirectLanes / kGroup)) return GR_ERR_TOO_LARGE;
     DirectArgs d{};
     d.s = src;
     d.instK = f->instK; d.hD = f->hD; d.tabR = f->tabR; d.tabS = f->tabS; d.tabGH = f->tabGH;
@@ -2086,7 +2086,8 @@ static int launch_pair_by_pair(gr_fleet* f, const ReqSrc& src, const ScoreOut& o
     // lanes per request: an instance each as far as a workgroup goes (few requests: the chain of reads
     // of one instance is the time of the call); 64 lanes leave the fewest idle on small fleets, and
     // where there are requests enough, 16 with two instances each up to 32 (16 384 requests x 32 instances
-    // 6.7 us, 8.9 with 64 lanes; 110 x 17 a microsecond more)
+    // 6.7 us, 8.9 with 64 lanes; 110 x 17 a microsecond more); with two each they do for 128 instances (6 000 requests 9.0 us,
+    // with 256 lanes 10.4; four each for 256: 100 requests 4.9 us instead of 3.6)
     {
         ProfScope ps(f, kDirect, s);
 #define GR_LAUNCH_DIRECT(N, U) do { \
@@ -2103,6 +2104,7 @@ static int launch_pair_by_pair(gr_fleet* f, const ReqSrc& src, const ScoreOut& o
         if (M <= 16) GR_LAUNCH_DIRECT(16, 1);
         else if (M <= 32 && n > kDirectMax) GR_LAUNCH_DIRECT(16, 2);
         else if (M <= 64) GR_LAUNCH_DIRECT(64, 1);
+        else if (M <= 128) GR_LAUNCH_DIRECT(64, 2);
         else if (M <= 512) GR_LAUNCH_DIRECT(256, 1);
         else if (M <= 1024) GR_LAUNCH_DIRECT(1024, 1);
         else GR_LAUNCH_DIRECT(1024, 4);
@@ -2121,17 +2123,20 @@ int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream
     return launch_pair_by_pair<false>(f, src, out, false, s);
 }
 
-// Whether a batch is scored pair by pair: as the caller says (gr_set_small_batch_pairs), or by the number of pairs.
-// A pass over the table is three or four launches, 15 to 20 us whatever the batch; this is one of 4 us
-// and grows with the pairs.  Routing call, us, table / pairs:
-//   4 096 requests x 32 instances 17.1 / 4.6, x 64 17.8 / 6.5, x 128 18.8 / 10.3; x 256 19.5 / 18.9
-//   2 048 x 256                   19.4 / 11.5   1 024 x 256 19.2 / 7.9;  1 024 x 1 024 20.3 / 24.9
-// and a risk scan with its status build, 32 x 512 requests 23.6 / 11.2, 64 x 128 18.9 / 10.5, 16 x 1 000 29.1 / 13.0.
-// (A request takes 16 lanes at least.)
+// Whether a batch is scored pair by pair: as the caller says (gr_set_small_batch_pairs), or by the number of pairs,
+// and of those that its lanes go through (see launch_pair_by_pair).  A pass over the table is two to four launches whose time hardly depends on
+// the batch; this is one that grows with the pairs.  Whole calls, us, table / pairs, with the status build where it says refresh or scan:
+//   routing  64 instances x 12 000 requests 9.9 / 8.2, 16 384 10.1 / 9.9, 32 768 10.4 / 17.5;  128 x 6 000 10.2 / 9.0, 8 192 10.2 / 11.4
+//            256 x 3 000 11.4 / 10.4, 4 096 11.3 / 13.0
+//   refresh  256 x 3 000 19.6 / 16.8, 4 096 19.5 / 19.6, 8 192 19.6 / 28.9;  1 024 x 700 29.3 / 22.4, 1 024 29.3 / 26.0, 1 500 30.3 / 31.6
+//            4 096 x 200 42.6 / 37.8, 300 42.6 / 52
+//   scan     64 x 150 requests each 16.9 / 12.6, 256 17.0 / 16.0, 512 17.8 / 26.7;  128 x 40 15.4 / 12.1, 100 17.1 / 22;  40 x 600 18.8 / 23.9
+// The line is where routing on a standing status still gains, whose table has its class order already.
 bool pair_by_pair(const gr_fleet* f, int64_t n)
 {
     if (f->small_batch_pairs >= 0) return n <= kDirectMax && n * f->m_pad <= f->small_batch_pairs;
-    return n * std::max(f->n_inst, kGroup) <= kDirectPairs;
+    const int pairs = std::max(f->n_inst, kGroup), lanes = pairs <= 2 * kGroup ? pairs : (pairs + kWave - 1) / kWave * kWave;
+    return n * pairs <= kDirectPairs || n * lanes <= kDirectLanes;
 }
 
 // Whether an infinite latency (or a NaN) of a routing batch scored pair by pair is none, as in the pass over the table: small
