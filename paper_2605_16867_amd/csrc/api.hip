@@ -132,7 +132,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     const size_t tab = (size_t)n_inst * f->cap, seen_bytes = (size_t)(f->bins + 15) / 16 * 16;
     const bool ok =
         dev_alloc(&f->cls, n_class) && dev_alloc(&f->inst_class, n_inst) &&
-        dev_alloc(&f->tabR, tab + kWave) && dev_alloc(&f->tabGH, (size_t)n_inst * (f->cap + 2)) &&
+        dev_alloc(&f->tabR, tab + kWave) && dev_alloc(&f->tabGH, (size_t)n_inst * (f->cap + 2) + kWave) &&
         dev_alloc(&f->hD, n_inst) &&
         dev_alloc(&f->emaQ, n_inst) && dev_alloc(&f->emaP, n_inst) && dev_alloc(&f->emaD, n_inst) &&
         dev_alloc(&f->instK, n_inst) && dev_alloc(&f->tabS, (size_t)n_inst * f->n_split) &&
@@ -174,7 +174,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     sent = sent && hipMemset(f->tabR, 0xFF, (tab + kWave) * sizeof(uint16_t)) == hipSuccess &&
            hipMemset(f->len_row + f->bins, 0xFF, sizeof(uint16_t)) == hipSuccess &&
            hipMemset(f->tabS, 0xFF, (size_t)n_inst * f->n_split * sizeof(uint16_t)) == hipSuccess;
-    clear(f->tabGH, (size_t)n_inst * (f->cap + 2) * sizeof(float2));
+    clear(f->tabGH, ((size_t)n_inst * (f->cap + 2) + kWave) * sizeof(float2));
     clear(f->instK, sizeof(float4) * n_inst);
     clear(f->hD, sizeof(double) * n_inst);
     clear(f->pend_cnt, sizeof(int) * n_inst);

@@ -161,7 +161,7 @@ struct gr_fleet {
     // per-instance tables written by the status build
     // E_g(L) = Gq + L*H + tri(L)*gamma*(n+1) on the segment after the k shortest requests (n still running)
     uint16_t* tabR = nullptr; // [M][cap] remaining lengths, ascending; 0xFFFF past the last entry (and room for a wave's reads behind it)
-    float2* tabGH = nullptr;  // [M][cap + 2] (Gq, H) of segment k, see gh_at; segment 0 is (q_g, alpha + beta*(N+1) + gamma*sum of contexts)
+    float2* tabGH = nullptr;  // [M][cap + 2] (Gq, H) of segment k, see gh_at (and room for a wave's reads behind it); segment 0 is (q_g, alpha + beta*(N+1) + gamma*sum of contexts)
     double* hD = nullptr;    // [M] d_g
     // [M] what a pair needs of its instance besides the tables: (delta, gamma) of the latency's prefill
     // part T = E + c0 * (delta + gamma * L), blended as the tables are; the curvature gamma of E; entries (int bits, see entries_of)

@@ -246,18 +246,19 @@ __device__ inline float quad_move(float x)
 // E of every (distinct length, instance).  A workgroup takes a run of kMemoP positions of the class
 // order and a block of kMemoU consecutive distinct lengths ("rows", ascending), a wave four of the
 // positions, a lane four rows.  The segment of a row is k = #{R_i <= L}.  The instance's lengths R
-// and the rows are both sorted: every eighth length (a lane each) says where the entries of the
-// block begin to within eight, and the entries from there on (a lane each, almost always one read) add one to the counter
-// of the first row that is at least as long; a prefix sum over the counters gives k for every
-// row.  The four instances of a wave are in flight together.
+// and the rows are both sorted: the last of every eight lengths (a lane each; tables of up to 512 are read whole, eight
+// lengths a lane, and kept in LDS) says where the entries of the block begin to within eight, and the entries from there on
+// (a lane each, almost always one read) add one to the counter of the first row that is at least as long; a prefix sum
+// over the counters gives k for every row.  The four instances of a wave are in flight together.
 //
-// What bounds it is the chain of reads a workgroup begins with (instance; its every eighth length; its entries; their
-// rows; the segments), then the vector ALU and the store.  A lane has four rows of four positions: the values are
+// What bounds it is the chain of reads a workgroup begins with (instance; its lengths; the entries' rows; the
+// segments), then the vector ALU and the store.  A lane has four rows of four positions: the values are
 // turned in LDS, so that the store is consecutive, and the least of a run is taken on the way out.  A run's blocks are
 // all on one XCD (every eighth workgroup), whose L2 then has its instances' tables.  Kernel time, us, on 4 096 instances of 512
-// requests 2 726 rows 29, 7 061 rows 41; 1 024 x 1 000, 3 900 rows 15.5; 256 x 512 8.2.  With two searches per instance
-// (splitters, then a stride), 64 entries at a time, 30 / 46 / 18.6 / 11.2, without the XCDs 31 / 43 / 17.5 / 8.5.
-// A workgroup for several blocks, the next one's entries on their way: 104 registers, 27 / 43 / 21.5 / 9.0.
+// requests 2 726 rows 25, 7 061 rows 33 (its 117 MB at the rate of a copy 23); 1 024 x 1 000, 3 900 rows 15.5; 256 x 512 8.2.
+// With two searches per instance (splitters, then a stride), 64 entries at a time, 30 / 46 / 18.6 / 11.2, without the XCDs 31 / 43 / 17.5 / 8.5.
+// A workgroup for several blocks, the next one's entries on their way: 104 registers, 27 / 43 / 21.5 / 9.0.  Workgroups for blocks
+// that are not there cost nothing (four rounds of workgroups and blocks in a loop: 42.5 instead of 41).
 constexpr int kMemoPerSimd = 7;     // waves per SIMD
 constexpr int kMemoWaves = kBlock / kWave;
 constexpr unsigned kMemoRound = kSimds * kMemoPerSimd / kMemoWaves;      // workgroups on the chip at once
@@ -473,9 +474,15 @@ __device__ __forceinline__ void rank_run(const MemoArgs& a, int run, int* lds)
 constexpr int kTileRow = kMemoP + 4;
 __device__ inline int tile_at(int row, int piece) { return row * kTileRow + 4 * (piece ^ ((row >> 4) & 3)); }
 
-//
 // kDense: every length up to the largest has a row (see dense_rows): no list, no row numbers to look up.
-template <int kEighths, bool kBlocks, bool kDense, bool kOwn>     // kEighths x 64 eighths of an instance's lengths at most
+//
+// kSparse: an instance has few entries in a block of rows (see sparse_rows); where a wave's four have up to kFewEntries, none of
+// which is the last of its 64, the rows go through those one after the other, and the segments come with the entries: no rows
+// of the entries to look up, no counters, no gather.  4 096 instances x 512 with long tails, 7 061 rows: the kernel 41 us
+// before, 36 this way, 33 with the lengths read whole; the whole scan 109.2 / 103.5.
+constexpr int kFewEntries = 16;
+
+template <int kEighths, bool kBlocks, bool kDense, bool kOwn, bool kSparse>     // kEighths x 64 eighths of an instance's lengths at most
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMemoPerSimd, kMemoPerSimd))) void k_memo(MemoArgs a)
 {
     __shared__ __align__(16) int lds[kMemoU * kTileRow];       // the counters, then the tile
@@ -508,79 +515,75 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMemoPer
     }
     // this lane's rows, the length before the block, the wave's instances: one trip, and the number of rows with it
     int4 r;
-    int L_before = ub - 1, U = a.bins;
+    int L_before = ub - 1, L_last = 0, U = a.bins;      // the lengths before the block's first row and of its last
     if constexpr (kDense) {
         r = make_int4(ub + 4 * lane, ub + 4 * lane + 1, ub + 4 * lane + 2, ub + 4 * lane + 3);
     } else {
         r = *reinterpret_cast<const int4*>(a.row_len + ub + 4 * lane);
         if (ub > 0) L_before = a.row_len[ub - 1];
+        if constexpr (kSparse) L_last = a.row_len[ub + kMemoU - 1];
         U = a.totals[1];
         asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w));
         if (ub >= U) return;
+        if (kSparse && U - ub < kMemoU) L_last = kMaxLen;
     }
     const int2 rc = a.run_cls[run];
     const int here = rc.x + rc.y - run * kMemoP;      // positions of the run that have an instance (or more)
     const int ue = ub + kMemoU;
 
     float4 K[kMemoInst];
-    int eighth[kMemoInst][kEighths];
     const uint16_t* R[kMemoInst];
+    // Of each instance the 64 entries from kb on, this lane's.  kb: entries before the block, less up to seven.  (0xFFFF:
+    // behind the instance's table.)
+    int* const cnt = lds + wave * kMemoInst * kMemoU;
+    int kb[kMemoInst], er[kMemoInst];
+    float2 seg[kMemoInst];
 #pragma unroll
     for (int j = 0; j < kMemoInst; ++j) {
         gs[j] = max(g[j], 0);
         K[j] = a.instK[gs[j]];
         R[j] = a.tabR + (size_t)gs[j] * a.cap;
-#pragma unroll
-        for (int c = 0; c < kEighths; ++c) eighth[j][c] = R[j][(unsigned)min(8 * (lane + c * kWave) + 7, a.cap - 1)];      // (past the table: the last one again)
     }
-    int* const cnt = lds + wave * kMemoInst * kMemoU;
+    if constexpr (kEighths == 1) {
+        // all of the lengths, eight a lane, and through LDS (where the counters will be) those from kb on
+        static_assert(kWave * sizeof(uint4) == kMemoU * sizeof(int), "an instance's lengths fit where its counters will be");
+        uint4 w[kMemoInst];
 #pragma unroll
-    for (int j = 0; j < kMemoInst; ++j) reinterpret_cast<int4*>(cnt + j * kMemoU)[lane] = make_int4(0, 0, 0, 0);
-
-    // Of each instance the 64 entries from kb on, this lane's: its row (the first one at least as long).  kb: entries before
-    // the block, less up to seven.  (What lies behind the instance's table is read as well, and masked.)
-    int kb[kMemoInst], er[kMemoInst];
-    unsigned long long valid[kMemoInst];
+        for (int j = 0; j < kMemoInst; ++j) w[j] = reinterpret_cast<const uint4*>(R[j])[min(lane, a.cap / 8 - 1)];
 #pragma unroll
-    for (int j = 0; j < kMemoInst; ++j) {
-        int n = 0;
+        for (int j = 0; j < kMemoInst; ++j) {
+            kb[j] = min(8 * __popcll(__ballot((int)(w[j].w >> 16) <= L_before)), a.cap);      // (past the table: the last ones again)
+            if constexpr (kSparse) seg[j] = a.tabGH[gh_at(gs[j], kb[j], a.cap) + lane];      // (segment kb + lane: what is before that entry has left)
+            reinterpret_cast<uint4*>(cnt + j * kMemoU)[lane] = w[j];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 #pragma unroll
-        for (int c = 0; c < kEighths; ++c) n += __popcll(__ballot(eighth[j][c] <= L_before));
-        kb[j] = min(8 * n, a.cap);
-        valid[j] = a.cap - kb[j] >= kWave ? ~0ull : (1ull << (a.cap - kb[j])) - 1ull;
-        er[j] = R[j][(unsigned)(kb[j] + lane)];
+        for (int j = 0; j < kMemoInst; ++j) er[j] = reinterpret_cast<const uint16_t*>(cnt + j * kMemoU)[min(kb[j] + lane, 8 * kWave - 1)];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+        static_assert(!kSparse, "tables of more than 512 lengths have many of them in a block (see sparse_rows)");
+        int eighth[kMemoInst][kEighths];
+#pragma unroll
+        for (int j = 0; j < kMemoInst; ++j) {
+#pragma unroll
+            for (int c = 0; c < kEighths; ++c) eighth[j][c] = R[j][(unsigned)min(8 * (lane + c * kWave) + 7, a.cap - 1)];      // (past the table: the last one again)
+        }
+#pragma unroll
+        for (int j = 0; j < kMemoInst; ++j) {
+            int n = 0;
+#pragma unroll
+            for (int c = 0; c < kEighths; ++c) n += __popcll(__ballot(eighth[j][c] <= L_before));
+            kb[j] = min(8 * n, a.cap);
+            er[j] = R[j][(unsigned)(kb[j] + lane)];      // (what lies behind the instance's table is read as well)
+        }
     }
 #pragma unroll
     for (int j = 0; j < kMemoInst; ++j)
-        if (!kDense) er[j] = a.len_row[(unsigned)min(er[j], a.bins)];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int j = 0; j < kMemoInst; ++j) {
-        const bool in = ((valid[j] >> lane) & 1ull) && (unsigned)(er[j] - ub) < (unsigned)kMemoU;
-        if (in) atomicAdd(&cnt[j * kMemoU + er[j] - ub], 1);
-        const int from = kb[j] + kWave;
-        kb[j] += __popcll(__ballot(er[j] < ub) & valid[j]);
-        // more than 64 are in the block (the shortest lengths): 512 at a time
-        if (!(__ballot(in) >> (kWave - 1))) continue;
-        for (int e0 = from; e0 < a.cap; e0 += 8 * kWave) {
-            const int e = e0 + 8 * lane;
-            uint4 w = make_uint4(~0u, ~0u, ~0u, ~0u);
-            if (e < a.cap) w = *reinterpret_cast<const uint4*>(R[j] + (unsigned)e);
-            const uint32_t words[4] = {w.x, w.y, w.z, w.w};
-            int row[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                row[i] = (int)(i % 2 ? words[i / 2] >> 16 : words[i / 2] & 0xFFFFu);
-                if (!kDense) row[i] = a.len_row[(unsigned)min(row[i], a.bins)];
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (row[i] < ue) atomicAdd(&cnt[j * kMemoU + row[i] - ub], 1);       // (in order: none is before the block)
-            if (__builtin_amdgcn_readlane(row[7], kWave - 1) >= ue) break;
-        }
-    }
+        if (lane >= a.cap - kb[j]) er[j] = 0xFFFF;
     float Lf[4], tri[4];
     {
         const int L[4] = {r.x, r.y, r.z, r.w};        // (past the last row: whatever is there, never read)
@@ -590,27 +593,101 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMemoPer
             tri[i] = Lf[i] * (Lf[i] - 1.0f) * 0.5f;
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    int k[kMemoInst][4];
-    float2 gh[kMemoInst][4];
-#pragma unroll
-    for (int j = 0; j < kMemoInst; ++j) {
-        int4 c = reinterpret_cast<const int4*>(cnt + j * kMemoU)[lane];
-        c.y += c.x; c.z += c.y; c.w += c.z;
-        const int before = kb[j] + wave_incl_scan_i32(c.w) - c.w;
-        k[j][0] = before + c.x; k[j][1] = before + c.y; k[j][2] = before + c.z; k[j][3] = before + c.w;
-        const char* __restrict__ GH = reinterpret_cast<const char*>(a.tabGH + gh_at(gs[j], 0, a.cap));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) gh[j][i] = *reinterpret_cast<const float2*>(GH + (unsigned)k[j][i] * (unsigned)sizeof(float2));
-    }
     float E[4][kMemoInst];
+    bool few = false;
+    if constexpr (kSparse) {
+        unsigned long long in[kMemoInst];
+        int begin[kMemoInst], n_in = 0;
+        bool more = false;
 #pragma unroll
-    for (int j = 0; j < kMemoInst; ++j) {
-        const int N1 = entries_of(K[j]) + 1;
+        for (int j = 0; j < kMemoInst; ++j) {
+            const unsigned long long up_to = __ballot(er[j] <= L_last), before = __ballot(er[j] <= L_before);
+            in[j] = up_to & ~before;
+            begin[j] = __popcll(before);
+            n_in += __popcll(in[j]);
+            more = more || (in[j] >> (kWave - 1));
+        }
+        few = n_in <= kFewEntries && !more;
+        if (few) {
+            const auto lane_of = [](float x, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)); };
 #pragma unroll
-        for (int i = 0; i < 4; ++i) E[i][j] = fmaf(tri[i], K[j].z * (float)(N1 - k[j][i]), fmaf(Lf[i], gh[j][i].y, gh[j][i].x));
+            for (int j = 0; j < kMemoInst; ++j) {
+                const int N1 = entries_of(K[j]) + 1 - kb[j];
+                float Gq[4], H[4], curve[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    Gq[i] = lane_of(seg[j].x, begin[j]); H[i] = lane_of(seg[j].y, begin[j]); curve[i] = K[j].z * (float)(N1 - begin[j]);
+                }
+                for (; in[j]; in[j] &= in[j] - 1) {
+                    const int l = __ffsll((long long)in[j]);      // (its segment is that of the next lane)
+                    const float R_l = (float)__builtin_amdgcn_readlane(er[j], l - 1);
+                    const float g_l = lane_of(seg[j].x, l), h_l = lane_of(seg[j].y, l), c_l = K[j].z * (float)(N1 - l);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const bool left = R_l <= Lf[i];
+                        Gq[i] = left ? g_l : Gq[i]; H[i] = left ? h_l : H[i]; curve[i] = left ? c_l : curve[i];
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) E[i][j] = fmaf(tri[i], curve[i], fmaf(Lf[i], H[i], Gq[i]));
+            }
+        }
+    }
+    if (!few) {
+#pragma unroll
+        for (int j = 0; j < kMemoInst; ++j) reinterpret_cast<int4*>(cnt + j * kMemoU)[lane] = make_int4(0, 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < kMemoInst; ++j)
+            if (!kDense) er[j] = a.len_row[(unsigned)min(er[j], a.bins)];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int j = 0; j < kMemoInst; ++j) {
+            const bool in = (unsigned)(er[j] - ub) < (unsigned)kMemoU;
+            if (in) atomicAdd(&cnt[j * kMemoU + er[j] - ub], 1);
+            const int from = kb[j] + kWave;
+            kb[j] += __popcll(__ballot(er[j] < ub));
+            // more than 64 are in the block (the shortest lengths): 512 at a time
+            if (!(__ballot(in) >> (kWave - 1))) continue;
+            for (int e0 = from; e0 < a.cap; e0 += 8 * kWave) {
+                const int e = e0 + 8 * lane;
+                uint4 w = make_uint4(~0u, ~0u, ~0u, ~0u);
+                if (e < a.cap) w = *reinterpret_cast<const uint4*>(R[j] + (unsigned)e);
+                const uint32_t words[4] = {w.x, w.y, w.z, w.w};
+                int row[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    row[i] = (int)(i % 2 ? words[i / 2] >> 16 : words[i / 2] & 0xFFFFu);
+                    if (!kDense) row[i] = a.len_row[(unsigned)min(row[i], a.bins)];
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (row[i] < ue) atomicAdd(&cnt[j * kMemoU + row[i] - ub], 1);       // (in order: none is before the block)
+                if (__builtin_amdgcn_readlane(row[7], kWave - 1) >= ue) break;
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        int k[kMemoInst][4];
+        float2 gh[kMemoInst][4];
+#pragma unroll
+        for (int j = 0; j < kMemoInst; ++j) {
+            int4 c = reinterpret_cast<const int4*>(cnt + j * kMemoU)[lane];
+            c.y += c.x; c.z += c.y; c.w += c.z;
+            const int before = kb[j] + wave_incl_scan_i32(c.w) - c.w;
+            k[j][0] = before + c.x; k[j][1] = before + c.y; k[j][2] = before + c.z; k[j][3] = before + c.w;
+            const char* __restrict__ GH = reinterpret_cast<const char*>(a.tabGH + gh_at(gs[j], 0, a.cap));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) gh[j][i] = *reinterpret_cast<const float2*>(GH + (unsigned)k[j][i] * (unsigned)sizeof(float2));
+        }
+#pragma unroll
+        for (int j = 0; j < kMemoInst; ++j) {
+            const int N1 = entries_of(K[j]) + 1;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) E[i][j] = fmaf(tri[i], K[j].z * (float)(N1 - k[j][i]), fmaf(Lf[i], gh[j][i].y, gh[j][i].x));
+        }
     }
     __syncthreads();        // (every wave has its counters)
 #pragma unroll
@@ -2240,6 +2317,12 @@ static bool dense_rows(const gr_fleet* f)
 
 bool needs_marks(const gr_fleet* f, int64_t n) { return !pair_by_pair(f, n) && !dense_rows(f); }
 
+// Whether the instances are expected to have few entries in a block of rows (see k_memo): by the room of their tables and the
+// rows there may be.  Whole calls, us, before / this way: scan of 4 096 instances x 512, lengths up to 16 384 (8 an instance and block) 109.2 /
+// 103.5, refresh and 262 144 requests 72.1 / 70.9; 2 000 x 300, 60 000 requests 42.6 / 41.9; scan of 1 309 x 125 (2) 39.8 / 40.0.  1 024 x 1 000
+// with lengths up to 4 096 have 64, and are never few.
+static bool sparse_rows(const gr_fleet* f, int64_t max_rows) { return f->cap <= 512 && (int64_t)f->cap * kMemoU <= 8 * max_rows; }
+
 // How the rows of a pass are found.  (Lines and classes first are for fleets of more runs than have a row per length.)
 struct RowsOf {
     const int* totals;
@@ -2388,10 +2471,11 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
         const dim3 grid((unsigned)((f->n_run + 7) / 8 * 8), (unsigned)(1 + (max_rows + kMemoU - 1) / kMemoU));
         ProfScope ps(f, kMemoRoute + off, s);
 #define GR_LAUNCH_MEMO(B, D, O) do { \
-        if (f->cap > 1024) hipLaunchKernelGGL((k_memo<4, B, D, O>), grid, dim3(kBlock), 0, s, m); \
-        else if (f->cap > 512) hipLaunchKernelGGL((k_memo<2, B, D, O>), grid, dim3(kBlock), 0, s, m); \
-        else hipLaunchKernelGGL((k_memo<1, B, D, O>), grid, dim3(kBlock), 0, s, m); } while (0)
-        if (blocks) GR_LAUNCH_MEMO(true, false, false);
+        if (f->cap > 1024) hipLaunchKernelGGL((k_memo<4, B, D, O, false>), grid, dim3(kBlock), 0, s, m); \
+        else if (f->cap > 512) hipLaunchKernelGGL((k_memo<2, B, D, O, false>), grid, dim3(kBlock), 0, s, m); \
+        else hipLaunchKernelGGL((k_memo<1, B, D, O, false>), grid, dim3(kBlock), 0, s, m); } while (0)
+        if (blocks && sparse_rows(f, max_rows)) hipLaunchKernelGGL((k_memo<1, true, false, false, true>), grid, dim3(kBlock), 0, s, m);
+        else if (blocks) GR_LAUNCH_MEMO(true, false, false);
         else if (own) GR_LAUNCH_MEMO(false, true, true);
         else if (dense) GR_LAUNCH_MEMO(false, true, false);
         else GR_LAUNCH_MEMO(false, false, false);
