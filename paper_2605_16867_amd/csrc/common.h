@@ -203,6 +203,7 @@ struct gr_fleet {
     int* totals = nullptr;    // [4] -, distinct lengths, 1: flags that the risk scan's build has not set (zero between calls)
     float* memo = nullptr;       // [row_cap / kMemoU][n_run][kMemoU][kMemoP] E per distinct length and position
     float* grp_min = nullptr;    // [row_cap][run_pad] least E of each run, per row (see runs_at)
+    float* row_min = nullptr;    // [row_cap][run_pad] the same row by row, of a routing batch whose classes are looked at first
     uint32_t* run_rank = nullptr;   // [n_run] runs whose first instance is more capable than the run's first
     int* run_at = nullptr;          // [n_run] the run of each rank
     uint32_t* pos_thr = nullptr;    // [m_pos] runs whose first instance is more capable than the position's

@@ -732,6 +732,7 @@ struct ClassArgs {
     const int* order;
     const float *memo, *grp_min;
     const float4* run_k;
+    float* row_min;       // see k_class
     float* class_min;
     uint2* class_next;
     float4* cls_bound;
@@ -743,10 +744,17 @@ struct ClassArgs {
 // class, so these decide a request's least latency (k_select).  A workgroup takes 64 rows and one
 // class, a lane per row (the reads are whole cache lines) and a quarter of the class's runs per wave: the
 // runs first, then four positions per wave of the run that holds the least E.
-template <bool kBlocks>
+//
+// kRows: the runs' minima are left row by row as well, for a selection many of whose requests get as far as the runs (a
+// request's 16 lanes read 16 runs from one cache line).  They pass here anyway and are turned in LDS; written row by row
+// by the table's workgroups, four bytes to a line, they cost the table 3 us of 26 and this kernel's reads 2 of 7.5 (refresh and 262 144
+// requests, 4 096 instances: 70.4 us before, 68.4 with both; in blocks alone 66.6, but 101.5 instead of 94.2 with deadlines that many meet).
+template <bool kRows>
 __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
 {
-    constexpr int kW = kBlock / kWave;
+    constexpr bool kBlocks = true;
+    constexpr int kW = kBlock / kWave, kAhead = 8, kCols = kAhead * kW;
+    __shared__ float turned[kRows ? kWave * (kCols + 1) : 1];
     static_assert(kMemoU % kWave == 0, "the rows of a workgroup are in one block");
     __shared__ float m1_lds[kW][kWave], m2_lds[kW][kWave];
     __shared__ int r1_lds[kW][kWave], low_lds[kW][kWave];
@@ -775,17 +783,32 @@ __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
 
     float m1 = inf, m2 = inf;       // of this wave's runs: the least, the least of the others
     int r1 = 0;
-    constexpr int kAhead = 8;
-    for (int r0 = w; r0 < cr.y; r0 += kAhead * kW) {
+    for (int b = 0; b < cr.y; b += kCols) {
+        const int r0 = b + w;
         float e[kAhead];
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) e[k] = runs[(size_t)min(r0 + k * kW, cr.y - 1) * kRunStride<kBlocks>];
+        if constexpr (kRows) {
+            if (b) __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) turned[lane * (kCols + 1) + k * kW + w] = e[k];
+        }
 #pragma unroll
         for (int k = 0; k < kAhead; ++k) {
             const int r = r0 + k * kW;
             if (r >= cr.y) break;
             if (e[k] < m1) { m2 = m1; m1 = e[k]; r1 = r; }
             else m2 = fminf(m2, e[k]);
+        }
+        if constexpr (kRows) {
+            __syncthreads();
+            const int col = threadIdx.x % kCols;
+            float* __restrict__ out = a.row_min + (size_t)u0 * a.run_pad + cr.x + b + col;
+#pragma unroll
+            for (int i = 0; i < kWave * kCols / kBlock; ++i) {
+                const int row = threadIdx.x / kCols + i * (kBlock / kCols);
+                if (b + col < cr.y && u0 + row < U) out[(size_t)row * a.run_pad] = turned[row * (kCols + 1) + col];
+            }
         }
     }
     m1_lds[w][lane] = m1; m2_lds[w][lane] = m2; r1_lds[w][lane] = r1;
@@ -2451,10 +2474,10 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     const bool by_lines = select && (blended || f->n_class > kGroup) && n >= (migrate ? kLinesScanMin : kByClassMin) &&
                           f->n_run > (migrate && n >= kByClassMany ? 2 : 5) * kGroup;
     const bool listed = by_lines && migrate && f->n_run <= kRestRuns;
-    // The runs' minima in blocks of rows where few requests get as far as the runs (6 us less for the
-    // table of 7 061 rows x 4 096 instances); row by row where many may: a request's 16 lanes then read 16
-    // runs from one cache line, not from sixteen.
-    const bool blocks = by_class && migrate;
+    // The runs' minima in blocks of rows where the classes are looked at first (6 us less for the
+    // table of 7 061 rows x 4 096 instances); else row by row: a request's 16 lanes then read 16
+    // runs from one cache line, not from sixteen.  (Of a routing batch many requests may get as far as the runs, see k_class.)
+    const bool blocks = by_class, rows_too = by_class && !migrate;
     const bool own = dense && with_order;
     {
         MemoArgs m{};
@@ -2484,16 +2507,16 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     if (by_class) {
         ClassArgs c{};
         c.totals = f->totals; c.cls_run = f->cls_run; c.order = f->order; c.memo = f->memo; c.grp_min = f->grp_min;
-        c.run_k = f->run_k; c.class_min = f->class_min; c.class_next = f->class_next; c.cls_bound = f->cls_bound;
+        c.run_k = f->run_k; c.row_min = f->row_min; c.class_min = f->class_min; c.class_next = f->class_next; c.cls_bound = f->cls_bound;
         c.n_class = f->n_class; c.c_pad = f->c_pad; c.n_run = f->n_run; c.run_pad = f->run_pad;
         ProfScope ps(f, kClassRoute + off, s);
         const dim3 grid((unsigned)((max_rows + kWave - 1) / kWave * f->n_class));
-        if (blocks) hipLaunchKernelGGL(k_class<true>, grid, dim3(kBlock), 0, s, c);
+        if (rows_too) hipLaunchKernelGGL(k_class<true>, grid, dim3(kBlock), 0, s, c);
         else hipLaunchKernelGGL(k_class<false>, grid, dim3(kBlock), 0, s, c);
     }
     if (select) {
         SelectArgs a{};
-        a.s = src; a.len_row = rows.len_row; a.order = f->order; a.memo = f->memo; a.grp_min = f->grp_min; a.run_k = f->run_k;
+        a.s = src; a.len_row = rows.len_row; a.order = f->order; a.memo = f->memo; a.grp_min = rows_too ? f->row_min : f->grp_min; a.run_k = f->run_k;
         a.posK = f->posK; a.posKey = f->posKey; a.run_rank = f->run_rank; a.pos_thr = f->pos_thr; a.run_at = f->run_at; a.cls_run = f->cls_run; a.class_min = f->class_min; a.class_next = f->class_next; a.clsK = f->clsK; a.cls_bound = f->cls_bound;
         a.out_inst = out.inst; a.out_slack = out.slack; a.out_fallback = out.fallback;
         a.run_pad = f->run_pad; a.n_run = f->n_run; a.n_class = f->n_class; a.c_pad = f->c_pad;
