@@ -485,6 +485,7 @@ constexpr int kFewEntries = 16;
 template <int kEighths, bool kBlocks, bool kDense, bool kOwn, bool kSparse>     // kEighths x 64 eighths of an instance's lengths at most
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMemoPerSimd, kMemoPerSimd))) void k_memo(MemoArgs a)
 {
+    if constexpr (kDense) fetch_args<MemoArgs>();
     __shared__ __align__(16) int lds[kMemoU * kTileRow];       // the counters, then the tile
     static_assert(kMemoU * kTileRow >= kMemoWaves * kMemoInst * kMemoU, "room for the counters");
     // (the first workgroups rank the runs for the selection: next to the others, not behind them)
@@ -1100,6 +1101,7 @@ struct Selection {
 template <bool kMigrate, int kChunks>
 __global__ __launch_bounds__(kBlock) void k_select(SelectArgs a)
 {
+    fetch_args<SelectArgs>();
     const int sub = threadIdx.x % kGroup;
     const int64_t i = a.first + (int64_t)blockIdx.x * (kBlock / kGroup) + threadIdx.x / kGroup;
     if (i >= a.s.n) return;
@@ -1140,6 +1142,7 @@ __device__ __forceinline__ uint32_t lanes_or(uint32_t v)
 template <bool kMigrate, int kRuns, bool kBlend>
 __global__ __launch_bounds__(kBlock) void k_select_lanes(SelectArgs a)
 {
+    fetch_args<SelectArgs>();
     // of each run: its least delta, gamma, largest delta, its rank as a bit; the run of each rank; delta and gamma by position
     __shared__ float4 of_run[kRuns];
     __shared__ int at_rank[kRuns];
@@ -1907,6 +1910,7 @@ __device__ __forceinline__ int count_pieces(const uint4 (&w)[kW], uint32_t L)
 template <bool kMigrate, int kLanes, int kU, int kS, int kB>
 __global__ __launch_bounds__(kLanes <= 64 ? kBlock : kLanes) void k_direct(DirectArgs a)
 {
+    fetch_args<DirectArgs>();
     constexpr int kThreads = kLanes <= 64 ? kBlock : kLanes;
     __shared__ int sums[kThreads / kWave];
     if (kMigrate && blockIdx.x == gridDim.x - 1) return count_flagged(a.count, kThreads, sums);

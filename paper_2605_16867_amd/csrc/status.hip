@@ -280,6 +280,7 @@ constexpr long long kLowMask = (1ll << kLowBits) - 1;
 template <int kEPL>
 __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
 {
+    fetch_args<BuildArgs>();
     extern __shared__ uint32_t smem[];
     constexpr int kCap = kWave * kEPL;
     constexpr int kIdxBits = log2_of(kCap);
@@ -1171,6 +1172,7 @@ __device__ __forceinline__ void clamp_instance(const BuildArgs& a, InstanceIn& i
 template <int kEPL, int kSplit, bool kFit, bool kQuiet>
 __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_build_lean(BuildArgs a)
 {
+    if constexpr (kSplit > 1) fetch_args<BuildArgs>();
     extern __shared__ uint32_t smem[];
     constexpr int kTab = kWave * kEPL * kSplit;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -1214,8 +1216,6 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
 // 256 instances x 512, 32 rounds of 64, with the status build 400 us, this way 333.  An instance only finds out
 // whether it is chosen itself: looking for everybody's choice took 17 us a round instead of 10.5 (8 bytes of every instance
 // as scalars, one after the other), and 12.3 with those read a lane each.
-// (in the order in which they are needed: a launch reads them anew, a line of 64 bytes at a time; the 33 launches of 2 048 requests,
-// 64 at a time, take 338 us this way, 339 with next_n at the end, 345 with it right behind b)
 struct FeedArgs {
     BuildArgs b;                        // with the chunk that is decided here
     const int *next_ctx0, *next_len, *next_exclude;     // the chunk to offer for
@@ -1274,6 +1274,7 @@ __device__ __forceinline__ unsigned long long wave_or_u64(unsigned long long v)
 template <int kEPL, int kSplit>
 __global__ __launch_bounds__(kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_feedback(FeedArgs f)
 {
+    fetch_args<FeedArgs>();
     extern __shared__ uint32_t smem[];
     __shared__ uint32_t share[kSplit][kWave];
     __shared__ unsigned long long met_by[kSplit][2];
