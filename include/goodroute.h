@@ -100,7 +100,7 @@ enum {
  *                                    worst case whatever the batches turn out to be (313 MB for 4 096
  *                                    instances of 6 classes and max_len 16 384),
  *   at most 64 MB, or 1 024 * n_inst bytes if that is more   rows of that table for out_T,
- *   544 * n_inst bytes               feedback routing, up to 512 instances: what they offer a chunk,
+ *   (24 * cap + 608) * n_inst bytes  feedback routing, up to 512 instances: what they offer a chunk, sums behind the tables,
  *   0.4 MB                           selections of small batches on fleets of more than 4 096 instances,
  * plus a few arrays of n_inst, M' or max_len + 1 words.
  */

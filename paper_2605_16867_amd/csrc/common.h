@@ -93,6 +93,13 @@ struct DirectPart {
     uint32_t g, T;              // the feasible choice and its latency
 };
 
+// Feedback routing: the sums behind an instance's table as it was built last.
+struct FeedBase {
+    double ctx, q_ctx;      // of all contexts, of those that are prefilled first
+    int n, listed, room;    // entries; requests of its list among them; the most of those that there is room for
+    int pad;
+};
+
 enum KernelId {
     kBuild = 0, kRank, kMarkRoute, kScanRoute, kMemoRoute, kClassRoute, kLinesRoute, kSelectRoute,
     kScanMigrate, kMemoMigrate, kClassMigrate, kLinesMigrate, kSelectMigrate, kHitsRoute, kPairsRoute, kDirect, kDirectMerge, kFeedback,
@@ -203,7 +210,7 @@ struct gr_fleet {
     int* totals = nullptr;    // [4] -, distinct lengths, 1: flags that the risk scan's build has not set (zero between calls)
     float* memo = nullptr;       // [row_cap / kMemoU][n_run][kMemoU][kMemoP] E per distinct length and position
     float* grp_min = nullptr;    // [row_cap][run_pad] least E of each run, per row (see runs_at)
-    float* row_min = nullptr;    // [row_cap][run_pad] the same row by row, of a routing batch whose classes are looked at first
+    float* row_min = nullptr;    // [row_cap][run_pad] (behind grp_min) the same row by row, of a routing batch whose classes are looked at first
     uint32_t* run_rank = nullptr;   // [n_run] runs whose first instance is more capable than the run's first
     int* run_at = nullptr;          // [n_run] the run of each rank
     uint32_t* pos_thr = nullptr;    // [m_pos] runs whose first instance is more capable than the position's
@@ -229,6 +236,10 @@ struct gr_fleet {
     uint32_t* feed_T = nullptr;             // [2][M][kWave] latency as an integer of the same order; all ones: not allowed
     unsigned long long* feed_met = nullptr; // [2][M] bit j: request j's deadline is met
     unsigned long long* feed_key = nullptr; // [2][M] d_g as an integer that falls with it
+    // the sums behind the tables (Y_k, X_k and the contexts of the k shortest), by segment, and those of whole instances (one allocation)
+    double2* feed_yx = nullptr;             // [M][cap + 1]
+    double* feed_c = nullptr;               // [M][cap + 1]
+    gr::FeedBase* feed_base = nullptr;      // [M]
     gr::DirectPart* direct_part = nullptr;       // [kDirectParts] selections of the parts of a wide fleet, scored pair by pair
 };
 

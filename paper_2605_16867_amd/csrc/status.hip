@@ -793,6 +793,10 @@ struct Offer {
     int L;
     float c0, T;
     unsigned long long key;     // d_g as an integer that falls with it
+    // the sums that the table is made from, kept for the rounds to come (null: not asked for), see gr_fleet
+    double2* sums_yx;
+    double* sums_c;
+    FeedBase* base;
 };
 
 // kEPL sort words per lane; kSplit waves share an instance (kSplit = 1: a workgroup is four instances, a wave each; 2 or 4:
@@ -806,7 +810,7 @@ struct Offer {
 //
 // kQuiet: nobody asks for finish times or flags.  With an `offer` (of the instance's first wave) the latency of its
 // request is formed from the new table, as k_direct would.
-template <int kEPL, int kSplit, int kTab, bool kQuiet, bool kOffer = false>
+template <int kEPL, int kSplit, int kTab, bool kQuiet, bool kOffer = false, bool kSums = false>
 __device__ __forceinline__ void build_instance(const BuildArgs& a, const InstanceIn& in, int wave, uint32_t* smem, Offer* offer = nullptr)
 {
     const bool risk = !kQuiet && a.act_budget;
@@ -1014,6 +1018,11 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
             // black-box finish: d per remaining token; a queued request also waits and prefills
             fin = keep * fin + a.lam * (idx[r] < A ? bd * Rd : (bq + bp * cd) + bd * Rd);
         }
+        if constexpr (kSums) {      // of the segment after this position
+            const size_t at = (size_t)g * (kTab + 1) + first + lane * kEPL + r + 1;
+            offer->sums_yx[at] = make_double2(Y, X);
+            offer->sums_c[at] = Pc;
+        }
         fin32[r] = (float)fin;
         if (risk) late |= (unsigned)(fin > (double)bud[r]) << r;     // decided in double precision
         tR[r] = r < mine ? (uint16_t)Ri[r] : (uint16_t)0xFFFFu;
@@ -1112,6 +1121,11 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
     float4 K;
     if constexpr (kOffer) own_figures(Gq0, H0, d, K);
     if (lane == 0 && part == 0) {
+        if constexpr (kSums) {
+            offer->sums_yx[(size_t)g * (kTab + 1)] = make_double2(0.0, 0.0);
+            offer->sums_c[(size_t)g * (kTab + 1)] = 0.0;
+            offer->base[g] = FeedBase{Ctot, qtot, N, in.pend + (int)__popcll(in.joins), min(kTab, a.max_entries - A - Q), 0};
+        }
         if constexpr (!kOffer) own_figures(Gq0, H0, d, K);
         a.tabGH[gh_at(g, 0, kTab)] = make_float2((float)Gq0, (float)H0);
         a.instK[g] = K;
@@ -1213,7 +1227,7 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
 // What bounds it is the chain of a round: the offers (64 requests x 256 instances are 64 KB for every workgroup, from
 // L2), the choice, then the rebuild, whose table is still in LDS when the next requests are looked up in it.  A round was
 // two launches, a scoring and a rebuild, each with its own start and its own reads of what the other had just written:
-// 256 instances x 512, 32 rounds of 64, with the status build 400 us, this way 333.  An instance only finds out
+// 256 instances x 512, 32 rounds of 64, with the status build 400 us, this way 329.  An instance only finds out
 // whether it is chosen itself: looking for everybody's choice took 17 us a round instead of 10.5 (8 bytes of every instance
 // as scalars, one after the other), and 12.3 with those read a lane each.
 struct FeedArgs {
@@ -1231,9 +1245,23 @@ struct FeedArgs {
     uint8_t* out_fallback;
 };
 
+// Where what comes is added to the tables' sums (see gr_fleet) instead of building them anew.
+struct FeedAddArgs {
+    FeedArgs f;
+    int move;
+    double2* sums_yx;
+    double* sums_c;
+    FeedBase* base;
+};
+
+// What such a launch does to the tables: nothing; all of them are built; what has come since an instance's table was
+// built is added to its sums; all that have been given requests since are built.
+enum FeedMove { kFeedNone = 0, kFeedAll, kFeedAdd, kFeedTouched };
+constexpr int kFeedListed = 32;      // requests added to an instance's sums before its table is built anew (a wave holds them)
+
 // Segment and latency of a request in the instance's table as it stands, in two steps as k_direct.
 template <int kTab>
-__device__ __forceinline__ float latency_in_table(const BuildArgs& a, int g, float c0, int L)
+__device__ __forceinline__ int segment_in_table(const BuildArgs& a, int g, int L)
 {
     constexpr int kS = split_count(kTab), kStride = kTab / kS;
     const uint4* __restrict__ S = reinterpret_cast<const uint4*>(a.tabS + (size_t)g * kS);
@@ -1247,6 +1275,13 @@ __device__ __forceinline__ float latency_in_table(const BuildArgs& a, int g, flo
     for (int i = 0; i < kStride / 8; ++i) w[i] = R[i];
 #pragma unroll
     for (int i = 0; i < kStride / 8; ++i) k += count_upto(w[i], (uint32_t)L);
+    return k;
+}
+
+template <int kTab>
+__device__ __forceinline__ float latency_in_table(const BuildArgs& a, int g, float c0, int L)
+{
+    const int k = segment_in_table<kTab>(a, g, L);
     return latency_at(c0, L, a.instK[g], a.tabGH[gh_at(g, k, kTab)], k);
 }
 
@@ -1271,15 +1306,27 @@ __device__ __forceinline__ unsigned long long wave_or_u64(unsigned long long v)
     return ((unsigned long long)wave_or_u32((uint32_t)(v >> 32)) << 32) | wave_or_u32((uint32_t)v);
 }
 
-template <int kEPL, int kSplit>
-__global__ __launch_bounds__(kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_feedback(FeedArgs f)
+//
+// kAdd: the tables stay as they were built last, with the sums behind them, and what has come since is added to those for
+// every request anew (see adds_up), in fp64, so that a segment comes to the same (Gq, H) bit for bit.  One wave more than share the
+// instance gathers what it takes (the segments of the table, the list since then) while the others decide.  A round of one request on 256
+// instances 9.6 us with a rebuild, 6.6 this way; of 64 requests 10.0 / 9.3.
+template <int kEPL, int kSplit, bool kAdd>
+__global__ __launch_bounds__(kWave * (kSplit + kAdd), (kEPL <= 8 ? 4 : 1)) void k_feedback(std::conditional_t<kAdd, FeedAddArgs, FeedArgs> args)
 {
-    fetch_args<FeedArgs>();
     extern __shared__ uint32_t smem[];
     __shared__ uint32_t share[kSplit][kWave];
     __shared__ unsigned long long met_by[kSplit][2];
     constexpr int kTab = kWave * kEPL * kSplit;
+    fetch_args<decltype(args)>();
+    const auto of = [&]() -> const FeedArgs& {
+        if constexpr (kAdd) return args.f;
+        else return args;
+    };
+    const FeedArgs& f = of();
     const BuildArgs& a = f.b;
+    int move = kFeedNone;
+    if constexpr (kAdd) move = args.move;
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     InstanceIn in;
     in.g = blockIdx.x;
@@ -1287,15 +1334,38 @@ __global__ __launch_bounds__(kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_feedbac
     const int g = in.g, M = a.n_inst;
     const int a_begin = a.act_off[g], a_end = a.act_off[g + 1], q_begin = a.q_off[g], q_end = a.q_off[g + 1];
     const int pend = a.pend_cnt[g];
+    const int touched = move == kFeedTouched ? a.pend_touched[g] : 0;
     Offer offer{};
+    if constexpr (kAdd) { offer.sums_yx = args.sums_yx; offer.sums_c = args.sums_c; offer.base = args.base; }
     float D = 0.f;
     int ex = -1;
-    if (f.next_n && wave == 0) {
+    // what the sums are added up from, on its way while the chunk is decided: of the table the requests' segments, and a
+    // lane each what has come since
+    FeedBase base{};
+    ClassCoef cc{};
+    double2 yx{};
+    double pc = 0.0;
+    int k = 0, since_ctx = 0, since_len = 0, join_ctx = 0, join_len = 0;
+    const bool adds = kAdd && move == kFeedAdd && wave == kSplit;
+    if (kAdd && move == kFeedAdd) base = offer.base[g];
+    if (f.next_n && (wave == 0 || adds)) {
         const int j = min(lane, f.next_n - 1);
         offer.L = min(max(f.next_len[j], 0), a.max_len);
         offer.c0 = (float)f.next_ctx0[j];
         D = f.next_budget[j];
         if (f.next_exclude) ex = f.next_exclude[j];
+        if (adds) {
+            cc = a.cls[a.inst_class[g]];
+            const int c = min(lane, a.chunk_n - 1);
+            join_ctx = a.chunk_ctx0[c];
+            join_len = a.chunk_len[c];
+            const size_t at = (size_t)g * kTab + min(base.listed + lane, kTab - 1);
+            since_ctx = a.pend_prompt[at];
+            since_len = a.pend_len[at];
+            k = segment_in_table<kTab>(a, g, offer.L);
+            yx = offer.sums_yx[(size_t)g * (kTab + 1) + k];
+            pc = offer.sums_c[(size_t)g * (kTab + 1) + k];
+        }
     }
 
     if (a.chunk_n) {
@@ -1304,7 +1374,7 @@ __global__ __launch_bounds__(kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_feedbac
         const uint32_t own = f.T_in[(size_t)g * kWave + lane];
         const unsigned long long own_key = f.key_in[g], own_met = f.met_in[g];
         unsigned long long any = 0, above = 0;         // requests whose deadline is met by somebody, by somebody more capable
-        for (int h = threadIdx.x; h < M; h += kSplit * kWave) {
+        for (int h = threadIdx.x; (!kAdd || wave < kSplit) && h < M; h += kSplit * kWave) {
             const unsigned long long met = f.met_in[h], key = f.key_in[h];
             any |= met;
             above |= key < own_key || (key == own_key && h < g) ? met : 0ull;
@@ -1312,7 +1382,7 @@ __global__ __launch_bounds__(kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_feedbac
         // the waves share the latencies; those at lower indices count as one less, so that `own` has to be below them
         const int per = (M + kSplit - 1) / kSplit, h0 = wave * per, n_here = min(per, M - h0);
         uint32_t least = ~0u;
-        if (n_here > 0) {
+        if ((!kAdd || wave < kSplit) && n_here > 0) {
             constexpr int kAhead = 16;
             const uint32_t* __restrict__ row = f.T_in + (size_t)h0 * kWave + lane;
             const int end = n_here * kWave, below = (g - h0) * kWave;
@@ -1332,8 +1402,8 @@ __global__ __launch_bounds__(kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_feedbac
         }
         any = wave_or_u64(any);
         above = wave_or_u64(above);
-        share[wave][lane] = least;
-        if (lane == 0) { met_by[wave][0] = any; met_by[wave][1] = above; }
+        if (!kAdd || wave < kSplit) share[wave][lane] = least;
+        if ((!kAdd || wave < kSplit) && lane == 0) { met_by[wave][0] = any; met_by[wave][1] = above; }
         __syncthreads();
         any = above = 0;
 #pragma unroll
@@ -1357,20 +1427,69 @@ __global__ __launch_bounds__(kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_feedbac
         in.joins = __ballot(mine);
     }
 
-    if (a.chunk_n && (in.joins || !a.only_touched)) {
+    const int joined = __popcll(in.joins);
+    const bool rebuild = !kAdd ? a.chunk_n && (in.joins || !a.only_touched)
+                         : move == kFeedAdd ? pend + joined - base.listed > kFeedListed
+                         : move == kFeedTouched ? in.joins || touched : move == kFeedAll;
+    if (rebuild) {
+        if (kAdd && wave == kSplit) return;
         clamp_instance<kTab>(a, in, a_begin, a_end, q_begin, q_end, pend);
         const int N = in.A + in.Q + in.P;
         bool built = false;
         if constexpr (kEPL >= 4)
-            if (N <= kTab / 4) { build_instance<kEPL / 4, kSplit, kTab, true, true>(a, in, wave, smem, &offer); built = true; }
+            if (N <= kTab / 4) { build_instance<kEPL / 4, kSplit, kTab, true, true, kAdd>(a, in, wave, smem, &offer); built = true; }
         if constexpr (kEPL >= 2)
-            if (!built && N <= kTab / 2) { build_instance<kEPL / 2, kSplit, kTab, true, true>(a, in, wave, smem, &offer); built = true; }
-        if (!built) build_instance<kEPL, kSplit, kTab, true, true>(a, in, wave, smem, &offer);
+            if (!built && N <= kTab / 2) { build_instance<kEPL / 2, kSplit, kTab, true, true, kAdd>(a, in, wave, smem, &offer); built = true; }
+        if (!built) build_instance<kEPL, kSplit, kTab, true, true, kAdd>(a, in, wave, smem, &offer);
+    } else if (kAdd && move == kFeedAdd) {
+        if (!adds) return;
+        if (in.joins) {      // they join the list here
+            const int nth = pend + __popcll(in.joins & ((1ull << lane) - 1ull));
+            if (((in.joins >> lane) & 1ull) && nth < kTab) {
+                a.pend_prompt[(size_t)g * kTab + nth] = join_ctx;
+                a.pend_len[(size_t)g * kTab + nth] = join_len;
+            }
+            if (lane == 0) { a.pend_cnt[g] = pend + joined; a.pend_touched[g] = 1; }
+        }
+        // Every sum is one of integers below 2^53, so the order does not matter, and what the segments come to is what a
+        // build would leave in the table (as in build_instance).  Requests beyond the instance's room are none.
+        double sum_ctx = 0.0;
+        int N = base.n, room = max(base.room - base.listed, 0);
+        const auto add = [&](int ctx, int length) {
+            const int R = min(max(length, 0), a.max_len);
+            const double Rd = (double)R, cd = (double)ctx, xe = fma(cd, Rd, (double)(R * (R - 1) / 2));
+            const bool left = R <= offer.L;
+            yx.x += left ? Rd : 0.0;
+            yx.y += left ? xe : 0.0;
+            pc += left ? cd : 0.0;
+            k += left;
+            sum_ctx += cd;
+            ++N;
+        };
+        for (int i = 0; i < pend - base.listed && room > 0; ++i, --room)
+            add(__builtin_amdgcn_readlane(since_ctx, i), __builtin_amdgcn_readlane(since_len, i));
+        for (unsigned long long m = in.joins; m && room > 0; m &= m - 1, --room) {
+            const int i = __ffsll((long long)m) - 1;
+            add(__builtin_amdgcn_readlane(join_ctx, i), __builtin_amdgcn_readlane(join_len, i));
+        }
+        const bool blended = a.lam != 0.0;
+        const double Ctot = base.ctx + sum_ctx, keep = 1.0 - a.lam, q = cc.delta * (base.q_ctx + sum_ctx);
+        const double bq = blended ? a.emaQ[g] : 0.0, bp = blended ? a.emaP[g] : 0.0, bd = blended ? a.emaD[g] : 0.0;
+        double Gq = k ? fma(cc.gamma, yx.y, fma(cc.beta, yx.x, q)) : q;
+        double Hs = fma(cc.gamma, Ctot - pc, fma(cc.beta, (double)(N - k + 1), cc.alpha));
+        double d = fma(cc.gamma, Ctot, fma(cc.beta, (double)N, cc.alpha));
+        if (blended) {
+            Gq = keep * Gq + a.lam * bq;
+            Hs = keep * Hs + a.lam * bd;
+            d = keep * d + a.lam * bd;
+        }
+        offer.T = latency_at(offer.c0, offer.L, inst_coef(a, cc, bp, N), make_float2((float)Gq, (float)Hs), k);
+        offer.key = falling_bits(d);
     } else if (f.next_n && wave == 0) {
         offer.T = latency_in_table<kTab>(a, g, offer.c0, offer.L);
         offer.key = falling_bits(a.hD[g]);
     }
-    if (!f.next_n || wave != 0) return;
+    if (!f.next_n || !(wave == 0 || (adds && !rebuild))) return;
     const float Dc = D > FLT_MAX ? FLT_MAX : D;
     const bool ok = g != ex;      // (batches of this size take infinite latencies for latencies, see pairs_finite)
     const unsigned long long met = __ballot(ok && offer.T <= Dc);
@@ -1695,8 +1814,9 @@ int status_prepare()
     GR_SET_SPLIT(1, 2); GR_SET_SPLIT(2, 2); GR_SET_SPLIT(4, 2); GR_SET_SPLIT(8, 2); GR_SET_SPLIT(16, 2);
     GR_SET_SPLIT(1, 4); GR_SET_SPLIT(2, 4); GR_SET_SPLIT(4, 4); GR_SET_SPLIT(8, 4);
 #undef GR_SET_SPLIT
-    set(k_feedback<1, 2>, split_lds<2, 2>()); set(k_feedback<1, 4>, split_lds<4, 4>()); set(k_feedback<2, 4>, split_lds<8, 4>());
-    set(k_feedback<4, 4>, split_lds<16, 4>()); set(k_feedback<8, 4>, split_lds<32, 4>());
+#define GR_SET_FEEDBACK(E, W) set(k_feedback<E, W, false>, split_lds<E * W, W>()); set(k_feedback<E, W, true>, split_lds<E * W, W>())
+    GR_SET_FEEDBACK(1, 2); GR_SET_FEEDBACK(1, 4); GR_SET_FEEDBACK(2, 4); GR_SET_FEEDBACK(4, 4); GR_SET_FEEDBACK(8, 4);
+#undef GR_SET_FEEDBACK
     set(k_build_capped<1>, 3 * word * 1); set(k_build_capped<2>, 3 * word * 2); set(k_build_capped<4>, 3 * word * 4);
     set(k_build_capped<8>, 3 * word * 8); set(k_build_capped<16>, 3 * word * 16); set(k_build_capped<32>, 3 * word * 32);
     return ok ? GR_OK : GR_ERR_HIP;
@@ -1758,15 +1878,32 @@ bool feedback_by_round(const gr_fleet* f, int64_t chunk)
     return f->feed_T && !f->has_cap && chunk <= kWave && waves_per_instance(f->epl, f->n_inst) > 1 && pair_by_pair(f, chunk);
 }
 
+// Whether the tables stay as they are while requests are routed and what comes is added to their sums: for three rounds and more
+// (the first launch then builds all tables, to have the sums), where an instance is hardly chosen twice a round (each
+// request of its list is a step of a chain of its own) and the rounds are not bound by the reads of the offers.  Whole
+// calls, us, chosen ones rebuilt / added up (`N/c`: N instances, chunks of c):
+//   256/1, 100 requests 966 / 665   256/1, 3 38.1 / 35.5   256/8, 200 252 / 186   32/1, 200 1 350 / 1 077   8/8, 100 99 / 94   500/1, 100 1 162 / 1 110
+//   256/64, 2 048 329 / 308   256/32, 1 000 302 / 286   128/32, 1 000 256 / 243   64/16, 500 234 / 209   512/40, 2 048 655 / 641
+//   64/64, 2 048 266 / 299   128/64, 1 500 195 / 203   32/32, 600 144 / 148   500/64, 2 000 410 / 416
+static bool adds_up(int64_t M, int64_t chunk, int64_t rounds)
+{
+    return rounds >= 3 && (chunk <= 8 || (4 * chunk <= M && chunk * M <= 20480));
+}
+
 int launch_feedback(gr_fleet* f, const StatusIn& in, const FeedbackIn& r, hipStream_t s)
 {
-    FeedArgs a{};
+    FeedAddArgs add{};
+    FeedArgs& a = add.f;
     a.b = build_args(f, in);
     const size_t M = f->n_inst;
     const int64_t rounds = (r.n + r.chunk - 1) / r.chunk;
+    const bool adding = adds_up((int64_t)M, r.chunk, rounds);
+    add.sums_yx = f->feed_yx; add.sums_c = f->feed_c; add.base = f->feed_base;
     for (int64_t k = 0; k <= rounds; ++k) {       // launch k decides chunk k - 1 and offers for chunk k
         const int64_t at = k * r.chunk, was = at - r.chunk;
         a.b.chunk_n = k ? (int)std::min<int64_t>(r.n - was, r.chunk) : 0;
+        const int64_t all = r.current ? 0 : 1;      // the launch that builds every table anew
+        add.move = k == rounds ? kFeedTouched : k > all ? kFeedAdd : k == all ? kFeedAll : kFeedNone;
         a.b.only_touched = r.current || k != 1;
         if (k) {
             a.b.chunk_ctx0 = r.ctx0 + was; a.b.chunk_len = r.pred_len + was;
@@ -1784,7 +1921,9 @@ int launch_feedback(gr_fleet* f, const StatusIn& in, const FeedbackIn& r, hipStr
         ProfScope ps(f, kFeedback, s);
         const int waves = waves_per_instance(f->epl, f->n_inst);
 #define GR_LAUNCH_FEEDBACK(E, W) \
-        hipLaunchKernelGGL((k_feedback<E / W, W>), dim3((unsigned)M), dim3(W * kWave), (split_lds<E, W>()), s, a); break
+        if (adding) hipLaunchKernelGGL((k_feedback<E / W, W, true>), dim3((unsigned)M), dim3((W + 1) * kWave), (split_lds<E, W>()), s, add); \
+        else hipLaunchKernelGGL((k_feedback<E / W, W, false>), dim3((unsigned)M), dim3(W * kWave), (split_lds<E, W>()), s, a); \
+        break
         switch (f->epl * 8 + waves) {
             case 2 * 8 + 2: GR_LAUNCH_FEEDBACK(2, 2);
             case 4 * 8 + 4: GR_LAUNCH_FEEDBACK(4, 4);
