@@ -479,11 +479,13 @@ __device__ inline int tile_at(int row, int piece) { return row * kTileRow + 4 * 
 // kSparse: an instance has few entries in a block of rows (see sparse_rows); where a wave's four have up to kFewEntries, none of
 // which is the last of its 64, the rows go through those one after the other, and the segments come with the entries: no rows
 // of the entries to look up, no counters, no gather.  4 096 instances x 512 with long tails, 7 061 rows: the kernel 41 us
-// before, 36 this way, 33 with the lengths read whole; the whole scan 109.2 / 103.5.
+// before, 36 this way, 33 with the lengths read whole; the whole scan 109.2 / 103.5.  With six waves per SIMD instead of seven no register is
+// spilled (16 bytes a lane were 18 MB written): scan 105.7 / 102.0, refresh and 262 144 requests 67.3 / 67.0.
 constexpr int kFewEntries = 16;
+constexpr int kSparsePerSimd = 6;
 
 template <int kEighths, bool kBlocks, bool kDense, bool kOwn, bool kSparse>     // kEighths x 64 eighths of an instance's lengths at most
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kMemoPerSimd, kMemoPerSimd))) void k_memo(MemoArgs a)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSparse ? kSparsePerSimd : kMemoPerSimd, kSparse ? kSparsePerSimd : kMemoPerSimd))) void k_memo(MemoArgs a)
 {
     if constexpr (kDense) fetch_args<MemoArgs>();
     __shared__ __align__(16) int lds[kMemoU * kTileRow];       // the counters, then the tile
