@@ -1174,7 +1174,8 @@ __device__ __forceinline__ void clamp_instance(const BuildArgs& a, InstanceIn& i
     if (in.Q > a.max_entries - in.A) { in.Q = a.max_entries - in.A; in.status |= GR_DEV_ENTRIES_DROPPED; }
     in.pend = pend;
     in.P = in.pend + __popcll(in.joins);
-    if (in.P > kTab) { in.P = kTab; if (in.joins) in.status |= GR_DEV_ENTRIES_DROPPED; }
+    // (whoever builds says so, with or without requests that join: what came while sums were added up is only cut here)
+    if (in.P > kTab) { in.P = kTab; in.status |= GR_DEV_ENTRIES_DROPPED; }
     if (in.P > a.max_entries - in.A - in.Q) { in.P = a.max_entries - in.A - in.Q; in.status |= GR_DEV_ENTRIES_DROPPED; }
 }
 

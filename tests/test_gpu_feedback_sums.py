@@ -8,6 +8,7 @@ import pytest
 import torch
 
 from paper_2605_16867_amd import workloads
+from tests.fleets import fleet
 from tests.parity import make_handle, upload
 
 pytestmark = pytest.mark.gpu
@@ -56,3 +57,28 @@ def test_same_as_rebuilt(n_inst, held, entries, chunk, n, blend, odd_lengths):
     for a, b in zip(got, want):
         assert torch.equal(a, b)
     assert status == want_status
+
+
+@pytest.mark.parametrize("entries,sent", [(128, 128), (128, 129), (128, 131), (128, 132), (256, 256), (256, 257), (256, 263)])
+def test_dropped_requests_are_reported(entries, sent):
+    """Idle instances whose room is the whole table.  All requests but the last go to one of them (the most loaded instance is
+    the least capable one that still serves in time), the last one elsewhere: what is beyond the room is only
+    seen by the build at the end, which nothing joins."""
+    n = sent + 1
+    fl = fleet([0, 1, 2, 0, 1], [[]] * 5, [[]] * 5, [(100 + i % 7, 50 + i % 5) for i in range(n)], np.full(n, 1e9))
+    got = []
+    for pairs in (None, 0):
+        h, d = make_handle(fl, max_entries=entries), upload(fl)
+        if pairs is not None:
+            h.gr_set_small_batch_pairs(pairs)
+        out = [torch.full((n,), -7, dtype=torch.int32, device="cuda"), torch.zeros(n, device="cuda")]
+        h.gr_build_status(d["act_off"], d["act_prompt"], d["act_gen"], d["act_rem"], d["q_off"], d["q_prompt"], d["q_len"],
+                          torch.zeros(0, device="cuda"))
+        exclude = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+        exclude[-1] = 2
+        h.gr_route_feedback(1, d["in_prompt"], d["in_len"], d["in_budget"], *out, exclude_inst=exclude)
+        got.append((*out, h.gr_device_status()))
+        h.close()
+    assert torch.all(got[0][0][:-1] == 2) and got[0][0][-1] != 2
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert got[0][2] == got[1][2] == (2 if sent > entries else 0)      # (GR_DEV_ENTRIES_DROPPED)
