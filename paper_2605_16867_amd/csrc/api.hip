@@ -130,6 +130,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     if (hipGetDevice(&f->device) != hipSuccess) { delete f; return GR_ERR_HIP; }
 
     const size_t tab = (size_t)n_inst * f->cap, segments = (size_t)n_inst * (f->cap + 1), seen_bytes = (size_t)(f->bins + 15) / 16 * 16;
+    const bool by_row = classes_first(f, false, max_requests), by_round = n_inst <= kFeedInst && waves_per_instance(f->epl, n_inst) > 1;
     const bool ok =
         dev_alloc(&f->cls, n_class) && dev_alloc(&f->inst_class, n_inst) &&
         dev_alloc(&f->tabR, tab + kWave) && dev_alloc(&f->tabGH, (size_t)n_inst * (f->cap + 2) + kWave) &&
@@ -143,16 +144,16 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
         dev_alloc(&f->scratch_finish, f->max_active + kBlock * kRestItems) && dev_alloc(&f->batch_cap, n_inst) &&
         dev_alloc(&f->seen, seen_bytes) && dev_alloc(&f->late_cnt, (size_t)n_inst * 4) &&
         dev_alloc(&f->row_len, f->row_cap) && dev_alloc(&f->len_row, f->bins + 1) && dev_alloc(&f->totals, 4) && dev_alloc(&f->dense_totals, 2) &&
-        dev_alloc(&f->memo, (size_t)f->row_cap * f->m_pos) && dev_alloc(&f->grp_min, (size_t)f->row_cap * f->run_pad * 2) &&
+        dev_alloc(&f->memo, (size_t)f->row_cap * f->m_pos) && dev_alloc(&f->grp_min, (size_t)f->row_cap * f->run_pad * (by_row ? 2 : 1)) &&
         dev_alloc(&f->run_k, f->n_run) && dev_alloc(&f->run_rank, f->n_run) && dev_alloc(&f->run_at, f->n_run) && dev_alloc(&f->pos_thr, f->m_pos) && dev_alloc(&f->class_min, (size_t)f->row_cap * f->c_pad) &&
         dev_alloc(&f->cls_bound, n_class) && dev_alloc(&f->class_next, (size_t)f->row_cap * n_class) &&
         dev_alloc(&f->rest_cnt, kRestParts * kRestStride) && dev_alloc(&f->lines, (size_t)f->row_cap * kRanges * 2) && dev_alloc(&f->turned, (size_t)f->turned_rows * n_inst) && dev_alloc(&f->direct_part, (size_t)kDirectParts) &&
-        (n_inst > kFeedInst || (dev_alloc(&f->feed_T, (size_t)2 * n_inst * kWave) && dev_alloc(&f->feed_met, (size_t)2 * n_inst) &&
-                                dev_alloc(&f->feed_key, (size_t)2 * n_inst) &&
-                                dev_alloc(&f->feed_base, n_inst + (segments * (sizeof(double2) + sizeof(double)) + sizeof(FeedBase) - 1) / sizeof(FeedBase))));
+        (!by_round || (dev_alloc(&f->feed_T, (size_t)2 * n_inst * kWave) && dev_alloc(&f->feed_met, (size_t)2 * n_inst) &&
+                       dev_alloc(&f->feed_key, (size_t)2 * n_inst) &&
+                       dev_alloc(&f->feed_base, n_inst + (segments * (sizeof(double2) + sizeof(double)) + sizeof(FeedBase) - 1) / sizeof(FeedBase))));
     if (!ok) { gr_destroy(f); return GR_ERR_NOMEM; }
     // (parts of one allocation: each takes its time)
-    f->row_min = f->grp_min + (size_t)f->row_cap * f->run_pad;
+    if (by_row) f->row_min = f->grp_min + (size_t)f->row_cap * f->run_pad;
     static_assert(sizeof(FeedBase) % sizeof(double2) == 0, "the sums begin at a multiple of 16 bytes");
     if (f->feed_base) {
         f->feed_yx = reinterpret_cast<double2*>(f->feed_base + n_inst);

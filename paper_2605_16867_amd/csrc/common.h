@@ -210,7 +210,7 @@ struct gr_fleet {
     int* totals = nullptr;    // [4] -, distinct lengths, 1: flags that the risk scan's build has not set (zero between calls)
     float* memo = nullptr;       // [row_cap / kMemoU][n_run][kMemoU][kMemoP] E per distinct length and position
     float* grp_min = nullptr;    // [row_cap][run_pad] least E of each run, per row (see runs_at)
-    float* row_min = nullptr;    // [row_cap][run_pad] (behind grp_min) the same row by row, of a routing batch whose classes are looked at first
+    float* row_min = nullptr;    // [row_cap][run_pad] (behind grp_min) the same row by row, of a routing batch whose classes are looked at first; null where none can be
     uint32_t* run_rank = nullptr;   // [n_run] runs whose first instance is more capable than the run's first
     int* run_at = nullptr;          // [n_run] the run of each rank
     uint32_t* pos_thr = nullptr;    // [m_pos] runs whose first instance is more capable than the position's
@@ -231,7 +231,7 @@ struct gr_fleet {
     bool recorded = false, blend_recorded = false;
     int* pend_touched = nullptr;   // [M] 1: given requests since its table was built
     int64_t small_batch_pairs = -1;   // largest batch, in pairs, scored pair by pair; -1: by the sizes (see pair_by_pair)
-    // feedback routing, a launch per round (null on fleets of more than kFeedInst instances), two of each in turn: what
+    // feedback routing, a launch per round (null on fleets of more than kFeedInst instances, and where one wave takes an instance), two of each in turn: what
     // every instance offers the requests of a chunk
     uint32_t* feed_T = nullptr;             // [2][M][kWave] latency as an integer of the same order; all ones: not allowed
     unsigned long long* feed_met = nullptr; // [2][M] bit j: request j's deadline is met
@@ -319,6 +319,16 @@ struct FeedbackIn {
     uint8_t* out_fallback;
     bool current;
 };
+// Waves that share an instance of a fleet of M whose tables take epl sort words per lane of one wave (without caps):
+// fewer instances than the chip takes waves at four per SIMD, several waves per instance (measured on 1 024
+// instances x 1 000 requests: 19.8 us with one wave each, 17.7 with two, 16.0 with four, 18.0 with eight, 29 with
+// sixteen; on 256 x 512: 9.2, 8.5, 7.7-8.2, 8.1)
+inline int waves_per_instance(int epl, int M)
+{
+    const int room = 4 * kSimds / M;
+    return epl >= 4 && room >= 4 ? 4 : epl >= 2 && room >= 2 ? 2 : 1;
+}
+
 bool feedback_by_round(const gr_fleet* f, int64_t chunk);
 int launch_feedback(gr_fleet* f, const StatusIn& in, const FeedbackIn& r, hipStream_t s);
 int launch_commit(gr_fleet* f, int64_t n, const int* inst, const int* ctx0, const int* pred_len, hipStream_t s);
@@ -327,6 +337,7 @@ int launch_ema(gr_fleet* f, double w, const float* s_q, const float* s_p, const 
 // score.hip
 int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& out, hipStream_t s,
                  bool small_batch_ok = false);
+bool classes_first(const gr_fleet* f, bool migrate, int64_t n);
 bool needs_marks(const gr_fleet* f, int64_t n);      // a risk scan's table pass makes a list of lengths
 bool pair_by_pair(const gr_fleet* f, int64_t n);
 int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream_t s);

@@ -2344,6 +2344,13 @@ static bool dense_rows(const gr_fleet* f)
            (int64_t)f->bins * f->m_pos <= kDenseValues;
 }
 
+// Whether the fleet and the size of a batch are for the classes first (see launch_score).
+bool classes_first(const gr_fleet* f, bool migrate, int64_t n)
+{
+    return !dense_rows(f) && n >= kByClassMin && f->n_class <= kGroup && f->n_run >= 4 * f->n_class &&
+           f->n_run >= (migrate ? 2 * kGroup : 4 * kGroup);
+}
+
 bool needs_marks(const gr_fleet* f, int64_t n) { return !pair_by_pair(f, n) && !dense_rows(f); }
 
 // Whether the instances are expected to have few entries in a block of rows (see k_memo): by the room of their tables and the
@@ -2465,8 +2472,7 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     // 29.9 / 35.7 (27.1 / 34.3), x 512 33.1 / 38.7 (31.4 / 40.2).
     const PairsPlan pairs(f, out.T);
     const bool select = !(out.T && pairs.select);
-    const bool by_class = select && !dense && !blended && n >= kByClassMin && f->n_class <= kGroup && f->n_run >= 4 * f->n_class &&
-                          f->n_run >= (migrate ? 2 * kGroup : 4 * kGroup);
+    const bool by_class = select && !blended && classes_first(f, migrate, n);
     // The lines first where no class decides a request: with a blend (every instance has its own prefill rate), and where
     // there are more classes than a group has lanes.  Whole calls, us, a group of lanes per request over the runs / lines
     // first (weight 1; in brackets deadlines that many instances meet):

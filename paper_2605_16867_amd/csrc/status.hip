@@ -1738,16 +1738,6 @@ int launch_build_split(const BuildArgs& b, int M, hipStream_t s)
     return kSplit;
 }
 
-// Waves that share an instance of a fleet of M whose tables take kEPL sort words per lane of one wave (without caps):
-// fewer instances than the chip takes waves at four per SIMD, several waves per instance (measured on 1 024
-// instances x 1 000 requests: 19.8 us with one wave each, 17.7 with two, 16.0 with four, 18.0 with eight, 29 with
-// sixteen; on 256 x 512: 9.2, 8.5, 7.7-8.2, 8.1)
-int waves_per_instance(int epl, int M)
-{
-    const int room = 4 * kSimds / M;
-    return epl >= 4 && room >= 4 ? 4 : epl >= 2 && room >= 2 ? 2 : 1;
-}
-
 // kEPL: sort words per lane if one wave takes an instance.  Returns the waves that share an instance.
 template <int kEPL>
 int launch_build(const BuildArgs& b, int M, hipStream_t s)
@@ -1876,7 +1866,7 @@ static_assert(kWave <= kDirectMax && kWave * kFeedInst <= kDirectInfinite, "an i
 // times in the former; without them 1.5 less); wider fleets are not taken.
 bool feedback_by_round(const gr_fleet* f, int64_t chunk)
 {
-    return f->feed_T && !f->has_cap && chunk <= kWave && waves_per_instance(f->epl, f->n_inst) > 1 && pair_by_pair(f, chunk);
+    return f->feed_T && !f->has_cap && chunk <= kWave && pair_by_pair(f, chunk);
 }
 
 // Whether the tables stay as they are while requests are routed and what comes is added to their sums: for three rounds and more
