@@ -346,11 +346,17 @@ int launch_hits(gr_fleet* f, const ReqSrc& src, const int* hit_off, const int* h
 
 // ------------------------------------------------------------------ wave helpers
 // A launch's arguments come from memory, a line of 64 bytes at a time, and what the compiler reads where it is first
-// used is waited for there.  This has all of a kernel's lines on their way together, at its start, which is worth up to a microsecond a
-// launch where all workgroups start at once and each is a chain of reads: status refresh and one request on 256 instances 9.2 us
-// without / 8.65 with it, a control interval of 32 x 256 21.2 / 20.0, of 256 x 512 with 65 536 arrivals 45.9 / 44.5, feedback routing, 33
-// launches, 338 / 329.  Launches of many rounds of workgroups only have more to wait for (the table by a list of lengths and
-// the selections by class, scan of 4 096 x 512 109.0 / 110.8, refresh with 262 144 requests 71.4 / 72.8), and do without.
+// used is waited for there.  This has all of a kernel's lines on their way together, at its start: for kernels that are a
+// chain of reads.  Whole calls, us, without it in the one kernel / with it:
+//   feedback routing  33 launches of 64 requests 333.5 / 307.3, 101 launches of one 766 / 665
+//   builds            status of 256 x 512 9.1 / 8.75, 1 024 x 1 000 16.1 / 15.9, 1 024 x 200 and 40 queued under caps 32.6 / 31.8
+//                     (eight words a lane and two or four waves spill two to four registers for it, 12 to 20 bytes a
+//                     lane, and gain all the same: 600 x 1 500 19.4 / 18.9, 1 024 x 2 000 24.2 / 23.9, 2 000 x 1 000 22.65 / 22.7)
+//   table             a row per length: step of 256 x 512 with 65 536 requests 45.0 / 44.6; with a list it loses (scan of 4 096 x 512
+//                     109.0 / 110.8), as the selections by class do
+//   pair by pair      64 instances x 12 000 requests 9.3 / 9.15, 16 x 40 000 7.2 / 7.05, 1 024 x 500 11.0 / 11.1
+//   k_select          1 024 instances x 8 000 18.6 / 18.3, x 100 000 29.9 / 29.6, 4 096 x 400 20.8 / 20.7
+// No difference in k_select_lanes (that step 45.6 / 45.5), k_scan and k_hits, which do without.
 template <typename Args>
 __device__ __forceinline__ void fetch_args()
 {

@@ -1144,7 +1144,6 @@ __device__ __forceinline__ uint32_t lanes_or(uint32_t v)
 template <bool kMigrate, int kRuns, bool kBlend>
 __global__ __launch_bounds__(kBlock) void k_select_lanes(SelectArgs a)
 {
-    fetch_args<SelectArgs>();
     // of each run: its least delta, gamma, largest delta, its rank as a bit; the run of each rank; delta and gamma by position
     __shared__ float4 of_run[kRuns];
     __shared__ int at_rank[kRuns];
