@@ -232,7 +232,12 @@ int gr_score_route_cached(gr_fleet* f, int64_t n_req,
  * Cost: one scoring pass and one status rebuild per chunk; the rebuild leaves
  * instances that were given nothing in the chunk as they are (unless the blend
  * weight, the observations or the caps have changed since the tables were built:
- * then the first rebuild of the call takes every instance).
+ * then the first rebuild of the call takes every instance).  Chunks of up to 64 on
+ * fleets of up to 512 instances, without caps and with max_entries_per_inst above 64,
+ * are one launch each; three and more of them of up to 8 requests, or of up to a quarter
+ * of the instances with at most 20 480 pairs, rebuild every instance at the start of
+ * the call, then add what comes to the sums behind the tables, and rebuild the
+ * instances that were given any at the end.
  *
  *   chunk      requests per decision round, >= 1 (cut to max_requests)
  * Other arguments as gr_score_route (no out_T).

@@ -478,9 +478,9 @@ __device__ inline int tile_at(int row, int piece) { return row * kTileRow + 4 * 
 //
 // kSparse: an instance has few entries in a block of rows (see sparse_rows); where a wave's four have up to kFewEntries, none of
 // which is the last of its 64, the rows go through those one after the other, and the segments come with the entries: no rows
-// of the entries to look up, no counters, no gather.  4 096 instances x 512 with long tails, 7 061 rows: the kernel 41 us
-// before, 36 this way, 33 with the lengths read whole; the whole scan 109.2 / 103.5.  With six waves per SIMD instead of seven no register is
-// spilled (16 bytes a lane were 18 MB written): scan 105.7 / 102.0, refresh and 262 144 requests 67.3 / 67.0.
+// of the entries to look up, no counters, no gather.  Scan of 4 096 instances x 512 with long tails, 7 061 rows, in turn on one card:
+// 106.3 us without, 100.3 this way with six waves per SIMD (seven spill 16 bytes a lane, 18 MB written: 3.7 us more).  Up to 24 or 32 entries
+// 99.8 and 99.3, but spread evenly, four an instance, 153 and 154 instead of 146.5; 48 and more lose there and at eight.
 constexpr int kFewEntries = 16;
 constexpr int kSparsePerSimd = 6;
 
@@ -568,7 +568,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kSparse 
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     } else {
-        static_assert(!kSparse, "tables of more than 512 lengths have many of them in a block (see sparse_rows)");
+        static_assert(!kSparse, "the segments come with the entries only where the lengths are read whole");
         int eighth[kMemoInst][kEighths];
 #pragma unroll
         for (int j = 0; j < kMemoInst; ++j) {
@@ -755,7 +755,6 @@ struct ClassArgs {
 template <bool kRows>
 __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
 {
-    constexpr bool kBlocks = true;
     constexpr int kW = kBlock / kWave, kAhead = 8, kCols = kAhead * kW;
     __shared__ float turned[kRows ? kWave * (kCols + 1) : 1];
     static_assert(kMemoU % kWave == 0, "the rows of a workgroup are in one block");
@@ -780,7 +779,7 @@ __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
                             fmaxf(k.z, __shfl_xor(k.z, d, kWave)), 0.f);
         if (lane == 0) a.cls_bound[c] = k;
     }
-    const float* __restrict__ runs = a.grp_min + runs_at<kBlocks>(min(u, (int64_t)U - 1), a.run_pad) + (size_t)cr.x * kRunStride<kBlocks>;
+    const float* __restrict__ runs = a.grp_min + runs_at<true>(min(u, (int64_t)U - 1), a.run_pad) + (size_t)cr.x * kRunStride<true>;
     const float* __restrict__ E = a.memo + memo_at(u, cr.x, a.n_run);
     const int* __restrict__ order = a.order + cr.x * kMemoP;
 
@@ -790,7 +789,7 @@ __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
         const int r0 = b + w;
         float e[kAhead];
 #pragma unroll
-        for (int k = 0; k < kAhead; ++k) e[k] = runs[(size_t)min(r0 + k * kW, cr.y - 1) * kRunStride<kBlocks>];
+        for (int k = 0; k < kAhead; ++k) e[k] = runs[(size_t)min(r0 + k * kW, cr.y - 1) * kRunStride<true>];
         if constexpr (kRows) {
             if (b) __syncthreads();
 #pragma unroll
@@ -853,7 +852,7 @@ __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
 #pragma unroll
             for (int q = 1; q < kW; ++q) low1 = min(low1, low_lds[q][lane]);
             for (int r = w; r < cr.y; r += kW) {
-                const float e = runs[(size_t)r * kRunStride<kBlocks>];
+                const float e = runs[(size_t)r * kRunStride<true>];
                 if (e > E1) above = fminf(above, e);
                 else if (r != r1 && __float_as_int(a.run_k[cr.x + r].w) < low1)
                     for (int q = 0; q < kW; ++q) take(r, q);
@@ -2231,12 +2230,15 @@ int launch_direct(gr_fleet* f, const ReqSrc& src, const ScoreOut& out, hipStream
 // Whether a batch is scored pair by pair: as the caller says (gr_set_small_batch_pairs), or by the number of pairs,
 // and of those that its lanes go through (see launch_pair_by_pair).  A pass over the table is two to four launches whose time hardly depends on
 // the batch; this is one that grows with the pairs.  Whole calls, us, table / pairs, with the status build where it says refresh or scan:
-//   routing  64 instances x 12 000 requests 9.9 / 8.2, 16 384 10.1 / 9.9, 32 768 10.4 / 17.5;  128 x 6 000 10.2 / 9.0, 8 192 10.2 / 11.4
-//            256 x 3 000 11.4 / 10.4, 4 096 11.3 / 13.0
-//   refresh  256 x 3 000 19.6 / 16.8, 4 096 19.5 / 19.6, 8 192 19.6 / 28.9;  1 024 x 700 29.3 / 22.4, 1 024 29.3 / 26.0, 1 500 30.3 / 31.6
-//            4 096 x 200 42.6 / 37.8, 300 42.6 / 52
-//   scan     64 x 150 requests each 16.9 / 12.6, 256 17.0 / 16.0, 512 17.8 / 26.7;  128 x 40 15.4 / 12.1, 100 17.1 / 22;  40 x 600 18.8 / 23.9
-// The line is where routing on a standing status still gains, whose table has its class order already.
+//   routing  16 instances x 40 000 requests 11.4 / 6.4, 49 152 11.3 / 7.05;  24 x 32 768 11.0 / 7.7;  32 x 24 576 11.05 / 6.7
+//            64 x 12 000 9.9 / 8.2, 16 384 10.1 / 9.9, 32 768 10.4 / 17.5;  128 x 6 000 10.2 / 9.0, 8 192 10.2 / 11.4
+//            256 x 3 000 11.4 / 10.4, 4 096 11.3 / 13.0;  with out_T 64 x 12 000 15.8 / 8.5, 256 x 3 000 24.8 / 10.4
+//   refresh  16 x 49 152 17.8 / 12.0;  24 x 32 768 17.4 / 12.9;  256 x 3 000 19.6 / 16.8, 4 096 19.5 / 19.6, 8 192 19.6 / 28.9
+//            1 024 x 700 29.3 / 22.4, 1 024 29.3 / 26.0, 1 500 30.3 / 31.6;  4 096 x 200 42.6 / 37.8, 300 42.6 / 52
+//   scan     32 x 700 requests each 19.1 / 16.2 (all of them late 18.9 / 16.3), 64 x 190 17.7 / 13.8 (17.3 / 14.1), 128 x 47 16.7 / 11.4 (16.5 / 12.2)
+//            64 x 256 17.0 / 16.0, 512 17.8 / 26.7;  128 x 100 17.1 / 22;  40 x 600 18.8 / 23.9
+// The line is where routing on a standing status still gains, whose table has its class order already; a refresh makes it anew and
+// would gain to somewhat larger batches.
 bool pair_by_pair(const gr_fleet* f, int64_t n)
 {
     if (f->small_batch_pairs >= 0) return n <= kDirectMax && n * f->m_pad <= f->small_batch_pairs;
@@ -2352,10 +2354,15 @@ bool classes_first(const gr_fleet* f, bool migrate, int64_t n)
 
 bool needs_marks(const gr_fleet* f, int64_t n) { return !pair_by_pair(f, n) && !dense_rows(f); }
 
-// Whether the instances are expected to have few entries in a block of rows (see k_memo): by the room of their tables and the
-// rows there may be.  Whole calls, us, before / this way: scan of 4 096 instances x 512, lengths up to 16 384 (8 an instance and block) 109.2 /
-// 103.5, refresh and 262 144 requests 72.1 / 70.9; 2 000 x 300, 60 000 requests 42.6 / 41.9; scan of 1 309 x 125 (2) 39.8 / 40.0.  1 024 x 1 000
-// with lengths up to 4 096 have 64, and are never few.
+// Whether the instances are expected to have few entries in most blocks of rows (see k_memo): by the room of their tables and the
+// rows there may be.  (Only tables that are read whole have that way.)  The line is at eight an instance and block on average, twice
+// what a wave takes it with: decode lengths have long tails, which leave most blocks with far fewer and a few with most.
+// Whole scans, us, without / with it, lengths up to 16 384 (128 and 64 of them: up to 4 096), in brackets spread evenly:
+//   8 an instance and block   4 096 x 512 106.3 / 100.3 (211.5 / 212)   2 000 x 512 63.0 / 61.2 (100.2 / 104.0)   4 096 x 128 77.1 / 74.8 (65.7 / 67.5)
+//   4                         4 096 x 250 74.5 / 70.3 (160 / 146)       3 000 x 64 52.4 / 51.4 (52.5 / 53.1)
+//   2, 1                      4 096 x 125 68.8 / 66.7 (139 / 120)       4 096 x 60 52.8 / 51.5 (118.5 / 96.9)
+// and refresh of 4 096 x 512 with 262 144 requests 66.8 / 66.1 (162.4 / 162.8).  Evenly spread, eight are never few, and the reads of the segments
+// and a wave per SIMD less are for nothing; half as many are.
 static bool sparse_rows(const gr_fleet* f, int64_t max_rows) { return f->cap <= 512 && (int64_t)f->cap * kMemoU <= 8 * max_rows; }
 
 // How the rows of a pass are found.  (Lines and classes first are for fleets of more runs than have a row per length.)

@@ -1221,9 +1221,11 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
 
 // Feedback routing, a launch per decision round (chunks of up to kWave requests; a workgroup per instance, all
 // of whose waves share it).  Launch k decides the chunk before it from what every instance has offered (every
-// workgroup for itself: a lane per request, the waves share the instances), rebuilds the instances that were
-// chosen, and offers for the next chunk: each request's latency here, whether its deadline is met, and d_g.
-// The launches themselves are the wait of one round for the other.
+// workgroup for itself: a lane per request, the waves share the instances), takes in what was sent to the instance, and
+// offers for the next chunk: each request's latency here, whether its deadline is met, and d_g.
+// The launches themselves are the wait of one round for the other.  What was sent to an instance is taken in by building its
+// table anew, or (kAdd, for small rounds, see adds_up) by adding it to the sums of the table as it was built last: the tables
+// are all built once at the start, one with more than kFeedListed requests added anew, and at the end those that were given any.
 //
 // What bounds it is the chain of a round: the offers (64 requests x 256 instances are 64 KB for every workgroup, from
 // L2), the choice, then the rebuild, whose table is still in LDS when the next requests are looked up in it.  A round was
@@ -1307,9 +1309,8 @@ __device__ __forceinline__ unsigned long long wave_or_u64(unsigned long long v)
     return ((unsigned long long)wave_or_u32((uint32_t)(v >> 32)) << 32) | wave_or_u32((uint32_t)v);
 }
 
-//
 // kAdd: the tables stay as they were built last, with the sums behind them, and what has come since is added to those for
-// every request anew (see adds_up), in fp64, so that a segment comes to the same (Gq, H) bit for bit.  One wave more than share the
+// every request anew, in fp64, so that a segment comes to the same (Gq, H) bit for bit (while the sums are below 2^53).  One wave more than share the
 // instance gathers what it takes (the segments of the table, the list since then) while the others decide.  A round of one request on 256
 // instances 9.6 us with a rebuild, 6.6 this way; of 64 requests 10.0 / 9.3.
 template <int kEPL, int kSplit, bool kAdd>
