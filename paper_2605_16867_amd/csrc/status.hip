@@ -1160,8 +1160,9 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
     }
 }
 
-// The instance's slices and the lengths of its lists, from the caller's offsets.
-template <int kTab>
+// The instance's slices and the lengths of its lists, from the caller's offsets.  kListed: its list may have grown beyond the
+// table without anybody having said so (requests that were added to sums).
+template <int kTab, bool kListed = false>
 __device__ __forceinline__ void clamp_instance(const BuildArgs& a, InstanceIn& in, int a_begin, int a_end, int q_begin, int q_end, int pend)
 {
     // offsets are clamped into the arrays, so broken CSR data cannot index outside them
@@ -1174,8 +1175,7 @@ __device__ __forceinline__ void clamp_instance(const BuildArgs& a, InstanceIn& i
     if (in.Q > a.max_entries - in.A) { in.Q = a.max_entries - in.A; in.status |= GR_DEV_ENTRIES_DROPPED; }
     in.pend = pend;
     in.P = in.pend + __popcll(in.joins);
-    // (whoever builds says so, with or without requests that join: what came while sums were added up is only cut here)
-    if (in.P > kTab) { in.P = kTab; in.status |= GR_DEV_ENTRIES_DROPPED; }
+    if (in.P > kTab) { in.P = kTab; if (kListed || in.joins) in.status |= GR_DEV_ENTRIES_DROPPED; }
     if (in.P > a.max_entries - in.A - in.Q) { in.P = a.max_entries - in.A - in.Q; in.status |= GR_DEV_ENTRIES_DROPPED; }
 }
 
@@ -1435,7 +1435,7 @@ __global__ __launch_bounds__(kWave * (kSplit + kAdd), (kEPL <= 8 ? 4 : 1)) void 
                          : move == kFeedTouched ? in.joins || touched : move == kFeedAll;
     if (rebuild) {
         if (kAdd && wave == kSplit) return;
-        clamp_instance<kTab>(a, in, a_begin, a_end, q_begin, q_end, pend);
+        clamp_instance<kTab, kAdd>(a, in, a_begin, a_end, q_begin, q_end, pend);
         const int N = in.A + in.Q + in.P;
         bool built = false;
         if constexpr (kEPL >= 4)
