@@ -9,10 +9,9 @@
 // words (remaining length in the high bits, entry index in the low bits, so
 // all words differ and the order is stable), kEPL consecutive positions of the
 // sorted order per lane.  A bitonic network sorts them: exchanges inside a lane
-// are a min/max pair, exchanges between lanes fetch the partner's word (a DPP
-// move inside a row of 16 lanes where a pattern exists, else the LDS crossbar)
-// and keep the smaller or the larger of the two with one median-of-three
-// against 0 or 0xFFFFFFFF.  No atomics; barriers only between the waves that
+// are a min/max pair, exchanges between lanes fetch the partner's word (through
+// the register file or the LDS crossbar, see kShortChain) and keep the smaller
+// or the larger of the two, mostly with one median-of-three against 0 or 0xFFFFFFFF.  No atomics; barriers only between the waves that
 // share an instance.
 #include <algorithm>
 #include <cfloat>
@@ -87,26 +86,59 @@ __device__ __forceinline__ uint32_t dpp_move(uint32_t x)
     return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, kCtrl, 0xf, 0xf, false);
 }
 
-// The copy of x held by lane (lane ^ mask); lane4 = 4 * lane.  Partners inside a
-// row of 16 lanes that a DPP pattern reaches come straight from the register
-// file; the others through the LDS crossbar.
-__device__ __forceinline__ uint32_t fetch_xor(uint32_t x, int mask, int lane4)
-{
-    switch (mask) {
-        case 1: return dpp_move<0xB1>(x);      // quad_perm [1,0,3,2]
-        case 2: return dpp_move<0x4E>(x);      // quad_perm [2,3,0,1]
-        case 3: return dpp_move<0x1B>(x);      // quad_perm [3,2,1,0]
-        case 7: return dpp_move<0x141>(x);     // row_half_mirror
-        case 15: return dpp_move<0x140>(x);    // row_mirror
-        default: return (uint32_t)__builtin_amdgcn_ds_bpermute(lane4 ^ (mask << 2), (int)x);
-    }
-}
-
 __device__ __forceinline__ void order2(uint32_t& lo, uint32_t& hi)
 {
     const uint32_t a = lo, b = hi;
     lo = a < b ? a : b;
     hi = a < b ? b : a;
+}
+
+// How a lane gets its partner's word.  What bounds a build decides.  With up to two words a lane several waves share an instance and a
+// SIMD hardly has a wave to run meanwhile, and under caps it never has: an exchange is a step of a chain, and stays in the
+// register file, whose step is shorter than the crossbar's.  With more words the vector ALU is what the waves of a SIMD wait for,
+// and the fetches that no single pattern does are left to the crossbar.  Whole calls, us, everywhere like that / as here: refresh of 256 x 512 and
+// one request 8.77 / 8.42, step of 32 x 256 20.43 / 20.00, of 4 x 64 14.69 / 14.50, 1 024 x 240 under caps 60.1 / 59.9.  (All fetches through
+// the crossbar: 8.85, 20.2, 15.2, 61.1; status of 4 096 x 512 21.3 / 21.0, but its scan 108.6 / 109.6; scan of 1 024 x 1 000 60.4 / 59.9 to 60.6.)
+template <int kEPL>
+constexpr bool kShortChain = kEPL <= 2;
+
+// The copy of x held by lane (lane ^ kMask); lane4 = 4 * lane.
+template <bool kChain, int kMask>
+__device__ __forceinline__ uint32_t fetch_xor(uint32_t x, int lane4)
+{
+    if constexpr (kMask == 1) return dpp_move<0xB1>(x);       // quad_perm [1,0,3,2]
+    else if constexpr (kMask == 2) return dpp_move<0x4E>(x);       // quad_perm [2,3,0,1]
+    else if constexpr (kMask == 3) return dpp_move<0x1B>(x);       // quad_perm [3,2,1,0]
+    else if constexpr (kMask == 7) return dpp_move<0x141>(x);      // row_half_mirror
+    else if constexpr (kMask == 8 && kChain) return dpp_move<0x128>(x);      // row_ror:8
+    else if constexpr (kMask == 15) return dpp_move<0x140>(x);     // row_mirror
+    else return (uint32_t)__builtin_amdgcn_ds_bpermute(lane4 ^ (kMask << 2), (int)x);
+}
+
+// Words of lanes kMask apart in order, the lesser one in the lower lane, without the crossbar: shifts inside a row of which either half
+// of the lanes takes one, or the halves of two registers changed over and back.
+template <int kMask>
+__device__ __forceinline__ void order_lanes(uint32_t& a, uint32_t& b)
+{
+    static_assert(kMask == 4 || kMask == 16 || kMask == 32);
+    if constexpr (kMask == 4) {
+        const auto both = [](uint32_t x) {
+            const uint32_t lower = min((uint32_t)__builtin_amdgcn_update_dpp(-1, (int)x, 0x104, 0xf, 0x5, false), x);      // row_shl:4
+            return max((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xa, false), lower);                   // row_shr:4
+        };
+        a = both(a);
+        b = both(b);
+    } else {
+        const auto change = [](uint32_t& x, uint32_t& y) {
+            const auto v = kMask == 16 ? __builtin_amdgcn_permlane16_swap(x, y, false, false)
+                                       : __builtin_amdgcn_permlane32_swap(x, y, false, false);
+            x = v[0];
+            y = v[1];
+        };
+        change(a, b);
+        order2(a, b);
+        change(a, b);
+    }
 }
 
 // Ascending bitonic sort of 64 * kEPL words, word v = lane * kEPL + r in key[r].
@@ -116,7 +148,7 @@ __device__ __forceinline__ void order2(uint32_t& lo, uint32_t& hi)
 // (the network is straight-line code with every register named at compile
 // time; as loops over K and the distance the larger sizes were left rolled,
 // with registers addressed indirectly).
-template <int kEPL, int K>
+template <bool kChain, int kEPL, int K>
 __device__ __forceinline__ void bitonic_mirror(uint32_t (&key)[kEPL], int lane, int lane4)
 {
     if constexpr (K <= kEPL) {
@@ -128,13 +160,13 @@ __device__ __forceinline__ void bitonic_mirror(uint32_t (&key)[kEPL], int lane, 
         const uint32_t bound = (lane & (K / kEPL / 2)) ? 0xFFFFFFFFu : 0u;   // upper partner keeps the larger
         uint32_t p[kEPL];
 #pragma unroll
-        for (int r = 0; r < kEPL; ++r) p[r] = fetch_xor(key[kEPL - 1 - r], lm, lane4);
+        for (int r = 0; r < kEPL; ++r) p[r] = fetch_xor<kChain, lm>(key[kEPL - 1 - r], lane4);
 #pragma unroll
         for (int r = 0; r < kEPL; ++r) key[r] = med3_u32(key[r], p[r], bound);
     }
 }
 
-template <int kEPL, int J>
+template <bool kChain, int kEPL, int J>
 __device__ __forceinline__ void bitonic_distances(uint32_t (&key)[kEPL], int lane, int lane4)
 {
     if constexpr (J >= 1) {
@@ -144,28 +176,34 @@ __device__ __forceinline__ void bitonic_distances(uint32_t (&key)[kEPL], int lan
                 if ((r & J) == 0) order2(key[r], key[r | J]);
         } else {
             constexpr int lm = J / kEPL;
-            const uint32_t bound = (lane & lm) ? 0xFFFFFFFFu : 0u;
+            if constexpr (kChain && (lm == 4 || lm >= 16)) {
+                uint32_t same = key[0];      // (one word a lane: two registers alike come to the same)
 #pragma unroll
-            for (int r = 0; r < kEPL; ++r) key[r] = med3_u32(key[r], fetch_xor(key[r], lm, lane4), bound);
+                for (int r = 0; r < kEPL; r += 2) order_lanes<lm>(key[r], kEPL > 1 ? key[r + 1 < kEPL ? r + 1 : r] : same);
+            } else {
+                const uint32_t bound = (lane & lm) ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+                for (int r = 0; r < kEPL; ++r) key[r] = med3_u32(key[r], fetch_xor<kChain, lm>(key[r], lane4), bound);
+            }
         }
-        bitonic_distances<kEPL, J / 2>(key, lane, lane4);
+        bitonic_distances<kChain, kEPL, J / 2>(key, lane, lane4);
     }
 }
 
-template <int kEPL, int K>
+template <bool kChain, int kEPL, int K>
 __device__ __forceinline__ void bitonic_levels(uint32_t (&key)[kEPL], int lane, int lane4)
 {
     if constexpr (K <= kWave * kEPL) {
-        bitonic_mirror<kEPL, K>(key, lane, lane4);
-        bitonic_distances<kEPL, K / 4>(key, lane, lane4);
-        bitonic_levels<kEPL, 2 * K>(key, lane, lane4);
+        bitonic_mirror<kChain, kEPL, K>(key, lane, lane4);
+        bitonic_distances<kChain, kEPL, K / 4>(key, lane, lane4);
+        bitonic_levels<kChain, kEPL, 2 * K>(key, lane, lane4);
     }
 }
 
-template <int kEPL>
+template <bool kChain, int kEPL>
 __device__ __forceinline__ void bitonic_sort(uint32_t (&key)[kEPL], int lane)
 {
-    bitonic_levels<kEPL, 2>(key, lane, lane << 2);
+    bitonic_levels<kChain, kEPL, 2>(key, lane, lane << 2);
 }
 
 // The same network over the kSplit waves that share an instance (word v = (part * 64 + lane) *
@@ -196,7 +234,7 @@ __device__ __forceinline__ void bitonic_sort_split(uint32_t (&key)[kEPL], int la
     static_assert(kSplit >= 2 && (kSplit & (kSplit - 1)) == 0, "a power of two of waves per instance");
     constexpr int kWords = kWave * kEPL, kCap = kWords * kSplit;
     const int lane4 = lane << 2;
-    bitonic_levels<kEPL, 2>(key, lane, lane4);
+    bitonic_levels<kShortChain<kEPL>, kEPL, 2>(key, lane, lane4);
     int flip = 0;
 #pragma unroll
     for (int span = 2; span <= kSplit; span *= 2) {
@@ -209,7 +247,7 @@ __device__ __forceinline__ void bitonic_sort_split(uint32_t (&key)[kEPL], int la
             bitonic_exchange<kEPL, false>(key, lane, part, part ^ d, part & d, xch + flip * kCap);
             flip ^= 1;
         }
-        bitonic_distances<kEPL, kWords / 2>(key, lane, lane4);
+        bitonic_distances<kShortChain<kEPL>, kEPL, kWords / 2>(key, lane, lane4);
     }
 }
 
@@ -433,7 +471,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
             uint32_t run[kEPL];
 #pragma unroll
             for (int r = 0; r < kEPL; ++r) run[r] = r * kWave + lane < A ? key[r] : 0xFFFFFFFFu;
-            bitonic_sort<kEPL>(run, lane);
+            bitonic_sort<true, kEPL>(run, lane);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -543,7 +581,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
         }
     }
 
-    bitonic_sort<kEPL>(key, lane);
+    bitonic_sort<true, kEPL>(key, lane);
 
     // the wave's own LDS writes above must be visible to its reads below
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -928,7 +966,7 @@ __device__ __forceinline__ void build_instance(const BuildArgs& a, const Instanc
     }
 
     if constexpr (kSplit == 1) {
-        bitonic_sort<kEPL>(key, lane);
+        bitonic_sort<kShortChain<kEPL>, kEPL>(key, lane);
         // the wave's own LDS writes above must be visible to its reads below
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
