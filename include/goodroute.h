@@ -94,11 +94,12 @@ enum {
  * rows = min(max_len + 1, N) rounded up to a multiple of 256,
  *   18 * n_inst * cap bytes          instance tables and the lists of feedback routing,
  *   8 * n_inst * max_entries_per_inst bytes   per held request (its instance, a spare finish time),
- *   rows * (4 * M' + 4 * [M' / 16 rounded up to 16] + 4 * [n_class rounded up to 4] + 8 * n_class + 128) bytes
+ *   rows * (4 * M' + 4 * [M' / 16 rounded up to 16] + 128) bytes
  *                                    the per-(distinct length, instance) table of a scoring pass, its minima
- *                                    over runs and classes, and the instances that can be least, reserved for the
- *                                    worst case whatever the batches turn out to be (296 MB for 4 096
+ *                                    over runs, and the instances that can be least, reserved for the
+ *                                    worst case whatever the batches turn out to be (295 MB for 4 096
  *                                    instances of 6 classes and max_len 16 384),
+ *   8 * (max_len + 1) * [n_class rounded up to 2, 4, 8 or 16] bytes   the minima over classes, up to 16 classes (1 MB there),
  *   4 * rows * [M' / 16 rounded up to 16] bytes   the minima over runs once more (18 MB there), for max_requests of 131 072
  *                                    and more on fleets of up to 16 classes with M' of at least 1 024 and 64 * n_class,
  *   at most 64 MB, or 1 024 * n_inst bytes if that is more   rows of that table for out_T,

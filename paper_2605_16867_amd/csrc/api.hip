@@ -120,7 +120,8 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     f->n_run = (int)tab_h.run_cls.size();
     f->m_pos = f->n_run * kMemoP;
     f->run_pad = (f->n_run + kMemoP - 1) / kMemoP * kMemoP;
-    f->c_pad = (n_class + 3) / 4 * 4;
+    f->class_shift = 1;
+    while ((1 << f->class_shift) < n_class) ++f->class_shift;
     f->bins = max_len + 1;
     for (const int2 r : tab_h.run_cls) f->most_of_class = std::max(f->most_of_class, r.y);
     f->row_cap = f->req_cap < f->bins ? f->req_cap : f->bins;
@@ -145,8 +146,8 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
         dev_alloc(&f->seen, seen_bytes) && dev_alloc(&f->late_cnt, (size_t)n_inst * 4) &&
         dev_alloc(&f->row_len, f->row_cap) && dev_alloc(&f->len_row, f->bins + 1) && dev_alloc(&f->totals, 4) && dev_alloc(&f->dense_totals, 2) &&
         dev_alloc(&f->memo, (size_t)f->row_cap * f->m_pos) && dev_alloc(&f->grp_min, (size_t)f->row_cap * f->run_pad * (by_row ? 2 : 1)) &&
-        dev_alloc(&f->run_k, f->n_run) && dev_alloc(&f->run_rank, f->n_run) && dev_alloc(&f->run_at, f->n_run) && dev_alloc(&f->pos_thr, f->m_pos) && dev_alloc(&f->class_min, (size_t)f->row_cap * f->c_pad) &&
-        dev_alloc(&f->cls_bound, n_class) && dev_alloc(&f->class_next, (size_t)f->row_cap * n_class) &&
+        dev_alloc(&f->run_k, f->n_run) && dev_alloc(&f->run_rank, f->n_run) && dev_alloc(&f->run_at, f->n_run) && dev_alloc(&f->pos_thr, f->m_pos) &&
+        dev_alloc(&f->cls_rank, n_class) && (n_class > kMemoP || dev_alloc(&f->class_least, (size_t)f->bins << f->class_shift)) &&
         dev_alloc(&f->rest_cnt, kRestParts * kRestStride) && dev_alloc(&f->lines, (size_t)f->row_cap * kRanges * 2) && dev_alloc(&f->turned, (size_t)f->turned_rows * n_inst) && dev_alloc(&f->direct_part, (size_t)kDirectParts) &&
         (!by_round || (dev_alloc(&f->feed_T, (size_t)2 * n_inst * kWave) && dev_alloc(&f->feed_met, (size_t)2 * n_inst) &&
                        dev_alloc(&f->feed_key, (size_t)2 * n_inst) &&
@@ -205,7 +206,7 @@ int gr_destroy(gr_fleet* f)
     void* ptrs[] = {f->cls, f->inst_class, f->tabR, f->tabGH, f->hD, f->emaQ, f->emaP, f->emaD, f->instK, f->tabS,
                     f->clsK, f->slot_inst, f->slot_of, f->slot_key, f->run_cls, f->cls_run, f->order, f->pos_of, f->posK, f->posKey, f->run_head, f->act_inst, f->pend_cnt, f->commit_mark, f->pend_touched, f->pend_prompt, f->pend_len,
                     f->scratch_finish, f->batch_cap, f->counters, f->seen, f->late_cnt, f->row_len,
-                    f->len_row, f->totals, f->dense_totals, f->memo, f->grp_min, f->run_k, f->run_rank, f->run_at, f->pos_thr, f->class_min, f->cls_bound, f->class_next, f->rest_cnt, f->lines, f->turned, f->feed_T, f->feed_met, f->feed_key, f->feed_base, f->direct_part};
+                    f->len_row, f->totals, f->dense_totals, f->memo, f->grp_min, f->run_k, f->run_rank, f->run_at, f->pos_thr, f->cls_rank, f->class_least, f->rest_cnt, f->lines, f->turned, f->feed_T, f->feed_met, f->feed_key, f->feed_base, f->direct_part};
     int rc = GR_OK;
     for (void* p : ptrs)
         if (p && hipFree(p) != hipSuccess) rc = GR_ERR_HIP;

@@ -152,7 +152,7 @@ struct gr_fleet {
     int m_pos = 0;         // positions of the class order: every class rounded up to whole runs of kMemoP
     int n_run = 0;         // m_pos / kMemoP
     int run_pad = 0;       // n_run rounded up to whole runs of kMemoP: row length of grp_min
-    int c_pad = 0;         // n_class rounded up to a multiple of 4: row length of class_min
+    int class_shift = 0;   // n_class rounded up to 2, 4, 8 or 16, as a power of two: row length of class_least
     int bins = 0;          // max_len + 1
     int most_of_class = 0; // instances of the largest class
     int64_t row_cap = 0;   // rows of the memo table, rounded up to whole blocks of kMemoU
@@ -215,13 +215,12 @@ struct gr_fleet {
     int* run_at = nullptr;          // [n_run] the run of each rank
     uint32_t* pos_thr = nullptr;    // [m_pos] runs whose first instance is more capable than the position's
     float4* run_k = nullptr;     // [n_run] least delta of the run, gamma, largest delta, lowest instance (int bits)
-    float* class_min = nullptr;  // [row_cap][c_pad] least E of each class, per row
-    float4* cls_bound = nullptr; // [n_class] least delta of the class, gamma, largest delta
+    uint32_t* cls_rank = nullptr;   // [n_class] run_rank of each class's first run
     float4* lines = nullptr;     // [row_cap][kRanges][2] with a blend: the instances that can have the least latency, see k_lines
     int* rest_cnt = nullptr;     // [kRestParts][kRestStride] length of each list (the lists themselves: scratch_finish)
     float* turned = nullptr;     // [turned_rows][M] a part of memo with a row's values together, for out_T
     int turned_rows = 0;         // multiple of kMemoU
-    uint2* class_next = nullptr; // [row_cap][n_class] next larger E of the class (bits), lowest instance that has the least
+    uint2* class_least = nullptr; // [bins][1 << class_shift] by length: least E of each class (bits), the instance that has it and how near the next is; null on more than 16 classes
     // What the host knows of the tables.  A call that is being recorded runs nothing, and what it records
     // changes the tables at every replay without the host: calls of a capture keep an account of their
     // own (`rec`, of capture `rec_id`), and once one of them may change the tables, or what they are made

@@ -736,11 +736,22 @@ struct ClassArgs {
     const float *memo, *grp_min;
     const float4* run_k;
     float* row_min;       // see k_class
-    float* class_min;
-    uint2* class_next;
-    float4* cls_bound;
-    int n_class, c_pad, n_run, run_pad;
+    const int* row_len;
+    uint2* class_least;   // see class_at
+    const uint32_t* run_rank;
+    uint32_t* cls_rank;   // of each class's first run
+    int n_class, class_shift, n_run, run_pad;
 };
+
+// What decides most requests of a large batch is kept by length, not by row: the least E of every class, and in one word the lowest
+// instance that has it and the exponent of the distance to the next larger E (which says whether rounding may have made the two
+// latencies equal).  A length's classes are 16, 32, 64 or 128 bytes together, and the lanes of a request read them side by side.
+__device__ inline size_t class_at(int L, int shift) { return (size_t)L << shift; }
+constexpr int kLowBits = 20, kCountAt = 28;      // bits of the instance (gr_create takes no more); see least_of_classes
+__device__ inline uint32_t low_and_gap(int low, float least, float next)
+{
+    return ((__float_as_uint(next - least) >> 23 & 0xFFu) << kLowBits) | ((uint32_t)low & ((1u << kLowBits) - 1u));
+}
 
 // Per row and class: the least E, the lowest instance that has it, and the least E above it among
 // what could still change the answer.  Without a blend the prefill part is the same for all of a
@@ -766,19 +777,9 @@ __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
     const int U = a.totals[1];
     if (u0 >= U) return;
     const int2 cr = a.cls_run[c];
+    const int L = a.row_len[min(u, (int64_t)U - 1)];
     const float inf = __builtin_inff();
-    if (u0 == 0 && w == 0) {        // least and largest delta of the class, and its gamma, as for a run
-        float4 k = make_float4(inf, 0.f, -inf, 0.f);
-        for (int r = lane; r < cr.y; r += kWave) {
-            const float4 x = a.run_k[cr.x + r];
-            k = make_float4(fminf(k.x, x.x), fmaxf(k.y, x.y), fmaxf(k.z, x.z), 0.f);
-        }
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1)
-            k = make_float4(fminf(k.x, __shfl_xor(k.x, d, kWave)), fmaxf(k.y, __shfl_xor(k.y, d, kWave)),
-                            fmaxf(k.z, __shfl_xor(k.z, d, kWave)), 0.f);
-        if (lane == 0) a.cls_bound[c] = k;
-    }
+    if (u0 == 0 && threadIdx.x == 0) a.cls_rank[c] = cr.y ? a.run_rank[cr.x] : ~0u;
     const float* __restrict__ runs = a.grp_min + runs_at<true>(min(u, (int64_t)U - 1), a.run_pad) + (size_t)cr.x * kRunStride<true>;
     const float* __restrict__ E = a.memo + memo_at(u, cr.x, a.n_run);
     const int* __restrict__ order = a.order + cr.x * kMemoP;
@@ -869,8 +870,7 @@ __global__ __launch_bounds__(kBlock) void k_class(ClassArgs a)
         low = min(low, low_lds[q][lane]);
         above = fminf(above, m2_lds[q][lane]);
     }
-    a.class_min[u * a.c_pad + c] = E1;
-    a.class_next[u * a.n_class + c] = make_uint2(__float_as_uint(above), (uint32_t)low);
+    a.class_least[class_at(L, a.class_shift) + c] = make_uint2(__float_as_uint(E1), low_and_gap(low, E1, above));
 }
 
 struct SelectArgs {
@@ -884,17 +884,16 @@ struct SelectArgs {
     const uint32_t *run_rank, *pos_thr;
     const int* run_at;
     const int2* cls_run;
-    const float* class_min;
-    const uint2* class_next;
+    const uint2* class_least;
     const float2* clsK;
-    const float4* cls_bound;
+    const uint32_t* cls_rank;
     float4* lines;           // see k_lines
     int *rest, *rest_cnt;    // see k_select_lines
     const int *totals, *row_len, *pos_of;
     int* out_inst;
     float* out_slack;
     uint8_t* out_fallback;
-    int run_pad, n_run, n_class, c_pad, max_len, n_inst;
+    int run_pad, n_run, n_class, class_shift, max_len, n_inst;
     int segments;      // by classes or lines first: workgroups of the launch
     int64_t first;     // a group of lanes per request: the launch's first request
 };
@@ -1281,40 +1280,119 @@ __global__ __launch_bounds__(kBlock) void k_select_lanes(SelectArgs a)
     reply(bestG, bestG >= 0 ? q.D - bestT : 0.f, false);
 }
 
-// The same where the least E of every class is known: the runs of one class after the other, as long
-// as the bound of a class (formed like that of a run; exact without a blend) leaves it in question.
-template <bool kMigrate, int kChunks, bool kBlocks>
-__device__ __forceinline__ void select_by_class(const SelectArgs& a, int64_t i, const Request& q, int row, int sub)
+// The same where the least E of every class is known, and all of a class have the same prefill part: only the classes, and of
+// those the runs, that can hold the answer.  A class's runs are in capability order, so the first run whose least latency meets a
+// deadline has the class's choice (unless that is the excluded instance).
+//
+// Of the requests that large batches leave to this there are one or two to a workgroup, at its end: what it takes is the chain of
+// one of them, reads and instructions (a lone wave's take eight cycles each, one after the other).  Kernel time of a scan of 1 024 x 1 000, of
+// which one in 600 gets here, 19.6 us with the bounds, ranks and reads of Selection, 15.0 this way; refresh and 262 144 requests on 4 096
+// instances, one in 30, 12.5 and 9.4; with deadlines that many meet (x 16) whole calls of 85.3 and 85.7 us, now 69.3 and 70.3.
+template <bool kMigrate, bool kBlocks>
+__device__ __forceinline__ void select_by_class(const SelectArgs& a, int64_t i, const Request& q, int sub)
 {
-    const float inf = __builtin_inff();
-    Selection<kChunks, kBlocks> sel(a, q, row, sub);
-    const int c = min(sub, a.n_class - 1);
-    const float e = a.class_min[(size_t)row * a.c_pad + c];
+    constexpr int kChunks = 4;      // times kGroup runs that are read together
+    const float inf = __builtin_inff(), c0 = (float)q.c0, Lf = (float)q.L, Dc = q.D > FLT_MAX ? FLT_MAX : q.D;
+    const int c = min(sub, a.n_class - 1), row = a.len_row[q.L];
+    const float e = __uint_as_float(a.class_least[class_at(q.L, a.class_shift) + c].x);
     const int2 range = a.cls_run[c];
-    const uint32_t rank = a.run_rank[min(range.x, a.n_run - 1)];      // (of the class's most capable instance)
-    const float T = sub < a.n_class && e < inf ? sel.bound(e, a.cls_bound[c]) : inf;      // (none of the class's is less)
-    uint32_t left_rank = T <= sel.Dc ? rank : ~0u;
+    const float kappa = kappa_of(a.clsK[c], Lf);
+    const uint32_t rank = a.cls_rank[c];      // of the class's most capable instance
+    const float T_least = sub < a.n_class && e < inf ? fmaf(c0, kappa, e) : inf;
+    const float* __restrict__ runs = a.grp_min + runs_at<kBlocks>(row, a.run_pad);
+    const float* __restrict__ E = a.memo + memo_at(row, 0, a.n_run) + sub;
+
+    int first, n;      // the runs of the class at hand; its kappa
+    float kap;
+    const auto enter = [&](int l) { first = group_lane(range.x, l); n = group_lane(range.y, l); kap = group_lane(kappa, l); };
+    const auto bounds = [&](int r0, float (&b)[kChunks]) {
+#pragma unroll
+        for (int j = 0; j < kChunks; ++j) b[j] = runs[(size_t)(first + min(r0 + j * kGroup + sub, n - 1)) * kRunStride<kBlocks>];
+#pragma unroll
+        for (int j = 0; j < kChunks; ++j) b[j] = r0 + j * kGroup + sub < n ? fmaf(c0, kap, b[j]) : inf;
+    };
+
+    unsigned long long feasKey = ~0ull;
+    int feasG = -1;
+    float feasT = 0.f;
+    uint32_t feasThr = ~0u;
+    uint32_t left_rank = T_least <= Dc ? rank : ~0u;
     for (;;) {
-        const uint32_t least = min_over<true>(left_rank < sel.feasThr ? left_rank : ~0u);      // the most capable of them
-        if (least == ~0u) break;
-        const int l = __ffs(group_ballot(left_rank == least)) - 1;
+        const uint32_t top = min_over<true>(left_rank < feasThr ? left_rank : ~0u);      // the most capable of them
+        if (top == ~0u) break;
+        const int l = __ffs(group_ballot(left_rank == top)) - 1;
         if (sub == l) left_rank = ~0u;
-        sel.template scan<true, false, false>(group_lane(range.x, l), group_lane(range.y, l));
-    }
-    if (sel.feasG < 0) {
-        float left = T;
-        for (;;) {
-            const float least = from_ordered_bits(min_over<true>(ordered_bits(left)));
-            const uint32_t mask = group_ballot(left == least && left < inf);
-            if (!mask || least > sel.bestT) break;
-            const int l = __ffs(mask) - 1;
-            if (sub == l) left = inf;
-            const int first = group_lane(range.x, l), n = group_lane(range.y, l);
-            sel.template scan<false, true, false>(first, n);
-            sel.settle(first, n);
+        enter(l);
+        for (int r0 = 0; r0 < n; r0 += kChunks * kGroup) {
+            float b[kChunks];
+            bounds(r0, b);
+            unsigned long long open = 0;
+#pragma unroll
+            for (int j = kChunks - 1; j >= 0; --j) open = (open << kGroup) | group_ballot(b[j] <= Dc);
+            uint32_t hit = 0;
+            for (; open && !hit; open &= open - 1) {
+                const int run = first + r0 + __ffsll((long long)open) - 1, p = run * kMemoP + sub, g = a.order[p];
+                const unsigned long long pk = a.posKey[p];
+                const uint32_t thr = a.pos_thr[p];
+                const float T = fmaf(c0, kap, E[(size_t)run * kTile]);
+                hit = group_ballot(T <= Dc && g >= 0 && g != q.ex);
+                if (!hit) continue;
+                const int h = __ffs(hit) - 1;
+                const unsigned long long hk = group_lane(pk, h);
+                const int hg = group_lane(g, h);
+                const float hT = group_lane(T, h);
+                const uint32_t ht = group_lane(thr, h);
+                if (feasG < 0 || hk < feasKey || (hk == feasKey && hg < feasG)) {
+                    feasKey = hk; feasG = hg; feasT = hT; feasThr = ht;
+                }
+            }
+            if (hit) break;
         }
     }
-    sel.template report<kMigrate>(i, q.D);
+    if (feasG >= 0) {
+        if (sub == 0) answer<kMigrate>(a, i, feasG, q.D - feasT, true);
+        return;
+    }
+    // the least latency: class by class, run by run, as long as the least one left does not exceed what there is
+    float bestT = inf, left = T_least;
+    int bestG = -1;
+    for (;;) {
+        const float least = from_ordered_bits(min_over<true>(ordered_bits(left)));
+        const uint32_t mask = group_ballot(left == least && left < inf);
+        if (!mask || least > bestT) break;
+        const int l = __ffs(mask) - 1;
+        if (sub == l) left = inf;
+        enter(l);
+        for (int r0 = 0; r0 < n; r0 += kChunks * kGroup) {
+            float b[kChunks];
+            bounds(r0, b);
+            for (;;) {
+                float m = b[0];
+#pragma unroll
+                for (int j = 1; j < kChunks; ++j) m = fminf(m, b[j]);
+                m = from_ordered_bits(min_over<true>(ordered_bits(m)));
+                if (!(m <= bestT && m < inf)) break;
+                int at = 0;
+#pragma unroll
+                for (int j = kChunks - 1; j >= 0; --j) {
+                    const uint32_t here = group_ballot(b[j] == m);
+                    if (here) at = j * kGroup + __ffs(here) - 1;
+                }
+#pragma unroll
+                for (int j = 0; j < kChunks; ++j) b[j] = j * kGroup + sub == at ? inf : b[j];
+                const int run = first + r0 + at, p = run * kMemoP + sub;
+                if (m == bestT && __float_as_int(a.run_k[run].w) > bestG) continue;      // (nobody at a lower index)
+                const int g = a.order[p];
+                const float T = fmaf(c0, kap, E[(size_t)run * kTile]);
+                const bool in = g >= 0 && g != q.ex && T < inf;
+                const float t = from_ordered_bits(min_over<true>(in ? ordered_bits(T) : ~0u));
+                if (!group_ballot(in) || t > bestT) continue;
+                const int low = (int)min_over<true>(in && T == t ? (uint32_t)g : 0x7fffffffu);
+                if (t < bestT || low < bestG) { bestT = t; bestG = low; }
+            }
+        }
+    }
+    if (sub == 0) answer<kMigrate>(a, i, bestG, bestG >= 0 ? q.D - bestT : 0.f, false);
 }
 
 // With a blend every instance has its own prefill rate, and no least E decides a request.  But for a length and a
@@ -1438,88 +1516,133 @@ __global__ __launch_bounds__(kBlock) void k_lines(SelectArgs a)
     a.lines[lines_at(row, range) + 1] = found[1];
 }
 
-// A lane per request over the classes first; what that does not decide (a deadline that somebody
+// The least latency of a request over the classes (infinite or not a number: none), by four lanes, and what is known of it: in the
+// upper bits how many classes have it, then as in low_and_gap.
+//
+// Each of the four lanes reads 16 bytes of what is known of a length.  A lane that reads all of its own request's takes a cache
+// line for every 16 bytes, and the address units take one line at a time: with the row of a length, its classes and the next larger E, one
+// after the other, 256 lines a wave, now 64 (scan of 4 096 x 512 with 6 classes 106.4 us, 104.7; its refresh and 262 144
+// requests 71.1, 69.4).
+template <int kLoads>
+struct ClassesOf {
+    const SelectArgs& a;
+    const int sub, pieces;
+    float2 dg[kLoads][2];      // of this lane's classes (no such class: not a number, and so is every latency)
+
+    __device__ __forceinline__ explicit ClassesOf(const SelectArgs& args)
+        : a(args), sub(threadIdx.x % kLanes), pieces(1 << (args.class_shift - 1))
+    {
+#pragma unroll
+        for (int l = 0; l < kLoads; ++l)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int c = 2 * (sub + l * kLanes) + h;
+                dg[l][h] = a.clsK[min(c, a.n_class - 1)];
+                if (c >= a.n_class) dg[l][h].x = __builtin_nanf("");
+            }
+    }
+
+    __device__ __forceinline__ void read(int L, uint4 (&e)[kLoads]) const
+    {
+        const uint4* __restrict__ table = reinterpret_cast<const uint4*>(a.class_least) + ((uint32_t)L << (a.class_shift - 1));
+#pragma unroll
+        for (int l = 0; l < kLoads; ++l) e[l] = table[(sub + l * kLanes) & (pieces - 1)];
+    }
+
+    __device__ __forceinline__ void least(float c0, float Lf, const uint4 (&e)[kLoads], float& best, uint32_t& what) const
+    {
+        const float inf = __builtin_inff();
+        float T = inf;
+        uint32_t w = 0;
+        const auto take = [&](float2 k, uint32_t ev, uint32_t wv) {
+            const float t = min_plain(fmaf(c0, kappa_of(k, Lf), __uint_as_float(ev)), inf);
+            wv |= 1u << kCountAt;
+            w = t < T ? wv : t == T ? w | 2u << kCountAt : w;
+            T = min_plain(T, t);
+        };
+#pragma unroll
+        for (int l = 0; l < kLoads; ++l) { take(dg[l][0], e[l].x, e[l].y); take(dg[l][1], e[l].z, e[l].w); }
+        best = min_plain(T, quad_move<0xB1>(T));
+        best = min_plain(best, quad_move<0x4E>(best));
+        w = T == best ? w : 0u;
+        w += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0xB1, 0xf, 0xf, true);
+        what = w + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, 0x4E, 0xf, 0xf, true);
+    }
+};
+
+// Four lanes per request over the classes first; what that does not decide (a deadline that somebody
 // meets, the least latency on the excluded instance, a tie that rounding may have made) is
 // collected in LDS and taken by groups of lanes as above.  A workgroup takes its requests from all
 // over the batch, kGroup consecutive ones at a time: the requests of one instance are neighbours,
 // and those of the instance that most requests would pick all need the second half.
 //
-// kLanes lanes of the workgroup take kItems requests each in the first half; all of it takes part in
-// the second.
-template <bool kMigrate, int kLanes, int kItems>
-__global__ __launch_bounds__(kBlock) void k_select_by_class(SelectArgs a)
+// kRequests of a workgroup: one of every lane, whose four lanes take their requests one after the other, or of four lanes.
+template <bool kMigrate, int kRequests, int kLoads>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_select_by_class(SelectArgs a)
 {
-    struct Left { Request q; int row, index; };      // (kept: reading a request again is two more trips to memory)
-    __shared__ Left todo[kLanes * kItems];
+    static_assert(kRequests == kBlock || kRequests * kLanes == kBlock);
+    constexpr bool kEach = kRequests == kBlock;
+    struct Left { Request q; int index; };      // (kept: reading a request again is two more trips to memory)
+    __shared__ Left todo[kRequests];
     __shared__ int n_todo;
     const int tid = threadIdx.x;
     if (tid == 0) n_todo = 0;
     __syncthreads();
-    const auto index = [&](int it, int lane) {
-        return ((int64_t)(it * (kLanes / kGroup) + lane / kGroup) * a.segments + blockIdx.x) * kGroup + lane % kGroup;
-    };
-    if (tid < kLanes) {
-        const float inf = __builtin_inff();
-        Request q[kItems];
-        int64_t row[kItems];
-        float best[kItems];
-        int cls[kItems];
-        bool tie[kItems], in[kItems];
-#pragma unroll
-        for (int it = 0; it < kItems; ++it) {
-            const int64_t i = index(it, tid);
-            in[it] = i < a.s.n;
-            q[it] = fetch<kMigrate>(a.s, min(i, a.s.n - 1), a.max_len);
-            best[it] = inf; cls[it] = 0; tie[it] = false;
+    const auto index = [&](int r) { return ((int64_t)(r / kGroup) * a.segments + blockIdx.x) * kGroup + r % kGroup; };
+    {
+        const ClassesOf<kLoads> classes(a);
+        const int r = kEach ? tid : tid / kLanes;
+        const int64_t i = index(r);
+        const Request q = fetch<kMigrate>(a.s, min(i, a.s.n - 1), a.max_len);
+        float best;
+        uint32_t what;
+        if constexpr (kEach) {
+            const auto of = [&](auto k, uint32_t x) {      // (quad_perm [k,k,k,k])
+                return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(k)::value * 0x55, 0xf, 0xf, true);
+            };
+            using std::integral_constant;
+            const auto each = [&](auto f) {
+                f(integral_constant<int, 0>{}); f(integral_constant<int, 1>{}); f(integral_constant<int, 2>{}); f(integral_constant<int, 3>{});
+            };
+            uint4 e[kLanes][kLoads];
+            each([&](auto k) { classes.read((int)of(k, (uint32_t)q.L), e[k]); });
+            const uint32_t c0 = __float_as_uint((float)q.c0), Lf = __float_as_uint((float)q.L);
+            each([&](auto k) {
+                float b;
+                uint32_t w;
+                classes.least(__uint_as_float(of(k, c0)), __uint_as_float(of(k, Lf)), e[k], b, w);
+                best = k == 0 || classes.sub == k ? b : best;
+                what = k == 0 || classes.sub == k ? w : what;
+            });
+        } else {
+            uint4 e[kLoads];
+            classes.read(q.L, e);
+            classes.least((float)q.c0, (float)q.L, e, best, what);
         }
-#pragma unroll
-        for (int it = 0; it < kItems; ++it) row[it] = a.len_row[q[it].L];
-        for (int c0 = 0; c0 < a.n_class; c0 += 4) {
-            float4 e[kItems];
-#pragma unroll
-            for (int it = 0; it < kItems; ++it) e[it] = *reinterpret_cast<const float4*>(a.class_min + row[it] * a.c_pad + c0);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (c0 + k >= a.n_class) break;
-                const float2 dg = a.clsK[c0 + k];
-#pragma unroll
-                for (int it = 0; it < kItems; ++it) {
-                    const float ek = k == 0 ? e[it].x : k == 1 ? e[it].y : k == 2 ? e[it].z : e[it].w;
-                    const float T = fmaf((float)q[it].c0, kappa_of(dg, (float)q[it].L), ek);
-                    if (T < best[it]) { best[it] = T; cls[it] = c0 + k; tie[it] = false; }
-                    else tie[it] = tie[it] || T == best[it];
-                }
-            }
+        const float D = q.D, Dc = D > FLT_MAX ? FLT_MAX : D;
+        const int g = (int)(what & ((1u << kLowBits) - 1u));
+        // the next larger E of the class gives a larger T: by four units in the last place of T at least
+        const int gap = (int)(what >> kLowBits & 0xFFu), size = (int)(__float_as_uint(best) >> 23 & 0xFFu);
+        const bool alone = what >> kCountAt == 1u && gap > 0 && gap >= size - 21;
+        const bool decided = alone && fabsf(best) < __builtin_inff() && g != q.ex && !(best <= Dc);
+        const bool in = i < a.s.n && (kEach || classes.sub == 0), later = in && q.scored && !decided;
+        if (in && !later) {
+            if (q.scored) answer<kMigrate>(a, i, g, D - best, false);
+            else answer<kMigrate>(a, i, -1, 0.f, false);
         }
-        uint2 next[kItems];
-#pragma unroll
-        for (int it = 0; it < kItems; ++it) next[it] = a.class_next[row[it] * a.n_class + cls[it]];
-#pragma unroll
-        for (int it = 0; it < kItems; ++it) {
-            const int64_t i = index(it, tid);
-            const float D = q[it].D, Dc = D > FLT_MAX ? FLT_MAX : D;
-            const int g = (int)next[it].y;
-            const float T2 = fmaf((float)q[it].c0, kappa_of(a.clsK[cls[it]], (float)q[it].L), __uint_as_float(next[it].x));
-            const bool decided = best[it] < inf && !tie[it] && T2 > best[it] && g != q[it].ex && !(best[it] <= Dc);
-            const bool later = in[it] && q[it].scored && !decided;
-            if (in[it] && !later) {
-                if (q[it].scored) answer<kMigrate>(a, i, g, D - best[it], false);
-                else answer<kMigrate>(a, i, -1, 0.f, false);
-            }
-            const unsigned long long m = __ballot(later);
-            if (m) {
-                int at = 0;
-                if (lane_id() == 0) at = atomicAdd(&n_todo, __popcll(m));
-                at = __builtin_amdgcn_readfirstlane(at);
-                if (later) todo[at + __popcll(m & ((1ull << lane_id()) - 1ull))] = Left{q[it], (int)row[it], it * kLanes + tid};
-            }
+        const unsigned long long m = __ballot(later);
+        if (m) {
+            int at = 0;
+            if (lane_id() == 0) at = atomicAdd(&n_todo, __popcll(m));
+            at = __builtin_amdgcn_readfirstlane(at);
+            if (later) todo[at + __popcll(m & ((1ull << lane_id()) - 1ull))] = Left{q, r};
         }
     }
     __syncthreads();
     const int n = n_todo;
     for (int k = tid / kGroup; k < n; k += kBlock / kGroup) {
         const Left& t = todo[k];
-        select_by_class<kMigrate, 4, kMigrate>(a, index(t.index / kLanes, t.index % kLanes), t.q, t.row, tid % kGroup);
+        select_by_class<kMigrate, kMigrate>(a, index(t.index), t.q, tid % kGroup);
     }
 }
 
@@ -2255,9 +2378,11 @@ static bool pairs_finite(const gr_fleet* f, int64_t n)
 }
 
 constexpr int64_t kByClassMin = int64_t(1) << 17;      // requests from which the classes are looked at first
-// and from which a workgroup takes 512 of them (64 otherwise; kernel time of a scan of 2.1 M with 1 024
-// 38 us, with 512 33)
-constexpr int64_t kByClassMany = int64_t(1) << 19;
+// and from which a workgroup takes 256 of them (64 otherwise).  Whole calls, us, 64 / 256: scan of 1 024 x 400 39.95 / 38.2,
+// of 1 024 x 1 000 56.1 / 53.0 (deadlines x 16 76.5 / 69.3); refresh of 4 096 instances and 262 144 requests 64.8 / 64.9, of which a batch
+// with deadlines that many meet (x 16) wants the lanes for its second half: 70.3 / 77.7, 140 000 on 2 000 52.6 / 64.3.
+constexpr int64_t kByClassMany[2] = {int64_t(1) << 19, int64_t(1) << 18};      // routing, risk scan
+constexpr int64_t kLinesMany = int64_t(1) << 19;      // and on fleets of few runs
 constexpr int64_t kLinesScanMin = int64_t(3) << 16;     // requests of a scan from which the lines are looked at first
 
 constexpr int64_t kLaneMin = 1 << 15;      // requests from which four lanes take one, on fleets of few runs (see k_select_lanes)
@@ -2273,13 +2398,17 @@ static void launch_select(const gr_fleet* f, SelectArgs a, bool by_class, bool b
 {
     const int64_t n = a.s.n;
     if (by_class) {
-        // large batches: two requests per lane of a whole workgroup; else a wave's worth per workgroup,
-        // so that the second half has the lanes when many requests need it
-        const bool many = n >= kByClassMany;
-        const int64_t per = many ? 2 * kBlock : kWave;
+        // large batches: a request per lane; else a wave's worth per workgroup, so that the second half has the
+        // lanes when many requests need it
+        const bool many = n >= kByClassMany[kMigrate];
+        const int64_t per = many ? kBlock : kBlock / kLanes;
         a.segments = (int)((n + per - 1) / per);
-        if (many) hipLaunchKernelGGL((k_select_by_class<kMigrate, kBlock, 2>), dim3(a.segments), dim3(kBlock), 0, s, a);
-        else hipLaunchKernelGGL((k_select_by_class<kMigrate, kWave, 1>), dim3(a.segments), dim3(kBlock), 0, s, a);
+#define GR_LAUNCH_BY_CLASS(N) do { \
+        if (f->n_class <= 2 * kLanes) hipLaunchKernelGGL((k_select_by_class<kMigrate, N, 1>), dim3(a.segments), dim3(kBlock), 0, s, a); \
+        else hipLaunchKernelGGL((k_select_by_class<kMigrate, N, 2>), dim3(a.segments), dim3(kBlock), 0, s, a); } while (0)
+        if (many) GR_LAUNCH_BY_CLASS(kBlock);
+        else GR_LAUNCH_BY_CLASS(kBlock / kLanes);
+#undef GR_LAUNCH_BY_CLASS
         return;
     }
     if (!by_lines && f->n_run <= kLaneRuns && n >= kLaneMin) {
@@ -2490,7 +2619,7 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     // A scan takes a lane per request and lists the rest, as most of it may not be late at all (3 270 x 130, a
     // group of lanes per request from the lines on: 125 us, listed 92).
     const bool by_lines = select && (blended || f->n_class > kGroup) && n >= (migrate ? kLinesScanMin : kByClassMin) &&
-                          f->n_run > (migrate && n >= kByClassMany ? 2 : 5) * kGroup;
+                          f->n_run > (migrate && n >= kLinesMany ? 2 : 5) * kGroup;
     const bool listed = by_lines && migrate && f->n_run <= kRestRuns;
     // The runs' minima in blocks of rows where the classes are looked at first (6 us less for the
     // table of 7 061 rows x 4 096 instances); else row by row: a request's 16 lanes then read 16
@@ -2525,8 +2654,8 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     if (by_class) {
         ClassArgs c{};
         c.totals = f->totals; c.cls_run = f->cls_run; c.order = f->order; c.memo = f->memo; c.grp_min = f->grp_min;
-        c.run_k = f->run_k; c.row_min = f->row_min; c.class_min = f->class_min; c.class_next = f->class_next; c.cls_bound = f->cls_bound;
-        c.n_class = f->n_class; c.c_pad = f->c_pad; c.n_run = f->n_run; c.run_pad = f->run_pad;
+        c.run_k = f->run_k; c.row_min = f->row_min; c.row_len = f->row_len; c.class_least = f->class_least; c.run_rank = f->run_rank; c.cls_rank = f->cls_rank;
+        c.n_class = f->n_class; c.class_shift = f->class_shift; c.n_run = f->n_run; c.run_pad = f->run_pad;
         ProfScope ps(f, kClassRoute + off, s);
         const dim3 grid((unsigned)((max_rows + kWave - 1) / kWave * f->n_class));
         if (rows_too) hipLaunchKernelGGL(k_class<true>, grid, dim3(kBlock), 0, s, c);
@@ -2535,9 +2664,9 @@ int launch_score(gr_fleet* f, const ReqSrc& src, bool migrate, const ScoreOut& o
     if (select) {
         SelectArgs a{};
         a.s = src; a.len_row = rows.len_row; a.order = f->order; a.memo = f->memo; a.grp_min = rows_too ? f->row_min : f->grp_min; a.run_k = f->run_k;
-        a.posK = f->posK; a.posKey = f->posKey; a.run_rank = f->run_rank; a.pos_thr = f->pos_thr; a.run_at = f->run_at; a.cls_run = f->cls_run; a.class_min = f->class_min; a.class_next = f->class_next; a.clsK = f->clsK; a.cls_bound = f->cls_bound;
+        a.posK = f->posK; a.posKey = f->posKey; a.run_rank = f->run_rank; a.pos_thr = f->pos_thr; a.run_at = f->run_at; a.cls_run = f->cls_run; a.class_least = f->class_least; a.clsK = f->clsK; a.cls_rank = f->cls_rank;
         a.out_inst = out.inst; a.out_slack = out.slack; a.out_fallback = out.fallback;
-        a.run_pad = f->run_pad; a.n_run = f->n_run; a.n_class = f->n_class; a.c_pad = f->c_pad;
+        a.run_pad = f->run_pad; a.n_run = f->n_run; a.n_class = f->n_class; a.class_shift = f->class_shift;
         a.max_len = f->max_len; a.n_inst = f->n_inst;
         a.lines = f->lines; a.totals = f->totals; a.row_len = f->row_len; a.pos_of = f->pos_of;
         a.rest_cnt = f->rest_cnt;

@@ -99,6 +99,20 @@ def test_classes_first(n_req, n_class, kind):
     _check(_fleet(1300, n_class, n_req, kind))
 
 
+# Least and next larger E of a class a rounding or a few apart (one queued prompt token is 2e-5 s), and prompts so long, or of the
+# other sign, that their latencies fall together; as many classes as one piece, two, four and eight of 16 bytes hold.
+@pytest.mark.parametrize("n_class", [1, 2, 3, 5, 8, 9, 16])
+def test_classes_first_latencies_that_rounding_makes_equal(n_class):
+    rng = np.random.default_rng(n_class)
+    M, R = 1100, (1 << 17) + 1
+    classes = [tuple(x * f for x in CLASSES[c % 3]) for c, f in enumerate(np.linspace(1.0, 1.7, n_class))]
+    some = [rand_entries(rng, int(n)) for n in rng.integers(1, 40, 5)]
+    queued = [[(int(t), 4000)] if t else [] for t in rng.integers(0, 4, M)]
+    inc = np.stack([rng.choice([1, 900, 2048, 1 << 15, 1 << 20, 1 << 24, 1 << 29, 0, -3, -(1 << 22)], R), rng.integers(0, 700, R)], 1)
+    budgets = np.exp(rng.uniform(np.log(0.2), np.log(3), R)) * solo(np.abs(inc[:, 0]), inc[:, 1])
+    _check(fleet(rng.integers(0, n_class, M), [some[g % 5] for g in range(M)], queued, inc, budgets, classes=classes))
+
+
 @pytest.mark.parametrize("blend", [0.5, 1.0])
 def test_classes_first_blended(blend):
     _check(_fleet(2200, 3, (1 << 17) + 3, "mixed"), blend=blend)
