@@ -76,7 +76,8 @@ enum {
 /* bits of gr_device_status */
 enum {
     GR_DEV_LEN_CLAMPED = 1,   /* a length outside [0, max_len] was clamped */
-    GR_DEV_ENTRIES_DROPPED = 2 /* an instance held more than max_entries_per_inst entries */
+    GR_DEV_ENTRIES_DROPPED = 2, /* an instance held more than max_entries_per_inst entries */
+    GR_DEV_STALLED = 4         /* feedback routing gave up a wait inside the device (not expected to happen) */
 };
 
 /*
@@ -103,8 +104,8 @@ enum {
  *   4 * rows * [M' / 16 rounded up to 16] bytes   the minima over runs once more (18 MB there), for max_requests of 131 072
  *                                    and more on fleets of up to 16 classes with M' of at least 1 024 and 64 * n_class,
  *   at most 64 MB, or 1 024 * n_inst bytes if that is more   rows of that table for out_T,
- *   (24 * cap + 600) * n_inst bytes  feedback routing, up to 512 instances with cap of 128 and more: what they offer a chunk, sums
- *                                    behind the tables,
+ *   (50 * cap + 1000) * n_inst bytes  feedback routing, up to 512 instances with cap of 128 and more: what they offer a chunk, sums
+ *                                    behind the tables and of what is routed,
  *   0.4 MB                           selections of small batches on fleets of more than 4 096 instances,
  * plus a few arrays of n_inst, M' or max_len + 1 words.
  */
@@ -354,6 +355,14 @@ int gr_set_batch_cap(gr_fleet* f, const int32_t* cap);
  * at most 4096 requests and n * (n_inst rounded up to 128) at most 262 144.
  */
 int gr_set_small_batch_pairs(gr_fleet* f, int64_t max_pairs);
+
+/*
+ * How often the workgroups of a feedback routing that runs in one launch look for each other (about a microsecond
+ * each) before one of them does the work of all, one instance after the other: at least once, 4096 times if it is never
+ * set.  The results are the same; on a device that cannot run all of them at once (a stream of few compute units) it
+ * takes many times as long.
+ */
+int gr_set_feedback_wait(gr_fleet* f, int32_t looks);
 
 /*
  * Synchronises the device and returns the OR of the GR_DEV_* bits raised by

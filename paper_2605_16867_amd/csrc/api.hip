@@ -132,6 +132,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
 
     const size_t tab = (size_t)n_inst * f->cap, segments = (size_t)n_inst * (f->cap + 1), seen_bytes = (size_t)(f->bins + 15) / 16 * 16;
     const bool by_row = classes_first(f, false, max_requests), by_round = n_inst <= kFeedInst && waves_per_instance(f->epl, n_inst) > 1;
+    const size_t groups = feed_groups(n_inst), words = 2 * groups * kWave + 2 * (size_t)n_inst * 4 + 1;
     const bool ok =
         dev_alloc(&f->cls, n_class) && dev_alloc(&f->inst_class, n_inst) &&
         dev_alloc(&f->tabR, tab + kWave) && dev_alloc(&f->tabGH, (size_t)n_inst * (f->cap + 2) + kWave) &&
@@ -150,11 +151,18 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
         dev_alloc(&f->cls_rank, n_class) && (n_class > kMemoP || dev_alloc(&f->class_least, (size_t)f->bins << f->class_shift)) &&
         dev_alloc(&f->rest_cnt, kRestParts * kRestStride) && dev_alloc(&f->lines, (size_t)f->row_cap * kRanges * 2) && dev_alloc(&f->turned, (size_t)f->turned_rows * n_inst) && dev_alloc(&f->direct_part, (size_t)kDirectParts) &&
         (!by_round || (dev_alloc(&f->feed_T, (size_t)2 * n_inst * kWave) && dev_alloc(&f->feed_met, (size_t)2 * n_inst) &&
-                       dev_alloc(&f->feed_key, (size_t)2 * n_inst) &&
+                       dev_alloc(&f->feed_key, (size_t)2 * n_inst) && dev_alloc(&f->feed_words.least, words) && dev_alloc(&f->feed_blocks.yx, tab + (tab * 10 + 15) / 16) &&
                        dev_alloc(&f->feed_base, n_inst + (segments * (sizeof(double2) + sizeof(double)) + sizeof(FeedBase) - 1) / sizeof(FeedBase))));
     if (!ok) { gr_destroy(f); return GR_ERR_NOMEM; }
     // (parts of one allocation: each takes its time)
     if (by_row) f->row_min = f->grp_min + (size_t)f->row_cap * f->run_pad;
+    if (by_round) {
+        f->feed_words.own = f->feed_words.least + 2 * groups * kWave;
+        f->feed_words.mode = reinterpret_cast<uint32_t*>(f->feed_words.own + 2 * (size_t)n_inst * 4);
+        f->feed_words.n = (int)words;
+        f->feed_blocks.c = reinterpret_cast<double*>(f->feed_blocks.yx + tab);
+        f->feed_blocks.R = reinterpret_cast<uint16_t*>(f->feed_blocks.c + tab);
+    }
     static_assert(sizeof(FeedBase) % sizeof(double2) == 0, "the sums begin at a multiple of 16 bytes");
     if (f->feed_base) {
         f->feed_yx = reinterpret_cast<double2*>(f->feed_base + n_inst);
@@ -206,7 +214,7 @@ int gr_destroy(gr_fleet* f)
     void* ptrs[] = {f->cls, f->inst_class, f->tabR, f->tabGH, f->hD, f->emaQ, f->emaP, f->emaD, f->instK, f->tabS,
                     f->clsK, f->slot_inst, f->slot_of, f->slot_key, f->run_cls, f->cls_run, f->order, f->pos_of, f->posK, f->posKey, f->run_head, f->act_inst, f->pend_cnt, f->commit_mark, f->pend_touched, f->pend_prompt, f->pend_len,
                     f->scratch_finish, f->batch_cap, f->counters, f->seen, f->late_cnt, f->row_len,
-                    f->len_row, f->totals, f->dense_totals, f->memo, f->grp_min, f->run_k, f->run_rank, f->run_at, f->pos_thr, f->cls_rank, f->class_least, f->rest_cnt, f->lines, f->turned, f->feed_T, f->feed_met, f->feed_key, f->feed_base, f->direct_part};
+                    f->len_row, f->totals, f->dense_totals, f->memo, f->grp_min, f->run_k, f->run_rank, f->run_at, f->pos_thr, f->cls_rank, f->class_least, f->rest_cnt, f->lines, f->turned, f->feed_T, f->feed_met, f->feed_key, f->feed_base, f->feed_words.least, f->feed_blocks.yx, f->direct_part};
     int rc = GR_OK;
     for (void* p : ptrs)
         if (p && hipFree(p) != hipSuccess) rc = GR_ERR_HIP;
@@ -408,6 +416,13 @@ int gr_set_small_batch_pairs(gr_fleet* f, int64_t max_pairs)
 {
     if (!f || max_pairs < 0) return GR_ERR_INVALID_ARG;
     f->small_batch_pairs = max_pairs;
+    return GR_OK;
+}
+
+int gr_set_feedback_wait(gr_fleet* f, int32_t looks)
+{
+    if (!f || looks < 0) return GR_ERR_INVALID_ARG;
+    f->feed_polls = looks;
     return GR_OK;
 }
 

@@ -100,6 +100,20 @@ struct FeedBase {
     int pad;
 };
 
+// Words that the workgroups of a feedback routing in one launch leave for each other (see k_feedback_rounds).
+struct FeedWords {
+    unsigned long long *least = nullptr, *own = nullptr;   // [2][feed_groups][kWave], [2][M][4]
+    uint32_t* mode = nullptr;                              // [1]
+    int n = 0;                                             // all of them, in words of 8 bytes, from `least` on
+};
+// and where they put away what has come to an instance since its table was built, 64 requests at a time
+struct FeedBlocks {
+    double2* yx = nullptr;     // [M][cap] sums of R, c*R + tri(R) up to each of the 64, in order of length
+    double* c = nullptr;       // [M][cap] of contexts
+    uint16_t* R = nullptr;     // [M][cap] the lengths
+};
+constexpr int feed_groups(int n_inst) { return (n_inst + 3) / 4; }
+
 enum KernelId {
     kBuild = 0, kRank, kMarkRoute, kScanRoute, kMemoRoute, kClassRoute, kLinesRoute, kSelectRoute,
     kScanMigrate, kMemoMigrate, kClassMigrate, kLinesMigrate, kSelectMigrate, kHitsRoute, kPairsRoute, kDirect, kDirectMerge, kFeedback,
@@ -239,6 +253,9 @@ struct gr_fleet {
     double2* feed_yx = nullptr;             // [M][cap + 1]
     double* feed_c = nullptr;               // [M][cap + 1]
     gr::FeedBase* feed_base = nullptr;      // [M]
+    gr::FeedWords feed_words;
+    gr::FeedBlocks feed_blocks;
+    int feed_polls = 4096;                  // see gr_set_feedback_wait
     gr::DirectPart* direct_part = nullptr;       // [kDirectParts] selections of the parts of a wide fleet, scored pair by pair
 };
 

@@ -190,13 +190,13 @@ __device__ __forceinline__ void bitonic_distances(uint32_t (&key)[kEPL], int lan
     }
 }
 
-template <bool kChain, int kEPL, int K>
+template <bool kChain, int kEPL, int K, int kMost = kWave * kEPL>
 __device__ __forceinline__ void bitonic_levels(uint32_t (&key)[kEPL], int lane, int lane4)
 {
-    if constexpr (K <= kWave * kEPL) {
+    if constexpr (K <= kMost) {
         bitonic_mirror<kChain, kEPL, K>(key, lane, lane4);
         bitonic_distances<kChain, kEPL, K / 4>(key, lane, lane4);
-        bitonic_levels<kChain, kEPL, 2 * K>(key, lane, lane4);
+        bitonic_levels<kChain, kEPL, 2 * K, kMost>(key, lane, lane4);
     }
 }
 
@@ -1262,8 +1262,8 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
 // workgroup for itself: a lane per request, the waves share the instances), takes in what was sent to the instance, and
 // offers for the next chunk: each request's latency here, whether its deadline is met, and d_g.
 // The launches themselves are the wait of one round for the other.  What was sent to an instance is taken in by building its
-// table anew, or (kAdd, for small rounds, see adds_up) by adding it to the sums of the table as it was built last: the tables
-// are all built once at the start, one with more than kFeedListed requests added anew, and at the end those that were given any.
+// table anew.  (For one or two rounds, and for many requests to an instance and round: see in_one_launch.  Else the tables are all built once at
+// the start, with the sums behind them, kSums, and those that have been given any at the end.)
 //
 // What bounds it is the chain of a round: the offers (64 requests x 256 instances are 64 KB for every workgroup, from
 // L2), the choice, then the rebuild, whose table is still in LDS when the next requests are looked up in it.  A round was
@@ -1286,19 +1286,18 @@ struct FeedArgs {
     uint8_t* out_fallback;
 };
 
-// Where what comes is added to the tables' sums (see gr_fleet) instead of building them anew.
-struct FeedAddArgs {
+// The launches before and behind k_feedback_rounds, which adds what comes to the tables' sums (see gr_fleet).
+struct FeedSumsArgs {
     FeedArgs f;
     int move;
     double2* sums_yx;
     double* sums_c;
     FeedBase* base;
+    FeedWords words;      // n = 0: nobody exchanges any
 };
 
-// What such a launch does to the tables: nothing; all of them are built; what has come since an instance's table was
-// built is added to its sums; all that have been given requests since are built.
-enum FeedMove { kFeedNone = 0, kFeedAll, kFeedAdd, kFeedTouched };
-constexpr int kFeedListed = 32;      // requests added to an instance's sums before its table is built anew (a wave holds them)
+// What such a launch does to the tables: nothing; all of them are built; all that have been given requests since are.
+enum FeedMove { kFeedNone = 0, kFeedAll, kFeedTouched };
 
 // Segment and latency of a request in the instance's table as it stands, in two steps as k_direct.
 template <int kTab>
@@ -1347,12 +1346,8 @@ __device__ __forceinline__ unsigned long long wave_or_u64(unsigned long long v)
     return ((unsigned long long)wave_or_u32((uint32_t)(v >> 32)) << 32) | wave_or_u32((uint32_t)v);
 }
 
-// kAdd: the tables stay as they were built last, with the sums behind them, and what has come since is added to those for
-// every request anew, in fp64, so that a segment comes to the same (Gq, H) bit for bit (while the sums are below 2^53).  One wave more than share the
-// instance gathers what it takes (the segments of the table, the list since then) while the others decide.  A round of one request on 256
-// instances 9.6 us with a rebuild, 6.6 this way; of 64 requests 10.0 / 9.3.
-template <int kEPL, int kSplit, bool kAdd>
-__global__ __launch_bounds__(kWave * (kSplit + kAdd), (kEPL <= 8 ? 4 : 1)) void k_feedback(std::conditional_t<kAdd, FeedAddArgs, FeedArgs> args)
+template <int kEPL, int kSplit, bool kSums>
+__global__ __launch_bounds__(kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_feedback(std::conditional_t<kSums, FeedSumsArgs, FeedArgs> args)
 {
     extern __shared__ uint32_t smem[];
     __shared__ uint32_t share[kSplit][kWave];
@@ -1360,13 +1355,13 @@ __global__ __launch_bounds__(kWave * (kSplit + kAdd), (kEPL <= 8 ? 4 : 1)) void 
     constexpr int kTab = kWave * kEPL * kSplit;
     fetch_args<decltype(args)>();
     const auto of = [&]() -> const FeedArgs& {
-        if constexpr (kAdd) return args.f;
+        if constexpr (kSums) return args.f;
         else return args;
     };
     const FeedArgs& f = of();
     const BuildArgs& a = f.b;
     int move = kFeedNone;
-    if constexpr (kAdd) move = args.move;
+    if constexpr (kSums) move = args.move;
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     InstanceIn in;
     in.g = blockIdx.x;
@@ -1376,36 +1371,19 @@ __global__ __launch_bounds__(kWave * (kSplit + kAdd), (kEPL <= 8 ? 4 : 1)) void 
     const int pend = a.pend_cnt[g];
     const int touched = move == kFeedTouched ? a.pend_touched[g] : 0;
     Offer offer{};
-    if constexpr (kAdd) { offer.sums_yx = args.sums_yx; offer.sums_c = args.sums_c; offer.base = args.base; }
+    if constexpr (kSums) {
+        offer.sums_yx = args.sums_yx; offer.sums_c = args.sums_c; offer.base = args.base;
+        if (move == kFeedAll)
+            for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < args.words.n; i += gridDim.x * blockDim.x) args.words.least[i] = 0;
+    }
     float D = 0.f;
     int ex = -1;
-    // what the sums are added up from, on its way while the chunk is decided: of the table the requests' segments, and a
-    // lane each what has come since
-    FeedBase base{};
-    ClassCoef cc{};
-    double2 yx{};
-    double pc = 0.0;
-    int k = 0, since_ctx = 0, since_len = 0, join_ctx = 0, join_len = 0;
-    const bool adds = kAdd && move == kFeedAdd && wave == kSplit;
-    if (kAdd && move == kFeedAdd) base = offer.base[g];
-    if (f.next_n && (wave == 0 || adds)) {
+    if (f.next_n && wave == 0) {
         const int j = min(lane, f.next_n - 1);
         offer.L = min(max(f.next_len[j], 0), a.max_len);
         offer.c0 = (float)f.next_ctx0[j];
         D = f.next_budget[j];
         if (f.next_exclude) ex = f.next_exclude[j];
-        if (adds) {
-            cc = a.cls[a.inst_class[g]];
-            const int c = min(lane, a.chunk_n - 1);
-            join_ctx = a.chunk_ctx0[c];
-            join_len = a.chunk_len[c];
-            const size_t at = (size_t)g * kTab + min(base.listed + lane, kTab - 1);
-            since_ctx = a.pend_prompt[at];
-            since_len = a.pend_len[at];
-            k = segment_in_table<kTab>(a, g, offer.L);
-            yx = offer.sums_yx[(size_t)g * (kTab + 1) + k];
-            pc = offer.sums_c[(size_t)g * (kTab + 1) + k];
-        }
     }
 
     if (a.chunk_n) {
@@ -1414,7 +1392,7 @@ __global__ __launch_bounds__(kWave * (kSplit + kAdd), (kEPL <= 8 ? 4 : 1)) void 
         const uint32_t own = f.T_in[(size_t)g * kWave + lane];
         const unsigned long long own_key = f.key_in[g], own_met = f.met_in[g];
         unsigned long long any = 0, above = 0;         // requests whose deadline is met by somebody, by somebody more capable
-        for (int h = threadIdx.x; (!kAdd || wave < kSplit) && h < M; h += kSplit * kWave) {
+        for (int h = threadIdx.x; h < M; h += kSplit * kWave) {
             const unsigned long long met = f.met_in[h], key = f.key_in[h];
             any |= met;
             above |= key < own_key || (key == own_key && h < g) ? met : 0ull;
@@ -1422,7 +1400,7 @@ __global__ __launch_bounds__(kWave * (kSplit + kAdd), (kEPL <= 8 ? 4 : 1)) void 
         // the waves share the latencies; those at lower indices count as one less, so that `own` has to be below them
         const int per = (M + kSplit - 1) / kSplit, h0 = wave * per, n_here = min(per, M - h0);
         uint32_t least = ~0u;
-        if ((!kAdd || wave < kSplit) && n_here > 0) {
+        if (n_here > 0) {
             constexpr int kAhead = 16;
             const uint32_t* __restrict__ row = f.T_in + (size_t)h0 * kWave + lane;
             const int end = n_here * kWave, below = (g - h0) * kWave;
@@ -1442,8 +1420,8 @@ __global__ __launch_bounds__(kWave * (kSplit + kAdd), (kEPL <= 8 ? 4 : 1)) void 
         }
         any = wave_or_u64(any);
         above = wave_or_u64(above);
-        if (!kAdd || wave < kSplit) share[wave][lane] = least;
-        if ((!kAdd || wave < kSplit) && lane == 0) { met_by[wave][0] = any; met_by[wave][1] = above; }
+        share[wave][lane] = least;
+        if (lane == 0) { met_by[wave][0] = any; met_by[wave][1] = above; }
         __syncthreads();
         any = above = 0;
 #pragma unroll
@@ -1467,75 +1445,475 @@ __global__ __launch_bounds__(kWave * (kSplit + kAdd), (kEPL <= 8 ? 4 : 1)) void 
         in.joins = __ballot(mine);
     }
 
-    const int joined = __popcll(in.joins);
-    const bool rebuild = !kAdd ? a.chunk_n && (in.joins || !a.only_touched)
-                         : move == kFeedAdd ? pend + joined - base.listed > kFeedListed
+    const bool rebuild = !kSums ? a.chunk_n && (in.joins || !a.only_touched)
                          : move == kFeedTouched ? in.joins || touched : move == kFeedAll;
     if (rebuild) {
-        if (kAdd && wave == kSplit) return;
-        clamp_instance<kTab, kAdd>(a, in, a_begin, a_end, q_begin, q_end, pend);
+        clamp_instance<kTab, kSums>(a, in, a_begin, a_end, q_begin, q_end, pend);
         const int N = in.A + in.Q + in.P;
         bool built = false;
         if constexpr (kEPL >= 4)
-            if (N <= kTab / 4) { build_instance<kEPL / 4, kSplit, kTab, true, true, kAdd>(a, in, wave, smem, &offer); built = true; }
+            if (N <= kTab / 4) { build_instance<kEPL / 4, kSplit, kTab, true, true, kSums>(a, in, wave, smem, &offer); built = true; }
         if constexpr (kEPL >= 2)
-            if (!built && N <= kTab / 2) { build_instance<kEPL / 2, kSplit, kTab, true, true, kAdd>(a, in, wave, smem, &offer); built = true; }
-        if (!built) build_instance<kEPL, kSplit, kTab, true, true, kAdd>(a, in, wave, smem, &offer);
-    } else if (kAdd && move == kFeedAdd) {
-        if (!adds) return;
-        if (in.joins) {      // they join the list here
-            const int nth = pend + __popcll(in.joins & ((1ull << lane) - 1ull));
-            if (((in.joins >> lane) & 1ull) && nth < kTab) {
-                a.pend_prompt[(size_t)g * kTab + nth] = join_ctx;
-                a.pend_len[(size_t)g * kTab + nth] = join_len;
-            }
-            if (lane == 0) { a.pend_cnt[g] = pend + joined; a.pend_touched[g] = 1; }
-        }
-        // Every sum is one of integers below 2^53, so the order does not matter, and what the segments come to is what a
-        // build would leave in the table (as in build_instance).  Requests beyond the instance's room are none.
-        double sum_ctx = 0.0;
-        int N = base.n, room = max(base.room - base.listed, 0);
-        const auto add = [&](int ctx, int length) {
-            const int R = min(max(length, 0), a.max_len);
-            const double Rd = (double)R, cd = (double)ctx, xe = fma(cd, Rd, (double)(R * (R - 1) / 2));
-            const bool left = R <= offer.L;
-            yx.x += left ? Rd : 0.0;
-            yx.y += left ? xe : 0.0;
-            pc += left ? cd : 0.0;
-            k += left;
-            sum_ctx += cd;
-            ++N;
-        };
-        for (int i = 0; i < pend - base.listed && room > 0; ++i, --room)
-            add(__builtin_amdgcn_readlane(since_ctx, i), __builtin_amdgcn_readlane(since_len, i));
-        for (unsigned long long m = in.joins; m && room > 0; m &= m - 1, --room) {
-            const int i = __ffsll((long long)m) - 1;
-            add(__builtin_amdgcn_readlane(join_ctx, i), __builtin_amdgcn_readlane(join_len, i));
-        }
-        const bool blended = a.lam != 0.0;
-        const double Ctot = base.ctx + sum_ctx, keep = 1.0 - a.lam, q = cc.delta * (base.q_ctx + sum_ctx);
-        const double bq = blended ? a.emaQ[g] : 0.0, bp = blended ? a.emaP[g] : 0.0, bd = blended ? a.emaD[g] : 0.0;
-        double Gq = k ? fma(cc.gamma, yx.y, fma(cc.beta, yx.x, q)) : q;
-        double Hs = fma(cc.gamma, Ctot - pc, fma(cc.beta, (double)(N - k + 1), cc.alpha));
-        double d = fma(cc.gamma, Ctot, fma(cc.beta, (double)N, cc.alpha));
-        if (blended) {
-            Gq = keep * Gq + a.lam * bq;
-            Hs = keep * Hs + a.lam * bd;
-            d = keep * d + a.lam * bd;
-        }
-        offer.T = latency_at(offer.c0, offer.L, inst_coef(a, cc, bp, N), make_float2((float)Gq, (float)Hs), k);
-        offer.key = falling_bits(d);
+            if (!built && N <= kTab / 2) { build_instance<kEPL / 2, kSplit, kTab, true, true, kSums>(a, in, wave, smem, &offer); built = true; }
+        if (!built) build_instance<kEPL, kSplit, kTab, true, true, kSums>(a, in, wave, smem, &offer);
     } else if (f.next_n && wave == 0) {
         offer.T = latency_in_table<kTab>(a, g, offer.c0, offer.L);
         offer.key = falling_bits(a.hD[g]);
     }
-    if (!f.next_n || !(wave == 0 || (adds && !rebuild))) return;
+    if (!f.next_n || wave != 0) return;
     const float Dc = D > FLT_MAX ? FLT_MAX : D;
     const bool ok = g != ex;      // (batches of this size take infinite latencies for latencies, see pairs_finite)
     const unsigned long long met = __ballot(ok && offer.T <= Dc);
     // (the least and the largest integer are NaNs with every bit set; here nothing is below the one, and the other is not allowed)
     f.T_out[(size_t)g * kWave + lane] = ok ? min(max(ordered_bits(offer.T), 1u), ~0u - 1u) : ~0u;
     if (lane == 0) { f.met_out[g] = met; f.key_out[g] = offer.key; }
+}
+
+// Feedback routing, all rounds in one launch.  A launch for every round costs its start, its arguments and cold reads, 9 us of which
+// the round itself is a third; here the workgroups go from round to round by words that they leave for each other in memory: each
+// carries its round in its lower half, is written and read past the caches that are not common (relaxed, agent scope), and is valid by itself,
+// so nothing is fenced or flushed.  32 to 64 workgroups see each other's words 1.55 us after they are written, 128 2.2 us, 256 3.6 us
+// (512 bytes each; on one XCD or on all of them alike): hence four instances to a workgroup, a wave each.
+//
+// A round.  Each wave has left d_g and the met deadlines of its instance, the workgroup the least latency over its four, per
+// request (with the instance, so that the least word is the answer).  While those are on their way the wave gathers what its next
+// offers are added up from.  Then every workgroup takes the least words of all for itself, each wave finds the
+// requests that its own instance is chosen for, puts them on its list, adds them to the sums and offers for the next chunk.  Nothing is built
+// anew meanwhile: what has come is held in LDS, as terms of the sums, and kFeedBlock of them are put away sorted, with their prefix sums,
+// as a block that is searched like the table itself.
+//
+// A lone wave's instructions are eight cycles each, so their number is what counts next to the exchange: other waves wait for the words,
+// so that the look at them is not behind the gathering (5.4 us a round instead of 6.5), and new requests are terms in LDS, written by
+// their lanes (as lanes read off one by one 5.4, now 4.1).  A form that built long lists' tables anew on the way spilled 150 registers: 13.
+//
+// Every wait ends.  In the first one nothing has been changed yet, and it is bounded: when all workgroups are seen to be running,
+// workgroup 0 says so (kFeedTogether), and from there on a wait is for workgroups that run; where one has waited in vain (a
+// stream on a few compute units, a chip full of others' work) the mode is kFeedAlone, all return, and a second launch of
+// one workgroup, which otherwise returns at once, takes all instances in turn.
+// Two sets of words in turn are enough: a workgroup writes a round's when it has seen all of the round before, whose writers had read
+// all of the one before that.
+//
+// 256 instances x 512, 32 rounds of 64, with the status build: 309 us with a launch for each, this way 164: a round is 4.1 us, of which the words
+// take 0.9, gathering with two blocks 1.3, the choice 0.5 to 0.9, adding and offering 0.6.
+enum FeedMode { kFeedUndecided = 0, kFeedTogether, kFeedAlone };
+constexpr int kFeedTagBits = 22, kFeedInstAt = kFeedTagBits;      // of a least word, below the latency: the round, the instance
+static_assert(kFeedInst <= 1 << (32 - kFeedInstAt));
+constexpr int kFeedMostRounds = 1 << (kFeedTagBits - 1);      // of one launch
+constexpr int kFeedPollsMore = 1 << 21;   // looks at the words of later rounds, which are there in microseconds
+constexpr int kFeedWaves = 4;             // instances of a workgroup
+constexpr int kFeedBlock = 32;            // requests that are put away together
+constexpr int kFeedHeld = kFeedBlock + kWave;      // requests of an instance that are held: less than a block, and a chunk
+
+struct FeedRoundsArgs {
+    BuildArgs b;
+    const int *ctx0, *pred_len, *exclude;
+    const float* budget;
+    int* out_inst;
+    float* out_slack;
+    uint8_t* out_fallback;
+    int64_t n;
+    int chunk, first, rounds;      // requests of a round, the first round here, rounds in all
+    int polls;                     // looks at the words of the first round, about a microsecond each, before a workgroup gives up
+    const double2* sums_yx;
+    const double* sums_c;
+    const FeedBase* base;
+    FeedBlocks blocks;
+    FeedWords words;
+    uint32_t* T;                   // [M][kWave] (several instances a wave) latencies offered
+};
+
+__device__ __forceinline__ unsigned long long peek(const unsigned long long* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void leave(unsigned long long* p, unsigned long long v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// An instance's sorted lengths in LDS, with the last of every eight and of every 64: #{R_i <= L} is three short steps.  And those
+// of its blocks.
+template <int kTab>
+struct FeedLengths {
+    uint4 all[kTab / 8], eighths[kTab / 64], splits[(kTab / 64 + 7) / 8], blocks[kTab / 8];
+
+    __device__ __forceinline__ void load(const uint16_t* __restrict__ R)
+    {
+        uint16_t* const e = reinterpret_cast<uint16_t*>(eighths);
+        uint16_t* const s = reinterpret_cast<uint16_t*>(splits);
+        const int lane = lane_id();
+        if (kTab / 64 < 8 && lane < 8) s[lane] = 0xFFFF;
+#pragma unroll
+        for (int i = lane; i < kTab / 8; i += kWave) {
+            const uint4 w = reinterpret_cast<const uint4*>(R)[i];
+            all[i] = w;
+            e[i] = (uint16_t)(w.w >> 16);
+            if (i % 8 == 7) s[i / 8] = (uint16_t)(w.w >> 16);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+
+    __device__ __forceinline__ int upto(uint32_t L) const
+    {
+        uint32_t c = 0;
+#pragma unroll
+        for (int i = 0; i < (kTab / 64 + 7) / 8; ++i) c += count_upto2(splits[i], L);
+        const int b = min(both_counts(c), kTab / 64 - 1);
+        const int e = 8 * b + min(count_upto(eighths[b], L), 7);
+        return 8 * e + count_upto(all[e], L);
+    }
+};
+
+// kAlone: the second launch.
+template <int kTab, bool kAlone>
+__global__ __launch_bounds__(2 * kFeedWaves * kWave, 2) void k_feedback_rounds(FeedRoundsArgs f)
+{
+    constexpr int kAhead = 16;
+    static_assert(kFeedWaves * kFeedWaves == 16 && kAhead * 16 == kFeedWaves * kWave, "a wave's share of the workgroups and of their instances is read together");
+    __shared__ FeedLengths<kTab> lengths_by[kFeedWaves];
+    __shared__ unsigned long long least_by[kFeedWaves][kWave], offer_by[kFeedWaves][kWave], met_by[kFeedWaves];
+    __shared__ double4 held_by[kFeedWaves][kFeedHeld];      // R, c*R + tri(R), the context
+    __shared__ ulonglong2 infos[kFeedInst];      // met deadlines and d_g (as an integer that falls with it) of every instance
+    __shared__ int over;
+    fetch_args<FeedRoundsArgs>();
+    const BuildArgs& a = f.b;
+    const int lane = lane_id(), both = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), wave = both % kFeedWaves;
+    const bool reader = both >= kFeedWaves;      // these wait for the words of all, the others have the instances
+    const int M = a.n_inst, W = kAlone ? 1 : gridDim.x, w = kAlone ? 0 : blockIdx.x;
+    const auto inst_of = [&](int u) { return (u * W + w) * kFeedWaves + wave; };      // (alone a wave has several)
+    const auto each_inst = [&](auto turn) {
+        if constexpr (kAlone) { for (int u = 0; !reader && inst_of(u) < M; ++u) turn(u); }
+        else if (!reader && inst_of(0) < M) turn(0);
+    };
+    if (kAlone && __hip_atomic_load(f.words.mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kFeedAlone) return;
+    if (threadIdx.x == 0) over = 0;
+    FeedLengths<kTab>& lengths = lengths_by[wave];
+    const bool blended = a.lam != 0.0;
+    const double keep = 1.0 - a.lam;
+
+    // the requests of a round, a lane each
+    struct Requests { int n, ctx0, length, ex; float D; };
+    const auto requests = [&](int round) {
+        Requests q;
+        const int64_t at = (int64_t)round * f.chunk;
+        q.n = (int)min(f.n - at, (int64_t)f.chunk);
+        const int64_t i = at + min(lane, q.n - 1);
+        q.ctx0 = f.ctx0[i]; q.length = f.pred_len[i]; q.D = f.budget[i];
+        q.ex = f.exclude ? f.exclude[i] : -1;
+        return q;
+    };
+    const auto clamped = [&](int length) { return min(max(length, 0), a.max_len); };
+
+    // The instance at hand: its table's sums, and what has come since that was built: whole blocks in memory, the
+    // others held in LDS.
+    int g = 0, pend = 0, room = 0, since = 0, away = 0;      // requests on its list, those that count (up to its room), those put away
+    FeedBase base{};
+    ClassCoef cc{};
+    double bq = 0.0, bp = 0.0, bd = 0.0;
+    double since_ctx = 0.0;
+    double4* const held = held_by[wave];
+    const auto block_at = [&](int b) { return (size_t)g * kTab + b * kFeedBlock; };
+    const auto settled = [&]() {      // (the wave's own words in LDS)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    const auto terms = [&](int ctx, int length) {
+        const int R = clamped(length);
+        const double Rd = (double)R, cd = (double)ctx;
+        return make_double4(Rd, fma(cd, Rd, (double)(R * (R - 1) / 2)), cd, 0.0);
+    };
+    const auto enter = [&](int inst) {
+        g = inst;
+        base = f.base[g];
+        cc = a.cls[a.inst_class[g]];
+        if (blended) { bq = a.emaQ[g]; bp = a.emaP[g]; bd = a.emaD[g]; }
+        pend = a.pend_cnt[g];
+        room = max(base.room - base.listed, 0);
+        since = min(max(pend - base.listed, 0), room);
+        away = since / kFeedBlock * kFeedBlock;
+        lengths.load(a.tabR + (size_t)g * kTab);
+        const size_t at = (size_t)g * kTab + min(base.listed + away + lane, kTab - 1);
+        const double4 e = terms(a.pend_prompt[at], a.pend_len[at]);
+        if (lane < since - away) held[lane] = e;
+        since_ctx = readlane_f64(wave_incl_scan_f64(lane < since - away ? e.z : 0.0), kWave - 1);
+        for (int b = 0; b < away / kFeedBlock; ++b) since_ctx += f.blocks.c[block_at(b) + kFeedBlock - 1];
+        for (int i = lane; i < away / 8; i += kWave) lengths.blocks[i] = reinterpret_cast<const uint4*>(f.blocks.R + block_at(0))[i];
+        settled();
+    };
+    // The first kFeedBlock of those held put away: their lengths sorted, and the sums up to each.
+    const auto put_away = [&]() {
+        uint32_t key[1] = {((uint32_t)(int)held[lane].x << 6) | (uint32_t)lane};
+        bitonic_levels<true, 1, 2, kFeedBlock>(key, lane, lane << 2);
+        const double4 e = held[key[0] & 63u];
+        const double y = wave_incl_scan_f64(e.x), x = wave_incl_scan_f64(e.y), c = wave_incl_scan_f64(e.z);
+        if (lane < kFeedBlock) {
+            const size_t at = block_at(away / kFeedBlock) + lane;
+            reinterpret_cast<uint16_t*>(lengths.blocks)[away + lane] = (uint16_t)(key[0] >> 6);
+            if (kAlone) f.blocks.R[at] = (uint16_t)(key[0] >> 6);
+            f.blocks.yx[at] = make_double2(y, x);
+            f.blocks.c[at] = c;
+        }
+        const double4 left = held[kFeedBlock + lane];      // (what is left moves down)
+        settled();
+        held[lane] = left;
+        away += kFeedBlock;
+        settled();
+    };
+    // What the offers for `q` are added up from, with all that has come so far.  Every sum is one of integers below 2^53, so the order
+    // does not matter.
+    struct Gathered { double y, x, pc; int k; };
+    const auto add_held = [&](Gathered& G, int from, int to, double L) {
+        for (int i = from; i < to; i += 4) {      // (those behind the last one: not read for what they are)
+            double4 e[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) e[t] = held[min(i + t, kFeedHeld - 1)];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const bool left = i + t < to && e[t].x <= L;
+                G.y += left ? e[t].x : 0.0; G.x += left ? e[t].y : 0.0; G.pc += left ? e[t].z : 0.0;
+                G.k += left;
+            }
+        }
+    };
+    const auto gather = [&](const Requests& q) {
+        Gathered G;
+        const uint32_t L = (uint32_t)clamped(q.length);
+        constexpr int kTogether = 4, kWords = kFeedBlock / 8;      // blocks side by side, on their way with the table's own segment
+        const int blocks = away / kFeedBlock;
+        double2 yx[kTogether];
+        double c[kTogether];
+        int n[kTogether];
+        const auto read = [&](int b0) {
+            uint4 R[kTogether][kWords];
+#pragma unroll
+            for (int t = 0; t < kTogether; ++t)
+#pragma unroll
+                for (int i = 0; i < kWords; ++i) R[t][i] = lengths.blocks[min(b0 + t, blocks - 1) * kWords + i];
+#pragma unroll
+            for (int t = 0; t < kTogether; ++t) {
+                uint32_t c2 = 0;
+#pragma unroll
+                for (int i = 0; i < kWords; ++i) c2 += count_upto2(R[t][i], L);
+                n[t] = b0 + t < blocks ? both_counts(c2) : 0;
+                const size_t last = block_at(min(b0 + t, blocks - 1)) + max(n[t] - 1, 0);
+                yx[t] = f.blocks.yx[last];
+                c[t] = f.blocks.c[last];
+            }
+        };
+        const auto sum = [&]() {
+#pragma unroll
+            for (int t = 0; t < kTogether; ++t) {
+                const double m = n[t] ? 1.0 : 0.0;
+                G.y = fma(m, yx[t].x, G.y); G.x = fma(m, yx[t].y, G.x); G.pc = fma(m, c[t], G.pc);
+                G.k += n[t];
+            }
+        };
+        if (blocks) read(0);
+        G.k = lengths.upto(L);
+        const size_t at = (size_t)g * (kTab + 1) + G.k;
+        const double2 own_yx = f.sums_yx[at];
+        const double own_c = f.sums_c[at];
+        G.y = G.x = G.pc = 0.0;
+        add_held(G, 0, since - away, (double)(int)L);
+        G.y += own_yx.x; G.x += own_yx.y; G.pc += own_c;
+        if (blocks) sum();
+        for (int b0 = kTogether; b0 < blocks; b0 += kTogether) { read(b0); sum(); }
+        return G;
+    };
+    // The offers, left for all: what the segments come to is what a build would leave in the table.
+    struct Own { uint32_t T; unsigned long long met, key; } own{~0u, 0, 0};
+    const auto offer = [&](const Gathered& G, const Requests& q, uint32_t tag) {
+        const int L = clamped(q.length), N = base.n + since;
+        const double Ctot = base.ctx + since_ctx, qd = cc.delta * (base.q_ctx + since_ctx);
+        double Gq = G.k ? fma(cc.gamma, G.x, fma(cc.beta, G.y, qd)) : qd;
+        double Hs = fma(cc.gamma, Ctot - G.pc, fma(cc.beta, (double)(N - G.k + 1), cc.alpha));
+        double d = fma(cc.gamma, Ctot, fma(cc.beta, (double)N, cc.alpha));
+        if (blended) {
+            Gq = keep * Gq + a.lam * bq;
+            Hs = keep * Hs + a.lam * bd;
+            d = keep * d + a.lam * bd;
+        }
+        const float T = latency_at((float)q.ctx0, L, inst_coef(a, cc, bp, N), make_float2((float)Gq, (float)Hs), G.k);
+        const float Dc = q.D > FLT_MAX ? FLT_MAX : q.D;
+        const bool ok = lane < q.n && g != q.ex;      // (as in k_feedback)
+        own.T = ok ? min(max(ordered_bits(T), 1u), ~0u - 1u) : ~0u;
+        own.met = __ballot(ok && T <= Dc);
+        own.key = falling_bits(d);
+        const unsigned long long v = lane < 2 ? own.met : own.key;
+        if (lane < 4) leave(f.words.own + ((size_t)(tag & 1) * M + g) * 4 + lane, ((lane & 1 ? v >> 32 : v & 0xFFFFFFFFu) << 32) | tag);
+        if (kAlone) f.T[(size_t)g * kWave + lane] = own.T;
+        return ((unsigned long long)own.T << 32) | ((unsigned)g << kFeedInstAt) | tag;
+    };
+    const auto publish = [&](unsigned long long least, uint32_t tag) {      // of this wave's instances
+        if (!reader) offer_by[wave][lane] = least;
+        __syncthreads();
+        if (both != kFeedWaves) return;
+        least = offer_by[0][lane];
+#pragma unroll
+        for (int v = 1; v < kFeedWaves; ++v) least = min(least, offer_by[v][lane]);
+        leave(f.words.least + ((size_t)(tag & 1) * W + w) * kWave + lane, least);
+    };
+    constexpr unsigned long long kNobody = ~0ull << 32;
+
+    Requests q = requests(f.first), next = requests(min(f.first + 1, f.rounds - 1));
+    {
+        unsigned long long least = kNobody | 1u;
+        each_inst([&](int u) {
+            enter(inst_of(u));
+            least = min(least, offer(gather(q), q, 1u));
+        });
+        publish(least, 1u);
+    }
+    for (int round = f.first; round < f.rounds; ++round) {
+        const uint32_t tag = (uint32_t)(round - f.first) + 1u;
+        const bool more = round + 1 < f.rounds;
+        // (on their way while the others' words are)
+        const Requests after = requests(min(round + 2, f.rounds - 1));
+        Gathered G{};
+        if (!kAlone && more && !reader && inst_of(0) < M) {
+            while (since - away >= kFeedBlock) put_away();
+            G = gather(next);
+        }
+
+        // the words of all, shared by the waves
+        unsigned long long least, met;
+        bool greet = !kAlone && round == f.first;
+        for (int polls = greet ? f.polls : kFeedPollsMore;; polls = kFeedPollsMore) {
+            const unsigned long long* __restrict__ words = f.words.least + (size_t)(tag & 1) * W * kWave + lane;
+            const unsigned long long* __restrict__ theirs = f.words.own + (size_t)(tag & 1) * M * 4;
+            const int per = (W + kFeedWaves - 1) / kFeedWaves, h0 = min(wave * per, W - 1), h1 = min(h0 + per, W);
+            // (one trip for as much as there usually is: 16 workgroups and 64 instances for a wave.  A wave's share of the workgroups is
+            // at most M / 16 rounded up, and alone, where there is one workgroup, so many trips still pass all instances)
+            least = ~0ull;
+            met = 0;
+            int looks = 0;
+            for (int b = 0; reader && b < (M + 15) / 16; b += kAhead) {
+                unsigned long long v[kAhead], m[4];
+                const int h = (b / kAhead * kFeedWaves + wave) * kWave + lane;
+                for (;; ++looks) {
+#pragma unroll
+                    for (int i = 0; i < kAhead; ++i) v[i] = peek(words + (size_t)min(h0 + b + i, h1 - 1) * kWave);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) m[i] = peek(theirs + (size_t)min(h, M - 1) * 4 + i);
+                    bool all = true;
+#pragma unroll
+                    for (int i = 0; i < kAhead; ++i) all = all && ((uint32_t)v[i] & ((1u << kFeedTagBits) - 1u)) == tag;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) all = all && (uint32_t)m[i] == tag;
+                    if (__all(all)) break;
+                    if (looks >= polls) { over = 1; break; }
+                }
+#pragma unroll
+                for (int i = 0; i < kAhead; ++i) least = min(least, v[i]);
+                const unsigned long long their_met = (m[0] >> 32) | (m[1] >> 32 << 32);
+                met |= their_met;
+                if (h < M) infos[h] = make_ulonglong2(their_met, (m[2] >> 32) | (m[3] >> 32 << 32));
+            }
+            if (reader) {
+                least_by[wave][lane] = least;
+                met = wave_or_u64(met);
+                if (lane == 0) met_by[wave] = met;
+            }
+            __syncthreads();
+            if (!greet) break;
+            if (threadIdx.x == 0) {      // are all here?
+                uint32_t mode = kFeedUndecided;
+                const auto say = [&](uint32_t mine) {
+                    if (__hip_atomic_compare_exchange_strong(f.words.mode, &mode, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                        mode = mine;
+                };
+                if (over || w == 0) say(over ? kFeedAlone : kFeedTogether);
+                for (int looks = 0; mode == kFeedUndecided; ++looks) {
+                    mode = __hip_atomic_load(f.words.mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (mode == kFeedUndecided && looks > f.polls) say(kFeedAlone);
+                }
+                over = mode == kFeedAlone ? 2 : over ? 3 : 0;
+            }
+            __syncthreads();
+            if (over != 3) break;
+            // (all are here, and have been seen by workgroup 0 alone so far: their words again)
+            greet = false;
+            __syncthreads();
+            if (threadIdx.x == 0) over = 0;
+            __syncthreads();
+        }
+        if (over) {
+            if (threadIdx.x == 0 && over == 1) atomicOr(&a.counters[0], GR_DEV_STALLED);
+            return;
+        }
+        least = least_by[0][lane];
+        met = met_by[0];
+#pragma unroll
+        for (int v = 1; v < kFeedWaves; ++v) {
+            least = min(least, least_by[v][lane]);
+            met |= met_by[v];
+        }
+        const bool live = lane < q.n, served = (met >> lane) & 1ull;
+        const uint32_t least_T = (uint32_t)(least >> 32);
+        const int64_t at = (int64_t)round * f.chunk + lane;
+        if (w == 0 && both == 0 && live && !served && least_T == ~0u) {      // nobody is allowed
+            f.out_inst[at] = -1;
+            f.out_slack[at] = 0.f;
+            if (f.out_fallback) f.out_fallback[at] = 1;
+        }
+
+        unsigned long long offered = kNobody | (tag + 1u);
+        each_inst([&](int u) {
+            if (kAlone) {
+                enter(inst_of(u));
+                own.met = infos[g].x;
+                own.key = infos[g].y;
+                own.T = f.T[(size_t)g * kWave + lane];
+            }
+            // Alg. 1 for the instance itself: where a deadline can be met, it is met here and by nobody more capable; else nobody's
+            // latency is less, or as little at a lower index
+            unsigned long long above = 0;      // requests whose deadline is met by somebody more capable
+            if (own.met) {
+                for (int h = lane; h < M; h += kWave) {
+                    const ulonglong2 o = infos[h];
+                    above |= o.y < own.key || (o.y == own.key && h < g) ? o.x : 0ull;
+                }
+                above = wave_or_u64(above);
+            }
+            const bool mine = live && (served ? ((own.met & ~above) >> lane) & 1ull
+                                              : least_T != ~0u && (int)((uint32_t)least >> kFeedInstAt) == g);
+            const unsigned long long joins = __ballot(mine);
+            if (kAlone && more) G = gather(next);
+            if (joins) {
+                if (mine) {
+                    f.out_inst[at] = g;
+                    f.out_slack[at] = q.D - from_ordered_bits(own.T);
+                    if (f.out_fallback) f.out_fallback[at] = !served;
+                    const int nth = pend + __popcll(joins & ((1ull << lane) - 1ull));
+                    if (nth < kTab) {
+                        a.pend_prompt[(size_t)g * kTab + nth] = q.ctx0;
+                        a.pend_len[(size_t)g * kTab + nth] = q.length;
+                    }
+                }
+                pend += __popcll(joins);
+                if (lane == 0) { a.pend_cnt[g] = pend; a.pend_touched[g] = 1; }
+            }
+            if (joins && more) {      // (less than a block is held before: a chunk finds room)
+                const int nth = __popcll(joins & ((1ull << lane) - 1ull)), taken = min(__popcll(joins), room - since);      // (beyond its room there are none)
+                const bool in = mine && nth < taken;
+                const double4 e = terms(q.ctx0, q.length);
+                if (in) held[since - away + nth] = e;
+                settled();
+                add_held(G, since - away, since - away + taken, (double)clamped(next.length));
+                since_ctx += readlane_f64(wave_incl_scan_f64(in ? e.z : 0.0), kWave - 1);
+                since += taken;
+                if (kAlone) while (since - away >= kFeedBlock) put_away();
+            }
+            if (more) offered = min(offered, offer(G, next, tag + 1u));
+        });
+        if (!more) break;
+        publish(offered, tag + 1u);
+        q = next;
+        next = after;
+    }
 }
 
 // The capability rank of every instance, for the caller (Alg. 1's argmax d_g: rank 0 = largest d_g,
@@ -1908,50 +2286,76 @@ bool feedback_by_round(const gr_fleet* f, int64_t chunk)
     return f->feed_T && !f->has_cap && chunk <= kWave && pair_by_pair(f, chunk);
 }
 
-// Whether the tables stay as they are while requests are routed and what comes is added to their sums: for three rounds and more
-// (the first launch then builds all tables, to have the sums), where an instance is hardly chosen twice a round (each
-// request of its list is a step of a chain of its own) and the rounds are not bound by the reads of the offers.  Whole
-// calls, us, chosen ones rebuilt / added up (`N/c`: N instances, chunks of c):
-//   256/1, 100 requests 966 / 665   256/1, 3 38.1 / 35.5   256/8, 200 252 / 186   32/1, 200 1 350 / 1 077   8/8, 100 99 / 94   500/1, 100 1 162 / 1 110
-//   256/64, 2 048 329 / 308   256/32, 1 000 302 / 286   128/32, 1 000 256 / 243   64/16, 500 234 / 209   512/40, 2 048 655 / 641
-//   64/64, 2 048 266 / 299   128/64, 1 500 195 / 203   32/32, 600 144 / 148   500/64, 2 000 410 / 416
-static bool adds_up(int64_t M, int64_t chunk, int64_t rounds)
+// Whether the rounds are one launch (k_feedback_rounds, with one before it that builds all tables for the sums and one behind): from three
+// rounds on where a chunk is hardly more than a request or two; else where what the launches of every round take (5 us, and 1 us more
+// for every 64 instances, whose offers each workgroup reads) is more than what the requests of a chunk take that all go to one
+// instance (0.08 us each), by as much as the three launches.  Whole calls, us, a launch per round / one, N/c: N instances, chunks of c, deadlines that
+// few meet, in brackets such that all go for the same instances:
+//   256/64, 2 048 requests 309 / 164 (358 / 240)   500/64, 2 000 410 / 193   128/32, 1 000 243 / 155 (448: 116 / 100)   64/32, 448 (103 / 100)
+//   256/1, 100 676 / 306   32/1, 200 1 070 / 613   4/4, 24 (41.4 / 38.0)   4/8, 48 (46.2 / 40.2)   4/8, 24 24.2 / 28.3   256/3, 9 35.4 / 35.1
+//   24/16, 224 (98 / 84), 96 (44.6 / 45.2)   40/20, 120 (45.6 / 48.1)   64/64, 2 048 243 / 181 (896: 112 / 121)   4/64, 1 024 (125 / 149)
+static bool in_one_launch(const gr_fleet* f, int64_t chunk, int64_t rounds)
 {
-    return rounds >= 3 && (chunk <= 8 || (4 * chunk <= M && chunk * M <= 20480));
+    if (chunk <= 4) return rounds >= 3;
+    return (double)rounds * (2.9 + f->n_inst / 64.0 - 0.08 * (double)chunk) > 13.0;
+}
+
+static void launch_feedback_rounds(gr_fleet* f, const BuildArgs& b, const FeedbackIn& r, int first, int rounds, hipStream_t s)
+{
+    FeedRoundsArgs a{};
+    a.b = b;
+    a.b.chunk_n = 0;
+    a.ctx0 = r.ctx0; a.pred_len = r.pred_len; a.exclude = r.exclude; a.budget = r.budget;
+    a.out_inst = r.out_inst; a.out_slack = r.out_slack; a.out_fallback = r.out_fallback;
+    a.n = r.n; a.chunk = r.chunk; a.first = first; a.rounds = rounds; a.polls = f->feed_polls;
+    a.sums_yx = f->feed_yx; a.sums_c = f->feed_c; a.base = f->feed_base; a.blocks = f->feed_blocks; a.words = f->feed_words; a.T = f->feed_T;
+    const dim3 grid(feed_groups(f->n_inst)), block(2 * kFeedWaves * kWave);
+#define GR_LAUNCH_ROUNDS(E) do { \
+        { ProfScope ps(f, kFeedback, s); hipLaunchKernelGGL((k_feedback_rounds<E * kWave, false>), grid, block, 0, s, a); } \
+        ProfScope ps(f, kFeedback, s); \
+        hipLaunchKernelGGL((k_feedback_rounds<E * kWave, true>), dim3(1), block, 0, s, a); } while (0)
+    switch (f->epl) {
+        case 2: GR_LAUNCH_ROUNDS(2); break;
+        case 4: GR_LAUNCH_ROUNDS(4); break;
+        case 8: GR_LAUNCH_ROUNDS(8); break;
+        case 16: GR_LAUNCH_ROUNDS(16); break;
+        default: GR_LAUNCH_ROUNDS(32); break;
+    }
+#undef GR_LAUNCH_ROUNDS
 }
 
 int launch_feedback(gr_fleet* f, const StatusIn& in, const FeedbackIn& r, hipStream_t s)
 {
-    FeedAddArgs add{};
-    FeedArgs& a = add.f;
+    FeedSumsArgs sums{};
+    FeedArgs& a = sums.f;
     a.b = build_args(f, in);
     const size_t M = f->n_inst;
     const int64_t rounds = (r.n + r.chunk - 1) / r.chunk;
-    const bool adding = adds_up((int64_t)M, r.chunk, rounds);
-    add.sums_yx = f->feed_yx; add.sums_c = f->feed_c; add.base = f->feed_base;
-    for (int64_t k = 0; k <= rounds; ++k) {       // launch k decides chunk k - 1 and offers for chunk k
-        const int64_t at = k * r.chunk, was = at - r.chunk;
-        a.b.chunk_n = k ? (int)std::min<int64_t>(r.n - was, r.chunk) : 0;
-        const int64_t all = r.current ? 0 : 1;      // the launch that builds every table anew
-        add.move = k == rounds ? kFeedTouched : k > all ? kFeedAdd : k == all ? kFeedAll : kFeedNone;
-        a.b.only_touched = r.current || k != 1;
-        if (k) {
+    const bool together = in_one_launch(f, r.chunk, rounds);
+    sums.sums_yx = f->feed_yx; sums.sums_c = f->feed_c; sums.base = f->feed_base; sums.words = f->feed_words;
+    int launches = 0;
+    // one launch that decides a chunk (-1: none) and offers for another
+    const auto queue = [&](int64_t decided, int64_t offered) {
+        const int64_t at = offered * r.chunk, was = decided * r.chunk;
+        a.b.chunk_n = decided >= 0 ? (int)std::min<int64_t>(r.n - was, r.chunk) : 0;
+        a.b.only_touched = r.current || decided != 0;
+        if (a.b.chunk_n) {
             a.b.chunk_ctx0 = r.ctx0 + was; a.b.chunk_len = r.pred_len + was;
             a.budget = r.budget + was; a.out_inst = r.out_inst + was; a.out_slack = r.out_slack + was;
             a.out_fallback = r.out_fallback ? r.out_fallback + was : nullptr;
         }
-        a.next_n = (int)std::max<int64_t>(0, std::min<int64_t>(r.n - at, r.chunk));
+        a.next_n = offered >= 0 ? (int)std::max<int64_t>(0, std::min<int64_t>(r.n - at, r.chunk)) : 0;
         if (a.next_n) {
             a.next_ctx0 = r.ctx0 + at; a.next_len = r.pred_len + at; a.next_budget = r.budget + at;
             a.next_exclude = r.exclude ? r.exclude + at : nullptr;
         }
-        const size_t out = k & 1, got = out ^ 1;
+        const size_t out = launches++ & 1, got = out ^ 1;
         a.T_in = f->feed_T + got * M * kWave; a.met_in = f->feed_met + got * M; a.key_in = f->feed_key + got * M;
         a.T_out = f->feed_T + out * M * kWave; a.met_out = f->feed_met + out * M; a.key_out = f->feed_key + out * M;
         ProfScope ps(f, kFeedback, s);
         const int waves = waves_per_instance(f->epl, f->n_inst);
 #define GR_LAUNCH_FEEDBACK(E, W) \
-        if (adding) hipLaunchKernelGGL((k_feedback<E / W, W, true>), dim3((unsigned)M), dim3((W + 1) * kWave), (split_lds<E, W>()), s, add); \
+        if (together) hipLaunchKernelGGL((k_feedback<E / W, W, true>), dim3((unsigned)M), dim3(W * kWave), (split_lds<E, W>()), s, sums); \
         else hipLaunchKernelGGL((k_feedback<E / W, W, false>), dim3((unsigned)M), dim3(W * kWave), (split_lds<E, W>()), s, a); \
         break
         switch (f->epl * 8 + waves) {
@@ -1962,6 +2366,20 @@ int launch_feedback(gr_fleet* f, const StatusIn& in, const FeedbackIn& r, hipStr
             default: GR_LAUNCH_FEEDBACK(32, 4);
         }
 #undef GR_LAUNCH_FEEDBACK
+    };
+    if (together) {
+        // (the first chunk is decided from the tables as they stand, whose rebuild may change them all)
+        const int64_t first = r.current ? 0 : 1;
+        if (first) queue(-1, 0);
+        for (int64_t from = first; from < rounds; from += kFeedMostRounds) {
+            sums.move = kFeedAll;
+            queue(from == first && first ? 0 : -1, -1);
+            launch_feedback_rounds(f, a.b, r, (int)from, (int)std::min<int64_t>(rounds, from + kFeedMostRounds), s);
+        }
+        sums.move = kFeedTouched;
+        queue(-1, -1);
+    } else {
+        for (int64_t k = 0; k <= rounds; ++k) queue(k - 1, k);
     }
     if (hipGetLastError() != hipSuccess) {
         TableAccount(f, s).v->current = false;

@@ -1,0 +1,109 @@
+"""Feedback routing whose rounds are one launch, against the same rounds through the table of lengths and a rebuild each, bit for bit: by all
+workgroups together and by one of them alone (which the others leave it to when they have not seen each other soon enough),
+lists of several blocks, two fleets at once on two streams, and recorded and replayed."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_16867_amd import binding, workloads
+from tests.parity import upload
+
+pytestmark = pytest.mark.gpu
+
+
+def _fleet(n_inst, held, n, slo, seed):
+    return workloads.make_fleet(dataclasses.replace(workloads.spec("mid"), n_inst=n_inst, n_active=held, n_queued=held // 10,
+                                                    n_incoming=n, slo_scale=slo, occupancy_jitter=True, seed=seed))
+
+
+class _Routing:
+    def __init__(self, fl, chunk, entries, pairs=None, looks=None, blend=0.0):
+        dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+        self.chunk, self.n, self.d = chunk, len(fl.in_prompt), upload(fl)
+        self.h = binding.Fleet(fl.coef["delta"], fl.coef["alpha"], fl.coef["beta"], fl.coef["gamma"], fl.inst_class, entries,
+                               int(fl.spec.max_len), self.n)
+        if pairs is not None:
+            self.h.gr_set_small_batch_pairs(pairs)
+        if looks is not None:
+            self.h.gr_set_feedback_wait(looks)
+        if blend:
+            for w, wait, prefill, decode in workloads.observed_status(fl, rounds=2, seed=3):
+                self.h.gr_observe(w, dev(wait), dev(prefill), dev(decode))
+            self.h.gr_set_blend(blend)
+        z = lambda t, v=0: torch.full((self.n,), v, dtype=t, device="cuda")
+        self.fin = torch.zeros(max(len(fl.act_prompt), 1), device="cuda")
+        self.exclude = dev(np.where(np.arange(self.n) % 3 == 0, np.arange(self.n) % fl.n_inst, -1).astype(np.int32))
+        self.out = [z(torch.int32, -7), z(torch.float32), z(torch.uint8, 9)]
+        self.after = [z(torch.int32, -7), z(torch.float32), z(torch.uint8, 9)]
+
+    def run(self):
+        d = self.d
+        self.h.gr_build_status(d["act_off"], d["act_prompt"], d["act_gen"], d["act_rem"], d["q_off"], d["q_prompt"], d["q_len"], self.fin)
+        self.h.gr_route_feedback(self.chunk, d["in_prompt"], d["in_len"], d["in_budget"], self.out[0], self.out[1],
+                                 exclude_inst=self.exclude, out_fallback=self.out[2])
+        self.h.gr_score_route(d["in_prompt"], d["in_len"], d["in_budget"], self.after[0], self.after[1], out_fallback=self.after[2])
+
+    def result(self):
+        torch.cuda.synchronize()
+        assert self.h.gr_device_status() == 0
+        return [x.clone() for x in self.out + self.after]
+
+
+@pytest.mark.parametrize("n_inst,held,entries,chunk,n,slo", [
+    (1, 5, 700, 4, 600, 16.0), (3, 20, 500, 1, 160, 1.0), (5, 30, 1024, 4, 400, 16.0), (17, 10, 128, 3, 90, 4.0), (64, 200, 512, 8, 300, 16.0),
+    (256, 100, 2048, 64, 700, 16.0), (257, 60, 400, 30, 300, 1.0), (400, 30, 300, 3, 60, 16.0), (512, 40, 256, 64, 450, 4.0)])
+@pytest.mark.parametrize("blend", [0.0, 0.5])
+def test_together_and_alone(n_inst, held, entries, chunk, n, slo, blend):
+    fl = _fleet(n_inst, held, n, slo, n_inst + chunk)
+    got = []
+    for pairs, looks in ((0, None), (None, None), (None, 0)):
+        r = _Routing(fl, chunk, entries, pairs, looks, blend)
+        r.run()
+        got.append(r.result())
+        r.h.close()
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
+            assert torch.equal(a, b)
+
+
+def test_two_at_once():
+    rs, wants = [], []
+    for k, (n_inst, chunk) in enumerate(((256, 32), (300, 24))):
+        fl = _fleet(n_inst, 80, 500, (1.0, 16.0)[k], 40 + k)
+        want = _Routing(fl, chunk, 600, pairs=0)
+        want.run()
+        wants.append(want.result())
+        rs.append(_Routing(fl, chunk, 600))
+    streams = [torch.cuda.Stream() for _ in rs]
+    torch.cuda.synchronize()
+    for _ in range(4):
+        for r, s in zip(rs, streams):
+            with torch.cuda.stream(s):
+                r.run()
+    for r, want in zip(rs, wants):
+        for a, b in zip(r.result(), want):
+            assert torch.equal(a, b)
+
+
+def test_recorded():
+    fl = _fleet(256, 90, 400, 4.0, 9)
+    want = _Routing(fl, 16, 700, pairs=0)
+    want.run()
+    expected = want.result()
+    r = _Routing(fl, 16, 700)
+    r.run()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        r.run()
+    for _ in range(4):
+        for x in r.out + r.after:
+            x.fill_(3)
+        graph.replay()
+        for a, b in zip(r.result(), expected):
+            assert torch.equal(a, b)
+        r.run()      # (a direct call between the replays)
+        for a, b in zip(r.result(), expected):
+            assert torch.equal(a, b)
