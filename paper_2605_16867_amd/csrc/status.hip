@@ -2329,8 +2329,9 @@ bool feedback_by_round(const gr_fleet* f, int64_t chunk)
     return f->feed_T && !f->has_cap && chunk <= kWave && pair_by_pair(f, chunk);
 }
 
-// Whether the rounds are one launch (k_feedback_rounds, with one before it that builds all tables for the sums and one behind): from three
-// rounds on where a chunk is hardly more than a request or two; else where what the launches of every round take (5 us, and 1 us more
+// Whether the rounds are one launch (k_feedback_rounds, with one before it that builds all tables for the sums and one behind): from five
+// rounds on where a chunk is hardly more than a request or two (three rounds 16/4 27.4 / 30.7, 4/1 26.2 / 29.5); else, from three rounds on
+// (two: 256/2 24.6 / 28.1, 500/40 32.9 / 35.2, but three 512/1 45 / 35), where what the launches of every round take (5 us, and 1 us more
 // for every 64 instances, whose offers each workgroup reads) is more than what the requests of a chunk take that all go to one
 // instance (0.08 us each), by as much as the three launches.  Whole calls, us, a launch per round / one, N/c: N instances, chunks of c, deadlines that
 // few meet, in brackets such that all go for the same instances:
@@ -2339,7 +2340,8 @@ bool feedback_by_round(const gr_fleet* f, int64_t chunk)
 //   24/16, 224 (98 / 84), 96 (44.6 / 45.2)   40/20, 120 (45.6 / 48.1)   64/64, 2 048 243 / 181 (896: 112 / 121)   4/64, 1 024 (125 / 149)
 static bool in_one_launch(const gr_fleet* f, int64_t chunk, int64_t rounds)
 {
-    if (chunk <= 4) return rounds >= 3;
+    if (rounds < 3) return false;
+    if (chunk <= 4 && rounds >= 5) return true;
     return (double)rounds * (2.9 + f->n_inst / 64.0 - 0.08 * (double)chunk) > 13.0;
 }
 
