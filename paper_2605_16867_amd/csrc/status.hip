@@ -94,11 +94,15 @@ __device__ __forceinline__ void order2(uint32_t& lo, uint32_t& hi)
 }
 
 // How a lane gets its partner's word.  What bounds a build decides.  With up to two words a lane several waves share an instance and a
-// SIMD hardly has a wave to run meanwhile, and under caps it never has: an exchange is a step of a chain, and stays in the
+// SIMD hardly has a wave to run meanwhile: an exchange is a step of a chain, and stays in the
 // register file, whose step is shorter than the crossbar's.  With more words the vector ALU is what the waves of a SIMD wait for,
 // and the fetches that no single pattern does are left to the crossbar.  Whole calls, us, everywhere like that / as here: refresh of 256 x 512 and
-// one request 8.77 / 8.42, step of 32 x 256 20.43 / 20.00, of 4 x 64 14.69 / 14.50, 1 024 x 240 under caps 60.1 / 59.9.  (All fetches through
-// the crossbar: 8.85, 20.2, 15.2, 61.1; status of 4 096 x 512 21.3 / 21.0, but its scan 108.6 / 109.6; scan of 1 024 x 1 000 60.4 / 59.9 to 60.6.)
+// one request 8.77 / 8.42, step of 32 x 256 20.43 / 20.00, of 4 x 64 14.69 / 14.50.  (All fetches through
+// the crossbar: 8.85, 20.2, 15.2; status of 4 096 x 512 21.3 / 21.0, but its scan 108.6 / 109.6; scan of 1 024 x 1 000 60.4 / 59.9 to 60.6.)
+// Under caps an instance has one wave, whose sort is a chain between the turns of others': in the register file at every size.  Status
+// under caps, crossbar / here: 1 024 x (56 + 7) 11.45 / 11.10, (110 + 13) 14.83 / 14.87, (224 + 28) 23.8 / 23.7, (450 + 56) 40.1 / 40.8 (long tails
+// 27.7 / 27.7), (900 + 112) 78.5 / 77.1 (47.7 / 46.1), (1 820 + 227) 138.2 / 136.4 (88.5 / 85.1); 4 096 x 450 38.4 / 38.2, x (450 + 56) 90.8 / 92.3
+// (61.0 / 60.7), x (900 + 112) 276 / 272 (154 / 149); 64 x 1 820 the same.
 template <int kEPL>
 constexpr bool kShortChain = kEPL <= 2;
 
@@ -315,6 +319,8 @@ constexpr int log2_of(int v) { return v <= 1 ? 0 : 1 + log2_of(v / 2); }
 // 27.9 where a turn of one departure and one admission has no sums over the lanes: the newcomer's context is read from LDS, the
 // other's off its lane; an entry's context when it leaves is known beforehand, and one that has left is
 // marked, so that the minimum needs no comparison with the step.  1 000 x (1 000 + 125) 167 -> 136, 4 096 x (400 + 50) 103 -> 89.
+// An instance without a queue plays no turn, and what the turns need is not prepared for it: 64 x 1 000 24.2 -> 22.8 us,
+// 4 096 x 900 95.5 -> 91, 1 024 x 1 820 60.7 -> 56.6.
 constexpr int kLowBits = 24;     // a lane's sum of contexts is added up over the wave in two parts of 32 bits
 constexpr long long kLowMask = (1ll << kLowBits) - 1;
 
@@ -452,7 +458,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
     const bool capped = cap_g <= N;
     int Nrun = N;
     double d_first = -1.0;
-    if (capped) {
+    if (capped && A < N) {
         // decode step at which the entry leaves (kNever and more: not in yet, gone, none), steps it stays once it is admitted,
         // its context when it leaves
         constexpr uint32_t kNever = 0x7fffffffu;
@@ -475,7 +481,7 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
         // More running than the cap allows: nobody is admitted until enough of them have left, and up to
         // then every finish time is the closed form over the sorted lengths: the turns of the loop
         // below start with the first admission.  (An entry without a token left is the loop's business.)
-        if (A >= cap_g && A < N) {
+        if (A >= cap_g) {
             uint32_t run[kEPL];
 #pragma unroll
             for (int r = 0; r < kEPL; ++r) run[r] = r * kWave + lane < A ? key[r] : 0xFFFFFFFFu;
@@ -622,6 +628,9 @@ __global__ __launch_bounds__(kBlock, 1) void k_build_capped(BuildArgs a)
             key[r] = running ? ((fstep[r] - (uint32_t)s) << kIdxBits) | (uint32_t)i : 0xFFFFFFFFu;
             if (running) ctx[i] = ctx_end[r] - (int)(fstep[r] - (uint32_t)s);
         }
+    } else if (capped) {      // nobody waits: what is running is left as it is (one without a token is not)
+#pragma unroll
+        for (int r = 0; r < kEPL; ++r) key[r] = key[r] >> kIdxBits ? key[r] : 0xFFFFFFFFu;
     }
 
     bitonic_sort<true, kEPL>(key, lane);
