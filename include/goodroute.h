@@ -365,6 +365,13 @@ int gr_set_small_batch_pairs(gr_fleet* f, int64_t max_pairs);
 int gr_set_feedback_wait(gr_fleet* f, int32_t looks);
 
 /*
+ * How many of the device's compute units a feedback routing may count on (others may have work that stays on the rest).  All
+ * rounds are one launch only where its workgroups, one for every four instances, fit these and those that the
+ * stream may use at once; else every round is a launch.  The results are the same.  As many as there are if it is never set.
+ */
+int gr_set_feedback_units(gr_fleet* f, int32_t units);
+
+/*
  * Synchronises the device and returns the OR of the GR_DEV_* bits raised by
  * kernels since gr_create (HOST int32 out).  Not for the hot path.
  */

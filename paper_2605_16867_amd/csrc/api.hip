@@ -202,7 +202,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
         gr_destroy(f);
         return GR_ERR_HIP;
     }
-    if (status_prepare() != GR_OK) { gr_destroy(f); return GR_ERR_HIP; }
+    if (status_prepare() != GR_OK || (by_round && feedback_prepare(f) != GR_OK)) { gr_destroy(f); return GR_ERR_HIP; }
     *out = f;
     return GR_OK;
 }
@@ -423,6 +423,13 @@ int gr_set_feedback_wait(gr_fleet* f, int32_t looks)
 {
     if (!f || looks < 0) return GR_ERR_INVALID_ARG;
     f->feed_polls = looks;
+    return GR_OK;
+}
+
+int gr_set_feedback_units(gr_fleet* f, int32_t units)
+{
+    if (!f || units < 0) return GR_ERR_INVALID_ARG;
+    f->feed_units = units;
     return GR_OK;
 }
 

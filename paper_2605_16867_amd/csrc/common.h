@@ -256,6 +256,8 @@ struct gr_fleet {
     gr::FeedWords feed_words;
     gr::FeedBlocks feed_blocks;
     int feed_polls = 4096;                  // see gr_set_feedback_wait
+    int feed_per_unit = 0;                  // workgroups of k_feedback_rounds that a compute unit runs at once
+    int units = 0, feed_units = INT32_MAX;  // compute units of the device; see gr_set_feedback_units
     gr::DirectPart* direct_part = nullptr;       // [kDirectParts] selections of the parts of a wide fleet, scored pair by pair
 };
 
@@ -321,6 +323,7 @@ struct OrderArgs {
 
 // status.hip
 int status_prepare();
+int feedback_prepare(gr_fleet* f);
 int launch_ranks(gr_fleet* f, int* out_rank, hipStream_t s);
 int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s);
 // A whole feedback routing in chunks of up to kWave requests, a launch per round (see k_feedback).  `in`: the status inputs to

@@ -2354,6 +2354,45 @@ static bool in_one_launch(const gr_fleet* f, int64_t chunk, int64_t rounds)
     return (double)rounds * (2.9 + f->n_inst / 64.0 - 0.08 * (double)chunk) > 13.0;
 }
 
+// The kernel for tables of epl * kWave entries.
+template <typename Use>
+static auto with_rounds_kernel(int epl, Use use)
+{
+    switch (epl) {
+        case 2: return use(k_feedback_rounds<2 * kWave, false>);
+        case 4: return use(k_feedback_rounds<4 * kWave, false>);
+        case 8: return use(k_feedback_rounds<8 * kWave, false>);
+        case 16: return use(k_feedback_rounds<16 * kWave, false>);
+        default: return use(k_feedback_rounds<32 * kWave, false>);
+    }
+}
+
+int feedback_prepare(gr_fleet* f)
+{
+    const bool ok = hipDeviceGetAttribute(&f->units, hipDeviceAttributeMultiprocessorCount, f->device) == hipSuccess &&
+                    with_rounds_kernel(f->epl, [&](auto kernel) {
+                        return hipOccupancyMaxActiveBlocksPerMultiprocessor(&f->feed_per_unit, kernel, 2 * kFeedWaves * kWave, 0);
+                    }) == hipSuccess;
+    return ok ? GR_OK : GR_ERR_HIP;
+}
+
+// Whether the workgroups of k_feedback_rounds, which wait for each other, can all run at once: on a stream of few compute units, or a
+// device of few, a call would wait in vain, then take many times as long as a launch for each round.  (A recorded call
+// is asked about the stream that records it.)
+static bool all_run_at_once(const gr_fleet* f, hipStream_t s)
+{
+    int units = std::min(f->units, f->feed_units);
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(s, sizeof mask / sizeof *mask, mask) == hipSuccess) {
+        int usable = 0;
+        for (const uint32_t m : mask) usable += __builtin_popcount(m);
+        if (usable) units = std::min(units, usable);
+    } else {
+        (void)hipGetLastError();
+    }
+    return (int64_t)units * f->feed_per_unit >= feed_groups(f->n_inst);
+}
+
 static void launch_feedback_rounds(gr_fleet* f, const BuildArgs& b, const FeedbackIn& r, int first, int rounds, hipStream_t s)
 {
     FeedRoundsArgs a{};
@@ -2385,7 +2424,7 @@ int launch_feedback(gr_fleet* f, const StatusIn& in, const FeedbackIn& r, hipStr
     a.b = build_args(f, in);
     const size_t M = f->n_inst;
     const int64_t rounds = (r.n + r.chunk - 1) / r.chunk;
-    const bool together = in_one_launch(f, r.chunk, rounds);
+    const bool together = in_one_launch(f, r.chunk, rounds) && all_run_at_once(f, s);
     sums.sums_yx = f->feed_yx; sums.sums_c = f->feed_c; sums.base = f->feed_base; sums.words = f->feed_words;
     int launches = 0;
     // one launch that decides a chunk (-1: none) and offers for another

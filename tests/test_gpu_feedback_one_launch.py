@@ -1,6 +1,7 @@
 """Feedback routing whose rounds are one launch, against the same rounds through the table of lengths and a rebuild each, bit for bit: by all
 workgroups together and by one of them alone (which the others leave it to when they have not seen each other soon enough),
-lists of several blocks, two fleets at once on two streams, and recorded and replayed."""
+lists of several blocks, two fleets at once on two streams, and recorded and replayed.  Where its workgroups do not fit the
+compute units, each round is a launch."""
 import dataclasses
 
 import numpy as np
@@ -106,4 +107,26 @@ def test_recorded():
             assert torch.equal(a, b)
         r.run()      # (a direct call between the replays)
         for a, b in zip(r.result(), expected):
+            assert torch.equal(a, b)
+
+
+# A workgroup for every four instances: on as many compute units as there are of those, and one fewer.
+@pytest.mark.parametrize("n_inst", [5, 8, 254])
+def test_a_launch_for_each_round_where_the_workgroups_do_not_fit(n_inst):
+    fl = _fleet(n_inst, 60, 200, 4.0, n_inst)
+    groups, rounds = (n_inst + 3) // 4, 25
+    got, launches = [], []
+    for units in (None, groups, groups - 1, 0):
+        r = _Routing(fl, 8, 500)
+        if units is not None:
+            r.h.gr_set_feedback_units(units)
+        r.h.gr_profile_enable(200)
+        r.run()
+        got.append(r.result())
+        launches.append(r.h.gr_profile_read()["k_feedback"][1])
+        r.h.close()
+    assert launches[0] == launches[1] < 6
+    assert launches[2] == launches[3] == rounds + 1
+    for other in got[1:]:
+        for a, b in zip(got[0], other):
             assert torch.equal(a, b)
