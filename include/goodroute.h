@@ -104,7 +104,7 @@ enum {
  *   4 * rows * [M' / 16 rounded up to 16] bytes   the minima over runs once more (18 MB there), for max_requests of 131 072
  *                                    and more on fleets of up to 16 classes with M' of at least 1 024 and 64 * n_class,
  *   at most 64 MB, or 1 024 * n_inst bytes if that is more   rows of that table for out_T,
- *   (50 * cap + 1000) * n_inst bytes  feedback routing, up to 512 instances with cap of 128 and more: what they offer a chunk, sums
+ *   (50 * cap + 1300) * n_inst bytes  feedback routing, up to 512 instances with cap of 128 and more: what they offer a chunk, sums
  *                                    behind the tables and of what is routed,
  *   0.4 MB                           selections of small batches on fleets of more than 4 096 instances,
  * plus a few arrays of n_inst, M' or max_len + 1 words.
@@ -358,11 +358,19 @@ int gr_set_small_batch_pairs(gr_fleet* f, int64_t max_pairs);
 
 /*
  * How often the workgroups of a feedback routing that runs in one launch look for each other (about a microsecond
- * each) before one of them does the work of all, one instance after the other: at least once, 4096 times if it is never
- * set.  The results are the same; on a device that cannot run all of them at once (a stream of few compute units) it
- * takes many times as long.
+ * each) before those that have started share the work of all, several instances to each of their wavefronts in turn: `looks` times, 64 if it
+ * is never set, divided by the share of them that has started.  The results are the same.  It takes about twice as long with
+ * half of the workgroups, and 20 to 75 times as long with one of 64 or 128 (256 or 512 instances).
  */
 int gr_set_feedback_wait(gr_fleet* f, int32_t looks);
+
+/*
+ * At most how many workgroups share that work, >= 1 (all that there are if it is never set).  The results are the same.
+ * gr_feedback_team synchronises the device and says how many did in the last feedback routing that was one launch and has
+ * ended (HOST int32 out; 0: there was none).  For tests and measurements.
+ */
+int gr_set_feedback_team(gr_fleet* f, int32_t workgroups);
+int gr_feedback_team(gr_fleet* f, int32_t* out_workgroups);
 
 /*
  * How many of the device's compute units a feedback routing may count on (others may have work that stays on the rest).  All

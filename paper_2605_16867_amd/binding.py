@@ -15,7 +15,7 @@ LIB_PATH = os.path.join(_HERE, "csrc", "libgoodroute.so")
 MARSHAL_PATH = os.path.join(_HERE, "csrc", "goodroute_marshal.so")
 
 EXPORTS = ("gr_create", "gr_destroy", "gr_build_status", "gr_score_route", "gr_score_route_noalloc", "gr_score_route_cached", "gr_route_feedback",
-           "gr_risk_scan", "gr_observe", "gr_set_blend", "gr_set_batch_cap", "gr_set_small_batch_pairs", "gr_set_feedback_wait", "gr_set_feedback_units",
+           "gr_risk_scan", "gr_observe", "gr_set_blend", "gr_set_batch_cap", "gr_set_small_batch_pairs", "gr_set_feedback_wait", "gr_set_feedback_units", "gr_set_feedback_team", "gr_feedback_team",
            "gr_device_status", "gr_strerror", "gr_profile_enable", "gr_profile_select", "gr_profile_read",
            "gr_profile_read_launches", "gr_profile_kernel_count", "gr_profile_kernel_name")
 
@@ -63,6 +63,10 @@ def lib() -> C.CDLL:
         l.gr_set_feedback_wait.argtypes = [p, i32]
         l.gr_set_feedback_units.restype = C.c_int
         l.gr_set_feedback_units.argtypes = [p, i32]
+        l.gr_set_feedback_team.restype = C.c_int
+        l.gr_set_feedback_team.argtypes = [p, i32]
+        l.gr_feedback_team.restype = C.c_int
+        l.gr_feedback_team.argtypes = [p, C.POINTER(i32)]
         l.gr_set_batch_cap.restype = C.c_int
         l.gr_set_batch_cap.argtypes = [p, p]
         l.gr_device_status.restype = C.c_int
@@ -303,6 +307,14 @@ class Fleet:
 
     def gr_set_feedback_units(self, units: int) -> None:
         _check(lib().gr_set_feedback_units(self._h, int(units)), "gr_set_feedback_units")
+
+    def gr_set_feedback_team(self, workgroups: int) -> None:
+        _check(lib().gr_set_feedback_team(self._h, int(workgroups)), "gr_set_feedback_team")
+
+    def gr_feedback_team(self) -> int:
+        v = C.c_int32(0)
+        _check(lib().gr_feedback_team(self._h, C.byref(v)), "gr_feedback_team")
+        return v.value
 
     def gr_set_small_batch_pairs(self, max_pairs: int) -> None:
         _check(lib().gr_set_small_batch_pairs(self._h, int(max_pairs)), "gr_set_small_batch_pairs")

@@ -132,7 +132,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
 
     const size_t tab = (size_t)n_inst * f->cap, segments = (size_t)n_inst * (f->cap + 1), seen_bytes = (size_t)(f->bins + 15) / 16 * 16;
     const bool by_row = classes_first(f, false, max_requests), by_round = n_inst <= kFeedInst && waves_per_instance(f->epl, n_inst) > 1;
-    const size_t groups = feed_groups(n_inst), words = 2 * groups * kWave + 2 * (size_t)n_inst * 4 + 1;
+    const size_t words = 2 * (size_t)FeedWords::set(n_inst) + 1;
     const bool ok =
         dev_alloc(&f->cls, n_class) && dev_alloc(&f->inst_class, n_inst) &&
         dev_alloc(&f->tabR, tab + kWave) && dev_alloc(&f->tabGH, (size_t)n_inst * (f->cap + 2) + kWave) &&
@@ -157,8 +157,9 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     // (parts of one allocation: each takes its time)
     if (by_row) f->row_min = f->grp_min + (size_t)f->row_cap * f->run_pad;
     if (by_round) {
-        f->feed_words.own = f->feed_words.least + 2 * groups * kWave;
-        f->feed_words.mode = reinterpret_cast<uint32_t*>(f->feed_words.own + 2 * (size_t)n_inst * 4);
+        f->feed_words.own = f->feed_words.least + 2 * feed_groups(n_inst) * kWave;
+        f->feed_words.gate = reinterpret_cast<uint32_t*>(f->feed_words.least + words - 1);
+        f->feed_words.team = f->feed_words.gate + 1;
         f->feed_words.n = (int)words;
         f->feed_blocks.c = reinterpret_cast<double*>(f->feed_blocks.yx + tab);
         f->feed_blocks.R = reinterpret_cast<uint16_t*>(f->feed_blocks.c + tab);
@@ -195,6 +196,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     clear(f->tabGH, ((size_t)n_inst * (f->cap + 2) + kWave) * sizeof(float2));
     clear(f->instK, sizeof(float4) * n_inst);
     clear(f->hD, sizeof(double) * n_inst);
+    if (by_round) clear(f->feed_words.least, words * sizeof(unsigned long long));
     clear(f->pend_cnt, sizeof(int) * n_inst);
     clear(f->pend_touched, sizeof(int) * n_inst);
     clear(f->commit_mark, sizeof(int) * n_inst);
@@ -424,6 +426,22 @@ int gr_set_feedback_wait(gr_fleet* f, int32_t looks)
     if (!f || looks < 0) return GR_ERR_INVALID_ARG;
     f->feed_polls = looks;
     return GR_OK;
+}
+
+int gr_set_feedback_team(gr_fleet* f, int32_t workgroups)
+{
+    if (!f || workgroups < 1) return GR_ERR_INVALID_ARG;
+    f->feed_team = workgroups;
+    return GR_OK;
+}
+
+int gr_feedback_team(gr_fleet* f, int32_t* out_workgroups)
+{
+    if (!f || !out_workgroups) return GR_ERR_INVALID_ARG;
+    *out_workgroups = 0;
+    if (!f->feed_words.team) return GR_OK;
+    return hipDeviceSynchronize() == hipSuccess &&
+           hipMemcpy(out_workgroups, f->feed_words.team, sizeof(int32_t), hipMemcpyDeviceToHost) == hipSuccess ? GR_OK : GR_ERR_HIP;
 }
 
 int gr_set_feedback_units(gr_fleet* f, int32_t units)

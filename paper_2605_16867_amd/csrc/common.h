@@ -100,19 +100,27 @@ struct FeedBase {
     int pad;
 };
 
+__host__ __device__ constexpr int feed_groups(int n_inst) { return (n_inst + 3) / 4; }
+
 // Words that the workgroups of a feedback routing in one launch leave for each other (see k_feedback_rounds).
 struct FeedWords {
-    unsigned long long *least = nullptr, *own = nullptr;   // [2][feed_groups][kWave], [2][M][4]
-    uint32_t* mode = nullptr;                              // [1]
+    unsigned long long *least = nullptr, *own = nullptr;   // [2][feed_groups][kWave], [2][M][4]; behind them as many for a part of the workgroups
+    uint32_t *gate = nullptr, *team = nullptr;             // workgroups that have started, and at the end how many shared the work
     int n = 0;                                             // all of them, in words of 8 bytes, from `least` on
+    __host__ __device__ FeedWords of(bool part, int n_inst) const
+    {
+        FeedWords w = *this;
+        if (part) { w.least += set(n_inst); w.own += set(n_inst); }
+        return w;
+    }
+    __host__ __device__ static constexpr int set(int n_inst) { return 2 * feed_groups(n_inst) * kWave + 2 * n_inst * 4; }
 };
-// and where they put away what has come to an instance since its table was built, 64 requests at a time
+// and where they put away what has come to an instance since its table was built, 32 requests at a time
 struct FeedBlocks {
-    double2* yx = nullptr;     // [M][cap] sums of R, c*R + tri(R) up to each of the 64, in order of length
+    double2* yx = nullptr;     // [M][cap] sums of R, c*R + tri(R) up to each of the 32, in order of length
     double* c = nullptr;       // [M][cap] of contexts
     uint16_t* R = nullptr;     // [M][cap] the lengths
 };
-constexpr int feed_groups(int n_inst) { return (n_inst + 3) / 4; }
 
 enum KernelId {
     kBuild = 0, kRank, kMarkRoute, kScanRoute, kMemoRoute, kClassRoute, kLinesRoute, kSelectRoute,
@@ -255,7 +263,7 @@ struct gr_fleet {
     gr::FeedBase* feed_base = nullptr;      // [M]
     gr::FeedWords feed_words;
     gr::FeedBlocks feed_blocks;
-    int feed_polls = 4096;                  // see gr_set_feedback_wait
+    int feed_polls = 64, feed_team = INT32_MAX;   // see gr_set_feedback_wait, gr_set_feedback_team
     int feed_per_unit = 0;                  // workgroups of k_feedback_rounds that a compute unit runs at once
     int units = 0, feed_units = INT32_MAX;  // compute units of the device; see gr_set_feedback_units
     gr::DirectPart* direct_part = nullptr;       // [kDirectParts] selections of the parts of a wide fleet, scored pair by pair

@@ -1538,16 +1538,20 @@ __global__ __launch_bounds__(kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_feedbac
 // so that the look at them is not behind the gathering (5.4 us a round instead of 6.5), and new requests are terms in LDS, written by
 // their lanes (as lanes read off one by one 5.4, now 4.1).  A form that built long lists' tables anew on the way spilled 150 registers: 13.
 //
-// Every wait ends.  In the first one nothing has been changed yet, and it is bounded: when all workgroups are seen to be running,
-// workgroup 0 says so (kFeedTogether), and from there on a wait is for workgroups that run; where one has waited in vain (a
-// stream on a few compute units, a chip full of others' work) the mode is kFeedAlone, all return, and a second launch of
-// one workgroup, which otherwise returns at once, takes all instances in turn.
+// Every wait ends.  A workgroup is counted as it starts (FeedWords::gate), and looks until all have been, which takes no longer than its first
+// offers.  Where one has looked in vain (compute units full of others' work, several such
+// launches of which each has a part of the chip) it closes the gate.  Who comes later returns at once, and those counted until then
+// share the instances, several to a wave in turn; nothing has been changed up to there, and they use words of their own.  So all that
+// anybody waits for is running.  Four streams of 512 instances each, 2 048 requests, 64 a round, which do not fit side by side: 141 to 174 us a
+// call (a launch per round 182; where a lone workgroup did what the others had given up 95 to 485).  By how many workgroups: 256/64, 2 048
+// requests 160 us by all 64, 326 by 32, 512 by 16, 6 400 by one; 512/64, 2 000 186 by all 128, 354 by 64, 575 by 32.
 // Two sets of words in turn are enough: a workgroup writes a round's when it has seen all of the round before, whose writers had read
 // all of the one before that.
 //
 // 256 instances x 512, 32 rounds of 64, with the status build: 309 us with a launch for each, this way 164: a round is 4.1 us, of which the words
 // take 0.9, gathering with two blocks 1.3, the choice 0.5 to 0.9, adding and offering 0.6.
-enum FeedMode { kFeedUndecided = 0, kFeedTogether, kFeedAlone };
+constexpr uint32_t kFeedCount = 0xFFFFu, kFeedClosed = 1u << 31;      // of the gate: workgroups that have started; closed, and in between how many had then
+constexpr int kFeedShareAt = 16;
 constexpr int kFeedTagBits = 22, kFeedInstAt = kFeedTagBits;      // of a least word, below the latency: the round, the instance
 static_assert(kFeedInst <= 1 << (32 - kFeedInstAt));
 constexpr int kFeedMostRounds = 1 << (kFeedTagBits - 1);      // of one launch
@@ -1565,13 +1569,14 @@ struct FeedRoundsArgs {
     uint8_t* out_fallback;
     int64_t n;
     int chunk, first, rounds;      // requests of a round, the first round here, rounds in all
-    int polls;                     // looks at the words of the first round, about a microsecond each, before a workgroup gives up
+    int polls;                     // looks at the gate, about a microsecond each, before a workgroup closes it, if all but itself were here
+    int team;                      // workgroups that may share the work (see gr_set_feedback_team)
     const double2* sums_yx;
     const double* sums_c;
     const FeedBase* base;
     FeedBlocks blocks;
     FeedWords words;
-    uint32_t* T;                   // [M][kWave] (several instances a wave) latencies offered
+    uint32_t* T;                   // [M][kWave] latencies offered, where a wave has several instances
 };
 
 __device__ __forceinline__ unsigned long long peek(const unsigned long long* p)
@@ -1618,30 +1623,58 @@ struct FeedLengths {
     }
 };
 
-// kAlone: the second launch.
-template <int kTab, bool kAlone>
-__global__ __launch_bounds__(2 * kFeedWaves * kWave, 2) void k_feedback_rounds(FeedRoundsArgs f)
+// What the waves of a workgroup share, in LDS: arrays of their own (as members of one object, each write was in the way of the reads of
+// the others, 0.13 us a round).
+struct FeedState {
+    int over, ticket, team;           // a wait was in vain; see pass_gate
+};
+template <int kTab>
+struct FeedShared {
+    FeedLengths<kTab>* lengths;                                // [kFeedWaves]
+    unsigned long long (*least)[kWave], (*offer)[kWave], *met; // [kFeedWaves]
+    double4 (*held)[kFeedHeld];       // [kFeedWaves] R, c*R + tri(R), the context
+    ulonglong2* infos;                // [kFeedInst] met deadlines and d_g (as an integer that falls with it) of every instance
+    FeedState& state;
+};
+
+__device__ __forceinline__ uint32_t gate_of(const FeedWords& words)
+{
+    return __hip_atomic_load(words.gate, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Counts this workgroup, one of W, and waits for the others: how many share the work, and the how manieth of them this is (-1: come too late).
+__device__ inline int2 pass_gate(const FeedWords& words, int W, int polls)
+{
+    uint32_t v = __hip_atomic_fetch_add(words.gate, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int ticket = v & kFeedClosed ? -1 : (int)(v & kFeedCount);
+    v += v & kFeedClosed ? 0u : 1u;
+    for (int64_t looks = 0; !(v & kFeedClosed); ++looks) {
+        const int here = (int)(v & kFeedCount);
+        if (here == W) return make_int2(W, ticket);
+        if (looks * here < (int64_t)polls * W) { v = gate_of(words); continue; }      // (the fewer are here, the more is to be gained by those to come)
+        const uint32_t closed = kFeedClosed | (uint32_t)here << kFeedShareAt | (uint32_t)here;
+        if (__hip_atomic_compare_exchange_strong(words.gate, &v, closed, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) v = closed;
+    }
+    return make_int2((int)(v >> kFeedShareAt & (kFeedClosed - 1u) >> kFeedShareAt), ticket);
+}
+
+// The rounds by W workgroups, of which this is the w-th.  kPart: by fewer than have an instance for every wave.  Otherwise nothing is done where not
+// all have come in time.
+template <int kTab, bool kPart>
+__device__ __forceinline__ void feedback_rounds(const FeedRoundsArgs& f, const FeedShared<kTab>& sh, const int W, const int w)
 {
     constexpr int kAhead = 16;
     static_assert(kFeedWaves * kFeedWaves == 16 && kAhead * 16 == kFeedWaves * kWave, "a wave's share of the workgroups and of their instances is read together");
-    __shared__ FeedLengths<kTab> lengths_by[kFeedWaves];
-    __shared__ unsigned long long least_by[kFeedWaves][kWave], offer_by[kFeedWaves][kWave], met_by[kFeedWaves];
-    __shared__ double4 held_by[kFeedWaves][kFeedHeld];      // R, c*R + tri(R), the context
-    __shared__ ulonglong2 infos[kFeedInst];      // met deadlines and d_g (as an integer that falls with it) of every instance
-    __shared__ int over;
-    fetch_args<FeedRoundsArgs>();
     const BuildArgs& a = f.b;
     const int lane = lane_id(), both = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), wave = both % kFeedWaves;
     const bool reader = both >= kFeedWaves;      // these wait for the words of all, the others have the instances
-    const int M = a.n_inst, W = kAlone ? 1 : gridDim.x, w = kAlone ? 0 : blockIdx.x;
-    const auto inst_of = [&](int u) { return (u * W + w) * kFeedWaves + wave; };      // (alone a wave has several)
+    const int M = a.n_inst;
+    const FeedWords words = f.words.of(kPart, M);
+    const auto inst_of = [&](int u) { return (u * W + w) * kFeedWaves + wave; };
     const auto each_inst = [&](auto turn) {
-        if constexpr (kAlone) { for (int u = 0; !reader && inst_of(u) < M; ++u) turn(u); }
+        if constexpr (kPart) { for (int u = 0; !reader && inst_of(u) < M; ++u) turn(u); }
         else if (!reader && inst_of(0) < M) turn(0);
     };
-    if (kAlone && __hip_atomic_load(f.words.mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kFeedAlone) return;
-    if (threadIdx.x == 0) over = 0;
-    FeedLengths<kTab>& lengths = lengths_by[wave];
+    FeedLengths<kTab>& lengths = sh.lengths[wave];
     const bool blended = a.lam != 0.0;
     const double keep = 1.0 - a.lam;
 
@@ -1665,7 +1698,7 @@ __global__ __launch_bounds__(2 * kFeedWaves * kWave, 2) void k_feedback_rounds(F
     ClassCoef cc{};
     double bq = 0.0, bp = 0.0, bd = 0.0;
     double since_ctx = 0.0;
-    double4* const held = held_by[wave];
+    double4* const held = sh.held[wave];
     const auto block_at = [&](int b) { return (size_t)g * kTab + b * kFeedBlock; };
     const auto settled = [&]() {      // (the wave's own words in LDS)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1704,7 +1737,7 @@ __global__ __launch_bounds__(2 * kFeedWaves * kWave, 2) void k_feedback_rounds(F
         if (lane < kFeedBlock) {
             const size_t at = block_at(away / kFeedBlock) + lane;
             reinterpret_cast<uint16_t*>(lengths.blocks)[away + lane] = (uint16_t)(key[0] >> 6);
-            if (kAlone) f.blocks.R[at] = (uint16_t)(key[0] >> 6);
+            if (kPart) f.blocks.R[at] = (uint16_t)(key[0] >> 6);
             f.blocks.yx[at] = make_double2(y, x);
             f.blocks.c[at] = c;
         }
@@ -1795,18 +1828,18 @@ __global__ __launch_bounds__(2 * kFeedWaves * kWave, 2) void k_feedback_rounds(F
         own.met = __ballot(ok && T <= Dc);
         own.key = falling_bits(d);
         const unsigned long long v = lane < 2 ? own.met : own.key;
-        if (lane < 4) leave(f.words.own + ((size_t)(tag & 1) * M + g) * 4 + lane, ((lane & 1 ? v >> 32 : v & 0xFFFFFFFFu) << 32) | tag);
-        if (kAlone) f.T[(size_t)g * kWave + lane] = own.T;
+        if (lane < 4) leave(words.own + ((size_t)(tag & 1) * M + g) * 4 + lane, ((lane & 1 ? v >> 32 : v & 0xFFFFFFFFu) << 32) | tag);
+        if (kPart) f.T[(size_t)g * kWave + lane] = own.T;
         return ((unsigned long long)own.T << 32) | ((unsigned)g << kFeedInstAt) | tag;
     };
     const auto publish = [&](unsigned long long least, uint32_t tag) {      // of this wave's instances
-        if (!reader) offer_by[wave][lane] = least;
+        if (!reader) sh.offer[wave][lane] = least;
         __syncthreads();
         if (both != kFeedWaves) return;
-        least = offer_by[0][lane];
+        least = sh.offer[0][lane];
 #pragma unroll
-        for (int v = 1; v < kFeedWaves; ++v) least = min(least, offer_by[v][lane]);
-        leave(f.words.least + ((size_t)(tag & 1) * W + w) * kWave + lane, least);
+        for (int v = 1; v < kFeedWaves; ++v) least = min(least, sh.offer[v][lane]);
+        leave(words.least + ((size_t)(tag & 1) * W + w) * kWave + lane, least);
     };
     constexpr unsigned long long kNobody = ~0ull << 32;
 
@@ -1818,6 +1851,7 @@ __global__ __launch_bounds__(2 * kFeedWaves * kWave, 2) void k_feedback_rounds(F
             least = min(least, offer(gather(q), q, 1u));
         });
         publish(least, 1u);
+        if (!kPart && sh.state.team != W) return;      // (known since the barrier)
     }
     for (int round = f.first; round < f.rounds; ++round) {
         const uint32_t tag = (uint32_t)(round - f.first) + 1u;
@@ -1825,83 +1859,59 @@ __global__ __launch_bounds__(2 * kFeedWaves * kWave, 2) void k_feedback_rounds(F
         // (on their way while the others' words are)
         const Requests after = requests(min(round + 2, f.rounds - 1));
         Gathered G{};
-        if (!kAlone && more && !reader && inst_of(0) < M) {
+        if (!kPart && more && !reader && inst_of(0) < M) {
             while (since - away >= kFeedBlock) put_away();
             G = gather(next);
         }
 
         // the words of all, shared by the waves
         unsigned long long least, met;
-        bool greet = !kAlone && round == f.first;
-        for (int polls = greet ? f.polls : kFeedPollsMore;; polls = kFeedPollsMore) {
-            const unsigned long long* __restrict__ words = f.words.least + (size_t)(tag & 1) * W * kWave + lane;
-            const unsigned long long* __restrict__ theirs = f.words.own + (size_t)(tag & 1) * M * 4;
-            const int per = (W + kFeedWaves - 1) / kFeedWaves, h0 = min(wave * per, W - 1), h1 = min(h0 + per, W);
-            // (one trip for as much as there usually is: 16 workgroups and 64 instances for a wave.  A wave's share of the workgroups is
-            // at most M / 16 rounded up, and alone, where there is one workgroup, so many trips still pass all instances)
-            least = ~0ull;
-            met = 0;
-            int looks = 0;
-            for (int b = 0; reader && b < (M + 15) / 16; b += kAhead) {
-                unsigned long long v[kAhead], m[4];
-                const int h = (b / kAhead * kFeedWaves + wave) * kWave + lane;
-                for (;; ++looks) {
+        const unsigned long long* __restrict__ leasts = words.least + (size_t)(tag & 1) * W * kWave + lane;
+        const unsigned long long* __restrict__ theirs = words.own + (size_t)(tag & 1) * M * 4;
+        const int per = (W + kFeedWaves - 1) / kFeedWaves, h0 = min(wave * per, W - 1), h1 = min(h0 + per, W);
+        // (one trip for as much as there usually is: 16 workgroups and 64 instances for a wave.  A wave's share of the workgroups is
+        // at most M / 16 rounded up, and where they are fewer, so many trips still pass all instances)
+        least = ~0ull;
+        met = 0;
+        int looks = 0;
+        for (int b = 0; reader && b < (M + 15) / 16; b += kAhead) {
+            unsigned long long v[kAhead], m[4];
+            const int h = (b / kAhead * kFeedWaves + wave) * kWave + lane;
+            for (;; ++looks) {
 #pragma unroll
-                    for (int i = 0; i < kAhead; ++i) v[i] = peek(words + (size_t)min(h0 + b + i, h1 - 1) * kWave);
+                for (int i = 0; i < kAhead; ++i) v[i] = peek(leasts + (size_t)min(h0 + b + i, h1 - 1) * kWave);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) m[i] = peek(theirs + (size_t)min(h, M - 1) * 4 + i);
-                    bool all = true;
+                for (int i = 0; i < 4; ++i) m[i] = peek(theirs + (size_t)min(h, M - 1) * 4 + i);
+                bool all = true;
 #pragma unroll
-                    for (int i = 0; i < kAhead; ++i) all = all && ((uint32_t)v[i] & ((1u << kFeedTagBits) - 1u)) == tag;
+                for (int i = 0; i < kAhead; ++i) all = all && ((uint32_t)v[i] & ((1u << kFeedTagBits) - 1u)) == tag;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) all = all && (uint32_t)m[i] == tag;
-                    if (__all(all)) break;
-                    if (looks >= polls) { over = 1; break; }
-                }
-#pragma unroll
-                for (int i = 0; i < kAhead; ++i) least = min(least, v[i]);
-                const unsigned long long their_met = (m[0] >> 32) | (m[1] >> 32 << 32);
-                met |= their_met;
-                if (h < M) infos[h] = make_ulonglong2(their_met, (m[2] >> 32) | (m[3] >> 32 << 32));
+                for (int i = 0; i < 4; ++i) all = all && (uint32_t)m[i] == tag;
+                if (__all(all)) break;
+                if (looks >= kFeedPollsMore) { sh.state.over = 1; break; }
             }
-            if (reader) {
-                least_by[wave][lane] = least;
-                met = wave_or_u64(met);
-                if (lane == 0) met_by[wave] = met;
-            }
-            __syncthreads();
-            if (!greet) break;
-            if (threadIdx.x == 0) {      // are all here?
-                uint32_t mode = kFeedUndecided;
-                const auto say = [&](uint32_t mine) {
-                    if (__hip_atomic_compare_exchange_strong(f.words.mode, &mode, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                        mode = mine;
-                };
-                if (over || w == 0) say(over ? kFeedAlone : kFeedTogether);
-                for (int looks = 0; mode == kFeedUndecided; ++looks) {
-                    mode = __hip_atomic_load(f.words.mode, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (mode == kFeedUndecided && looks > f.polls) say(kFeedAlone);
-                }
-                over = mode == kFeedAlone ? 2 : over ? 3 : 0;
-            }
-            __syncthreads();
-            if (over != 3) break;
-            // (all are here, and have been seen by workgroup 0 alone so far: their words again)
-            greet = false;
-            __syncthreads();
-            if (threadIdx.x == 0) over = 0;
-            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) least = min(least, v[i]);
+            const unsigned long long their_met = (m[0] >> 32) | (m[1] >> 32 << 32);
+            met |= their_met;
+            if (h < M) sh.infos[h] = make_ulonglong2(their_met, (m[2] >> 32) | (m[3] >> 32 << 32));
         }
-        if (over) {
-            if (threadIdx.x == 0 && over == 1) atomicOr(&a.counters[0], GR_DEV_STALLED);
+        if (reader) {
+            sh.least[wave][lane] = least;
+            met = wave_or_u64(met);
+            if (lane == 0) sh.met[wave] = met;
+        }
+        __syncthreads();
+        if (sh.state.over) {
+            if (threadIdx.x == 0) atomicOr(&a.counters[0], GR_DEV_STALLED);
             return;
         }
-        least = least_by[0][lane];
-        met = met_by[0];
+        least = sh.least[0][lane];
+        met = sh.met[0];
 #pragma unroll
         for (int v = 1; v < kFeedWaves; ++v) {
-            least = min(least, least_by[v][lane]);
-            met |= met_by[v];
+            least = min(least, sh.least[v][lane]);
+            met |= sh.met[v];
         }
         const bool live = lane < q.n, served = (met >> lane) & 1ull;
         const uint32_t least_T = (uint32_t)(least >> 32);
@@ -1914,10 +1924,10 @@ __global__ __launch_bounds__(2 * kFeedWaves * kWave, 2) void k_feedback_rounds(F
 
         unsigned long long offered = kNobody | (tag + 1u);
         each_inst([&](int u) {
-            if (kAlone) {
+            if (kPart) {
                 enter(inst_of(u));
-                own.met = infos[g].x;
-                own.key = infos[g].y;
+                own.met = sh.infos[g].x;
+                own.key = sh.infos[g].y;
                 own.T = f.T[(size_t)g * kWave + lane];
             }
             // Alg. 1 for the instance itself: where a deadline can be met, it is met here and by nobody more capable; else nobody's
@@ -1925,7 +1935,7 @@ __global__ __launch_bounds__(2 * kFeedWaves * kWave, 2) void k_feedback_rounds(F
             unsigned long long above = 0;      // requests whose deadline is met by somebody more capable
             if (own.met) {
                 for (int h = lane; h < M; h += kWave) {
-                    const ulonglong2 o = infos[h];
+                    const ulonglong2 o = sh.infos[h];
                     above |= o.y < own.key || (o.y == own.key && h < g) ? o.x : 0ull;
                 }
                 above = wave_or_u64(above);
@@ -1933,7 +1943,7 @@ __global__ __launch_bounds__(2 * kFeedWaves * kWave, 2) void k_feedback_rounds(F
             const bool mine = live && (served ? ((own.met & ~above) >> lane) & 1ull
                                               : least_T != ~0u && (int)((uint32_t)least >> kFeedInstAt) == g);
             const unsigned long long joins = __ballot(mine);
-            if (kAlone && more) G = gather(next);
+            if (kPart && more) G = gather(next);
             if (joins) {
                 if (mine) {
                     f.out_inst[at] = g;
@@ -1957,7 +1967,7 @@ __global__ __launch_bounds__(2 * kFeedWaves * kWave, 2) void k_feedback_rounds(F
                 add_held(G, since - away, since - away + taken, (double)clamped(next.length));
                 since_ctx += readlane_f64(wave_incl_scan_f64(in ? e.z : 0.0), kWave - 1);
                 since += taken;
-                if (kAlone) while (since - away >= kFeedBlock) put_away();
+                if (kPart) while (since - away >= kFeedBlock) put_away();
             }
             if (more) offered = min(offered, offer(G, next, tag + 1u));
         });
@@ -1966,6 +1976,34 @@ __global__ __launch_bounds__(2 * kFeedWaves * kWave, 2) void k_feedback_rounds(F
         q = next;
         next = after;
     }
+    if (w == 0 && threadIdx.x == 0) *f.words.team = (uint32_t)W;
+}
+
+template <int kTab>
+__global__ __launch_bounds__(2 * kFeedWaves * kWave, 2) void k_feedback_rounds(FeedRoundsArgs f)
+{
+    __shared__ FeedLengths<kTab> lengths[kFeedWaves];
+    __shared__ unsigned long long least[kFeedWaves][kWave], offer[kFeedWaves][kWave], met[kFeedWaves];
+    __shared__ double4 held[kFeedWaves][kFeedHeld];
+    __shared__ ulonglong2 infos[kFeedInst];
+    __shared__ FeedState state;
+    const FeedShared<kTab> sh{lengths, least, offer, met, held, infos, state};
+    fetch_args<FeedRoundsArgs>();
+    const int all = gridDim.x;
+    if (threadIdx.x == kFeedWaves * kWave) {      // (of a wave that has nothing else to do yet)
+        const int2 at = pass_gate(f.words, all, f.polls);
+        state.team = min(at.x, f.team);
+        state.ticket = at.y;
+        state.over = 0;
+    }
+    feedback_rounds<kTab, false>(f, sh, all, blockIdx.x);
+    const int team = state.team, ticket = state.ticket;
+    if (team == all || ticket < 0 || ticket >= team) return;
+    __syncthreads();
+    // (its arguments are read here anew: kept from the start, their addresses were 75 more scalar registers put away in the rounds of all)
+    auto args = (const __attribute__((address_space(4))) FeedRoundsArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    feedback_rounds<kTab, true>(*(const FeedRoundsArgs*)args, sh, team, ticket);
 }
 
 // The capability rank of every instance, for the caller (Alg. 1's argmax d_g: rank 0 = largest d_g,
@@ -2359,11 +2397,11 @@ template <typename Use>
 static auto with_rounds_kernel(int epl, Use use)
 {
     switch (epl) {
-        case 2: return use(k_feedback_rounds<2 * kWave, false>);
-        case 4: return use(k_feedback_rounds<4 * kWave, false>);
-        case 8: return use(k_feedback_rounds<8 * kWave, false>);
-        case 16: return use(k_feedback_rounds<16 * kWave, false>);
-        default: return use(k_feedback_rounds<32 * kWave, false>);
+        case 2: return use(k_feedback_rounds<2 * kWave>);
+        case 4: return use(k_feedback_rounds<4 * kWave>);
+        case 8: return use(k_feedback_rounds<8 * kWave>);
+        case 16: return use(k_feedback_rounds<16 * kWave>);
+        default: return use(k_feedback_rounds<32 * kWave>);
     }
 }
 
@@ -2377,7 +2415,7 @@ int feedback_prepare(gr_fleet* f)
 }
 
 // Whether the workgroups of k_feedback_rounds, which wait for each other, can all run at once: on a stream of few compute units, or a
-// device of few, a call would wait in vain, then take many times as long as a launch for each round.  (A recorded call
+// device of few, every call would wait in vain, then share the work of those that did not come.  (A recorded call
 // is asked about the stream that records it.)
 static bool all_run_at_once(const gr_fleet* f, hipStream_t s)
 {
@@ -2400,21 +2438,12 @@ static void launch_feedback_rounds(gr_fleet* f, const BuildArgs& b, const Feedba
     a.b.chunk_n = 0;
     a.ctx0 = r.ctx0; a.pred_len = r.pred_len; a.exclude = r.exclude; a.budget = r.budget;
     a.out_inst = r.out_inst; a.out_slack = r.out_slack; a.out_fallback = r.out_fallback;
-    a.n = r.n; a.chunk = r.chunk; a.first = first; a.rounds = rounds; a.polls = f->feed_polls;
+    a.n = r.n; a.chunk = r.chunk; a.first = first; a.rounds = rounds; a.polls = f->feed_polls; a.team = f->feed_team;
     a.sums_yx = f->feed_yx; a.sums_c = f->feed_c; a.base = f->feed_base; a.blocks = f->feed_blocks; a.words = f->feed_words; a.T = f->feed_T;
-    const dim3 grid(feed_groups(f->n_inst)), block(2 * kFeedWaves * kWave);
-#define GR_LAUNCH_ROUNDS(E) do { \
-        { ProfScope ps(f, kFeedback, s); hipLaunchKernelGGL((k_feedback_rounds<E * kWave, false>), grid, block, 0, s, a); } \
-        ProfScope ps(f, kFeedback, s); \
-        hipLaunchKernelGGL((k_feedback_rounds<E * kWave, true>), dim3(1), block, 0, s, a); } while (0)
-    switch (f->epl) {
-        case 2: GR_LAUNCH_ROUNDS(2); break;
-        case 4: GR_LAUNCH_ROUNDS(4); break;
-        case 8: GR_LAUNCH_ROUNDS(8); break;
-        case 16: GR_LAUNCH_ROUNDS(16); break;
-        default: GR_LAUNCH_ROUNDS(32); break;
-    }
-#undef GR_LAUNCH_ROUNDS
+    ProfScope ps(f, kFeedback, s);
+    with_rounds_kernel(f->epl, [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(feed_groups(f->n_inst)), dim3(2 * kFeedWaves * kWave), 0, s, a);
+    });
 }
 
 int launch_feedback(gr_fleet* f, const StatusIn& in, const FeedbackIn& r, hipStream_t s)

@@ -1,5 +1,5 @@
 """Feedback routing whose rounds are one launch, against the same rounds through the table of lengths and a rebuild each, bit for bit: by all
-workgroups together and by one of them alone (which the others leave it to when they have not seen each other soon enough),
+workgroups together, by a part of them and by one alone (those that have come in time, or as many as the caller allows),
 lists of several blocks, two fleets at once on two streams, and recorded and replayed.  Where its workgroups do not fit the
 compute units, each round is a launch."""
 import dataclasses
@@ -20,7 +20,7 @@ def _fleet(n_inst, held, n, slo, seed):
 
 
 class _Routing:
-    def __init__(self, fl, chunk, entries, pairs=None, looks=None, blend=0.0):
+    def __init__(self, fl, chunk, entries, pairs=None, looks=None, blend=0.0, team=None):
         dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
         self.chunk, self.n, self.d = chunk, len(fl.in_prompt), upload(fl)
         self.h = binding.Fleet(fl.coef["delta"], fl.coef["alpha"], fl.coef["beta"], fl.coef["gamma"], fl.inst_class, entries,
@@ -29,6 +29,8 @@ class _Routing:
             self.h.gr_set_small_batch_pairs(pairs)
         if looks is not None:
             self.h.gr_set_feedback_wait(looks)
+        if team is not None:
+            self.h.gr_set_feedback_team(team)
         if blend:
             for w, wait, prefill, decode in workloads.observed_status(fl, rounds=2, seed=3):
                 self.h.gr_observe(w, dev(wait), dev(prefill), dev(decode))
@@ -59,10 +61,13 @@ class _Routing:
 def test_together_and_alone(n_inst, held, entries, chunk, n, slo, blend):
     fl = _fleet(n_inst, held, n, slo, n_inst + chunk)
     got = []
-    for pairs, looks in ((0, None), (None, None), (None, 0)):
-        r = _Routing(fl, chunk, entries, pairs, looks, blend)
+    groups = (n_inst + 3) // 4
+    for pairs, looks, team in ((0, None, None), (None, None, None), (None, 0, None), *((None, None, k) for k in {1, groups // 3, groups - 1} if k > 0)):
+        r = _Routing(fl, chunk, entries, pairs, looks, blend, team)
         r.run()
         got.append(r.result())
+        shared = r.h.gr_feedback_team()
+        assert shared == (0 if pairs == 0 else team or groups) if looks is None else 1 <= shared <= groups
         r.h.close()
     for other in got[1:]:
         for a, b in zip(got[0], other):
