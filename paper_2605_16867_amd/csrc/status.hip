@@ -2376,20 +2376,20 @@ bool feedback_by_round(const gr_fleet* f, int64_t chunk)
     return f->feed_T && !f->has_cap && chunk <= kWave && pair_by_pair(f, chunk);
 }
 
-// Whether the rounds are one launch (k_feedback_rounds, with one before it that builds all tables for the sums and one behind): from five
-// rounds on where a chunk is hardly more than a request or two (three rounds 16/4 27.4 / 30.7, 4/1 26.2 / 29.5); else, from three rounds on
-// (two: 256/2 24.6 / 28.1, 500/40 32.9 / 35.2, but three 512/1 45 / 35), where what the launches of every round take (5 us, and 1 us more
-// for every 64 instances, whose offers each workgroup reads) is more than what the requests of a chunk take that all go to one
-// instance (0.08 us each), by as much as the three launches.  Whole calls, us, a launch per round / one, N/c: N instances, chunks of c, deadlines that
-// few meet, in brackets such that all go for the same instances:
-//   256/64, 2 048 requests 309 / 164 (358 / 240)   500/64, 2 000 410 / 193   128/32, 1 000 243 / 155 (448: 116 / 100)   64/32, 448 (103 / 100)
-//   256/1, 100 676 / 306   32/1, 200 1 070 / 613   4/4, 24 (41.4 / 38.0)   4/8, 48 (46.2 / 40.2)   4/8, 24 24.2 / 28.3   256/3, 9 35.4 / 35.1
-//   24/16, 224 (98 / 84), 96 (44.6 / 45.2)   40/20, 120 (45.6 / 48.1)   64/64, 2 048 243 / 181 (896: 112 / 121)   4/64, 1 024 (125 / 149)
+// Whether the rounds are one launch (k_feedback_rounds, with one before it that builds all tables for the sums and one behind): where what the
+// launches of every round take (3 us, and 1 us more for every 64 instances, whose offers each workgroup reads) is more than what the requests of a
+// chunk take that all go to one instance (0.08 us each), by as much as the three launches: from four rounds on, and three on fleets
+// of some size (two: 256/1 23.6 / 24.3; 512/1 30.1 / 27.5, left a launch each).  Whole calls, us, a launch per round / one, N/c x r: N instances, chunks of
+// c, r rounds, deadlines that few meet, in brackets such that all go for the same instances:
+//   256/64 x 32 331 / 160 (358 / 240)   256/1 x 100 970 / 300   64/8 x 38 309 / 135   4/1 x 4 32.4 / 29.4   64/8 x 4 34.0 / 31.2 (32.1 / 29.8)
+//   4/16 x 4 32.8 / 31.3 (32.5 / 31.7)   32/32 x 4 33.7 / 31.9 (33.3 / 34.7)   64/32 x 5 39.9 / 37.5 (38.1 / 41.0)   128/32 x 4 36.2 / 32.2 (35.4 / 35.0)
+//   128/64 x 5 42.9 / 39.4 (42.2 / 48.5)   256/64 x 4 41.5 / 37.4 (41.5 / 42.1)   16/32 x 8 59.0 / 51.6 (59.1 / 59.3)   16/64 x 8 59.8 / 58.1 (62.1 / 69.4)
+//   three: 1/1 23.7 / 24.1   4/4 25.8 / 26.5   64/1 26.1 / 26.4   128/1 27.7 / 26.4   128/16 28.7 / 28.1 (27.9 / 27.6)   128/32 28.9 / 28.7 (28.3 / 29.9)
+//   256/32 32.8 / 30.1   256/64 33.0 / 31.8 (32.7 / 34.9)   512/64 43.2 / 36.8
 static bool in_one_launch(const gr_fleet* f, int64_t chunk, int64_t rounds)
 {
-    if (rounds < 3) return false;
-    if (chunk <= 4 && rounds >= 5) return true;
-    return (double)rounds * (2.9 + f->n_inst / 64.0 - 0.08 * (double)chunk) > 13.0;
+    const double more = (double)rounds * (2.9 + f->n_inst / 64.0 - 0.08 * (double)chunk);
+    return rounds >= 4 ? more > 7.0 : rounds == 3 && f->n_inst > 64 && more > 10.0;
 }
 
 // The kernel for tables of epl * kWave entries.

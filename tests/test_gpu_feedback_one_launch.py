@@ -74,6 +74,23 @@ def test_together_and_alone(n_inst, held, entries, chunk, n, slo, blend):
             assert torch.equal(a, b)
 
 
+# Sizes on either side of the choice: rounds in all, instances, and requests of a chunk that the gain of a round is weighed against.
+@pytest.mark.parametrize("n_inst,chunk,n,one", [
+    (512, 1, 2, False), (64, 1, 3, False), (65, 1, 3, True), (128, 19, 57, True), (128, 20, 60, False), (4, 15, 60, True), (4, 16, 64, False),
+    (4, 16, 65, True), (1, 16, 64, False), (1, 14, 56, True), (64, 44, 924, True), (64, 46, 966, False), (256, 64, 193, True), (256, 63, 189, False)])
+def test_where_rounds_are_one_launch(n_inst, chunk, n, one):
+    fl = _fleet(n_inst, 70, n, 4.0, n_inst + n)
+    got = []
+    for pairs in (0, None):
+        r = _Routing(fl, chunk, 700, pairs)
+        r.run()
+        got.append(r.result())
+        assert r.h.gr_feedback_team() == ((n_inst + 3) // 4 if one and pairs is None else 0)
+        r.h.close()
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+
+
 def test_two_at_once():
     rs, wants = [], []
     for k, (n_inst, chunk) in enumerate(((256, 32), (300, 24))):

@@ -1,6 +1,6 @@
 """Feedback routing that adds what has come to the sums of the tables as they were built last, against the same rounds through
 the table of lengths and a rebuild each, bit for bit: instances whose lists are taken in several times, that run out of
-room, that have requests from an earlier call, lengths out of range, and the sizes around the choice between the two."""
+room, that have requests from an earlier call, and lengths out of range."""
 import dataclasses
 
 import numpy as np
