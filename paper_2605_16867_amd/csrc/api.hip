@@ -2,6 +2,7 @@
 // order in which the kernels of status.hip and score.hip are queued.
 #include <algorithm>
 #include <new>
+#include <type_traits>
 
 #include "common.h"
 
@@ -133,6 +134,17 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     const size_t tab = (size_t)n_inst * f->cap, segments = (size_t)n_inst * (f->cap + 1), seen_bytes = (size_t)(f->bins + 15) / 16 * 16;
     const bool by_row = classes_first(f, false, max_requests), by_round = n_inst <= kFeedInst && waves_per_instance(f->epl, n_inst) > 1;
     const size_t words = 2 * (size_t)FeedWords::set(n_inst) + 1;
+    // (parts of one allocation: each takes its time, 8 us)
+    const auto feedback_parts = [&](auto part) {
+        part(&f->feed_base, (size_t)n_inst);
+        part(&f->feed_yx, segments); part(&f->feed_c, segments);
+        part(&f->feed_blocks.yx, tab); part(&f->feed_blocks.c, tab); part(&f->feed_blocks.R, tab);
+        part(&f->feed_words.least, words);
+        part(&f->feed_T, (size_t)2 * n_inst * kWave); part(&f->feed_met, (size_t)2 * n_inst); part(&f->feed_key, (size_t)2 * n_inst);
+    };
+    const auto bytes_of = [](size_t each, size_t n) { return (each * n + 255) / 256 * 256; };
+    size_t feed_bytes = 0;
+    if (by_round) feedback_parts([&](auto** p, size_t n) { feed_bytes += bytes_of(sizeof **p, n); });
     const bool ok =
         dev_alloc(&f->cls, n_class) && dev_alloc(&f->inst_class, n_inst) &&
         dev_alloc(&f->tabR, tab + kWave) && dev_alloc(&f->tabGH, (size_t)n_inst * (f->cap + 2) + kWave) &&
@@ -141,7 +153,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
         dev_alloc(&f->instK, n_inst) && dev_alloc(&f->tabS, (size_t)n_inst * f->n_split) &&
         dev_alloc(&f->clsK, n_class) && dev_alloc(&f->slot_inst, f->m_pos) && dev_alloc(&f->slot_of, n_inst) && dev_alloc(&f->slot_key, f->m_pos) && dev_alloc(&f->run_cls, f->n_run) && dev_alloc(&f->cls_run, n_class) &&
         dev_alloc(&f->order, f->m_pos) && dev_alloc(&f->pos_of, n_inst) && dev_alloc(&f->posK, f->m_pos) && dev_alloc(&f->posKey, f->m_pos) && dev_alloc(&f->run_head, f->n_run) &&
-        dev_alloc(&f->act_inst, f->max_active) && dev_alloc(&f->counters, 1) &&
+        dev_alloc(&f->act_inst, f->max_active) && dev_alloc(&f->counters, 2) &&
         dev_alloc(&f->pend_cnt, n_inst) && dev_alloc(&f->commit_mark, n_inst) && dev_alloc(&f->pend_touched, n_inst) && dev_alloc(&f->pend_prompt, tab) && dev_alloc(&f->pend_len, tab) &&
         dev_alloc(&f->scratch_finish, f->max_active + kBlock * kRestItems) && dev_alloc(&f->batch_cap, n_inst) &&
         dev_alloc(&f->seen, seen_bytes) && dev_alloc(&f->late_cnt, (size_t)n_inst * 4) &&
@@ -150,24 +162,19 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
         dev_alloc(&f->run_k, f->n_run) && dev_alloc(&f->run_rank, f->n_run) && dev_alloc(&f->run_at, f->n_run) && dev_alloc(&f->pos_thr, f->m_pos) &&
         dev_alloc(&f->cls_rank, n_class) && (n_class > kMemoP || dev_alloc(&f->class_least, (size_t)f->bins << f->class_shift)) &&
         dev_alloc(&f->rest_cnt, kRestParts * kRestStride) && dev_alloc(&f->lines, (size_t)f->row_cap * kRanges * 2) && dev_alloc(&f->turned, (size_t)f->turned_rows * n_inst) && dev_alloc(&f->direct_part, (size_t)kDirectParts) &&
-        (!by_round || (dev_alloc(&f->feed_T, (size_t)2 * n_inst * kWave) && dev_alloc(&f->feed_met, (size_t)2 * n_inst) &&
-                       dev_alloc(&f->feed_key, (size_t)2 * n_inst) && dev_alloc(&f->feed_words.least, words) && dev_alloc(&f->feed_blocks.yx, tab + (tab * 10 + 15) / 16) &&
-                       dev_alloc(&f->feed_base, n_inst + (segments * (sizeof(double2) + sizeof(double)) + sizeof(FeedBase) - 1) / sizeof(FeedBase))));
+        (!by_round || dev_alloc(&f->feed_parts, feed_bytes));
     if (!ok) { gr_destroy(f); return GR_ERR_NOMEM; }
-    // (parts of one allocation: each takes its time)
     if (by_row) f->row_min = f->grp_min + (size_t)f->row_cap * f->run_pad;
     if (by_round) {
+        char* at = f->feed_parts;
+        feedback_parts([&](auto** p, size_t n) {
+            *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>(at);
+            at += bytes_of(sizeof **p, n);
+        });
         f->feed_words.own = f->feed_words.least + 2 * feed_groups(n_inst) * kWave;
         f->feed_words.gate = reinterpret_cast<uint32_t*>(f->feed_words.least + words - 1);
-        f->feed_words.team = f->feed_words.gate + 1;
+        f->feed_words.team = reinterpret_cast<uint32_t*>(f->counters + 1);
         f->feed_words.n = (int)words;
-        f->feed_blocks.c = reinterpret_cast<double*>(f->feed_blocks.yx + tab);
-        f->feed_blocks.R = reinterpret_cast<uint16_t*>(f->feed_blocks.c + tab);
-    }
-    static_assert(sizeof(FeedBase) % sizeof(double2) == 0, "the sums begin at a multiple of 16 bytes");
-    if (f->feed_base) {
-        f->feed_yx = reinterpret_cast<double2*>(f->feed_base + n_inst);
-        f->feed_c = reinterpret_cast<double*>(f->feed_yx + segments);
     }
 
     bool sent = true;
@@ -184,7 +191,7 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     const int dense[2] = {0, f->bins};
     send(f->dense_totals, dense, sizeof dense);
     send(f->inst_class, inst_class, sizeof(int) * n_inst);
-    clear(f->counters, sizeof(int));
+    clear(f->counters, 2 * sizeof(int));
     clear(f->seen, seen_bytes);
     clear(f->slot_key, sizeof(unsigned long long) * f->m_pos);
     clear(f->totals, sizeof(int) * 4);
@@ -196,7 +203,6 @@ int gr_create(gr_fleet** out, int32_t n_inst, int32_t n_class,
     clear(f->tabGH, ((size_t)n_inst * (f->cap + 2) + kWave) * sizeof(float2));
     clear(f->instK, sizeof(float4) * n_inst);
     clear(f->hD, sizeof(double) * n_inst);
-    if (by_round) clear(f->feed_words.least, words * sizeof(unsigned long long));
     clear(f->pend_cnt, sizeof(int) * n_inst);
     clear(f->pend_touched, sizeof(int) * n_inst);
     clear(f->commit_mark, sizeof(int) * n_inst);
@@ -216,7 +222,7 @@ int gr_destroy(gr_fleet* f)
     void* ptrs[] = {f->cls, f->inst_class, f->tabR, f->tabGH, f->hD, f->emaQ, f->emaP, f->emaD, f->instK, f->tabS,
                     f->clsK, f->slot_inst, f->slot_of, f->slot_key, f->run_cls, f->cls_run, f->order, f->pos_of, f->posK, f->posKey, f->run_head, f->act_inst, f->pend_cnt, f->commit_mark, f->pend_touched, f->pend_prompt, f->pend_len,
                     f->scratch_finish, f->batch_cap, f->counters, f->seen, f->late_cnt, f->row_len,
-                    f->len_row, f->totals, f->dense_totals, f->memo, f->grp_min, f->run_k, f->run_rank, f->run_at, f->pos_thr, f->cls_rank, f->class_least, f->rest_cnt, f->lines, f->turned, f->feed_T, f->feed_met, f->feed_key, f->feed_base, f->feed_words.least, f->feed_blocks.yx, f->direct_part};
+                    f->len_row, f->totals, f->dense_totals, f->memo, f->grp_min, f->run_k, f->run_rank, f->run_at, f->pos_thr, f->cls_rank, f->class_least, f->rest_cnt, f->lines, f->turned, f->feed_parts, f->direct_part};
     int rc = GR_OK;
     for (void* p : ptrs)
         if (p && hipFree(p) != hipSuccess) rc = GR_ERR_HIP;

@@ -221,7 +221,7 @@ struct gr_fleet {
     float* scratch_finish = nullptr;  // [max_active + kBlock * kRestItems] finish times of rebuilds nobody asked to see
     int* batch_cap = nullptr;     // [M] requests that may decode together on each instance
     bool has_cap = false;
-    int* counters = nullptr; // [1] GR_DEV_* bits
+    int* counters = nullptr; // [2] GR_DEV_* bits, FeedWords::team
     // scoring workspace
     uint8_t* seen = nullptr;  // [bins, to 16] 1: some request of the batch has the length; all zero between calls
     int* late_cnt = nullptr;  // [4][M] flagged requests, counted by the build (late_parts counts per instance)
@@ -254,10 +254,11 @@ struct gr_fleet {
     int64_t small_batch_pairs = -1;   // largest batch, in pairs, scored pair by pair; -1: by the sizes (see pair_by_pair)
     // feedback routing, a launch per round (null on fleets of more than kFeedInst instances, and where one wave takes an instance), two of each in turn: what
     // every instance offers the requests of a chunk
+    char* feed_parts = nullptr;             // (all of this)
     uint32_t* feed_T = nullptr;             // [2][M][kWave] latency as an integer of the same order; all ones: not allowed
     unsigned long long* feed_met = nullptr; // [2][M] bit j: request j's deadline is met
     unsigned long long* feed_key = nullptr; // [2][M] d_g as an integer that falls with it
-    // the sums behind the tables (Y_k, X_k and the contexts of the k shortest), by segment, and those of whole instances (one allocation)
+    // the sums behind the tables (Y_k, X_k and the contexts of the k shortest), by segment, and those of whole instances
     double2* feed_yx = nullptr;             // [M][cap + 1]
     double* feed_c = nullptr;               // [M][cap + 1]
     gr::FeedBase* feed_base = nullptr;      // [M]
