@@ -94,17 +94,18 @@ def test_blended(n_inst, blend):
 
 
 @pytest.mark.parametrize("kind", ["mixed", "clones", "idle"])
-@pytest.mark.parametrize("n_req,n_class", [((1 << 17) - 1, 3), (1 << 17, 3), ((1 << 17) + 37, 16), ((1 << 19) + 5, 4)])
+@pytest.mark.parametrize("n_req,n_class", [((1 << 17) - 1, 3), (1 << 17, 3), ((1 << 17) + 37, 16), ((1 << 19) + 5, 4),
+                                           ((1 << 19) - 1, 16), (1 << 19, 9), ((1 << 19) + 1, 16)])
 def test_classes_first(n_req, n_class, kind):
     _check(_fleet(1300, n_class, n_req, kind))
 
 
 # Least and next larger E of a class a rounding or a few apart (one queued prompt token is 2e-5 s), and prompts so long, or of the
 # other sign, that their latencies fall together; as many classes as one piece, two, four and eight of 16 bytes hold.
-@pytest.mark.parametrize("n_class", [1, 2, 3, 5, 8, 9, 16])
-def test_classes_first_latencies_that_rounding_makes_equal(n_class):
+@pytest.mark.parametrize("n_class,R", [(n, (1 << 17) + 1) for n in (1, 2, 3, 5, 8, 9, 16)] + [(n, (1 << 19) + 1) for n in (2, 9, 16)])
+def test_classes_first_latencies_that_rounding_makes_equal(n_class, R):
     rng = np.random.default_rng(n_class)
-    M, R = 1100, (1 << 17) + 1
+    M = 1100
     classes = [tuple(x * f for x in CLASSES[c % 3]) for c, f in enumerate(np.linspace(1.0, 1.7, n_class))]
     some = [rand_entries(rng, int(n)) for n in rng.integers(1, 40, 5)]
     queued = [[(int(t), 4000)] if t else [] for t in rng.integers(0, 4, M)]

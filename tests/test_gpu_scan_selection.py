@@ -28,12 +28,15 @@ def _observe(h, M, rng, kind):
     h.gr_observe(1.0, *[torch.from_numpy(x.astype(np.float32)).cuda() for x in obs])
 
 
-def _scan(n_inst, held, n_class, late, blend=0.0, obs="many", clones=False, seed=0):
+def _scan(n_inst, held, n_class, late, blend=0.0, obs="many", clones=False, seed=0, total=None):
     import torch
     rng = np.random.default_rng([n_inst, held, n_class, seed])
     classes = [tuple(x * f for x in CLASSES[c % 3]) for c, f in enumerate(np.linspace(1.0, 1.7, n_class))]
     sizes = np.full(n_inst, held)
     sizes[rng.integers(0, n_inst, 3)] = [0, 1, held - 1]
+    if total is not None:
+        sizes[:] = held
+        sizes[:n_inst * held - total] -= 1
     some = rand_entries(rng, held)
     acts = [some[:n] if clones else rand_entries(rng, int(n)) for n in sizes]
     all_ = np.concatenate(acts)
@@ -73,13 +76,22 @@ def _scan(n_inst, held, n_class, late, blend=0.0, obs="many", clones=False, seed
     return na, len(idx) / na, feasible / max(len(idx), 1)
 
 
-# the classes first: 2^17 requests and more, 2^19 and more
+# the classes first: 2^17 requests and more, 2^18 and more
 @pytest.mark.parametrize("clones", [False, True])
 @pytest.mark.parametrize("late", ["all", "some"])
 @pytest.mark.parametrize("n_inst,held,n_class", [(520, 257, 3), (1100, 121, 16), (530, 1001, 4)])
 def test_scan_classes_first(n_inst, held, n_class, late, clones):
     na, share, _ = _scan(n_inst, held, n_class, late, clones=clones)
     assert na >= 1 << 17 and share > 0.01
+
+
+# the classes first, by four lanes a request up to 2^18 of them, by one from there on; up to 8 classes, and more
+@pytest.mark.parametrize("late", ["all", "some"])
+@pytest.mark.parametrize("n_class", [3, 9, 16])
+@pytest.mark.parametrize("total", [(1 << 18) - 1, 1 << 18, (1 << 18) + 1])
+def test_scan_classes_first_by_lanes(total, n_class, late):
+    na, share, _ = _scan(1100, 239, n_class, late, total=total)
+    assert na == total and share > 0.01
 
 
 # over the runs (less than 3 * 2^16 requests), and the lines first (more than 80 runs, less than 2^19 requests)
