@@ -747,7 +747,7 @@ struct ClassArgs {
 // instance that has it and the exponent of the distance to the next larger E (which says whether rounding may have made the two
 // latencies equal).  A length's classes are 16, 32, 64 or 128 bytes together, and the lanes of a request read them side by side.
 __device__ inline size_t class_at(int L, int shift) { return (size_t)L << shift; }
-constexpr int kLowBits = 20, kCountAt = 28;      // bits of the instance (gr_create takes no more); see least_of_classes
+constexpr int kLowBits = 20, kCountAt = 28;      // bits of the instance (gr_create takes no more); see ClassesOf::least
 __device__ inline uint32_t low_and_gap(int low, float least, float next)
 {
     return ((__float_as_uint(next - least) >> 23 & 0xFFu) << kLowBits) | ((uint32_t)low & ((1u << kLowBits) - 1u));
@@ -929,15 +929,15 @@ __device__ __forceinline__ void answer(const SelectArgs& a, int64_t i, int g, fl
 
 // Alg. 1 for one request by the kGroup lanes of a group, in two moves that take a range of runs.
 //
-// Feasible choice (scan<true, .>): of every run whose bound meets the deadline and whose most capable
+// Feasible choice (scan<true, ., .>): of every run whose bound meets the deadline and whose most capable
 // instance would be an improvement, the first feasible position (a run's positions are in
 // capability order, and classes of slow steps come first).  The improvement is one comparison: the runs are
 // ranked by their first instances, and every position knows how many runs begin with a better one (with
-// the d_g themselves, 64 bits and the index on ties, the search took half of the selection's instructions).  Least latency (scan<., true>, then
+// the d_g themselves, 64 bits and the index on ties, the search took half of the selection's instructions).  Least latency (scan<., true, .>, then
 // settle): the run with the least bound is looked at, then every other run whose bound does not
 // exceed the least latency at hand (equal ones only if they hold a lower instance).  kChunks x
 // kGroup runs are read together: the reads of the runs' values are what a request waits for.
-template <int kChunks, bool kBlocks>
+template <int kChunks>
 struct Selection {
     const SelectArgs& a;
     const int sub, ex;
@@ -959,7 +959,7 @@ struct Selection {
     int r1;
 
     __device__ __forceinline__ Selection(const SelectArgs& args, const Request& q, int row, int sub_)
-        : a(args), sub(sub_), ex(q.ex), runs(args.grp_min + runs_at<kBlocks>(row, args.run_pad)),
+        : a(args), sub(sub_), ex(q.ex), runs(args.grp_min + runs_at<false>(row, args.run_pad)),
           E(args.memo + memo_at(row, 0, args.n_run) + sub_), run_at(args.run_at), run_k(args.run_k), Lf((float)q.L), c0((float)q.c0),
           Dc(q.D > FLT_MAX ? FLT_MAX : q.D) {}
 
@@ -981,7 +981,7 @@ struct Selection {
             float b[kChunks];
             float4 k[kChunks];
             int run[kChunks];
-            uint32_t rank[kChunks];      // (read with the rest where a feasible run is known to be there)
+            uint32_t rank[kChunks];      // (in class order read where there is a run in question)
 #pragma unroll
             for (int j = 0; j < kChunks; ++j) {
                 const int i = min(r0 + j * kGroup + sub, n - 1);
@@ -990,8 +990,7 @@ struct Selection {
             }
 #pragma unroll
             for (int j = 0; j < kChunks; ++j) {
-                if (!kRanked && !kLeast) rank[j] = a.run_rank[run[j]];
-                b[j] = runs[(size_t)run[j] * kRunStride<kBlocks>];
+                b[j] = runs[run[j]];
                 k[j] = run_k[run[j]];
             }
             bool any = false;
@@ -1007,7 +1006,7 @@ struct Selection {
             if (!kFeasible || !__any(any)) continue;
 #pragma unroll
             for (int j = 0; j < kChunks; ++j) {
-                if (!kRanked && kLeast) rank[j] = a.run_rank[run[j]];
+                if (!kRanked) rank[j] = a.run_rank[run[j]];
                 if (!(b[j] <= Dc)) rank[j] = ~0u;      // (not, or no longer, in question)
             }
             for (;;) {
@@ -1078,7 +1077,7 @@ struct Selection {
         if (!group_ballot(m2 <= bestT && m2 < inf)) return;
         for (int rb = 0; rb < n; rb += kGroup) {       // some lane has a second run to look at: all runs again
             const int r = first + min(rb + sub, n - 1);
-            const float b = rb + sub < n ? bound(runs[(size_t)r * kRunStride<kBlocks>], a.run_k[r]) : inf;
+            const float b = rb + sub < n ? bound(runs[r], a.run_k[r]) : inf;
             uint32_t again = group_ballot(b <= bestT && b < inf && r != r1);
             while (again) {
                 const int lo = __ffs(again) - 1;
@@ -1110,7 +1109,7 @@ __global__ __launch_bounds__(kBlock) void k_select(SelectArgs a)
         if (sub == 0) answer<kMigrate>(a, i, -1, 0.f, false);      // not flagged: no migration target
         return;
     }
-    Selection<kChunks, false> sel(a, q, row_at(a.len_row, q.L), sub);
+    Selection<kChunks> sel(a, q, row_at(a.len_row, q.L), sub);
     sel.template scan<true, true, false>(0, a.n_run);
     if (sel.feasG < 0) sel.settle(0, a.n_run);
     sel.template report<kMigrate>(i, q.D);
@@ -1679,7 +1678,7 @@ __device__ __forceinline__ LineChoice choose_line(const Request& q, const float4
 // What the lines leave open, by a group of lanes: mostly requests that can be served in time, so the least
 // latency is not looked for along the way.
 template <bool kMigrate>
-__device__ __forceinline__ void select_rest(const SelectArgs& a, int64_t i, const Request& q, Selection<4, false>& sel)
+__device__ __forceinline__ void select_rest(const SelectArgs& a, int64_t i, const Request& q, Selection<4>& sel)
 {
     sel.template scan<true, false, true>(0, a.n_run);
     if (sel.feasG < 0) {
@@ -1708,7 +1707,7 @@ __global__ __launch_bounds__(kBlock) void k_select_lines(SelectArgs a)
         if (sub == 0) answer<kMigrate>(a, i, c.g, q.D - c.T, false);
         return;
     }
-    Selection<4, false> sel(a, q, row, sub);
+    Selection<4> sel(a, q, row, sub);
     select_rest<kMigrate>(a, i, q, sel);
 }
 
@@ -1788,7 +1787,7 @@ __global__ __launch_bounds__(kBlock, 6) void k_late_rest(SelectArgs a, int wg_re
     for (; k < n; k += kStep) {
         const int i3 = index(k + 3 * kStep), row1 = a.len_row[q1.L];
         const Request q2 = fetch<true>(a.s, i2, a.max_len);
-        Selection<4, false> sel(a, q, row, sub);
+        Selection<4> sel(a, q, row, sub);
         sel.run_at = lds_at;
         sel.run_k = lds_k;
         select_rest<true>(a, i, q, sel);
