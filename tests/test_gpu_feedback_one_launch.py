@@ -1,6 +1,6 @@
 """Feedback routing whose rounds are one launch, against the same rounds through the table of lengths and a rebuild each, bit for bit: by all
 workgroups together, by a part of them and by one alone (those that have come in time, or as many as the caller allows),
-lists of several blocks, two fleets at once on two streams, and recorded and replayed.  Where its workgroups do not fit the
+lists of several blocks, several fleets at once on a stream each, and recorded and replayed.  Where its workgroups do not fit the
 compute units, each round is a launch."""
 import dataclasses
 
@@ -91,14 +91,16 @@ def test_where_rounds_are_one_launch(n_inst, chunk, n, one):
         assert torch.equal(a, b)
 
 
-def test_two_at_once():
+# (four of 512 instances do not fit side by side: each gets a part of the chip, and goes on with the workgroups that have started)
+@pytest.mark.parametrize("fleets,looks", [(((256, 32), (300, 24)), None), (((512, 16),) * 4, None), (((512, 16),) * 4, 2)])
+def test_several_at_once(fleets, looks):
     rs, wants = [], []
-    for k, (n_inst, chunk) in enumerate(((256, 32), (300, 24))):
-        fl = _fleet(n_inst, 80, 500, (1.0, 16.0)[k], 40 + k)
+    for k, (n_inst, chunk) in enumerate(fleets):
+        fl = _fleet(n_inst, 80, 500, (1.0, 16.0)[k % 2], 40 + k)
         want = _Routing(fl, chunk, 600, pairs=0)
         want.run()
         wants.append(want.result())
-        rs.append(_Routing(fl, chunk, 600))
+        rs.append(_Routing(fl, chunk, 600, looks=looks))
     streams = [torch.cuda.Stream() for _ in rs]
     torch.cuda.synchronize()
     for _ in range(4):
