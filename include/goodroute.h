@@ -77,7 +77,10 @@ enum {
 enum {
     GR_DEV_LEN_CLAMPED = 1,   /* a length outside [0, max_len] was clamped */
     GR_DEV_ENTRIES_DROPPED = 2, /* an instance held more than max_entries_per_inst entries */
-    GR_DEV_STALLED = 4         /* feedback routing gave up a wait inside the device (not expected to happen) */
+    GR_DEV_STALLED = 4         /* feedback routing gave up a wait inside the device after some two seconds (not expected to happen: all that
+                                  it waits for is running).  The call had returned GR_OK; from some request on its outputs are
+                                  what they were before, and the handle's tables and lists hold a part of what was routed: both
+                                  are of no use until the next gr_build_status or gr_risk_scan. */
 };
 
 /*
@@ -236,10 +239,11 @@ int gr_score_route_cached(gr_fleet* f, int64_t n_req,
  * weight, the observations or the caps have changed since the tables were built:
  * then the first rebuild of the call takes every instance).  Chunks of up to 64 on
  * fleets of up to 512 instances, without caps and with max_entries_per_inst above 64,
- * are one launch each; three and more of them of up to 8 requests, or of up to a quarter
- * of the instances with at most 20 480 pairs, rebuild every instance at the start of
- * the call, then add what comes to the sums behind the tables, and rebuild the
- * instances that were given any at the end.
+ * that are scored pair by pair (see gr_set_small_batch_pairs) are one launch each, or all
+ * of them are one: between a launch that builds every instance and one that rebuilds those that were
+ * given any, what comes is added to sums behind the tables.  That takes at least four rounds (three on more than 64 instances), and more
+ * the larger the chunks are for the fleet (rounds * (2.9 + n_inst / 64 - 0.08 * chunk) above 7, or 10 for three), and
+ * compute units for all its workgroups (see gr_set_feedback_units).  The results are the same.
  *
  *   chunk      requests per decision round, >= 1 (cut to max_requests)
  * Other arguments as gr_score_route (no out_T).

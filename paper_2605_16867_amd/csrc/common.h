@@ -43,7 +43,7 @@ constexpr int64_t kDirectPairs = int64_t(1) << 19;   // pairs of a batch that is
 constexpr int64_t kDirectLanes = int64_t(3) << 18;   // and pairs that its lanes go through
 constexpr int64_t kDirectInfinite = int64_t(1) << 18;   // pairs (of whole 128 instances) up to which infinite latencies count there
 constexpr int kDirectSpan = 4096;  // instances that one workgroup takes of a request scored pair by pair
-constexpr int kFeedInst = 512;     // most instances of a fleet whose feedback routing is a launch per round
+constexpr int kFeedInst = 512;     // most instances of a fleet whose feedback routing is a launch a round, or one for all
 constexpr int kDirectParts = 16384;  // room for the selections of such parts
 constexpr int64_t kDenseValues = int64_t(1) << 22;   // values of a table that has a row for every length
 constexpr int kMemoP = 16;         // positions of a run of the class order
@@ -252,7 +252,7 @@ struct gr_fleet {
     bool recorded = false, blend_recorded = false;
     int* pend_touched = nullptr;   // [M] 1: given requests since its table was built
     int64_t small_batch_pairs = -1;   // largest batch, in pairs, scored pair by pair; -1: by the sizes (see pair_by_pair)
-    // feedback routing, a launch per round (null on fleets of more than kFeedInst instances, and where one wave takes an instance), two of each in turn: what
+    // feedback routing, a launch a round or one for all (null on fleets of more than kFeedInst instances, and where one wave takes an instance), two of each in turn: what
     // every instance offers the requests of a chunk
     char* feed_parts = nullptr;             // (all of this)
     uint32_t* feed_T = nullptr;             // [2][M][kWave] latency as an integer of the same order; all ones: not allowed
@@ -335,7 +335,7 @@ int status_prepare();
 int feedback_prepare(gr_fleet* f);
 int launch_ranks(gr_fleet* f, int* out_rank, hipStream_t s);
 int launch_status(gr_fleet* f, const StatusIn& in, hipStream_t s);
-// A whole feedback routing in chunks of up to kWave requests, a launch per round (see k_feedback).  `in`: the status inputs to
+// A whole feedback routing in chunks of up to kWave requests, a launch a round (see k_feedback) or one for all (k_feedback_rounds).  `in`: the status inputs to
 // rebuild from; `current`: instances that are given nothing keep their tables.
 struct FeedbackIn {
     int64_t n;

@@ -97,8 +97,8 @@ __device__ __forceinline__ void order2(uint32_t& lo, uint32_t& hi)
 // SIMD hardly has a wave to run meanwhile: an exchange is a step of a chain, and stays in the
 // register file, whose step is shorter than the crossbar's.  With more words the vector ALU is what the waves of a SIMD wait for,
 // and the fetches that no single pattern does are left to the crossbar.  Whole calls, us, everywhere like that / as here: refresh of 256 x 512 and
-// one request 8.77 / 8.42, step of 32 x 256 20.43 / 20.00, of 4 x 64 14.69 / 14.50.  (All fetches through
-// the crossbar: 8.85, 20.2, 15.2; status of 4 096 x 512 21.3 / 21.0, but its scan 108.6 / 109.6; scan of 1 024 x 1 000 60.4 / 59.9 to 60.6.)
+// one request 8.77 / 8.42, step of 32 x 256 20.43 / 20.00 (of 4 x 64: no difference that timing shows).  (All fetches through
+// the crossbar: 8.85, 20.2; status of 4 096 x 512 21.3 / 21.0, but its scan 108.6 / 109.6; scan of 1 024 x 1 000 60.4 / 59.9 to 60.6.)
 // Under caps an instance has one wave, whose sort is a chain between the turns of others': in the register file at every size.  Status
 // under caps, crossbar / here: 1 024 x (56 + 7) 11.45 / 11.10, (110 + 13) 14.83 / 14.87, (224 + 28) 23.8 / 23.7, (450 + 56) 40.1 / 40.8 (long tails
 // 27.7 / 27.7), (900 + 112) 78.5 / 77.1 (47.7 / 46.1), (1 820 + 227) 138.2 / 136.4 (88.5 / 85.1); 4 096 x 450 38.4 / 38.2, x (450 + 56) 90.8 / 92.3
@@ -319,6 +319,7 @@ constexpr int log2_of(int v) { return v <= 1 ? 0 : 1 + log2_of(v / 2); }
 // 27.9 where a turn of one departure and one admission has no sums over the lanes: the newcomer's context is read from LDS, the
 // other's off its lane; an entry's context when it leaves is known beforehand, and one that has left is
 // marked, so that the minimum needs no comparison with the step.  1 000 x (1 000 + 125) 167 -> 136, 4 096 x (400 + 50) 103 -> 89.
+// (Less is won than prepared where one or two wait in tables of 513 to 1 024 entries: 64 x (1 000 + 1) 31.6 -> 32.1, + 2 32.0 -> 32.0, + 8 36.4 -> 35.2.)
 // An instance without a queue plays no turn, and what the turns need is not prepared for it: 64 x 1 000 24.2 -> 22.8 us,
 // 4 096 x 900 95.5 -> 91, 1 024 x 1 820 60.7 -> 56.6.
 constexpr int kLowBits = 24;     // a lane's sum of contexts is added up over the wave in two parts of 32 bits
@@ -1314,7 +1315,7 @@ __global__ __launch_bounds__(kSplit == 1 ? kBlock : kWave * kSplit, (kEPL <= 8 ?
 // workgroup for itself: a lane per request, the waves share the instances), takes in what was sent to the instance, and
 // offers for the next chunk: each request's latency here, whether its deadline is met, and d_g.
 // The launches themselves are the wait of one round for the other.  What was sent to an instance is taken in by building its
-// table anew.  (For one or two rounds, and for many requests to an instance and round: see in_one_launch.  Else the tables are all built once at
+// table anew.  (For few rounds, and for many requests to an instance and round: see in_one_launch.  Else the tables are all built once at
 // the start, with the sums behind them, kSums, and those that have been given any at the end.)
 //
 // What bounds it is the chain of a round: the offers (64 requests x 256 instances are 64 KB for every workgroup, from
@@ -1548,7 +1549,7 @@ __global__ __launch_bounds__(kWave * kSplit, (kEPL <= 8 ? 4 : 1)) void k_feedbac
 // Two sets of words in turn are enough: a workgroup writes a round's when it has seen all of the round before, whose writers had read
 // all of the one before that.
 //
-// 256 instances x 512, 32 rounds of 64, with the status build: 309 us with a launch for each, this way 164: a round is 4.1 us, of which the words
+// 256 instances x 512, 32 rounds of 64, with the status build: 309 us with a launch for each, this way 160: a round is 4.1 us, of which the words
 // take 0.9, gathering with two blocks 1.3, the choice 0.5 to 0.9, adding and offering 0.6.
 constexpr uint32_t kFeedCount = 0xFFFFu, kFeedClosed = 1u << 31;      // of the gate: workgroups that have started; closed, and in between how many had then
 constexpr int kFeedShareAt = 16;
